@@ -47,7 +47,7 @@ struct CompressBuffers {
     // candidate buffer
     uint32_t* tmp_idx;
     float* tmp_x;
-    uint32_t* ncompact;       // layers whose selection needs the streaming compaction pass
+    uint32_t* ncompact;       // [0] layers whose selection needs the streaming compaction pass, [1] of which served from g and h throughout (SEL_DIRECT)
     uint32_t* fresh;          // 1 while the profile's cache describes the current g - h (see ProfileBuffers)
     const LayerState* state;      // fused-profile state (spill range) per big layer
     // outputs
@@ -87,12 +87,12 @@ __device__ __forceinline__ float emit_value(const CompressBuffers& cb, uint64_t 
 __global__ __launch_bounds__(256) void k_lookup(CompressBuffers cb, int32_t err_offgrid, int32_t err_offsets,
                                                 int32_t err_stale, uint32_t use_candidates) {
     __shared__ int bad;
-    __shared__ uint32_t need_pass;
+    __shared__ uint32_t need_pass, n_direct;
     const uint32_t tid = threadIdx.x;
     // Thresholds may be reused only if a profile wrote them for the g - h that is there now: the compression
     // itself changes h, so a second call without a new profile in between is refused (status err_stale).
     const bool stale = use_candidates && *cb.fresh != 1u;
-    if (tid == 0) { bad = stale ? 3 : 0; need_pass = 0u; }
+    if (tid == 0) { bad = stale ? 3 : 0; need_pass = 0u; n_direct = 0u; }
     __syncthreads();
     // validate offsets / K for every layer
     for (uint32_t i = tid; i < cb.L; i += 256) {
@@ -154,9 +154,10 @@ __global__ __launch_bounds__(256) void k_lookup(CompressBuffers cb, int32_t err_
         // the classic pass reserves its candidates from zero; the spilled ones keep their records
         if (r.mode != SEL_CAND) cb.cursor[b] = 0u;
         if (r.mode == SEL_PREFIX || r.mode == SEL_DIRECT) atomicAdd(&need_pass, 1u);
+        if (r.mode == SEL_DIRECT) atomicAdd(&n_direct, 1u);
     }
     __syncthreads();
-    if (tid == 0) *cb.ncompact = bad ? 0u : need_pass;
+    if (tid == 0) { cb.ncompact[0] = bad ? 0u : need_pass; cb.ncompact[1] = bad ? 0u : n_direct; }
     if (bad) {
         // refuse the whole call: nothing is written by the later kernels
         for (uint32_t b = tid; b < cb.B; b += 256) { cb.sel[b].mode = SEL_NONE; cb.sel[b].cap = 0; cb.sel[b].K = 0; }
@@ -198,6 +199,16 @@ __device__ __forceinline__ void compact_tiles(const CompressBuffers& cb, uint32_
         if (chunk_in_layer >= L.nchunks) break;
         const uint32_t chunk = L.chunk0 + chunk_in_layer;
         const uint32_t vbase = chunk_in_layer * CHUNK;
+        if (S.mode == SEL_DIRECT && S.amb == 0u) {
+            // everything is kept: the count follows from the layer's ends, nothing is read
+            const uint32_t v0 = max(vbase, L.mis), v1 = min(vbase + CHUNK, L.mis + L.n);
+            const uint32_t inside = v1 > v0 ? v1 - v0 : 0u;
+            if (lane == 0) {
+                cb.rec_start[chunk] = 0u; cb.rec_cnt[chunk] = inside; cb.rec_amb[chunk] = 0u;
+                cb.c_gt[chunk] = inside; cb.c_eq[chunk] = 0u;
+            }
+            continue;
+        }
         Quad q[NQ];
 #pragma unroll
         for (int u = 0; u < (int)NQ; ++u) load_quad(L, vbase + u * 256u + lane * 4u, q[u]);
@@ -213,10 +224,8 @@ __device__ __forceinline__ void compact_tiles(const CompressBuffers& cb, uint32_
                 const uint32_t key = q[u].key[c];
                 if (key == KEY_INVALID) continue;
                 const uint32_t p = key >> D2_SHIFT;
-                const bool all = S.mode == SEL_DIRECT && S.amb == 0u;
-                const bool sure = all || p > S.prefix;
-                const bool amb = !all && p == S.prefix;
-                if (sure || amb) selm[u] |= 1u << c;
+                const bool amb = p == S.prefix;
+                if (p >= S.prefix) selm[u] |= 1u << c;
                 if (amb) { ambm[u] |= 1u << c; ++mine_amb; }
             }
         }
@@ -420,21 +429,60 @@ __global__ __launch_bounds__(256) void k_resolve(CompressBuffers cb) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Per chunk: how many candidates lie above tau and how many equal it.  Four lanes per chunk.
-__global__ __launch_bounds__(256) void k_chunk_count(CompressBuffers cb, uint32_t nchunks_total,
-                                                     const uint32_t* chunk_big) {
+// Per chunk: how many candidates lie above tau and how many equal it.
+
+// Layers served from g and h (SEL_DIRECT with a threshold): one wave per chunk with an entry in the threshold's
+// prefix bin, all of its loads in flight together.  Tiles in a grid-stride loop, as in the compaction.
+// (Four lanes of the candidates' half of this launch read such a chunk one element at a time before: 256 dependent
+// memory round trips.  Six tensors of 266 K elements in all: 59 us, now 4; ResNet-50 with two fifths of its bytes sent:
+// 63 us, now 8.)
+__device__ __forceinline__ void count_direct_tiles(const CompressBuffers& cb, uint32_t ntiles, uint32_t block, uint32_t nblocks) {
+    if (cb.ncompact[1] == 0u) return;
+    const uint32_t wave = threadIdx.x >> 6, lane = lane_id();
+    const uint32_t chunks_per_tile = cb.tile_elems / CHUNK;
+    for (uint32_t tile = block; tile < ntiles; tile += nblocks) {
+        const LayerDesc L = cb.layers[cb.chunk_layer[tile]];
+        const SelRec S = cb.sel[L.big];
+        if (S.mode != SEL_DIRECT || S.amb == 0u) continue;
+        const uint32_t tau = cb.tau[L.big];
+        for (uint32_t cc = wave; cc < chunks_per_tile; cc += 4u) {
+            const uint32_t chunk_in_layer = (tile - L.tile0) * chunks_per_tile + cc;
+            if (chunk_in_layer >= L.nchunks) break;
+            const uint32_t chunk = L.chunk0 + chunk_in_layer;
+            uint32_t gt = cb.rec_cnt[chunk], eq = 0u;
+            if (cb.rec_amb[chunk] != 0u) {       // (else every entry at or above the prefix is above tau)
+                QuadGH q[NQ];
+                uint32_t valid;
+                load_chunk<NQ>(L, chunk_in_layer * CHUNK, q, valid);
+                uint32_t both = 0u;              // above in the low half, equal in the high half: at most 1024 each
+#pragma unroll
+                for (int u = 0; u < (int)NQ; ++u)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const uint32_t key = key_of(q[u].g[c] - q[u].h[c]);
+                        const bool in = (valid >> (4 * u + c)) & 1u;
+                        both += in && key > tau ? 1u : 0u;
+                        both += in && key == tau ? 0x10000u : 0u;
+                    }
+                both = wave_scan_add_u32(both);
+                both = (uint32_t)__builtin_amdgcn_readlane((int)both, 63);
+                gt = both & 0xFFFFu; eq = both >> 16;
+            }
+            if (lane == 0) { cb.c_gt[chunk] = gt; cb.c_eq[chunk] = eq; }
+        }
+    }
+}
+
+// Layers with candidates: four lanes per chunk.
+__device__ __forceinline__ void count_candidates(const CompressBuffers& cb, uint32_t nchunks_total, const uint32_t* chunk_big,
+                                                 uint32_t block) {
     constexpr uint32_t S = SUB_COUNT;
     const SubGroup g = sub_group<S>();
-    const uint32_t chunk = blockIdx.x * (256u / S) + threadIdx.x / S;
+    const uint32_t chunk = block * (256u / S) + threadIdx.x / S;
     const bool live = chunk < nchunks_total;
     uint32_t cnt = 0, tau = 0, total = 0;
     uint64_t base = 0;
     bool settled = false;
-    // a chunk of a layer that is served from g and h: its 1024 positions take the place of its candidates
-    bool direct = false;
-    const float* gL = nullptr;
-    const float* hL = nullptr;
-    uint32_t vb = 0, mis = 0, nL = 0;
     if (live) {
         // what the chunk index alone addresses goes out together, then the layer's record
         const uint32_t b = chunk_big[chunk], first = cb.chunk_first[chunk];
@@ -445,40 +493,32 @@ __global__ __launch_bounds__(256) void k_chunk_count(CompressBuffers cb, uint32_
         const uint32_t t = cb.tau[b];
         // Only chunks with entries in the threshold's prefix bin are read again.  Of the others, those
         // of the classic pass hold nothing below the threshold prefix and pass whole; those of the
-        // spilled candidates were counted by k_hist3c.
+        // spilled candidates were counted by hist3_candidates.
         if ((S.mode == SEL_CAND || S.mode == SEL_PREFIX) && amb != 0u) {
             cnt = total;
             tau = t;
             base = region_start(first, b) + start;
         }
-        settled = S.mode == SEL_CAND && cnt == 0u;      // counted by k_hist3c
-        if (S.mode == SEL_DIRECT && amb != 0u) {
-            const LayerDesc L = cb.layers[cb.big_layer[b]];
-            direct = true; cnt = CHUNK; tau = t;
-            gL = L.g; hL = L.h; vb = (chunk - L.chunk0) * CHUNK; mis = L.mis; nL = L.n;
-        }
+        // counted by hist3_candidates, or by the workgroups that look after the layers served from g and h
+        settled = (S.mode == SEL_CAND && cnt == 0u) || S.mode == SEL_DIRECT;
     }
     uint32_t gt = 0, eq = 0;
-    if (direct) {
-        for (uint32_t k = g.sub; k < CHUNK; k += S) {
-            const uint32_t v = vb + k, e = v - mis;
-            if (v >= mis && e < nL) {
-                const uint32_t key = key_of(gload(gL + e) - gload(hL + e));
-                gt += key > tau;
-                eq += key == tau;
-            }
-        }
-    } else {
-        for (uint32_t k = g.sub; k < cnt; k += S) {
-            const uint32_t key = key_of(cb.tmp_x[base + k]);
-            gt += key > tau;
-            eq += key == tau;
-        }
+    for (uint32_t k = g.sub; k < cnt; k += S) {
+        const uint32_t key = key_of(cb.tmp_x[base + k]);
+        gt += key > tau;
+        eq += key == tau;
     }
 #pragma unroll
     for (int d = S / 2; d > 0; d >>= 1) { gt += __shfl_xor(gt, d, 64); eq += __shfl_xor(eq, d, 64); }
     if (cnt == 0) { gt = total; eq = 0; }
     if (live && !settled && g.sub == 0) { cb.c_gt[chunk] = gt; cb.c_eq[chunk] = eq; }
+}
+
+// One launch for both, as in k_candidates; the two write the counts of different layers.
+__global__ __launch_bounds__(256) void k_chunk_count(CompressBuffers cb, uint32_t nchunks_total, const uint32_t* chunk_big,
+                                                     uint32_t cand_blocks, uint32_t ntiles) {
+    if (blockIdx.x < cand_blocks) count_candidates(cb, nchunks_total, chunk_big, blockIdx.x);
+    else count_direct_tiles(cb, ntiles, blockIdx.x - cand_blocks, gridDim.x - cand_blocks);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -529,19 +569,73 @@ __global__ __launch_bounds__(1024) void k_chunk_bases(CompressBuffers cb) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Per chunk (sixteen lanes each): write the surviving candidates as payload and update the estimator.
-__global__ __launch_bounds__(256) void k_finalize(CompressBuffers cb, uint32_t nchunks_total,
-                                                  const uint32_t* chunk_big) {
+// Write the surviving entries as payload and update the estimator.
+
+// Layers served from g and h: one wave per chunk.  Lane l holds elements l, l + 64, ... of the chunk, so every load and
+// store of a wave is one run of memory, in index order; ranks come from ballots.  All 32 loads are in flight together.
+// (Sixteen lanes of the candidates' half of this launch walked such a chunk in sixteen dependent rounds before: 34 us
+// for six tensors of 266 K elements in all, now 6; ResNet-50 with two fifths of its bytes sent 84 us, now 59, most of
+// it the candidates' half.)
+__device__ __forceinline__ void finalize_direct_tiles(const CompressBuffers& cb, uint32_t ntiles, uint32_t block, uint32_t nblocks) {
+    if (cb.ncompact[1] == 0u) return;
+    constexpr int R = (int)(CHUNK / 64u);
+    const uint32_t wave = threadIdx.x >> 6, lane = lane_id();
+    const uint32_t chunks_per_tile = cb.tile_elems / CHUNK;
+    for (uint32_t tile = block; tile < ntiles; tile += nblocks) {
+        const LayerDesc L = cb.layers[cb.chunk_layer[tile]];
+        const SelRec S = cb.sel[L.big];
+        if (S.mode != SEL_DIRECT) continue;
+        const bool filter = S.amb != 0u;         // amb == 0: every entry is kept
+        const uint32_t tau = cb.tau[L.big];
+        for (uint32_t cc = wave; cc < chunks_per_tile; cc += 4u) {
+            const uint32_t chunk_in_layer = (tile - L.tile0) * chunks_per_tile + cc;
+            if (chunk_in_layer >= L.nchunks) break;
+            const uint32_t chunk = L.chunk0 + chunk_in_layer;
+            const uint32_t allow = cb.o_allow[chunk], keepn = cb.c_gt[chunk];
+            if (keepn + allow == 0u) continue;
+            uint32_t out_run = cb.o_base[chunk], eq_run = 0u;
+            const uint32_t vb = chunk_in_layer * CHUNK + lane;
+            float g[R], h[R];
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+                // (positions outside the layer read its entry 0, a valid address, and are dropped)
+                const uint32_t v = vb + (uint32_t)t * 64u, e = v - L.mis;
+                const uint32_t at = v >= L.mis && e < L.n ? e : 0u;
+                g[t] = gload(L.g + at); h[t] = gload(L.h + at);
+            }
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+                const uint32_t v = vb + (uint32_t)t * 64u, e = v - L.mis;
+                const bool in = v >= L.mis && e < L.n;
+                const float x = g[t] - h[t];
+                const uint32_t key = key_of(x);
+                const bool iseq = in && filter && key == tau;
+                const uint64_t eqm = ballot(iseq);
+                const bool keep = in && (!filter || key > tau || (iseq && eq_run + mbcnt(eqm) < allow));
+                eq_run += (uint32_t)__popcll(eqm);
+                const uint64_t km = ballot(keep);
+                const uint32_t pos = out_run + mbcnt(km);
+                out_run += (uint32_t)__popcll(km);
+                if (keep && pos < S.K) {
+                    const uint64_t o = S.dst + pos;
+                    cb.idx_out[o] = e;
+                    const float add = emit_value(cb, o, x);
+                    gstore(L.h + e, h[t] + add);
+                }
+            }
+        }
+    }
+}
+
+// Layers with candidates: sixteen lanes per chunk.
+__device__ __forceinline__ void finalize_candidates(const CompressBuffers& cb, uint32_t nchunks_total, const uint32_t* chunk_big,
+                                                    uint32_t block) {
     const SubGroup g = sub_group();
-    const uint32_t chunk = blockIdx.x * CHUNKS_PER_WG + threadIdx.x / SUB;
+    const uint32_t chunk = block * CHUNKS_PER_WG + threadIdx.x / SUB;
     uint32_t cnt = 0, tau = 0, allow = 0, room = 0, out_run = 0, eq_run = 0;
     uint64_t src = 0, dst = 0;
     bool filter = false;
     float* h = nullptr;
-    // a chunk of a layer that is served from g and h: its 1024 positions take the place of its candidates
-    bool direct = false;
-    const float* gL = nullptr;
-    uint32_t vb = 0, mis = 0, nL = 0;
     if (chunk < nchunks_total) {
         // everything indexed by the chunk is fetched at once; one more round trip brings the layer's record
         const uint32_t b = chunk_big[chunk], first = cb.chunk_first[chunk];
@@ -553,34 +647,21 @@ __global__ __launch_bounds__(256) void k_finalize(CompressBuffers cb, uint32_t n
         materialise(allow); materialise(out_run);
         // most chunks keep nothing (the candidates are several times the payload): not read at all
         if (keepn + allow != 0u) {
-            // every field of the record is valid whatever the mode; SEL_NONE only empties the chunk.
+            // every field of the record is valid whatever the mode; SEL_NONE and SEL_DIRECT only empty the chunk.
             // (Kept free of a nested branch on the mode: with one, the generated code left dst undefined
             // for SEL_CAND lanes.)
             const SelRec S = cb.sel[b];
             tau = cb.tau[b];
-            cnt = S.mode != SEL_NONE ? n_rec : 0u;
+            cnt = S.mode == SEL_CAND || S.mode == SEL_PREFIX ? n_rec : 0u;
             h = S.h;
             filter = S.mode == SEL_CAND || (S.mode == SEL_PREFIX && amb != 0u);
             src = region_start(first, b) + start;
             dst = S.dst;
             room = S.K;                            // payload slots of this layer
-            if (S.mode == SEL_DIRECT) {
-                const LayerDesc L = cb.layers[cb.big_layer[b]];
-                direct = true; cnt = CHUNK; filter = S.amb != 0u;      // amb == 0: every entry is kept
-                gL = L.g; vb = (chunk - L.chunk0) * CHUNK; mis = L.mis; nL = L.n;
-            }
         }
     }
-    // entry k of the chunk: a candidate (index, x), or position k of the chunk itself
+    // candidate k of the chunk
     auto fetch = [&](uint32_t k, uint32_t& idx, float& x) -> bool {
-        if (direct) {
-            const uint32_t v = vb + k, e = v - mis;
-            const bool in = k < cnt && v >= mis && e < nL;
-            const uint32_t at = in ? e : 0u;
-            idx = at;
-            x = gload(gL + at) - gload(h + at);
-            return in;
-        }
         const bool in = k < cnt;
         const uint64_t at = in ? src + k : 0ull;
         idx = cb.tmp_idx[at]; x = cb.tmp_x[at];
@@ -603,7 +684,7 @@ __global__ __launch_bounds__(256) void k_finalize(CompressBuffers cb, uint32_t n
     // so the wave pays one memory round trip for them instead of four; likewise the estimator entries of what the
     // four rounds keep are read together, then written (the entries of a chunk are distinct elements).
     constexpr int AHEAD = 4;
-    // (positions past the chunk's last entry read entry 0 of the buffer or the layer, a valid address, and are dropped)
+    // (positions past the chunk's last entry read entry 0 of the buffer, a valid address, and are dropped)
     for (uint32_t k0 = 0; k0 < cmax; k0 += AHEAD * SUB) {
         uint32_t pidx[AHEAD], pos[AHEAD];
         float px[AHEAD], ph[AHEAD];
@@ -628,6 +709,13 @@ __global__ __launch_bounds__(256) void k_finalize(CompressBuffers cb, uint32_t n
             }
         }
     }
+}
+
+// One launch for both, as in k_candidates; the two write different layers' payload and estimator entries.
+__global__ __launch_bounds__(256) void k_finalize(CompressBuffers cb, uint32_t nchunks_total, const uint32_t* chunk_big,
+                                                  uint32_t cand_blocks, uint32_t ntiles) {
+    if (blockIdx.x < cand_blocks) finalize_candidates(cb, nchunks_total, chunk_big, blockIdx.x);
+    else finalize_direct_tiles(cb, ntiles, blockIdx.x - cand_blocks, gridDim.x - cand_blocks);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -911,9 +911,11 @@ int kimad_compress_ef(kimad_plan_t* p, const uint64_t* K, const uint64_t* offset
         KLAUNCH(p, s, "k_candidates", k_candidates, dim3(hblocks + std::min<uint32_t>(lo.ntiles, 4u * FALLBACK_GRID)), dim3(256), cb,
                 lo.nchunks, chunk_big, hblocks, lo.ntiles, (int32_t)KIMAD_ERR_INTERNAL);
         KLAUNCH(p, s, "k_resolve", k_resolve, dim3(lo.B), dim3(256), cb);
-        KLAUNCH(p, s, "k_chunk_count", k_chunk_count, dim3(nblocks), dim3(256), cb, lo.nchunks, chunk_big);
+        // (the workgroups behind the candidates' leave after one load when no layer is served from g and h throughout)
+        const uint32_t dblocks = std::min<uint32_t>(lo.ntiles, FALLBACK_GRID);
+        KLAUNCH(p, s, "k_chunk_count", k_chunk_count, dim3(nblocks + dblocks), dim3(256), cb, lo.nchunks, chunk_big, nblocks, lo.ntiles);
         KLAUNCH(p, s, "k_chunk_bases", k_chunk_bases, dim3(lo.ncblk), dim3(1024), cb);
-        KLAUNCH(p, s, "k_finalize", k_finalize, dim3(cblocks), dim3(256), cb, lo.nchunks, chunk_big);
+        KLAUNCH(p, s, "k_finalize", k_finalize, dim3(cblocks + dblocks), dim3(256), cb, lo.nchunks, chunk_big, cblocks, lo.ntiles);
     }
     return join_side(p, s, ss);
 }

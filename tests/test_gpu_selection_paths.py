@@ -1,0 +1,56 @@
+"""Selection and payload, bit for bit against the oracle, at the sizes where the kernels that look after a layer change
+or end: layers served from g and h throughout (more is kept than a layer's candidate region holds), layers sorted or
+selected whole in LDS."""
+import numpy as np
+import pytest
+
+from kimad_synth.gen import Workload
+from oracle import kimad_oracle as ko
+from tests import gpu_harness as gh
+
+pytestmark = pytest.mark.gpu
+
+
+def _layers(sizes, seed, ties):
+    rng = np.random.default_rng(seed)
+    g = [(rng.standard_t(3, size=n) * 10.0 ** rng.uniform(-4, 0)).astype(np.float32) for n in sizes]
+    if ties:
+        g = [np.round(x / np.abs(x).max() * 40).astype(np.float32) for x in g]     # few magnitudes: every threshold is tied
+    h = [(0.3 * rng.standard_normal(n) * np.abs(x).mean()).astype(np.float32) if not ties else np.zeros(n, np.float32)
+         for n, x in zip(sizes, g)]
+    return np.concatenate(g), np.concatenate(h)
+
+
+def _compress(sizes, K, seed, ties, shift, f16=False):
+    import torch
+    import paper_2312_08053_amd as kimad
+    g, h = _layers(sizes, seed, ties)
+    n = g.size
+    gd, hd = (torch.empty(n + shift, dtype=torch.float32, device="cuda")[shift:] for _ in range(2))
+    gd.copy_(torch.from_numpy(g)); hd.copy_(torch.from_numpy(h))
+    off = np.concatenate([[0], np.cumsum(K)])
+    plan = kimad.Plan(gd, hd, list(sizes), [1.0], capacity_pairs=int(off[-1]), value_format=1 if f16 else 0,
+                      max_budget_bytes=8)
+    idx, val, st = plan.compress_ef(torch.tensor(K).cuda(), torch.from_numpy(off).cuda())
+    torch.cuda.synchronize()
+    assert int(st.item()) == 0
+    work = Workload(name="sel", sizes=np.asarray(sizes, dtype=np.uint64), g=g, h=h, ratios=np.array([1.0]),
+                    budget_bytes=8, cost_units_D=0)
+    gh.check_compress(work, plan, hd, K, off, idx, val)
+    return plan
+
+
+@pytest.mark.parametrize("ties", [False, True])
+@pytest.mark.parametrize("shift", [0, 1, 3])
+def test_layers_served_from_g_and_h(shift, ties):
+    sizes = [8193, 9215, 9216, 9217, 65536 + 1021, 8200, 12345, 30001]
+    K = [8193, 9214, 4700, 8000, 65000, 1, 12344, 30001]
+    plan = _compress(sizes, K, 5, ties, shift)
+    assert 4 in [s["mode"] for s in plan.layer_states()]
+
+
+@pytest.mark.parametrize("ties", [False, True])
+def test_small_layers_of_every_shape(ties):
+    sizes = [1, 2, 3, 63, 64, 65, 511, 512, 513, 1023, 1024, 1025, 2049, 4095, 4097, 8191, 8192, 8192, 8192, 700]
+    K = [1, 1, 3, 5, 64, 64, 1, 100, 513, 1022, 1, 600, 2048, 4095, 17, 8191, 8192, 4096, 1, 0]
+    _compress(sizes, K, 6, ties, 1)
