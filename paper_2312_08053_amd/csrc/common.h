@@ -19,7 +19,7 @@ constexpr uint32_t NO_SLOT = 0xFF;
 constexpr uint32_t KIMAD_MAX_J_CONST = 64;   // must equal KIMAD_MAX_J of the public header
 constexpr uint32_t KEY_INVALID = 0xFFFFFFFFu; // marks lanes outside the layer
 
-constexpr uint32_t SMALL_MAX = 8192;          // layers up to this size are sorted whole in LDS
+constexpr uint32_t SMALL_MAX = 8192;          // layers up to this size are looked after by one workgroup each
 constexpr uint32_t CHUNK = 1024;              // elements one wave compacts at a time (4 quads per lane)
 constexpr uint32_t NQ = CHUNK / 256;          // quads per lane and chunk
 constexpr uint32_t CBLOCK = 1024;             // chunks per chunk block (one workgroup scans one block)

@@ -605,23 +605,96 @@ __global__ __launch_bounds__(256) void k_scan3p(ProfileBuffers pb, double* err_t
 }
 
 // ---------------------------------------------------------------------------------------------
-// Small layers: the whole layer is sorted in LDS by (magnitude descending, index ascending);
-// E_ij is the suffix sum of squares in sorted order, in fp64.  One workgroup per layer.
-// Sort key: (0x7fffffff - key) << 32 | index, ascending.
-template <uint32_t THREADS>
-__device__ __forceinline__ void bitonic_sort_lds(unsigned long long* a, uint32_t P) {
-    for (uint32_t k = 2; k <= P; k <<= 1) {
-        for (uint32_t jj = k >> 1; jj > 0; jj >>= 1) {
-            for (uint32_t t = threadIdx.x; t < P / 2; t += THREADS) {
-                const uint32_t i = 2 * t - (t & (jj - 1));     // index with bit jj clear
-                const uint32_t l = i + jj;
-                const bool up = ((i & k) == 0);
-                const unsigned long long x = a[i], y = a[l];
-                if ((x > y) == up) { a[i] = y; a[l] = x; }
+// Small layers: the magnitudes of the whole layer are sorted, largest first, by one workgroup; E_ij is the suffix sum
+// of squares in that order, in fp64.
+constexpr uint32_t SMALL_THREADS = 1024;
+constexpr uint32_t SORT_PER = SMALL_MAX / SMALL_THREADS;     // 8 values a thread
+static_assert(SORT_PER == 8, "the sort below is written for eight values a thread");
+
+// The value the lane `X` away (lane index xor X) holds, X = 1, 2, 4, 8, 16, 32.
+template <int X>
+__device__ __forceinline__ uint32_t lane_xor_u32(uint32_t v) {
+    if (X == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);      // quad_perm [1,0,3,2]
+    if (X == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);      // quad_perm [2,3,0,1]
+    if (X == 4) {                                                                                    // reversed quads, then reversed eights
+        const int q = __builtin_amdgcn_update_dpp(0, (int)v, 0x1B, 0xF, 0xF, false);
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, q, 0x141, 0xF, 0xF, false);
+    }
+    if (X == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, false);     // row_ror:8
+    return __shfl_xor(v, X, 64);
+}
+
+// Compare-exchange of every value with the lane X away: the lane whose bit X is clear keeps the smaller if `up`.
+template <int X>
+__device__ __forceinline__ void sort_lanes(uint32_t (&v)[SORT_PER], bool up) {
+    const bool keep_min = ((lane_id() & (uint32_t)X) == 0u) == up;
+#pragma unroll
+    for (int r = 0; r < (int)SORT_PER; ++r) {
+        const uint32_t o = lane_xor_u32<X>(v[r]);
+        v[r] = keep_min ? min(v[r], o) : max(v[r], o);
+    }
+}
+// The same among a thread's own values, distance D = 1, 2, 4; K: the run length being merged if it is inside a thread
+// (2, 4: the direction then alternates among its values), else 8 and `up` holds for all of them.
+template <int D, int K>
+__device__ __forceinline__ void sort_own(uint32_t (&v)[SORT_PER], bool up) {
+#pragma unroll
+    for (int r = 0; r < (int)SORT_PER; ++r) {
+        if (r & D) continue;
+        const uint32_t lo = min(v[r], v[r + D]), hi = max(v[r], v[r + D]);
+        const bool u = K < 8 ? (r & K) == 0 : up;
+        v[r] = u ? lo : hi;
+        v[r + D] = u ? hi : lo;
+    }
+}
+
+// Bitonic sort, ascending, of P values (a power of two, 8 to SMALL_MAX): value 8 t + r is v[r] of thread t; threads
+// from P / 8 on take part in the barriers only.  The result is left in `a` (P words), behind a barrier.  Distances below
+// 8 are inside a thread, below 512 inside a wave (DPP moves, two shuffles for the widest), and only the ten steps of the
+// largest layer that cross waves go through LDS.  Sorting (magnitude, index) pairs of 64 bits through LDS at every
+// step, as before, took 65 to 79 us of k_small_profile on a layer of 8192 entries and 40 us on one of 4096; the order
+// among equal magnitudes changes no sum.
+__device__ __forceinline__ void sort_small(uint32_t (&v)[SORT_PER], uint32_t* a, uint32_t P) {
+    const uint32_t tid = threadIdx.x, base = tid * SORT_PER;
+    const bool mine = base < P;                  // (wave-uniform from P = 512 on; below, one wave holds everything)
+    sort_own<1, 2>(v, true);
+    sort_own<2, 4>(v, true);
+    sort_own<1, 4>(v, true);
+    for (uint32_t k = 8; k <= P; k <<= 1) {
+        const bool up = (base & k) == 0u;
+        for (uint32_t d = k >> 1; d >= 512u; d >>= 1) {
+            if (mine) {
+                uint4* at = reinterpret_cast<uint4*>(a + base);
+                at[0] = make_uint4(v[0], v[1], v[2], v[3]);
+                at[1] = make_uint4(v[4], v[5], v[6], v[7]);
+            }
+            __syncthreads();
+            if (mine) {
+                const uint4* from = reinterpret_cast<const uint4*>(a + (base ^ d));
+                const uint4 o0 = from[0], o1 = from[1];
+                const uint32_t o[SORT_PER] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
+                const bool keep_min = ((base & d) == 0u) == up;
+#pragma unroll
+                for (int r = 0; r < (int)SORT_PER; ++r) v[r] = keep_min ? min(v[r], o[r]) : max(v[r], o[r]);
             }
             __syncthreads();
         }
+        if (k >= 512u) sort_lanes<32>(v, up);
+        if (k >= 256u) sort_lanes<16>(v, up);
+        if (k >= 128u) sort_lanes<8>(v, up);
+        if (k >= 64u) sort_lanes<4>(v, up);
+        if (k >= 32u) sort_lanes<2>(v, up);
+        if (k >= 16u) sort_lanes<1>(v, up);
+        sort_own<4, 8>(v, up);
+        sort_own<2, 8>(v, up);
+        sort_own<1, 8>(v, up);
     }
+    if (mine) {
+        uint4* at = reinterpret_cast<uint4*>(a + base);
+        at[0] = make_uint4(v[0], v[1], v[2], v[3]);
+        at[1] = make_uint4(v[4], v[5], v[6], v[7]);
+    }
+    __syncthreads();
 }
 
 __device__ __forceinline__ uint32_t next_pow2(uint32_t n) {
@@ -630,31 +703,41 @@ __device__ __forceinline__ uint32_t next_pow2(uint32_t n) {
     return p;
 }
 
-__device__ __forceinline__ void load_sorted_small(const LayerDesc& L, unsigned long long* a, uint32_t P) {
-    for (uint32_t e = threadIdx.x; e < P; e += blockDim.x) {
-        unsigned long long v = ~0ull;
-        if (e < L.n) {
-            const uint32_t key = key_of(gload(L.g + e) - gload(L.h + e));
-            v = ((unsigned long long)(0x7FFFFFFFu - key) << 32) | e;
-        }
-        a[e] = v;
-    }
-    __syncthreads();
-}
-
-constexpr uint32_t SMALL_THREADS = 1024;
-
 __global__ __launch_bounds__(SMALL_THREADS) void k_small_profile(ProfileBuffers pb, const uint32_t* Ktab, uint32_t J,
                                                                  double* err_table, uint32_t mark_fresh) {
-    __shared__ unsigned long long a[SMALL_MAX];       // 64 KB
+    __shared__ __align__(16) uint32_t a[SMALL_MAX];   // 32 KB: 0x7fffffff - key, ascending
     __shared__ double loc[SMALL_THREADS];             // per-thread sums, then exclusive suffix sums
     __shared__ double sd[16];
     const uint32_t li = pb.small_layer[blockIdx.x];
     const LayerDesc L = pb.layers[li];
     if (blockIdx.x == 0 && threadIdx.x == 0 && mark_fresh) *pb.fresh = 1u;   // (plans without tiled layers have no other profile kernel)
-    const uint32_t P = next_pow2(L.n < 2 ? 2 : L.n);
-    load_sorted_small(L, a, P);
-    bitonic_sort_lds<SMALL_THREADS>(a, P);
+    const uint32_t P = next_pow2(L.n < SORT_PER ? SORT_PER : L.n);
+    {
+        uint32_t v[SORT_PER];
+        // coalesced loads, all in flight together; which thread holds which value does not matter to the sort
+#pragma unroll
+        for (int r = 0; r < (int)SORT_PER; ++r) {
+            const uint32_t e = threadIdx.x + (uint32_t)r * SMALL_THREADS;
+            v[r] = 0xFFFFFFFFu;
+            if (e < L.n) v[r] = 0x7FFFFFFFu - key_of(gload(L.g + e) - gload(L.h + e));
+        }
+        if (P < SMALL_MAX) {
+            // a shorter layer's values lie with the first rows of threads: hand every thread below P / 8 its eight
+#pragma unroll
+            for (int r = 0; r < (int)SORT_PER; ++r) {
+                const uint32_t e = threadIdx.x + (uint32_t)r * SMALL_THREADS;
+                if (e < P) a[e] = v[r];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < (int)SORT_PER; ++r) {
+                const uint32_t e = threadIdx.x * SORT_PER + (uint32_t)r;
+                v[r] = e < P ? a[e] : 0xFFFFFFFFu;
+            }
+            __syncthreads();
+        }
+        sort_small(v, a, P);
+    }
     // thread t owns ranks [t*per, (t+1)*per) and sums their squares from the smallest upward
     const uint32_t per = P / SMALL_THREADS ? P / SMALL_THREADS : 1u;
     const uint32_t tid = threadIdx.x;
@@ -662,7 +745,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_profile(ProfileBuffers 
     for (uint32_t k = per; k-- > 0;) {
         const uint32_t rk = tid * per + k;
         if (rk < L.n) {
-            const uint32_t key = 0x7FFFFFFFu - (uint32_t)(a[rk] >> 32);
+            const uint32_t key = 0x7FFFFFFFu - a[rk];
             const double v = (double)__uint_as_float(key);
             local += v * v;
         }
@@ -684,7 +767,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_profile(ProfileBuffers 
             E = loc[owner];
             for (uint32_t rk = (owner + 1) * per; rk-- > K;) {
                 if (rk < L.n) {
-                    const uint32_t key = 0x7FFFFFFFu - (uint32_t)(a[rk] >> 32);
+                    const uint32_t key = 0x7FFFFFFFu - a[rk];
                     const double v = (double)__uint_as_float(key);
                     E += v * v;
                 }
