@@ -83,15 +83,16 @@ __device__ __forceinline__ float emit_value(const CompressBuffers& cb, uint64_t 
 
 // ---------------------------------------------------------------------------------------------
 // Per layer: turn K[i] into a selection record using the profile's threshold cache.
-// One workgroup; thread b handles big layer b (looping).
+// One workgroup; thread b handles big layer b (looping).  `reuse`: the thresholds are those of an earlier profile;
+// `use_candidates`: a single pass over g and h (that profile's, or this call's own) has left candidates.
 __global__ __launch_bounds__(256) void k_lookup(CompressBuffers cb, int32_t err_offgrid, int32_t err_offsets,
-                                                int32_t err_stale, uint32_t use_candidates) {
+                                                int32_t err_stale, uint32_t reuse, uint32_t use_candidates) {
     __shared__ int bad;
     __shared__ uint32_t need_pass, n_direct;
     const uint32_t tid = threadIdx.x;
     // Thresholds may be reused only if a profile wrote them for the g - h that is there now: the compression
     // itself changes h, so a second call without a new profile in between is refused (status err_stale).
-    const bool stale = use_candidates && *cb.fresh != 1u;
+    const bool stale = reuse && *cb.fresh != 1u;
     if (tid == 0) { bad = stale ? 3 : 0; need_pass = 0u; n_direct = 0u; }
     __syncthreads();
     // validate offsets / K for every layer
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(256) void k_lookup(CompressBuffers cb, int32_t err_
     }
     // From here on the cache no longer describes g - h (the estimator is about to change, or a selection from
     // scratch has overwritten the cache); a refused call that reuses the profile leaves both as they were.
-    if (tid == 0 && (!use_candidates || !bad)) *cb.fresh = 0u;
+    if (tid == 0 && (!reuse || !bad)) *cb.fresh = 0u;
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -156,7 +156,8 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
         const uint32_t K0 = Ktab[(size_t)li * J];
         const double k0s = 2.0 * (double)K0 / scale;
         uint32_t floor_rank = (uint32_t)fmin((double)ns_total, ceil(k0s + 3.0 * sqrt(k0s) + 2.0));
-        floor_rank = max(floor_rank, max(1u, ns_total / 50u));
+        // (a selection has one target: nothing above it needs a slot)
+        floor_rank = max(floor_rank, J == 1u ? 1u : max(1u, ns_total / 50u));
         uint32_t b = find_bin(floor_rank);
         if (budget_pairs) b = min(b, sh_gbin);
         // never more than the top eighth of the layer: the bin that holds the entry of that rank is spilled only
@@ -165,6 +166,9 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
         uint32_t bc = find_bin(k8);
         if ((bc == 0u ? ns_total : above[bc - 1u]) > k8) ++bc;     // D1_BINS: nothing is spilled
         sh_spill = max(b, bc);
+        // with one target, candidates that cannot serve it are not written: nothing or everything is kept, or more
+        // than the eighth that may be spilled
+        if (J == 1u && (K0 == 0u || K0 >= L.n || (double)K0 / scale > (double)k8)) sh_spill = D1_BINS;
     }
     __syncthreads();
     const uint32_t spill_bin = sh_spill;

@@ -452,37 +452,42 @@ int launch_small_profile(kimad_plan* p, double* err_table, hipStream_t s, hipStr
     return KIMAD_OK;
 }
 
-int run_fused_profile(kimad_plan* p, double* err_table, uint64_t budget_pairs, hipStream_t s, hipStream_t* side) {
+// ktab, J: the targets, the plan's grid or one size per layer; without an err_table only thresholds and candidates are
+// wanted (a selection: no small layers, no certified errors).
+int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err_table, uint64_t budget_pairs, hipStream_t s,
+                    hipStream_t* side) {
     const Layout& lo = p->lo;
-    const uint32_t* ktab = at<uint32_t>(p, lo.ktab);
     if (!lo.B) {
         int rc0 = zero_range(p, lo.zero1_mid, lo.zero1_end, s);
-        if (rc0) return rc0;
+        if (rc0 || !err_table) return rc0;
         return launch_small_profile(p, err_table, s, side);
     }
     int rc = KIMAD_OK;
     if (p->hist_valid && !(p->cfg.flags & KIMAD_CFG_SAMPLE_ALWAYS)) {
-        // prediction from the previous profile's exact histogram: no sampling pass, no clearing launch
-        KLAUNCH(p, s, "k_predict", k_predict, dim3(lo.B), dim3(256), p->pb, ktab, lo.J, (unsigned long long)budget_pairs,
+        // prediction from the previous pass's exact histogram: no sampling pass, no clearing launch
+        KLAUNCH(p, s, "k_predict", k_predict, dim3(lo.B), dim3(256), p->pb, ktab, J, (unsigned long long)budget_pairs,
                 (const uint32_t*)p->pb.hprev, (const unsigned long long*)p->pb.gprev, 1u);
     } else {
         rc = zero_range(p, lo.zero1_mid, lo.zero1_end, s);   // the histogram tables are written whole by k_reduce_parts
         if (rc) return rc;
         KLAUNCH(p, s, "k_sample", k_sample, dim3(lo.nswg), dim3(SAMPLE_THREADS), p->pb);
-        KLAUNCH(p, s, "k_predict", k_predict, dim3(lo.B), dim3(256), p->pb, ktab, lo.J, (unsigned long long)budget_pairs,
+        KLAUNCH(p, s, "k_predict", k_predict, dim3(lo.B), dim3(256), p->pb, ktab, J, (unsigned long long)budget_pairs,
                 (const uint32_t*)p->pb.shist, (const unsigned long long*)p->pb.ghist, 0u);
     }
     p->hist_valid = true;
     KLAUNCH(p, s, "k_main", k_main, dim3(p->main_wgs), dim3(FUSED_THREADS), p->pb, p->chunks_per_wg);
     KLAUNCH(p, s, "k_reduce_parts", k_reduce_parts, dim3((LAYER_ENTRIES + REDUCE_ENTRIES - 1) / REDUCE_ENTRIES, lo.B), dim3(256), p->pb);
-    rc = launch_small_profile(p, err_table, s, side);
-    if (rc) return rc;
-    KLAUNCH(p, s, "k_scan1x", k_scan1x, dim3(lo.B), dim3(256), p->pb, ktab, lo.J);
+    if (err_table) {
+        rc = launch_small_profile(p, err_table, s, side);
+        if (rc) return rc;
+    }
+    KLAUNCH(p, s, "k_scan1x", k_scan1x, dim3(lo.B), dim3(256), p->pb, ktab, J);
     KLAUNCH(p, s, "k_hist2c", k_hist2c, dim3((lo.nchunks + 256u / SUB_HIST - 1) / (256u / SUB_HIST)), dim3(256), p->pb);
     // fallbacks that normally find nothing to do: small grids
     KLAUNCH(p, s, "k_hist2", k_hist2, dim3(std::min<uint32_t>(lo.ntiles, FALLBACK_GRID)), dim3(512), p->pb, lo.ntiles,
             (const uint32_t*)(at<uint32_t>(p, lo.diag) + 3), 1u);   // layers marked redo only
-    KLAUNCH(p, s, "k_scan2", k_scan2, dim3(lo.B), dim3(SCAN2_THREADS), p->pb, ktab, lo.J, err_table, CERT_TOL, SLOT_WIDEN);
+    KLAUNCH(p, s, "k_scan2", k_scan2, dim3(lo.B), dim3(SCAN2_THREADS), p->pb, ktab, J, err_table, CERT_TOL, SLOT_WIDEN);
+    if (!err_table) return KIMAD_OK;
     KLAUNCH(p, s, "k_hist3p", k_hist3p, dim3(std::min<uint32_t>(lo.ntiles, FALLBACK_GRID)), dim3(256), p->pb, lo.ntiles);
     KLAUNCH(p, s, "k_scan3p", k_scan3p, dim3(std::min(lo.pool_cap, POOL_GRID)), dim3(256), p->pb, err_table, 1u);
     return KIMAD_OK;
@@ -804,7 +809,7 @@ int kimad_profile(kimad_plan_t* p, double* err_table, uint64_t budget_hint_bytes
         if (!rc) rc = launch_small_profile(p, err_table, s, &ss);
         if (!rc) rc = run_select_passes(p, at<uint32_t>(p, lo.ktab), lo.J, err_table, s, 1u, false);
     } else {
-        rc = run_fused_profile(p, err_table, budget_hint_bytes / p->cfg.pair_bytes, s, &ss);
+        rc = run_single_pass(p, at<uint32_t>(p, lo.ktab), lo.J, err_table, budget_hint_bytes / p->cfg.pair_bytes, s, &ss);
     }
     const int rj = join_side(p, s, ss);       // always join, also after an error
     return rc ? rc : rj;
@@ -885,11 +890,15 @@ int kimad_compress_ef(kimad_plan_t* p, const uint64_t* K, const uint64_t* offset
     cb.value_f16 = p->cfg.value_format == KIMAD_VALUES_F16 ? 1u : 0u;
     cb.capacity_pairs = capacity_pairs; cb.status = status_out;
     mark(p, s, "begin");
-    if (!(flags & KIMAD_REUSE_PROFILE)) {
-        // select from scratch: the two histogram passes with one target per layer
+    const bool reuse = (flags & KIMAD_REUSE_PROFILE) != 0, classic = (p->cfg.flags & KIMAD_CFG_CLASSIC_PROFILE) != 0;
+    if (!reuse) {
+        // Select from scratch, one target per layer: by the single pass over g and h that the profile takes, whose
+        // candidates then serve the selection.  (Two histogram passes and a compaction, three reads of g and h, take
+        // 811 us on the headline set at half a percent of the entries, this 337; KIMAD_CFG_CLASSIC_PROFILE keeps them.)
         uint32_t* ksel = at<uint32_t>(p, lo.ksel);
         KLAUNCH(p, s, "k_make_ksel", k_make_ksel, dim3((lo.L + 255) / 256), dim3(256), K, cb.layers, lo.L, ksel);
-        int rc = run_select_passes(p, ksel, 1, nullptr, s);
+        hipStream_t unused = s;
+        const int rc = classic ? run_select_passes(p, ksel, 1, nullptr, s) : run_single_pass(p, ksel, 1, nullptr, 0, s, &unused);
         if (rc) return rc;
         cb.Ktab = ksel;
         cb.J = 1;
@@ -897,7 +906,7 @@ int kimad_compress_ef(kimad_plan_t* p, const uint64_t* K, const uint64_t* offset
     // (the last-digit histograms are zero here: k_resolve clears what it has read)
     KLAUNCH(p, s, "k_lookup", k_lookup, dim3(1), dim3(256), cb, (int32_t)KIMAD_ERR_OFFGRID,
             (int32_t)KIMAD_ERR_BAD_OFFSETS, (int32_t)KIMAD_ERR_STALE_PROFILE,
-            (uint32_t)((flags & KIMAD_REUSE_PROFILE) ? 1u : 0u));
+            (uint32_t)(reuse ? 1u : 0u), (uint32_t)(reuse || !classic ? 1u : 0u));
     hipStream_t ss = s;
     if (lo.S) {
         ss = fork_side(p, s);                 // after the lookup: the small layers read its verdict

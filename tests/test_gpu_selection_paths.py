@@ -54,3 +54,28 @@ def test_small_layers_of_every_shape(ties):
     sizes = [1, 2, 3, 63, 64, 65, 511, 512, 513, 1023, 1024, 1025, 2049, 4095, 4097, 8191, 8192, 8192, 8192, 700]
     K = [1, 1, 3, 5, 64, 64, 1, 100, 513, 1022, 1, 600, 2048, 4095, 17, 8191, 8192, 4096, 1, 0]
     _compress(sizes, K, 6, ties, 1)
+
+
+@pytest.mark.parametrize("share", [0.0, 0.001, 0.06, 0.124, 0.13, 0.7, 1.0])
+def test_selection_from_scratch_over_several_rounds(share):
+    """One size per layer, from the single pass: the first call predicts from a sample, the later ones from the
+    histogram of the call before; a gradient scaled by 64 in between makes every prediction miss."""
+    import torch
+    import paper_2312_08053_amd as kimad
+    sizes = [9000, 200001, 5000, 1048576 + 77, 8193]
+    K = [min(n, int(np.ceil(share * n))) for n in sizes]
+    off = np.concatenate([[0], np.cumsum(K)])
+    g, h = _layers(sizes, 7, False)
+    gd, hd = torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda()
+    plan = kimad.Plan(gd, hd, sizes, [1.0], capacity_pairs=max(1, int(off[-1])), max_budget_bytes=8)
+    Kd, offd = torch.tensor(K).cuda(), torch.from_numpy(off).cuda()
+    for scale in (1.0, 1.1, 64.0, 1.0):
+        g1 = (g * np.float32(scale)).astype(np.float32)
+        gd.copy_(torch.from_numpy(g1))
+        h0 = hd.cpu().numpy()
+        idx, val, st = plan.compress_ef(Kd, offd)
+        torch.cuda.synchronize()
+        assert int(st.item()) == 0
+        work = Workload(name="scratch", sizes=np.asarray(sizes, dtype=np.uint64), g=g1, h=h0, ratios=np.array([1.0]),
+                        budget_bytes=8, cost_units_D=0)
+        gh.check_compress(work, plan, hd, K, off, idx, val)
