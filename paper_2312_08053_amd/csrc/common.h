@@ -111,6 +111,11 @@ __device__ __forceinline__ void gstore4(float* p, float4 v) {
     t.x = v.x; t.y = v.y; t.z = v.z; t.w = v.w;
     *reinterpret_cast<g_f32x4*>((uintptr_t)p) = t;
 }
+__device__ __forceinline__ void gstore4_stream(float* p, float4 v) {
+    f32x4 t;
+    t.x = v.x; t.y = v.y; t.z = v.z; t.w = v.w;
+    __builtin_nontemporal_store(t, reinterpret_cast<g_f32x4*>((uintptr_t)p));
+}
 
 // ---- small device helpers ----------------------------------------------------------------
 // Makes the compiler hold a loaded value in a register here.  Placed after a group of independent

@@ -1043,23 +1043,34 @@ int kimad_server_apply(const kimad_payload_t* payloads, float* const* u_hat, con
         !status_out)
         return KIMAD_ERR_INVALID_ARG;
     ServerArgs a{};
+    DecodeArgs da{};
     bool vec_ok = x && (reinterpret_cast<uintptr_t>(x) % 16 == 0);
+    bool apart = true;                           // no two workers' estimators share memory
+    uint64_t pairs = 0;                          // largest payload capacity
     for (uint32_t m = 0; m < M; ++m) {
         if (!payloads[m].idx || !payloads[m].val || !payloads[m].offsets || !u_hat[m]) return KIMAD_ERR_INVALID_ARG;
         if (payloads[m].value_format > KIMAD_VALUES_F16) return KIMAD_ERR_INVALID_ARG;
         a.u_hat[m] = u_hat[m]; a.w[m] = weights[m];
+        da.idx[m] = payloads[m].idx; da.val[m] = static_cast<const float*>(payloads[m].val); da.off[m] = payloads[m].offsets;
+        da.capacity_pairs[m] = payloads[m].capacity_pairs; da.u_hat[m] = u_hat[m];
+        if (payloads[m].value_format == KIMAD_VALUES_F16) da.f16 |= 1u << m;
         vec_ok = vec_ok && (reinterpret_cast<uintptr_t>(u_hat[m]) % 16 == 0);
+        pairs = std::max<uint64_t>(pairs, payloads[m].capacity_pairs);
+        for (uint32_t k = 0; k < m; ++k) {
+            const uintptr_t p0 = reinterpret_cast<uintptr_t>(u_hat[m]), p1 = reinterpret_cast<uintptr_t>(u_hat[k]);
+            if ((p0 > p1 ? p0 - p1 : p1 - p0) / 4 < d) apart = false;
+        }
     }
     a.M = M; a.d = d;
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, status_out, M, 0);
     if (hipGetLastError() != hipSuccess) return KIMAD_ERR_HIP;
-    // payload sizes live on the device: a fixed grid strides over whatever the worker sent
-    for (uint32_t m = 0; m < M; ++m) {
-        hipLaunchKernelGGL(k_server_decode, dim3(1024), dim3(256), 0, s, payloads[m].idx, payloads[m].val,
-                           payloads[m].offsets, payloads[m].capacity_pairs, u_hat[m], layer_start, L, d,
-                           status_out + m, (int32_t)KIMAD_ERR_BAD_PAYLOAD,
-                           payloads[m].value_format == KIMAD_VALUES_F16 ? 1u : 0u);
+    // payload sizes live on the device: a grid for the capacity, of at most 1024 workgroups a worker, strides over
+    // whatever the worker sent.  Workers whose estimators share memory are decoded one after another.
+    const uint32_t dblocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((pairs + 256 * DECODE_PAIRS - 1) / (256 * DECODE_PAIRS), 1024));
+    for (uint32_t m = 0; m < M; m += apart ? M : 1u) {
+        hipLaunchKernelGGL(k_server_decode, dim3(dblocks, apart ? M : 1u), dim3(256), 0, s, da, m, layer_start, L, d, status_out,
+                           (int32_t)KIMAD_ERR_BAD_PAYLOAD);
         if (hipGetLastError() != hipSuccess) return KIMAD_ERR_HIP;
     }
     if (x) {

@@ -163,3 +163,32 @@ def test_payloads_that_do_not_fit_the_layers_are_flagged_and_write_nothing_out_o
     u = torch.zeros(d, device="cuda")
     status = kimad.kimad_server_apply([_dev_payload(offsets, idx, val)], [u], [1.0], st_bad, d, None, 0.0)
     assert int(status.item()) == -13 and not u.cpu().numpy().any()
+
+
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("L", [1, 2, 1023, 1024, 1500])
+def test_layer_counts_around_the_lds_table_and_workers_that_share_an_estimator(L, shared):
+    # offsets and starts of up to 1023 layers sit in LDS; workers that share an estimator are applied in order
+    import torch
+    import paper_2312_08053_amd as kimad
+    rng = np.random.default_rng(L)
+    sizes = [int(n) for n in rng.integers(1, 40, size=L)]
+    starts = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    d = int(starts[-1])
+    pls = []
+    for _ in range(3):
+        g = [rng.standard_normal(n).astype(np.float32) for n in sizes]
+        K = np.array([rng.integers(0, n + 1) for n in sizes], dtype=np.uint64)
+        pls.append(ko.compress_ef(g, [np.zeros(n, np.float32) for n in sizes], K)[:3])
+    hats = [rng.standard_normal(d).astype(np.float32) for _ in range(3)]
+    dev = [torch.from_numpy(u.copy()).cuda() for u in hats]
+    if shared:
+        dev[2] = dev[0]
+    kimad.kimad_server_apply([_dev_payload(*p) for p in pls], dev, [1.0] * 3, torch.from_numpy(starts).cuda(), d)
+    torch.cuda.synchronize()
+    for m, p in enumerate(pls):
+        into = 0 if shared and m == 2 else m
+        pos = np.repeat(starts[:-1], np.diff(p[0].astype(np.int64))) + p[1].astype(np.int64)
+        hats[into][pos] += p[2]
+    for m in (0, 1) if shared else (0, 1, 2):
+        assert np.array_equal(dev[m].cpu().numpy().view(np.uint32), hats[m].view(np.uint32)), m
