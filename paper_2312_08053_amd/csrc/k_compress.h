@@ -516,7 +516,8 @@ __device__ __forceinline__ void count_candidates(const CompressBuffers& cb, uint
 }
 
 // One launch for both, as in k_candidates; the two write the counts of different layers.
-__global__ __launch_bounds__(256) void k_chunk_count(CompressBuffers cb, uint32_t nchunks_total, const uint32_t* chunk_big,
+// (at least eight waves a SIMD, which the candidates' half lives by)
+__global__ __launch_bounds__(256, 8) void k_chunk_count(CompressBuffers cb, uint32_t nchunks_total, const uint32_t* chunk_big,
                                                      uint32_t cand_blocks, uint32_t ntiles) {
     if (blockIdx.x < cand_blocks) count_candidates(cb, nchunks_total, chunk_big, blockIdx.x);
     else count_direct_tiles(cb, ntiles, blockIdx.x - cand_blocks, gridDim.x - cand_blocks);
@@ -573,13 +574,14 @@ __global__ __launch_bounds__(1024) void k_chunk_bases(CompressBuffers cb) {
 // Write the surviving entries as payload and update the estimator.
 
 // Layers served from g and h: one wave per chunk.  Lane l holds elements l, l + 64, ... of the chunk, so every load and
-// store of a wave is one run of memory, in index order; ranks come from ballots.  All 32 loads are in flight together.
+// store of a wave is one run of memory, in index order; ranks come from ballots.
 // (Sixteen lanes of the candidates' half of this launch walked such a chunk in sixteen dependent rounds before: 34 us
 // for six tensors of 266 K elements in all, now 6; ResNet-50 with two fifths of its bytes sent 84 us, now 59, most of
 // it the candidates' half.)
 __device__ __forceinline__ void finalize_direct_tiles(const CompressBuffers& cb, uint32_t ntiles, uint32_t block, uint32_t nblocks) {
     if (cb.ncompact[1] == 0u) return;
-    constexpr int R = (int)(CHUNK / 64u);
+    constexpr int R = 8;                          // rows of 64 elements loaded together: sixteen loads in flight
+    static_assert(CHUNK % (64u * R) == 0, "whole trips");
     const uint32_t wave = threadIdx.x >> 6, lane = lane_id();
     const uint32_t chunks_per_tile = cb.tile_elems / CHUNK;
     for (uint32_t tile = block; tile < ntiles; tile += nblocks) {
@@ -595,33 +597,35 @@ __device__ __forceinline__ void finalize_direct_tiles(const CompressBuffers& cb,
             const uint32_t allow = cb.o_allow[chunk], keepn = cb.c_gt[chunk];
             if (keepn + allow == 0u) continue;
             uint32_t out_run = cb.o_base[chunk], eq_run = 0u;
-            const uint32_t vb = chunk_in_layer * CHUNK + lane;
-            float g[R], h[R];
+#pragma unroll 1
+            for (uint32_t v0 = chunk_in_layer * CHUNK; v0 < (chunk_in_layer + 1u) * CHUNK; v0 += 64u * (uint32_t)R) {
+                float g[R], h[R];
 #pragma unroll
-            for (int t = 0; t < R; ++t) {
-                // (positions outside the layer read its entry 0, a valid address, and are dropped)
-                const uint32_t v = vb + (uint32_t)t * 64u, e = v - L.mis;
-                const uint32_t at = v >= L.mis && e < L.n ? e : 0u;
-                g[t] = gload(L.g + at); h[t] = gload(L.h + at);
-            }
+                for (int t = 0; t < R; ++t) {
+                    // (positions outside the layer read its entry 0, a valid address, and are dropped)
+                    const uint32_t v = v0 + lane + (uint32_t)t * 64u, e = v - L.mis;
+                    const uint32_t at = v >= L.mis && e < L.n ? e : 0u;
+                    g[t] = gload(L.g + at); h[t] = gload(L.h + at);
+                }
 #pragma unroll
-            for (int t = 0; t < R; ++t) {
-                const uint32_t v = vb + (uint32_t)t * 64u, e = v - L.mis;
-                const bool in = v >= L.mis && e < L.n;
-                const float x = g[t] - h[t];
-                const uint32_t key = key_of(x);
-                const bool iseq = in && filter && key == tau;
-                const uint64_t eqm = ballot(iseq);
-                const bool keep = in && (!filter || key > tau || (iseq && eq_run + mbcnt(eqm) < allow));
-                eq_run += (uint32_t)__popcll(eqm);
-                const uint64_t km = ballot(keep);
-                const uint32_t pos = out_run + mbcnt(km);
-                out_run += (uint32_t)__popcll(km);
-                if (keep && pos < S.K) {
-                    const uint64_t o = S.dst + pos;
-                    cb.idx_out[o] = e;
-                    const float add = emit_value(cb, o, x);
-                    gstore(L.h + e, h[t] + add);
+                for (int t = 0; t < R; ++t) {
+                    const uint32_t v = v0 + lane + (uint32_t)t * 64u, e = v - L.mis;
+                    const bool in = v >= L.mis && e < L.n;
+                    const float x = g[t] - h[t];
+                    const uint32_t key = key_of(x);
+                    const bool iseq = in && filter && key == tau;
+                    const uint64_t eqm = ballot(iseq);
+                    const bool keep = in && (!filter || key > tau || (iseq && eq_run + mbcnt(eqm) < allow));
+                    eq_run += (uint32_t)__popcll(eqm);
+                    const uint64_t km = ballot(keep);
+                    const uint32_t pos = out_run + mbcnt(km);
+                    out_run += (uint32_t)__popcll(km);
+                    if (keep && pos < S.K) {
+                        const uint64_t o = S.dst + pos;
+                        cb.idx_out[o] = e;
+                        const float add = emit_value(cb, o, x);
+                        gstore(L.h + e, h[t] + add);
+                    }
                 }
             }
         }
@@ -713,7 +717,8 @@ __device__ __forceinline__ void finalize_candidates(const CompressBuffers& cb, u
 }
 
 // One launch for both, as in k_candidates; the two write different layers' payload and estimator entries.
-__global__ __launch_bounds__(256) void k_finalize(CompressBuffers cb, uint32_t nchunks_total, const uint32_t* chunk_big,
+// (at least eight waves a SIMD: with five, the Llama-shaped set's 314 us were 357)
+__global__ __launch_bounds__(256, 8) void k_finalize(CompressBuffers cb, uint32_t nchunks_total, const uint32_t* chunk_big,
                                                   uint32_t cand_blocks, uint32_t ntiles) {
     if (blockIdx.x < cand_blocks) finalize_candidates(cb, nchunks_total, chunk_big, blockIdx.x);
     else finalize_direct_tiles(cb, ntiles, blockIdx.x - cand_blocks, gridDim.x - cand_blocks);
