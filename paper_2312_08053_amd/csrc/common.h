@@ -66,8 +66,9 @@ struct LayerState {
     uint32_t redo;         // prediction missed: digit 2 is recounted by a full pass over this layer
     uint32_t spill_cnt;    // entries in the candidate region
     uint32_t spill_valid;  // the region holds every entry with bin >= spill_bin, in index order per chunk
-    uint32_t slot_lo;      // single-pass profile: the predicted slots 0..nslots_d-1 are the bins slot_lo, slot_lo+1, ...
-    uint32_t pad;
+    uint32_t slot_lo;      // single-pass profile: the predicted slots are two runs of consecutive bins, run_a of them from
+                           // bin slot_lo & 0xffff, then nslots_d - run_a from bin slot_lo >> 16
+    uint32_t run_a;
 };
 
 // Per big layer, what the compaction pass needs.

@@ -92,7 +92,7 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
     __shared__ uint32_t bitmap[D1_BINS / 32];
     __shared__ uint32_t su[16];
     __shared__ unsigned long long s64[16];
-    __shared__ uint32_t sh_gbin, sh_spill, sh_ns;
+    __shared__ uint32_t sh_gbin, sh_spill, sh_eighth, sh_ns, sh_gap;
     const uint32_t tid = threadIdx.x, big = blockIdx.x;
     const uint32_t li = pb.big_layer[big];
     const LayerDesc L = pb.layers[li];
@@ -166,12 +166,13 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
         uint32_t bc = find_bin(k8);
         if ((bc == 0u ? ns_total : above[bc - 1u]) > k8) ++bc;     // D1_BINS: nothing is spilled
         sh_spill = max(b, bc);
+        sh_eighth = bc;
         // with one target, candidates that cannot serve it are not written: nothing or everything is kept, or more
         // than the eighth that may be spilled
         if (J == 1u && (K0 == 0u || K0 >= L.n || (double)K0 / scale > (double)k8)) sh_spill = D1_BINS;
     }
     __syncthreads();
-    const uint32_t spill_bin = sh_spill;
+    uint32_t spill_bin = sh_spill;
     // (3) bins that may hold a candidate's boundary: +-5 sigma of the sample rank, every bin in between.
     // Bin 0 (zeros and the tiniest denormals) never gets a slot here: its squares need the exact
     // accumulators of the full recount.
@@ -183,7 +184,8 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
             const double klo = floor(ks - 5.0 * sg) - 2.0, khi = ceil(ks + 5.0 * sg) + 2.0;
             const uint32_t rlo = (uint32_t)fmin((double)ns_total, fmax(1.0, klo));
             const uint32_t rhi = (uint32_t)fmin((double)ns_total, fmax(1.0, khi));
-            const uint32_t btop = find_bin(rlo), bbot = khi > (double)ns_total ? 0u : find_bin(rhi);
+            // (no lower than the smallest entry above bin 0: where many entries are exactly zero, all bins below it are empty)
+            const uint32_t btop = find_bin(rlo), bbot = max(khi > (double)ns_total ? 0u : find_bin(rhi), find_bin(max(1u, above[0])));
             // A boundary in the spilled range can also be resolved from the candidates, which is
             // cheap only where few entries lie above it: skip the prediction for the sparse top
             // (fewer than 64 sample entries above), where it would cost many bins.
@@ -193,15 +195,18 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
         }
     }
     __syncthreads();
-    // (4) slots: one run of consecutive bins from the lowest marked bin (low bins hold the most
-    // entries) to the highest, at most PRE_SLOTS.  A run lets the streaming pass find an entry's slot
-    // with a subtraction instead of a table look-up; what is cut off at the top lies in the spilled
-    // range or makes the layer a redo.
+    // (4) slots: runs of consecutive bins from the lowest marked bin (low bins hold the most
+    // entries) upward, at most PRE_SLOTS in all.  A run lets the streaming pass find an entry's slot
+    // with a subtraction instead of a table look-up.  One run if it reaches the highest marked bin or the spilled range;
+    // else two, with the widest stretch of unmarked bins left out between them, and if those still end below both, what
+    // is above them is spilled as well, as far as the eighth allows.  (A grid that goes up to nearly all entries, as the
+    // paper's, marks 150 bins, with such a stretch at the sparse lower end.  With one run and no more spilled than the
+    // budget asks for, every layer was recounted in every round.)
+    // What is cut off below the spilled range makes the layer a redo.
     uint8_t* lut = pb.lut1 + (size_t)big * D1_BINS;
     for (uint32_t b = tid; b < D1_BINS; b += 256) lut[b] = (uint8_t)NO_SLOT;
-    __syncthreads();
     // lowest and highest marked bin: one bitmap word per thread
-    if (tid == 0) { sh_gbin = D1_BINS; sh_ns = 0u; }      // reused: lowest / highest marked bin
+    if (tid == 0) { sh_gbin = D1_BINS; sh_ns = 0u; sh_gap = 0u; }      // the first two reused: lowest / highest marked bin
     __syncthreads();
     if (tid < D1_BINS / 32) {
         const uint32_t m = bitmap[tid];
@@ -211,16 +216,49 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
         }
     }
     __syncthreads();
-    uint32_t lo_bin = sh_gbin, ns = 0;
-    if (lo_bin < D1_BINS) ns = min(PRE_SLOTS, sh_ns - lo_bin + 1u); else lo_bin = 0;
+    const bool any = sh_gbin < D1_BINS;
+    const uint32_t lo_bin = any ? sh_gbin : 0u, hi_bin = sh_ns;
+    uint32_t ns = any ? min(PRE_SLOTS, hi_bin - lo_bin + 1u) : 0u, run_a = ns, lo_b = 0u;
+    if (any && lo_bin + PRE_SLOTS <= min(hi_bin, spill_bin - 1u)) {    // (the same in every thread; spill_bin is never 0 then)
+        // the widest stretch that ends before a marked bin: its width, then that bin
+        if (tid < D1_BINS / 32) {
+            uint32_t m = bitmap[tid], before = 0xFFFFFFFFu;
+            if (m) {
+                for (uint32_t w = tid; w-- > 0u && before == 0xFFFFFFFFu;)
+                    if (bitmap[w]) before = w * 32u + 31u - (uint32_t)__clz((int)bitmap[w]);
+                uint32_t widest = 0u;
+                while (m) {
+                    const uint32_t b = tid * 32u + (uint32_t)__ffs((int)m) - 1u;
+                    m &= m - 1u;
+                    if (before != 0xFFFFFFFFu) widest = max(widest, ((b - before - 1u) << D1_BITS) | b);
+                    before = b;
+                }
+                atomicMax(&sh_gap, widest);
+            }
+        }
+        __syncthreads();
+        const uint32_t gap = sh_gap >> D1_BITS;
+        uint32_t end = lo_bin + PRE_SLOTS;                             // first bin above the runs
+        if (gap) {
+            const uint32_t first_b = sh_gap & (D1_BINS - 1u);
+            if (first_b - gap - lo_bin < PRE_SLOTS) {
+                lo_b = first_b;
+                run_a = lo_b - gap - lo_bin;
+                ns = min(PRE_SLOTS, run_a + (hi_bin - lo_b + 1u));
+                end = lo_b + (ns - run_a);
+            }
+        }
+        if (end <= min(hi_bin, spill_bin - 1u)) spill_bin = min(spill_bin, max(end, sh_eighth));
+    }
     if (tid < ns) {
-        lut[lo_bin + tid] = (uint8_t)tid;
-        pb.slot_bin[(size_t)big * SLOT_STRIDE + tid] = lo_bin + tid;
+        const uint32_t b = tid < run_a ? lo_bin + tid : lo_b + (tid - run_a);
+        lut[b] = (uint8_t)tid;
+        pb.slot_bin[(size_t)big * SLOT_STRIDE + tid] = b;
     }
     if (tid == 0) {
         LayerState st;
         st.spill_bin = spill_bin; st.nslots_d = ns; st.nslots_t = 0; st.redo = 0;
-        st.spill_cnt = 0; st.spill_valid = 0; st.slot_lo = lo_bin; st.pad = 0;
+        st.spill_cnt = 0; st.spill_valid = 0; st.slot_lo = lo_bin | (lo_b << 16); st.run_a = run_a;
         pb.state[big] = st;
     }
     if (fold_zero) {
@@ -260,20 +298,48 @@ __device__ __forceinline__ unsigned long long pk_term(uint32_t key) {
 struct MainCtx {
     unsigned long long* pk;
     unsigned long long* sq0;
-    uint32_t lo19;         // 19-bit key prefix of the first digit-2 entry of the first slot
-    uint32_t span;         // digit-2 entries of all slots: a key is in a slot bin iff (key >> 12) - lo19 < span
+    // a run of slot bins: 19-bit key prefix of its first digit-2 entry, and how many digit-2 entries it has: a key is in
+    // one of its bins iff (key >> 12) - lo19 < span
+    uint32_t lo19, span;   // the first run: LDS entries D1_BINS..
+    uint32_t lo19b, spanb; // the second run, right behind it (spanb = 0: there is none)
     uint32_t spill_key;
 };
 
-// LDS entry of a key: inside the run of slot bins the digit-2 entries of consecutive bins are
+// LDS entry of a key: inside a run of slot bins the digit-2 entries of consecutive bins are
 // consecutive 19-bit prefixes, so the entry is the prefix minus the run's first one
+template <bool TWO>
 __device__ __forceinline__ uint32_t main_entry(const MainCtx& cx, uint32_t k) {
     const uint32_t rel = (k >> D2_SHIFT) - cx.lo19;
-    return rel < cx.span ? D1_BINS + rel : (k >> D1_SHIFT);
+    const uint32_t e = rel < cx.span ? D1_BINS + rel : (k >> D1_SHIFT);
+    if (!TWO) return e;
+    const uint32_t relb = (k >> D2_SHIFT) - cx.lo19b;
+    return relb < cx.spanb ? D1_BINS + cx.span + relb : e;
+}
+
+// the same for all entries of a chunk that lies inside the layer and holds only normal numbers
+template <bool TWO>
+__device__ __forceinline__ void main_count_plain(const MainCtx& cx, const float (&x)[NQ][4], uint32_t (&selm)[NQ]) {
+#pragma unroll
+    for (int u = 0; u < (int)NQ; ++u) {
+        uint32_t sel = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t k = key_of(x[u][c]);
+            const uint32_t m24 = (k & 0x7FFFFFu) | 0x800000u;
+            // the shifted square has 24 bits: as a 32-bit value it is the low word of the packed
+            // operand and the count's 1 is a constant high word
+            const unsigned long long sq = (unsigned long long)m24 * m24;
+            const uint32_t t = __builtin_amdgcn_alignbit((uint32_t)(sq >> 32), (uint32_t)sq, PK_SHIFT);
+            atomicAdd(&cx.pk[main_entry<TWO>(cx, k)], PK_ONE | (unsigned long long)t);
+            sel |= (k >= cx.spill_key ? 1u : 0u) << c;
+        }
+        selm[u] = sel;
+    }
 }
 
 // histogram updates and spill flags of one chunk.  A chunk that lies inside the layer and holds
 // only normal numbers (no zeros, denormals, Inf, NaN) takes a branch-free path.
+template <bool TWO>
 __device__ __forceinline__ void main_count(const MainCtx& cx, const float (&x)[NQ][4], uint32_t valid,
                                            uint32_t (&selm)[NQ]) {
     // exponent field 0 or 255 anywhere in the lane's 16 keys: smallest and largest key
@@ -287,22 +353,7 @@ __device__ __forceinline__ void main_count(const MainCtx& cx, const float (&x)[N
     const bool special = kmin < 0x00800000u || kmax >= 0x7F800000u;
     const bool plain = ballot(special || valid != (1u << (4 * NQ)) - 1u) == 0;
     if (plain) {
-#pragma unroll
-        for (int u = 0; u < (int)NQ; ++u) {
-            uint32_t sel = 0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t k = key_of(x[u][c]);
-                const uint32_t m24 = (k & 0x7FFFFFu) | 0x800000u;
-                // the shifted square has 24 bits: as a 32-bit value it is the low word of the packed
-                // operand and the count's 1 is a constant high word
-                const unsigned long long sq = (unsigned long long)m24 * m24;
-                const uint32_t t = __builtin_amdgcn_alignbit((uint32_t)(sq >> 32), (uint32_t)sq, PK_SHIFT);
-                atomicAdd(&cx.pk[main_entry(cx, k)], PK_ONE | (unsigned long long)t);
-                sel |= (k >= cx.spill_key ? 1u : 0u) << c;
-            }
-            selm[u] = sel;
-        }
+        main_count_plain<TWO>(cx, x, selm);
         return;
     }
 #pragma unroll
@@ -313,7 +364,7 @@ __device__ __forceinline__ void main_count(const MainCtx& cx, const float (&x)[N
             if (!(valid & (1u << (4 * u + c)))) continue;
             const uint32_t k = key_of(x[u][c]);
             if ((k >> D1_SHIFT) != 0u) {
-                atomicAdd(&cx.pk[main_entry(cx, k)], PK_ONE | pk_term(k));
+                atomicAdd(&cx.pk[main_entry<TWO>(cx, k)], PK_ONE | pk_term(k));
             } else {
                 atomicAdd(&cx.pk[0], PK_ONE);
                 if (k) atomicAdd(cx.sq0, sq_exact(k));
@@ -388,12 +439,13 @@ __device__ __forceinline__ uint32_t spill_take(WaveSpill& ws, uint32_t entries, 
 
 // One chunk of the streaming pass for one wave: histogram updates, ranks of the entries to spill,
 // space for them, window writes, chunk record.
+template <bool TWO>
 __device__ __forceinline__ void main_chunk(const ProfileBuffers& pb, const MainCtx& cx, const LayerDesc& L, WaveSpill& ws,
                                            uint32_t chunk, const float (&x)[NQ][4], uint32_t valid) {
     const uint32_t lane = lane_id();
     const uint32_t vbase = (chunk - L.chunk0) * CHUNK;
     uint32_t selm[NQ];
-    main_count(cx, x, valid, selm);
+    main_count<TWO>(cx, x, valid, selm);
     // ranks in index order (quad, lane, element): per quad a prefix sum over the lanes of the lane's
     // count (0..4); two quads share a scan in 16-bit fields (a quad holds at most 256)
     static_assert(NQ == 4, "two packed scans cover four quads");
@@ -482,6 +534,26 @@ __device__ __forceinline__ void main_chunk(const ProfileBuffers& pb, const MainC
     }
 }
 
+// A wave's chunks of a segment: its first one, then what the segment's counter hands out.
+template <bool TWO>
+__device__ __forceinline__ void main_walk(const ProfileBuffers& pb, const MainCtx& cx, const LayerDesc& L, WaveSpill& ws,
+                                          uint32_t chunk, uint32_t seg_end, uint32_t* next_chunk) {
+    while (chunk < seg_end) {
+        uint32_t taken = 0;
+        if (lane_id() == 0) taken = atomicAdd(next_chunk, 1u);
+        QuadGH q[NQ];
+        float x[NQ][4];
+        uint32_t valid = 0;
+        load_chunk<NQ>(L, (chunk - L.chunk0) * CHUNK, q, valid);
+#pragma unroll
+        for (int u = 0; u < (int)NQ; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[u][c] = q[u].g[c] - q[u].h[c];
+        main_chunk<TWO>(pb, cx, L, ws, chunk, x, valid);
+        chunk = __builtin_amdgcn_readfirstlane(taken);
+    }
+}
+
 __global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint32_t chunks_per_wg) {
     __shared__ __align__(16) unsigned long long pk[PK_ENTRIES];   // 140 KB
     __shared__ unsigned long long sq0;
@@ -506,7 +578,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint3
         __syncthreads();
         MainCtx cx;
         cx.pk = pk; cx.sq0 = &sq0;
-        cx.lo19 = st.slot_lo << (D1_SHIFT - D2_SHIFT); cx.span = st.nslots_d * D2_BINS;
+        cx.lo19 = (st.slot_lo & 0xFFFFu) << (D1_SHIFT - D2_SHIFT); cx.span = st.run_a * D2_BINS;
+        cx.lo19b = (st.slot_lo >> 16) << (D1_SHIFT - D2_SHIFT); cx.spanb = (st.nslots_d - st.run_a) * D2_BINS;
         cx.spill_key = st.spill_bin >= D1_BINS ? 0x80000000u : (st.spill_bin << D1_SHIFT);
         WaveSpill ws;
         ws.win = stage + wave * STAGE;
@@ -526,21 +599,9 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint3
         // wave for a good tenth of the pass.  The next chunk is asked for before the current one is
         // worked on, so the counter's round trip is never waited for.  No result depends on which wave
         // had which chunk.
-        uint32_t chunk = cur + wave;
-        while (chunk < seg_end) {
-            uint32_t taken = 0;
-            if (lane_id() == 0) taken = atomicAdd(&next_chunk, 1u);
-            QuadGH q[NQ];
-            float x[NQ][4];
-            uint32_t valid = 0;
-            load_chunk<NQ>(L, (chunk - L.chunk0) * CHUNK, q, valid);
-#pragma unroll
-            for (int u = 0; u < (int)NQ; ++u)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) x[u][c] = q[u].g[c] - q[u].h[c];
-            main_chunk(pb, cx, L, ws, chunk, x, valid);
-            chunk = __builtin_amdgcn_readfirstlane(taken);
-        }
+        // (one copy of the loop per number of slot runs: testing for the second run in the loop cost 2 % of the pass)
+        if (cx.spanb == 0u) main_walk<false>(pb, cx, L, ws, cur + wave, seg_end, &next_chunk);
+        else main_walk<true>(pb, cx, L, ws, cur + wave, seg_end, &next_chunk);
         spill_flush(pb, ws, L.tmp0);
         __syncthreads();
         // This segment's histogram goes out as it is, with plain coalesced stores, as one "part" of the
@@ -648,6 +709,7 @@ __global__ __launch_bounds__(256) void k_reduce_parts(ProfileBuffers pb) {
 // bins), boundary bin per candidate, and what each boundary needs:
 //   - its bin already has a slot                          -> nothing
 //   - its bin is in the spilled range                     -> a slot PRE_SLOTS.. filled from the candidates
+//   - it is bin 0, and that holds zeros only              -> such a slot too, filled here: the count, in digit 2 = 0
 //   - neither (prediction missed), or slots run out       -> redo: exact slots, full recount
 __global__ __launch_bounds__(256) void k_scan1x(ProfileBuffers pb, const uint32_t* Ktab, uint32_t J) {
     __shared__ uint32_t cnt[D1_BINS];
@@ -657,7 +719,7 @@ __global__ __launch_bounds__(256) void k_scan1x(ProfileBuffers pb, const uint32_
     __shared__ double sd[16];
     __shared__ uint32_t tbin[MAX_SLOTS];
     __shared__ uint8_t lut[D1_BINS];
-    __shared__ uint32_t sh_redo;
+    __shared__ uint32_t sh_redo, sh_zeros;
     __shared__ uint32_t slot_c[PRE_SLOTS];
     __shared__ unsigned long long slot_s[PRE_SLOTS];
     const uint32_t tid = threadIdx.x, big = blockIdx.x;
@@ -710,6 +772,7 @@ __global__ __launch_bounds__(256) void k_scan1x(ProfileBuffers pb, const uint32_
         csum += cc;
         ssum += s[k];
     }
+    if (tid == 0) sh_zeros = s[0] == 0.0 ? 1u : 0u;       // (bin 0's sum is exact: 0 only if every entry there is zero)
     {
         // the exact histogram stays for the next profile's prediction, with its sum over the layers
         uint4* hp = reinterpret_cast<uint4*>(pb.hprev + (size_t)big * D1_BINS + tid * 16u);
@@ -757,7 +820,7 @@ __global__ __launch_bounds__(256) void k_scan1x(ProfileBuffers pb, const uint32_
             pb.tgt_r[(size_t)li * J + tid] = K - above[bin];
             pb.tgt_above1[(size_t)li * J + tid] = above[bin];
             pb.tgt_below[(size_t)li * J + tid] = below[bin];
-            if (lut[bin] == NO_SLOT && !(spill_valid && bin >= st.spill_bin)) atomicOr(&sh_redo, 1u);
+            if (lut[bin] == NO_SLOT && !(spill_valid && bin >= st.spill_bin) && !(bin == 0u && sh_zeros)) atomicOr(&sh_redo, 1u);
         }
         tbin[tid] = bin;
     }
@@ -803,7 +866,8 @@ __global__ __launch_bounds__(256) void k_scan1x(ProfileBuffers pb, const uint32_
             } else {
                 slot = PRE_SLOTS + (uint32_t)__popcll(heads_c & upto) - 1u;
                 if (newrun) {
-                    glutc[bin] = (uint8_t)slot;
+                    if (bin == 0u && !(spill_valid && st.spill_bin == 0u)) pb.cnt2[((size_t)big * SLOT_STRIDE + slot) * D2_BINS] = cnt[0];
+                    else glutc[bin] = (uint8_t)slot;
                     pb.slot_bin[(size_t)big * SLOT_STRIDE + slot] = bin;
                 }
             }
@@ -861,6 +925,78 @@ __global__ __launch_bounds__(256) void k_hist2c(ProfileBuffers pb) {
             atomicAdd(&c2[e], 1u);
             if (s) atomicAdd(&s2[e], s);
         }
+    }
+}
+
+// The same where the slots hold many entries (the grid's smallest ratio is no small share of the layer): the additions
+// queue up on the slots' few lines, so the layer that has a fair share of a workgroup's 256 chunks is counted in LDS, in
+// the packed form of the streaming pass, and added to the layer's tables once; other layers' candidates go there one by
+// one.  (ResNet-18 with the paper's grid: 39 to 71 us one by one, 15 so.  The headline set, whose slots are sparse, takes
+// 21 us this way instead of 16, the Llama-shaped one 101 instead of 87.)
+constexpr uint32_t DENSE_THREADS = 1024;
+constexpr uint32_t DENSE_CHUNKS = DENSE_THREADS / SUB_HIST;
+constexpr uint32_t DENSE_SHARE = 64;           // chunks of one layer from which on the table in LDS pays
+__global__ __launch_bounds__(DENSE_THREADS) void k_hist2c_dense(ProfileBuffers pb) {
+    constexpr uint32_t S = SUB_HIST;
+    __shared__ unsigned long long tab[(SLOT_STRIDE - PRE_SLOTS) * D2_BINS];     // 64 KB
+    const SubGroup g = sub_group<S>();
+    const uint32_t c0 = blockIdx.x * DENSE_CHUNKS, chunk = c0 + threadIdx.x / S;
+    uint32_t big = 0u, first = 0u, cnt = 0u, start = 0u;
+    if (chunk < pb.nchunks_total) { big = pb.chunk_big[chunk]; first = pb.chunk_first[chunk]; cnt = pb.rec_cnt[chunk]; start = pb.rec_start[chunk]; }
+    materialise(big); materialise(first); materialise(cnt); materialise(start);
+    // the layer of the middle chunk (any layer with more than half of the chunks is that one)
+    const uint32_t c_end = min(pb.nchunks_total, c0 + DENSE_CHUNKS);
+    const uint32_t main_big = pb.chunk_big[c0 + (c_end - c0) / 2u];
+    const LayerState main_st = pb.state[main_big];
+    const LayerDesc& ML = pb.layers[pb.big_layer[main_big]];
+    const uint32_t m0 = max(c0, ML.chunk0), m1 = min(c_end, ML.chunk0 + ML.nchunks);
+    const uint32_t nt = main_st.redo || m1 - m0 < DENSE_SHARE ? 0u : main_st.nslots_t;          // slots in LDS (0: none)
+    for (uint32_t e = threadIdx.x; e < nt * D2_BINS; e += DENSE_THREADS) tab[e] = 0ull;
+    __syncthreads();
+    if (cnt != 0u) {
+        const uint64_t base = region_start(first, big) + start;
+        const LayerState st = pb.state[big];
+        const uint8_t* lutc = pb.lutc + (size_t)big * D1_BINS;
+        uint32_t* c2 = pb.cnt2 + (size_t)big * SLOT_STRIDE * D2_BINS;
+        unsigned long long* s2 = reinterpret_cast<unsigned long long*>(pb.sq2) + (size_t)big * SLOT_STRIDE * D2_BINS;
+        const bool in_lds = nt != 0u && big == main_big;
+        constexpr int AHEAD = 8;
+        for (uint32_t k0 = g.sub; k0 < cnt; k0 += AHEAD * S) {
+            uint32_t key[AHEAD], slot[AHEAD];
+#pragma unroll
+            for (int t = 0; t < AHEAD; ++t)
+                key[t] = key_of(pb.tmp_x[base + min(k0 + (uint32_t)t * S, cnt - 1u)]);
+            if (st.redo || st.nslots_t == 0u) break;
+#pragma unroll
+            for (int t = 0; t < AHEAD; ++t) slot[t] = (uint32_t)lutc[key[t] >> D1_SHIFT];
+#pragma unroll
+            for (int t = 0; t < AHEAD; ++t) {
+                if (slot[t] == NO_SLOT || k0 + (uint32_t)t * S >= cnt) continue;
+                const uint32_t bin = key[t] >> D1_SHIFT, d2 = (key[t] >> D2_SHIFT) & (D2_BINS - 1);
+                if (in_lds && bin != 0u) {
+                    // (at most 256 chunks' entries: the count field holds 1023)
+                    atomicAdd(&tab[(slot[t] - PRE_SLOTS) * D2_BINS + d2], PK_ONE | pk_term(key[t]));
+                } else {
+                    const uint32_t e = slot[t] * D2_BINS + d2;
+                    const unsigned long long s = bin ? (unsigned long long)sq_coarse(key[t]) : sq_exact(key[t]);
+                    atomicAdd(&c2[e], 1u);
+                    if (s) atomicAdd(&s2[e], s);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    uint32_t* c2 = pb.cnt2 + ((size_t)main_big * SLOT_STRIDE + PRE_SLOTS) * D2_BINS;
+    unsigned long long* s2 = reinterpret_cast<unsigned long long*>(pb.sq2) + ((size_t)main_big * SLOT_STRIDE + PRE_SLOTS) * D2_BINS;
+    for (uint32_t e = threadIdx.x; e < nt * D2_BINS; e += DENSE_THREADS) {
+        const unsigned long long v = tab[e];
+        if (v == 0ull) continue;
+        const uint32_t n = (uint32_t)(v >> 44);
+        const uint32_t bin = pb.slot_bin[(size_t)main_big * SLOT_STRIDE + PRE_SLOTS + e / D2_BINS];
+        // the sums as midpoints in units of 2^16, as k_reduce_parts writes them (exponent 255: the NaN count)
+        const unsigned long long s = (bin >> 4) == 255u ? (v & PK_MASK) : ((v & PK_MASK) << 8) + ((unsigned long long)n << 7);
+        atomicAdd(&c2[e], n);
+        if (s) atomicAdd(&s2[e], s);
     }
 }
 

@@ -340,6 +340,7 @@ struct kimad_plan {
     std::vector<HostLayer> hl;
     std::vector<uint32_t> ktab;      // host copy of K_ij
     std::vector<uint32_t> kmax;      // K_{i,J-1}
+    double ratio0 = 0.0;             // the grid's smallest ratio
     char* ws = nullptr;
     int device = 0;
     uint32_t main_wgs = 256;         // persistent workgroups of the fused pass (one per compute unit)
@@ -482,7 +483,12 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
         if (rc) return rc;
     }
     KLAUNCH(p, s, "k_scan1x", k_scan1x, dim3(lo.B), dim3(256), p->pb, ktab, J);
-    KLAUNCH(p, s, "k_hist2c", k_hist2c, dim3((lo.nchunks + 256u / SUB_HIST - 1) / (256u / SUB_HIST)), dim3(256), p->pb);
+    // a grid whose smallest ratio keeps a five-hundredth of a layer has no sparse slots (the two kernels' comments have both sides)
+    if (err_table && p->ratio0 >= 1.0 / 512.0) {
+        KLAUNCH(p, s, "k_hist2c", k_hist2c_dense, dim3((lo.nchunks + DENSE_CHUNKS - 1) / DENSE_CHUNKS), dim3(DENSE_THREADS), p->pb);
+    } else {
+        KLAUNCH(p, s, "k_hist2c", k_hist2c, dim3((lo.nchunks + 256u / SUB_HIST - 1) / (256u / SUB_HIST)), dim3(256), p->pb);
+    }
     // fallbacks that normally find nothing to do: small grids
     KLAUNCH(p, s, "k_hist2", k_hist2, dim3(std::min<uint32_t>(lo.ntiles, FALLBACK_GRID)), dim3(512), p->pb, lo.ntiles,
             (const uint32_t*)(at<uint32_t>(p, lo.diag) + 3), 1u);   // layers marked redo only
@@ -643,6 +649,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
     kimad_plan* p = new (std::nothrow) kimad_plan();
     if (!p) return KIMAD_ERR_INVALID_ARG;
     p->cfg = normalise(cfg);
+    p->ratio0 = ratios[0];
     PartTables pt;
     int rc = make_layout(n.data(), L, J, p->cfg, p->lo, &p->hl, &pt);
     if (rc) { delete p; return rc; }

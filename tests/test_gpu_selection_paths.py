@@ -79,3 +79,30 @@ def test_selection_from_scratch_over_several_rounds(share):
         work = Workload(name="scratch", sizes=np.asarray(sizes, dtype=np.uint64), g=g1, h=h0, ratios=np.array([1.0]),
                         budget_bytes=8, cost_units_D=0)
         gh.check_compress(work, plan, hd, K, off, idx, val)
+
+
+@pytest.mark.parametrize("zeros", [0.0, 0.015, 0.3])
+@pytest.mark.parametrize("n", [8193, 70001, 400003])
+def test_profile_on_a_grid_up_to_nearly_all_entries(n, zeros):
+    """The paper's grid needs digit-2 tables over more bins than one run of them covers, and more spilled than the
+    budget asks for; with exact zeros in the layer, a ratio's boundary lies among them."""
+    import torch
+    import paper_2312_08053_amd as kimad
+    from kimad_synth.gen import paper_grid
+    rng = np.random.default_rng(n)
+    sizes, ratios = [n, n, 12000], paper_grid()
+    gd = torch.empty(sum(sizes), dtype=torch.float32, device="cuda")
+    hd = torch.zeros_like(gd)
+    plan = kimad.Plan(gd, hd, sizes, ratios.tolist(), D=1000, max_budget_bytes=4 * sum(sizes))
+    Kt = plan.grid_sizes()
+    starts = np.concatenate([[0], np.cumsum(sizes)])
+    for _ in range(3):
+        g = rng.standard_t(3, size=sum(sizes)).astype(np.float32)
+        g[rng.random(g.size) < zeros] = 0.0
+        gd.copy_(torch.from_numpy(g))
+        E = plan.profile(budget_hint_bytes=int(0.05 * 4 * sum(sizes))).cpu().numpy().reshape(len(sizes), -1)
+        gL = [g[a:b] for a, b in zip(starts[:-1], starts[1:])]
+        E_ref, _ = ko.profile(gL, [np.zeros_like(x) for x in gL], ratios)
+        gh.assert_table_close(E, E_ref, Kt, sizes)
+    if n == 400003:
+        assert plan.diagnostics()["redo_layers"] <= 1       # (the layer of 12000 entries may be recounted)
