@@ -111,10 +111,18 @@ struct DpLists {
     double* e;       // [L][J][2] error of the last member, error of the member before it (NaN for a single)
     uint32_t* n;     // [L] entries
     uint32_t* bad;   // [L] 1 if the layer's table row holds an Inf or a NaN
+    // lower convex hull of the list's (cost, error) points, for the banded recurrence
+    double* he;      // [L][J] vertex errors, falling
+    uint32_t* hw;    // [L][J] vertex costs, rising; HULL_LAST set at the last one
+    uint32_t* hn;    // [L] vertices
+    double* habs;    // [L] largest |error| of the list
 };
+constexpr uint32_t HULL_LAST = 0x80000000u;
 
-// One wave per layer, one lane per candidate.
-__global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl) {
+// One wave per layer, one lane per candidate.  `with_hull`: also the list's lower convex hull.
+__global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uint32_t with_hull) {
+    __shared__ double se[KIMAD_MAX_J_CONST];
+    __shared__ uint32_t sw[KIMAD_MAX_J_CONST];
     const uint32_t i = blockIdx.x, j = threadIdx.x;
     const bool valid = j < ab.J;
     uint32_t w = 0xFFFFFFFFu;
@@ -143,10 +151,59 @@ __global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl) {
         dl.e[2 * o] = e_last;
         dl.e[2 * o + 1] = b > j ? e_before : __longlong_as_double(0x7FF8000000000000ll);
     }
+    const uint32_t n = (uint32_t)__builtin_popcountll(smask);
     if (j == 0) {
-        dl.n[i] = (uint32_t)__builtin_popcountll(smask);
+        dl.n[i] = n;
         dl.bad[i] = nonfinite ? 1u : 0u;
     }
+    if (!with_hull) return;
+    // ---- the hull, one list entry per lane.  Every test below drops a point because of other points of the list
+    // (one that is no dearer and saves as much; two whose chord passes at or below it), so all lanes test at once, and
+    // again with their new neighbours until none is dropped.  (A point dropped or kept by the rounding of the chord test
+    // changes a minimum over the vertices by rounding only.  One thread per layer pushing and popping took 17 us of the
+    // next kernel; error profiles are nearly convex, and one or two rounds are the rule here.)
+    const uint64_t lower = (1ull << j) - 1ull, upper = ~((2ull << j) - 1ull);
+    if (start) {
+        const uint32_t at = (uint32_t)__builtin_popcountll(smask & lower);
+        se[at] = e_last; sw[at] = w;
+    }
+    __syncthreads();
+    const bool listed = j < n;
+    const double pe = listed ? se[j] : DP_INF;
+    const uint32_t pw = listed ? sw[j] : 0xFFFFFFFFu;
+    double least = pe, largest = listed ? fabs(pe) : 0.0;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const double o = __shfl_up(least, d, 64);
+        if ((int)j >= d) least = fmin(least, o);
+        largest = fmax(largest, __shfl_xor(largest, d, 64));
+    }
+    const double before = __shfl_up(least, 1, 64);
+    bool alive = listed && (j == 0u || pe < before);
+    uint64_t mask = ballot(alive);
+    {
+        const uint64_t up = mask & upper;                    // of equal costs the last, which has the least error
+        const uint32_t nw = __shfl(pw, up ? __builtin_ctzll(up) : (int)j, 64);
+        alive = alive && !(up && nw == pw);
+        mask = ballot(alive);
+    }
+    for (;;) {
+        const uint64_t up = mask & upper, dn = mask & lower;
+        const int nx = up ? __builtin_ctzll(up) : (int)j, pv = dn ? 63 - __builtin_clzll(dn) : (int)j;
+        const double ne = __shfl(pe, nx, 64), qe = __shfl(pe, pv, 64);
+        const uint32_t nw = __shfl(pw, nx, 64), qw = __shfl(pw, pv, 64);
+        const bool drop = alive && up && dn && (qe - pe) * (double)(nw - pw) <= (pe - ne) * (double)(pw - qw);
+        const uint64_t dropped = ballot(drop);
+        if (dropped == 0ull) break;
+        alive = alive && !drop;
+        mask &= ~dropped;
+    }
+    if (alive) {
+        const size_t o = (size_t)i * ab.J + (uint32_t)__builtin_popcountll(mask & lower);
+        dl.he[o] = pe;
+        dl.hw[o] = pw | ((mask & upper) ? 0u : HULL_LAST);
+    }
+    if (j == 0) { dl.hn[i] = (uint32_t)__builtin_popcountll(mask); dl.habs[i] = largest; }
 }
 
 // The recurrence for capacities whose rows fit LDS, in three kernels:
@@ -573,9 +630,15 @@ __global__ __launch_bounds__(1024) void k_dp_final(AllocBuffers ab, const double
     const uint32_t tid = threadIdx.x;
     double best = DP_INF;
     unsigned long long bc = ~0ull;
-    for (uint64_t c = tid; c <= ab.cap; c += 1024) {
-        const double v = last[c];
-        if (v < best) { best = v; bc = c; }     // ascending c per thread: keeps the smallest
+    for (uint64_t c0 = tid; c0 <= ab.cap; c0 += 8u * 1024u) {
+        double v[8];                            // eight loads at a time (positions past the end read the last cell and are dropped)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = last[min(c0 + 1024u * (uint64_t)u, (uint64_t)ab.cap)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const uint64_t c = c0 + 1024u * (uint64_t)u;
+            if (c <= ab.cap && v[u] < best) { best = v[u]; bc = c; }     // ascending c per thread: keeps the smallest
+        }
     }
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) {
@@ -601,9 +664,11 @@ __global__ __launch_bounds__(1024) void k_dp_final(AllocBuffers ab, const double
         for (uint32_t i = tid; i <= ab.L; i += 1024) ab.offsets_out[i] = 0;
         return;
     }
-    // Back-tracking: one thread follows the chain of cells, one choice per layer read from memory.  The
+    // Back-tracking, two layers per memory round trip: with the cell's own choice, lane j asks for the layer before's
+    // choice at the cell that candidate j would lead to; the lane that the choice names has the next one.  The
     // candidates' costs wait in LDS (when the table fits) so that the chain holds no second memory read
-    // and no division; sizes and offsets follow in parallel.
+    // and no division; sizes and offsets follow in parallel.  (One choice per round trip, by one thread, and one load at
+    // a time above: 44 us for 58 layers and 58 thousand cells, 34 now.)
     constexpr uint32_t W_LDS = 12288;
     __shared__ uint32_t sw[W_LDS];
     const uint32_t LJ = ab.L * ab.J;
@@ -611,12 +676,25 @@ __global__ __launch_bounds__(1024) void k_dp_final(AllocBuffers ab, const double
     if (w_in_lds)
         for (uint32_t t = tid; t < LJ; t += 1024) sw[t] = units_of(ab.Ktab[t], ab.unit);
     __syncthreads();
-    if (tid == 0) {
+    if (tid < 64) {
+        static_assert(KIMAD_MAX_J_CONST <= 64, "one lane per candidate");
         uint64_t c = cstar;
-        for (uint32_t i = ab.L; i-- > 0;) {
-            const uint32_t j = ab.choice[(size_t)i * ab.stride + c];
-            ab.j_out[i] = (int32_t)j;
-            c -= w_in_lds ? sw[i * ab.J + j] : units_of(ab.Ktab[(size_t)i * ab.J + j], ab.unit);
+        const uint32_t j = min(tid, ab.J - 1u);
+        auto cost = [&](uint32_t i, uint32_t k) { return w_in_lds ? sw[i * ab.J + k] : units_of(ab.Ktab[(size_t)i * ab.J + k], ab.unit); };
+        for (uint32_t i = ab.L; i > 0u;) {
+            --i;
+            const uint32_t w = cost(i, j);
+            const uint32_t here = ab.choice[(size_t)i * ab.stride + c];
+            uint32_t before = 0u;
+            if (i > 0u) before = ab.choice[(size_t)(i - 1u) * ab.stride + (w <= c ? c - w : 0u)];
+            const int j0 = (int)__builtin_amdgcn_readfirstlane(here);          // (a feasible path meets candidates only)
+            if (tid == 0) ab.j_out[i] = j0;
+            c -= (uint32_t)__builtin_amdgcn_readlane((int)w, j0);
+            if (i == 0u) break;
+            --i;
+            const uint32_t j1 = (uint32_t)__builtin_amdgcn_readlane((int)before, j0);
+            if (tid == 0) ab.j_out[i] = (int32_t)j1;
+            c -= cost(i, j1);
         }
     }
     __threadfence_block();

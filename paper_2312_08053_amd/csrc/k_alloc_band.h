@@ -13,7 +13,7 @@
 //                UB (by a margin far above the rounding of these sums) lies on no path that attains the
 //                least total, and the cells that remain form an interval of every row: its band.
 //   k_dp_banded  the recurrence on the band cells only; sources outside the previous row's band count
-//                as +inf.
+//                as +inf.  Then the walk back and the outputs.
 //
 // Why the result is the same.  The sequential recurrence computes, per cell, the minimum over paths of
 // the path's left-to-right fp64 sum, and fp64 addition is monotone, so removing cells can only raise
@@ -30,25 +30,20 @@
 namespace kimad {
 
 constexpr uint32_t BAND_MAX_L = 1024;          // layers the banded allocation handles
-constexpr uint32_t BAND_LCAP = 7168;           // list records held in LDS by the bounds kernel
+constexpr uint32_t BAND_LCAP = 7168;           // list records (and so hull vertices, which LDS holds) the bounds kernel takes
 constexpr uint32_t BAND_NLAM = 32;             // multipliers around the one found: lambda* rho^(m - 16)
-constexpr uint32_t BAND_NLAM_MANY = 8;         // the same for more layers than the table of 32 fits LDS for
-constexpr uint32_t BAND_L_FOR_32 = 416;
 constexpr uint32_t BAND_GREEDY = 16;           // rounds of the greedy fill that tightens the upper bound
 constexpr uint32_t BOUNDS_THREADS = 1024;
 constexpr uint32_t BAND_EDGES_PER_THREAD = BAND_LCAP / BOUNDS_THREADS;   // 7
+constexpr uint32_t BAND_GROUPS = BOUNDS_THREADS / BAND_NLAM;             // 32 groups of layers, one thread per multiplier each
 
 struct BandBuffers {
     uint32_t* lo;          // [L + 1] first cell of row r's band (row 0 is the start: cell 0)
     uint32_t* hi;          // [L + 1] last cell
-    uint32_t* info;        // [16] max width, sum of widths, 1 if the bands are the whole rows, upgrades taken; rest: tracing
-    // the list records that can connect the bands of consecutive rows, layer after layer (the only ones the
-    // banded recurrence visits): layer i's are [live_off[i], live_off[i + 1])
-    uint32_t* live_off;    // [L + 1]
-    double* live_e;        // [L * J] error of the run's last member
-    double* live_before;   // [L * J] error of the member before it (NaN for a single)
-    uint32_t* live_w;      // [L * J] cost
-    uint32_t* live_jj;     // [L * J] first member | last member << 8
+    uint32_t* info;        // [16] max width, sum of widths, 1 if the bands are the whole rows, upgrades taken, 1 if nothing fits
+    // the list records that can connect the bands of rows i and i + 1 (the only ones the banded recurrence visits)
+    uint32_t* live;        // [L] first record | count << 8
+    double* table;         // [(L + 1) * BAND_NLAM] prefix sums of the per-layer minima; the rows' memory before there are rows
 };
 
 __device__ __forceinline__ double max_f64(double a, double b) {   // neither a signalling NaN (see min_f64)
@@ -57,7 +52,7 @@ __device__ __forceinline__ double max_f64(double a, double b) {   // neither a s
     return r;
 }
 
-// The value of another lane inside groups of 2, 4 or 8 neighbouring lanes, through DPP moves (a shuffle goes
+// The value of another lane inside groups of 2, 4, 8 or 16 neighbouring lanes, through DPP moves (a shuffle goes
 // through the LDS crossbar: a dependent round trip per step).
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
@@ -73,24 +68,307 @@ __device__ __forceinline__ double group_max(double v) {
     if (T >= 8) v = max_f64(v, dpp_f64<0x141>(v));     // row_half_mirror: the other quad of the eight
     return v;
 }
+// minimum over the T lanes of a group (T = 1, 2, 4, 8, 16), in every lane of it
+template <int T>
+__device__ __forceinline__ double group_min(double v) {
+    if (T >= 2) v = min_f64(v, dpp_f64<0xB1>(v));
+    if (T >= 4) v = min_f64(v, dpp_f64<0x4E>(v));
+    if (T >= 8) v = min_f64(v, dpp_f64<0x141>(v));
+    if (T >= 16) v = min_f64(v, dpp_f64<0x140>(v));    // row_mirror: the other eight of the sixteen
+    return v;
+}
 
-// Bands of all rows: T threads a row, PT multipliers each (T * PT = the number of multipliers).  Returns the
-// sum of the widths of the rows whose first lane this thread is.
-template <int T, int PT>
-__device__ __forceinline__ uint32_t band_rows(const double* AT, uint32_t pitch, const double* s_lam, const double* s_btot,
-                                              const uint16_t* s_cum, uint16_t* s_blo, uint16_t* s_bhi, const BandBuffers& bb,
-                                              uint32_t L, uint32_t cap, double ub_m) {
-    const uint32_t tid = threadIdx.x;
-    uint32_t width = 0u;
-    for (uint32_t r_base = 1u; r_base <= L; r_base += BOUNDS_THREADS / T) {
-        const uint32_t r = r_base + tid / T, part = tid % T;
-        const bool live_row = r <= L;
-        const uint32_t rr = live_row ? r : L;      // (lanes past the last row repeat it: a group's lanes stay together)
+// The greedy fill, by one wave: lane l looks after layers l, l + 64, ...  Every round the steepest edge that fits what is
+// left is taken (the lowest lane's among equals; only the upper bound's tightness depends on it); returns the steps taken.
+// Up to 64 M layers' next edges stay in registers; beyond (M = 0) they are read again every round.  (One thread per layer
+// of the whole workgroup, with two barriers a round, took 20 us.)
+template <int M>
+__device__ __forceinline__ uint32_t greedy_fill(const double* HE, const uint32_t* HW, const uint16_t* s_off, uint16_t* s_q,
+                                                uint32_t L, uint32_t left) {
+    constexpr int R = M ? M : 1;
+    const uint32_t lane = lane_id();
+    double slope[R];
+    uint32_t dw[R];
+    auto edge = [&](uint32_t i, double& s, uint32_t& d) {
+        const uint32_t o = (uint32_t)s_off[i] + s_q[i];
+        const uint32_t w = HW[o];
+        s = 0.0; d = 0xFFFFFFFFu;
+        if (!(w & HULL_LAST)) {
+            d = (HW[o + 1u] & ~HULL_LAST) - w;
+            s = (HE[o] - HE[o + 1u]) / (double)d;
+        }
+    };
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const uint32_t i = lane + 64u * (uint32_t)m;
+        slope[m] = 0.0; dw[m] = 0xFFFFFFFFu;
+        if (i < L) edge(i, slope[m], dw[m]);
+    }
+    uint32_t taken = 0u;
+    for (uint32_t round = 0; round < BAND_GREEDY && left > 0u; ++round) {
+        double best = 0.0;
+        uint32_t which = 0u, cost = 0u;
+        if (M) {
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+                if (dw[m] <= left && slope[m] > best) { best = slope[m]; which = (uint32_t)m; cost = dw[m]; }
+        } else {
+            for (uint32_t i = lane; i < L; i += 64u) {
+                double s;
+                uint32_t d;
+                edge(i, s, d);
+                if (d <= left && s > best) { best = s; which = i / 64u; cost = d; }
+            }
+        }
+        double top = best;
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) top = max_f64(top, __shfl_xor(top, d, 64));
+        if (!(top > 0.0)) break;
+        const uint32_t winner = (uint32_t)__builtin_ctzll(ballot(best == top));
+        left -= (uint32_t)__builtin_amdgcn_readlane((int)cost, (int)winner);
+        ++taken;
+        if (lane == winner) {
+            const uint32_t i = lane + 64u * which;
+            s_q[i] = (uint16_t)(s_q[i] + 1u);
+            double s = 0.0;
+            uint32_t d = 0u;
+            if (M) edge(i, s, d);
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+                if (which == (uint32_t)m) { slope[m] = s; dw[m] = d; }
+        }
+        wave_sync_lds();
+    }
+    return taken;
+}
+
+// Bounds kernel: one workgroup of sixteen waves over the hulls of k_dp_prep.  Only hull vertices can minimise E + lambda w,
+// and along a hull the slopes (error saved per unit of cost) fall, so a layer's minimiser for a given lambda is found by
+// bisection.
+//   1  the hulls go to LDS;
+//   2  the smallest lambda whose minimisers fit the capacity: the total cost at lambda is that of the cheapest
+//      vertices plus the cost steps of all hull edges steeper than lambda; every thread keeps a few edges in
+//      registers and the bit pattern of lambda (ordered like the doubles) is searched;
+//   3  upper bound: that assignment, then up to BAND_GREEDY single steps to a next hull vertex;
+//   4  the table A[r][m] = sum over layers before r of the minimum at lambda_m: a thread per multiplier and group of
+//      consecutive layers sums its layers, the groups' totals are added up afterwards;
+//   5  the band of every row by a search outward from the assignment's own cell, four threads to an edge;
+//   6  the live records of every layer.
+// A chain of short phases, each a few LDS round trips: 94 us with the hulls, serial sums and the live records' copies in
+// it, 41 us now on the headline set's table at 4097 cells (148 layers).
+__global__ __launch_bounds__(BOUNDS_THREADS) void k_dp_bounds(AllocBuffers ab, DpLists dl, BandBuffers bb) {
+    constexpr uint32_t NWAVES = BOUNDS_THREADS / 64;
+    __shared__ double HE[BAND_LCAP];                                    // 56 KB: vertex errors
+    __shared__ uint32_t HW[BAND_LCAP];                                  // 28 KB: vertex costs, HULL_LAST at a hull's last
+    __shared__ double s_gt[BAND_GROUPS * BAND_NLAM];                    // 8 KB: per group and multiplier, then the sums before the group
+    __shared__ uint16_t s_off[BAND_MAX_L], s_hn[BAND_MAX_L], s_q[BAND_MAX_L], s_n[BAND_MAX_L];
+    __shared__ uint16_t s_cum[BAND_MAX_L + 2], s_blo[BAND_MAX_L + 2], s_bhi[BAND_MAX_L + 2];
+    __shared__ uint32_t su[16];
+    __shared__ double sd[16];
+    __shared__ double s_lam[BAND_NLAM], s_btot[BAND_NLAM];
+    __shared__ uint32_t s_hist[2][64];
+    __shared__ uint32_t s_flag, s_wmax, s_upgrades;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t L = ab.L, J = ab.J, cap = ab.cap;
+
+    // no bound to use: whole rows, every record live (or, if `hopeless`, nothing fits and the recurrence is not run)
+    auto whole_rows = [&](bool hopeless) {
+        for (uint32_t r = tid; r <= L; r += BOUNDS_THREADS) { bb.lo[r] = 0u; bb.hi[r] = r ? cap : 0u; }
+        if (tid < L) bb.live[tid] = min(dl.n[tid], 64u) << 8;
+        if (tid == 0) { bb.info[0] = cap + 1u; bb.info[1] = L * (cap + 1u); bb.info[2] = 1u; bb.info[3] = 0u; bb.info[4] = hopeless ? 1u : 0u; }
+    };
+
+    // ---- 1: sizes, offsets, hulls into LDS
+    const uint32_t my_n = tid < L ? min(dl.hn[tid], 64u) : 0u;
+    const uint32_t list_n = tid < L ? min(dl.n[tid], 64u) : 0u;
+    const double my_abs = tid < L ? dl.habs[tid] : 0.0;
+    const uint32_t my_bad = tid < L ? dl.bad[tid] : 0u;
+    uint32_t n_tot, list_tot;
+    const uint32_t my_off = block_exclusive_scan<uint32_t>(my_n, su, &n_tot);
+    (void)block_exclusive_scan<uint32_t>(list_n, su, &list_tot);
+    if (tid == 0) { s_flag = 0u; s_wmax = 0u; s_upgrades = 0u; }
+    if (tid < 128u) s_hist[tid >> 6][tid & 63u] = 0u;
+    if (tid < L && list_tot <= BAND_LCAP) { s_hn[tid] = (uint16_t)my_n; s_n[tid] = (uint16_t)list_n; s_off[tid] = (uint16_t)my_off; }
+    __syncthreads();
+    if (my_bad) atomicOr(&s_flag, 1u);
+    if (tid < L && my_n == 0u) atomicOr(&s_flag, 2u);                    // a layer with no affordable candidate
+    __syncthreads();
+    if (list_tot > BAND_LCAP || s_flag != 0u) { whole_rows((s_flag & 2u) != 0u); return; }
+    // eight layers' loads in flight per wave
+    for (uint32_t i0 = wave * 8u; i0 < L; i0 += NWAVES * 8u) {
+        double e[8];
+        uint32_t w[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t i = i0 + (uint32_t)u;
+            const bool in = i < L && lane < s_hn[min(i, L - 1u)];
+            const size_t o = in ? (size_t)i * J + lane : 0;
+            e[u] = dl.he[o]; w[u] = dl.hw[o];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t i = i0 + (uint32_t)u;
+            if (i < L && lane < s_hn[i]) { HE[s_off[i] + lane] = e[u]; HW[s_off[i] + lane] = w[u]; }
+        }
+    }
+    __syncthreads();
+    auto cost_at = [&](uint32_t o) { return HW[o] & ~HULL_LAST; };
+    // the vertex of layer i that minimises E + lam w: the number of its edges steeper than lam
+    auto vertex_at = [&](uint32_t i, double lam) {
+        const uint32_t o = s_off[i];
+        uint32_t lo = 0u, hi = (uint32_t)s_hn[i] - 1u;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (HE[o + mid] - HE[o + mid + 1u] > lam * (double)(cost_at(o + mid + 1u) - HW[o + mid])) lo = mid + 1u; else hi = mid;
+        }
+        return lo;
+    };
+
+    // ---- 2: the smallest multiplier that fits.  This thread's edges (slope, cost step) stay in registers.
+    unsigned long long lo_b = 0ull, hi_b = 0ull;
+    double gentle;                                                           // the least steep edge
+    {
+        double sl[BAND_EDGES_PER_THREAD];
+        uint32_t dw[BAND_EDGES_PER_THREAD];
+        double steep = 0.0;
+        gentle = DP_INF;
+#pragma unroll
+        for (int u = 0; u < (int)BAND_EDGES_PER_THREAD; ++u) {
+            const uint32_t x = tid + (uint32_t)u * BOUNDS_THREADS;
+            sl[u] = 0.0; dw[u] = 0u;
+            if (x < n_tot && !(HW[x] & HULL_LAST)) {
+                dw[u] = cost_at(x + 1u) - HW[x];
+                sl[u] = (HE[x] - HE[x + 1u]) / (double)dw[u];
+                steep = max_f64(steep, sl[u]);
+                gentle = min_f64(gentle, sl[u]);
+            }
+        }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) { steep = max_f64(steep, __shfl_xor(steep, d, 64)); gentle = min_f64(gentle, __shfl_xor(gentle, d, 64)); }
+        if (lane == 0) { sd[wave] = steep; s_lam[wave] = gentle; }
+        uint32_t cheapest;
+        (void)block_exclusive_scan<uint32_t>(tid < L ? cost_at(my_off) : 0u, su, &cheapest);        // (has barriers)
+        for (uint32_t v = 0; v < NWAVES; ++v) { steep = max_f64(steep, sd[v]); gentle = min_f64(gentle, s_lam[v]); }
+        __syncthreads();
+        if (cheapest > cap) { whole_rows(true); return; }                    // nothing fits
+        const uint32_t room = cap - cheapest;
+        // The smallest multiplier (as a bit pattern: non-negative doubles order like their patterns) at which the
+        // edges steeper than it fit the room.  Sixty-four-way search: the patterns between lo_b (does not fit, or 0)
+        // and lo_b + 2^k are cut into 64 buckets, every edge inside adds its cost step to its bucket in LDS, and
+        // every wave finds for itself the lowest bucket boundary at which what lies above fits: six bits of the
+        // pattern per round and two barriers, down to a gap of 2^27 patterns (2^-25 relative: closer breakpoints
+        // make no difference worth a round).
+        uint32_t above = 0u;                                                 // cost steps of the edges at or beyond lo_b + 2^k
+        uint32_t buf = 0u;
+        for (int k = 63; k > 27; k -= 6) {
+            const int sh = k - 6;                                            // log2 of a bucket's size
+#pragma unroll
+            for (int u = 0; u < (int)BAND_EDGES_PER_THREAD; ++u) {
+                const unsigned long long bits = (unsigned long long)__double_as_longlong(sl[u]);
+                // bucket b holds the patterns in (lo_b + b 2^sh, lo_b + (b + 1) 2^sh]
+                if (dw[u] && bits > lo_b && ((bits - lo_b - 1ull) >> sh) < 64ull)
+                    atomicAdd(&s_hist[buf][(uint32_t)((bits - lo_b - 1ull) >> sh)], dw[u]);
+            }
+            __syncthreads();
+            const uint32_t mine = s_hist[buf][lane];
+            s_hist[buf ^ 1u][lane] = 0u;                                     // the other table, for the next round
+            const uint32_t inc = wave_scan_add_u32(mine);                    // buckets 0..lane
+            const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+            const uint32_t from_here = tot - inc + mine;                     // buckets lane..63
+            // cost at boundary m (edges strictly above lo_b + m 2^sh) = above + buckets m..63
+            const uint64_t fits = ballot(above + from_here <= room);
+            // boundary 64 always fits (the invariant); the lowest fitting boundary of 0..63, if any
+            const uint32_t m = fits ? (uint32_t)__ffsll((long long)fits) - 1u : 64u;
+            const uint32_t keep = m < 64u ? (uint32_t)__builtin_amdgcn_readlane((int)from_here, (int)min(m, 63u)) : 0u;
+            above += keep;
+            hi_b = lo_b + ((unsigned long long)m << sh);
+            if (m > 0u) lo_b += (unsigned long long)(m - 1u) << sh;          // boundary m - 1 does not fit
+            __syncthreads();
+            buf ^= 1u;
+            if (m == 0u) {
+                // boundary 0 itself fits: either everything fits (lo_b = 0: the multiplier is 0) or the gap has
+                // closed onto a pattern that does not fit and its successor that does
+                break;
+            }
+            // the next round looks inside (boundary m - 1, boundary m], a range of 2^sh patterns
+        }
+        // (a first round that finds even its last boundary too low ends beyond the finite patterns: the steepest
+        // slope itself always fits, nothing being steeper)
+        hi_b = min(hi_b, (unsigned long long)__double_as_longlong(steep));
+    }
+    // (a little above, so that an edge as steep as the multiplier is not taken by the rounding of vertex_at's product)
+    const double lam_star = __longlong_as_double((long long)hi_b) * (1.0 + 1e-12);
+
+    // ---- 3: a feasible assignment and its total
+    if (tid < L) s_q[tid] = (uint16_t)vertex_at(tid, lam_star);
+    uint32_t used;
+    (void)block_exclusive_scan<uint32_t>(tid < L ? cost_at(my_off + s_q[tid]) : 0u, su, &used);      // (its own s_q: no barrier needed before)
+    if (used > cap) { whole_rows(false); return; }                            // (cannot happen; a bound that is no bound must not be used)
+    if (wave == 0u) {
+        const uint32_t taken = L <= 256u ? greedy_fill<4>(HE, HW, s_off, s_q, L, cap - used) : greedy_fill<0>(HE, HW, s_off, s_q, L, cap - used);
+        if (lane == 0) s_upgrades = taken;
+    }
+    __syncthreads();
+    double ub, abs_tot;
+    (void)block_exclusive_scan<double>(tid < L ? HE[my_off + s_q[tid]] : 0.0, sd, &ub);
+    (void)block_exclusive_scan<double>(my_abs, sd, &abs_tot);
+    {
+        const uint32_t w_mine = tid < L ? cost_at(my_off + s_q[tid]) : 0u;
+        const uint32_t before = block_exclusive_scan<uint32_t>(w_mine, su, nullptr);
+        if (tid < L) s_cum[tid + 1u] = (uint16_t)(before + w_mine);
+        if (tid == 0) s_cum[0] = 0u;
+    }
+    const double ub_m = ub + 1e-9 * (fabs(ub) + abs_tot);
+    if (!(ub_m - ub_m == 0.0) || !(gentle <= 1e300)) {                        // sums beyond the doubles, or one vertex per layer
+        if (!(ub_m - ub_m == 0.0)) { whole_rows(false); return; }
+        gentle = 0.0;
+    }
+
+    // ---- 4: multipliers around lam_star (around the least steep slope if everything fits); per (layer, multiplier) the
+    // minimum, summed over the layers
+    if (tid < BAND_NLAM) {
+        const double base = lam_star > 0.0 ? lam_star : gentle;
+        double f = 1.0;
+        const int p = (int)tid - (int)(BAND_NLAM / 2u);
+        for (int q = 0; q < (p < 0 ? -p : p); ++q) f *= 1.15;
+        s_lam[tid] = p < 0 ? base / f : base * f;
+    }
+    __syncthreads();
+    const uint32_t m_mine = tid % BAND_NLAM, g_mine = tid / BAND_NLAM, per_group = (L + BAND_GROUPS - 1u) / BAND_GROUPS;
+    {
+        const double lam = s_lam[m_mine];
+        double run = 0.0;
+        const uint32_t i1 = min(L, (g_mine + 1u) * per_group);
+        for (uint32_t i = g_mine * per_group; i < i1; ++i) {
+            const uint32_t o = s_off[i] + vertex_at(i, lam);
+            run += HE[o] + lam * (double)cost_at(o);
+            bb.table[(size_t)(i + 1u) * BAND_NLAM + m_mine] = run;
+        }
+        s_gt[tid] = run;
+    }
+    __syncthreads();
+    {
+        double before = 0.0;
+        for (uint32_t g = 0; g < g_mine; ++g) before += s_gt[g * BAND_NLAM + m_mine];
+        const double mine = s_gt[tid];
+        __syncthreads();
+        s_gt[tid] = before;
+        if (g_mine == BAND_GROUPS - 1u) s_btot[m_mine] = before + mine;
+    }
+    __syncthreads();
+
+    // ---- 5: the band of every row: four threads an edge, eight multipliers each, towards cell 0 and towards the last
+    for (uint32_t x0 = 0u; x0 < 2u * L; x0 += BOUNDS_THREADS / 4u) {
+        constexpr int T = 4, PT = (int)BAND_NLAM / T;
+        const uint32_t x = x0 + tid / T, part = tid % T, side = x & 1u;
+        const bool mine = x < 2u * L;
+        const uint32_t r = mine ? (x >> 1) + 1u : L;                          // (lanes past the last row repeat it: a group's lanes stay together)
         double a[PT], lm[PT], bt[PT];
 #pragma unroll
         for (int u = 0; u < PT; ++u) {
             const uint32_t m = part + (uint32_t)u * T;
-            a[u] = AT[(size_t)rr * pitch + m]; lm[u] = s_lam[m]; bt[u] = s_btot[m] - a[u];
+            a[u] = bb.table[(size_t)r * BAND_NLAM + m] + s_gt[(r - 1u) / per_group * BAND_NLAM + m];
+            lm[u] = s_lam[m]; bt[u] = s_btot[m] - a[u];
         }
         auto within = [&](uint32_t c) {
             const double cd = (double)c, rd = (double)(cap - c);
@@ -102,641 +380,335 @@ __device__ __forceinline__ uint32_t band_rows(const double* AT, uint32_t pitch, 
             }
             return group_max<T>(pre) + group_max<T>(suf) <= ub_m;
         };
-        // One search per edge: towards cell 0, then towards the last cell.  Steps of 8, 32, 128, ... away from the
-        // assignment's own cell until a probe falls outside (or the row's end is inside), then bisection between
-        // the last cell inside and the first outside.
-        const uint32_t on_path = s_cum[rr];
-        uint32_t edge[2];
-#pragma unroll 1
-        for (int side = 0; side < 2; ++side) {
-            const uint32_t room = side ? cap - on_path : on_path;  // cells between the path and the row's end
-            uint32_t in = 0u, out = room + 1u;                      // distances from the path: `in` inside, `out` outside (room + 1: beyond the row)
-            uint32_t stepd = 8u;
-            while (out - in > 1u) {
-                uint32_t probe;
-                if (out == room + 1u) { probe = min(in + stepd, room); stepd *= 4u; }
-                else probe = in + (out - in) / 2u;
-                const uint32_t c = side ? on_path + probe : on_path - probe;
-                if (within(c)) { in = probe; if (probe == room) break; }
-                else out = probe;
-            }
-            edge[side] = side ? on_path + in : on_path - in;
+        // Steps of 8, 32, 128, ... away from the assignment's own cell until a probe falls outside (or the row's end is
+        // inside), then bisection between the last cell inside and the first outside.
+        const uint32_t on_path = s_cum[r];
+        const uint32_t room = side ? cap - on_path : on_path;                // cells between the path and the row's end
+        uint32_t in = 0u, out = room + 1u, stepd = 8u;                       // distances from the path: `in` inside, `out` outside (room + 1: beyond the row)
+        while (out - in > 1u) {
+            uint32_t probe;
+            if (out == room + 1u) { probe = min(in + stepd, room); stepd *= 4u; }
+            else probe = in + (out - in) / 2u;
+            if (within(side ? on_path + probe : on_path - probe)) { in = probe; if (probe == room) break; }
+            else out = probe;
         }
-        if (live_row && part == 0u) {
-            bb.lo[r] = edge[0]; bb.hi[r] = edge[1];
-            s_blo[r] = (uint16_t)edge[0]; s_bhi[r] = (uint16_t)edge[1];
-            width += edge[1] - edge[0] + 1u;
+        if (mine && part == 0u) {
+            const uint32_t edge = side ? on_path + in : on_path - in;
+            if (side) { bb.hi[r] = edge; s_bhi[r] = (uint16_t)edge; } else { bb.lo[r] = edge; s_blo[r] = (uint16_t)edge; }
         }
-    }
-    return width;
-}
-
-// Bounds kernel: one workgroup of sixteen waves.
-//   1  the lists go to LDS; per layer (one thread each) the lower convex hull of its (cost, error) points is
-//      built in place: only hull vertices can minimise E + lambda w, and along the hull the slopes
-//      (error saved per unit of cost) fall, so a layer's minimiser for a given lambda is found by bisection.
-//      (A vertex dropped or kept by a rounding of the hull test changes such a minimum by rounding only, far
-//      inside the margin below.)
-//   2  the smallest lambda whose minimisers fit the capacity: the total cost at lambda is that of the cheapest
-//      vertices plus the cost steps of all hull edges steeper than lambda; every thread keeps a few edges in
-//      registers and the bit pattern of lambda (ordered like the doubles) is bisected;
-//   3  upper bound: that assignment, then up to BAND_GREEDY single steps to a next hull vertex, steepest edge
-//      that still fits first;
-//   4  the table A[r][m] = sum over layers before r of the minimum at lambda_m, in LDS over the hulls;
-//   5  the band of every row by a search outward from the assignment's own cell;
-//   6  the live records of every layer, written out for the recurrence.
-__global__ __launch_bounds__(BOUNDS_THREADS) void k_dp_bounds(AllocBuffers ab, DpLists dl, BandBuffers bb) {
-    constexpr uint32_t NWAVES = BOUNDS_THREADS / 64;
-    __shared__ __align__(16) unsigned char pool[BAND_LCAP * 18];        // 126 KB: hulls (HE, HS, HW), later the table A
-    __shared__ uint16_t raw_w[BAND_LCAP];                               // 14 KB: the lists' costs as they came
-    __shared__ uint16_t s_n[BAND_MAX_L], s_off[BAND_MAX_L], s_hn[BAND_MAX_L], s_q[BAND_MAX_L];
-    __shared__ uint16_t s_cum[BAND_MAX_L + 2], s_blo[BAND_MAX_L + 2], s_bhi[BAND_MAX_L + 2];
-    __shared__ uint32_t su[16];
-    __shared__ double sd[16];
-    __shared__ double s_lam[BAND_NLAM], s_btot[BAND_NLAM];
-    __shared__ unsigned long long s_key[2];
-    __shared__ uint32_t s_hist[2][64], s_dw[2];
-    __shared__ uint32_t s_flag, s_wmax;
-    double* const HE = reinterpret_cast<double*>(pool);                 // vertex errors
-    double* const HS = HE + BAND_LCAP;                                  // slope of the edge to the next vertex; 0 where there is none
-    uint16_t* const HW = reinterpret_cast<uint16_t*>(HS + BAND_LCAP);   // vertex costs (rows that fit LDS: below 65536)
-    double* const AT = reinterpret_cast<double*>(pool);                 // [(L + 1)][nl + 1], once the hulls are done with
-    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t L = ab.L, J = ab.J, cap = ab.cap;
-#ifdef KIMAD_STAMPS
-    unsigned long long stamp[10]; int ns = 0;
-#define STAMP() do { stamp[ns++] = __builtin_readcyclecounter(); } while (0)
-#else
-#define STAMP() do {} while (0)
-#endif
-    STAMP();
-
-    // ---- 1: sizes, offsets, lists into LDS
-    const uint32_t my_n = tid < L ? min(dl.n[tid], 64u) : 0u;
-    const uint32_t my_bad = tid < L ? (dl.bad[tid] | (my_n == 0u ? 1u : 0u)) : 0u;    // or a layer with no affordable candidate
-    uint32_t n_tot;
-    const uint32_t my_off = block_exclusive_scan<uint32_t>(my_n, su, &n_tot);
-    if (tid == 0) { s_flag = 0u; s_key[0] = 0ull; s_key[1] = 0ull; s_wmax = 0u; }
-    if (tid < 128u) s_hist[tid >> 6][tid & 63u] = 0u;
-    __syncthreads();
-    if (my_bad) s_flag = 1u;
-    bool whole = n_tot > BAND_LCAP;
-    if (tid < L && !whole) { s_n[tid] = (uint16_t)my_n; s_off[tid] = (uint16_t)my_off; }
-    __syncthreads();
-    whole = whole || s_flag != 0u;
-    if (!whole) {
-        for (uint32_t x = tid; x < BAND_LCAP; x += BOUNDS_THREADS) HS[x] = 0.0;
-        // four layers' loads in flight per wave
-        for (uint32_t i0 = wave * 4u; i0 < L; i0 += NWAVES * 4u) {
-            double e[4];
-            uint32_t w[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t i = i0 + (uint32_t)u;
-                const bool in = i < L && lane < s_n[min(i, L - 1u)];
-                const size_t o = in ? (size_t)i * J + lane : 0;
-                e[u] = dl.e[2 * o]; w[u] = dl.w[o];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t i = i0 + (uint32_t)u;
-                if (i < L && lane < s_n[i]) { HE[s_off[i] + lane] = e[u]; HW[s_off[i] + lane] = (uint16_t)w[u]; raw_w[s_off[i] + lane] = (uint16_t)w[u]; }
-            }
-        }
-    }
-    __syncthreads();
-    STAMP();
-    // lower hull, in place, one thread per layer (the vertex count never exceeds the entries read); entries are
-    // read four at a time
-    double my_first_abs = 0.0;
-    if (!whole && tid < L) {
-        const uint32_t o = my_off;
-        uint32_t hn = 0u;
-        double te = 0.0, pe = 0.0;                       // top vertex and the one below it
-        uint32_t tw = 0u, pw = 0u;
-        for (uint32_t k0 = 0; k0 < my_n; k0 += 4u) {
-            double e4[4];
-            uint32_t w4[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { const uint32_t k = min(k0 + (uint32_t)u, my_n - 1u); e4[u] = HE[o + k]; w4[u] = HW[o + k]; }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (k0 + (uint32_t)u >= my_n) break;
-                const double e = e4[u];
-                const uint32_t w = w4[u];
-                if (hn == 0u) { HE[o] = e; HW[o] = (uint16_t)w; hn = 1u; te = e; tw = w; my_first_abs = fabs(e); continue; }
-                if (!(e < te)) continue;                      // costs no less, saves nothing: never a minimiser
-                if (w == tw) { --hn; if (hn) { te = pe; tw = pw; if (hn >= 2u) { pe = HE[o + hn - 2u]; pw = HW[o + hn - 2u]; } } }
-                // pop while the slope into the top is not above the slope out of it: (pe - te)(w - tw) <= (te - e)(tw - pw)
-                while (hn >= 2u && (pe - te) * (double)(w - tw) <= (te - e) * (double)(tw - pw)) {
-                    --hn; te = pe; tw = pw;
-                    if (hn >= 2u) { pe = HE[o + hn - 2u]; pw = HW[o + hn - 2u]; }
-                }
-                if (hn == 0u) my_first_abs = fmax(my_first_abs, fabs(e));
-                HE[o + hn] = e; HW[o + hn] = (uint16_t)w;
-                pe = te; pw = tw; te = e; tw = w; ++hn;
-            }
-        }
-        s_hn[tid] = (uint16_t)hn;
-        my_first_abs = fmax(my_first_abs, fabs(te));
-    }
-    __syncthreads();
-    if (!whole) {
-        for (uint32_t i = wave; i < L; i += NWAVES) {
-            const uint32_t hn = s_hn[i], o = s_off[i];
-            if (lane + 1u < hn)
-                HS[o + lane] = (HE[o + lane] - HE[o + lane + 1u]) / (double)((uint32_t)HW[o + lane + 1u] - (uint32_t)HW[o + lane]);
-        }
-    }
-    __syncthreads();
-    STAMP();
-    // the vertex of layer i that minimises E + lam w: the number of its edges steeper than lam
-    auto vertex_at = [&](uint32_t i, double lam) {
-        const uint32_t o = s_off[i];
-        uint32_t lo = 0u, hi = (uint32_t)s_hn[i] - 1u;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (HS[o + mid] > lam) lo = mid + 1u; else hi = mid;
-        }
-        return lo;
-    };
-
-    // ---- 2: the smallest multiplier that fits.  This thread's edges (slope, cost step) stay in registers.
-    unsigned long long lo_b = 0ull, hi_b = 0ull;
-    uint32_t room = 0u;
-    if (!whole) {
-        double sl[BAND_EDGES_PER_THREAD];
-        uint32_t dw[BAND_EDGES_PER_THREAD];
-        double steep = 0.0;
-#pragma unroll
-        for (int u = 0; u < (int)BAND_EDGES_PER_THREAD; ++u) {
-            const uint32_t x = tid + (uint32_t)u * BOUNDS_THREADS;
-            sl[u] = HS[x];
-            dw[u] = sl[u] > 0.0 ? (uint32_t)HW[x + 1u] - (uint32_t)HW[x] : 0u;     // (HS is 0 wherever x + 1 is not on the same hull)
-            steep = max_f64(steep, sl[u]);
-        }
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) steep = max_f64(steep, __shfl_xor(steep, d, 64));
-        if (lane == 0) sd[wave] = steep;
-        uint32_t cheapest;
-        (void)block_exclusive_scan<uint32_t>(tid < L ? (uint32_t)HW[my_off] : 0u, su, &cheapest);   // (has barriers)
-        for (uint32_t v = 0; v < NWAVES; ++v) steep = max_f64(steep, sd[v]);
-        __syncthreads();
-        if (cheapest > cap) whole = true;                                   // nothing fits: the recurrence will say so
-        else room = cap - cheapest;
-        // The smallest multiplier (as a bit pattern: non-negative doubles order like their patterns) at which the
-        // edges steeper than it fit the room.  Sixty-four-way search: the patterns between lo_b (does not fit, or 0)
-        // and lo_b + 2^k are cut into 64 buckets, every edge inside adds its cost step to its bucket in LDS, and
-        // every wave finds for itself the lowest bucket boundary at which what lies above fits: six bits of the
-        // pattern per round and two barriers, down to a gap of 2^15 patterns (2^-37 relative: closer breakpoints
-        // make no difference worth a round).
-        if (!whole) {
-            uint32_t above = 0u;                                             // cost steps of the edges at or beyond lo_b + 2^k
-            uint32_t buf = 0u;
-            for (int k = 63; k > 15; k -= 6) {
-                const int sh = k - 6;                                        // log2 of a bucket's size
-#pragma unroll
-                for (int u = 0; u < (int)BAND_EDGES_PER_THREAD; ++u) {
-                    const unsigned long long bits = (unsigned long long)__double_as_longlong(sl[u]);
-                    // bucket b holds the patterns in (lo_b + b 2^sh, lo_b + (b + 1) 2^sh]
-                    if (dw[u] && bits > lo_b && ((bits - lo_b - 1ull) >> sh) < 64ull)
-                        atomicAdd(&s_hist[buf][(uint32_t)((bits - lo_b - 1ull) >> sh)], dw[u]);
-                }
-                __syncthreads();
-                const uint32_t mine = s_hist[buf][lane];
-                s_hist[buf ^ 1u][lane] = 0u;                                 // the other table, for the next round
-                const uint32_t inc = wave_scan_add_u32(mine);                // buckets 0..lane
-                const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-                const uint32_t from_here = tot - inc + mine;                 // buckets lane..63
-                // cost at boundary m (edges strictly above lo_b + m 2^sh) = above + buckets m..63
-                const uint64_t fits = ballot(above + from_here <= room);
-                // boundary 64 always fits (the invariant); the lowest fitting boundary of 0..63, if any
-                const uint32_t m = fits ? (uint32_t)__ffsll((long long)fits) - 1u : 64u;
-                const uint32_t keep = m < 64u ? (uint32_t)__builtin_amdgcn_readlane((int)from_here, (int)min(m, 63u)) : 0u;
-                above += keep;
-                hi_b = lo_b + ((unsigned long long)m << sh);
-                if (m > 0u) lo_b += (unsigned long long)(m - 1u) << sh;      // boundary m - 1 does not fit
-                __syncthreads();
-                buf ^= 1u;
-                if (m == 0u) {
-                    // boundary 0 itself fits: either everything fits (lo_b = 0: the multiplier is 0) or the gap has
-                    // closed onto a pattern that does not fit and its successor that does
-                    break;
-                }
-                // the next round looks inside (boundary m - 1, boundary m], a range of 2^sh patterns
-            }
-            // (a first round that finds even its last boundary too low ends beyond the finite patterns: the steepest
-            // slope itself always fits, nothing being steeper)
-            hi_b = min(hi_b, (unsigned long long)__double_as_longlong(steep));
-        }
-    }
-    if (whole) {
-        // no bound to use: whole rows, every record live (the lists copied as they are)
-        for (uint32_t r = tid; r <= L; r += BOUNDS_THREADS) { bb.lo[r] = 0u; bb.hi[r] = r ? cap : 0u; }
-        if (tid < L) bb.live_off[tid] = my_off;
-        if (tid == 0) bb.live_off[L] = n_tot;
-        if (tid < L) {
-            for (uint32_t k = 0; k < my_n; ++k) {
-                const size_t o = (size_t)tid * J + k, t = my_off + k;
-                bb.live_e[t] = dl.e[2 * o]; bb.live_before[t] = dl.e[2 * o + 1];
-                bb.live_w[t] = dl.w[o]; bb.live_jj[t] = dl.jj[o];
-            }
-        }
-        if (tid == 0) { bb.info[0] = cap + 1u; bb.info[1] = L * (cap + 1u); bb.info[2] = 1u; bb.info[3] = 0u; }
-        return;
-    }
-    const double lam_star = __longlong_as_double((long long)hi_b);
-    STAMP();
-
-    // ---- 3: a feasible assignment and its total; the greedy fill names the layer to step through one LDS maximum:
-    // the slope's bit pattern with the low 10 bits replaced by 1023 - layer
-    if (tid < L) s_q[tid] = (uint16_t)vertex_at(tid, lam_star);
-    __syncthreads();
-    uint32_t used;
-    (void)block_exclusive_scan<uint32_t>(tid < L ? (uint32_t)HW[my_off + s_q[tid]] : 0u, su, &used);
-    uint32_t left = cap - used;                                             // used <= cap: lam_star fits
-    uint32_t upgrades = 0u;
-    // A round: every layer whose next hull edge fits what is left bids with its slope; the steepest wins (lowest
-    // layer among equals), its owner takes the step and says what it cost.  The bids of consecutive rounds go to two
-    // words in turn, so a round needs two barriers.
-    for (uint32_t round = 0; round < BAND_GREEDY && left > 0u; ++round) {
-        const uint32_t buf = round & 1u;
-        if (tid < L) {
-            const uint32_t q = s_q[tid];
-            if (q + 1u < s_hn[tid] && (uint32_t)HW[my_off + q + 1u] - (uint32_t)HW[my_off + q] <= left) {
-                const unsigned long long key = ((unsigned long long)__double_as_longlong(HS[my_off + q]) & ~0x3FFull) | (1023u - tid);
-                atomicMax(&s_key[buf], key);
-            }
-        }
-        __syncthreads();
-        const unsigned long long best = s_key[buf];
-        if (best == 0ull) break;                                             // (the same word in every thread)
-        if (tid == 1023u - (uint32_t)(best & 0x3FFull)) {
-            const uint32_t q = s_q[tid];
-            s_dw[buf] = (uint32_t)HW[my_off + q + 1u] - (uint32_t)HW[my_off + q];
-            s_q[tid] = (uint16_t)(q + 1u);
-            s_key[buf ^ 1u] = 0ull;                                          // the next round's word: last read before the previous round's second barrier
-        }
-        __syncthreads();
-        left -= s_dw[buf];
-        ++upgrades;
-    }
-    __syncthreads();
-    double ub, abs_tot;
-    (void)block_exclusive_scan<double>(tid < L ? HE[my_off + s_q[tid]] : 0.0, sd, &ub);
-    (void)block_exclusive_scan<double>(my_first_abs, sd, &abs_tot);        // sum over layers of the largest |error| on the hull
-    {
-        const uint32_t w_mine = tid < L ? (uint32_t)HW[my_off + s_q[tid]] : 0u;
-        const uint32_t before = block_exclusive_scan<uint32_t>(w_mine, su, nullptr);
-        if (tid < L) s_cum[tid + 1u] = (uint16_t)(before + w_mine);
-        if (tid == 0) s_cum[0] = 0u;
-    }
-    const double ub_m = ub + 1e-9 * (fabs(ub) + abs_tot);
-    STAMP();
-
-    // ---- 4: multipliers around lam_star; per (layer, multiplier) the minimum, then prefix sums over the layers
-    const uint32_t nl = L <= BAND_L_FOR_32 ? BAND_NLAM : BAND_NLAM_MANY, pitch = nl + 1u;
-    if (tid < nl) {
-        // (lam_star may be 0 when everything fits: the set then collapses and the bands stay wide)
-        double f = 1.0;
-        const int p = (int)tid - (int)(nl / 2u);
-        for (int q = 0; q < (p < 0 ? -p : p); ++q) f *= 1.15;
-        s_lam[tid] = p < 0 ? lam_star / f : lam_star * f;
-    }
-    __syncthreads();
-    constexpr int PER_THREAD = (BAND_L_FOR_32 * BAND_NLAM + BOUNDS_THREADS - 1) / BOUNDS_THREADS;   // 13 (and 1024 * 8 / 1024 = 8)
-    double val[PER_THREAD];
-#pragma unroll
-    for (int u = 0; u < PER_THREAD; ++u) {
-        const uint32_t x = tid + (uint32_t)u * BOUNDS_THREADS;
-        val[u] = 0.0;
-        if (x < L * nl) {
-            const uint32_t i = x / nl, m = x % nl;
-            const double lam = s_lam[m];
-            const uint32_t o = s_off[i] + vertex_at(i, lam);
-            val[u] = HE[o] + lam * (double)HW[o];
-        }
-    }
-    __syncthreads();                                     // the hulls are done with: the pool becomes the table
-#pragma unroll
-    for (int u = 0; u < PER_THREAD; ++u) {
-        const uint32_t x = tid + (uint32_t)u * BOUNDS_THREADS;
-        if (x < L * nl) AT[(size_t)(x / nl + 1u) * pitch + x % nl] = val[u];
-    }
-    if (tid < nl) AT[tid] = 0.0;
-    __syncthreads();
-    if (tid < nl) {
-        // one thread per multiplier runs down its column (rows are read eight ahead)
-        double run = 0.0;
-        uint32_t r = 1u;
-        for (; r + 8u <= L + 1u; r += 8u) {
-            double v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = AT[(size_t)(r + (uint32_t)u) * pitch + tid];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) { run += v[u]; AT[(size_t)(r + (uint32_t)u) * pitch + tid] = run; }
-        }
-        for (; r <= L; ++r) { run += AT[(size_t)r * pitch + tid]; AT[(size_t)r * pitch + tid] = run; }
-        s_btot[tid] = run;
-    }
-    __syncthreads();
-    STAMP();
-
-    // ---- 5: the band of every row
-    uint32_t width;
-    if (nl == BAND_NLAM) {
-        if (L <= 128u) width = band_rows<8, 4>(AT, pitch, s_lam, s_btot, s_cum, s_blo, s_bhi, bb, L, cap, ub_m);
-        else width = band_rows<4, 8>(AT, pitch, s_lam, s_btot, s_cum, s_blo, s_bhi, bb, L, cap, ub_m);
-    } else {
-        width = band_rows<1, BAND_NLAM_MANY>(AT, pitch, s_lam, s_btot, s_cum, s_blo, s_bhi, bb, L, cap, ub_m);
     }
     if (tid == 0) { bb.lo[0] = 0u; bb.hi[0] = 0u; s_blo[0] = 0u; s_bhi[0] = 0u; }
     __syncthreads();
-    STAMP();
 
     // ---- 6: the records that can connect the bands of rows i and i + 1: a cell of each differ by a cost in
     // [lo' - hi, hi' - lo]; costs ascend along a list, so they are a run of it
-    uint32_t kf = 0u, cnt = 0u;
-    if (tid < L) {
-        const uint32_t plo = s_blo[tid], phi = s_bhi[tid], clo = s_blo[tid + 1u], chi = s_bhi[tid + 1u];
-        if (chi >= plo) {
-            const uint32_t w_min = clo > phi ? clo - phi : 0u, w_max = chi - plo;
-            uint32_t k = 0u;
-            while (k < my_n && (uint32_t)raw_w[my_off + k] < w_min) ++k;
-            kf = k;
-            while (k < my_n && (uint32_t)raw_w[my_off + k] <= w_max) ++k;
-            cnt = k - kf;
-        }
-    }
-    uint32_t total_live;
-    const uint32_t at = block_exclusive_scan<uint32_t>(cnt, su, &total_live);
-    if (tid < L) { bb.live_off[tid] = at; s_q[tid] = (uint16_t)at; s_hn[tid] = (uint16_t)(kf | (cnt << 8)); }
-    if (tid == 0) bb.live_off[L] = total_live;
-    __syncthreads();
     for (uint32_t i0 = wave * 8u; i0 < L; i0 += NWAVES * 8u) {
-        double e[8], b[8];
-        uint32_t w[8], jj[8], dst[8];
-        bool in[8];
+        uint32_t w[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const uint32_t i = min(i0 + (uint32_t)u, L - 1u);
-            const uint32_t f = (uint32_t)s_hn[i] & 0xFFu, c = (uint32_t)s_hn[i] >> 8;
-            in[u] = i0 + (uint32_t)u < L && lane < c;
-            const size_t o = in[u] ? (size_t)i * J + f + lane : 0;
-            dst[u] = (uint32_t)s_q[i] + lane;
-            e[u] = dl.e[2 * o]; b[u] = dl.e[2 * o + 1]; w[u] = dl.w[o]; jj[u] = dl.jj[o];
+            w[u] = dl.w[(size_t)i * J + min(lane, (uint32_t)s_n[i] - 1u)];   // (every list has an entry)
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (in[u]) { bb.live_e[dst[u]] = e[u]; bb.live_before[dst[u]] = b[u]; bb.live_w[dst[u]] = w[u]; bb.live_jj[dst[u]] = jj[u]; }
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t i = i0 + (uint32_t)u;
+            if (i >= L) break;
+            const uint32_t plo = s_blo[i], phi = s_bhi[i], clo = s_blo[i + 1u], chi = s_bhi[i + 1u];
+            const uint32_t w_min = clo > phi ? clo - phi : 0u;
+            const uint64_t in = ballot(lane < s_n[i] && w[u] >= w_min && w[u] + plo <= chi);
+            if (lane == 0) bb.live[i] = in ? (uint32_t)__builtin_ctzll(in) | ((uint32_t)__popcll(in) << 8) : 0u;
+        }
     }
-    STAMP();
-#ifdef KIMAD_STAMPS
-    if (tid == 0) for (int q = 1; q < ns; ++q) bb.info[4 + q - 1] = (uint32_t)(stamp[q] - stamp[q - 1]);
-#endif
     // diagnostics
+    const uint32_t width = tid < L ? (uint32_t)s_bhi[tid + 1u] - (uint32_t)s_blo[tid + 1u] + 1u : 0u;
     uint32_t wsum;
     (void)block_exclusive_scan<uint32_t>(width, su, &wsum);
-    if (tid >= 1u && tid <= L) atomicMax(&s_wmax, (uint32_t)s_bhi[tid] - (uint32_t)s_blo[tid] + 1u);
+    if (width) atomicMax(&s_wmax, width);
     __syncthreads();
-    if (tid == 0) { bb.info[0] = s_wmax; bb.info[1] = wsum; bb.info[2] = 0u; bb.info[3] = upgrades; }
+    if (tid == 0) { bb.info[0] = s_wmax; bb.info[1] = wsum; bb.info[2] = 0u; bb.info[3] = s_upgrades; bb.info[4] = 0u; }
 }
 
-// The recurrence on the band cells, by one workgroup of sixteen waves.  Both rows sit in LDS, indexed from their
-// band's first cell.  Only the list records that can connect the bands of the two rows are visited (k_dp_bounds
-// wrote them out, layer after layer); they wait in LDS, a group of layers at a time.
+// The recurrence on the band cells, by one workgroup, then the walk back and the outputs.
 //
-// The chain of L layers is sequential and a layer is little work (a hundred-odd cells, a few records each), so a
-// layer is spread over the whole workgroup: a group of NP = 1, 2, 4, 8 or 16 neighbouring lanes shares a cell,
-// lane s of the group takes records s, s + NP, ... in ascending order with a strict "<", and the group's minimum of
-// (total, record) in that order, the total first, is formed with DPP moves (no LDS traffic).  That is the candidate
-// the sequential scan of the whole list with a strict "<" would have kept: the first one, in list order, that attains
-// the minimum.  The group's first lane then takes the lowest member of the winner's run whose rounded total is the
-// same, and stores the cell's value, its winner and the cell it came from.  One barrier per layer.
+// The chain of L layers is sequential and a layer is little work (tens to hundreds of cells, a few records each), so what
+// counts is the length of one layer's dependent steps: a barrier, one LDS read of the previous row, an addition and a
+// minimum.  The layer loop therefore computes values only, in LDS, indexed from the band's first cell: a group of NP
+// neighbouring lanes shares a cell, its lanes take records s, s + NP, ... four at a time and form the minimum with DPP
+// moves; which record attained it is asked along the optimal path alone, afterwards.  Only the records that can connect
+// the bands are visited; they wait in LDS, a group of layers at a time.
 //
-// When the bands are narrow enough the winners stay in LDS (a global store inside the loop would be waited for
-// before the registers it used can be written again); otherwise they go to the tables in memory, as in the
-// whole-row recurrence.  The least total of the last row at its smallest cost, the walk back through the winners
-// and the outputs j, K and offsets follow in the same launch.
-constexpr uint32_t BANDED_THREADS = 1024;
-static_assert(BANDED_THREADS >= BAND_MAX_L, "the set-up and the outputs give a thread to every layer");
+// All rows stay in LDS if they fit (BAND_CELLS), else two of them do and every row is also written to memory, from where
+// the walk stages them again, as many layers at a time as fit.
+//
+// The walk: at a layer and cell, lane k tests record k: the first, in list order, whose total equals the cell's value
+// is the one the sequential scan with a strict "<" would have kept.  One wave, two LDS reads deep per layer.  The lowest
+// member of a winner's run with the same rounded total, sizes and offsets follow for all layers in parallel.
+//
+// A layer costs what its instructions take to issue (a wave issues one every 8 to 10 cycles whatever it waits for) and the
+// barrier: about 0.85 us with the walk, however few cells there are.  Four waves serve bands of up to some two hundred
+// cells best, sixteen the wide ones: 134 against 176 us at a mean width of 74 cells (148 layers, rows of 4097 cells), 233
+// against 230 at 187.  One loop that also kept winner and source cell of every cell, by sixteen waves, took 176 us there.
+constexpr uint32_t BANDED_NARROW = 256, BANDED_WIDE = 1024;   // threads, for narrow and for wide bands
+constexpr uint32_t BANDED_MEAN = 128;           // mean width of a row up to which the bands are narrow
 constexpr uint32_t BAND_LIVE_CAP = 2048;       // live records held in LDS at a time
-constexpr uint32_t BANDED_POOL = 140 * 1024;   // bytes of LDS carved at run time: two rows, live records, winners
+constexpr uint32_t BAND_CELLS = 12288;         // row cells held in LDS (96 KB); two of the longest rows fit
+static_assert(2u * DP_PAD_WIDE <= BAND_CELLS, "two rows fit");
 
-// (total, record) of another lane of the group; the smaller pair stays
-template <int CTRL>
-__device__ __forceinline__ void take_min_dpp(double& t, uint32_t& k) {
-    const double ot = dpp_f64<CTRL>(t);
-    const uint32_t ok = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, CTRL, 0xF, 0xF, false);
-    if (ot < t || (ot == t && ok < k)) { t = ot; k = ok; }
-}
-template <int NP>
-__device__ __forceinline__ void group_min_pair(double& t, uint32_t& k) {
-    if (NP >= 2) take_min_dpp<0xB1>(t, k);       // quad_perm [1,0,3,2]
-    if (NP >= 4) take_min_dpp<0x4E>(t, k);       // quad_perm [2,3,0,1]
-    if (NP >= 8) take_min_dpp<0x141>(t, k);      // row_half_mirror: the other quad of the eight
-    if (NP >= 16) take_min_dpp<0x140>(t, k);     // row_mirror: the other eight of the sixteen
+// Rows and layers as the recurrence sees them: first cell, last cell - first cell, first of the row's cells among all
+// rows' cells, first of layer r's live records among all layers'.
+struct BandRow { uint32_t lo, span, at, rec; };
+__device__ __forceinline__ BandRow band_row(const uint4& v) {
+    BandRow b;
+    b.lo = __builtin_amdgcn_readfirstlane(v.x); b.span = __builtin_amdgcn_readfirstlane(v.y);
+    b.at = __builtin_amdgcn_readfirstlane(v.z); b.rec = __builtin_amdgcn_readfirstlane(v.w);
+    return b;
 }
 
-struct BandedLds {
-    double* row0; double* row1;
-    double* l_e; double* l_before; uint32_t* l_w; uint32_t* l_jj;
-    uint32_t* out_w;
-    uint32_t live_cap;
-};
-
-// one layer: NP lanes per cell
-template <int NP, bool IN_LDS>
-__device__ __forceinline__ void banded_layer(const AllocBuffers& ab, const BandedLds& z, uint32_t i, uint32_t base, uint32_t n,
-                                             uint32_t plo, uint32_t pspan, uint32_t clo, uint32_t chi, uint32_t wc) {
-    const uint32_t tid = threadIdx.x, sub = tid % NP, J = ab.J;
-    const double* prow = (i & 1u) ? z.row1 : z.row0;
-    double* crow = (i & 1u) ? z.row0 : z.row1;
-    for (uint32_t c0 = clo; c0 <= chi; c0 += BANDED_THREADS / NP) {
-        const uint32_t c = c0 + tid / NP, cm = c - plo;
+// One layer: NP lanes per cell.  lrec, n: the layer's records; prow, crow: where the previous row and this one start in
+// `rows`, whose cell BAND_CELLS holds +inf; out: the row's copy in memory, or null.
+template <int NP, uint32_t T>
+__device__ __forceinline__ void banded_layer(const uint4* lrec, double* rows, uint32_t prow, uint32_t crow, double* out, uint32_t n,
+                                             const BandRow& p, const BandRow& c) {
+    const uint32_t tid = threadIdx.x, sub = tid % NP, shift = c.lo - p.lo;      // (may wrap: so does the source below, beyond the span)
+    for (uint32_t c0 = 0; c0 <= c.span; c0 += T / NP) {
+        const uint32_t cell = c0 + tid / NP, cm = cell + shift;
         double best = DP_INF;
-        uint32_t bk = 0xFFu;
-        if (c <= chi) {
-            for (uint32_t k = sub; k < n; k += NP) {
-                const uint32_t src = cm - z.l_w[base + k];      // a cell cheaper than the record wraps far beyond the span
-                if (src <= pspan) {
-                    const double t = prow[src] + z.l_e[base + k];
-                    if (t < best) { best = t; bk = k; }
-                }
+        for (uint32_t k = sub; k < n; k += 4u * NP) {
+            // four records, then four cells: two LDS round trips, not eight (left to itself the compiler waits for each)
+            uint4 r[4];
+            double v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) r[u] = lrec[min(k + (uint32_t)u * NP, n - 1u)];   // (positions past the last record repeat it, which changes no minimum)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { materialise(r[u].x); materialise(r[u].y); materialise(r[u].z); }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t src = cm - r[u].z;                               // a cell cheaper than the record wraps far beyond the span
+                v[u] = rows[src <= p.span ? prow + src : BAND_CELLS];
             }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) asm volatile("" ::"v"(v[u]));
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] += rec_err(r[u]);
+            best = min_f64(min_f64(best, v[0]), min_f64(v[1], min_f64(v[2], v[3])));
         }
-        group_min_pair<NP>(best, bk);
-        if (sub == 0u && c <= chi) {
-            uint32_t bj = 0xFFu, from = 0xFFFFu;
-            if (bk != 0xFFu) {
-                const uint32_t wj = z.l_jj[base + bk];
-                from = c - z.l_w[base + bk];
-                const double bp = prow[from - plo];
-                bj = wj >> 8;
-                if (bp + z.l_before[base + bk] == best) {
-                    const uint32_t jlo = wj & 0xFFu;
-                    uint32_t j = bj - 1u;
-                    while (j > jlo && bp + ab.E[(size_t)i * J + j - 1u] == best) --j;
-                    bj = j;
-                }
-            }
-            crow[c - clo] = best;
-            if (IN_LDS) {
-                z.out_w[wc + (c - clo)] = bj | (from << 16);
-            } else {
-                ab.choice[(size_t)i * ab.stride + c] = (uint8_t)bj;
-                ab.cprev[(size_t)i * ab.stride + c] = (uint16_t)from;
-            }
+        best = group_min<NP>(best);
+        if (sub == 0u && cell <= c.span) {
+            rows[crow + cell] = best;
+            if (out) out[cell] = best;
         }
     }
 }
 
-template <bool IN_LDS>
-__device__ __forceinline__ void banded_layers(const AllocBuffers& ab, const BandBuffers& bb, const BandedLds& z,
-                                              const uint32_t* s_lo, const uint32_t* s_hi, const uint32_t* s_off,
-                                              const uint32_t* s_wcum) {
-    const uint32_t tid = threadIdx.x;
-    const uint32_t L = ab.L;
-    uint32_t i = 0;
-    while (i < L) {
-        // a group of layers whose live records fit LDS (at least one layer: a list has at most 64 records)
-        const uint32_t g0 = s_off[i];
-        uint32_t i1 = i + 1u;
-        while (i1 < L && s_off[i1 + 1u] - g0 <= z.live_cap) ++i1;
-        const uint32_t gcount = min(s_off[i1] - g0, z.live_cap);
-        for (uint32_t t = tid; t < gcount; t += BANDED_THREADS) {
-            z.l_e[t] = bb.live_e[g0 + t]; z.l_before[t] = bb.live_before[g0 + t];
-            z.l_w[t] = bb.live_w[g0 + t]; z.l_jj[t] = bb.live_jj[g0 + t];
-        }
-        lds_barrier();
-        for (; i < i1; ++i) {
-            const uint32_t base = s_off[i] - g0, n = s_off[i + 1u] - s_off[i];
-            const uint32_t plo = s_lo[i], pspan = s_hi[i] - plo, clo = s_lo[i + 1u], chi = s_hi[i + 1u], wc = s_wcum[i];
-            // lanes per cell: as many as there are records, up to 16 (all of these are the same in every lane)
-            if (n <= 1u) banded_layer<1, IN_LDS>(ab, z, i, base, n, plo, pspan, clo, chi, wc);
-            else if (n <= 2u) banded_layer<2, IN_LDS>(ab, z, i, base, n, plo, pspan, clo, chi, wc);
-            else if (n <= 4u) banded_layer<4, IN_LDS>(ab, z, i, base, n, plo, pspan, clo, chi, wc);
-            else if (n <= 8u) banded_layer<8, IN_LDS>(ab, z, i, base, n, plo, pspan, clo, chi, wc);
-            else banded_layer<16, IN_LDS>(ab, z, i, base, n, plo, pspan, clo, chi, wc);
-            lds_barrier();                       // the next layer reads this row (and the next group overwrites the records)
-        }
-    }
-}
-
-__global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, BandBuffers bb, const uint32_t* __restrict__ bad,
-                                                              int32_t err_infeasible, int32_t err_nonfinite) {
-    __shared__ __align__(16) unsigned char pool[BANDED_POOL];
-    __shared__ uint32_t s_lo[BAND_MAX_L + 1], s_hi[BAND_MAX_L + 1], s_off[BAND_MAX_L + 1], s_wcum[BAND_MAX_L + 1];
-    __shared__ uint8_t s_j[BAND_MAX_L];
+template <uint32_t T>
+__global__ __launch_bounds__(T) void k_dp_banded(AllocBuffers ab, DpLists dl, BandBuffers bb, double* rows_g,
+                                                              uint32_t rstride, int32_t err_infeasible, int32_t err_nonfinite) {
+    constexpr uint32_t NWAVES = T / 64;
+    __shared__ double rows[BAND_CELLS + 1];               // and one cell of +inf
+    __shared__ uint4 recs[BAND_LIVE_CAP];                 // error bits, cost
+    __shared__ uint4 s_row[BAND_MAX_L + 1];
+    __shared__ double s_val[BAND_MAX_L + 1];              // the path's value per row
+    __shared__ uint8_t s_k[BAND_MAX_L];                   // the path's live record per layer
     __shared__ uint32_t su[16];
     __shared__ unsigned long long su64[16];
-    __shared__ uint32_t s_wmax, s_bad;
-    __shared__ unsigned long long s_best;        // bits of the least total (non-negative doubles order like their bit patterns)
-    __shared__ uint32_t s_bc;
-    const uint32_t tid = threadIdx.x;
+    __shared__ double sd[NWAVES];
+    __shared__ uint32_t sc[NWAVES];
+    __shared__ uint32_t s_bad;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t L = ab.L, J = ab.J, cap = ab.cap;
-#ifdef KIMAD_STAMPS
-    const unsigned long long t_begin = __builtin_readcyclecounter();
-#endif
-    if (tid == 0) { s_wmax = 1u; s_bad = 0u; s_best = ~0ull; s_bc = 0xFFFFFFFFu; }
+    // one of the two launches does the work: the bands' widths, known here only, say which
+    if ((bb.info[1] <= BANDED_MEAN * L) != (T == BANDED_NARROW)) return;
+    if (tid == 0) s_bad = 0u;
     __syncthreads();
-    // bands, live offsets, cumulative widths: rows 0..L (L <= BAND_MAX_L = the workgroup's size; row L by thread 0 again)
-    uint32_t wd = 0u;
-    for (uint32_t r = tid; r <= L; r += BANDED_THREADS) {
-        const uint32_t lo = min(bb.lo[r], cap), hi = max(lo, min(bb.hi[r], cap));
-        s_lo[r] = lo; s_hi[r] = hi; s_off[r] = bb.live_off[r];
+    // rows and records: running sums over the layers
+    uint32_t cells = 0u, live_total = 0u;
+    for (uint32_t r0 = 0u; r0 <= L; r0 += T) {
+        const uint32_t r = r0 + tid;
+        const bool in = r <= L;
+        const uint32_t lo = in ? min(bb.lo[r], cap) : 0u, hi = in ? max(lo, min(bb.hi[r], cap)) : 0u;
+        const uint32_t cnt = r < L ? min(bb.live[r] >> 8, 64u) : 0u;
+        if (r < L && dl.bad[r]) s_bad = 1u;
+        uint32_t ct, lt;
+        const uint32_t at = cells + block_exclusive_scan<uint32_t>(in ? hi - lo + 1u : 0u, su, &ct);
+        const uint32_t rec = live_total + block_exclusive_scan<uint32_t>(cnt, su, &lt);
+        if (in) s_row[r] = make_uint4(lo, hi - lo, at, rec);
+        cells += ct; live_total += lt;
     }
-    if (tid < L && bad[tid]) s_bad = 1u;
     __syncthreads();
-    // s_wcum[i] = first word of layer i's winners = widths of rows 1..i (row 0 stores nothing); thread r - 1 owns row r
-    if (tid < L) wd = s_hi[tid + 1u] - s_lo[tid + 1u] + 1u;
-    if (wd) atomicMax(&s_wmax, wd);
-    uint32_t total_words;
-    const uint32_t before = block_exclusive_scan<uint32_t>(wd, su, &total_words);
-    if (tid < L) s_wcum[tid] = before;
-    __syncthreads();
-    const uint32_t wmax = s_wmax;
-    const bool any_bad = s_bad != 0u;
-    // carve the pool
-    const uint32_t wr = (wmax + 63u) & ~63u;                                  // cells per row buffer
-    const uint32_t total_live = s_off[L];
-    BandedLds z;
-    z.live_cap = min(max(total_live, 64u), BAND_LIVE_CAP);
-    z.row0 = reinterpret_cast<double*>(pool);
-    z.row1 = z.row0 + wr;
-    z.l_e = z.row1 + wr;
-    z.l_before = z.l_e + z.live_cap;
-    z.l_w = reinterpret_cast<uint32_t*>(z.l_before + z.live_cap);
-    z.l_jj = z.l_w + z.live_cap;
-    z.out_w = z.l_jj + z.live_cap;
-    const uint32_t used_bytes = (uint32_t)(reinterpret_cast<unsigned char*>(z.out_w) - pool);
-    const uint32_t out_cap = (BANDED_POOL - used_bytes) / 4u;                 // (two rows of 4224 cells and 2048 records leave 23 KB)
-    const bool in_lds = total_words <= out_cap;
-    if (tid == 0) z.row0[0] = 0.0;
-    lds_barrier();
-    if (in_lds) banded_layers<true>(ab, bb, z, s_lo, s_hi, s_off, s_wcum);
-    else banded_layers<false>(ab, bb, z, s_lo, s_hi, s_off, s_wcum);
-#ifdef KIMAD_STAMPS
-    const unsigned long long t_layers = __builtin_readcyclecounter();
-#endif
-    // ---- least total of the last row, smallest cost attaining it (totals are sums of squares: never negative, so
-    // their bit patterns order like the numbers; +inf stays the largest)
-    const uint32_t llo = s_lo[L], lhi = s_hi[L];
-    const double* lrow = (L & 1u) ? z.row1 : z.row0;
-    {
-        double best = DP_INF;
-        for (uint32_t c = llo + tid; c <= lhi; c += BANDED_THREADS) best = min_f64(best, lrow[c - llo]);
-        atomicMin(&s_best, (unsigned long long)__double_as_longlong(best));
-        __syncthreads();
-        const double least = __longlong_as_double((long long)s_best);
-        for (uint32_t c = llo + tid; c <= lhi; c += BANDED_THREADS)
-            if (lrow[c - llo] == least) atomicMin(&s_bc, c);
-        __syncthreads();
-    }
-    const double best = __longlong_as_double((long long)s_best);
-    const uint32_t bc = s_bc;
-    int32_t st = 0;
-    if (any_bad) st = err_nonfinite;
-    else if (!(best < DP_INF)) st = err_infeasible;
-    if (tid == 0) *ab.status = st;
-    if (st != 0) {
-        for (uint32_t i = tid; i < L; i += BANDED_THREADS) { ab.j_out[i] = 0; ab.K_out[i] = 0; }
-        for (uint32_t i = tid; i <= L; i += BANDED_THREADS) ab.offsets_out[i] = 0;
-        return;
-    }
-    // ---- back-tracking by one thread, winners into LDS
-    if (tid == 0) {
-        uint32_t c = bc;
-        if (in_lds) {
-            for (uint32_t i = L; i-- > 0;) {
-                const uint32_t word = z.out_w[s_wcum[i] + (c - s_lo[i + 1u])];
-                s_j[i] = (uint8_t)word;
-                c = min(word >> 16, cap);
+    const bool any_bad = s_bad != 0u, hopeless = bb.info[4] != 0u;
+    const uint32_t wr = min(cap + 1u, BAND_CELLS / 2u);   // cells per row buffer when only two rows are kept
+    const bool all = cells <= BAND_CELLS;
+
+    // the records of layers [a, b) into LDS, eight layers' loads in flight per wave
+    auto load_records = [&](uint32_t a, uint32_t b) {
+        const uint32_t first = s_row[a].w;
+        for (uint32_t i0 = a + wave * 8u; i0 < b; i0 += NWAVES * 8u) {
+            double e[8];
+            uint32_t w[8], at[8];
+            bool in[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint32_t i = min(i0 + (uint32_t)u, b - 1u);
+                const uint32_t rec = s_row[i].w, cnt = s_row[i + 1u].w - rec;
+                in[u] = i0 + (uint32_t)u < b && lane < cnt;
+                at[u] = rec - first + lane;
+                const size_t o = in[u] ? (size_t)i * J + min((bb.live[i] & 0xFFu) + lane, J - 1u) : 0;
+                e[u] = dl.e[2 * o]; w[u] = dl.w[o];
             }
-        } else {
-            for (uint32_t i = L; i-- > 0;) {
-                s_j[i] = ab.choice[(size_t)i * ab.stride + c];
-                c = min((uint32_t)ab.cprev[(size_t)i * ab.stride + c], cap);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (in[u]) recs[at[u]] = make_uint4((uint32_t)__double2loint(e[u]), (uint32_t)__double2hiint(e[u]), w[u], 0u);
+        }
+    };
+    int32_t st = any_bad ? err_nonfinite : hopeless ? err_infeasible : 0;
+    uint32_t at_last = 0u;                                // where row L's cells are
+    uint32_t loaded = 0u;                                 // first layer of the records in LDS
+    if (st == 0) {
+        if (tid == 0) { rows[0] = 0.0; rows[BAND_CELLS] = DP_INF; if (!all) rows_g[0] = 0.0; }
+        uint32_t i = 0u;
+        while (i < L) {
+            // a group of layers whose live records fit LDS (at least one layer: a list has at most 64 records)
+            const uint32_t g0 = s_row[i].w;
+            uint32_t i1 = L;
+            if (live_total - g0 > BAND_LIVE_CAP) {
+                uint32_t lo = i + 1u, hi = L;              // largest end whose records fit
+                while (lo < hi) {
+                    const uint32_t mid = (lo + hi + 1u) >> 1;
+                    if (s_row[mid].w - g0 <= BAND_LIVE_CAP) lo = mid; else hi = mid - 1u;
+                }
+                i1 = lo;
+            }
+            load_records(i, i1);
+            loaded = i;
+            __syncthreads();
+            BandRow p = band_row(s_row[i]), c = band_row(s_row[i + 1u]);
+            for (; i < i1; ++i) {
+                const uint4 next = s_row[min(i + 2u, L)];                      // (asked for now: off the critical path)
+                const uint32_t n = c.rec - p.rec;
+                const uint4* lrec = recs + (p.rec - g0);
+                const uint32_t prow = all ? p.at : (i & 1u) * wr, crow = all ? c.at : ((i + 1u) & 1u) * wr;
+                double* out = all ? nullptr : rows_g + (size_t)(i + 1u) * rstride;
+                // lanes per cell: so that four records a lane cover the list, as far as the lanes go round
+                const uint32_t w = c.span + 1u;
+                const uint32_t np = min(n <= 4u ? 1u : n <= 8u ? 2u : n <= 16u ? 4u : n <= 32u ? 8u : 16u,
+                                        w <= T / 16u ? 16u : w <= T / 8u ? 8u : w <= T / 4u ? 4u : w <= T / 2u ? 2u : 1u);
+                if (np == 1u) banded_layer<1, T>(lrec, rows, prow, crow, out, n, p, c);
+                else if (np == 2u) banded_layer<2, T>(lrec, rows, prow, crow, out, n, p, c);
+                else if (np == 4u) banded_layer<4, T>(lrec, rows, prow, crow, out, n, p, c);
+                else if (np == 8u) banded_layer<8, T>(lrec, rows, prow, crow, out, n, p, c);
+                else banded_layer<16, T>(lrec, rows, prow, crow, out, n, p, c);
+                lds_barrier();                             // the next layer reads this row (and the next group overwrites the records)
+                p = c; c = band_row(next);
             }
         }
+        at_last = all ? s_row[L].z : (L & 1u) * wr;
+    }
+    // ---- least total of the last row, smallest cost attaining it
+    double best = DP_INF;
+    uint32_t bc = 0xFFFFFFFFu;
+    if (st == 0) {
+        const uint32_t llo = s_row[L].x, span = s_row[L].y;
+        for (uint32_t x = tid; x <= span; x += T) {
+            const double v = rows[at_last + x];
+            if (v < best) { best = v; bc = llo + x; }      // ascending: keeps the smallest cost
+        }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            const double ov = __shfl_xor(best, d, 64);
+            const uint32_t oc = __shfl_xor(bc, d, 64);
+            if (ov < best || (ov == best && oc < bc)) { best = ov; bc = oc; }
+        }
+        if (lane == 0) { sd[wave] = best; sc[wave] = bc; }
+        __syncthreads();
+        for (uint32_t v = 0; v < NWAVES; ++v)
+            if (sd[v] < best || (sd[v] == best && sc[v] < bc)) { best = sd[v]; bc = sc[v]; }
+        if (!(best < DP_INF)) st = err_infeasible;
+    }
+    if (tid == 0) *ab.status = st;
+    if (st != 0) {                                         // (the same in every thread)
+        for (uint32_t i = tid; i < L; i += T) { ab.j_out[i] = 0; ab.K_out[i] = 0; }
+        for (uint32_t i = tid; i <= L; i += T) ab.offsets_out[i] = 0;
+        return;
+    }
+    // ---- the walk back, in groups of layers whose records, and staged rows, fit LDS
+    if (tid == 0) s_val[L] = best;
+    uint32_t cell = bc;
+    double val = best;
+    uint32_t hi = L;
+    while (hi > 0u) {
+        uint32_t lo = 0u;
+        if (s_row[hi].w > BAND_LIVE_CAP || (!all && s_row[hi].z > BAND_CELLS)) {
+            uint32_t a = 0u, b = hi - 1u;                  // smallest start whose records and rows fit
+            while (a < b) {
+                const uint32_t mid = (a + b) >> 1;
+                if (s_row[hi].w - s_row[mid].w <= BAND_LIVE_CAP && (all || s_row[hi].z - s_row[mid].z <= BAND_CELLS)) b = mid; else a = mid + 1u;
+            }
+            lo = a;
+        }
+        __syncthreads();                                   // (also: the rows written to memory are there)
+        const uint32_t row0 = all ? 0u : s_row[lo].z;      // the cells in LDS start here
+        if (lo < loaded || !all) {
+            load_records(lo, hi);
+            loaded = lo;
+        }
+        const uint32_t rec0 = s_row[loaded].w;
+        if (!all) {
+            for (uint32_t r = lo + wave; r < hi; r += NWAVES) {
+                const uint4 d = s_row[r];
+                const double* src = rows_g + (size_t)r * rstride;
+                for (uint32_t x = lane; x <= d.y; x += 64u) rows[d.z - row0 + x] = src[x];
+            }
+        }
+        __syncthreads();
+        if (wave == 0u) {
+            BandRow c = band_row(s_row[hi]), p = band_row(s_row[hi - 1u]), next = band_row(s_row[hi - 1u > lo ? hi - 2u : lo]);
+            uint4 r = recs[p.rec - rec0 + min(lane, max(c.rec - p.rec, 1u) - 1u)];
+            for (uint32_t i = hi; i-- > lo;) {
+                const uint32_t n = c.rec - p.rec;
+                const uint4 after = s_row[i > lo + 1u ? i - 2u : lo];
+                // the record of the layer before (`next` is its row), asked for now, as the row before that
+                const uint4 rn = recs[next.rec - rec0 + min(lane, max(p.rec - next.rec, 1u) - 1u)];
+                const uint32_t src = cell - p.lo - r.z;
+                const bool in = lane < n && src <= p.span;
+                const double v = rows[p.at - row0 + (in ? src : 0u)];
+                const uint64_t hit = ballot(in && v + rec_err(r) == val);
+                const uint32_t k = hit ? (uint32_t)__builtin_ctzll(hit) : 0u;  // (there is one)
+                if (lane == k) { s_k[i] = (uint8_t)k; s_val[i] = v; }
+                cell -= (uint32_t)__builtin_amdgcn_readlane((int)r.z, (int)k);
+                val = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), (int)k),
+                                       __builtin_amdgcn_readlane(__double2loint(v), (int)k));
+                r = rn; c = p; p = next; next = band_row(after);
+            }
+        }
+        hi = lo;
     }
     __syncthreads();
-    // ---- sizes and offsets
-    {
+    // ---- winners, sizes and offsets, in parallel
+    unsigned long long carry = 0ull;
+    for (uint32_t i0 = 0u; i0 < L; i0 += T) {
+        const uint32_t i = i0 + tid;
         unsigned long long K = 0ull;
         uint32_t j = 0u;
-        if (tid < L) { j = s_j[tid]; K = ab.Kout[(size_t)tid * J + min(j, J - 1u)]; }
+        if (i < L) {
+            const size_t o = (size_t)i * J + min((bb.live[i] & 0xFFu) + (uint32_t)s_k[i], J - 1u);
+            const uint32_t jj = dl.jj[o];
+            const double from = s_val[i], to = s_val[i + 1u];
+            j = jj >> 8;
+            // the lowest member of the run whose rounded total is the same (NaN for a single: never equal)
+            if (from + dl.e[2 * o + 1] == to) {
+                const uint32_t jlo = jj & 0xFFu;
+                --j;
+                while (j > jlo && from + ab.E[(size_t)i * J + j - 1u] == to) --j;
+            }
+            j = min(j, J - 1u);
+            K = ab.Kout[(size_t)i * J + j];
+        }
         unsigned long long total;
-        const unsigned long long off = block_exclusive_scan<unsigned long long>(K, su64, &total);
-        if (tid < L) { ab.j_out[tid] = (int32_t)j; ab.K_out[tid] = K; ab.offsets_out[tid] = off; }
-        if (tid == 0) ab.offsets_out[L] = total;
+        const unsigned long long off = carry + block_exclusive_scan<unsigned long long>(K, su64, &total);
+        if (i < L) { ab.j_out[i] = (int32_t)j; ab.K_out[i] = K; ab.offsets_out[i] = off; }
+        carry += total;
     }
-#ifdef KIMAD_STAMPS
-    if (tid == 0) {
-        bb.info[12] = (uint32_t)(t_layers - t_begin); bb.info[13] = (uint32_t)(__builtin_readcyclecounter() - t_begin);
-        bb.info[14] = in_lds ? 1u : 0u; bb.info[15] = total_live;
-    }
-#endif
+    if (tid == 0) ab.offsets_out[L] = carry;
 }
 
 }  // namespace kimad

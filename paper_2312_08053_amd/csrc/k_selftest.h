@@ -9,6 +9,21 @@
 
 namespace kimad {
 
+// (total, record) of another lane of the group; the smaller pair stays: the moves of group_min, with a second word along
+template <int CTRL>
+__device__ __forceinline__ void take_min_dpp(double& t, uint32_t& k) {
+    const double ot = dpp_f64<CTRL>(t);
+    const uint32_t ok = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, CTRL, 0xF, 0xF, false);
+    if (ot < t || (ot == t && ok < k)) { t = ot; k = ok; }
+}
+template <int NP>
+__device__ __forceinline__ void group_min_pair(double& t, uint32_t& k) {
+    if (NP >= 2) take_min_dpp<0xB1>(t, k);       // quad_perm [1,0,3,2]
+    if (NP >= 4) take_min_dpp<0x4E>(t, k);       // quad_perm [2,3,0,1]
+    if (NP >= 8) take_min_dpp<0x141>(t, k);      // row_half_mirror: the other quad of the eight
+    if (NP >= 16) take_min_dpp<0x140>(t, k);     // row_mirror: the other eight of the sixteen
+}
+
 // out_u32: [0, 64) inclusive add-scan of in_u32 over the lanes;
 //          [64 + (k4 * 4 + u) * 64 + lane] = in_u32[lane] + in_u32[64 + 16 * (lane / 16) + 4 * k4 + u]
 //          (row_addr_sub4: the calling lane's base plus the second operand of lane K + u of its row of 16)

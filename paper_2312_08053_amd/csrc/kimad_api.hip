@@ -60,7 +60,7 @@ struct Layout {
     uint64_t ncompact;
     uint64_t row0, row1, choice, dp_flags, dl_wall, dl_w, dl_jj, dl_e, dl_n, dl_bad, rows_g;
     uint64_t dense_E, dense_Kcost, dense_Kout;
-    uint64_t band_lo, band_hi, band_info, live_off, live_e, live_before, live_w, live_jj;
+    uint64_t band_lo, band_hi, band_info, band_live, hull_e, hull_w, hull_n, hull_abs;
     uint64_t rstride = 0;            // cells per stored DP row (LDS-resident recurrence only)
     uint64_t total = 0;
 };
@@ -276,8 +276,8 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     lo.dense_E = take(8 * LJ); lo.dense_Kcost = take(4 * LJ); lo.dense_Kout = take(4 * LJ);
     lo.band_lo = take(4ull * (L + 1)); lo.band_hi = take(4ull * (L + 1));
     lo.band_info = take(64);
-    lo.live_off = take(4ull * (L + 1)); lo.live_e = take(8 * LJ); lo.live_before = take(8 * LJ);
-    lo.live_w = take(4 * LJ); lo.live_jj = take(4 * LJ);
+    lo.band_live = take(4ull * L);
+    lo.hull_e = take(8 * LJ); lo.hull_w = take(4 * LJ); lo.hull_n = take(4ull * L); lo.hull_abs = take(8ull * L);
     {
         // a stored row holds a whole number of the forward kernel's 512-thread sweeps (2, 4 or 6 cells per thread)
         const uint64_t cells = std::min<uint64_t>(lo.dp_cells, DP_PAD_WIDE);
@@ -295,7 +295,9 @@ kimad_config_t normalise(const kimad_config_t* cfg) {
     return c;
 }
 
-constexpr uint64_t BAND_AUTO_CELLS = 1537;  // rows from this many cost cells on take the banded recurrence by themselves
+// Rows from this many cost cells on take the banded recurrence by themselves.  (148 layers: 175 us against 530 at 4097
+// cells.  At 1000 cells 162 against 155, and 290 against 144 where the bands are wide, as on ResNet-50's table.)
+constexpr uint64_t BAND_AUTO_CELLS = 1537;
 constexpr uint32_t FALLBACK_GRID = 1024;   // workgroups of a pass that usually has nothing to do
 
 __global__ __launch_bounds__(256) void k_zero16(uint4* p, uint64_t n16) {
@@ -575,12 +577,17 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
         const DpLists& dl = ws.dl;
         double* rows_g = ws.rows_g;
         const uint32_t rstride = ws.rstride;
-        KLAUNCH(p, s, "k_dp_prep", k_dp_prep, dim3(lo.L), dim3(64), ab, dl);
-        const bool band = (p->cfg.flags & KIMAD_CFG_BAND_DP) || cap + 1 >= BAND_AUTO_CELLS;
-        if (lo.L <= BAND_MAX_L && band && !(p->cfg.flags & KIMAD_CFG_FULL_DP)) {
+        const bool band = lo.L <= BAND_MAX_L && !(p->cfg.flags & KIMAD_CFG_FULL_DP) &&
+                          ((p->cfg.flags & KIMAD_CFG_BAND_DP) || cap + 1 >= BAND_AUTO_CELLS);
+        KLAUNCH(p, s, "k_dp_prep", k_dp_prep, dim3(lo.L), dim3(64), ab, dl, band ? 1u : 0u);
+        if (band) {
             // the recurrence inside the band of cells that Lagrangian bounds leave (same result, a fraction of the cells)
-            KLAUNCH(p, s, "k_dp_bounds", k_dp_bounds, dim3(1), dim3(BOUNDS_THREADS), ab, dl, ws.band);
-            KLAUNCH(p, s, "k_dp_banded", k_dp_banded, dim3(1), dim3(BANDED_THREADS), ab, ws.band, (const uint32_t*)dl.bad,
+            BandBuffers bb = ws.band;
+            bb.table = rows_g;                    // (a stored row has at least BAND_NLAM cells)
+            KLAUNCH(p, s, "k_dp_bounds", k_dp_bounds, dim3(1), dim3(BOUNDS_THREADS), ab, dl, bb);
+            KLAUNCH(p, s, "k_dp_banded", (k_dp_banded<BANDED_NARROW>), dim3(1), dim3(BANDED_NARROW), ab, dl, bb, rows_g, rstride,
+                    (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE);
+            KLAUNCH(p, s, "k_dp_banded", (k_dp_banded<BANDED_WIDE>), dim3(1), dim3(BANDED_WIDE), ab, dl, bb, rows_g, rstride,
                     (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE);
             return KIMAD_OK;
         }
@@ -836,9 +843,9 @@ int kimad_allocate(kimad_plan_t* p, const double* err_table, uint64_t budget_byt
     ws.dense_Kout = at<uint32_t>(p, lo.dense_Kout);
     ws.band.lo = at<uint32_t>(p, lo.band_lo); ws.band.hi = at<uint32_t>(p, lo.band_hi);
     ws.band.info = at<uint32_t>(p, lo.band_info);
-    ws.band.live_off = at<uint32_t>(p, lo.live_off); ws.band.live_e = at<double>(p, lo.live_e);
-    ws.band.live_before = at<double>(p, lo.live_before); ws.band.live_w = at<uint32_t>(p, lo.live_w);
-    ws.band.live_jj = at<uint32_t>(p, lo.live_jj);
+    ws.band.live = at<uint32_t>(p, lo.band_live);
+    ws.dl.he = at<double>(p, lo.hull_e); ws.dl.hw = at<uint32_t>(p, lo.hull_w); ws.dl.hn = at<uint32_t>(p, lo.hull_n);
+    ws.dl.habs = at<double>(p, lo.hull_abs);
     ws.rows_g = at<double>(p, lo.rows_g);
     ws.rstride = (uint32_t)lo.rstride;
     ws.max_cells = lo.dp_cells;
@@ -873,9 +880,10 @@ int kimad_allocate_static(kimad_plan_t* p, const double* err_table, uint64_t bud
     ws.band.lo = reinterpret_cast<uint32_t*>(take(4ull * (KIMAD_STATIC_MAX_L + 1)));
     ws.band.hi = reinterpret_cast<uint32_t*>(take(4ull * (KIMAD_STATIC_MAX_L + 1)));
     ws.band.info = reinterpret_cast<uint32_t*>(take(64));
-    ws.band.live_off = reinterpret_cast<uint32_t*>(take(4ull * (KIMAD_STATIC_MAX_L + 1)));
-    ws.band.live_e = reinterpret_cast<double*>(take(8 * LJ)); ws.band.live_before = reinterpret_cast<double*>(take(8 * LJ));
-    ws.band.live_w = reinterpret_cast<uint32_t*>(take(4 * LJ)); ws.band.live_jj = reinterpret_cast<uint32_t*>(take(4 * LJ));
+    ws.band.live = reinterpret_cast<uint32_t*>(take(4ull * KIMAD_STATIC_MAX_L));
+    ws.dl.he = reinterpret_cast<double*>(take(8 * LJ)); ws.dl.hw = reinterpret_cast<uint32_t*>(take(4 * LJ));
+    ws.dl.hn = reinterpret_cast<uint32_t*>(take(4ull * KIMAD_STATIC_MAX_L));
+    ws.dl.habs = reinterpret_cast<double*>(take(8ull * KIMAD_STATIC_MAX_L));
     ws.rows_g = reinterpret_cast<double*>(take(8ull * (KIMAD_STATIC_MAX_L + 1) * CELLS));
     ws.rstride = (uint32_t)CELLS;
     ws.max_cells = CELLS;
