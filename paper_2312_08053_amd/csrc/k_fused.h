@@ -92,7 +92,7 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
     __shared__ uint32_t bitmap[D1_BINS / 32];
     __shared__ uint32_t su[16];
     __shared__ unsigned long long s64[16];
-    __shared__ uint32_t sh_gbin, sh_spill, sh_eighth, sh_ns, sh_gap;
+    __shared__ uint32_t sh_gbin, sh_spill, sh_eighth, sh_ns, sh_gap, sh_knext;
     const uint32_t tid = threadIdx.x, big = blockIdx.x;
     const uint32_t li = pb.big_layer[big];
     const LayerDesc L = pb.layers[li];
@@ -107,7 +107,9 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
             c[4 * k] = v.x; c[4 * k + 1] = v.y; c[4 * k + 2] = v.z; c[4 * k + 3] = v.w;
         }
     }
-    // (1) global threshold bin: the highest bin b with (entries of all layers in bins >= b) >= 2.5 x budget
+    bool narrow;                                           // the budget is known and at most a 32nd of all entries
+    // (1) global threshold bin: the highest bin b with (entries of all layers in bins >= b) >= 1.25 x budget
+    // (2.5 x for a wide link, whose sizes the estimate below says little about: most layers spill their eighth there)
     {
         unsigned long long gc[16], sum = 0;
 #pragma unroll
@@ -115,8 +117,9 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
         unsigned long long tot;
         const unsigned long long ex = block_exclusive_scan<unsigned long long>(sum, s64, &tot);
         unsigned long long ab = tot - ex - sum;            // entries above this thread's bins
-        const unsigned long long want = budget_pairs * 5ull / 2ull;
-        if (tid == 0) sh_gbin = 0u;                        // budget beyond everything: bin 0
+        narrow = budget_pairs != 0ull && budget_pairs <= tot / 32ull;
+        const unsigned long long want = narrow ? budget_pairs + budget_pairs / 4ull : budget_pairs * 5ull / 2ull;
+        if (tid == 0) { sh_gbin = 0u; sh_knext = 0xFFFFFFFFu; }    // budget beyond everything: bin 0
         __syncthreads();
         if (budget_pairs && ab < want && ab + sum >= want) {
 #pragma unroll
@@ -149,15 +152,30 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
         }
         return lo;
     };
+    // The size the allocation will choose for this layer: an allocation cuts all layers at about
+    // the same magnitude, rounded to the grid: the second grid size above this layer's entries in the global bins (the
+    // first one left a few of ResNet-50's layers short, which then read g and h again).
+    if (narrow && tid < J) {
+        const uint32_t K = Ktab[(size_t)li * J + tid], K2 = Ktab[(size_t)li * J + min(tid + 1u, J - 1u)];
+        const double here = scale * (double)(sh_gbin ? above[sh_gbin - 1u] : ns_total);
+        if ((double)K >= here) atomicMin(&sh_knext, K2);
+    }
+    __syncthreads();
     if (tid == 0) {
-        // Spill everything down to the global threshold bin; at least the top 2 % (the sparse upper
-        // tail would otherwise need a slot per candidate) and twice the smallest grid size (plus
-        // 3 sigma of the sample count); at most an eighth of the layer.
+        // Spill down to that size (plus 3 sigma of the sample count) and to the global threshold bin; at least a
+        // four-hundredth of the layer (without a narrow budget the top 2 %) and twice the smallest grid size (plus
+        // 3 sigma); at most an eighth of the layer.  What is spilled is written and read again several times: with 2 % of
+        // every layer and the entries of 2.5 budgets the Llama-shaped set's k_main took 2412 us and its step 3360, with this
+        // 2267 and 3204.
         const uint32_t K0 = Ktab[(size_t)li * J];
         const double k0s = 2.0 * (double)K0 / scale;
         uint32_t floor_rank = (uint32_t)fmin((double)ns_total, ceil(k0s + 3.0 * sqrt(k0s) + 2.0));
         // (a selection has one target: nothing above it needs a slot)
-        floor_rank = max(floor_rank, J == 1u ? 1u : max(1u, ns_total / 50u));
+        floor_rank = max(floor_rank, J == 1u ? 1u : max(1u, ns_total / (narrow ? 400u : 50u)));
+        if (narrow) {
+            const double kns = (double)min(sh_knext, L.n) / scale;
+            floor_rank = max(floor_rank, (uint32_t)fmin((double)ns_total, ceil(kns + 3.0 * sqrt(kns) + 2.0)));
+        }
         uint32_t b = find_bin(floor_rank);
         if (budget_pairs) b = min(b, sh_gbin);
         // never more than the top eighth of the layer: the bin that holds the entry of that rank is spilled only
