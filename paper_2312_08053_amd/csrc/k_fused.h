@@ -80,13 +80,15 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void k_sample(ProfileBuffers pb) {
 
 // ---------------------------------------------------------------------------------------------
 // Prediction: per big layer, the spill bin and the digit-1 bins that get a slot.
-// `budget_pairs` = expected budget of the following allocation in pairs (0 = unknown).
+// `budget_pairs` = expected budget of the following allocation in pairs (0 = unknown); `unit_pairs` = pairs of one cost
+// unit of that allocation.
 // `counts` / `gcounts`: per layer and summed digit-1 counts to predict from: the sample of k_sample (scaled to the
 // population through the layer's size), or the exact histogram of the previous profile on this plan (successive
 // gradients of a layer are distributed alike; a layer whose boundary bins moved is recounted like any other
 // misprediction).  `fold_zero`: also clear what a profile must find at zero (no separate clearing launch).
 __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32_t* Ktab, uint32_t J,
-                                                 unsigned long long budget_pairs, const uint32_t* __restrict__ counts,
+                                                 unsigned long long budget_pairs, unsigned long long unit_pairs,
+                                                 const uint32_t* __restrict__ counts,
                                                  const unsigned long long* __restrict__ gcounts, uint32_t fold_zero) {
     __shared__ uint32_t above[D1_BINS];        // sample entries in strictly higher bins
     __shared__ uint32_t bitmap[D1_BINS / 32];
@@ -162,18 +164,21 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
     }
     __syncthreads();
     if (tid == 0) {
-        // Spill down to that size (plus 3 sigma of the sample count) and to the global threshold bin; at least a
-        // four-hundredth of the layer (without a narrow budget the top 2 %) and twice the smallest grid size (plus
-        // 3 sigma); at most an eighth of the layer.  What is spilled is written and read again several times: with 2 % of
-        // every layer and the entries of 2.5 budgets the Llama-shaped set's k_main took 2412 us and its step 3360, with this
-        // 2267 and 3204.
+        // Spill down to that size, rounded up to whole cost units (a layer pays for its last unit whole and takes what fits
+        // it; one whose entries all lie below the cut still pays for one), plus 3 sigma of the sample count, and to the global
+        // threshold bin; at least a four-hundredth of the layer (without a narrow budget the top 2 %) and twice the smallest
+        // grid size (plus 3 sigma); at most an eighth of the layer.  What is spilled is written and read again several
+        // times: with 2 % of every layer and the entries of 2.5 budgets the Llama-shaped set's k_main took 2412 us and its
+        // step 3360, with this 2267 and 3204.  Without the rounding, 66 to 108 of that set's 169 tiled layers ended short with
+        // 2 to 6 % of the bytes to spend and read g and h again: steps of 3970 us at 2 % and 5720 at 6 %, now 3460 and 4530.
         const uint32_t K0 = Ktab[(size_t)li * J];
         const double k0s = 2.0 * (double)K0 / scale;
         uint32_t floor_rank = (uint32_t)fmin((double)ns_total, ceil(k0s + 3.0 * sqrt(k0s) + 2.0));
         // (a selection has one target: nothing above it needs a slot)
         floor_rank = max(floor_rank, J == 1u ? 1u : max(1u, ns_total / (narrow ? 400u : 50u)));
         if (narrow) {
-            const double kns = (double)min(sh_knext, L.n) / scale;
+            const unsigned long long aim = ((unsigned long long)min(sh_knext, L.n) + unit_pairs - 1ull) / unit_pairs * unit_pairs;
+            const double kns = (double)min(aim, (unsigned long long)L.n) / scale;
             floor_rank = max(floor_rank, (uint32_t)fmin((double)ns_total, ceil(kns + 3.0 * sqrt(kns) + 2.0)));
         }
         uint32_t b = find_bin(floor_rank);

@@ -295,6 +295,12 @@ kimad_config_t normalise(const kimad_config_t* cfg) {
     return c;
 }
 
+// Pairs of one cost unit of an allocation that spends P pairs.
+uint64_t cost_unit(const kimad_config_t& cfg, uint64_t P) {
+    const uint64_t D = cfg.cost_units_D;
+    return D == 0 || P <= D ? 1 : (P + D - 1) / D;
+}
+
 // Rows from this many cost cells on take the banded recurrence by themselves.  (148 layers: 175 us against 530 at 4097
 // cells.  At 1000 cells 162 against 155, and 290 against 144 where the bands are wide, as on ResNet-50's table.)
 constexpr uint64_t BAND_AUTO_CELLS = 1537;
@@ -466,15 +472,16 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
         return launch_small_profile(p, err_table, s, side);
     }
     int rc = KIMAD_OK;
+    const uint64_t unit = cost_unit(p->cfg, budget_pairs);
     if (p->hist_valid && !(p->cfg.flags & KIMAD_CFG_SAMPLE_ALWAYS)) {
         // prediction from the previous pass's exact histogram: no sampling pass, no clearing launch
-        KLAUNCH(p, s, "k_predict", k_predict, dim3(lo.B), dim3(256), p->pb, ktab, J, (unsigned long long)budget_pairs,
+        KLAUNCH(p, s, "k_predict", k_predict, dim3(lo.B), dim3(256), p->pb, ktab, J, (unsigned long long)budget_pairs, (unsigned long long)unit,
                 (const uint32_t*)p->pb.hprev, (const unsigned long long*)p->pb.gprev, 1u);
     } else {
         rc = zero_range(p, lo.zero1_mid, lo.zero1_end, s);   // the histogram tables are written whole by k_reduce_parts
         if (rc) return rc;
         KLAUNCH(p, s, "k_sample", k_sample, dim3(lo.nswg), dim3(SAMPLE_THREADS), p->pb);
-        KLAUNCH(p, s, "k_predict", k_predict, dim3(lo.B), dim3(256), p->pb, ktab, J, (unsigned long long)budget_pairs,
+        KLAUNCH(p, s, "k_predict", k_predict, dim3(lo.B), dim3(256), p->pb, ktab, J, (unsigned long long)budget_pairs, (unsigned long long)unit,
                 (const uint32_t*)p->pb.shist, (const unsigned long long*)p->pb.ghist, 0u);
     }
     p->hist_valid = true;
@@ -542,8 +549,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
                      int32_t* j_out, uint64_t* K_out, uint64_t* offsets_out, int32_t* status_out, hipStream_t s) {
     const Layout& lo = p->lo;
     const uint64_t P = budget_bytes / p->cfg.pair_bytes;
-    const uint64_t D = p->cfg.cost_units_D;
-    const uint64_t unit = (D == 0 || P <= D) ? 1 : (P + D - 1) / D;
+    const uint64_t unit = cost_unit(p->cfg, P);
     uint64_t cap = P / unit;
     // Costs above the dearest allocation are unreachable (+inf for ever): cutting the rows there
     // changes no finite cell and so neither the least total nor the smallest cost attaining it.

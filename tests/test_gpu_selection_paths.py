@@ -106,3 +106,30 @@ def test_profile_on_a_grid_up_to_nearly_all_entries(n, zeros):
         gh.assert_table_close(E, E_ref, Kt, sizes)
     if n == 400003:
         assert plan.diagnostics()["redo_layers"] <= 1       # (the layer of 12000 entries may be recounted)
+
+
+@pytest.mark.parametrize("D", [30, 60, 1000])
+def test_layers_that_pay_for_a_whole_cost_unit_are_served_from_the_candidates(D):
+    """Layers far below the budget's cut still get what one cost unit holds, more than a four-hundredth of a layer where
+    units are coarse: the pass spills that much of them, so nothing is read a second time."""
+    import torch
+    import paper_2312_08053_amd as kimad
+    rng = np.random.default_rng(3)
+    sizes = [200000 + 13 * i for i in range(12)]
+    ratios = np.logspace(-4, 0, 48)
+    d = sum(sizes)
+    budget = int(0.02 * 4 * d)
+    gd = torch.empty(d, dtype=torch.float32, device="cuda")
+    hd = torch.zeros_like(gd)
+    plan = kimad.Plan(gd, hd, sizes, ratios.tolist(), D=D, max_budget_bytes=budget)
+    scales = np.repeat(10.0 ** np.linspace(-5, -2, len(sizes)), sizes)
+    for _ in range(3):
+        g = (rng.standard_t(3, size=d) * scales).astype(np.float32)
+        gd.copy_(torch.from_numpy(g))
+        hd.zero_()
+        assert plan.step(budget).cpu().tolist() == [0, 0]
+        K = plan.K.cpu().numpy()
+        assert all(s["mode"] == 3 for s in plan.layer_states()), (K, plan.layer_states())
+        work = Workload(name="units", sizes=np.asarray(sizes, dtype=np.uint64), g=g, h=np.zeros_like(g), ratios=ratios,
+                        budget_bytes=budget, cost_units_D=D)
+        gh.check_compress(work, plan, hd, K.tolist(), np.concatenate([[0], np.cumsum(K)]), plan.idx, plan.val)
