@@ -232,26 +232,31 @@ __global__ __launch_bounds__(256) void k_scan1(ProfileBuffers pb, const uint32_t
 
 // ---------------------------------------------------------------------------------------------
 // Pass 2: digit-2 histograms (count + squares) of the entries that fall in a boundary bin.
-// Workgroups take groups of consecutive tiles in a grid-stride loop, as many tiles as the 16-bit counts admit, and add
-// their tables to the layer's once per group: on a small set, whose tiles are short, the additions of every tile's few
-// thousand entries were nearly all of the pass (ResNet-18 with 50 ratios, every layer: 154 us with a flush per 4096
-// elements, 36 us with this).  `gate` (optional) points at a device word that is
+// Workgroups take groups of consecutive tiles in a grid-stride loop and add their tables to the layer's once per group:
+// on a small set, whose tiles are short, the additions of every tile's few thousand entries were nearly all of the pass
+// (ResNet-18 with 50 ratios, every layer: 154 us with a flush per 4096 elements, 36 us with one per 32768).
+// hist2_group_tiles says how long a group is.  `gate` (optional) points at a device word that is
 // zero when no layer needs this pass: the single-pass profile launches it as a fallback that
 // normally has nothing to do, with a small grid that leaves after one load, and with `coarse` set
 // so that the recount holds the same numbers the pass itself would have put into the slot.
 constexpr uint32_t HIST2_MAX_ELEMS = 32768;    // elements a workgroup may count before it flushes: the count field has 16 bits
-__global__ __launch_bounds__(512) void k_hist2(ProfileBuffers pb, uint32_t ntiles, const uint32_t* gate,
+// As many tiles as the counts admit, but at least 256 groups, one a compute unit, where the set has the tiles for them.
+// (Groups of 32768 elements left a perceptron of 266 K elements nine workgroups: k_hist2 9 -> 22 us, a classic profile
+// 61 -> 80 us.  At least 512 or 1024 groups: ResNet-18 with every layer recounted 320 -> 337 or 358 us.)
+inline uint32_t hist2_group_tiles(uint32_t ntiles, uint32_t tile_elems) {
+    const uint32_t most = HIST2_MAX_ELEMS / tile_elems, share = ntiles / 256u;
+    return share < 1u ? 1u : share < most ? share : most;
+}
+__global__ __launch_bounds__(512) void k_hist2(ProfileBuffers pb, uint32_t ntiles, uint32_t group_tiles, const uint32_t* gate,
                                                uint32_t coarse) {
     __shared__ unsigned long long sub[MAX_SLOTS * D2_BINS];   // 64 KB
     __shared__ unsigned long long sub0[D2_BINS];              // exact squares when the slot is bin 0
     __shared__ uint8_t lut[D1_BINS];
     const uint32_t tid = threadIdx.x;
     if (gate && *gate == 0u) return;
-    const uint32_t per_group = max(1u, HIST2_MAX_ELEMS / pb.tile_elems);
-    const uint32_t ngroups = (ntiles + per_group - 1u) / per_group;
-    for (uint32_t group = blockIdx.x; group < ngroups; group += gridDim.x) {
-    uint32_t tile = group * per_group;
-    const uint32_t tile_end = min(ntiles, tile + per_group);
+    for (uint32_t tile0 = blockIdx.x * group_tiles; tile0 < ntiles; tile0 += gridDim.x * group_tiles) {
+    uint32_t tile = tile0;
+    const uint32_t tile_end = min(ntiles, tile + group_tiles);
     while (tile < tile_end) {
     // the group's tiles of one layer
     const uint32_t li = pb.tile_layer[tile];

@@ -432,7 +432,9 @@ int run_select_passes(kimad_plan* p, const uint32_t* ktab_dev, uint32_t J, doubl
     if (lo.B) {
         KLAUNCH(p, s, "k_hist1", k_hist1, dim3(lo.ntiles), dim3(256), p->pb);
         KLAUNCH(p, s, "k_scan1", k_scan1, dim3(lo.B), dim3(256), p->pb, ktab_dev, J);
-        KLAUNCH(p, s, "k_hist2", k_hist2, dim3(lo.ntiles), dim3(512), p->pb, lo.ntiles, (const uint32_t*)nullptr, 0u);
+        const uint32_t group = hist2_group_tiles(lo.ntiles, lo.tile_elems);
+        KLAUNCH(p, s, "k_hist2", k_hist2, dim3((lo.ntiles + group - 1) / group), dim3(512), p->pb, lo.ntiles, group,
+                (const uint32_t*)nullptr, 0u);
         KLAUNCH(p, s, "k_scan2", k_scan2, dim3(lo.B), dim3(SCAN2_THREADS), p->pb, ktab_dev, J, err_table, CERT_TOL, 0.0);
         if (err_table) {
             // exact last-digit pass for the entries scan 2 could not certify (usually none)
@@ -499,8 +501,9 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
         KLAUNCH(p, s, "k_hist2c", k_hist2c, dim3((lo.nchunks + 256u / SUB_HIST - 1) / (256u / SUB_HIST)), dim3(256), p->pb);
     }
     // fallbacks that normally find nothing to do: small grids
-    KLAUNCH(p, s, "k_hist2", k_hist2, dim3(std::min<uint32_t>(lo.ntiles, FALLBACK_GRID)), dim3(512), p->pb, lo.ntiles,
-            (const uint32_t*)(at<uint32_t>(p, lo.diag) + 3), 1u);   // layers marked redo only
+    const uint32_t group = hist2_group_tiles(lo.ntiles, lo.tile_elems);
+    KLAUNCH(p, s, "k_hist2", k_hist2, dim3(std::min<uint32_t>((lo.ntiles + group - 1) / group, FALLBACK_GRID)), dim3(512), p->pb,
+            lo.ntiles, group, (const uint32_t*)(at<uint32_t>(p, lo.diag) + 3), 1u);   // layers marked redo only
     KLAUNCH(p, s, "k_scan2", k_scan2, dim3(lo.B), dim3(SCAN2_THREADS), p->pb, ktab, J, err_table, CERT_TOL, SLOT_WIDEN);
     if (!err_table) return KIMAD_OK;
     KLAUNCH(p, s, "k_hist3p", k_hist3p, dim3(std::min<uint32_t>(lo.ntiles, FALLBACK_GRID)), dim3(256), p->pb, lo.ntiles);

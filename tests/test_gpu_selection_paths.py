@@ -133,3 +133,25 @@ def test_layers_that_pay_for_a_whole_cost_unit_are_served_from_the_candidates(D)
         work = Workload(name="units", sizes=np.asarray(sizes, dtype=np.uint64), g=g, h=np.zeros_like(g), ratios=ratios,
                         budget_bytes=budget, cost_units_D=D)
         gh.check_compress(work, plan, hd, K.tolist(), np.concatenate([[0], np.cumsum(K)]), plan.idx, plan.val)
+
+
+@pytest.mark.parametrize("L", [100, 103, 154, 420])
+def test_recount_in_groups_of_tiles(L):
+    """Layers of a few tiles each, so that a group of tiles ends inside a layer, spans several, or is one tile: below and
+    above the tiles per compute unit from which on groups form."""
+    import torch
+    import paper_2312_08053_amd as kimad
+    from paper_2312_08053_amd import binding
+    rng = np.random.default_rng(L)
+    sizes = [8193 + 2048 * int(rng.integers(0, 2)) + i % 7 for i in range(L)]
+    ratios = np.logspace(-2, 0, 12)
+    g = (rng.standard_t(3, size=sum(sizes)) * 1e-3).astype(np.float32)
+    g[rng.random(g.size) < 0.02] = 0.0
+    gd = torch.from_numpy(g).cuda()
+    plan = kimad.Plan(gd, torch.zeros_like(gd), sizes, ratios.tolist(), D=1000, max_budget_bytes=8 * sum(sizes),
+                      cfg_flags=binding.KIMAD_CFG_CLASSIC_PROFILE)
+    E = plan.profile().cpu().numpy().reshape(L, -1)
+    starts = np.concatenate([[0], np.cumsum(sizes)])
+    gL = [g[a:b] for a, b in zip(starts[:-1], starts[1:])]
+    E_ref, _ = ko.profile(gL, [np.zeros_like(x) for x in gL], ratios)
+    gh.assert_table_close(E, E_ref, plan.grid_sizes(), sizes)
