@@ -30,16 +30,16 @@ struct DecodeArgs {
     uint32_t f16;                            // bit m: worker m's values are binary16
 };
 
-// The workers' payloads into their estimators, worker first + blockIdx.y by a row of workgroups: four pairs per thread
-// and trip.  The pair's layer is found by bisection in the worker's offsets; indices inside a payload are distinct, so
+// The workers' payloads into their estimators, worker first + blockIdx.y by a row of workgroups: one thread per pair.
+// The pair's layer is found by bisection in the worker's offsets; indices inside a payload are distinct, so
 // the additions need no atomics.  The payload is what a worker sent, not something this library produced: every
 // workgroup first checks the offsets (non-decreasing, starting at 0, the total within the buffers'
 // capacity, the layer starts non-decreasing up to d) and leaves without a write if they are not; a
 // pair whose index lies outside its layer is skipped.  Either way the status word gets err_payload.
 // Bound by the 128-byte lines that the 4-byte updates touch.  One launch for all workers (they write disjoint
-// estimators; the caller sends them one by one where they do not), the offsets bisected in LDS and four pairs' loads in
-// flight: sixteen payloads of 58 K pairs 86 -> 40 us, four of 622 K pairs 155 -> 96 us.
-constexpr uint32_t DECODE_PAIRS = 4;         // pairs per thread and trip
+// estimators; the caller sends them one by one where they do not), the offsets bisected in LDS.  Calls without a model,
+// against a launch per worker: sixteen payloads of 58 K pairs 103 -> 57 us, four of 622 K 129 -> 103, one of 622 K 32 and
+// one of 58 K 16 either way.  (Four pairs per thread with their loads together: 59, 110, 33 and 18 us.)
 constexpr uint32_t DECODE_LDS_L = 1023;      // layers whose offsets and starts are kept in LDS
 __global__ __launch_bounds__(256) void k_server_decode(DecodeArgs a, uint32_t first, const uint64_t* __restrict__ layer_start,
                                                        uint32_t L, uint64_t d, int32_t* status_out, int32_t err_payload) {
@@ -73,44 +73,21 @@ __global__ __launch_bounds__(256) void k_server_decode(DecodeArgs a, uint32_t fi
         return;
     }
     const uint64_t total = off[L];
-    const uint64_t stride = (uint64_t)gridDim.x * (256u * DECODE_PAIRS);
-    for (uint64_t p0 = (uint64_t)blockIdx.x * (256u * DECODE_PAIRS) + threadIdx.x; p0 < total; p0 += stride) {
-        uint32_t t[DECODE_PAIRS], lo[DECODE_PAIRS], hi[DECODE_PAIRS];
-        float v[DECODE_PAIRS];
-#pragma unroll
-        for (uint32_t k = 0; k < DECODE_PAIRS; ++k) {
-            const uint64_t p = min(p0 + 256u * k, total - 1u);       // (positions past the end repeat the last pair and are dropped)
-            t[k] = idx[p];
-            // half-precision payloads carry binary16 bit patterns: the worker added the decoded value, so does the server
-            v[k] = f16 ? __half2float(__ushort_as_half(reinterpret_cast<const uint16_t*>(val)[p])) : val[p];
-            lo[k] = 0; hi[k] = L;                // largest layer i with off[i] <= p
+    const uint64_t stride = (uint64_t)gridDim.x * 256u;
+    for (uint64_t p = (uint64_t)blockIdx.x * 256u + threadIdx.x; p < total; p += stride) {
+        const uint32_t t = idx[p];
+        // half-precision payloads carry binary16 bit patterns: the worker added the decoded value, so does the server
+        const float v = f16 ? __half2float(__ushort_as_half(reinterpret_cast<const uint16_t*>(val)[p])) : val[p];
+        uint32_t lo = 0, hi = L;                 // largest layer i with off[i] <= p
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if ((in_lds ? s_off[mid] : off[mid]) <= p) lo = mid; else hi = mid;
         }
-        // the four bisections go side by side: all end within the same number of halvings
-        for (uint32_t span = L; span > 1u; span = (span + 1u) >> 1) {
-#pragma unroll
-            for (uint32_t k = 0; k < DECODE_PAIRS; ++k) {
-                const uint32_t mid = (lo[k] + hi[k]) >> 1;
-                const uint64_t p = min(p0 + 256u * k, total - 1u);
-                const uint64_t o = in_lds ? s_off[mid] : off[mid];
-                if (mid > lo[k]) { if (o <= p) lo[k] = mid; else hi[k] = mid; }
-            }
-        }
-        float* u[DECODE_PAIRS];
-        float old[DECODE_PAIRS];
-#pragma unroll
-        for (uint32_t k = 0; k < DECODE_PAIRS; ++k) {
-            const uint64_t start = in_lds ? s_start[lo[k]] : layer_start[lo[k]];
-            const uint64_t n = (in_lds ? s_start[lo[k] + 1u] : layer_start[lo[k] + 1u]) - start;
-            u[k] = nullptr;
-            old[k] = 0.0f;
-            if (p0 + 256u * k < total) {
-                if ((uint64_t)t[k] < n) { u[k] = u_hat + start + t[k]; old[k] = gload(u[k]); }
-                else atomicMin(status_out + m, err_payload);
-            }
-        }
-#pragma unroll
-        for (uint32_t k = 0; k < DECODE_PAIRS; ++k)
-            if (u[k]) gstore(u[k], old[k] + v[k]);
+        const uint64_t start = in_lds ? s_start[lo] : layer_start[lo];
+        const uint64_t n = (in_lds ? s_start[lo + 1u] : layer_start[lo + 1u]) - start;
+        if ((uint64_t)t >= n) { atomicMin(status_out + m, err_payload); continue; }
+        float* u = u_hat + start + t;
+        gstore(u, gload(u) + v);
     }
 }
 

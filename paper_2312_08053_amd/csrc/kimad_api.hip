@@ -1091,7 +1091,7 @@ int kimad_server_apply(const kimad_payload_t* payloads, float* const* u_hat, con
     if (hipGetLastError() != hipSuccess) return KIMAD_ERR_HIP;
     // payload sizes live on the device: a grid for the capacity, of at most 1024 workgroups a worker, strides over
     // whatever the worker sent.  Workers whose estimators share memory are decoded one after another.
-    const uint32_t dblocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((pairs + 256 * DECODE_PAIRS - 1) / (256 * DECODE_PAIRS), 1024));
+    const uint32_t dblocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((pairs + 255) / 256, 1024));
     for (uint32_t m = 0; m < M; m += apart ? M : 1u) {
         hipLaunchKernelGGL(k_server_decode, dim3(dblocks, apart ? M : 1u), dim3(256), 0, s, da, m, layer_start, L, d, status_out,
                            (int32_t)KIMAD_ERR_BAD_PAYLOAD);
