@@ -93,11 +93,31 @@ __global__ __launch_bounds__(256) void k_server_decode(DecodeArgs a, uint32_t fi
 
 // The model step, four elements per thread and trip; the tail and unaligned buffers take the
 // scalar loop.  fp64 arithmetic per element, workers in order: every result is reproducible and
-// equal to a plain sequential evaluation.  HBM-bound; the model is written with nontemporal stores, so that its lines do
-// not take the cache from the estimators' in passing: 530 -> 468 us for four estimators of 124 M elements (6.4 TB/s); the next
-// decode finds the cache without the model's dirty lines, too (part of its 155 -> 96 us).
-// (All of a thread's loads asked for together, the worker count fixed at compile time, was slower: 557 us; two or four
-// quads a thread and runs of blocks per XCD as well.)
+// equal to a plain sequential evaluation.  HBM-bound.
+// (Four estimators of 124 M elements: 468 us, 6.4 TB/s.  All of a thread's loads asked for together, the worker count fixed at
+// compile time, 557; two or four quads a thread and runs of blocks per XCD were slower as well.)
+//
+// Nontemporal stores keep the model's lines from displacing the estimators' in passing, but then the next round
+// cannot find the model in the 256 MB cache either.  Whole calls with small payloads, round after round, us with ordinary
+// and with nontemporal stores:
+//     model (MiB)  1 worker       2 workers      3 workers      4 workers
+//      64          53   49        64   62        78   76        91   89
+//     128          83   85       108  112       133  136       161  166
+//     192 MB      112  117       151  158       190  201       219  227
+//     256 MB      141  152       204  213       249  248       314  302
+//     448 MB      250  260       408  361       513  427       619  509
+//     800 MB      447  452       694  616       877  739      1035  872
+//    1000          580  553       852  764      1064  919
+// (six to sixteen workers: equal up to 192 MB, nontemporal 7 to 20 % faster from 256 MB on; after a gigabyte of other
+// memory was written in between, nontemporal stores are as fast or faster at every size).  Ordinary stores where they win by
+// more than the runs differ (four workers have the single
+// decode launch to more than make up for it):
+inline bool model_stores_stream(uint32_t M, uint64_t d) {
+    const uint64_t mib = 4 * d >> 20;
+    return !(mib >= 112 && (M == 1 ? mib <= 768 : M <= 3 && mib <= 256));
+}
+// (A template: a branch between the two stores is merged into one ordinary store by the compiler.)
+template <bool STREAM_STORES>
 __global__ __launch_bounds__(256) void k_server_step(ServerArgs a, float* x, double gamma, uint32_t vec_ok) {
     const uint64_t gid = (uint64_t)blockIdx.x * 256u + threadIdx.x, stride = (uint64_t)gridDim.x * 256u;
     const uint64_t n4 = vec_ok ? a.d / 4 : 0;
@@ -116,7 +136,8 @@ __global__ __launch_bounds__(256) void k_server_step(ServerArgs a, float* x, dou
         float4 r;
         r.x = (float)((double)xv.x - gamma * s0); r.y = (float)((double)xv.y - gamma * s1);
         r.z = (float)((double)xv.z - gamma * s2); r.w = (float)((double)xv.w - gamma * s3);
-        gstore4_stream(x + 4 * q, r);
+        if (STREAM_STORES) gstore4_stream(x + 4 * q, r);
+        else gstore4(x + 4 * q, r);
     }
     for (uint64_t t = 4 * n4 + gid; t < a.d; t += stride) {
         double acc = 0.0;

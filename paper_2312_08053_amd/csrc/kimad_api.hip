@@ -1101,7 +1101,10 @@ int kimad_server_apply(const kimad_payload_t* payloads, float* const* u_hat, con
         const uint64_t work = (d + 3) / 4;
         // one quad per thread: measured 15 % faster here than a grid-stride loop over fewer blocks
         const uint32_t blocks = (uint32_t)std::min<uint64_t>((work + 255) / 256, 1ull << 22);
-        hipLaunchKernelGGL(k_server_step, dim3(blocks), dim3(256), 0, s, a, x, gamma, vec_ok ? 1u : 0u);
+        if (model_stores_stream(M, d))
+            hipLaunchKernelGGL(k_server_step<true>, dim3(blocks), dim3(256), 0, s, a, x, gamma, vec_ok ? 1u : 0u);
+        else
+            hipLaunchKernelGGL(k_server_step<false>, dim3(blocks), dim3(256), 0, s, a, x, gamma, vec_ok ? 1u : 0u);
         if (hipGetLastError() != hipSuccess) return KIMAD_ERR_HIP;
     }
     return KIMAD_OK;

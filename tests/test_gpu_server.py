@@ -192,3 +192,26 @@ def test_layer_counts_around_the_lds_table_and_workers_that_share_an_estimator(L
         hats[into][pos] += p[2]
     for m in (0, 1) if shared else (0, 1, 2):
         assert np.array_equal(dev[m].cpu().numpy().view(np.uint32), hats[m].view(np.uint32)), m
+
+
+@pytest.mark.parametrize("M,d", [(1, (28 << 20) - 1), (1, 28 << 20), (1, (192 << 20) + 262144), (2, (28 << 20) + 3), (3, 64 << 20),
+                                 (3, (64 << 20) + 262144), (4, 28 << 20)])
+def test_model_step_with_ordinary_and_with_nontemporal_stores(M, d):
+    # the sizes around which the model's stores change kind; every element against the same fp64 sums, element by element
+    import torch
+    import paper_2312_08053_amd as kimad
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M)
+    hats = [torch.randn(d, generator=gen, device="cuda") for _ in range(M)]
+    x = torch.randn(d, generator=gen, device="cuda")
+    w, gamma = [0.25 + 0.125 * m for m in range(M)], 0.037
+    acc = torch.zeros(d, dtype=torch.float64, device="cuda")
+    for m in range(M):
+        acc = acc + w[m] * hats[m].double()
+    want = (x.double() - gamma * acc).float()
+    none = torch.zeros(1, dtype=torch.int32, device="cuda")
+    payload = (none, torch.zeros(1, device="cuda"), torch.zeros(2, dtype=torch.int64, device="cuda"))
+    starts = torch.tensor([0, d], dtype=torch.int64, device="cuda")
+    status = kimad.kimad_server_apply([payload] * M, hats, w, starts, d, x, gamma)
+    assert status.cpu().tolist() == [0] * M
+    assert torch.equal(x.view(torch.int32), want.view(torch.int32))
