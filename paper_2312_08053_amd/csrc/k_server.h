@@ -100,18 +100,17 @@ __global__ __launch_bounds__(256) void k_server_decode(DecodeArgs a, uint32_t fi
 // Nontemporal stores keep the model's lines from displacing the estimators' in passing, but then the next round
 // cannot find the model in the 256 MB cache either.  Whole calls with small payloads, round after round, us with ordinary
 // and with nontemporal stores:
-//     model (MiB)  1 worker       2 workers      3 workers      4 workers
-//      64          53   49        64   62        78   76        91   89
-//     128          83   85       108  112       133  136       161  166
-//     192 MB      112  117       151  158       190  201       219  227
-//     256 MB      141  152       204  213       249  248       314  302
-//     448 MB      250  260       408  361       513  427       619  509
-//     800 MB      447  452       694  616       877  739      1035  872
-//    1000          580  553       852  764      1064  919
-// (six to sixteen workers: equal up to 192 MB, nontemporal 7 to 20 % faster from 256 MB on; after a gigabyte of other
-// memory was written in between, nontemporal stores are as fast or faster at every size).  Ordinary stores where they win by
-// more than the runs differ (four workers have the single
-// decode launch to more than make up for it):
+//     model (MiB)  1 worker    2 workers   3 workers   4 workers
+//       64          53  49      64  62      78  76      91  89
+//      128          83  85     108 112     133 136     161 166
+//      192         112 117     151 158     190 201     219 227
+//      256         141 152     204 213     249 248     314 302
+//      448         250 260     408 361     513 427     619 509
+//      800         447 452     694 616     877 739    1035 872
+//     1000         580 553     852 764    1064 919
+// (Six to sixteen workers: equal up to 192 MiB, nontemporal 7 to 20 % faster from 256 on.  After a gigabyte of other memory
+// was written in between, nontemporal stores are as fast or faster at every size.)  Ordinary stores where they win in the
+// table, but for four workers, whose one decode launch gives more than that:
 inline bool model_stores_stream(uint32_t M, uint64_t d) {
     const uint64_t mib = 4 * d >> 20;
     return !(mib >= 112 && (M == 1 ? mib <= 768 : M <= 3 && mib <= 256));
