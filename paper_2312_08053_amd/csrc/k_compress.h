@@ -433,7 +433,7 @@ __global__ __launch_bounds__(256) void k_resolve(CompressBuffers cb) {
 // Per chunk: how many candidates lie above tau and how many equal it.
 
 // Layers served from g and h (SEL_DIRECT with a threshold): one wave per chunk with an entry in the threshold's
-// prefix bin, all of its loads in flight together.  Tiles in a grid-stride loop, as in the compaction.
+// prefix bin, half a chunk of loads in flight together.  Tiles in a grid-stride loop, as in the compaction.
 // (Four lanes of the candidates' half of this launch read such a chunk one element at a time before: 256 dependent
 // memory round trips.  Six tensors of 266 K elements in all: 59 us, now 4; ResNet-50 with two fifths of its bytes sent:
 // 63 us, now 8.)
@@ -452,19 +452,24 @@ __device__ __forceinline__ void count_direct_tiles(const CompressBuffers& cb, ui
             const uint32_t chunk = L.chunk0 + chunk_in_layer;
             uint32_t gt = cb.rec_cnt[chunk], eq = 0u;
             if (cb.rec_amb[chunk] != 0u) {       // (else every entry at or above the prefix is above tau)
-                QuadGH q[NQ];
-                uint32_t valid;
-                load_chunk<NQ>(L, chunk_in_layer * CHUNK, q, valid);
                 uint32_t both = 0u;              // above in the low half, equal in the high half: at most 1024 each
+                // (half a chunk at a time: a whole one took this kernel past the 64 registers that eight waves a SIMD leave)
+                constexpr uint32_t HALF = NQ / 2u;
+#pragma unroll 1
+                for (uint32_t v0 = chunk_in_layer * CHUNK; v0 < (chunk_in_layer + 1u) * CHUNK; v0 += CHUNK / 2u) {
+                    QuadGH q[HALF];
+                    uint32_t valid;
+                    load_chunk<(int)HALF>(L, v0, q, valid);
 #pragma unroll
-                for (int u = 0; u < (int)NQ; ++u)
+                    for (int u = 0; u < (int)HALF; ++u)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const uint32_t key = key_of(q[u].g[c] - q[u].h[c]);
-                        const bool in = (valid >> (4 * u + c)) & 1u;
-                        both += in && key > tau ? 1u : 0u;
-                        both += in && key == tau ? 0x10000u : 0u;
-                    }
+                        for (int c = 0; c < 4; ++c) {
+                            const uint32_t key = key_of(q[u].g[c] - q[u].h[c]);
+                            const bool in = (valid >> (4 * u + c)) & 1u;
+                            both += in && key > tau ? 1u : 0u;
+                            both += in && key == tau ? 0x10000u : 0u;
+                        }
+                }
                 both = wave_scan_add_u32(both);
                 both = (uint32_t)__builtin_amdgcn_readlane((int)both, 63);
                 gt = both & 0xFFFFu; eq = both >> 16;

@@ -30,6 +30,18 @@ def test_library_exports_every_declared_symbol():
     assert sorted(kimad.EXPORTED_SYMBOLS) == _declared()
 
 
+def test_no_kernel_uses_scratch_memory():
+    """Every kernel's record in the code object (MessagePack: the key, then an unsigned integer) says how much memory a lane
+    has for registers that were spilled; a launch sets it up for every wave, needed or not."""
+    import paper_2312_08053_amd as kimad
+    blob, key, sizes = open(kimad.LIB_PATH, "rb").read(), b".private_segment_fixed_size", []
+    for m in re.finditer(re.escape(key), blob):
+        v = blob[m.end():m.end() + 5]
+        wide = {0xcc: 1, 0xcd: 2, 0xce: 4}.get(v[0], 0)
+        sizes.append(int.from_bytes(v[1:1 + wide], "big") if wide else v[0])
+    assert len(sizes) > 30 and not any(sizes), sizes
+
+
 def test_host_side_argument_checks_need_no_gpu():
     import paper_2312_08053_amd as kimad
     assert kimad.kimad_workspace_bytes([100, 20000], 8) > 0
