@@ -319,10 +319,10 @@ __global__ __launch_bounds__(BOUNDS_THREADS) void k_dp_bounds(AllocBuffers ab, D
         if (tid == 0) s_cum[0] = 0u;
     }
     const double ub_m = ub + 1e-9 * (fabs(ub) + abs_tot);
-    if (!(ub_m - ub_m == 0.0) || !(gentle <= 1e300)) {                        // sums beyond the doubles, or one vertex per layer
-        if (!(ub_m - ub_m == 0.0)) { whole_rows(false); return; }
-        gentle = 0.0;
-    }
+    // Errors times costs must stay inside the doubles (a hull test whose products overflow drops true vertices, and the bound
+    // is none), and the margin above the smallest denormal times the layers.
+    if (!(abs_tot <= 1e290) || (abs_tot > 0.0 && abs_tot < 1e-290)) { whole_rows(false); return; }
+    if (!(gentle <= 1e300)) gentle = 0.0;                                     // one vertex per layer
 
     // ---- 4: multipliers around lam_star (around the least steep slope if everything fits); per (layer, multiplier) the
     // minimum, summed over the layers

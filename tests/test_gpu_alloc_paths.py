@@ -126,6 +126,23 @@ def test_nonfinite_tables_are_reported_by_both_paths():
         assert info["whole_rows"] == 1
 
 
+@pytest.mark.parametrize("largest", [1.7e308, 1e307, 1e300, 1e-290, 1e-310, 1e-318, 5e-322])
+def test_tables_at_the_ends_of_the_doubles(largest):
+    """Products of errors and costs that overflow, and errors of a few units of the smallest denormal, must not mislead
+    the bounds: a band that leaves out the optimal path is a wrong allocation."""
+    rng = np.random.default_rng(5)
+    for trial in range(40):
+        L, J = int(rng.integers(2, 12)), int(rng.integers(3, 16))
+        ratios = np.append(np.sort(rng.uniform(0.01, 0.99, size=J)), 1.0)
+        sizes = [int(x) for x in rng.integers(3000, 100000, size=L)]
+        K = np.array([ko.grid_sizes(ratios, n) for n in sizes], dtype=np.float64)
+        n = np.array(sizes, dtype=np.float64)[:, None]
+        E = rng.uniform(0.2, 1.0, size=(L, 1)) * (1.0 - K / n) ** rng.uniform(1, 14, size=(L, 1))
+        if trial % 2:
+            E = E * rng.uniform(0.9, 1.0, size=E.shape)
+        _check(sizes, ratios, E * (largest / L), int(rng.uniform(0.05, 0.6) * 8 * sum(sizes)), int(rng.choice([1000, 2000, 4000])))
+
+
 def test_many_layers_and_many_list_records():
     rng = np.random.default_rng(16)
     # 600 layers of 10 ratios: the multiplier table falls back to 8 columns, one thread a row
