@@ -316,8 +316,7 @@ int kimad_plan_get_timings(kimad_plan_t* plan, char* names, uint32_t names_bytes
  *   out_f64[(4 k + u) * 64 + lane]         = in_f64[lane] + in_f64[64 + 16 (lane / 16) + 4 k + u]
  *   out_f64[1024 + 64 t + lane]            = max of in_f64 over the lane's aligned group of 2, 4, 8 lanes (t = 0, 1, 2)
  *   out_f64[1216 + 64 t + lane]            = min of in_f64 over the lane's aligned group of 2, 4, 8, 16 lanes (t = 0..3)
- *   out_u32[1088 + 64 t + lane]            = the smallest in_u32[64 + l] & 255 among the lanes l of that group that hold
- *                                            this minimum (the pair minimum of the banded recurrence) */
+ *   out_u32[1088 + 64 t + lane]            = in_u32[lane xor 1, 2, 4, 8] (t = 0..3) */
 int kimad_selftest_wave_primitives(const uint32_t* in_u32, const double* in_f64, uint32_t* out_u32, double* out_f64,
                                    void* stream);
 

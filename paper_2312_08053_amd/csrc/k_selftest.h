@@ -6,23 +6,9 @@
 #include "common.h"
 #include "k_alloc.h"
 #include "k_alloc_band.h"
+#include "k_profile.h"
 
 namespace kimad {
-
-// (total, record) of another lane of the group; the smaller pair stays: the moves of group_min, with a second word along
-template <int CTRL>
-__device__ __forceinline__ void take_min_dpp(double& t, uint32_t& k) {
-    const double ot = dpp_f64<CTRL>(t);
-    const uint32_t ok = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, CTRL, 0xF, 0xF, false);
-    if (ot < t || (ot == t && ok < k)) { t = ot; k = ok; }
-}
-template <int NP>
-__device__ __forceinline__ void group_min_pair(double& t, uint32_t& k) {
-    if (NP >= 2) take_min_dpp<0xB1>(t, k);       // quad_perm [1,0,3,2]
-    if (NP >= 4) take_min_dpp<0x4E>(t, k);       // quad_perm [2,3,0,1]
-    if (NP >= 8) take_min_dpp<0x141>(t, k);      // row_half_mirror: the other quad of the eight
-    if (NP >= 16) take_min_dpp<0x140>(t, k);     // row_mirror: the other eight of the sixteen
-}
 
 // out_u32: [0, 64) inclusive add-scan of in_u32 over the lanes;
 //          [64 + (k4 * 4 + u) * 64 + lane] = in_u32[lane] + in_u32[64 + 16 * (lane / 16) + 4 * k4 + u]
@@ -30,9 +16,8 @@ __device__ __forceinline__ void group_min_pair(double& t, uint32_t& k) {
 // out_f64: [(k4 * 4 + u) * 64 + lane] = in_f64[lane] + in_f64[64 + 16 * (lane / 16) + 4 * k4 + u]
 //          (acc_rec_error4: the accumulator plus the error of lane K + u of the row)
 //          [1024 + t * 64 + lane], t = 0, 1, 2: maximum of in_f64 over the lane's group of 2, 4, 8 lanes (group_max)
-//          [1216 + t * 64 + lane], t = 0..3: the smallest in_f64 of the lane's group of 2, 4, 8, 16 lanes, and
-// out_u32: [1088 + t * 64 + lane]: the smallest in_u32[64 + lane'] & 255 among the lanes of the group that hold it
-//          (group_min_pair: the minimum of (value, record) pairs, the value first)
+//          [1216 + t * 64 + lane], t = 0..3: minimum of in_f64 over the lane's group of 2, 4, 8, 16 lanes (group_min)
+// out_u32: [1088 + t * 64 + lane], t = 0..3: in_u32[lane xor 1, 2, 4, 8] (lane_xor_u32; its wider moves are shuffles)
 __global__ __launch_bounds__(64) void k_selftest_wave(const uint32_t* in_u32, const double* in_f64, uint32_t* out_u32,
                                                       double* out_f64) {
     const uint32_t lane = threadIdx.x;
@@ -59,14 +44,14 @@ __global__ __launch_bounds__(64) void k_selftest_wave(const uint32_t* in_u32, co
     out_f64[1024 + lane] = group_max<2>(acc);
     out_f64[1024 + 64 + lane] = group_max<4>(acc);
     out_f64[1024 + 128 + lane] = group_max<8>(acc);
-    {
-        double v;
-        uint32_t k;
-        v = acc; k = second & 255u; group_min_pair<2>(v, k); out_f64[1216 + lane] = v; out_u32[1088 + lane] = k;
-        v = acc; k = second & 255u; group_min_pair<4>(v, k); out_f64[1216 + 64 + lane] = v; out_u32[1088 + 64 + lane] = k;
-        v = acc; k = second & 255u; group_min_pair<8>(v, k); out_f64[1216 + 128 + lane] = v; out_u32[1088 + 128 + lane] = k;
-        v = acc; k = second & 255u; group_min_pair<16>(v, k); out_f64[1216 + 192 + lane] = v; out_u32[1088 + 192 + lane] = k;
-    }
+    out_f64[1216 + lane] = group_min<2>(acc);
+    out_f64[1216 + 64 + lane] = group_min<4>(acc);
+    out_f64[1216 + 128 + lane] = group_min<8>(acc);
+    out_f64[1216 + 192 + lane] = group_min<16>(acc);
+    out_u32[1088 + lane] = lane_xor_u32<1>(base);
+    out_u32[1088 + 64 + lane] = lane_xor_u32<2>(base);
+    out_u32[1088 + 128 + lane] = lane_xor_u32<4>(base);
+    out_u32[1088 + 192 + lane] = lane_xor_u32<8>(base);
 }
 
 }  // namespace kimad

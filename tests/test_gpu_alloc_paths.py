@@ -2,8 +2,8 @@
 one inside the band that Lagrangian bounds leave must both return the oracle's dynamic programme (Appendix C)
 bit for bit: the chosen j per layer, K, the offsets and the status.  The tables here are drawn to stress what the
 band's construction leans on: convex and non-convex rows, runs of equal costs and equal errors, ties between
-totals, one layer, one ratio, ample and starved budgets, non-finite entries, more layers than its multiplier
-table of 32 holds, more list records than its LDS holds."""
+totals, one layer, one ratio, ample and starved budgets, non-finite entries, many layers, more list records than the
+bounds kernel takes."""
 import numpy as np
 import pytest
 
@@ -145,14 +145,15 @@ def test_tables_at_the_ends_of_the_doubles(largest):
 
 def test_many_layers_and_many_list_records():
     rng = np.random.default_rng(16)
-    # 600 layers of 10 ratios: the multiplier table falls back to 8 columns, one thread a row
+    # 600 layers of 10 ratios: several layers to a group of the multiplier sums, two trips of the band search, and the greedy
+    # fill's edges read again every round (more than 256 layers)
     ratios = np.logspace(-3, 0, 10)
     sizes = [int(x) for x in rng.integers(50000, 400000, size=600)]
     E = _convex_table(rng, sizes, ratios, -2, 2)
     d = sum(sizes)
     _check(sizes, ratios, E, int(0.3 * 8 * d), 4000, expect_band=True)
-    # 230 layers x 64 ratios with mostly distinct costs: more list records than the bounds kernel holds in LDS,
-    # so it declares whole rows and the recurrence visits every cell: same result
+    # 230 layers x 64 ratios with mostly distinct costs: more list records than the bounds kernel takes (they set its LDS
+    # for the hulls' vertices), so it declares whole rows and the recurrence visits every cell: same result
     ratios = np.logspace(-4, 0, 64)
     sizes = [int(x) for x in rng.integers(3000000, 4000000, size=230)]
     E = _convex_table(rng, sizes, ratios, -2, 2)

@@ -20,7 +20,7 @@ def test_every_lane_of_the_dpp_primitives(seed):
         u = rng.integers(0, 1 << 20, size=128).astype(np.uint32)
         f = rng.standard_normal(128) * 10.0 ** rng.uniform(-3, 3, size=128)
     if seed == 3:
-        f[:64] = np.round(f[:64] / np.abs(f[:64]).max() * 3.0)     # few distinct values: the pair minimum must break ties by the record
+        f[:64] = np.round(f[:64] / np.abs(f[:64]).max() * 3.0)     # few distinct values, most of them tied
     u[64:] = (0 - u[64:].astype(np.int64)).astype(np.uint32) if seed == 2 else u[64:]   # negated costs, as the recurrence passes them
     in_u = torch.from_numpy(u.view(np.int32).copy()).cuda()
     in_f = torch.from_numpy(f.copy()).cuda()
@@ -42,11 +42,8 @@ def test_every_lane_of_the_dpp_primitives(seed):
     for t, width in enumerate((2, 4, 8)):
         want = f[:64].reshape(-1, width).max(axis=1).repeat(width)
         assert np.array_equal(got_f[1024 + 64 * t:][:64], want), width
-    rec = u[64:] & 255
     for t, width in enumerate((2, 4, 8, 16)):
-        v = f[:64].reshape(-1, width)
-        r = rec.reshape(-1, width)
-        vmin = v.min(axis=1)
-        rmin = np.where(v == vmin[:, None], r, 256).min(axis=1)
-        assert np.array_equal(got_f[1216 + 64 * t:][:64], vmin.repeat(width)), width
-        assert np.array_equal(got_u[1088 + 64 * t:][:64], rmin.repeat(width).astype(np.uint32)), width
+        want = f[:64].reshape(-1, width).min(axis=1).repeat(width)
+        assert np.array_equal(got_f[1216 + 64 * t:][:64], want), width
+    for t, away in enumerate((1, 2, 4, 8)):
+        assert np.array_equal(got_u[1088 + 64 * t:][:64], u[lanes ^ away]), away
