@@ -445,11 +445,16 @@ __global__ __launch_bounds__(BOUNDS_THREADS) void k_dp_bounds(AllocBuffers ab, D
 // member of a winner's run with the same rounded total, sizes and offsets follow for all layers in parallel.
 //
 // A layer costs what its instructions take to issue (a wave issues one every 8 to 10 cycles whatever it waits for) and the
-// barrier: about 0.85 us with the walk, however few cells there are.  Four waves serve bands of up to some two hundred
-// cells best, sixteen the wide ones: 134 against 176 us at a mean width of 74 cells (148 layers, rows of 4097 cells), 233
-// against 230 at 187.  One loop that also kept winner and source cell of every cell, by sixteen waves, took 176 us there.
+// barrier: about 0.85 us with the walk, however few cells there are (0.75 where a layer has one or two records, which
+// get a form of their own).  Four waves serve the narrow bands, sixteen the wide ones: 134 against 176 us at a mean width
+// of 74 cells (148 layers, rows of 4097 cells), 233 against 230 at 187.  (Eight waves: 145 and 209; they would cost every
+// allocation a third launch of 4 us.)  With fewer ratios there is less work in a cell, and four waves serve wider bands
+// as well: 500 layers with 5 ratios at a mean width of 157, 699 us by sixteen and 603 by four; 148 layers with 2 ratios
+// at 819, 264 and 313.  One loop that also kept winner and source cell of every cell, by sixteen waves, took 211 us on
+// the headline set, where these two kernels take 187 and 4; it was faster with two or three ratios only (500 layers,
+// 3 ratios, rows of 4097 cells: 629 us, now 667).
 constexpr uint32_t BANDED_NARROW = 256, BANDED_WIDE = 1024;   // threads, for narrow and for wide bands
-constexpr uint32_t BANDED_MEAN = 128;           // mean width of a row up to which the bands are narrow
+constexpr uint32_t BANDED_MEAN = 128;           // mean width of a row up to which the bands are narrow (16 ratios or more; wider with fewer)
 constexpr uint32_t BAND_LIVE_CAP = 2048;       // live records held in LDS at a time
 constexpr uint32_t BAND_CELLS = 12288;         // row cells held in LDS (96 KB); two of the longest rows fit
 static_assert(2u * DP_PAD_WIDE <= BAND_CELLS, "two rows fit");
@@ -464,33 +469,34 @@ __device__ __forceinline__ BandRow band_row(const uint4& v) {
     return b;
 }
 
-// One layer: NP lanes per cell.  lrec, n: the layer's records; prow, crow: where the previous row and this one start in
+// One layer: NP lanes per cell, U records of a lane at a time.  lrec, n: the layer's records; prow, crow: where the previous row and this one start in
 // `rows`, whose cell BAND_CELLS holds +inf; out: the row's copy in memory, or null.
-template <int NP, uint32_t T>
+template <int NP, uint32_t T, int U = 4>
 __device__ __forceinline__ void banded_layer(const uint4* lrec, double* rows, uint32_t prow, uint32_t crow, double* out, uint32_t n,
                                              const BandRow& p, const BandRow& c) {
     const uint32_t tid = threadIdx.x, sub = tid % NP, shift = c.lo - p.lo;      // (may wrap: so does the source below, beyond the span)
     for (uint32_t c0 = 0; c0 <= c.span; c0 += T / NP) {
         const uint32_t cell = c0 + tid / NP, cm = cell + shift;
         double best = DP_INF;
-        for (uint32_t k = sub; k < n; k += 4u * NP) {
-            // four records, then four cells: two LDS round trips, not eight (left to itself the compiler waits for each)
-            uint4 r[4];
-            double v[4];
+        for (uint32_t k = sub; k < n; k += (uint32_t)U * NP) {
+            // U records, then U cells: two LDS round trips, not 2 U (left to itself the compiler waits for each)
+            uint4 r[U];
+            double v[U];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) r[u] = lrec[min(k + (uint32_t)u * NP, n - 1u)];   // (positions past the last record repeat it, which changes no minimum)
+            for (int u = 0; u < U; ++u) r[u] = lrec[min(k + (uint32_t)u * NP, n - 1u)];   // (positions past the last record repeat it, which changes no minimum)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { materialise(r[u].x); materialise(r[u].y); materialise(r[u].z); }
+            for (int u = 0; u < U; ++u) { materialise(r[u].x); materialise(r[u].y); materialise(r[u].z); }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const uint32_t src = cm - r[u].z;                               // a cell cheaper than the record wraps far beyond the span
                 v[u] = rows[src <= p.span ? prow + src : BAND_CELLS];
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) asm volatile("" ::"v"(v[u]));
+            for (int u = 0; u < U; ++u) asm volatile("" ::"v"(v[u]));
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] += rec_err(r[u]);
-            best = min_f64(min_f64(best, v[0]), min_f64(v[1], min_f64(v[2], v[3])));
+            for (int u = 0; u < U; ++u) v[u] += rec_err(r[u]);
+#pragma unroll
+            for (int u = 0; u < U; ++u) best = min_f64(best, v[u]);
         }
         best = group_min<NP>(best);
         if (sub == 0u && cell <= c.span) {
@@ -517,7 +523,7 @@ __global__ __launch_bounds__(T) void k_dp_banded(AllocBuffers ab, DpLists dl, Ba
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t L = ab.L, J = ab.J, cap = ab.cap;
     // one of the two launches does the work: the bands' widths, known here only, say which
-    if ((bb.info[1] <= BANDED_MEAN * L) != (T == BANDED_NARROW)) return;
+    if (((uint64_t)bb.info[1] * min(max(J, 4u), 16u) <= (uint64_t)BANDED_MEAN * 16u * L) != (T == BANDED_NARROW)) return;
     if (tid == 0) s_bad = 0u;
     __syncthreads();
     // rows and records: running sums over the layers
@@ -592,7 +598,8 @@ __global__ __launch_bounds__(T) void k_dp_banded(AllocBuffers ab, DpLists dl, Ba
                 const uint32_t w = c.span + 1u;
                 const uint32_t np = min(n <= 4u ? 1u : n <= 8u ? 2u : n <= 16u ? 4u : n <= 32u ? 8u : 16u,
                                         w <= T / 16u ? 16u : w <= T / 8u ? 8u : w <= T / 4u ? 4u : w <= T / 2u ? 2u : 1u);
-                if (np == 1u) banded_layer<1, T>(lrec, rows, prow, crow, out, n, p, c);
+                if (n <= 2u) banded_layer<1, T, 2>(lrec, rows, prow, crow, out, n, p, c);
+                else if (np == 1u) banded_layer<1, T>(lrec, rows, prow, crow, out, n, p, c);
                 else if (np == 2u) banded_layer<2, T>(lrec, rows, prow, crow, out, n, p, c);
                 else if (np == 4u) banded_layer<4, T>(lrec, rows, prow, crow, out, n, p, c);
                 else if (np == 8u) banded_layer<8, T>(lrec, rows, prow, crow, out, n, p, c);

@@ -304,6 +304,11 @@ uint64_t cost_unit(const kimad_config_t& cfg, uint64_t P) {
 // Rows from this many cost cells on take the banded recurrence by themselves.  (148 layers: 175 us against 530 at 4097
 // cells.  At 1000 cells 162 against 155, and 290 against 144 where the bands are wide, as on ResNet-50's table.)
 constexpr uint64_t BAND_AUTO_CELLS = 1537;
+// With few ratios the lists are short and whole rows cheap, as long as a thread has no more than four cells: 500 layers
+// with 5 ratios 433 us against 563 in the band at 1601 cells, 448 against 521 at 2001 and 631 against 578 at 2601; with 7
+// ratios 462 against 551 and 477 against 477, with 10 531 against 559 but for 148 layers 193 against 180.
+constexpr uint32_t WHOLE_ROWS_J = 7;
+constexpr uint64_t WHOLE_ROWS_CELLS = 2048;
 constexpr uint32_t FALLBACK_GRID = 1024;   // workgroups of a pass that usually has nothing to do
 
 __global__ __launch_bounds__(256) void k_zero16(uint4* p, uint64_t n16) {
@@ -587,7 +592,8 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
         double* rows_g = ws.rows_g;
         const uint32_t rstride = ws.rstride;
         const bool band = lo.L <= BAND_MAX_L && !(p->cfg.flags & KIMAD_CFG_FULL_DP) &&
-                          ((p->cfg.flags & KIMAD_CFG_BAND_DP) || cap + 1 >= BAND_AUTO_CELLS);
+                          ((p->cfg.flags & KIMAD_CFG_BAND_DP) ||
+                           (cap + 1 >= BAND_AUTO_CELLS && !(lo.J <= WHOLE_ROWS_J && cap + 1 <= WHOLE_ROWS_CELLS)));
         KLAUNCH(p, s, "k_dp_prep", k_dp_prep, dim3(lo.L), dim3(64), ab, dl, band ? 1u : 0u);
         if (band) {
             // the recurrence inside the band of cells that Lagrangian bounds leave (same result, a fraction of the cells)
