@@ -98,22 +98,28 @@ __global__ __launch_bounds__(256) void k_server_decode(DecodeArgs a, uint32_t fi
 // compile time, 557; two or four quads a thread and runs of blocks per XCD were slower as well.)
 //
 // Nontemporal stores keep the model's lines from displacing the estimators' in passing, but then the next round
-// cannot find the model in the 256 MB cache either.  Whole calls with small payloads, round after round, us with ordinary
+// cannot find the model in the 256 MB cache either.  Ten rounds back to back with small payloads, us a round with ordinary
 // and with nontemporal stores:
 //     model (MiB)  1 worker    2 workers   3 workers   4 workers
-//       64          53  49      64  62      78  76      91  89
-//      128          83  85     108 112     133 136     161 166
-//      192         112 117     151 158     190 201     219 227
-//      256         141 152     204 213     249 248     314 302
-//      448         250 260     408 361     513 427     619 509
-//      800         447 452     694 616     877 739    1035 872
-//     1000         580 553     852 764    1064 919
+//       48          36  33      45  43      55  53      63  62
+//       80          51  50      67  68      84  83      99  97
+//       96          59  58      78  79      95  98     111 113
+//      128          74  75      98 105     120 126     145 150
+//      192         105 112     140 149     175 190     212 217
+//      256         134 144     190 196     239 239     298 284
+//      288         151 161     216 220     296 269     370 319
+//      320         170 179     273 244     353 298     425 363
+//      448         247 255     398 350     509 414     611 503
+//      576         307 320     528 445     643 537     774 635
+//      720         420 401     647 550     788 664     951 783
+//     1000         586 555     851 755    1069 914    1307 1087
 // (Six to sixteen workers: equal up to 192 MiB, nontemporal 7 to 20 % faster from 256 on.  After a gigabyte of other memory
-// was written in between, nontemporal stores are as fast or faster at every size.)  Ordinary stores where they win in the
-// table, but for four workers, whose one decode launch gives more than that:
+// was written in between, nontemporal stores are as fast or faster at every size.)  So ordinary stores for models of
+// 96 MiB and more as long as model and estimators together are at most three and a half times the cache, with one worker
+// five times.
 inline bool model_stores_stream(uint32_t M, uint64_t d) {
     const uint64_t mib = 4 * d >> 20;
-    return !(mib >= 112 && (M == 1 ? mib <= 768 : M <= 3 && mib <= 256));
+    return mib < 96 || (M + 1) * mib > (M == 1 ? 1280 : 896);
 }
 // (A template: a branch between the two stores is merged into one ordinary store by the compiler.)
 template <bool STREAM_STORES>

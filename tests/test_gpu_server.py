@@ -194,8 +194,8 @@ def test_layer_counts_around_the_lds_table_and_workers_that_share_an_estimator(L
         assert np.array_equal(dev[m].cpu().numpy().view(np.uint32), hats[m].view(np.uint32)), m
 
 
-@pytest.mark.parametrize("M,d", [(1, (28 << 20) - 1), (1, 28 << 20), (1, (192 << 20) + 262144), (2, (28 << 20) + 3), (3, 64 << 20),
-                                 (3, (64 << 20) + 262144), (4, 28 << 20)])
+@pytest.mark.parametrize("M,d", [(1, (24 << 20) - 1), (1, 24 << 20), (1, (160 << 20) + 262144), (2, (24 << 20) + 3),
+                                 (2, (74 << 20) + 262145), (3, 56 << 20), (3, (56 << 20) + 262144), (4, 24 << 20), (16, 1 << 20)])
 def test_model_step_with_ordinary_and_with_nontemporal_stores(M, d):
     # the sizes around which the model's stores change kind; every element against the same fp64 sums, element by element
     import torch
