@@ -954,8 +954,9 @@ __global__ __launch_bounds__(256) void k_hist2c(ProfileBuffers pb) {
 // The same where the slots hold many entries (the grid's smallest ratio is no small share of the layer): the additions
 // queue up on the slots' few lines, so the layer that has a fair share of a workgroup's 256 chunks is counted in LDS, in
 // the packed form of the streaming pass, and added to the layer's tables once; other layers' candidates go there one by
-// one.  (ResNet-18 with the paper's grid: 39 to 71 us one by one, 15 so.  The headline set, whose slots are sparse, takes
-// 21 us this way instead of 16, the Llama-shaped one 101 instead of 87.)
+// one.  (The paper's grid, one by one and so: ResNet-18 32 and 20 us, ResNet-50 128 and 32, the GPT-2-shaped set 208 and 29,
+// the Llama-shaped one 942 and 150.  Logarithmic grids from a thousandth or less: 14 to 19 and 19 to 22 us GPT-2-shaped, 17
+// to 60 and 26 to 89 Llama-shaped; from more than a 512th on they need no such slots, and both kernels find nothing to do.)
 constexpr uint32_t DENSE_THREADS = 1024;
 constexpr uint32_t DENSE_CHUNKS = DENSE_THREADS / SUB_HIST;
 constexpr uint32_t DENSE_SHARE = 64;           // chunks of one layer from which on the table in LDS pays

@@ -924,7 +924,8 @@ int kimad_compress_ef(kimad_plan_t* p, const uint64_t* K, const uint64_t* offset
     if (!reuse) {
         // Select from scratch, one target per layer: by the single pass over g and h that the profile takes, whose
         // candidates then serve the selection.  (Two histogram passes and a compaction, three reads of g and h, take
-        // 811 us on the headline set at half a percent of the entries, this 337; KIMAD_CFG_CLASSIC_PROFILE keeps them.)
+        // 811 us on the headline set at half a percent of the entries, this 337, and 900 in a round whose every layer the
+        // prediction misses, as when all gradients are 64 times the round before's; KIMAD_CFG_CLASSIC_PROFILE keeps them.)
         uint32_t* ksel = at<uint32_t>(p, lo.ksel);
         KLAUNCH(p, s, "k_make_ksel", k_make_ksel, dim3((lo.L + 255) / 256), dim3(256), K, cb.layers, lo.L, ksel);
         hipStream_t unused = s;
