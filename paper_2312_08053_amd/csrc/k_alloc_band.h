@@ -154,8 +154,8 @@ __device__ __forceinline__ uint32_t greedy_fill(const double* HE, const uint32_t
 //      consecutive layers sums its layers, the groups' totals are added up afterwards;
 //   5  the band of every row by a search outward from the assignment's own cell, four threads to an edge;
 //   6  the live records of every layer.
-// A chain of short phases, each a few LDS round trips: 94 us with the hulls, serial sums and the live records' copies in
-// it, 41 us now on the headline set's table at 4097 cells (148 layers).
+// A chain of short phases, each a few LDS round trips: 92 us with the hulls, serial sums and the live records' copies in
+// it, 47 us now on the headline set's table at 4097 cells (148 layers).
 __global__ __launch_bounds__(BOUNDS_THREADS) void k_dp_bounds(AllocBuffers ab, DpLists dl, BandBuffers bb) {
     constexpr uint32_t NWAVES = BOUNDS_THREADS / 64;
     __shared__ double HE[BAND_LCAP];                                    // 56 KB: vertex errors
@@ -450,8 +450,8 @@ __global__ __launch_bounds__(BOUNDS_THREADS) void k_dp_bounds(AllocBuffers ab, D
 // of 74 cells (148 layers, rows of 4097 cells), 233 against 230 at 187.  (Eight waves: 145 and 209; they would cost every
 // allocation a third launch of 4 us.)  With fewer ratios there is less work in a cell, and four waves serve wider bands
 // as well: 500 layers with 5 ratios at a mean width of 157, 699 us by sixteen and 603 by four; 148 layers with 2 ratios
-// at 819, 264 and 313.  One loop that also kept winner and source cell of every cell, by sixteen waves, took 211 us on
-// the headline set, where these two kernels take 187 and 4; it was faster with two or three ratios only (500 layers,
+// at 819, 264 and 313.  One loop that also kept winner and source cell of every cell, by sixteen waves, took 212 us on
+// the headline set, where these two launches take 191 and 4; it was faster with two or three ratios only (500 layers,
 // 3 ratios, rows of 4097 cells: 629 us, now 667).
 constexpr uint32_t BANDED_NARROW = 256, BANDED_WIDE = 1024;   // threads, for narrow and for wide bands
 constexpr uint32_t BANDED_MEAN = 128;           // mean width of a row up to which the bands are narrow (16 ratios or more; wider with fewer)
