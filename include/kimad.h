@@ -203,7 +203,7 @@ int kimad_allocate_static(kimad_plan_t* plan, const double* err_table, uint64_t 
  *   K        DEVICE uint64[L], each 0..n_i
  *   offsets  DEVICE uint64[L+1], offsets[i] + K[i] <= capacity_pairs for every i
  *   idx_out  DEVICE uint32[capacity_pairs];  val_out DEVICE float[capacity_pairs]
- *   flags    0 (select from scratch: an extra pass over g, h) or KIMAD_REUSE_PROFILE
+ *   flags    0 (select from scratch: one to three passes over g, h) or KIMAD_REUSE_PROFILE
  *   status_out DEVICE int32[1] */
 int kimad_compress_ef(kimad_plan_t* plan, const uint64_t* K, const uint64_t* offsets,
                       uint32_t* idx_out, void* val_out /* float[], or uint16[] with KIMAD_VALUES_F16 */,

@@ -310,6 +310,15 @@ constexpr uint64_t BAND_AUTO_CELLS = 1537;
 constexpr uint32_t WHOLE_ROWS_J = 7;
 constexpr uint64_t WHOLE_ROWS_CELLS = 2048;
 constexpr uint32_t FALLBACK_GRID = 1024;   // workgroups of a pass that usually has nothing to do
+// A selection from scratch takes the single pass from this many chunks in tiled layers on, if these hold this many each on
+// average; below, its four more launches and its tables per layer cost more than the two reads of g and h it saves.
+// A hundredth kept, single pass and two histogram passes with a compaction, us: 4 layers 81 and 71 at 1 M elements, 95 and
+// 118 at 4 M; 60 layers 93 and 90 at 2.4 M, 101 and 133 at 6 M; one layer 98 and 93 at 2 M, 126 and 130 at 4 M, 134 and 196
+// at 8 M.  2000 layers of 9000 to 16000 elements 10 to 20 % the other way, of 24000 644 and 670.  On the headline set at
+// half a percent 337 and 811, and 900 in a round whose every layer the prediction misses, as when all gradients are 64
+// times the round before's.
+constexpr uint32_t SINGLE_SELECT_CHUNKS = 3072;
+constexpr uint32_t SINGLE_SELECT_PER_LAYER = 24;
 
 __global__ __launch_bounds__(256) void k_zero16(uint4* p, uint64_t n16) {
     const uint64_t stride = (uint64_t)gridDim.x * 256u;
@@ -920,16 +929,16 @@ int kimad_compress_ef(kimad_plan_t* p, const uint64_t* K, const uint64_t* offset
     cb.value_f16 = p->cfg.value_format == KIMAD_VALUES_F16 ? 1u : 0u;
     cb.capacity_pairs = capacity_pairs; cb.status = status_out;
     mark(p, s, "begin");
-    const bool reuse = (flags & KIMAD_REUSE_PROFILE) != 0, classic = (p->cfg.flags & KIMAD_CFG_CLASSIC_PROFILE) != 0;
+    const bool reuse = (flags & KIMAD_REUSE_PROFILE) != 0;
+    const bool single = !(p->cfg.flags & KIMAD_CFG_CLASSIC_PROFILE) && lo.nchunks >= SINGLE_SELECT_CHUNKS &&
+                        lo.nchunks >= SINGLE_SELECT_PER_LAYER * lo.B;
     if (!reuse) {
         // Select from scratch, one target per layer: by the single pass over g and h that the profile takes, whose
-        // candidates then serve the selection.  (Two histogram passes and a compaction, three reads of g and h, take
-        // 811 us on the headline set at half a percent of the entries, this 337, and 900 in a round whose every layer the
-        // prediction misses, as when all gradients are 64 times the round before's; KIMAD_CFG_CLASSIC_PROFILE keeps them.)
+        // candidates then serve the selection, or by two histogram passes and a compaction (SINGLE_SELECT_CHUNKS).
         uint32_t* ksel = at<uint32_t>(p, lo.ksel);
         KLAUNCH(p, s, "k_make_ksel", k_make_ksel, dim3((lo.L + 255) / 256), dim3(256), K, cb.layers, lo.L, ksel);
         hipStream_t unused = s;
-        const int rc = classic ? run_select_passes(p, ksel, 1, nullptr, s) : run_single_pass(p, ksel, 1, nullptr, 0, s, &unused);
+        const int rc = single ? run_single_pass(p, ksel, 1, nullptr, 0, s, &unused) : run_select_passes(p, ksel, 1, nullptr, s);
         if (rc) return rc;
         cb.Ktab = ksel;
         cb.J = 1;
@@ -937,7 +946,7 @@ int kimad_compress_ef(kimad_plan_t* p, const uint64_t* K, const uint64_t* offset
     // (the last-digit histograms are zero here: k_resolve clears what it has read)
     KLAUNCH(p, s, "k_lookup", k_lookup, dim3(1), dim3(256), cb, (int32_t)KIMAD_ERR_OFFGRID,
             (int32_t)KIMAD_ERR_BAD_OFFSETS, (int32_t)KIMAD_ERR_STALE_PROFILE,
-            (uint32_t)(reuse ? 1u : 0u), (uint32_t)(reuse || !classic ? 1u : 0u));
+            (uint32_t)(reuse ? 1u : 0u), (uint32_t)(reuse || single ? 1u : 0u));
     hipStream_t ss = s;
     if (lo.S) {
         ss = fork_side(p, s);                 // after the lookup: the small layers read its verdict

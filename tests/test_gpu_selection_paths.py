@@ -56,13 +56,15 @@ def test_small_layers_of_every_shape(ties):
     _compress(sizes, K, 6, ties, 1)
 
 
+@pytest.mark.parametrize("largest", [1048576 + 77, 2900000, 3145728])
 @pytest.mark.parametrize("share", [0.0, 0.001, 0.06, 0.124, 0.13, 0.7, 1.0])
-def test_selection_from_scratch_over_several_rounds(share):
-    """One size per layer, from the single pass: the first call predicts from a sample, the later ones from the
-    histogram of the call before; a gradient scaled by 64 in between makes every prediction miss."""
+def test_selection_from_scratch_over_several_rounds(share, largest):
+    """One size per layer, from histogram passes (the smaller sets) and from the single pass (the largest: 3287 chunks):
+    the first call predicts from a sample, the later ones from the histogram of the call before; a gradient scaled by 64
+    in between makes every prediction miss."""
     import torch
     import paper_2312_08053_amd as kimad
-    sizes = [9000, 200001, 5000, 1048576 + 77, 8193]
+    sizes = [9000, 200001, 5000, largest, 8193]
     K = [min(n, int(np.ceil(share * n))) for n in sizes]
     off = np.concatenate([[0], np.cumsum(K)])
     g, h = _layers(sizes, 7, False)

@@ -104,8 +104,8 @@ def test_selection_from_scratch_recorded_before_the_plan_has_run():
     import paper_2312_08053_amd as kimad
     from kimad_synth.gen import Workload
     rng = np.random.default_rng(8)
-    sizes = [9000, 200001, 5000, 300011]
-    K = [90, 2000, 5000, 40000]
+    sizes = [9000, 1200001, 5000, 2300011]         # (large enough for the single pass)
+    K = [90, 12000, 5000, 300000]
     off = np.concatenate([[0], np.cumsum(K)])
     torch.full((64 << 20,), -1, dtype=torch.int32, device="cuda")      # (memory that a workspace may get next: not zeros)
     gd = torch.empty(sum(sizes), dtype=torch.float32, device="cuda")
