@@ -26,7 +26,7 @@ struct AllocBuffers {
     uint64_t* K_out;
     uint64_t* offsets_out;
     int32_t* status;
-    uint32_t* flags;         // [0] non-finite seen
+    uint32_t* flags;         // [0] non-finite seen (rows by launch only), [1] workgroups started, [2] a wait was given up
 };
 
 constexpr double DP_INF = __builtin_huge_val();
@@ -119,11 +119,32 @@ struct DpLists {
 };
 constexpr uint32_t HULL_LAST = 0x80000000u;
 
+// A cell of a row that nobody has stored yet (a NaN that no total can be).
+constexpr unsigned long long ROW_EMPTY = ~0ull;
+
 // One wave per layer, one lane per candidate.  `with_hull`: also the list's lower convex hull.
-__global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uint32_t with_hull) {
+// `rows` (not null): the stored rows of the recurrence, `pitch` cells each, the first `pad` of them before cost 0: row i + 1
+// is filled with ROW_EMPTY (row 0: the start), by the gridDim.y workgroups of the layer; and its counters are cleared.
+__global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uint32_t with_hull, double* rows, uint64_t pitch, uint32_t pad) {
     __shared__ double se[KIMAD_MAX_J_CONST];
     __shared__ uint32_t sw[KIMAD_MAX_J_CONST];
     const uint32_t i = blockIdx.x, j = threadIdx.x;
+    if (rows) {
+        const uint64_t cells = ((uint64_t)pad + ab.cap + 64u) & ~63ull;        // (the pitch holds them)
+        auto fill = [&](uint64_t r) {
+            unsigned long long* row = reinterpret_cast<unsigned long long*>(rows + r * pitch);
+            for (uint64_t x = 2ull * (blockIdx.y * 64u + j); x < cells; x += 128ull * gridDim.y) {
+                ulonglong2 v = make_ulonglong2(ROW_EMPTY, ROW_EMPTY);
+                if (r == 0u || x < pad) v.x = x == pad ? 0ull : 0x7FF0000000000000ull;
+                if (r == 0u || x + 1u < pad) v.y = 0x7FF0000000000000ull;
+                *reinterpret_cast<ulonglong2*>(row + x) = v;
+            }
+        };
+        fill(i + 1ull);
+        if (i == 0u) fill(0ull);
+        if (i == 0u && blockIdx.y == 0u && j < 4u) ab.flags[j] = 0u;
+        if (blockIdx.y) return;
+    }
     const bool valid = j < ab.J;
     uint32_t w = 0xFFFFFFFFu;
     double e = 0.0;
@@ -152,6 +173,7 @@ __global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uin
         dl.e[2 * o + 1] = b > j ? e_before : __longlong_as_double(0x7FF8000000000000ll);
     }
     const uint32_t n = (uint32_t)__builtin_popcountll(smask);
+    if (valid && j >= n) dl.w[(size_t)i * ab.J + j] = 0xFFFFFFFFu;            // no entry
     if (j == 0) {
         dl.n[i] = n;
         dl.bad[i] = nonfinite ? 1u : 0u;
@@ -207,26 +229,12 @@ __global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uin
 }
 
 // The recurrence for capacities whose rows fit LDS, in three kernels:
-//   k_dp_forward  one workgroup: least totals only (a min per candidate and cell), every row also
-//                 written to global memory;
+//   k_dp_chain    (k_alloc_chain.h) least totals only, a min per candidate and cell, every row stored;
 //   k_dp_choice   all (layer, cell) pairs in parallel: the winning candidate, from the stored rows;
 //   k_dp_walk     one workgroup: status, smallest cost attaining the least total, back-tracking, outputs.
-// Only the forward kernel is a sequential chain of L steps, so it carries nothing but the minimum:
-// which candidate attains it is order-independent given the previous row and is found afterwards.
-//
-// LDS rows are stored behind DP_PAD cells of +inf, so a candidate that costs more than the cell
-// needs no test: it reads +inf and cannot win.
-// Two LDS shapes: rows of up to 3072 cells beside 3072 list records, or rows of up to 4224 cells (a
-// discretisation factor of 4096 fits) beside 1024 records, i.e. more groups of fewer layers.
-constexpr uint32_t DP_PAD = 3072;               // cells of +inf before cost 0; also the largest row of the first shape
-constexpr uint32_t DP_LIST_CAP = 3072;          // list records held in LDS at a time, first shape
-constexpr uint32_t DP_PAD_WIDE = 4224;          // the same for the second shape
-constexpr uint32_t DP_LIST_CAP_WIDE = 1024;
-
-// Workgroup barrier for data exchanged through LDS only.  __syncthreads() also waits for the
-// acknowledgement of every global store in flight, which would put a memory round trip into each
-// of the L sequential steps.
-constexpr uint32_t DP_UNROLL = 4;
+// Only the first is a sequential chain of L steps, so it carries nothing but the minimum: which candidate attains it is
+// order-independent given the previous row and is found afterwards.
+constexpr uint32_t DP_ROW_MAX = 4224;           // cells of the longest row (a discretisation factor of 4096 fits)
 
 // min of two doubles, neither a signalling NaN (the builtin would add a canonicalising max per operand)
 __device__ __forceinline__ double min_f64(double a, double b) {
@@ -235,6 +243,9 @@ __device__ __forceinline__ double min_f64(double a, double b) {
     return r;
 }
 
+// Workgroup barrier for data exchanged through LDS only.  __syncthreads() also waits for the
+// acknowledgement of every global store in flight, which would put a memory round trip into each
+// of the L sequential steps.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // A wave holds 16 list records per register set, record k in lane k of every 16-lane row, and
@@ -277,192 +288,13 @@ __device__ __forceinline__ uint32_t lds_addr(const double* p) { return (uint32_t
 // distance in the row.
 __device__ __forceinline__ double rec_err(const uint4& r) { return __hiloint2double((int)r.y, (int)r.x); }
 
-// One trip of the recurrence covers records 4*K4 .. 4*K4+3 of a block of 16: dp_issue starts its
-// row reads, dp_consume does its arithmetic.  (Issuing trip t+1 before consuming trip t was tried
-// and measured no faster: a wave issues an instruction every 8 to 10 cycles whatever it waits for,
-// and the trip is bound by its instruction count.)
-template <int NT, int CPT, int K4>
-__device__ __forceinline__ void dp_issue(uint32_t neg_cost, uint32_t prev, double (&p)[4][CPT]) {
-    constexpr int K = 4 * K4;
-    uint32_t q[4];
-    row_addr_sub4<K>(prev, neg_cost, q);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-#pragma unroll
-        for (int m = 0; m < CPT; ++m)
-            p[u][m] = *(lds_cdouble_ptr)(uintptr_t)(q[u] + (uint32_t)m * NT * 8u);
-    }
-}
-
-template <int CPT, int K4>
-__device__ __forceinline__ void dp_consume(const double (&p)[4][CPT], double err, double one, double (&best)[CPT]) {
-    constexpr int K = 4 * K4;
-#pragma unroll
-    for (int m = 0; m < CPT; ++m) {
-        double t[4] = {p[0][m], p[1][m], p[2][m], p[3][m]};
-        acc_rec_error4<K>(t, err, one);
-        best[m] = min_f64(min_f64(best[m], t[0]), min_f64(t[1], min_f64(t[2], t[3])));
-    }
-}
-
-// Thread t owns cells t, t+NT, ... (CPT of them).  The lists of a group of layers sit in LDS as one
-// stream of 16-byte records, each layer padded to a multiple of DP_UNROLL with records (cost 0,
-// +inf) that change nothing.  A wave holds a layer's records in registers, record k of a block of
-// 16 in lane k of every 16-lane row, and hands record k to all lanes with a DPP row broadcast
-// (a readlane or a broadcast LDS read per record and wave costs several times the arithmetic).
-// Per record and cell the work is one LDS read, one add and one min.  The records of the next
-// layer are fetched while the current one is computed.
-template <int NT, int CPT, uint32_t PAD = DP_PAD, uint32_t LCAP = DP_LIST_CAP>
-__global__ __launch_bounds__(NT) void k_dp_forward(AllocBuffers ab, const uint32_t* __restrict__ ent_w,
-                                                               const double* __restrict__ ent_e,
-                                                               const uint32_t* __restrict__ ent_n,
-                                                               double* __restrict__ rows_g, uint32_t rstride) {
-    __shared__ double rows[2][2 * PAD];                 // 96 KB (132 KB in the wide shape)
-    __shared__ uint4 recs[LCAP + 64];                   // 49 KB (17 KB); a layer's fetch may run 63 records past its list
-    __shared__ uint32_t loff[NT + 1];         // first record of each layer of the group
-    __shared__ uint32_t ln[NT];               // entries of each layer before padding
-    __shared__ uint32_t ltr[NT + 1];          // trips of each layer; 0 after the last
-    __shared__ uint32_t su[16];
-    __shared__ uint32_t sh_g;
-    const uint32_t tid = threadIdx.x;
-    const uint32_t ncell = ab.cap + 1;
-    for (uint32_t c = tid; c < 2 * PAD; c += NT) {
-        rows[0][c] = c == PAD ? 0.0 : DP_INF;
-        rows[1][c] = DP_INF;
-    }
-    for (uint32_t c = tid; c < ncell; c += NT) rows_g[c] = c ? DP_INF : 0.0;
-    // Layers are taken in groups whose candidate lists fit the LDS list buffer; the lists of a group
-    // are copied in one sweep, so the memory latency is paid once per group, not once per layer.
-    uint32_t i0 = 0;
-    while (i0 < ab.L) {
-        const uint32_t n_mine = (i0 + tid < ab.L) ? ent_n[i0 + tid] : 0u;
-        const uint32_t mine = (n_mine + DP_UNROLL - 1u) & ~(DP_UNROLL - 1u);
-        const uint32_t before = block_exclusive_scan<uint32_t>(mine, su, nullptr);
-        if (tid == 0) sh_g = 0u;
-        __syncthreads();
-        const bool fits = i0 + tid < ab.L && before + mine <= LCAP;
-        if (fits) {
-            loff[tid] = before;
-            ln[tid] = n_mine;
-            atomicMax(&sh_g, tid + 1u);          // layer counts are prefix-monotone: the group is layers 0..g-1
-        }
-        __syncthreads();
-        const uint32_t g = sh_g;                 // >= 1: one layer has at most J <= 64 entries
-        if (tid == g - 1u) loff[g] = before + mine;
-        __syncthreads();
-        // Lane k of a wave copies record k (a padded list has at most 64 of them) of one layer at a time,
-        // four layers per trip with their loads issued together: the copy costs a few memory round trips,
-        // not one per layer.  Idle positions read entry 0 of the table (a valid address) and drop it.
-        static_assert(KIMAD_MAX_J_CONST == 64, "one lane per list record");
-        {
-            const uint32_t k = tid & 63u;
-            constexpr uint32_t LSTEP = NT / 64;              // layers one trip of the workgroup covers
-            for (uint32_t l0 = tid >> 6; l0 < g; l0 += 4u * LSTEP) {
-                uint32_t at[4], w8[4];
-                double e[4];
-                bool act[4], real[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint32_t layer = l0 + (uint32_t)u * LSTEP;
-                    const bool in = layer < g;
-                    const uint32_t first = in ? loff[layer] : 0u;
-                    act[u] = in && k < loff[layer + 1] - first;
-                    real[u] = act[u] && k < ln[layer];
-                    at[u] = first + k;
-                    const size_t o = real[u] ? (size_t)(i0 + layer) * ab.J + k : 0;
-                    e[u] = ent_e[2 * o];
-                    w8[u] = ent_w[o];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (!act[u]) continue;
-                    const double ee = real[u] ? e[u] : DP_INF;
-                    const uint32_t ww = real[u] ? w8[u] * 8u : 0u;
-                    recs[at[u]] = make_uint4((uint32_t)__double2loint(ee), (uint32_t)__double2hiint(ee), 0u - ww, 0u);
-                }
-            }
-        }
-        // a layer's fetch and the row reads issued one trip ahead may run past the group's last
-        // record: what they find there is (cost 0, +inf) as well
-        if (tid < 64) recs[loff[g] + tid] = make_uint4(0u, 0x7FF00000u, 0u, 0u);
-        for (uint32_t l = tid; l <= g; l += NT) ltr[l] = l < g ? (loff[l + 1] - loff[l]) / DP_UNROLL : 0u;
-        __syncthreads();
-
-        // The stream is contiguous, so the first record of the next layer follows from the trip
-        // counts alone: its records are fetched while the current layer is computed, and the trip
-        // counts are read two layers ahead, which keeps every list access off the critical path.
-        const uint32_t sub = tid & 15u;
-        auto fetch_layer = [&](uint32_t first, uint4 (&R)[4]) {
-#pragma unroll
-            for (int b = 0; b < 4; ++b) R[b] = recs[first + 16u * b + sub];
-        };
-        double one = 1.0;
-        asm volatile("" : "+v"(one));          // keep 1.0 in a vector register pair
-        uint4 Rn[4];
-        fetch_layer(0u, Rn);
-        uint32_t first = 0u;
-        uint32_t nt_cur = __builtin_amdgcn_readfirstlane(ltr[0]);
-        uint32_t nt_n1 = __builtin_amdgcn_readfirstlane(ltr[min(1u, g)]);
-        uint32_t nt_n2 = ltr[min(2u, g)];
-        double* out = rows_g + (size_t)i0 * rstride + tid;
-        for (uint32_t i = i0; i < i0 + g; ++i) {
-            // LDS byte address of this thread's first cell in the previous row
-            const uint32_t prev = lds_addr(rows[i & 1] + PAD + tid);
-            double* cur = rows[(i + 1) & 1] + PAD + tid;
-            const uint32_t nt = nt_cur;
-            const uint4 R0 = Rn[0], R1 = Rn[1], R2 = Rn[2], R3 = Rn[3];
-            first += DP_UNROLL * nt;
-            fetch_layer(first, Rn);
-            nt_cur = nt_n1;
-            nt_n1 = __builtin_amdgcn_readfirstlane(nt_n2);
-            nt_n2 = ltr[min(i - i0 + 3u, g)];
-            double best[CPT];
-#pragma unroll
-            for (int m = 0; m < CPT; ++m) best[m] = DP_INF;
-            // trips in blocks of four: one register set of records per block
-            if (nt) {
-                uint4 Q0 = R0, Q1 = R1, Q2 = R2, Q3 = R3;
-                uint32_t rem = nt;
-                double p[4][CPT];
-                for (;;) {
-                    const double err = rec_err(Q0);
-                    dp_issue<NT, CPT, 0>(Q0.z, prev, p);
-                    dp_consume<CPT, 0>(p, err, one, best);
-                    if (rem == 1) break;
-                    dp_issue<NT, CPT, 1>(Q0.z, prev, p);
-                    dp_consume<CPT, 1>(p, err, one, best);
-                    if (rem == 2) break;
-                    dp_issue<NT, CPT, 2>(Q0.z, prev, p);
-                    dp_consume<CPT, 2>(p, err, one, best);
-                    if (rem == 3) break;
-                    dp_issue<NT, CPT, 3>(Q0.z, prev, p);
-                    dp_consume<CPT, 3>(p, err, one, best);
-                    if (rem == 4) break;
-                    rem -= 4u;
-                    Q0 = Q1; Q1 = Q2; Q2 = Q3;
-                }
-            }
-            out += rstride;                      // row i + 1; a stored row holds NT * CPT cells, so no cell is tested
-#pragma unroll
-            for (int m = 0; m < CPT; ++m) {
-                // (the last sweep of the wide shape runs past the row: those cells exist in the stored row only)
-                if ((uint32_t)(m + 1) * NT <= PAD || tid + (uint32_t)m * NT < PAD) cur[m * NT] = best[m];
-                out[m * NT] = best[m];
-            }
-            lds_barrier();
-        }
-        __syncthreads();                         // the next group overwrites the records
-        i0 += g;
-    }
-}
-
 // Winning candidate of every (layer, cell): candidates in list order with a strict "<", then the
 // lowest member of the winner's run whose rounded total is the same.
 __global__ __launch_bounds__(256) void k_dp_choice(AllocBuffers ab, DpLists dl, const double* __restrict__ rows_g,
                                                    uint32_t rstride) {
     __shared__ uint32_t lw[KIMAD_MAX_J_CONST], lj[KIMAD_MAX_J_CONST];
     __shared__ double le[2 * KIMAD_MAX_J_CONST];
-    __shared__ double prev[DP_PAD_WIDE];       // the previous row up to this workgroup's last cell
+    __shared__ double prev[DP_ROW_MAX];       // the previous row up to this workgroup's last cell
     const uint32_t i = blockIdx.y, tid = threadIdx.x;
     const uint32_t n = dl.n[i];
     if (tid < n) {
@@ -511,7 +343,7 @@ constexpr uint32_t DP_WALK_MAX_L = 4224;           // layers whose path cells k_
 
 __global__ __launch_bounds__(1024) void k_dp_walk(AllocBuffers ab, const double* __restrict__ last,
                                                   const uint32_t* __restrict__ bad,
-                                                  int32_t err_infeasible, int32_t err_nonfinite) {
+                                                  int32_t err_infeasible, int32_t err_nonfinite, int32_t err_internal) {
     __shared__ __attribute__((aligned(16))) uint8_t stage[DP_STAGE_BYTES];
     __shared__ uint16_t s_cell[DP_WALK_MAX_L];     // the path's cell per layer (a store to memory in the chain would be waited for)
     __shared__ double sv[16];
@@ -546,6 +378,7 @@ __global__ __launch_bounds__(1024) void k_dp_walk(AllocBuffers ab, const double*
             if (sv[w] < best || (sv[w] == best && sc[w] < bc)) { best = sv[w]; bc = sc[w]; }
         int32_t s = 0;
         if (any_bad) s = err_nonfinite;
+        else if (ab.flags[2]) s = err_internal;
         else if (!(best < DP_INF) || ab.L > DP_WALK_MAX_L) s = err_infeasible;   // (more layers than cells: no finite total)
         st = s;
         cstar = bc;
@@ -621,13 +454,22 @@ __global__ __launch_bounds__(1024) void k_dp_walk(AllocBuffers ab, const double*
 }
 
 // Smallest cost attaining the least total, back-tracking, outputs.  One workgroup.
-__global__ __launch_bounds__(1024) void k_dp_final(AllocBuffers ab, const double* last, int32_t err_infeasible,
-                                                   int32_t err_nonfinite) {
+// `bad` (not null): per layer, whether its table row holds an Inf or a NaN; else flags[0] says it of the table.
+__global__ __launch_bounds__(1024) void k_dp_final(AllocBuffers ab, const double* last, const uint32_t* __restrict__ bad,
+                                                   int32_t err_infeasible, int32_t err_nonfinite, int32_t err_internal) {
     __shared__ double sv[16];
     __shared__ unsigned long long sc[16];
     __shared__ unsigned long long cstar;
+    __shared__ uint32_t any_bad;
     __shared__ int32_t st;
     const uint32_t tid = threadIdx.x;
+    if (tid == 0) any_bad = bad ? 0u : ab.flags[0];
+    __syncthreads();
+    if (bad) {
+        uint32_t mine = 0u;
+        for (uint32_t i = tid; i < ab.L; i += 1024u) mine |= bad[i];
+        if (mine) atomicOr(&any_bad, 1u);
+    }
     double best = DP_INF;
     unsigned long long bc = ~0ull;
     for (uint64_t c0 = tid; c0 <= ab.cap; c0 += 8u * 1024u) {
@@ -652,7 +494,8 @@ __global__ __launch_bounds__(1024) void k_dp_final(AllocBuffers ab, const double
         for (uint32_t w = 1; w < 16; ++w)
             if (sv[w] < best || (sv[w] == best && sc[w] < bc)) { best = sv[w]; bc = sc[w]; }
         int32_t s = 0;
-        if (ab.flags[0]) s = err_nonfinite;
+        if (any_bad) s = err_nonfinite;
+        else if (bad && ab.flags[2]) s = err_internal;
         else if (!(best < DP_INF)) s = err_infeasible;
         st = s;
         cstar = bc;

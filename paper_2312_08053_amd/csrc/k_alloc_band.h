@@ -457,7 +457,7 @@ constexpr uint32_t BANDED_NARROW = 256, BANDED_WIDE = 1024;   // threads, for na
 constexpr uint32_t BANDED_MEAN = 128;           // mean width of a row up to which the bands are narrow (16 ratios or more; wider with fewer)
 constexpr uint32_t BAND_LIVE_CAP = 2048;       // live records held in LDS at a time
 constexpr uint32_t BAND_CELLS = 12288;         // row cells held in LDS (96 KB); two of the longest rows fit
-static_assert(2u * DP_PAD_WIDE <= BAND_CELLS, "two rows fit");
+static_assert(2u * DP_ROW_MAX <= BAND_CELLS, "two rows fit");
 
 // Rows and layers as the recurrence sees them: first cell, last cell - first cell, first of the row's cells among all
 // rows' cells, first of layer r's live records among all layers'.

@@ -1,0 +1,380 @@
+// The allocation's recurrence by workgroups that run side by side, each with its own cost cells (paper Appendix C).
+//
+// A layer's row needs nothing but the cells at or below its own of the row before.  So workgroup b keeps cells
+// [b W, (b + 1) W) through all the layers: the first one depends on nobody and runs ahead, the others follow at a
+// distance, and a layer is no longer a sweep of one compute unit over the whole row, nor a launch.
+//
+// A row's cells travel through memory and stand for themselves: k_dp_prep fills the rows with ROW_EMPTY, a bit pattern
+// that no total has (a total is a number or +inf: a minimum taken from +inf on is never a NaN), a workgroup stores each
+// cell once with a device-scope store, and a reader that finds ROW_EMPTY asks again.  There is no flag, and no order
+// between two stores matters.
+//
+// (One workgroup sweeping whole rows, bound by one compute unit's LDS, and a launch per layer where a row fits no LDS took,
+// against these: 148 layers of 999 cells 125 and 61 us, 161 layers of 996 cells 117 and 62; 62 layers with the exact cost
+// axis, 12 thousand cells 249 and 72, 58 thousand 395 and 149, 130 thousand with 64 candidates 702 and 374, 480 thousand 892
+// and 743.)
+//
+// Progress.  A workgroup takes its number b from a counter when it starts, so all lower numbers belong to workgroups
+// that are already running, and it waits for lower numbers only: the lowest unfinished one never waits for long,
+// however few of the others fit on the chip.  A wait is given up after CHAIN_POLLS reads (seconds), which the walk
+// back reports as an internal error.
+#pragma once
+#include "common.h"
+#include "k_alloc.h"
+
+namespace kimad {
+
+constexpr uint32_t CHAIN_POLLS = 1u << 22;
+
+__device__ __forceinline__ unsigned long long cell_load(const unsigned long long* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void cell_store(double* p, double v) {
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool cell_empty(unsigned long long v) { return (uint32_t)(v >> 32) == 0xFFFFFFFFu; }
+
+// Least value over the four 16-lane rows of a wave, in every row (min is exact: the order does not matter).
+__device__ __forceinline__ double min_over_rows(double v) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    {
+        const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+        const u32x2 a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        v = min_f64(__hiloint2double((int)b.x, (int)a.x), __hiloint2double((int)b.y, (int)a.y));
+    }
+    const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+    const u32x2 a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return min_f64(__hiloint2double((int)b.x, (int)a.x), __hiloint2double((int)b.y, (int)a.y));
+}
+
+// ---- rows that fit LDS -------------------------------------------------------------------------
+// A compute wave looks after sixteen cells, the same ones in each of its four 16-lane rows; lane 16 r + k holds list record
+// 4 k + r and hands it to its row by DPP, so the four rows share a layer's records and a minimum over the rows closes
+// the layer.  The workgroup's previous row is in LDS up to its own last cell: its own cells from its compute waves, the lower
+// ones from memory, brought by other waves: CHAIN_LOADERS groups of them take the rows in turn, each asking for its next row
+// when it has put down one, so that a row is asked for CHAIN_LOADERS layers before it is needed, and a wave that waits
+// for memory waits for its own row only; one more wave brings the layers' records.  One barrier a layer.
+// Bound by the chain barrier, LDS read, four fp64 additions, minimum over the rows, LDS write: 0.22 us a layer in the first
+// workgroup, and 1 to 2 us that each workgroup starts behind the one below it.  (The compute waves wait for no memory at
+// all: with the records asked for by them, and the cells' stores in the same queue, a layer took 0.4 us.  148 layers of
+// 999 cells: 4 compute waves 61 us, 8 62, 3 65; one loader wave a group 71, two 61, four 62; four groups of one wave 91.)
+constexpr uint32_t CHAIN_WAVES = 4;             // compute waves
+constexpr uint32_t CHAIN_CELLS = 16 * CHAIN_WAVES;
+constexpr uint32_t CHAIN_LOADERS = 2;
+constexpr uint32_t CHAIN_RECS = 4;              // layers whose records are in LDS, and under way from memory
+static_assert(CHAIN_RECS % 2 == 0, "the rows change places every layer");
+
+// Minimum over the records of the lane's row, of which there are at most 4 B.  All cells are asked for before the first is
+// used.  (`then`: what is asked for behind them.)
+template <int K4, int B>
+__device__ __forceinline__ void chain_ask(uint32_t neg_cost, uint32_t prev, double (&t)[B][4]) {
+    uint32_t q[4];
+    row_addr_sub4<4 * K4>(prev, neg_cost, q);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[K4][u] = *(lds_cdouble_ptr)(uintptr_t)q[u];
+}
+template <int B, typename F>
+__device__ __forceinline__ double chain_records(uint32_t neg_cost, double err, double one, uint32_t prev, F then) {
+    double t[B][4], m[B];
+    chain_ask<0>(neg_cost, prev, t);
+    if constexpr (B > 1) chain_ask<1>(neg_cost, prev, t);
+    if constexpr (B > 2) chain_ask<2>(neg_cost, prev, t);
+    if constexpr (B > 3) chain_ask<3>(neg_cost, prev, t);
+    then();
+    acc_rec_error4<0>(t[0], err, one);
+    if constexpr (B > 1) acc_rec_error4<4>(t[1], err, one);
+    if constexpr (B > 2) acc_rec_error4<8>(t[2], err, one);
+    if constexpr (B > 3) acc_rec_error4<12>(t[3], err, one);
+#pragma unroll
+    for (int k = 0; k < B; ++k) m[k] = min_f64(min_f64(t[k][0], t[k][1]), min_f64(t[k][2], t[k][3]));
+    double best = m[0];
+    if constexpr (B > 1) best = min_f64(best, m[1]);
+    if constexpr (B > 2) best = min_f64(best, m[2]);
+    if constexpr (B > 3) best = min_f64(best, m[3]);
+    return min_f64(best, DP_INF);                 // (never a NaN: a cell holds a number or ROW_EMPTY)
+}
+
+// The layers, for one compute wave.
+__device__ __forceinline__ void chain_compute(uint32_t layers, double* rows_g, uint32_t rstride, uint32_t c0, uint32_t wave, double* row_a,
+                                              double* row_b, const uint4 (*recs)[64]) {
+    const uint32_t lane = lane_id(), c = c0 + wave * 16u + (lane & 15u);
+    double one = 1.0;
+    asm volatile("" : "+v"(one));          // keep 1.0 in a vector register pair
+    double* out = rows_g + rstride + c;
+    uint4 R = recs[0][lane];
+    for (uint32_t i0 = 0; i0 < layers; i0 += CHAIN_RECS) {
+#pragma unroll
+        for (uint32_t u = 0; u < CHAIN_RECS; ++u) {
+            if (i0 + u >= layers) break;
+            const uint32_t at = lds_addr(((u & 1u) ? row_b : row_a) + CHAIN_CELLS + c);
+            const uint32_t neg = R.z, n = (uint32_t)__builtin_amdgcn_readfirstlane(R.w);
+            const double err = rec_err(R);
+            auto next = [&]() { R = recs[(u + 1u) % CHAIN_RECS][lane]; };
+            double best;
+            if (n <= 16u) best = chain_records<1>(neg, err, one, at, next);
+            else if (n <= 32u) best = chain_records<2>(neg, err, one, at, next);
+            else if (n <= 48u) best = chain_records<3>(neg, err, one, at, next);
+            else best = chain_records<4>(neg, err, one, at, next);
+            best = min_over_rows(best);
+            if (lane < 16u) {
+                ((u & 1u) ? row_a : row_b)[CHAIN_CELLS + c] = best;
+                cell_store(out, best);
+            }
+            out += rstride;
+            lds_barrier();
+        }
+    }
+}
+
+// The records that any cell of this workgroup can afford (the first ones: costs ascend, an unused record costs 0xFFFFFFFF),
+// for one wave: layer i + 2 is put down in layer i, for the compute waves to read in layer i + 1.
+struct ChainRecords {
+    const AllocBuffers& ab;
+    const DpLists& dl;
+    uint32_t c_hi;
+    uint4 (*recs)[64];
+    uint32_t rw[CHAIN_RECS];
+    double re[CHAIN_RECS];
+
+    __device__ __forceinline__ void ask(uint32_t i, uint32_t& w, double& e) {
+        const uint32_t rec = (lane_id() & 15u) * 4u + (lane_id() >> 4);
+        const size_t o = (size_t)min(i, ab.L - 1u) * ab.J + min(rec, ab.J - 1u);
+        w = rec < ab.J ? dl.w[o] : 0xFFFFFFFFu;
+        e = dl.e[2 * o];
+    }
+    __device__ __forceinline__ void put(uint32_t slot, uint32_t w, double e) {
+        const bool can = w <= c_hi;
+        const uint32_t n = (uint32_t)__popcll(ballot(can));
+        const double x = can ? e : DP_INF;
+        recs[slot][lane_id()] = make_uint4((uint32_t)__double2loint(x), (uint32_t)__double2hiint(x), can ? 0u - 8u * w : 0u, n);
+    }
+    __device__ __forceinline__ void start() {
+#pragma unroll
+        for (uint32_t a = 0; a < CHAIN_RECS; ++a) ask(a, rw[a], re[a]);
+        put(0u, rw[0], re[0]);
+        put(1u, rw[1], re[1]);
+#pragma unroll
+        for (uint32_t a = 0; a < 2u; ++a) ask(CHAIN_RECS + a, rw[a], re[a]);
+    }
+    __device__ __forceinline__ void run() {
+        for (uint32_t i0 = 0; i0 < ab.L; i0 += CHAIN_RECS) {
+#pragma unroll
+            for (uint32_t u = 0; u < CHAIN_RECS; ++u) {
+                if (i0 + u >= ab.L) break;
+                constexpr uint32_t A = CHAIN_RECS;
+                put((u + 2u) % A, rw[(u + 2u) % A], re[(u + 2u) % A]);
+                ask(i0 + u + 2u + A, rw[(u + 2u) % A], re[(u + 2u) % A]);
+                lds_barrier();
+            }
+        }
+    }
+};
+
+// The lower cells of rows g + 1, g + 1 + CHAIN_LOADERS, ..., for one wave of a loader group: cells first, first + 64 GW, ...
+template <int M, uint32_t GW>
+__device__ __forceinline__ void chain_load(const AllocBuffers& ab, const double* rows_g, uint32_t rstride, uint32_t c0, uint32_t g,
+                                           uint32_t first, double* row_a, double* row_b) {
+    constexpr uint32_t N = CHAIN_LOADERS;
+    unsigned long long v[M];
+    // (a row beyond the last: the last one again, not used)
+    auto ask = [&](uint32_t r) {
+        const unsigned long long* row = reinterpret_cast<const unsigned long long*>(rows_g + (size_t)min(r, ab.L) * rstride);
+#pragma unroll
+        for (int m = 0; m < M; ++m) v[m] = cell_load(row + min(first + (uint32_t)m * 64u * GW, c0 - 1u));
+    };
+    auto any_empty = [&]() {
+        uint32_t top = 0u;                            // (an empty cell has the greatest high word)
+#pragma unroll
+        for (int m = 0; m < M; ++m) top = max(top, (uint32_t)(v[m] >> 32));
+        return ballot(top == 0xFFFFFFFFu) != 0ull;
+    };
+    ask(g + 1u);
+    uint32_t i = 0;                                   // layers whose barrier is behind us
+    for (; i < min(g, ab.L); ++i) lds_barrier();
+    static_assert(N % 2 == 0, "a group's rows all go to the same half of LDS");
+    double* dst = ((g & 1u) ? row_a : row_b) + CHAIN_CELLS;
+    while (i < ab.L) {
+        uint32_t polls = 0;
+        while (any_empty()) {
+            if (++polls > CHAIN_POLLS) {
+                if (lane_id() == 0) atomicOr(&ab.flags[2], 1u);
+                break;
+            }
+            asm volatile("" ::: "memory");
+            ask(i + 1u);
+        }
+#pragma unroll
+        for (int m = 0; m < M; ++m) dst[min(first + (uint32_t)m * 64u * GW, c0 - 1u)] = __longlong_as_double((long long)v[m]);
+        ask(i + 1u + N);
+        for (uint32_t k = 0; k < N && i < ab.L; ++k, ++i) lds_barrier();
+    }
+}
+
+// GW: waves of a loader group.
+constexpr uint32_t chain_threads(uint32_t gw) { return 64u * (CHAIN_WAVES + 1u + CHAIN_LOADERS * gw); }
+template <uint32_t MAXC, uint32_t GW>
+__global__ __launch_bounds__(chain_threads(GW)) void k_dp_chain(AllocBuffers ab, DpLists dl, double* __restrict__ rows_g, uint32_t rstride) {
+    constexpr uint32_t NT = chain_threads(GW);
+    __shared__ double rows[2][CHAIN_CELLS + MAXC];       // CHAIN_CELLS cells of +inf before cost 0: a record costs at most c_hi here
+    __shared__ uint4 recs[CHAIN_RECS][64];
+    __shared__ uint32_t sh_b;
+    const uint32_t tid = threadIdx.x;
+    if (tid == 0) sh_b = atomicAdd(&ab.flags[1], 1u);
+    __syncthreads();
+    const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane(sh_b) * CHAIN_CELLS;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    for (uint32_t x = tid; x < 2u * CHAIN_CELLS + c0; x += NT) {
+        rows[0][x] = x == CHAIN_CELLS ? 0.0 : DP_INF;
+        rows[1][x] = DP_INF;
+    }
+    if (wave == CHAIN_WAVES) {
+        ChainRecords cr{ab, dl, c0 + CHAIN_CELLS - 1u, recs};
+        cr.start();
+        __syncthreads();
+        cr.run();
+        return;
+    }
+    __syncthreads();
+    if (wave < CHAIN_WAVES) {
+        chain_compute(ab.L, rows_g, rstride, c0, wave, rows[0], rows[1], recs);
+        return;
+    }
+    const uint32_t load = wave - CHAIN_WAVES - 1u, g = load / GW, first = load % GW * 64u + lane_id();
+    const uint32_t m = (c0 + 64u * GW - 1u) / (64u * GW);
+    constexpr uint32_t MOST = (MAXC + 64u * GW - 1u) / (64u * GW);
+    if (m == 0u) {
+        for (uint32_t i = 0; i < ab.L; ++i) lds_barrier();
+    } else if (m <= 4u) {
+        chain_load<4, GW>(ab, rows_g, rstride, c0, g, first, rows[0], rows[1]);
+    } else if (MOST <= 8u || m <= 8u) {
+        chain_load<8, GW>(ab, rows_g, rstride, c0, g, first, rows[0], rows[1]);
+    } else {
+        chain_load<(int)(MOST > 8u ? MOST : 8u), GW>(ab, rows_g, rstride, c0, g, first, rows[0], rows[1]);
+    }
+}
+
+// ---- rows too long for LDS ----------------------------------------------------------------------
+// Every wave is on its own with 64 cells, one a lane, and reads every source cell from memory, all of a layer's together.
+// CHAIN_PAD cells of +inf stand before cost 0.  SETS: sixteens of candidates; lane 16 r + k holds candidates k, k + 16, ... and
+// hands them to its row by DPP.  The total is stored as soon as it is known; which candidate it came from (the first one in
+// order that attains it) is looked for while the store is under way.  Bound by the way of a cell from one wave to the next
+// (store, poll, load: about 1 us) and, on long rows, by the source cells read (58 thousand cells, 32 candidates: 15 MB a
+// layer, 2.3 us).  With more than sixteen candidates the cheapest four's cells are waited for before all are asked for
+// through the caches (149 against 160 us with device-scope loads for all; with sixteen or fewer the wait costs more than it
+// saves, 83 against 72).  Sixteen cells a wave, the candidates shared by its four rows, read twice the lines: 190.
+constexpr uint32_t CHAIN_PAD = 64;
+constexpr uint32_t CHAIN_LONG_NT = 64;
+constexpr uint32_t CHAIN_LONG_CELLS = CHAIN_LONG_NT;
+
+template <int SETS>
+__global__ __launch_bounds__(CHAIN_LONG_NT) void k_dp_chain_long(AllocBuffers ab, const uint32_t* __restrict__ wall, double* rows, uint64_t pitch) {
+    const uint32_t lane = threadIdx.x;
+    uint32_t ticket = 0;
+    if (lane == 0) ticket = atomicAdd(&ab.flags[1], 1u);
+    const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane(ticket) * CHAIN_LONG_CELLS, c = c0 + lane, c_hi = c0 + 63u;
+    double one = 1.0;
+    asm volatile("" : "+v"(one));
+    bool gave_up = false;
+    uint32_t w_next[SETS];
+    double e_next[SETS];
+    auto ask_records = [&](uint32_t i) {
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            const uint32_t k = 16u * (uint32_t)s + (lane & 15u);
+            const size_t o = (size_t)min(i, ab.L - 1u) * ab.J + min(k, ab.J - 1u);
+            w_next[s] = k < ab.J ? wall[o] : 0xFFFFFFFFu;
+            e_next[s] = ab.E[o];
+        }
+    };
+    ask_records(0u);
+    for (uint32_t i = 0; i < ab.L; ++i) {
+        // a candidate that no cell here can afford reads the cells before cost 0
+        uint32_t n = 0, neg[SETS];
+        double err[SETS];
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            const bool can = w_next[s] <= c_hi;
+            n += (uint32_t)__popcll(ballot(can) & 0xFFFFull);            // (costs ascend: the first candidates)
+            neg[s] = 0u - 8u * (can ? w_next[s] : c_hi + 1u);
+            err[s] = can ? e_next[s] : DP_INF;
+        }
+        ask_records(i + 1u);
+        const char* row = reinterpret_cast<const char*>(rows + (size_t)i * pitch);
+        auto cell = [&](uint32_t at) { return reinterpret_cast<const unsigned long long*>(row + at); };
+        const uint32_t here = (CHAIN_PAD + c) * 8u;
+        unsigned long long v[SETS][16];
+        auto addresses = [&](int s, uint32_t (&q)[4][4]) {
+            row_addr_sub4<0>(here, neg[s], q[0]);
+            row_addr_sub4<4>(here, neg[s], q[1]);
+            row_addr_sub4<8>(here, neg[s], q[2]);
+            row_addr_sub4<12>(here, neg[s], q[3]);
+        };
+        uint32_t polls = 0;
+        auto give_up = [&]() {
+            if (++polls <= CHAIN_POLLS) return false;
+            gave_up = true;
+            if (lane == 0) atomicOr(&ab.flags[2], 1u);
+            return true;
+        };
+        if constexpr (SETS > 1) {
+            uint32_t q[4];
+            row_addr_sub4<0>(here, neg[0], q);
+            while (!gave_up && ballot(cell_empty(cell_load(cell(q[0])))) != 0ull && !give_up()) asm volatile("" ::: "memory");
+        }
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            if (s == 0 || n > 16u * (uint32_t)s) {
+                uint32_t q[4][4];
+                addresses(s, q);
+#pragma unroll
+                for (int k = 0; k < 16; ++k) v[s][k] = __hip_atomic_load(cell(q[k >> 2][k & 3]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 16; ++k) v[s][k] = 0x7FF0000000000000ull;
+            }
+        }
+        for (;;) {
+            uint32_t top = 0u;                                           // (an empty cell has the greatest high word)
+#pragma unroll
+            for (int s = 0; s < SETS; ++s)
+#pragma unroll
+                for (int k = 0; k < 16; ++k) top = max(top, (uint32_t)(v[s][k] >> 32));
+            if (ballot(top == 0xFFFFFFFFu) == 0ull || gave_up || give_up()) break;
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int s = 0; s < SETS; ++s) {
+                if (s == 0 || n > 16u * (uint32_t)s) {
+                    uint32_t q[4][4];
+                    addresses(s, q);
+#pragma unroll
+                    for (int k = 0; k < 16; ++k)
+                        if (cell_empty(v[s][k])) v[s][k] = cell_load(cell(q[k >> 2][k & 3]));
+                }
+            }
+        }
+        double t[SETS][16], best = DP_INF;
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) t[s][k] = __longlong_as_double((long long)v[s][k]);
+            double (*t4)[4] = reinterpret_cast<double (*)[4]>(t[s]);
+            acc_rec_error4<0>(t4[0], err[s], one);
+            acc_rec_error4<4>(t4[1], err[s], one);
+            acc_rec_error4<8>(t4[2], err[s], one);
+            acc_rec_error4<12>(t4[3], err[s], one);
+#pragma unroll
+            for (int k = 0; k < 16; k += 4)
+                best = min_f64(best, min_f64(min_f64(t[s][k], t[s][k + 1]), min_f64(t[s][k + 2], t[s][k + 3])));
+        }
+        cell_store(rows + (size_t)(i + 1u) * pitch + CHAIN_PAD + c, best);
+        uint32_t bj = 0xFFu;
+#pragma unroll
+        for (int s = SETS - 1; s >= 0; --s)
+#pragma unroll
+            for (int k = 15; k >= 0; --k) bj = t[s][k] == best ? 16u * (uint32_t)s + (uint32_t)k : bj;
+        ab.choice[(size_t)i * ab.stride + c] = (uint8_t)(best < DP_INF ? bj : 0xFFu);
+    }
+}
+
+}  // namespace kimad

@@ -16,6 +16,7 @@
 #include "k_fused.h"
 #include "k_compress.h"
 #include "k_alloc.h"
+#include "k_alloc_chain.h"
 #include "k_alloc_band.h"
 #include "k_server.h"
 #include "k_selftest.h"
@@ -74,6 +75,14 @@ struct HostLayer {
     uint64_t tmp0;                           // region start in the candidate buffer
     uint32_t tmp_cap;                        // entries of the region
 };
+
+// Rows too long for LDS: pitch of a stored row, and whether the workspace holds one per layer (k_dp_chain_long); else the
+// layers are launched one by one on two rows.  (The line is the memory: k_dp_chain_long was faster at every length tried.)
+constexpr uint64_t CHAIN_LONG_BYTES = 256ull << 20;
+inline uint64_t chain_long_pitch(uint64_t cells) { return (CHAIN_PAD + cells + 63ull) & ~63ull; }
+inline bool chain_long_fits(uint64_t L, uint64_t cells) {
+    return cells > DP_ROW_MAX && 8ull * (L + 1) * chain_long_pitch(cells) <= CHAIN_LONG_BYTES;
+}
 
 uint32_t pick_tile_elems(uint64_t d_big) {
     // aim at >= 8 tiles per compute unit on large inputs, keep tiles within the 16-bit LDS counters
@@ -268,7 +277,7 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     lo.row0 = take(8 * lo.dp_cells);
     lo.row1 = take(8 * lo.dp_cells);
     lo.choice = take((uint64_t)L * align_up(lo.dp_cells));
-    lo.cprev = take(2ull * L * align_up(std::min<uint64_t>(lo.dp_cells, DP_PAD_WIDE)));
+    lo.cprev = take(2ull * L * align_up(std::min<uint64_t>(lo.dp_cells, DP_ROW_MAX)));
     lo.dp_flags = take(16);
     lo.ncompact = take(16);
     lo.dl_wall = take(4 * LJ); lo.dl_w = take(4 * LJ); lo.dl_jj = take(4 * LJ); lo.dl_e = take(16 * LJ); lo.dl_n = take(4ull * L);
@@ -279,11 +288,10 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     lo.band_live = take(4ull * L);
     lo.hull_e = take(8 * LJ); lo.hull_w = take(4 * LJ); lo.hull_n = take(4ull * L); lo.hull_abs = take(8ull * L);
     {
-        // a stored row holds a whole number of the forward kernel's 512-thread sweeps (2, 4 or 6 cells per thread)
-        const uint64_t cells = std::min<uint64_t>(lo.dp_cells, DP_PAD_WIDE);
-        lo.rstride = 512ull * (cells <= 1024 ? 2 : cells <= 2048 ? 4 : cells <= DP_PAD ? 6 : 9);
+        const uint64_t cells = std::min<uint64_t>(lo.dp_cells, DP_ROW_MAX);
+        lo.rstride = 512ull * (cells <= 1024 ? 2 : cells <= 2048 ? 4 : cells <= 3072 ? 6 : 9);
     }
-    lo.rows_g = take(8ull * (L + 1) * lo.rstride);
+    lo.rows_g = take(8ull * (L + 1) * std::max(lo.rstride, chain_long_fits(L, lo.dp_cells) ? chain_long_pitch(lo.dp_cells) : 0));
     lo.total = off;
     return KIMAD_OK;
 }
@@ -301,8 +309,7 @@ uint64_t cost_unit(const kimad_config_t& cfg, uint64_t P) {
     return D == 0 || P <= D ? 1 : (P + D - 1) / D;
 }
 
-// Rows from this many cost cells on take the banded recurrence by themselves.  (148 layers: 175 us against 530 at 4097
-// cells.  At 1000 cells 162 against 155, and 290 against 144 where the bands are wide, as on ResNet-50's table.)
+// Rows from this many cost cells on take the banded recurrence by themselves.
 constexpr uint64_t BAND_AUTO_CELLS = 1537;
 // With few ratios the lists are short and whole rows cheap, as long as a thread has no more than four cells: 500 layers
 // with 5 ratios 433 us against 563 in the band at 1601 cells, 448 against 521 at 2001 and 631 against 578 at 2601; with 7
@@ -596,14 +603,15 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
         ab.E = ws.dense_E; ab.Ktab = ws.dense_Kcost; ab.Kout = ws.dense_Kout;
     }
     const uint32_t cell_blocks = (uint32_t)((cap + 1 + 255) / 256);
-    if (cap + 1 <= DP_PAD_WIDE) {
+    if (cap + 1 <= DP_ROW_MAX) {
         const DpLists& dl = ws.dl;
         double* rows_g = ws.rows_g;
         const uint32_t rstride = ws.rstride;
         const bool band = lo.L <= BAND_MAX_L && !(p->cfg.flags & KIMAD_CFG_FULL_DP) &&
                           ((p->cfg.flags & KIMAD_CFG_BAND_DP) ||
                            (cap + 1 >= BAND_AUTO_CELLS && !(lo.J <= WHOLE_ROWS_J && cap + 1 <= WHOLE_ROWS_CELLS)));
-        KLAUNCH(p, s, "k_dp_prep", k_dp_prep, dim3(lo.L), dim3(64), ab, dl, band ? 1u : 0u);
+        KLAUNCH(p, s, "k_dp_prep", k_dp_prep, dim3(lo.L), dim3(64), ab, dl, band ? 1u : 0u, band ? (double*)nullptr : rows_g,
+                (uint64_t)rstride, 0u);
         if (band) {
             // the recurrence inside the band of cells that Lagrangian bounds leave (same result, a fraction of the cells)
             BandBuffers bb = ws.band;
@@ -615,24 +623,32 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
                     (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE);
             return KIMAD_OK;
         }
-        // 512 threads: two waves per SIMD leave each thread the registers for two trips in flight
-        const uint32_t cpt = (uint32_t)((cap + 1 + 511) / 512);
-        if (cpt <= 2) {
-            KLAUNCH(p, s, "k_dp_forward", (k_dp_forward<512, 2>), dim3(1), dim3(512), ab, (const uint32_t*)dl.w,
-                    (const double*)dl.e, (const uint32_t*)dl.n, rows_g, rstride);
-        } else if (cpt <= 4) {
-            KLAUNCH(p, s, "k_dp_forward", (k_dp_forward<512, 4>), dim3(1), dim3(512), ab, (const uint32_t*)dl.w,
-                    (const double*)dl.e, (const uint32_t*)dl.n, rows_g, rstride);
-        } else if (cpt <= 6) {
-            KLAUNCH(p, s, "k_dp_forward", (k_dp_forward<512, 6>), dim3(1), dim3(512), ab, (const uint32_t*)dl.w,
-                    (const double*)dl.e, (const uint32_t*)dl.n, rows_g, rstride);
+        const uint32_t groups = (uint32_t)(cap / CHAIN_CELLS + 1);
+        if (cap + 1 <= 1024) {
+            KLAUNCH(p, s, "k_dp_chain", (k_dp_chain<1024, 2>), dim3(groups), dim3(chain_threads(2)), ab, dl, rows_g, rstride);
+        } else if (cap + 1 <= 2048) {
+            KLAUNCH(p, s, "k_dp_chain", (k_dp_chain<2048, 4>), dim3(groups), dim3(chain_threads(4)), ab, dl, rows_g, rstride);
         } else {
-            KLAUNCH(p, s, "k_dp_forward", (k_dp_forward<512, 9, DP_PAD_WIDE, DP_LIST_CAP_WIDE>), dim3(1), dim3(512), ab,
-                    (const uint32_t*)dl.w, (const double*)dl.e, (const uint32_t*)dl.n, rows_g, rstride);
+            KLAUNCH(p, s, "k_dp_chain", (k_dp_chain<DP_ROW_MAX, 5>), dim3(groups), dim3(chain_threads(5)), ab, dl, rows_g, rstride);
         }
         KLAUNCH(p, s, "k_dp_choice", k_dp_choice, dim3(cell_blocks, lo.L), dim3(256), ab, dl, (const double*)rows_g, rstride);
         KLAUNCH(p, s, "k_dp_walk", k_dp_walk, dim3(1), dim3(1024), ab, (const double*)(rows_g + (size_t)lo.L * rstride),
-                (const uint32_t*)dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE);
+                (const uint32_t*)dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL);
+    } else if (chain_long_fits(lo.L, ws.max_cells)) {
+        const uint64_t pitch = chain_long_pitch(cap + 1);
+        // (a row's filling takes several workgroups: one per 32 KB)
+        KLAUNCH(p, s, "k_dp_prep", k_dp_prep, dim3(lo.L, (uint32_t)(pitch / 4096 + 1)), dim3(64), ab, ws.dl, 0u, ws.rows_g, pitch, CHAIN_PAD);
+        const dim3 waves((uint32_t)(cap / CHAIN_LONG_CELLS + 1));
+        const uint32_t* wall = ws.dl.wall;
+        if (lo.J <= 16) {
+            KLAUNCH(p, s, "k_dp_chain", k_dp_chain_long<1>, waves, dim3(CHAIN_LONG_NT), ab, wall, ws.rows_g, pitch);
+        } else if (lo.J <= 32) {
+            KLAUNCH(p, s, "k_dp_chain", k_dp_chain_long<2>, waves, dim3(CHAIN_LONG_NT), ab, wall, ws.rows_g, pitch);
+        } else {
+            KLAUNCH(p, s, "k_dp_chain", k_dp_chain_long<4>, waves, dim3(CHAIN_LONG_NT), ab, wall, ws.rows_g, pitch);
+        }
+        KLAUNCH(p, s, "k_dp_final", k_dp_final, dim3(1), dim3(1024), ab, (const double*)(ws.rows_g + (uint64_t)lo.L * pitch + CHAIN_PAD),
+                (const uint32_t*)ws.dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL);
     } else {
         // (clears with a kernel, not hipMemsetAsync: the call may be recorded into a graph)
         KLAUNCH(p, s, "k_zero16", k_zero16, dim3(1), dim3(256), reinterpret_cast<uint4*>(ws.flags), (uint64_t)1);
@@ -641,8 +657,8 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
         for (uint32_t i = 0; i < lo.L; ++i) {
             KLAUNCH(p, s, "k_dp_layer", k_dp_layer, dim3(cell_blocks), dim3(256), ab, i, rows[i & 1], rows[(i + 1) & 1]);
         }
-        KLAUNCH(p, s, "k_dp_final", k_dp_final, dim3(1), dim3(1024), ab, (const double*)rows[lo.L & 1],
-                (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE);
+        KLAUNCH(p, s, "k_dp_final", k_dp_final, dim3(1), dim3(1024), ab, (const double*)rows[lo.L & 1], (const uint32_t*)nullptr,
+                (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL);
     }
     return KIMAD_OK;
 }
