@@ -82,6 +82,8 @@ struct SelRec {
     uint32_t K;
     float* h;          // the layer's estimator
     uint64_t dst;      // first payload slot of the layer
+    uint32_t mis;      // LayerDesc::mis
+    uint32_t pad;
 };
 
 // ---- global-memory accessors ----------------------------------------------------------------
@@ -263,7 +265,7 @@ constexpr uint32_t SPILL_BLOCK = 512;
 // REGION_SLACK: 21/128 of the layer.  The single-pass profile spills at most an eighth of a layer into it
 // (each workgroup into the slice that belongs to its chunks), the compaction pass whatever lies at or above a
 // threshold prefix if that fits; whatever does not fit is served from g and h directly.
-constexpr uint32_t REGION_PER_CHUNK = 168;        // a multiple of the 8 entries space is handed out in
+constexpr uint32_t REGION_PER_CHUNK = 168;        // (space is handed out in whole lines of values)
 constexpr uint32_t REGION_SLACK = 2048;
 // The regions of the tiled layers follow one another in the candidate buffer, so a layer's region starts where its
 // first chunk and its number among the tiled layers say: a kernel that walks chunks knows where a chunk's candidates

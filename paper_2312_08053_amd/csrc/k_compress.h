@@ -44,9 +44,9 @@ struct CompressBuffers {
     uint32_t* o_allow;            // ties this chunk may keep
     const uint32_t* chunk_first;  // chunk -> first chunk of its layer (with the big index: where its region starts)
     const uint32_t* cblk_big;     // block of 1024 chunks -> big index
-    // candidate buffer
-    uint32_t* tmp_idx;
+    // candidate buffer: x, and its position in the chunk's 1024
     float* tmp_x;
+    uint16_t* tmp_i;
     uint32_t* ncompact;       // [0] layers whose selection needs the streaming compaction pass, [1] of which served from g and h throughout (SEL_DIRECT)
     uint32_t* fresh;          // 1 while the profile's cache describes the current g - h (see ProfileBuffers)
     const LayerState* state;      // fused-profile state (spill range) per big layer
@@ -110,6 +110,7 @@ __global__ __launch_bounds__(256) void k_lookup(CompressBuffers cb, int32_t err_
         const uint32_t n = cb.layers[li].n;
         r.tmp_base = cb.layers[li].tmp0;
         r.h = cb.layers[li].h;
+        r.mis = cb.layers[li].mis;
         r.dst = cb.offsets[li];
         if (!offsets_bad && !stale) {
             const uint32_t K = (uint32_t)cb.K[li];
@@ -267,8 +268,8 @@ __device__ __forceinline__ void compact_tiles(const CompressBuffers& cb, uint32_
                 if (selm[u] & (1u << c)) {
                     if ((uint64_t)start + pos < S.cap) {
                         const uint64_t o = base + pos;
-                        cb.tmp_idx[o] = vbase + u * 256u + lane * 4u + c - L.mis;
                         cb.tmp_x[o] = q[u].g[c] - q[u].h[c];
+                        cb.tmp_i[o] = (uint16_t)(u * 256u + lane * 4u + c);
                     }
                     ++pos;
                 }
@@ -642,7 +643,7 @@ __device__ __forceinline__ void finalize_candidates(const CompressBuffers& cb, u
                                                     uint32_t block) {
     const SubGroup g = sub_group();
     const uint32_t chunk = block * CHUNKS_PER_WG + threadIdx.x / SUB;
-    uint32_t cnt = 0, tau = 0, allow = 0, room = 0, out_run = 0, eq_run = 0;
+    uint32_t cnt = 0, tau = 0, allow = 0, room = 0, out_run = 0, eq_run = 0, place0 = 0;   // place0: the entry at the chunk's position 0
     uint64_t src = 0, dst = 0;
     bool filter = false;
     float* h = nullptr;
@@ -666,6 +667,7 @@ __device__ __forceinline__ void finalize_candidates(const CompressBuffers& cb, u
             h = S.h;
             filter = S.mode == SEL_CAND || (S.mode == SEL_PREFIX && amb != 0u);
             src = region_start(first, b) + start;
+            place0 = (chunk - first) * CHUNK - S.mis;
             dst = S.dst;
             room = S.K;                            // payload slots of this layer
         }
@@ -674,7 +676,7 @@ __device__ __forceinline__ void finalize_candidates(const CompressBuffers& cb, u
     auto fetch = [&](uint32_t k, uint32_t& idx, float& x) -> bool {
         const bool in = k < cnt;
         const uint64_t at = in ? src + k : 0ull;
-        idx = cb.tmp_idx[at]; x = cb.tmp_x[at];
+        idx = place0 + cb.tmp_i[at]; x = cb.tmp_x[at];
         return in;
     };
     const uint32_t cmax = wave_max_over_groups(cnt);

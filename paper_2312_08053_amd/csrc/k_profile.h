@@ -72,8 +72,9 @@ struct ProfileBuffers {
     uint32_t* spill_over;         // [B] a reservation did not fit the layer's region
     uint32_t* rec_start;          // per chunk: start inside the layer's candidate region
     uint32_t* rec_cnt;            // per chunk: candidates written
-    uint32_t* tmp_idx;
+    // candidate buffer: x, and its position in the chunk's 1024
     float* tmp_x;
+    uint16_t* tmp_i;
 };
 
 // Pool of exact last-digit histograms: one entry per (layer, threshold prefix) whose error bound is

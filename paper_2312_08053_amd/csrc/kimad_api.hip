@@ -56,7 +56,7 @@ struct Layout {
     // compress
     uint64_t ksel, sel, zero2_begin, hist3, zero2_end, tau, quota, cblk_big;
     uint64_t rec_start, rec_cnt, rec_amb, c_gt, c_eq, o_base, o_allow;
-    uint64_t tmp_idx, tmp_x;
+    uint64_t tmp_x, tmp_i;
     // allocation
     uint64_t ncompact;
     uint64_t row0, row1, choice, dp_flags, dl_wall, dl_w, dl_jj, dl_e, dl_n, dl_bad, rows_g;
@@ -273,7 +273,7 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     const uint64_t ncb = 4ull * (nc ? nc : 1);
     lo.rec_start = take(ncb); lo.rec_amb = take(ncb);
     lo.c_gt = take(ncb); lo.c_eq = take(ncb); lo.o_base = take(ncb); lo.o_allow = take(ncb);
-    lo.tmp_idx = take(4 * lo.tmp_cap); lo.tmp_x = take(4 * lo.tmp_cap);
+    lo.tmp_x = take(4 * lo.tmp_cap); lo.tmp_i = take(2 * lo.tmp_cap);
     lo.row0 = take(8 * lo.dp_cells);
     lo.row1 = take(8 * lo.dp_cells);
     lo.choice = take((uint64_t)L * align_up(lo.dp_cells));
@@ -316,6 +316,11 @@ constexpr uint64_t BAND_AUTO_CELLS = 1537;
 // ratios 462 against 551 and 477 against 477, with 10 531 against 559 but for 148 layers 193 against 180.
 constexpr uint32_t WHOLE_ROWS_J = 7;
 constexpr uint64_t WHOLE_ROWS_CELLS = 2048;
+// From this many chunks in tiled layers on the candidates are stored nontemporally: what the pass writes no longer finds room
+// in the 256 MB cache.  us of k_main with ordinary and with nontemporal stores: 480 K chunks and 1.1 % of the entries 702 and
+// 709; 570 K and 4.6 % 954 and 924; 900 K and 4.6 % 1617 and 1477; 1.2 M and 1.1 % 1906 and 1807, 9 % 2593 and 2193.  Smaller
+// sets lose by it (240 K chunks, 3 %: 370 and 383; 120 K, 1.1 %: 181 and 185), and the kernels that read the candidates too.
+constexpr uint32_t STREAM_CANDIDATES_CHUNKS = 524288;
 constexpr uint32_t FALLBACK_GRID = 1024;   // workgroups of a pass that usually has nothing to do
 // A selection from scratch takes the single pass from this many chunks in tiled layers on, if these hold this many each on
 // average; below, its four more launches and its tables per layer cost more than the two reads of g and h it saves.
@@ -508,7 +513,11 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
                 (const uint32_t*)p->pb.shist, (const unsigned long long*)p->pb.ghist, 0u);
     }
     p->hist_valid = true;
-    KLAUNCH(p, s, "k_main", k_main, dim3(p->main_wgs), dim3(FUSED_THREADS), p->pb, p->chunks_per_wg);
+    if (lo.nchunks >= STREAM_CANDIDATES_CHUNKS) {
+        KLAUNCH(p, s, "k_main", k_main<true>, dim3(p->main_wgs), dim3(FUSED_THREADS), p->pb, p->chunks_per_wg);
+    } else {
+        KLAUNCH(p, s, "k_main", k_main<false>, dim3(p->main_wgs), dim3(FUSED_THREADS), p->pb, p->chunks_per_wg);
+    }
     KLAUNCH(p, s, "k_reduce_parts", k_reduce_parts, dim3((LAYER_ENTRIES + REDUCE_ENTRIES - 1) / REDUCE_ENTRIES, lo.B), dim3(256), p->pb);
     if (err_table) {
         rc = launch_small_profile(p, err_table, s, side);
@@ -795,7 +804,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
     pb.lutc = at<uint8_t>(p, lo.lutc); pb.cursor = at<uint32_t>(p, lo.cursor);
     pb.spill_over = at<uint32_t>(p, lo.spill_over);
     pb.rec_start = at<uint32_t>(p, lo.rec_start); pb.rec_cnt = at<uint32_t>(p, lo.rec_cnt);
-    pb.tmp_idx = at<uint32_t>(p, lo.tmp_idx); pb.tmp_x = at<float>(p, lo.tmp_x);
+    pb.tmp_x = at<float>(p, lo.tmp_x); pb.tmp_i = at<uint16_t>(p, lo.tmp_i);
     p->main_wgs = lo.main_wgs;
     p->chunks_per_wg = lo.chunks_per_wg;
     // Layer states start as "nothing spilled, nothing cached".
@@ -818,7 +827,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
     cb.rec_amb = at<uint32_t>(p, lo.rec_amb); cb.c_gt = at<uint32_t>(p, lo.c_gt); cb.c_eq = at<uint32_t>(p, lo.c_eq);
     cb.o_base = at<uint32_t>(p, lo.o_base); cb.o_allow = at<uint32_t>(p, lo.o_allow);
     cb.cblk_big = at<uint32_t>(p, lo.cblk_big);
-    cb.tmp_idx = at<uint32_t>(p, lo.tmp_idx); cb.tmp_x = at<float>(p, lo.tmp_x);
+    cb.tmp_x = at<float>(p, lo.tmp_x); cb.tmp_i = at<uint16_t>(p, lo.tmp_i);
     cb.ncompact = at<uint32_t>(p, lo.ncompact);
     cb.fresh = pb.fresh;
     cb.state = pb.state;
@@ -1020,7 +1029,7 @@ int kimad_debug_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_co
     int rc = make_layout(n, L, J, *cfg, lo, nullptr);
     if (rc) return rc;
     out[0] = lo.parts; out[1] = lo.small_layer; out[2] = lo.state; out[3] = lo.cnt1; out[4] = lo.rec_cnt; out[5] = lo.hprev;
-    out[6] = lo.pool_prefix; out[7] = lo.sel; out[8] = lo.hist3; out[9] = lo.rec_start; out[10] = lo.tmp_idx;
+    out[6] = lo.pool_prefix; out[7] = lo.sel; out[8] = lo.hist3; out[9] = lo.rec_start; out[10] = lo.tmp_i;
     out[11] = lo.tmp_x; out[12] = lo.row0; out[13] = lo.total;
     return 0;
 }

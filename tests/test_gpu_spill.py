@@ -1,0 +1,60 @@
+"""The streaming pass's candidates: chunks that hold any number of them, around the sixty-four that are written at a time and
+the lines that space is handed out in, in workgroups whose share is short (small blocks) and long (large ones), with
+layers that begin anywhere in a line.  Payload and estimator against the oracle, bit for bit, over rounds of one plan."""
+import numpy as np
+import pytest
+
+from kimad_synth.gen import Workload
+from oracle import kimad_oracle as ko
+from tests import gpu_harness as gh
+
+pytestmark = pytest.mark.gpu
+
+COUNTS = [0, 1, 2, 15, 16, 17, 31, 32, 33, 47, 63, 64, 65, 66, 95, 96, 97, 127, 128, 129, 130, 200, 5, 7, 9, 11, 0, 0]
+
+
+def _gradient(sizes, seed):
+    """Small values, and in each chunk one of COUNTS large ones (a share below an eighth)."""
+    rng = np.random.default_rng(seed)
+    out, large = [], 0
+    for n in sizes:
+        x = (1e-3 * rng.standard_normal(n)).astype(np.float32)
+        for c in range(0, n, 1024):
+            m = min(int(rng.choice(COUNTS)), n - c)
+            at = c + rng.choice(min(1024, n - c), size=m, replace=False)
+            x[at] = (rng.uniform(3.0, 9.0, size=m) * rng.choice([-1.0, 1.0], size=m)).astype(np.float32)
+            large += m
+        out.append(x)
+    return np.concatenate(out), large
+
+
+@pytest.mark.parametrize("max_workgroups", [0, 1, 2, 3])
+@pytest.mark.parametrize("shift", [0, 1, 3])
+def test_any_number_of_candidates_in_a_chunk(max_workgroups, shift):
+    import torch
+    import paper_2312_08053_amd as kimad
+    sizes = [700 * 1024 + 13, 8193, 40 * 1024, 9 * 1024 + 1, 700, 31 * 1024 - 5]
+    d = sum(sizes)
+    ratios = np.unique(np.round(np.logspace(-3, 0, 40), 6))
+    gd = torch.empty(d + shift, dtype=torch.float32, device="cuda")[shift:]
+    hd = torch.zeros(d + shift, dtype=torch.float32, device="cuda")[shift:]
+    plan, modes = None, set()
+    for step in range(3):
+        g, large = _gradient(sizes, 10 * step + shift)
+        gd.copy_(torch.from_numpy(g))
+        h = hd.cpu().numpy().copy()
+        if plan is None:
+            budget = 8 * int(1.05 * large)
+            plan = kimad.Plan(gd, hd, sizes, ratios.tolist(), D=0, max_budget_bytes=budget, capacity_pairs=d,
+                              max_workgroups=max_workgroups)
+        status = plan.step(budget)
+        torch.cuda.synchronize()
+        assert status.cpu().tolist() == [0, 0]
+        work = Workload(name="spill", sizes=np.asarray(sizes, dtype=np.uint64), g=g, h=h, ratios=ratios, budget_bytes=budget, cost_units_D=0)
+        gL, hL = gh.oracle_layers(work)
+        E_ref, Kt = ko.profile(gL, hL, ratios)
+        gh.assert_table_close(plan.err_table.cpu().numpy(), E_ref, Kt, sizes)
+        K = plan.K.cpu().numpy()
+        gh.check_compress(work, plan, hd, K, plan.offsets.cpu().numpy(), plan.idx, plan.val)
+        modes |= {s["mode"] for s in plan.layer_states()}
+    assert 3 in modes                                   # candidates of the streaming pass served some of it
