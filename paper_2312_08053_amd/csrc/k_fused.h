@@ -571,13 +571,66 @@ __device__ __forceinline__ void main_chunk(const ProfileBuffers& pb, const MainC
     }
 }
 
-// A wave's chunks of a segment: its first one, then what the segment's counter hands out.
+// How far a workgroup may go with one histogram.  A packed entry counts to 2^20 - 1, which any PK_MAX_CHUNKS chunks fit.
+// Real layers spread over thousands of entries: before a stretch ends, one wave reads the counts and allows as many more
+// chunks as the fullest entry has room for, whatever they hold, while the others go on.  Only where that is next to
+// nothing does the stretch end there, with a part written out and the histogram cleared.
+// (Parts at every 1023 chunks were 212 MB for 10 GB of g and h, and every one of them emptied the compute unit.)
+enum : uint32_t { LIMIT_FREE = 0, LIMIT_READING = 1, LIMIT_FINAL = 2 };
+constexpr uint32_t LIMIT_NEAR = 64;             // chunks before the limit at which a wave sees to it
+constexpr uint32_t LIMIT_LEAST = 128;           // chunks that are worth going on for
+
+struct Segment {
+    uint32_t end;          // end of the workgroup's share of the layer
+    uint32_t used;         // entries of the histogram
+    uint32_t* next_chunk;  // LDS: first chunk no wave has taken yet
+    uint32_t* allowed;     // LDS: chunks below it may be counted
+    uint32_t* state;       // LDS: LIMIT_*
+};
+__device__ __forceinline__ uint32_t lds_load(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+
+__device__ __forceinline__ void main_extend(const MainCtx& cx, const Segment& sg) {
+    const uint32_t lane = lane_id();
+    uint32_t was = 0;
+    if (lane == 0) was = atomicCAS(sg.state, (uint32_t)LIMIT_FREE, (uint32_t)LIMIT_READING);
+    if (__builtin_amdgcn_readfirstlane(was) != LIMIT_FREE) return;
+    // What is not in the counts read below: chunks from `taken` on, and of those before it the one that a wave is at and the
+    // one it has taken ahead (a wave's LDS instructions run in order: when it takes a chunk, all but its last are counted).
+    const uint32_t taken = lds_load(sg.next_chunk);
+    wave_sync_lds();
+    uint32_t most = 0;
+    for (uint32_t b = lane; b < sg.used; b += 64) most = max(most, lds_load(reinterpret_cast<const uint32_t*>(cx.pk) + 2 * b + 1) >> 12);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) most = max(most, (uint32_t)__shfl_xor(most, d, 64));
+    const uint32_t room = (0xFFFFFu - most) / CHUNK, open = 2u * FUSED_WAVES;
+    const uint32_t end = min(sg.end, taken + (room > open ? room - open : 0u));
+    if (lane == 0) {
+        const bool on = end == sg.end || end >= *sg.allowed + LIMIT_LEAST;
+        if (on) __hip_atomic_store(sg.allowed, end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(sg.state, (uint32_t)(on ? LIMIT_FREE : LIMIT_FINAL), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    wave_sync_lds();
+}
+
+// A wave's chunks of a segment: its first one, then what the segment's counter hands out.  Returns where the segment ends as
+// far as the wave knows: sg.end, or where the stretch does.
 template <bool TWO, bool STREAM>
-__device__ __forceinline__ void main_walk(const ProfileBuffers& pb, const MainCtx& cx, const LayerDesc& L, WaveSpill& ws,
-                                          uint32_t chunk, uint32_t seg_end, uint32_t* next_chunk) {
-    while (chunk < seg_end) {
+__device__ __forceinline__ uint32_t main_walk(const ProfileBuffers& pb, const MainCtx& cx, const LayerDesc& L, WaveSpill& ws,
+                                              uint32_t chunk, const Segment& sg) {
+    uint32_t limit = __builtin_amdgcn_readfirstlane(lds_load(sg.allowed));
+    for (;;) {
+        if (limit < sg.end && chunk + LIMIT_NEAR >= limit) {
+            for (;;) {
+                main_extend(cx, sg);
+                const uint32_t state = __builtin_amdgcn_readfirstlane(lds_load(sg.state));
+                limit = __builtin_amdgcn_readfirstlane(lds_load(sg.allowed));    // (read after the state: final with it)
+                if (chunk < limit || state == LIMIT_FINAL || limit == sg.end) break;
+                __builtin_amdgcn_s_sleep(1);                                     // (another wave is reading)
+            }
+        }
+        if (chunk >= limit) return limit;
         uint32_t taken = 0;
-        if (lane_id() == 0) taken = atomicAdd(next_chunk, 1u);
+        if (lane_id() == 0) taken = atomicAdd(sg.next_chunk, 1u);
         QuadGH q[NQ];
         float x[NQ][4];
         uint32_t valid = 0;
@@ -600,7 +653,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint3
     __shared__ uint16_t stage_i[FUSED_WAVES * STAGE];
     __shared__ uint32_t pend[FUSED_WAVES * PEND * 3];             // 3 KB
     __shared__ uint32_t lds_cursor;
-    __shared__ uint32_t next_chunk;                               // first chunk of the segment no wave has taken yet
+    __shared__ uint32_t next_chunk, allowed, limit_state;         // Segment
     const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t c_begin = blockIdx.x * chunks_per_wg;
     const uint32_t c_end = min(pb.nchunks_total, c_begin + chunks_per_wg);
@@ -611,11 +664,10 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint3
         const uint32_t li = pb.big_layer[big];
         const LayerDesc L = pb.layers[li];
         const LayerState st = pb.state[big];
-        const uint32_t seg_end = min(min(c_end, L.chunk0 + L.nchunks), cur + PK_MAX_CHUNKS);
+        const uint32_t seg_end = min(c_end, L.chunk0 + L.nchunks);
         const uint32_t used = D1_BINS + st.nslots_d * D2_BINS;
-        for (uint32_t b = tid; b < used; b += FUSED_THREADS) pk[b] = 0ull;
-        if (tid == 0) { sq0 = 0ull; lds_cursor = 0u; next_chunk = cur + FUSED_WAVES; }
-        __syncthreads();
+        const Segment sg{seg_end, used, &next_chunk, &allowed, &limit_state};
+        if (tid == 0) lds_cursor = 0u;
         MainCtx cx;
         cx.pk = pk; cx.sq0 = &sq0;
         cx.lo19 = (st.slot_lo & 0xFFFFu) << (D1_SHIFT - D2_SHIFT); cx.span = st.run_a * D2_BINS;
@@ -636,41 +688,52 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint3
         ws.blk = 0; ws.fill = 0; ws.flushed = 0; ws.npend = 0; ws.have_blk = false;
 
         // (Fetching the wave's next chunk while the current one is worked on was tried at 16, 12 and 8
-        // waves per workgroup: no gain.  Measured with one thing removed at a time, the candidate and
-        // record stores cost this pass 4 % and the histogram atomics nothing; a workgroup streams its
-        // share about as fast as a bare loop of the same loads does.  The pass ends with its slowest
-        // workgroup, a tenth behind the average.)
+        // waves per workgroup: no gain.)
         // Waves take chunks from a counter, not in a fixed rotation: a wave's pace varies with what it
         // finds (spills, flushes, memory), and with fixed shares the segment's end waited for its slowest
         // wave for a good tenth of the pass.  The next chunk is asked for before the current one is
         // worked on, so the counter's round trip is never waited for.  No result depends on which wave
         // had which chunk.
         // (one copy of the loop per number of slot runs: testing for the second run in the loop cost 2 % of the pass)
-        if (cx.spanb == 0u) main_walk<false, STREAM>(pb, cx, L, ws, cur + wave, seg_end, &next_chunk);
-        else main_walk<true, STREAM>(pb, cx, L, ws, cur + wave, seg_end, &next_chunk);
-        if (ws.have_blk) spill_write<STREAM>(pb, ws, L.tmp0, ws.fill);
-        spill_records(pb, ws);
-        __syncthreads();
-        // This segment's histogram goes out as it is, with plain coalesced stores, as one "part" of the
-        // layer; k_reduce_parts adds the parts up.  (Adding into the layer's arrays with global atomics
-        // from here held every workgroup of a layer up on the same cache lines at the same moment.)
-        // Stores that go through to memory at once: left dirty in the L2, the lines were written back one by one among the
-        // streaming reads (10 GB of g and h without candidates: 1735 us with ordinary stores, 1640 so, 1660 nontemporal, 1510
-        // without any).
-        __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(pb.parts + (size_t)part * PART_STRIDE, 0, PART_STRIDE * 8u, 0x00027000);
-        const uint4* pk4 = reinterpret_cast<const uint4*>(pk);
-        for (uint32_t b = tid; b < used / 2u; b += FUSED_THREADS) {                  // `used` is even
-            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-            const uint4 e = pk4[b];
-            u32x4 v;
-            v.x = e.x; v.y = e.y; v.z = e.z; v.w = e.w;
-            constexpr int SC1 = 16;                                                  // device scope
-            __builtin_amdgcn_raw_buffer_store_b128(v, out, (int)(b * 16u), 0, SC1);
+        uint32_t made = 0;                          // parts of this segment
+        for (uint32_t start = cur; start < seg_end;) {
+            for (uint32_t b = tid; b < used; b += FUSED_THREADS) pk[b] = 0ull;
+            if (tid == 0) { sq0 = 0ull; next_chunk = start + FUSED_WAVES; allowed = min(seg_end, start + PK_MAX_CHUNKS); limit_state = LIMIT_FREE; }
+            __syncthreads();
+            uint32_t stop;
+            if (cx.spanb == 0u) stop = main_walk<false, STREAM>(pb, cx, L, ws, start + wave, sg);
+            else stop = main_walk<true, STREAM>(pb, cx, L, ws, start + wave, sg);
+            if (stop == seg_end) {
+                if (ws.have_blk) spill_write<STREAM>(pb, ws, L.tmp0, ws.fill);
+                spill_records(pb, ws);
+            }
+            __syncthreads();
+            // The histogram goes out as it is, with plain coalesced stores, as one "part" of the
+            // layer; k_reduce_parts adds the parts up.  (Adding into the layer's arrays with global atomics
+            // from here held every workgroup of a layer up on the same cache lines at the same moment.)
+            // Stores that go through to memory at once: left dirty in the L2, the lines were written back one by one among the
+            // streaming reads (10 GB of g and h without candidates, 1512 parts: 1735 us with ordinary stores, 1640 so, 1660
+            // nontemporal, 1510 without any).
+            __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(pb.parts + (size_t)(part + made) * PART_STRIDE, 0, PART_STRIDE * 8u, 0x00027000);
+            const uint4* pk4 = reinterpret_cast<const uint4*>(pk);
+            for (uint32_t b = tid; b < used / 2u; b += FUSED_THREADS) {              // `used` is even
+                typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+                const uint4 e = pk4[b];
+                u32x4 v;
+                v.x = e.x; v.y = e.y; v.z = e.z; v.w = e.w;
+                constexpr int SC1 = 16;                                              // device scope
+                __builtin_amdgcn_raw_buffer_store_b128(v, out, (int)(b * 16u), 0, SC1);
+            }
+            if (tid == 0) pb.parts[(size_t)(part + made) * PART_STRIDE + PK_ENTRIES] = sq0;
+            ++made;
+            // the next stretch clears the LDS array: its reads above must be done, the stores need not be
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            start = stop;
         }
-        if (tid == 0) pb.parts[(size_t)part * PART_STRIDE + PK_ENTRIES] = sq0;
-        ++part;
-        // the next segment clears the LDS array: its reads above must be done, the stores need not be
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        // there is room for a part every PK_MAX_CHUNKS chunks: which are there
+        const uint32_t planned = (seg_end - cur + PK_MAX_CHUNKS - 1u) / PK_MAX_CHUNKS;
+        for (uint32_t k = tid; k < planned; k += FUSED_THREADS) pb.part_used[part + k] = k < made ? 1u : 0u;
+        part += planned;
         cur = seg_end;
     }
 }
@@ -684,6 +747,8 @@ constexpr uint32_t LAYER_ENTRIES = D1_BINS + SLOT_STRIDE * D2_BINS;
 constexpr uint32_t REDUCE_ENTRIES = 128;        // entries per workgroup: two per lane, each of the 4 waves takes a quarter of the parts
 __global__ __launch_bounds__(256) void k_reduce_parts(ProfileBuffers pb) {
     __shared__ unsigned long long sh_c[3][REDUCE_ENTRIES], sh_t[3][REDUCE_ENTRIES];
+    constexpr uint32_t LIST = 1024;
+    __shared__ uint32_t list[LIST], listed;
     const uint32_t big = blockIdx.y, lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
     const uint32_t e = blockIdx.x * REDUCE_ENTRIES + 2u * lane;     // and e + 1; `used` is even
     // The totals over the layers that the prediction of this profile read are done with (that launch has ended), and
@@ -692,20 +757,31 @@ __global__ __launch_bounds__(256) void k_reduce_parts(ProfileBuffers pb) {
         for (uint32_t b = threadIdx.x; b < D1_BINS; b += 256u) pb.gprev[b] = 0ull;
     const uint32_t used = D1_BINS + pb.state[big].nslots_d * D2_BINS;
     const uint32_t p0 = pb.big_part0[big], np = pb.big_nparts[big];
-    unsigned long long cnt[2] = {0, 0}, t[2] = {0, 0};
-    if (e < used) {
-        const unsigned long long* src = pb.parts + (size_t)p0 * PART_STRIDE + e;
-        auto take = [&](const ulonglong2 v) {
-            cnt[0] += v.x >> 44; t[0] += v.x & PK_MASK;
-            cnt[1] += v.y >> 44; t[1] += v.y & PK_MASK;
-        };
-        auto part = [&](uint32_t k) { return *reinterpret_cast<const ulonglong2*>(src + (size_t)k * PART_STRIDE); };
-        uint32_t k = w;
-        for (; k + 12 < np; k += 16) {
-            const ulonglong2 v0 = part(k), v1 = part(k + 4), v2 = part(k + 8), v3 = part(k + 12);
-            take(v0); take(v1); take(v2); take(v3);
+    unsigned long long cnt[2] = {0, 0}, t[2] = {0, 0}, zeros_sq = 0;
+    // which of the layer's parts were written, LIST of them at a time (every entry's block looks for itself)
+    for (uint32_t q0 = 0; q0 < np; q0 += LIST) {
+        __syncthreads();
+        if (threadIdx.x == 0) listed = 0u;
+        __syncthreads();
+        for (uint32_t k = q0 + threadIdx.x; k < min(np, q0 + LIST); k += 256u)
+            if (pb.part_used[p0 + k]) list[atomicAdd(&listed, 1u)] = p0 + k;
+        __syncthreads();
+        const uint32_t n = listed;
+        if (e < used) {
+            auto take = [&](const ulonglong2 v) {
+                cnt[0] += v.x >> 44; t[0] += v.x & PK_MASK;
+                cnt[1] += v.y >> 44; t[1] += v.y & PK_MASK;
+            };
+            auto part = [&](uint32_t k) { return *reinterpret_cast<const ulonglong2*>(pb.parts + (size_t)list[k] * PART_STRIDE + e); };
+            uint32_t k = w;
+            for (; k + 12 < n; k += 16) {
+                const ulonglong2 v0 = part(k), v1 = part(k + 4), v2 = part(k + 8), v3 = part(k + 12);
+                take(v0); take(v1); take(v2); take(v3);
+            }
+            for (; k < n; k += 4) take(part(k));
+            if (e == 0u && w == 0u)
+                for (uint32_t q = 0; q < n; ++q) zeros_sq += pb.parts[(size_t)list[q] * PART_STRIDE + PK_ENTRIES];
         }
-        for (; k < np; k += 4) take(part(k));
     }
     if (w) {
         sh_c[w - 1][2 * lane] = cnt[0]; sh_c[w - 1][2 * lane + 1] = cnt[1];
@@ -728,7 +804,7 @@ __global__ __launch_bounds__(256) void k_reduce_parts(ProfileBuffers pb) {
             if ((bin >> 4) == 255u) {
                 s2 = t[u];
             } else if (eu == 0u) {
-                for (uint32_t q = 0; q < np; ++q) s2 += pb.parts[(size_t)(p0 + q) * PART_STRIDE + PK_ENTRIES];
+                s2 = zeros_sq;
             } else {
                 s2 = (t[u] << 8) + (cnt[u] << 7);
             }

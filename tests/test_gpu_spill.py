@@ -58,3 +58,31 @@ def test_any_number_of_candidates_in_a_chunk(max_workgroups, shift):
         gh.check_compress(work, plan, hd, K, plan.offsets.cpu().numpy(), plan.idx, plan.val)
         modes |= {s["mode"] for s in plan.layer_states()}
     assert 3 in modes                                   # candidates of the streaming pass served some of it
+
+
+@pytest.mark.parametrize("equal", [1.0, 0.95, 0.5, 0.1])
+@pytest.mark.parametrize("max_workgroups", [1, 2])
+def test_counts_of_one_value_beyond_a_histogram_entry(equal, max_workgroups):
+    """2.6 million entries to one workgroup, a share of them of one magnitude: an entry of the packed histogram holds 2^20 - 1
+    of them, so the workgroup's share is cut where it would not be for values that spread."""
+    import torch
+    import paper_2312_08053_amd as kimad
+    rng = np.random.default_rng(int(100 * equal))
+    sizes = [2600 * 1024 + 77, 9000]
+    d = sum(sizes)
+    ratios = np.logspace(-3, 0, 20)
+    gd, hd = torch.empty(d, dtype=torch.float32, device="cuda"), torch.zeros(d, dtype=torch.float32, device="cuda")
+    budget = int(0.03 * 4 * d)
+    plan = kimad.Plan(gd, hd, sizes, ratios.tolist(), D=500, max_budget_bytes=budget, max_workgroups=max_workgroups)
+    for _ in range(2):
+        g = (1e-2 * rng.standard_t(3, size=d)).astype(np.float32)
+        same = rng.random(d) < equal
+        g[same] = (0.0123 * np.sign(g[same])).astype(np.float32)
+        gd.copy_(torch.from_numpy(g))
+        hd.zero_()
+        assert plan.step(budget).cpu().tolist() == [0, 0]
+        work = Workload(name="equal", sizes=np.asarray(sizes, dtype=np.uint64), g=g, h=np.zeros_like(g), ratios=ratios, budget_bytes=budget, cost_units_D=500)
+        gL, hL = gh.oracle_layers(work)
+        E_ref, Kt = ko.profile(gL, hL, ratios)
+        gh.assert_table_close(plan.err_table.cpu().numpy(), E_ref, Kt, sizes)
+        gh.check_compress(work, plan, hd, plan.K.cpu().numpy(), plan.offsets.cpu().numpy(), plan.idx, plan.val)
