@@ -312,6 +312,31 @@ constexpr uint32_t PK_ENTRIES = D1_BINS + PRE_SLOTS * D2_BINS;     // 17920 entr
 constexpr uint32_t STAGE = 128;                                    // candidates a wave's window holds
 constexpr uint32_t PART_STRIDE = PK_ENTRIES + 8;                   // entries of one part: the LDS array, then the bin-0 sum
 
+// A part's head: whether there is one, then a bit per block of PART_BLOCK entries: whether it was written with 64 bits an
+// entry (a digit-1 block without the bit has no entry, a slot's without it is packed).
+constexpr uint32_t PART_BLOCK = 128;
+constexpr uint32_t PART_HEAD = 8;
+static_assert(PART_BLOCK == D2_BINS && D1_BINS % PART_BLOCK == 0 && (PK_ENTRIES / PART_BLOCK + 31) / 32 < PART_HEAD, "a slot is a block");
+
+// digit-1 bin of a slot of the two runs
+__device__ __forceinline__ uint32_t slot_bin_of(const LayerState& st, uint32_t s) {
+    return s < st.run_a ? (st.slot_lo & 0xFFFFu) + s : (st.slot_lo >> 16) + (s - st.run_a);
+}
+// An entry of a slot in 32 bits, [count:10 | sum:22]: every significand of the entry is M 2^12 + d with the same M, d < 2^12, so
+// (its square >> 24) is M^2 and less than 2^13 more; the sum of what is more.  False where the count or that sum is too
+// large, and for the exponents 0 and 255, whose terms are others.
+constexpr uint32_t NARROW_SHIFT = 22;
+__device__ __forceinline__ uint32_t slot_square(uint32_t bin, uint32_t d2) {
+    const uint32_t m = 0x800u | ((bin & 15u) << D2_BITS) | d2;
+    return m * m;
+}
+__device__ __forceinline__ bool pack_slot_entry(uint32_t bin, uint32_t d2, unsigned long long e, uint32_t& packed) {
+    const uint32_t cnt = (uint32_t)(e >> 44), exponent = bin >> 4;
+    const unsigned long long more = (e & PK_MASK) - (unsigned long long)cnt * slot_square(bin, d2);
+    packed = (cnt << NARROW_SHIFT) | (uint32_t)more;
+    return cnt < (1u << (32u - NARROW_SHIFT)) && more < (1ull << NARROW_SHIFT) && exponent != 0u && exponent != 255u;
+}
+
 __device__ __forceinline__ unsigned long long pk_term(uint32_t key) {
     const uint32_t m = key & 0x7FFFFFu, e = key >> 23;
     const uint32_t m24 = e ? (m | 0x800000u) : m;
@@ -654,6 +679,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint3
     __shared__ uint32_t pend[FUSED_WAVES * PEND * 3];             // 3 KB
     __shared__ uint32_t lds_cursor;
     __shared__ uint32_t next_chunk, allowed, limit_state;         // Segment
+    __shared__ uint32_t head[PART_HEAD];
     const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t c_begin = blockIdx.x * chunks_per_wg;
     const uint32_t c_end = min(pb.nchunks_total, c_begin + chunks_per_wg);
@@ -699,6 +725,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint3
         for (uint32_t start = cur; start < seg_end;) {
             for (uint32_t b = tid; b < used; b += FUSED_THREADS) pk[b] = 0ull;
             if (tid == 0) { sq0 = 0ull; next_chunk = start + FUSED_WAVES; allowed = min(seg_end, start + PK_MAX_CHUNKS); limit_state = LIMIT_FREE; }
+            if (tid < PART_HEAD) head[tid] = tid ? 0u : 1u;
             __syncthreads();
             uint32_t stop;
             if (cx.spanb == 0u) stop = main_walk<false, STREAM>(pb, cx, L, ws, start + wave, sg);
@@ -708,31 +735,57 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint3
                 spill_records(pb, ws);
             }
             __syncthreads();
-            // The histogram goes out as it is, with plain coalesced stores, as one "part" of the
-            // layer; k_reduce_parts adds the parts up.  (Adding into the layer's arrays with global atomics
-            // from here held every workgroup of a layer up on the same cache lines at the same moment.)
+            // The histogram goes out as one "part" of the layer; k_reduce_parts adds the parts up.  (Adding into the layer's
+            // arrays with global atomics from here held every workgroup of a layer up on the same cache lines at the same
+            // moment.)  A wave takes 128 entries at a time.  Of the digit-1 bins, blocks without an entry stay out.  An entry of
+            // a slot is packed into 32 bits where its block allows it: all its squares share their top 12 bits, so their sum is
+            // known from the count but for 22 bits.  (146 KB a part whatever is in it made 45 MB of stores at the pass's end, when
+            // nothing is left to hide them behind.)
             // Stores that go through to memory at once: left dirty in the L2, the lines were written back one by one among the
             // streaming reads (10 GB of g and h without candidates, 1512 parts: 1735 us with ordinary stores, 1640 so, 1660
             // nontemporal, 1510 without any).
-            __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(pb.parts + (size_t)(part + made) * PART_STRIDE, 0, PART_STRIDE * 8u, 0x00027000);
-            const uint4* pk4 = reinterpret_cast<const uint4*>(pk);
-            for (uint32_t b = tid; b < used / 2u; b += FUSED_THREADS) {              // `used` is even
+            {
                 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-                const uint4 e = pk4[b];
-                u32x4 v;
-                v.x = e.x; v.y = e.y; v.z = e.z; v.w = e.w;
+                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
                 constexpr int SC1 = 16;                                              // device scope
-                __builtin_amdgcn_raw_buffer_store_b128(v, out, (int)(b * 16u), 0, SC1);
+                __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(pb.parts + (size_t)(part + made) * PART_STRIDE, 0, PART_STRIDE * 8u, 0x00027000);
+                const uint32_t lane = lane_id(), blocks = used / PART_BLOCK;
+                const ulonglong2* pk2 = reinterpret_cast<const ulonglong2*>(pk);
+                for (uint32_t k = wave; k < blocks; k += FUSED_WAVES) {
+                    const ulonglong2 e = pk2[k * (PART_BLOCK / 2u) + lane];
+                    const int at = (int)(k * PART_BLOCK * 8u);
+                    bool narrow = false;
+                    if (k >= D1_BINS / PART_BLOCK) {
+                        const uint32_t s = k - D1_BINS / PART_BLOCK, bin = slot_bin_of(st, s);
+                        uint32_t n0, n1;
+                        const bool ok = pack_slot_entry(bin, 2u * lane, e.x, n0) && pack_slot_entry(bin, 2u * lane + 1u, e.y, n1);
+                        narrow = ballot(!ok) == 0ull;
+                        if (narrow) {
+                            u32x2 v;
+                            v.x = n0; v.y = n1;
+                            __builtin_amdgcn_raw_buffer_store_b64(v, out, at + (int)(lane * 8u), 0, SC1);
+                        }
+                    } else if (ballot((e.x | e.y) != 0ull) == 0ull) {
+                        continue;
+                    }
+                    if (!narrow) {
+                        u32x4 v;
+                        v.x = (uint32_t)e.x; v.y = (uint32_t)(e.x >> 32); v.z = (uint32_t)e.y; v.w = (uint32_t)(e.y >> 32);
+                        __builtin_amdgcn_raw_buffer_store_b128(v, out, at + (int)(lane * 16u), 0, SC1);
+                        if (lane == 0) atomicOr(&head[1u + k / 32u], 1u << (k % 32u));
+                    }
+                }
+                if (tid == 0) pb.parts[(size_t)(part + made) * PART_STRIDE + PK_ENTRIES] = sq0;
             }
-            if (tid == 0) pb.parts[(size_t)(part + made) * PART_STRIDE + PK_ENTRIES] = sq0;
             ++made;
             // the next stretch clears the LDS array: its reads above must be done, the stores need not be
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (tid < PART_HEAD) pb.part_head[(size_t)(part + made - 1u) * PART_HEAD + tid] = head[tid];
             start = stop;
         }
-        // there is room for a part every PK_MAX_CHUNKS chunks: which are there
+        // there is room for a part every PK_MAX_CHUNKS chunks: those that are not there
         const uint32_t planned = (seg_end - cur + PK_MAX_CHUNKS - 1u) / PK_MAX_CHUNKS;
-        for (uint32_t k = tid; k < planned; k += FUSED_THREADS) pb.part_used[part + k] = k < made ? 1u : 0u;
+        for (uint32_t k = made + tid; k < planned; k += FUSED_THREADS) pb.part_head[(size_t)(part + k) * PART_HEAD] = 0u;
         part += planned;
         cur = seg_end;
     }
@@ -748,40 +801,64 @@ constexpr uint32_t REDUCE_ENTRIES = 128;        // entries per workgroup: two pe
 __global__ __launch_bounds__(256) void k_reduce_parts(ProfileBuffers pb) {
     __shared__ unsigned long long sh_c[3][REDUCE_ENTRIES], sh_t[3][REDUCE_ENTRIES];
     constexpr uint32_t LIST = 1024;
-    __shared__ uint32_t list[LIST], listed;
+    __shared__ uint32_t list[LIST], listed[2];
     const uint32_t big = blockIdx.y, lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
     const uint32_t e = blockIdx.x * REDUCE_ENTRIES + 2u * lane;     // and e + 1; `used` is even
     // The totals over the layers that the prediction of this profile read are done with (that launch has ended), and
     // the scan that follows this one adds the new ones up: cleared here, between the two.
     if (blockIdx.x == 0u && big == 0u)
         for (uint32_t b = threadIdx.x; b < D1_BINS; b += 256u) pb.gprev[b] = 0ull;
-    const uint32_t used = D1_BINS + pb.state[big].nslots_d * D2_BINS;
+    const LayerState st = pb.state[big];
+    const uint32_t used = D1_BINS + st.nslots_d * D2_BINS;
     const uint32_t p0 = pb.big_part0[big], np = pb.big_nparts[big];
     unsigned long long cnt[2] = {0, 0}, t[2] = {0, 0}, zeros_sq = 0;
-    // which of the layer's parts were written, LIST of them at a time (every entry's block looks for itself)
-    for (uint32_t q0 = 0; q0 < np; q0 += LIST) {
+    // which of the layer's parts hold this block, LIST of them at a time: with 64 bits an entry from the list's start,
+    // packed from its end
+    static_assert(REDUCE_ENTRIES == PART_BLOCK, "one workgroup per block");
+    const uint32_t blk = blockIdx.x, word = 1u + blk / 32u;
+    const bool slot = blk >= D1_BINS / PART_BLOCK;
+    for (uint32_t q0 = 0; q0 < np && blk < used / PART_BLOCK; q0 += LIST) {
         __syncthreads();
-        if (threadIdx.x == 0) listed = 0u;
+        if (threadIdx.x < 2u) listed[threadIdx.x] = 0u;
         __syncthreads();
-        for (uint32_t k = q0 + threadIdx.x; k < min(np, q0 + LIST); k += 256u)
-            if (pb.part_used[p0 + k]) list[atomicAdd(&listed, 1u)] = p0 + k;
+        for (uint32_t k = q0 + threadIdx.x; k < min(np, q0 + LIST); k += 256u) {
+            const uint32_t* h = pb.part_head + (size_t)(p0 + k) * PART_HEAD;
+            const bool there = h[0] != 0u, wide = (h[word] >> (blk % 32u)) & 1u;
+            if (there && wide) list[atomicAdd(&listed[0], 1u)] = p0 + k;
+            else if (there && slot) list[LIST - 1u - atomicAdd(&listed[1], 1u)] = p0 + k;
+        }
         __syncthreads();
-        const uint32_t n = listed;
-        if (e < used) {
-            auto take = [&](const ulonglong2 v) {
-                cnt[0] += v.x >> 44; t[0] += v.x & PK_MASK;
-                cnt[1] += v.y >> 44; t[1] += v.y & PK_MASK;
-            };
-            auto part = [&](uint32_t k) { return *reinterpret_cast<const ulonglong2*>(pb.parts + (size_t)list[k] * PART_STRIDE + e); };
+        const uint32_t n = listed[0], m = listed[1];
+        // the parts four apart, four of a wave's loads at a time
+        auto each = [&](uint32_t count, auto load, auto take) {
             uint32_t k = w;
-            for (; k + 12 < n; k += 16) {
-                const ulonglong2 v0 = part(k), v1 = part(k + 4), v2 = part(k + 8), v3 = part(k + 12);
+            for (; k + 12 < count; k += 16) {
+                const auto v0 = load(k), v1 = load(k + 4), v2 = load(k + 8), v3 = load(k + 12);
                 take(v0); take(v1); take(v2); take(v3);
             }
-            for (; k < n; k += 4) take(part(k));
-            if (e == 0u && w == 0u)
-                for (uint32_t q = 0; q < n; ++q) zeros_sq += pb.parts[(size_t)list[q] * PART_STRIDE + PK_ENTRIES];
+            for (; k < count; k += 4) take(load(k));
+        };
+        each(n, [&](uint32_t k) { return *reinterpret_cast<const ulonglong2*>(pb.parts + (size_t)list[k] * PART_STRIDE + e); },
+             [&](const ulonglong2 v) {
+                 cnt[0] += v.x >> 44; t[0] += v.x & PK_MASK;
+                 cnt[1] += v.y >> 44; t[1] += v.y & PK_MASK;
+             });
+        if (m) {
+            unsigned long long c[2] = {0, 0}, more[2] = {0, 0};
+            each(m, [&](uint32_t k) { return *reinterpret_cast<const uint2*>(pb.parts + (size_t)list[LIST - 1u - k] * PART_STRIDE + blk * PART_BLOCK + lane); },
+                 [&](const uint2 v) {
+                     c[0] += v.x >> NARROW_SHIFT; more[0] += v.x & ((1u << NARROW_SHIFT) - 1u);
+                     c[1] += v.y >> NARROW_SHIFT; more[1] += v.y & ((1u << NARROW_SHIFT) - 1u);
+                 });
+            const uint32_t bin = slot_bin_of(st, blk - D1_BINS / PART_BLOCK);
+#pragma unroll
+            for (uint32_t u = 0; u < 2u; ++u) {
+                cnt[u] += c[u];
+                t[u] += more[u] + c[u] * slot_square(bin, 2u * lane + u);
+            }
         }
+        if (e == 0u && w == 0u)
+            for (uint32_t q = 0; q < n; ++q) zeros_sq += pb.parts[(size_t)list[q] * PART_STRIDE + PK_ENTRIES];
     }
     if (w) {
         sh_c[w - 1][2 * lane] = cnt[0]; sh_c[w - 1][2 * lane + 1] = cnt[1];

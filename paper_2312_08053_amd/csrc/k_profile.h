@@ -56,8 +56,8 @@ struct ProfileBuffers {
     LayerState* state;            // [B]
     const uint64_t* big_tmp0;     // [B] start of the layer's region in the candidate buffer (LayerDesc::tmp0)
     // histograms of the streaming pass, one copy ("part") per workgroup and layer, or more where a copy's counts fill up
-    uint32_t* part_used;          // [nparts] 1 where there is one
-    unsigned long long* parts;    // [nparts][PART_STRIDE] packed LDS entries as they were, then the exact bin-0 sum
+    uint32_t* part_head;          // [nparts][PART_HEAD] whether there is one, and how its blocks were written
+    unsigned long long* parts;    // [nparts][PART_STRIDE] the LDS entries, in blocks, then the exact bin-0 sum
     const uint32_t* wg_part0;     // [workgroups] first part of each workgroup (its parts follow in order)
     const uint32_t* big_part0;    // [B] first part of each big layer (room for one every PK_MAX_CHUNKS chunks)
     const uint32_t* big_nparts;   // [B]

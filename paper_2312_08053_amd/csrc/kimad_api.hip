@@ -47,7 +47,7 @@ struct Layout {
     uint64_t fresh = 0, hprev = 0, gprev = 0;
     uint64_t zero1_begin, cnt1, sq1, cnt2, sq2, diag, layer_flag, shist, ghist, cursor, spill_over, zero1_end;
     uint64_t cprev = 0;
-    uint64_t big_tmp0, parts, part_used, wg_part0, big_part0, big_nparts, zero1_mid;
+    uint64_t big_tmp0, parts, part_head, wg_part0, big_part0, big_nparts, zero1_mid;
     uint32_t main_wgs = 256, chunks_per_wg = 1, nparts = 0;
     uint64_t pool_prefix, pool_big, pool_t0, pool_cnt, pool_hist, tgt_unsel, tgt_base;
     uint32_t pool_cap = 1;
@@ -222,7 +222,7 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     lo.pool_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>((uint64_t)B * J, 1), POOL_LIMIT);
     lo.parts = take(std::max<uint64_t>(8ull * PART_STRIDE * (lo.nparts ? lo.nparts : 1), 4ull * lo.pool_cap * D3_BINS));
     lo.pool_hist = lo.parts;
-    lo.part_used = take(4ull * (lo.nparts ? lo.nparts : 1));
+    lo.part_head = take(4ull * PART_HEAD * (lo.nparts ? lo.nparts : 1));
     lo.small_layer = take(4ull * (S ? S : 1));
     lo.swg_layer = take(4ull * (nsw ? nsw : 1));
     lo.swg_first = take(4ull * (nsw ? nsw : 1));
@@ -797,7 +797,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
     pb.pool_hist = at<uint32_t>(p, lo.pool_hist); pb.pool_cap = lo.pool_cap;
     pb.tgt_unsel = at<uint32_t>(p, lo.tgt_unsel); pb.tgt_base = at<double>(p, lo.tgt_base);
     pb.state = at<LayerState>(p, lo.state); pb.big_tmp0 = at<uint64_t>(p, lo.big_tmp0);
-    pb.parts = at<unsigned long long>(p, lo.parts); pb.part_used = at<uint32_t>(p, lo.part_used); pb.wg_part0 = at<uint32_t>(p, lo.wg_part0);
+    pb.parts = at<unsigned long long>(p, lo.parts); pb.part_head = at<uint32_t>(p, lo.part_head); pb.wg_part0 = at<uint32_t>(p, lo.wg_part0);
     pb.big_part0 = at<uint32_t>(p, lo.big_part0); pb.big_nparts = at<uint32_t>(p, lo.big_nparts);
     pb.chunk_big = at<uint32_t>(p, lo.chunk_big); pb.chunk_first = at<uint32_t>(p, lo.chunk_first); pb.nchunks_total = lo.nchunks;
     pb.swg_layer = at<uint32_t>(p, lo.swg_layer); pb.swg_first = at<uint32_t>(p, lo.swg_first);
