@@ -372,9 +372,10 @@ __device__ __forceinline__ void wave_scan_pair(T v, T& inc, T& exc) {
     if (lane_id() == 0) exc = 0;
 }
 
+// (`nw`: the block's waves, or as many of its first as are still there.)
 template <typename T>
-__device__ __forceinline__ T block_exclusive_scan(T v, T* scratch, T* total) {
-    const uint32_t w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+__device__ __forceinline__ T block_exclusive_scan(T v, T* scratch, T* total, uint32_t nw) {
+    const uint32_t w = threadIdx.x >> 6;
     T inc, exc;
     wave_scan_pair(v, inc, exc);
     if (lane_id() == 63) scratch[w] = inc;
@@ -388,6 +389,10 @@ __device__ __forceinline__ T block_exclusive_scan(T v, T* scratch, T* total) {
     __syncthreads();
     if (total) *total = tot;
     return base + exc;
+}
+template <typename T>
+__device__ __forceinline__ T block_exclusive_scan(T v, T* scratch, T* total) {
+    return block_exclusive_scan<T>(v, scratch, total, blockDim.x >> 6);
 }
 
 }  // namespace kimad

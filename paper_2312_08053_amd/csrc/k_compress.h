@@ -535,9 +535,9 @@ __global__ __launch_bounds__(256, 8) void k_chunk_count(CompressBuffers cb, uint
 // block together keep min(their ties, quota) of them: the block's starting point follows from two
 // sums over the earlier chunks of the layer, which every workgroup takes for itself (no atomics,
 // no serial pass over the layer).
-__global__ __launch_bounds__(1024) void k_chunk_bases(CompressBuffers cb) {
+__device__ __forceinline__ void chunk_bases(const CompressBuffers& cb, uint32_t blk) {
     __shared__ uint32_t su[16];
-    const uint32_t blk = blockIdx.x, tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x;
     const uint32_t b = cb.cblk_big[blk];
     const uint32_t li = cb.big_layer[b];
     const LayerDesc L = cb.layers[li];
@@ -738,14 +738,14 @@ __global__ __launch_bounds__(256, 8) void k_finalize(CompressBuffers cb, uint32_
 // (Sorting the layer whole to mark its first K, then writing an index range per thread in dependent loads, took 74 us for
 // a layer of 8192 entries, 40 us for 4096 and 28 us for 2048 or fewer: as long as all the other kernels of a compression.)
 constexpr uint32_t SMALL_PER = SMALL_MAX / SMALL_THREADS;
-__global__ __launch_bounds__(SMALL_THREADS) void k_small_compress(CompressBuffers cb) {
+__device__ __forceinline__ void small_compress(const CompressBuffers& cb, uint32_t which) {
     __shared__ uint32_t hist[2048];
     __shared__ uint32_t su[16];
     __shared__ uint32_t rows[SMALL_PER * (SMALL_THREADS / 64)];     // per (row, wave): entries above the threshold | equal << 16
     __shared__ uint32_t sh_digit, sh_need;
     __shared__ int bad;
     const uint32_t tid = threadIdx.x, wave = tid >> 6;
-    const uint32_t li = cb.small_layer[blockIdx.x];
+    const uint32_t li = cb.small_layer[which];
     const LayerDesc L = cb.layers[li];
     // the lookup kernel refuses the whole call through the status word; small layers re-check
     // their own slice so that nothing is written out of bounds
@@ -848,6 +848,16 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_compress(CompressBuffer
             gstore(L.h + e, h[r] + add);
         }
     }
+}
+
+__global__ __launch_bounds__(SMALL_THREADS) void k_small_compress(CompressBuffers cb) { small_compress(cb, blockIdx.x); }
+
+// One launch for both: the blocks of chunks, and, from `nblk` on, a workgroup per small layer, which touch nothing of each
+// other's (as with k_predict: on a stream of their own the small layers cost the events that bring them there and back).
+__global__ __launch_bounds__(SMALL_THREADS) void k_chunk_bases(CompressBuffers cb, uint32_t nblk) {
+    static_assert(SMALL_THREADS == CBLOCK, "one thread per chunk of a block");
+    if (blockIdx.x < nblk) chunk_bases(cb, blockIdx.x);
+    else small_compress(cb, blockIdx.x - nblk);
 }
 
 }  // namespace kimad

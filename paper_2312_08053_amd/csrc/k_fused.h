@@ -86,16 +86,18 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void k_sample(ProfileBuffers pb) {
 // population through the layer's size), or the exact histogram of the previous profile on this plan (successive
 // gradients of a layer are distributed alike; a layer whose boundary bins moved is recounted like any other
 // misprediction).  `fold_zero`: also clear what a profile must find at zero (no separate clearing launch).
-__global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32_t* Ktab, uint32_t J,
-                                                 unsigned long long budget_pairs, unsigned long long unit_pairs,
-                                                 const uint32_t* __restrict__ counts,
-                                                 const unsigned long long* __restrict__ gcounts, uint32_t fold_zero) {
+constexpr uint32_t PREDICT_THREADS = 256;
+__device__ __forceinline__ void predict(const ProfileBuffers& pb, uint32_t big, uint32_t nbig, const uint32_t* Ktab, uint32_t J,
+                                        unsigned long long budget_pairs, unsigned long long unit_pairs,
+                                        const uint32_t* __restrict__ counts, const unsigned long long* __restrict__ gcounts,
+                                        uint32_t fold_zero) {
+    constexpr uint32_t WAVES = PREDICT_THREADS / 64;
     __shared__ uint32_t above[D1_BINS];        // sample entries in strictly higher bins
     __shared__ uint32_t bitmap[D1_BINS / 32];
     __shared__ uint32_t su[16];
     __shared__ unsigned long long s64[16];
     __shared__ uint32_t sh_gbin, sh_spill, sh_eighth, sh_ns, sh_gap, sh_knext;
-    const uint32_t tid = threadIdx.x, big = blockIdx.x;
+    const uint32_t tid = threadIdx.x;
     const uint32_t li = pb.big_layer[big];
     const LayerDesc L = pb.layers[li];
 
@@ -113,11 +115,11 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
     // (1) global threshold bin: the highest bin b with (entries of all layers in bins >= b) >= 1.25 x budget
     // (2.5 x for a wide link, whose sizes the estimate below says little about: most layers spill their eighth there)
     {
-        unsigned long long gc[16], sum = 0;
+        unsigned long long sum = 0;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) { gc[k] = gcounts[tid * 16u + k]; sum += gc[k]; }
+        for (int k = 0; k < 16; ++k) sum += gcounts[tid * 16u + k];
         unsigned long long tot;
-        const unsigned long long ex = block_exclusive_scan<unsigned long long>(sum, s64, &tot);
+        const unsigned long long ex = block_exclusive_scan<unsigned long long>(sum, s64, &tot, WAVES);
         unsigned long long ab = tot - ex - sum;            // entries above this thread's bins
         narrow = budget_pairs != 0ull && budget_pairs <= tot / 32ull;
         const unsigned long long want = narrow ? budget_pairs + budget_pairs / 4ull : budget_pairs * 5ull / 2ull;
@@ -126,8 +128,9 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
         if (budget_pairs && ab < want && ab + sum >= want) {
 #pragma unroll
             for (int k = 15; k >= 0; --k) {
-                if (ab + gc[k] >= want) { sh_gbin = tid * 16u + k; break; }
-                ab += gc[k];
+                const unsigned long long gc = gcounts[tid * 16u + k];      // (one thread's: held by all they would not fit 64 registers)
+                if (ab + gc >= want) { sh_gbin = tid * 16u + k; break; }
+                ab += gc;
             }
         }
         __syncthreads();
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
 #pragma unroll
     for (int k = 0; k < 16; ++k) csum += c[k];
     uint32_t ns_total;
-    const uint32_t cex = block_exclusive_scan<uint32_t>(csum, su, &ns_total);
+    const uint32_t cex = block_exclusive_scan<uint32_t>(csum, su, &ns_total, WAVES);
     {
         uint32_t run = cex;
 #pragma unroll
@@ -287,13 +290,27 @@ __global__ __launch_bounds__(256) void k_predict(ProfileBuffers pb, const uint32
     if (fold_zero) {
         // chunk records start out as "nothing spilled": every workgroup clears an equal share of all layers' records
         // (a layer's own workgroup clearing them made the largest layer's the last to finish by far)
-        const uint32_t per = (pb.nchunks_total + gridDim.x - 1u) / gridDim.x;
+        const uint32_t per = (pb.nchunks_total + nbig - 1u) / nbig;
         const uint32_t c_lo = big * per, c_hi = min(pb.nchunks_total, c_lo + per);
         for (uint32_t c = c_lo + tid; c < c_hi; c += 256) pb.rec_cnt[c] = 0u;
         if (tid == 0) { pb.layer_flag[big] = 0u; pb.cursor[big] = 0u; pb.spill_over[big] = 0u; }
         if (big == 0u && tid < 4u) pb.diag[tid] = 0u;
         if (big == 0u && tid == 4u) *pb.fresh = 0u;
     }
+}
+
+// One launch for both: a workgroup per tiled layer that predicts, and, from `nbig` on, one per small layer that profiles it
+// (without an err_table there are none of these).  The predictions are a few dozen workgroups that wait for memory; on a
+// stream of their own beside the kernels behind the pass the small layers cost the two events, 6 us each, that bring them
+// there and back.  (GPT-2-shaped, 98 small layers: predictions 14 us, small layers 15, both 17.)
+// (at least eight waves a SIMD: two workgroups to a compute unit)
+__global__ __launch_bounds__(SMALL_THREADS, 8) void k_predict(ProfileBuffers pb, uint32_t nbig, const uint32_t* Ktab, uint32_t J,
+                                                           unsigned long long budget_pairs, unsigned long long unit_pairs,
+                                                           const uint32_t* __restrict__ counts,
+                                                           const unsigned long long* __restrict__ gcounts, uint32_t fold_zero,
+                                                           double* err_table) {
+    if (blockIdx.x >= nbig) small_profile(pb, blockIdx.x - nbig, Ktab, J, err_table);
+    else if (threadIdx.x < PREDICT_THREADS) predict(pb, blockIdx.x, nbig, Ktab, J, budget_pairs, unit_pairs, counts, gcounts, fold_zero);
 }
 
 // ---------------------------------------------------------------------------------------------

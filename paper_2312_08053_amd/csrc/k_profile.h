@@ -729,14 +729,12 @@ __device__ __forceinline__ uint32_t next_pow2(uint32_t n) {
     return p;
 }
 
-__global__ __launch_bounds__(SMALL_THREADS) void k_small_profile(ProfileBuffers pb, const uint32_t* Ktab, uint32_t J,
-                                                                 double* err_table, uint32_t mark_fresh) {
+__device__ __forceinline__ void small_profile(const ProfileBuffers& pb, uint32_t which, const uint32_t* Ktab, uint32_t J, double* err_table) {
     __shared__ __align__(16) uint32_t a[SMALL_MAX];   // 32 KB: 0x7fffffff - key, ascending
     __shared__ double loc[SMALL_THREADS];             // per-thread sums, then exclusive suffix sums
     __shared__ double sd[16];
-    const uint32_t li = pb.small_layer[blockIdx.x];
+    const uint32_t li = pb.small_layer[which];
     const LayerDesc L = pb.layers[li];
-    if (blockIdx.x == 0 && threadIdx.x == 0 && mark_fresh) *pb.fresh = 1u;   // (plans without tiled layers have no other profile kernel)
     const uint32_t P = next_pow2(L.n < SORT_PER ? SORT_PER : L.n);
     {
         uint32_t v[SORT_PER];
@@ -801,6 +799,12 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_profile(ProfileBuffers 
         }
         err_table[(size_t)li * J + tid] = E;
     }
+}
+
+__global__ __launch_bounds__(SMALL_THREADS) void k_small_profile(ProfileBuffers pb, const uint32_t* Ktab, uint32_t J,
+                                                                 double* err_table, uint32_t mark_fresh) {
+    if (blockIdx.x == 0 && threadIdx.x == 0 && mark_fresh) *pb.fresh = 1u;   // (plans without tiled layers have no other profile kernel)
+    small_profile(pb, blockIdx.x, Ktab, J, err_table);
 }
 
 }  // namespace kimad

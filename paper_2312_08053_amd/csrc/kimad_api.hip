@@ -322,6 +322,9 @@ constexpr uint64_t WHOLE_ROWS_CELLS = 2048;
 // 709; 570 K and 4.6 % 954 and 924; 900 K and 4.6 % 1617 and 1477; 1.2 M and 1.1 % 1906 and 1807, 9 % 2593 and 2193.  Smaller
 // sets lose by it (240 K chunks, 3 %: 370 and 383; 120 K, 1.1 %: 181 and 185), and the kernels that read the candidates too.
 constexpr uint32_t STREAM_CANDIDATES_CHUNKS = 524288;
+// Up to this many small layers share the launch of a kernel on the main stream; more of them, several to a compute unit in
+// turn, go to the side stream beside what follows.
+constexpr uint32_t SMALL_BESIDE = 512;
 constexpr uint32_t FALLBACK_GRID = 1024;   // workgroups of a pass that usually has nothing to do
 // A selection from scratch takes the single pass from this many chunks in tiled layers on, if these hold this many each on
 // average; below, its four more launches and its tables per layer cost more than the two reads of g and h it saves.
@@ -502,16 +505,18 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
     }
     int rc = KIMAD_OK;
     const uint64_t unit = cost_unit(p->cfg, budget_pairs);
+    const bool with_small = err_table && lo.S && lo.S <= SMALL_BESIDE;
+    const dim3 grid(lo.B + (with_small ? lo.S : 0u)), block(with_small ? SMALL_THREADS : PREDICT_THREADS);
     if (p->hist_valid && !(p->cfg.flags & KIMAD_CFG_SAMPLE_ALWAYS)) {
         // prediction from the previous pass's exact histogram: no sampling pass, no clearing launch
-        KLAUNCH(p, s, "k_predict", k_predict, dim3(lo.B), dim3(256), p->pb, ktab, J, (unsigned long long)budget_pairs, (unsigned long long)unit,
-                (const uint32_t*)p->pb.hprev, (const unsigned long long*)p->pb.gprev, 1u);
+        KLAUNCH(p, s, "k_predict", k_predict, grid, block, p->pb, lo.B, ktab, J, (unsigned long long)budget_pairs, (unsigned long long)unit,
+                (const uint32_t*)p->pb.hprev, (const unsigned long long*)p->pb.gprev, 1u, err_table);
     } else {
         rc = zero_range(p, lo.zero1_mid, lo.zero1_end, s);   // the histogram tables are written whole by k_reduce_parts
         if (rc) return rc;
         KLAUNCH(p, s, "k_sample", k_sample, dim3(lo.nswg), dim3(SAMPLE_THREADS), p->pb);
-        KLAUNCH(p, s, "k_predict", k_predict, dim3(lo.B), dim3(256), p->pb, ktab, J, (unsigned long long)budget_pairs, (unsigned long long)unit,
-                (const uint32_t*)p->pb.shist, (const unsigned long long*)p->pb.ghist, 0u);
+        KLAUNCH(p, s, "k_predict", k_predict, grid, block, p->pb, lo.B, ktab, J, (unsigned long long)budget_pairs, (unsigned long long)unit,
+                (const uint32_t*)p->pb.shist, (const unsigned long long*)p->pb.ghist, 0u, err_table);
     }
     p->hist_valid = true;
     if (lo.nchunks >= STREAM_CANDIDATES_CHUNKS) {
@@ -520,7 +525,7 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
         KLAUNCH(p, s, "k_main", k_main<false>, dim3(p->main_wgs), dim3(FUSED_THREADS), p->pb, p->chunks_per_wg);
     }
     KLAUNCH(p, s, "k_reduce_parts", k_reduce_parts, dim3((LAYER_ENTRIES + REDUCE_ENTRIES - 1) / REDUCE_ENTRIES, lo.B), dim3(256), p->pb);
-    if (err_table) {
+    if (err_table && !with_small) {
         rc = launch_small_profile(p, err_table, s, side);
         if (rc) return rc;
     }
@@ -974,7 +979,8 @@ int kimad_compress_ef(kimad_plan_t* p, const uint64_t* K, const uint64_t* offset
             (int32_t)KIMAD_ERR_BAD_OFFSETS, (int32_t)KIMAD_ERR_STALE_PROFILE,
             (uint32_t)(reuse ? 1u : 0u), (uint32_t)(reuse || single ? 1u : 0u));
     hipStream_t ss = s;
-    if (lo.S) {
+    const bool with_bases = lo.B && lo.S <= SMALL_BESIDE;
+    if (lo.S && !with_bases) {
         ss = fork_side(p, s);                 // after the lookup: the small layers read its verdict
         KLAUNCH(p, ss, "k_small_compress", k_small_compress, dim3(lo.S), dim3(SMALL_THREADS), cb);
     }
@@ -989,7 +995,7 @@ int kimad_compress_ef(kimad_plan_t* p, const uint64_t* K, const uint64_t* offset
         // (the workgroups behind the candidates' leave after one load when no layer is served from g and h throughout)
         const uint32_t dblocks = std::min<uint32_t>(lo.ntiles, FALLBACK_GRID);
         KLAUNCH(p, s, "k_chunk_count", k_chunk_count, dim3(nblocks + dblocks), dim3(256), cb, lo.nchunks, chunk_big, nblocks, lo.ntiles);
-        KLAUNCH(p, s, "k_chunk_bases", k_chunk_bases, dim3(lo.ncblk), dim3(1024), cb);
+        KLAUNCH(p, s, "k_chunk_bases", k_chunk_bases, dim3(lo.ncblk + (with_bases ? lo.S : 0u)), dim3(SMALL_THREADS), cb, lo.ncblk);
         KLAUNCH(p, s, "k_finalize", k_finalize, dim3(cblocks + dblocks), dim3(256), cb, lo.nchunks, chunk_big, cblocks, lo.ntiles);
     }
     return join_side(p, s, ss);
