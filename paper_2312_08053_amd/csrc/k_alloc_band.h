@@ -26,6 +26,7 @@
 #pragma once
 #include "common.h"
 #include "k_alloc.h"
+#include "k_alloc_chain.h"
 
 namespace kimad {
 
@@ -432,10 +433,12 @@ __global__ __launch_bounds__(BOUNDS_THREADS) void k_dp_bounds(AllocBuffers ab, D
 //
 // The chain of L layers is sequential and a layer is little work (tens to hundreds of cells, a few records each), so what
 // counts is the length of one layer's dependent steps: a barrier, one LDS read of the previous row, an addition and a
-// minimum.  The layer loop therefore computes values only, in LDS, indexed from the band's first cell: a group of NP
-// neighbouring lanes shares a cell, its lanes take records s, s + NP, ... four at a time and form the minimum with DPP
-// moves; which record attained it is asked along the optimal path alone, afterwards.  Only the records that can connect
-// the bands are visited; they wait in LDS, a group of layers at a time.
+// minimum.  The layer loop therefore computes values only, in LDS, indexed from the band's first cell: a wave looks after
+// sixteen cells, the same ones in each of its four 16-lane rows, lane 16 r + k holds live record 4 k + r and hands it to
+// its row by DPP, and a minimum over the rows closes the layer (as in k_dp_chain); which record attained it is asked along
+// the optimal path alone, afterwards.  A row ends with a cell of +inf, which sources outside the band read.  Only the
+// records that can connect the bands are visited; they wait in LDS, a group of layers at a time, and a layer's are read
+// one layer ahead.
 //
 // All rows stay in LDS if they fit (BAND_CELLS), else two of them do and every row is also written to memory, from where
 // the walk stages them again, as many layers at a time as fit.
@@ -444,17 +447,12 @@ __global__ __launch_bounds__(BOUNDS_THREADS) void k_dp_bounds(AllocBuffers ab, D
 // is the one the sequential scan with a strict "<" would have kept.  One wave, two LDS reads deep per layer.  The lowest
 // member of a winner's run with the same rounded total, sizes and offsets follow for all layers in parallel.
 //
-// A layer costs what its instructions take to issue (a wave issues one every 8 to 10 cycles whatever it waits for) and the
-// barrier: about 0.85 us with the walk, however few cells there are (0.75 where a layer has one or two records, which
-// get a form of their own).  Four waves serve the narrow bands, sixteen the wide ones: 134 against 176 us at a mean width
-// of 74 cells (148 layers, rows of 4097 cells), 233 against 230 at 187.  (Eight waves: 145 and 209; they would cost every
-// allocation a third launch of 4 us.)  With fewer ratios there is less work in a cell, and four waves serve wider bands
-// as well: 500 layers with 5 ratios at a mean width of 157, 699 us by sixteen and 603 by four; 148 layers with 2 ratios
-// at 819, 264 and 313.  One loop that also kept winner and source cell of every cell, by sixteen waves, took 212 us on
-// the headline set, where these two launches take 191 and 4; it was faster with two or three ratios only (500 layers,
-// 3 ratios, rows of 4097 cells: 629 us, now 667).
-constexpr uint32_t BANDED_NARROW = 256, BANDED_WIDE = 1024;   // threads, for narrow and for wide bands
-constexpr uint32_t BANDED_MEAN = 128;           // mean width of a row up to which the bands are narrow (16 ratios or more; wider with fewer)
+// As many waves stay for the layer loop as the widest band has sixteens of cells, four to sixteen: the others leave, and the
+// barrier does without them.  148 layers, rows of 4097 cells: 105 to 117 us at bands of 1 and of 76 cells on average (the
+// layers 55 and 75, the walk 30, records, least total and sizes 15); a loop whose lanes read records and cells from LDS in
+// turn took 108 and 137, and 5 more for a second launch that left at once (four waves for narrow bands, sixteen for wide).
+constexpr uint32_t BANDED_THREADS = 1024;
+constexpr uint32_t BAND_FEW = 8;               // records of a layer that a lane takes one after another where the band is wide
 constexpr uint32_t BAND_LIVE_CAP = 2048;       // live records held in LDS at a time
 constexpr uint32_t BAND_CELLS = 12288;         // row cells held in LDS (96 KB); two of the longest rows fit
 static_assert(2u * DP_ROW_MAX <= BAND_CELLS, "two rows fit");
@@ -469,80 +467,72 @@ __device__ __forceinline__ BandRow band_row(const uint4& v) {
     return b;
 }
 
-// One layer: NP lanes per cell, U records of a lane at a time.  lrec, n: the layer's records; prow, crow: where the previous row and this one start in
-// `rows`, whose cell BAND_CELLS holds +inf; out: the row's copy in memory, or null.
-template <int NP, uint32_t T, int U = 4>
-__device__ __forceinline__ void banded_layer(const uint4* lrec, double* rows, uint32_t prow, uint32_t crow, double* out, uint32_t n,
-                                             const BandRow& p, const BandRow& c) {
-    const uint32_t tid = threadIdx.x, sub = tid % NP, shift = c.lo - p.lo;      // (may wrap: so does the source below, beyond the span)
-    for (uint32_t c0 = 0; c0 <= c.span; c0 += T / NP) {
-        const uint32_t cell = c0 + tid / NP, cm = cell + shift;
-        double best = DP_INF;
-        for (uint32_t k = sub; k < n; k += (uint32_t)U * NP) {
-            // U records, then U cells: two LDS round trips, not 2 U (left to itself the compiler waits for each)
-            uint4 r[U];
-            double v[U];
+// Minimum over the live records of the lane's row, of which there are at most 4 B, for one cell: `at` is the byte distance of
+// the cell from the previous row's first one, `limit` that of the cell of +inf behind its last one.
+template <int K4, int B>
+__device__ __forceinline__ void band_ask(uint32_t neg_cost, uint32_t at, uint32_t limit, uint32_t row, double (&t)[B][4]) {
+    uint32_t q[4];
+    row_addr_sub4<4 * K4>(at, neg_cost, q);
 #pragma unroll
-            for (int u = 0; u < U; ++u) r[u] = lrec[min(k + (uint32_t)u * NP, n - 1u)];   // (positions past the last record repeat it, which changes no minimum)
+    for (int u = 0; u < 4; ++u) t[K4][u] = *(lds_cdouble_ptr)(uintptr_t)(min(q[u], limit) + row);   // (a source below the row wraps far beyond its end)
+}
+template <int B>
+__device__ __forceinline__ double band_records(uint32_t neg_cost, double err, double one, uint32_t at, uint32_t limit, uint32_t row) {
+    double t[B][4], m[B];
+    band_ask<0>(neg_cost, at, limit, row, t);
+    if constexpr (B > 1) band_ask<1>(neg_cost, at, limit, row, t);
+    if constexpr (B > 2) band_ask<2>(neg_cost, at, limit, row, t);
+    if constexpr (B > 3) band_ask<3>(neg_cost, at, limit, row, t);
+    acc_rec_error4<0>(t[0], err, one);
+    if constexpr (B > 1) acc_rec_error4<4>(t[1], err, one);
+    if constexpr (B > 2) acc_rec_error4<8>(t[2], err, one);
+    if constexpr (B > 3) acc_rec_error4<12>(t[3], err, one);
 #pragma unroll
-            for (int u = 0; u < U; ++u) { materialise(r[u].x); materialise(r[u].y); materialise(r[u].z); }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t src = cm - r[u].z;                               // a cell cheaper than the record wraps far beyond the span
-                v[u] = rows[src <= p.span ? prow + src : BAND_CELLS];
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) asm volatile("" ::"v"(v[u]));
-#pragma unroll
-            for (int u = 0; u < U; ++u) v[u] += rec_err(r[u]);
-#pragma unroll
-            for (int u = 0; u < U; ++u) best = min_f64(best, v[u]);
-        }
-        best = group_min<NP>(best);
-        if (sub == 0u && cell <= c.span) {
-            rows[crow + cell] = best;
-            if (out) out[cell] = best;
-        }
-    }
+    for (int k = 0; k < B; ++k) m[k] = min_f64(min_f64(t[k][0], t[k][1]), min_f64(t[k][2], t[k][3]));
+    double best = m[0];
+    if constexpr (B > 1) best = min_f64(best, m[1]);
+    if constexpr (B > 2) best = min_f64(best, m[2]);
+    if constexpr (B > 3) best = min_f64(best, m[3]);
+    return min_over_rows(best);
 }
 
-template <uint32_t T>
-__global__ __launch_bounds__(T) void k_dp_banded(AllocBuffers ab, DpLists dl, BandBuffers bb, double* rows_g,
+__global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, DpLists dl, BandBuffers bb, double* rows_g,
                                                               uint32_t rstride, int32_t err_infeasible, int32_t err_nonfinite) {
-    constexpr uint32_t NWAVES = T / 64;
-    __shared__ double rows[BAND_CELLS + 1];               // and one cell of +inf
+    constexpr uint32_t MAX_WAVES = BANDED_THREADS / 64;
+    __shared__ double rows[BAND_CELLS];
     __shared__ uint4 recs[BAND_LIVE_CAP];                 // error bits, cost
     __shared__ uint4 s_row[BAND_MAX_L + 1];
     __shared__ double s_val[BAND_MAX_L + 1];              // the path's value per row
     __shared__ uint8_t s_k[BAND_MAX_L];                   // the path's live record per layer
+    __shared__ uint8_t s_first[BAND_MAX_L + 1];           // first live record of a layer
     __shared__ uint32_t su[16];
     __shared__ unsigned long long su64[16];
-    __shared__ double sd[NWAVES];
-    __shared__ uint32_t sc[NWAVES];
+    __shared__ double sd[MAX_WAVES];
+    __shared__ uint32_t sc[MAX_WAVES];
     __shared__ uint32_t s_bad;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t L = ab.L, J = ab.J, cap = ab.cap;
-    // one of the two launches does the work: the bands' widths, known here only, say which
-    if (((uint64_t)bb.info[1] * min(max(J, 4u), 16u) <= (uint64_t)BANDED_MEAN * 16u * L) != (T == BANDED_NARROW)) return;
     if (tid == 0) s_bad = 0u;
     __syncthreads();
+    const uint32_t NWAVES = min(max((bb.info[0] + 16u) / 16u, 4u), MAX_WAVES), T = NWAVES * 64u;
+    if (wave >= NWAVES) return;
     // rows and records: running sums over the layers
     uint32_t cells = 0u, live_total = 0u;
     for (uint32_t r0 = 0u; r0 <= L; r0 += T) {
         const uint32_t r = r0 + tid;
         const bool in = r <= L;
         const uint32_t lo = in ? min(bb.lo[r], cap) : 0u, hi = in ? max(lo, min(bb.hi[r], cap)) : 0u;
-        const uint32_t cnt = r < L ? min(bb.live[r] >> 8, 64u) : 0u;
+        const uint32_t live = r < L ? bb.live[r] : 0u, cnt = min(live >> 8, 64u);
         if (r < L && dl.bad[r]) s_bad = 1u;
         uint32_t ct, lt;
-        const uint32_t at = cells + block_exclusive_scan<uint32_t>(in ? hi - lo + 1u : 0u, su, &ct);
-        const uint32_t rec = live_total + block_exclusive_scan<uint32_t>(cnt, su, &lt);
-        if (in) s_row[r] = make_uint4(lo, hi - lo, at, rec);
+        const uint32_t at = cells + block_exclusive_scan<uint32_t>(in ? hi - lo + 2u : 0u, su, &ct, NWAVES);
+        const uint32_t rec = live_total + block_exclusive_scan<uint32_t>(cnt, su, &lt, NWAVES);
+        if (in) { s_row[r] = make_uint4(lo, hi - lo, at, rec); s_first[r] = (uint8_t)(live & 0xFFu); }
         cells += ct; live_total += lt;
     }
     __syncthreads();
     const bool any_bad = s_bad != 0u, hopeless = bb.info[4] != 0u;
-    const uint32_t wr = min(cap + 1u, BAND_CELLS / 2u);   // cells per row buffer when only two rows are kept
+    const uint32_t wr = min(cap + 2u, BAND_CELLS / 2u);   // cells per row buffer when only two rows are kept
     const bool all = cells <= BAND_CELLS;
 
     // the records of layers [a, b) into LDS, eight layers' loads in flight per wave
@@ -558,7 +548,7 @@ __global__ __launch_bounds__(T) void k_dp_banded(AllocBuffers ab, DpLists dl, Ba
                 const uint32_t rec = s_row[i].w, cnt = s_row[i + 1u].w - rec;
                 in[u] = i0 + (uint32_t)u < b && lane < cnt;
                 at[u] = rec - first + lane;
-                const size_t o = in[u] ? (size_t)i * J + min((bb.live[i] & 0xFFu) + lane, J - 1u) : 0;
+                const size_t o = in[u] ? (size_t)i * J + min((uint32_t)s_first[i] + lane, J - 1u) : 0;
                 e[u] = dl.e[2 * o]; w[u] = dl.w[o];
             }
 #pragma unroll
@@ -570,7 +560,10 @@ __global__ __launch_bounds__(T) void k_dp_banded(AllocBuffers ab, DpLists dl, Ba
     uint32_t at_last = 0u;                                // where row L's cells are
     uint32_t loaded = 0u;                                 // first layer of the records in LDS
     if (st == 0) {
-        if (tid == 0) { rows[0] = 0.0; rows[BAND_CELLS] = DP_INF; if (!all) rows_g[0] = 0.0; }
+        if (tid == 0) { rows[0] = 0.0; rows[1] = DP_INF; if (!all) rows_g[0] = 0.0; }
+        double one = 1.0;
+        asm volatile("" : "+v"(one));      // keep 1.0 in a vector register pair
+        const uint32_t k = (lane & 15u) * 4u + (lane >> 4);     // this lane's record
         uint32_t i = 0u;
         while (i < L) {
             // a group of layers whose live records fit LDS (at least one layer: a list has at most 64 records)
@@ -587,25 +580,60 @@ __global__ __launch_bounds__(T) void k_dp_banded(AllocBuffers ab, DpLists dl, Ba
             load_records(i, i1);
             loaded = i;
             __syncthreads();
+            // layer a -> b's record of this lane (beyond the last: one that changes no minimum)
+            auto record = [&](const BandRow& a, const BandRow& b) {
+                const uint32_t n = b.rec - a.rec;
+                uint4 r = recs[min(a.rec - g0 + min(k, max(n, 1u) - 1u), BAND_LIVE_CAP - 1u)];
+                r.y = k < n ? r.y : 0x7FF00000u;
+                r.x = k < n ? r.x : 0u;
+                r.z = 0u - 8u * r.z;
+                return r;
+            };
             BandRow p = band_row(s_row[i]), c = band_row(s_row[i + 1u]);
+            uint4 R = record(p, c);
+            BandRow nx = band_row(s_row[min(i + 2u, i1)]);
             for (; i < i1; ++i) {
-                const uint4 next = s_row[min(i + 2u, L)];                      // (asked for now: off the critical path)
-                const uint32_t n = c.rec - p.rec;
-                const uint4* lrec = recs + (p.rec - g0);
+                const uint32_t n = c.rec - p.rec, neg = R.z;
+                const double err = rec_err(R);
+                // the next layer's record and the row after that, asked for now: off the critical path
+                const uint4 after = s_row[min(i + 3u, i1)];
+                R = record(c, nx);
                 const uint32_t prow = all ? p.at : (i & 1u) * wr, crow = all ? c.at : ((i + 1u) & 1u) * wr;
                 double* out = all ? nullptr : rows_g + (size_t)(i + 1u) * rstride;
-                // lanes per cell: so that four records a lane cover the list, as far as the lanes go round
-                const uint32_t w = c.span + 1u;
-                const uint32_t np = min(n <= 4u ? 1u : n <= 8u ? 2u : n <= 16u ? 4u : n <= 32u ? 8u : 16u,
-                                        w <= T / 16u ? 16u : w <= T / 8u ? 8u : w <= T / 4u ? 4u : w <= T / 2u ? 2u : 1u);
-                if (n <= 2u) banded_layer<1, T, 2>(lrec, rows, prow, crow, out, n, p, c);
-                else if (np == 1u) banded_layer<1, T>(lrec, rows, prow, crow, out, n, p, c);
-                else if (np == 2u) banded_layer<2, T>(lrec, rows, prow, crow, out, n, p, c);
-                else if (np == 4u) banded_layer<4, T>(lrec, rows, prow, crow, out, n, p, c);
-                else if (np == 8u) banded_layer<8, T>(lrec, rows, prow, crow, out, n, p, c);
-                else banded_layer<16, T>(lrec, rows, prow, crow, out, n, p, c);
+                const uint32_t row = lds_addr(rows + prow), limit = 8u * (p.span + 1u), shift = c.lo - p.lo;   // (may wrap: so does the source, beyond the limit)
+                if (n <= BAND_FEW && c.span + 1u >= NWAVES * 16u) {
+                    // few records and more cells than the waves have sixteens: a cell a lane, the records one after another
+                    for (uint32_t c0 = wave * 64u; c0 <= c.span + 1u; c0 += NWAVES * 64u) {
+                        const uint32_t cell = c0 + lane, at = 8u * (cell + shift);
+                        double best = DP_INF;
+                        for (uint32_t j = 0; j < n; ++j) {
+                            const int from = (int)((j & 3u) * 16u + (j >> 2));             // (the lane that holds record j)
+                            const double e = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(err), from),
+                                                              __builtin_amdgcn_readlane(__double2loint(err), from));
+                            const uint32_t q = min(at + (uint32_t)__builtin_amdgcn_readlane((int)neg, from), limit);
+                            best = min_f64(best, *(lds_cdouble_ptr)(uintptr_t)(q + row) + e);
+                        }
+                        if (cell <= c.span + 1u) {
+                            rows[crow + cell] = cell <= c.span ? best : DP_INF;
+                            if (out && cell <= c.span) out[cell] = best;
+                        }
+                    }
+                } else {
+                    for (uint32_t c0 = wave * 16u; c0 <= c.span + 1u; c0 += NWAVES * 16u) {
+                        const uint32_t cell = c0 + (lane & 15u), at = 8u * (cell + shift);
+                        double best;
+                        if (n <= 16u) best = band_records<1>(neg, err, one, at, limit, row);
+                        else if (n <= 32u) best = band_records<2>(neg, err, one, at, limit, row);
+                        else if (n <= 48u) best = band_records<3>(neg, err, one, at, limit, row);
+                        else best = band_records<4>(neg, err, one, at, limit, row);
+                        if (lane < 16u && cell <= c.span + 1u) {
+                            rows[crow + cell] = cell <= c.span ? best : DP_INF;
+                            if (out && cell <= c.span) out[cell] = best;
+                        }
+                    }
+                }
                 lds_barrier();                             // the next layer reads this row (and the next group overwrites the records)
-                p = c; c = band_row(next);
+                p = c; c = nx; nx = band_row(after);
             }
         }
         at_last = all ? s_row[L].z : (L & 1u) * wr;
@@ -697,7 +725,7 @@ __global__ __launch_bounds__(T) void k_dp_banded(AllocBuffers ab, DpLists dl, Ba
         unsigned long long K = 0ull;
         uint32_t j = 0u;
         if (i < L) {
-            const size_t o = (size_t)i * J + min((bb.live[i] & 0xFFu) + (uint32_t)s_k[i], J - 1u);
+            const size_t o = (size_t)i * J + min((uint32_t)s_first[i] + (uint32_t)s_k[i], J - 1u);
             const uint32_t jj = dl.jj[o];
             const double from = s_val[i], to = s_val[i + 1u];
             j = jj >> 8;
@@ -711,7 +739,7 @@ __global__ __launch_bounds__(T) void k_dp_banded(AllocBuffers ab, DpLists dl, Ba
             K = ab.Kout[(size_t)i * J + j];
         }
         unsigned long long total;
-        const unsigned long long off = carry + block_exclusive_scan<unsigned long long>(K, su64, &total);
+        const unsigned long long off = carry + block_exclusive_scan<unsigned long long>(K, su64, &total, NWAVES);
         if (i < L) { ab.j_out[i] = (int32_t)j; ab.K_out[i] = K; ab.offsets_out[i] = off; }
         carry += total;
     }

@@ -58,9 +58,12 @@ __device__ __forceinline__ double min_over_rows(double v) {
 // Bound by the chain barrier, LDS read, four fp64 additions, minimum over the rows, LDS write: 0.22 us a layer in the first
 // workgroup, and 1 to 2 us that each workgroup starts behind the one below it.  (The compute waves wait for no memory at
 // all: with the records asked for by them, and the cells' stores in the same queue, a layer took 0.4 us.  148 layers of
-// 999 cells: 4 compute waves 61 us, 8 62, 3 65; one loader wave a group 71, two 61, four 62; four groups of one wave 91.)
-constexpr uint32_t CHAIN_WAVES = 4;             // compute waves
-constexpr uint32_t CHAIN_CELLS = 16 * CHAIN_WAVES;
+// 999 cells: 4 compute waves 61 us, 8 62, 3 65; one loader wave a group 71, two 61, four 62; four groups of one wave 91.
+// Few layers want few workgroups, each of which starts behind the one below, many a short layer: all launches of the
+// allocation with 64 ratios and four or eight waves, 20 layers 41 and 39 us, 60 61 and 56, 148 91 and 91, 500 219 and 234, 1000
+// 309 and 342; with 2000 cells 60 layers 79 and 67.  Rows beyond 2048 cells take four, whose loaders leave no room for
+// eight: 148 layers of 4097 cells 260 and 455.)
+constexpr uint32_t CHAIN_NARROW_L = 128;        // layers from which on four waves look after rows of up to 1024 cells
 constexpr uint32_t CHAIN_LOADERS = 2;
 constexpr uint32_t CHAIN_RECS = 4;              // layers whose records are in LDS, and under way from memory
 static_assert(CHAIN_RECS % 2 == 0, "the rows change places every layer");
@@ -95,7 +98,8 @@ __device__ __forceinline__ double chain_records(uint32_t neg_cost, double err, d
     return min_f64(best, DP_INF);                 // (never a NaN: a cell holds a number or ROW_EMPTY)
 }
 
-// The layers, for one compute wave.
+// The layers, for one compute wave.  CELLS: cells of the workgroup, and of +inf before cost 0 of its rows.
+template <uint32_t CELLS>
 __device__ __forceinline__ void chain_compute(uint32_t layers, double* rows_g, uint32_t rstride, uint32_t c0, uint32_t wave, double* row_a,
                                               double* row_b, const uint4 (*recs)[64]) {
     const uint32_t lane = lane_id(), c = c0 + wave * 16u + (lane & 15u);
@@ -107,7 +111,7 @@ __device__ __forceinline__ void chain_compute(uint32_t layers, double* rows_g, u
 #pragma unroll
         for (uint32_t u = 0; u < CHAIN_RECS; ++u) {
             if (i0 + u >= layers) break;
-            const uint32_t at = lds_addr(((u & 1u) ? row_b : row_a) + CHAIN_CELLS + c);
+            const uint32_t at = lds_addr(((u & 1u) ? row_b : row_a) + CELLS + c);
             const uint32_t neg = R.z, n = (uint32_t)__builtin_amdgcn_readfirstlane(R.w);
             const double err = rec_err(R);
             auto next = [&]() { R = recs[(u + 1u) % CHAIN_RECS][lane]; };
@@ -118,7 +122,7 @@ __device__ __forceinline__ void chain_compute(uint32_t layers, double* rows_g, u
             else best = chain_records<4>(neg, err, one, at, next);
             best = min_over_rows(best);
             if (lane < 16u) {
-                ((u & 1u) ? row_a : row_b)[CHAIN_CELLS + c] = best;
+                ((u & 1u) ? row_a : row_b)[CELLS + c] = best;
                 cell_store(out, best);
             }
             out += rstride;
@@ -172,7 +176,7 @@ struct ChainRecords {
 };
 
 // The lower cells of rows g + 1, g + 1 + CHAIN_LOADERS, ..., for one wave of a loader group: cells first, first + 64 GW, ...
-template <int M, uint32_t GW>
+template <int M, uint32_t GW, uint32_t CELLS>
 __device__ __forceinline__ void chain_load(const AllocBuffers& ab, const double* rows_g, uint32_t rstride, uint32_t c0, uint32_t g,
                                            uint32_t first, double* row_a, double* row_b) {
     constexpr uint32_t N = CHAIN_LOADERS;
@@ -193,7 +197,7 @@ __device__ __forceinline__ void chain_load(const AllocBuffers& ab, const double*
     uint32_t i = 0;                                   // layers whose barrier is behind us
     for (; i < min(g, ab.L); ++i) lds_barrier();
     static_assert(N % 2 == 0, "a group's rows all go to the same half of LDS");
-    double* dst = ((g & 1u) ? row_a : row_b) + CHAIN_CELLS;
+    double* dst = ((g & 1u) ? row_a : row_b) + CELLS;
     while (i < ab.L) {
         uint32_t polls = 0;
         while (any_empty()) {
@@ -211,46 +215,47 @@ __device__ __forceinline__ void chain_load(const AllocBuffers& ab, const double*
     }
 }
 
-// GW: waves of a loader group.
-constexpr uint32_t chain_threads(uint32_t gw) { return 64u * (CHAIN_WAVES + 1u + CHAIN_LOADERS * gw); }
-template <uint32_t MAXC, uint32_t GW>
-__global__ __launch_bounds__(chain_threads(GW)) void k_dp_chain(AllocBuffers ab, DpLists dl, double* __restrict__ rows_g, uint32_t rstride) {
-    constexpr uint32_t NT = chain_threads(GW);
-    __shared__ double rows[2][CHAIN_CELLS + MAXC];       // CHAIN_CELLS cells of +inf before cost 0: a record costs at most c_hi here
+// W: compute waves, GW: waves of a loader group, MAXC: cells of the longest row.
+constexpr uint32_t chain_threads(uint32_t w, uint32_t gw) { return 64u * (w + 1u + CHAIN_LOADERS * gw); }
+template <uint32_t MAXC, uint32_t W, uint32_t GW>
+__global__ __launch_bounds__(chain_threads(W, GW)) void k_dp_chain(AllocBuffers ab, DpLists dl, double* __restrict__ rows_g, uint32_t rstride) {
+    constexpr uint32_t NT = chain_threads(W, GW), CELLS = 16u * W;
+    static_assert(MAXC % CELLS == 0, "whole workgroups");
+    __shared__ double rows[2][CELLS + MAXC];       // CELLS cells of +inf before cost 0: a record costs at most c_hi here
     __shared__ uint4 recs[CHAIN_RECS][64];
     __shared__ uint32_t sh_b;
     const uint32_t tid = threadIdx.x;
     if (tid == 0) sh_b = atomicAdd(&ab.flags[1], 1u);
     __syncthreads();
-    const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane(sh_b) * CHAIN_CELLS;
+    const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane(sh_b) * CELLS;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
-    for (uint32_t x = tid; x < 2u * CHAIN_CELLS + c0; x += NT) {
-        rows[0][x] = x == CHAIN_CELLS ? 0.0 : DP_INF;
+    for (uint32_t x = tid; x < 2u * CELLS + c0; x += NT) {
+        rows[0][x] = x == CELLS ? 0.0 : DP_INF;
         rows[1][x] = DP_INF;
     }
-    if (wave == CHAIN_WAVES) {
-        ChainRecords cr{ab, dl, c0 + CHAIN_CELLS - 1u, recs};
+    if (wave == W) {
+        ChainRecords cr{ab, dl, c0 + CELLS - 1u, recs};
         cr.start();
         __syncthreads();
         cr.run();
         return;
     }
     __syncthreads();
-    if (wave < CHAIN_WAVES) {
-        chain_compute(ab.L, rows_g, rstride, c0, wave, rows[0], rows[1], recs);
+    if (wave < W) {
+        chain_compute<CELLS>(ab.L, rows_g, rstride, c0, wave, rows[0], rows[1], recs);
         return;
     }
-    const uint32_t load = wave - CHAIN_WAVES - 1u, g = load / GW, first = load % GW * 64u + lane_id();
+    const uint32_t load = wave - W - 1u, g = load / GW, first = load % GW * 64u + lane_id();
     const uint32_t m = (c0 + 64u * GW - 1u) / (64u * GW);
     constexpr uint32_t MOST = (MAXC + 64u * GW - 1u) / (64u * GW);
     if (m == 0u) {
         for (uint32_t i = 0; i < ab.L; ++i) lds_barrier();
     } else if (m <= 4u) {
-        chain_load<4, GW>(ab, rows_g, rstride, c0, g, first, rows[0], rows[1]);
+        chain_load<4, GW, CELLS>(ab, rows_g, rstride, c0, g, first, rows[0], rows[1]);
     } else if (MOST <= 8u || m <= 8u) {
-        chain_load<8, GW>(ab, rows_g, rstride, c0, g, first, rows[0], rows[1]);
+        chain_load<8, GW, CELLS>(ab, rows_g, rstride, c0, g, first, rows[0], rows[1]);
     } else {
-        chain_load<(int)(MOST > 8u ? MOST : 8u), GW>(ab, rows_g, rstride, c0, g, first, rows[0], rows[1]);
+        chain_load<(int)(MOST > 8u ? MOST : 8u), GW, CELLS>(ab, rows_g, rstride, c0, g, first, rows[0], rows[1]);
     }
 }
 

@@ -312,9 +312,7 @@ uint64_t cost_unit(const kimad_config_t& cfg, uint64_t P) {
 
 // Rows from this many cost cells on take the banded recurrence by themselves.
 constexpr uint64_t BAND_AUTO_CELLS = 1537;
-// With few ratios the lists are short and whole rows cheap, as long as a thread has no more than four cells: 500 layers
-// with 5 ratios 433 us against 563 in the band at 1601 cells, 448 against 521 at 2001 and 631 against 578 at 2601; with 7
-// ratios 462 against 551 and 477 against 477, with 10 531 against 559 but for 148 layers 193 against 180.
+// With few ratios the lists are short, and whole rows by many workgroups are cheaper than a band by one.
 constexpr uint32_t WHOLE_ROWS_J = 7;
 constexpr uint64_t WHOLE_ROWS_CELLS = 2048;
 // From this many chunks in tiled layers on the candidates are stored nontemporally: what the pass writes no longer finds room
@@ -379,6 +377,8 @@ struct kimad_plan {
     std::vector<uint32_t> ktab;      // host copy of K_ij
     std::vector<uint32_t> kmax;      // K_{i,J-1}
     double ratio0 = 0.0;             // the grid's smallest ratio
+    uint64_t band_unit = 0, band_cap = 0;   // cost unit and capacity that band_fits holds for (band_takes)
+    bool band_fits = false;
     char* ws = nullptr;
     int device = 0;
     uint32_t main_wgs = 256;         // persistent workgroups of the fused pass (one per compute unit)
@@ -584,6 +584,28 @@ unsigned char* static_scratch_of_current_device() {
     return g_scratch_ptr[dev];
 }
 
+// Whether the candidate lists of all layers fit the bounds kernel, which otherwise leaves the bands as wide as the rows: one
+// workgroup then sweeps what many share in whole rows (500 layers with 64 ratios, rows of 4097 cells: 9.6 ms, and 0.63).  As
+// many entries as there are different costs up to the capacity, in a table whose errors fall along a row.
+bool band_takes(kimad_plan* p, uint64_t unit, uint64_t cap) {
+    const uint64_t L = p->lo.L, J = p->lo.J;
+    if (L * J <= BAND_LCAP) return true;
+    if (p->band_unit != unit || p->band_cap != cap) {        // (counted once per budget)
+        uint64_t entries = 0;
+        for (uint64_t i = 0; i < L && entries <= BAND_LCAP; ++i) {
+            uint64_t last = 0;
+            for (uint64_t j = 0; j < J; ++j) {
+                const uint64_t w = (p->ktab[i * J + j] + unit - 1) / unit;
+                if (w > cap) break;
+                entries += w != last;
+                last = w;
+            }
+        }
+        p->band_unit = unit; p->band_cap = cap; p->band_fits = entries <= BAND_LCAP;
+    }
+    return p->band_fits;
+}
+
 int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_table, uint64_t budget_bytes,
                      int32_t* j_out, uint64_t* K_out, uint64_t* offsets_out, int32_t* status_out, hipStream_t s) {
     const Layout& lo = p->lo;
@@ -624,7 +646,8 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
         const uint32_t rstride = ws.rstride;
         const bool band = lo.L <= BAND_MAX_L && !(p->cfg.flags & KIMAD_CFG_FULL_DP) &&
                           ((p->cfg.flags & KIMAD_CFG_BAND_DP) ||
-                           (cap + 1 >= BAND_AUTO_CELLS && !(lo.J <= WHOLE_ROWS_J && cap + 1 <= WHOLE_ROWS_CELLS)));
+                           (cap + 1 >= BAND_AUTO_CELLS && lo.J > 1 && !(lo.J <= WHOLE_ROWS_J && cap + 1 <= WHOLE_ROWS_CELLS) &&
+                            band_takes(p, unit, cap)));
         KLAUNCH(p, s, "k_dp_prep", k_dp_prep, dim3(lo.L), dim3(64), ab, dl, band ? 1u : 0u, band ? (double*)nullptr : rows_g,
                 (uint64_t)rstride, 0u);
         if (band) {
@@ -632,19 +655,18 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
             BandBuffers bb = ws.band;
             bb.table = rows_g;                    // (a stored row has at least BAND_NLAM cells)
             KLAUNCH(p, s, "k_dp_bounds", k_dp_bounds, dim3(1), dim3(BOUNDS_THREADS), ab, dl, bb);
-            KLAUNCH(p, s, "k_dp_banded", (k_dp_banded<BANDED_NARROW>), dim3(1), dim3(BANDED_NARROW), ab, dl, bb, rows_g, rstride,
-                    (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE);
-            KLAUNCH(p, s, "k_dp_banded", (k_dp_banded<BANDED_WIDE>), dim3(1), dim3(BANDED_WIDE), ab, dl, bb, rows_g, rstride,
+            KLAUNCH(p, s, "k_dp_banded", k_dp_banded, dim3(1), dim3(BANDED_THREADS), ab, dl, bb, rows_g, rstride,
                     (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE);
             return KIMAD_OK;
         }
-        const uint32_t groups = (uint32_t)(cap / CHAIN_CELLS + 1);
-        if (cap + 1 <= 1024) {
-            KLAUNCH(p, s, "k_dp_chain", (k_dp_chain<1024, 2>), dim3(groups), dim3(chain_threads(2)), ab, dl, rows_g, rstride);
+        if (cap + 1 <= 1024 && lo.L > CHAIN_NARROW_L) {
+            KLAUNCH(p, s, "k_dp_chain", (k_dp_chain<1024, 4, 2>), dim3((uint32_t)(cap / 64 + 1)), dim3(chain_threads(4, 2)), ab, dl, rows_g, rstride);
+        } else if (cap + 1 <= 1024) {
+            KLAUNCH(p, s, "k_dp_chain", (k_dp_chain<1024, 8, 2>), dim3((uint32_t)(cap / 128 + 1)), dim3(chain_threads(8, 2)), ab, dl, rows_g, rstride);
         } else if (cap + 1 <= 2048) {
-            KLAUNCH(p, s, "k_dp_chain", (k_dp_chain<2048, 4>), dim3(groups), dim3(chain_threads(4)), ab, dl, rows_g, rstride);
+            KLAUNCH(p, s, "k_dp_chain", (k_dp_chain<2048, 8, 3>), dim3((uint32_t)(cap / 128 + 1)), dim3(chain_threads(8, 3)), ab, dl, rows_g, rstride);
         } else {
-            KLAUNCH(p, s, "k_dp_chain", (k_dp_chain<DP_ROW_MAX, 5>), dim3(groups), dim3(chain_threads(5)), ab, dl, rows_g, rstride);
+            KLAUNCH(p, s, "k_dp_chain", (k_dp_chain<DP_ROW_MAX, 4, 5>), dim3((uint32_t)(cap / 64 + 1)), dim3(chain_threads(4, 5)), ab, dl, rows_g, rstride);
         }
         KLAUNCH(p, s, "k_dp_choice", k_dp_choice, dim3(cell_blocks, lo.L), dim3(256), ab, dl, (const double*)rows_g, rstride);
         KLAUNCH(p, s, "k_dp_walk", k_dp_walk, dim3(1), dim3(1024), ab, (const double*)(rows_g + (size_t)lo.L * rstride),

@@ -36,8 +36,8 @@ def _plan(sizes, ratios, budget):
 @pytest.mark.parametrize("J", [1, 5, 16, 17, 33, 64])
 def test_edges_of_the_rows(cells, J):
     import torch
-    for L in (1, 2, 3, 4, 5, 13):
-        if L >= cells:
+    for L in (1, 2, 3, 4, 5, 13, 130):
+        if L >= cells or (L == 130 and cells not in (1024, 1025)):        # (many layers of short rows: narrower workgroups)
             continue
         ratios, sizes, Kt, E = _case(cells, J, L, 1000 * cells + 10 * J + L)
         budget = 8 * (cells - 1)
