@@ -172,6 +172,19 @@ __global__ __launch_bounds__(256) void k_lookup(CompressBuffers cb, int32_t err_
     if (tid == 0 && (!reuse || !bad)) *cb.fresh = 0u;
 }
 
+// A value that is the same in every lane, in scalar registers.
+template <typename T>
+__device__ __forceinline__ T uniform(const T& v) {
+    static_assert(sizeof(T) % 4 == 0, "whole registers");
+    uint32_t w[sizeof(T) / 4];
+    __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+    for (size_t k = 0; k < sizeof(T) / 4; ++k) w[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[k]);
+    T r;
+    __builtin_memcpy(&r, w, sizeof(T));
+    return r;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Streaming compaction pass (layers whose threshold lies below the spilled range, or all layers
 // when no fused profile preceded).  One wave per chunk; a workgroup of 4 waves walks the chunks
@@ -180,16 +193,29 @@ __global__ __launch_bounds__(256) void k_lookup(CompressBuffers cb, int32_t err_
 // Tiles are taken in a grid-stride loop; *cb.ncompact (set by k_lookup) is the number of layers that
 // need this pass, so that after a single-pass profile, when the candidates serve every layer, a
 // small grid leaves after one load.
+// A threshold among zeros or equal values makes nearly every entry ambiguous, with one last digit: sixteen atomics per
+// chunk on one word then set the time, 12 ns each, not the read of g and h.  A wave counts such a run in a register and
+// a workgroup adds it once: 425 -> 22 us for a layer of 2.4 M entries that are zero but for a 67th, 6.85 ms -> 65 us for
+// 38.6 M.
+// The layer's records are in scalar registers, x alone is kept of g and h, and a mask holds a lane's sixteen verdicts: 96
+// registers for five waves a SIMD, where records in vector registers and Quads took 118 for four, which the candidates'
+// half of the launch had to live with too (38.6 M entries without ties 78 -> 58 us; 1.3 billion entries served from
+// candidates 57 -> 50).  Six and eight waves cost scratch memory here: 111 and 181 us.
 // (Workgroups `block` of `nblocks` of the launch that also histograms the spilled candidates: k_candidates.)
 __device__ __forceinline__ void compact_tiles(const CompressBuffers& cb, uint32_t ntiles, int32_t err_internal,
                                               uint32_t block, uint32_t nblocks) {
     if (*cb.ncompact == 0u) return;
-    const uint32_t wave = threadIdx.x >> 6, lane = lane_id();
+    const uint32_t wave = uniform(threadIdx.x >> 6), lane = lane_id();
     const uint32_t chunks_per_tile = cb.tile_elems / CHUNK;
+    __shared__ uint32_t* tie_at[4];
+    __shared__ uint32_t tie_n[4];
+    uint32_t* held_at = nullptr;                // (the same in all lanes)
+    uint32_t held_n = 0u;
     for (uint32_t tile = block; tile < ntiles; tile += nblocks) {
-    const uint32_t li = cb.chunk_layer[tile];
-    const LayerDesc L = cb.layers[li];
-    const SelRec S = cb.sel[L.big];
+    // (the same in every lane, and said so: in vector registers they left the launch four waves a SIMD)
+    const uint32_t li = uniform(cb.chunk_layer[tile]);
+    const LayerDesc L = uniform(cb.layers[li]);
+    const SelRec S = uniform(cb.sel[L.big]);
     const uint32_t tile_in_layer = tile - L.tile0;
     uint32_t* hist3 = cb.hist3 + (size_t)L.big * D3_BINS;
     // layers served from the spilled candidates (or with K = 0) need no pass over g, h
@@ -211,32 +237,29 @@ __device__ __forceinline__ void compact_tiles(const CompressBuffers& cb, uint32_
             }
             continue;
         }
-        Quad q[NQ];
+        float x[NQ][4];
+        // bit 4 u + c: the entry is a candidate; it shares the threshold's prefix
+        uint32_t sel = 0, ambig = 0;
+        {
+            QuadGH q[NQ];
+            uint32_t valid;
+            load_chunk<(int)NQ>(L, vbase, q, valid);
 #pragma unroll
-        for (int u = 0; u < (int)NQ; ++u) load_quad(L, vbase + u * 256u + lane * 4u, q[u]);
-
-        // flags: bit c of sel[u] = candidate, of amb[u] = ambiguous
-        uint32_t selm[NQ], ambm[NQ];
-        uint32_t mine_amb = 0;
+            for (int u = 0; u < (int)NQ; ++u)
 #pragma unroll
-        for (int u = 0; u < (int)NQ; ++u) {
-            selm[u] = 0; ambm[u] = 0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t key = q[u].key[c];
-                if (key == KEY_INVALID) continue;
-                const uint32_t p = key >> D2_SHIFT;
-                const bool amb = p == S.prefix;
-                if (p >= S.prefix) selm[u] |= 1u << c;
-                if (amb) { ambm[u] |= 1u << c; ++mine_amb; }
-            }
+                for (int c = 0; c < 4; ++c) {
+                    x[u][c] = q[u].g[c] - q[u].h[c];
+                    const uint32_t p = key_of(x[u][c]) >> D2_SHIFT, bit = (valid >> (4 * u + c)) & 1u;
+                    sel |= (p >= S.prefix ? bit : 0u) << (4 * u + c);
+                    ambig |= (p == S.prefix ? bit : 0u) << (4 * u + c);
+                }
         }
         // wave totals and the exclusive prefix of the lanes' counts, per quad row
         uint32_t total = 0, total_amb = 0;
         uint32_t rowbase[NQ];                   // candidates in earlier rows + earlier lanes of this row
 #pragma unroll
         for (int u = 0; u < (int)NQ; ++u) {
-            const uint32_t cnt = __popc(selm[u]);
+            const uint32_t cnt = __popc((sel >> (4 * u)) & 15u);
             // exclusive prefix over lanes of a small integer: three ballots on its bits
             const uint64_t b0 = ballot(cnt & 1u), b1 = ballot(cnt & 2u), b2 = ballot(cnt & 4u);
             const uint32_t ex = mbcnt(b0) + 2u * mbcnt(b1) + 4u * mbcnt(b2);
@@ -244,7 +267,7 @@ __device__ __forceinline__ void compact_tiles(const CompressBuffers& cb, uint32_
             total += __popcll(b0) + 2u * __popcll(b1) + 4u * __popcll(b2);
         }
         {
-            uint32_t a = mine_amb;
+            uint32_t a = __popc(ambig);
 #pragma unroll
             for (int d = 32; d > 0; d >>= 1) a += __shfl_xor(a, d, 64);
             total_amb = a;
@@ -265,10 +288,10 @@ __device__ __forceinline__ void compact_tiles(const CompressBuffers& cb, uint32_
             uint32_t pos = rowbase[u];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                if (selm[u] & (1u << c)) {
+                if ((sel >> (4 * u + c)) & 1u) {
                     if ((uint64_t)start + pos < S.cap) {
                         const uint64_t o = base + pos;
-                        cb.tmp_x[o] = q[u].g[c] - q[u].h[c];
+                        cb.tmp_x[o] = x[u][c];
                         cb.tmp_i[o] = (uint16_t)(u * 256u + lane * 4u + c);
                     }
                     ++pos;
@@ -281,15 +304,21 @@ __device__ __forceinline__ void compact_tiles(const CompressBuffers& cb, uint32_
             for (int u = 0; u < (int)NQ; ++u) {
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const bool a = (ambm[u] >> c) & 1u;
+                    const bool a = (ambig >> (4 * u + c)) & 1u;
                     const uint64_t am = ballot(a);
                     if (am == 0) continue;
-                    const uint32_t low = q[u].key[c] & (D3_BINS - 1);
-                    // one atomic per wave when every ambiguous lane holds the same key (zeros, constants)
-                    const uint32_t first = __shfl(low, __ffsll((long long)am) - 1, 64);
+                    const uint32_t low = key_of(x[u][c]) & (D3_BINS - 1);
+                    // every ambiguous lane holds the same key (zeros, constants): counted in the wave for as long as
+                    // the key stays the same
+                    const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)low, __ffsll((long long)am) - 1);
                     const bool uniform = ballot(a && low != first) == 0;
                     if (uniform) {
-                        if (lane == (uint32_t)(__ffsll((long long)am) - 1)) atomicAdd(&hist3[first], (uint32_t)__popcll(am));
+                        if (held_at != hist3 + first) {
+                            if (held_n && lane == 0) atomicAdd(held_at, held_n);
+                            held_at = hist3 + first;
+                            held_n = 0u;
+                        }
+                        held_n += (uint32_t)__popcll(am);
                     } else if (a) {
                         atomicAdd(&hist3[low], 1u);
                     }
@@ -297,6 +326,20 @@ __device__ __forceinline__ void compact_tiles(const CompressBuffers& cb, uint32_
             }
         }
     }
+    }
+    // what the waves still hold, one atomic for those that hold the same key
+    if (lane == 0) { tie_at[wave] = held_at; tie_n[wave] = held_n; }
+    // (LDS only: the records' stores need not be waited for)
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (threadIdx.x < 4u && tie_n[threadIdx.x]) {
+        uint32_t n = 0u;
+        bool lowest = true;
+        for (uint32_t w = 0; w < 4u; ++w) {
+            const bool same = tie_n[w] != 0u && tie_at[w] == tie_at[threadIdx.x];
+            n += same ? tie_n[w] : 0u;
+            lowest = lowest && !(same && w < threadIdx.x);
+        }
+        if (lowest) atomicAdd(tie_at[threadIdx.x], n);
     }
 }
 
@@ -374,7 +417,7 @@ __device__ __forceinline__ void hist3_candidates(const CompressBuffers& cb, uint
 // digit of the spilled candidates (layers in SEL_CAND mode), the others run the streaming compaction
 // for the layers that need it (none after a single-pass profile whose spilled range serves every
 // layer: they leave after one load).  The two touch different layers.
-__global__ __launch_bounds__(256) void k_candidates(CompressBuffers cb, uint32_t nchunks_total, const uint32_t* chunk_big,
+__global__ __launch_bounds__(256, 5) void k_candidates(CompressBuffers cb, uint32_t nchunks_total, const uint32_t* chunk_big,
                                                     uint32_t hist_blocks, uint32_t ntiles, int32_t err_internal) {
     if (blockIdx.x < hist_blocks) hist3_candidates(cb, nchunks_total, chunk_big, blockIdx.x);
     else compact_tiles(cb, ntiles, err_internal, blockIdx.x - hist_blocks, gridDim.x - hist_blocks);

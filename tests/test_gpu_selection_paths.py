@@ -157,3 +157,33 @@ def test_recount_in_groups_of_tiles(L):
     gL = [g[a:b] for a, b in zip(starts[:-1], starts[1:])]
     E_ref, _ = ko.profile(gL, [np.zeros_like(x) for x in gL], ratios)
     gh.assert_table_close(E, E_ref, plan.grid_sizes(), sizes)
+
+
+@pytest.mark.parametrize("share", [0.02, 0.3, 0.9])
+@pytest.mark.parametrize("sizes", [[8193, 12289, 40003, 9216], [17_000_001, 8193, 300_001]])
+def test_thresholds_among_equal_magnitudes(sizes, share):
+    """More is kept than lies above a magnitude that many entries share: zeros in the first layer; in the others two
+    magnitudes of one prefix bin, in runs of one chunk, of one quad and of one entry (the larger set has more tiles than
+    the pass has workgroups, and a layer's neighbours have a run of the same digit)."""
+    import torch
+    import paper_2312_08053_amd as kimad
+    rng = np.random.default_rng(11)
+    g = []
+    for i, n in enumerate(sizes):
+        near = np.array([1.0, np.float32(1.0) + np.float32(2.0 ** -22)], dtype=np.float32)
+        x = np.zeros(n, np.float32) if i == 0 else near[(np.arange(n) // [1024, 4, 1][i % 3]) % 2]
+        some = rng.choice(n, n // 200, replace=False)
+        x[some] = rng.standard_normal(some.size) * 10
+        g.append(x)
+    g = np.concatenate(g)
+    h = np.zeros_like(g)
+    K = [int(share * n) for n in sizes]
+    off = np.concatenate([[0], np.cumsum(K)])
+    gd, hd = torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda()
+    plan = kimad.Plan(gd, hd, sizes, [1.0], capacity_pairs=int(off[-1]), max_budget_bytes=8)
+    idx, val, st = plan.compress_ef(torch.tensor(K).cuda(), torch.from_numpy(off).cuda())
+    torch.cuda.synchronize()
+    assert int(st.item()) == 0
+    work = Workload(name="ties", sizes=np.asarray(sizes, dtype=np.uint64), g=g, h=h, ratios=np.array([1.0]),
+                    budget_bytes=8, cost_units_D=0)
+    gh.check_compress(work, plan, hd, K, off, idx, val)
