@@ -20,9 +20,9 @@
  *   - Every pointer is marked HOST or DEVICE.  The library never allocates or frees device
  *     memory: gradients, estimator, outputs and the workspace belong to the caller.
  *   - All GPU work is ordered with the given stream (a hipStream_t passed as void*; NULL is the
- *     default stream): it is enqueued there, except that kernels for layers of at most 8192
- *     entries run on a side stream of the plan between a fork and a join event on the given
- *     stream.  No call waits for the device except kimad_plan_create (synchronous uploads) and
+ *     default stream): it is enqueued there, except that kernels for more than 512 layers of at
+ *     most 8192 entries each (or for such layers alone) may run on a side stream of the plan between
+ *     a fork and a join event on the given stream.  No call waits for the device except kimad_plan_create (synchronous uploads) and
  *     the diagnostics getters.  kimad_profile, kimad_allocate, kimad_compress_ef, kimad_step and
  *     kimad_server_apply may be recorded into a HIP graph by stream capture (per-kernel timing off): tables
  *     are cleared by kernels, and the recording holds the pointers and the budget of the recorded call.

@@ -751,7 +751,7 @@ __device__ __forceinline__ void finalize_candidates(const CompressBuffers& cb, u
             keep[t] = false; pos[t] = 0u;
             if (k0 + (uint32_t)t * SUB < cmax) keep[t] = round(pin[t], px[t], pos[t]);
         }
-        // the estimator is read here: candidates carry (index, x) only
+        // the estimator is read here: candidates carry x and their place only
 #pragma unroll
         for (int t = 0; t < AHEAD; ++t) ph[t] = keep[t] ? gload(h + pidx[t]) : 0.0f;
 #pragma unroll

@@ -390,9 +390,9 @@ struct kimad_plan {
     std::vector<hipEvent_t> ev;
     std::vector<const char*> ev_name;
     uint32_t ev_n = 0;
-    // The small layers (one workgroup each) do not depend on the tiled layers: their kernels run on a
-    // side stream, forked from and joined back into the caller's stream with events, so that they
-    // overlap the short kernels of the tiled path instead of standing in line with them.
+    // The small layers (one workgroup each) do not depend on the tiled layers: where they are too many to share a
+    // launch (SMALL_BESIDE), their kernels run on a side stream, forked from and joined back into the caller's stream
+    // with events, so that they overlap the short kernels of the tiled path instead of standing in line with them.
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     // The single-pass profile predicts from the exact histogram its previous run on this plan left behind, once
