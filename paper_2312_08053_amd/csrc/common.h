@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "segment.h"
+
 namespace kimad {
 
 // ---- radix decomposition of the 31-bit magnitude key -------------------------------------
@@ -20,7 +22,6 @@ constexpr uint32_t KIMAD_MAX_J_CONST = 64;   // must equal KIMAD_MAX_J of the pu
 constexpr uint32_t KEY_INVALID = 0xFFFFFFFFu; // marks lanes outside the layer
 
 constexpr uint32_t SMALL_MAX = 8192;          // layers up to this size are looked after by one workgroup each
-constexpr uint32_t CHUNK = 1024;              // elements one wave compacts at a time (4 quads per lane)
 constexpr uint32_t NQ = CHUNK / 256;          // quads per lane and chunk
 constexpr uint32_t CBLOCK = 1024;             // chunks per chunk block (one workgroup scans one block)
 constexpr uint32_t PRE_SLOTS = 108;           // digit-2 slots the single-pass profile can hold in LDS
@@ -30,7 +31,6 @@ constexpr uint32_t SLOT_STRIDE = PRE_SLOTS + 64;  // slots per layer in the glob
 constexpr uint32_t PK_SHIFT = 24;
 constexpr uint64_t PK_ONE = 1ull << 44;
 constexpr uint64_t PK_MASK = PK_ONE - 1;
-constexpr uint32_t PK_MAX_CHUNKS = 1023;      // 1023 * 1024 entries < 2^20: the count field cannot overflow
 constexpr uint32_t SQ_SHIFT = 16;             // squares of 24-bit significands are kept >> 16
 constexpr uint64_t CNT_ONE = 1ull << 48;      // packed LDS entry: [count:16 | sum of squares:48]
 constexpr uint64_t SQ_MASK = CNT_ONE - 1;

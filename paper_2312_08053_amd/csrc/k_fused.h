@@ -613,15 +613,7 @@ __device__ __forceinline__ void main_chunk(const ProfileBuffers& pb, const MainC
     }
 }
 
-// How far a workgroup may go with one histogram.  A packed entry counts to 2^20 - 1, which any PK_MAX_CHUNKS chunks fit.
-// Real layers spread over thousands of entries: before a stretch ends, one wave reads the counts and allows as many more
-// chunks as the fullest entry has room for, whatever they hold, while the others go on.  Only where that is next to
-// nothing does the stretch end there, with a part written out and the histogram cleared.
-// (Parts at every 1023 chunks were 212 MB for 10 GB of g and h, and every one of them emptied the compute unit.)
-enum : uint32_t { LIMIT_FREE = 0, LIMIT_READING = 1, LIMIT_FINAL = 2 };
-constexpr uint32_t LIMIT_NEAR = 64;             // chunks before the limit at which a wave sees to it
-constexpr uint32_t LIMIT_LEAST = 128;           // chunks that are worth going on for
-
+// How far a workgroup may go with one histogram: segment.h.
 struct Segment {
     uint32_t end;          // end of the workgroup's share of the layer
     uint32_t used;         // entries of the histogram
@@ -644,12 +636,10 @@ __device__ __forceinline__ void main_extend(const MainCtx& cx, const Segment& sg
     for (uint32_t b = lane; b < sg.used; b += 64) most = max(most, lds_load(reinterpret_cast<const uint32_t*>(cx.pk) + 2 * b + 1) >> 12);
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) most = max(most, (uint32_t)__shfl_xor(most, d, 64));
-    const uint32_t room = (0xFFFFFu - most) / CHUNK, open = 2u * FUSED_WAVES;
-    const uint32_t end = min(sg.end, taken + (room > open ? room - open : 0u));
+    const StretchLimit l = stretch_limit_after(sg.end, lds_load(sg.allowed), taken, most, 2u * FUSED_WAVES);
     if (lane == 0) {
-        const bool on = end == sg.end || end >= *sg.allowed + LIMIT_LEAST;
-        if (on) __hip_atomic_store(sg.allowed, end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_store(sg.state, (uint32_t)(on ? LIMIT_FREE : LIMIT_FINAL), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (l.on) __hip_atomic_store(sg.allowed, l.end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(sg.state, (uint32_t)(l.on ? LIMIT_FREE : LIMIT_FINAL), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     wave_sync_lds();
 }

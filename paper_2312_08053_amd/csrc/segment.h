@@ -1,0 +1,33 @@
+// How far a workgroup of the streaming pass may go with one histogram: arithmetic only, the same on host and device.
+//
+// A packed histogram entry counts to 2^20 - 1, which any PK_MAX_CHUNKS chunks fit.  Real layers spread over thousands of
+// entries: before a stretch ends, one wave reads the counts and allows as many more chunks as the fullest entry has room
+// for, whatever they hold, while the others go on.  Only where that is next to nothing does the stretch end there, with a
+// part written out and the histogram cleared.
+// (Parts at every 1023 chunks were 212 MB for 10 GB of g and h, and every one of them emptied the compute unit.)
+#pragma once
+#include <cstdint>
+
+namespace kimad {
+
+constexpr uint32_t CHUNK = 1024;              // elements one wave compacts at a time (4 quads per lane)
+constexpr uint32_t PK_MAX_COUNT = 0xFFFFF;    // largest count of a packed histogram entry
+constexpr uint32_t PK_MAX_CHUNKS = PK_MAX_COUNT / CHUNK;     // (1023)
+
+enum : uint32_t { LIMIT_FREE = 0, LIMIT_READING = 1, LIMIT_FINAL = 2 };
+constexpr uint32_t LIMIT_NEAR = 64;             // chunks before the limit at which a wave sees to it
+constexpr uint32_t LIMIT_LEAST = 128;           // chunks that are worth going on for
+
+// Whether a stretch that may count the chunks below `allowed` goes on, and up to where.  `most`: the fullest entry's count,
+// read after `taken`, the first chunk that nobody had taken; of the chunks before it up to `open` may be missing from the
+// count.  Those count against the room like the ones to come: without room for them the limit stays, also where the
+// segment has no further chunks (`taken` passes its end while up to `open` of them are still to be counted).
+struct StretchLimit { uint32_t end; bool on; };
+constexpr StretchLimit stretch_limit_after(uint32_t seg_end, uint32_t allowed, uint32_t taken, uint32_t most, uint32_t open) {
+    const uint32_t room = (PK_MAX_COUNT - most) / CHUNK;
+    if (room <= open) return {allowed, false};
+    const uint32_t reach = taken + (room - open), end = reach < seg_end ? reach : seg_end;
+    return {end, end == seg_end || end >= allowed + LIMIT_LEAST};
+}
+
+}  // namespace kimad

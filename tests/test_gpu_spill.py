@@ -86,3 +86,28 @@ def test_counts_of_one_value_beyond_a_histogram_entry(equal, max_workgroups):
         E_ref, Kt = ko.profile(gL, hL, ratios)
         gh.assert_table_close(plan.err_table.cpu().numpy(), E_ref, Kt, sizes)
         gh.check_compress(work, plan, hd, plan.K.cpu().numpy(), plan.offsets.cpu().numpy(), plan.idx, plan.val)
+
+
+@pytest.mark.parametrize("chunks", [1024, 1030, 1039])
+def test_one_value_in_a_share_that_ends_soon_after_the_first_limit(chunks):
+    """Every entry of the layer in one histogram entry, and the layer ends where the other waves are through before the counts
+    are read: the chunks they have taken need room as well."""
+    import torch
+    import paper_2312_08053_amd as kimad
+    sizes = [chunks * 1024 - 3, 8200]
+    d = sum(sizes)
+    ratios = np.logspace(-3, 0, 20)
+    gd, hd = torch.empty(d, dtype=torch.float32, device="cuda"), torch.zeros(d, dtype=torch.float32, device="cuda")
+    budget = int(0.03 * 4 * d)
+    plan = kimad.Plan(gd, hd, sizes, ratios.tolist(), D=500, max_budget_bytes=budget, max_workgroups=1)
+    for step in range(2):
+        g = np.full(d, 0.0123 * (step + 1), dtype=np.float32)
+        g[1::2] *= -1.0
+        gd.copy_(torch.from_numpy(g))
+        hd.zero_()
+        assert plan.step(budget).cpu().tolist() == [0, 0]
+        work = Workload(name="one", sizes=np.asarray(sizes, dtype=np.uint64), g=g, h=np.zeros_like(g), ratios=ratios, budget_bytes=budget, cost_units_D=500)
+        gL, hL = gh.oracle_layers(work)
+        E_ref, Kt = ko.profile(gL, hL, ratios)
+        gh.assert_table_close(plan.err_table.cpu().numpy(), E_ref, Kt, sizes)
+        gh.check_compress(work, plan, hd, plan.K.cpu().numpy(), plan.offsets.cpu().numpy(), plan.idx, plan.val)
