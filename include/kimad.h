@@ -51,7 +51,8 @@ typedef enum kimad_status {
     KIMAD_ERR_INFEASIBLE = -6,          /* device status: budget below the cheapest allocation */
     KIMAD_ERR_NONFINITE = -7,           /* device status: error table holds Inf or NaN */
     KIMAD_ERR_OFFGRID = -8,             /* device status: KIMAD_REUSE_PROFILE given but K is not a grid size */
-    KIMAD_ERR_INTERNAL = -9,            /* device status: an internal capacity bound was violated (a bug) */
+    KIMAD_ERR_INTERNAL = -9,            /* device status: an internal capacity bound was violated (a bug), or a wait
+                                           inside the allocation was given up */
     KIMAD_ERR_BAD_OFFSETS = -10,        /* device status: offsets/K do not fit capacity_pairs */
     KIMAD_ERR_STATIC_LIMIT = -11,       /* kimad_allocate_static: more layers or longer rows than its fixed tables hold */
     KIMAD_ERR_STALE_PROFILE = -12,      /* device status: KIMAD_REUSE_PROFILE, but no kimad_profile has run on this plan
@@ -174,7 +175,8 @@ int kimad_profile(kimad_plan_t* plan, double* err_table, uint64_t budget_hint_by
  *   j_out       DEVICE int32[L]      chosen grid index per layer
  *   K_out       DEVICE uint64[L]     chosen size per layer
  *   offsets_out DEVICE uint64[L+1]   exclusive scan of K_out
- *   status_out  DEVICE int32[1]      KIMAD_OK, KIMAD_ERR_INFEASIBLE or KIMAD_ERR_NONFINITE
+ *   status_out  DEVICE int32[1]      KIMAD_OK, KIMAD_ERR_INFEASIBLE, KIMAD_ERR_NONFINITE, or KIMAD_ERR_INTERNAL (a
+ *                                    workgroup waited for seconds for another one's cells and gave up)
  * On a non-zero status the other outputs are zero-filled. */
 int kimad_allocate(kimad_plan_t* plan, const double* err_table, uint64_t budget_bytes,
                    int32_t* j_out, uint64_t* K_out, uint64_t* offsets_out,
@@ -188,7 +190,8 @@ int kimad_allocate(kimad_plan_t* plan, const double* err_table, uint64_t budget_
  * the candidate sizes K_ij only.  Limits: at most KIMAD_STATIC_MAX_L layers and rows of at most
  * KIMAD_STATIC_MAX_CELLS cost cells (capacity + 1; a cost_units_D of up to 1023 always fits): beyond them
  * the call returns KIMAD_ERR_STATIC_LIMIT and enqueues nothing.  Every call on a device shares that device's
- * array, whatever the plan: calls that overlap on one device race, also with each other across streams. */
+ * array, whatever the plan: calls that overlap on one device race, also with each other across streams (what they
+ * return is undefined, KIMAD_ERR_INTERNAL in status_out included). */
 #define KIMAD_STATIC_MAX_L 256u
 #define KIMAD_STATIC_MAX_CELLS 1024u
 int kimad_allocate_static(kimad_plan_t* plan, const double* err_table, uint64_t budget_bytes,
@@ -319,6 +322,14 @@ int kimad_plan_get_timings(kimad_plan_t* plan, char* names, uint32_t names_bytes
  *   out_u32[1088 + 64 t + lane]            = in_u32[lane xor 1, 2, 4, 8] (t = 0..3) */
 int kimad_selftest_wave_primitives(const uint32_t* in_u32, const double* in_f64, uint32_t* out_u32, double* out_f64,
                                    void* stream);
+
+/* Self-test of the allocation's bounded waits: kimad_allocate with the first workgroup of the recurrence withheld (its
+ * number is never given out, one past the last is instead) and waits given up after `polls` reads.  Rows that are computed
+ * whole by workgroups that wait for one another (see KIMAD_CFG_FULL_DP) then end with KIMAD_ERR_INTERNAL in *status_out
+ * and zero-filled outputs; *given_up_out (DEVICE) = waits given up and workgroups without cells.  Not for HIP graphs. */
+int kimad_selftest_allocate_withheld(kimad_plan_t* plan, const double* err_table, uint64_t budget_bytes, int32_t* j_out,
+                                     uint64_t* K_out, uint64_t* offsets_out, int32_t* status_out, uint32_t polls,
+                                     uint32_t* given_up_out, void* stream);
 
 /* Compression budget of one round (Section 3.1, Eq. budget): the bytes that fit into the up-link share
  * of the time budget t at the monitored bandwidth.  The paper's time split t = c/B + T_comp + alpha c/B

@@ -24,7 +24,8 @@ EXPORTED_SYMBOLS = [
     "kimad_profile", "kimad_allocate", "kimad_allocate_static", "kimad_compress_ef", "kimad_step",
     "kimad_error_at", "kimad_uniform_sizes", "kimad_payload_layer_counts",
     "kimad_profile_diagnostics", "kimad_allocate_diagnostics", "kimad_plan_layer_states", "kimad_plan_set_timing", "kimad_plan_get_timings",
-    "kimad_server_apply", "kimad_selftest_wave_primitives", "kimad_budget_bytes", "kimad_strerror", "kimad_version",
+    "kimad_server_apply", "kimad_selftest_wave_primitives", "kimad_selftest_allocate_withheld",
+    "kimad_budget_bytes", "kimad_strerror", "kimad_version",
 ]
 
 
@@ -83,6 +84,7 @@ def lib() -> C.CDLL:
     L.kimad_server_apply.argtypes = [C.POINTER(_Payload), C.POINTER(C.c_void_p), C.POINTER(C.c_double), u32, vp, u32, u64,
                                      vp, C.c_double, vp, vp]
     L.kimad_selftest_wave_primitives.argtypes = [vp, vp, vp, vp, vp]
+    L.kimad_selftest_allocate_withheld.argtypes = [vp, vp, u64, vp, vp, vp, i32p, u32, vp, vp]
     L.kimad_strerror.argtypes = [C.c_int]
     L.kimad_strerror.restype = C.c_char_p
     L.kimad_version.restype = C.c_char_p
@@ -241,6 +243,14 @@ def kimad_selftest_wave_primitives(in_u32, in_f64, out_u32, out_f64, stream=None
     _check(lib().kimad_selftest_wave_primitives(C.c_void_p(_ptr(in_u32)), C.c_void_p(_ptr(in_f64)), C.c_void_p(_ptr(out_u32)),
                                                 C.c_void_p(_ptr(out_f64)), C.c_void_p(_stream(stream))),
            "kimad_selftest_wave_primitives")
+
+
+def kimad_selftest_allocate_withheld(plan: int, err_table, budget_bytes: int, j_out, K_out, offsets_out, status_out,
+                                     polls: int, given_up_out, stream=None) -> None:
+    _check(lib().kimad_selftest_allocate_withheld(C.c_void_p(plan), C.c_void_p(_ptr(err_table)), int(budget_bytes),
+                                                  C.c_void_p(_ptr(j_out)), C.c_void_p(_ptr(K_out)), C.c_void_p(_ptr(offsets_out)),
+                                                  C.c_void_p(_ptr(status_out)), int(polls), C.c_void_p(_ptr(given_up_out)),
+                                                  C.c_void_p(_stream(stream))), "kimad_selftest_allocate_withheld")
 
 
 class Plan:

@@ -26,7 +26,9 @@ struct AllocBuffers {
     uint64_t* K_out;
     uint64_t* offsets_out;
     int32_t* status;
-    uint32_t* flags;         // [0] non-finite seen (rows by launch only), [1] workgroups started, [2] a wait was given up
+    uint32_t* flags;         // [0] non-finite seen (rows by launch only), [1] workgroups started, [2] waits given up
+    uint32_t polls;          // reads after which a wait for a row's cells is given up
+    uint32_t first_ticket;   // what flags[1] starts from: 0 (a test that withholds the first workgroups: their number)
 };
 
 constexpr double DP_INF = __builtin_huge_val();
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uin
         };
         fill(i + 1ull);
         if (i == 0u) fill(0ull);
-        if (i == 0u && blockIdx.y == 0u && j < 4u) ab.flags[j] = 0u;
+        if (i == 0u && blockIdx.y == 0u && j < 4u) ab.flags[j] = j == 1u ? ab.first_ticket : 0u;
         if (blockIdx.y) return;
     }
     const bool valid = j < ab.J;

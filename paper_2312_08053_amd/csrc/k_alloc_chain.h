@@ -17,7 +17,8 @@
 // Progress.  A workgroup takes its number b from a counter when it starts, so all lower numbers belong to workgroups
 // that are already running, and it waits for lower numbers only: the lowest unfinished one never waits for long,
 // however few of the others fit on the chip.  A wait is given up after CHAIN_POLLS reads (seconds), which the walk
-// back reports as an internal error.
+// back reports as an internal error.  A number beyond the grid, as calls that share one set of tables and overlap hand out,
+// owns no cells: its workgroup leaves, and the call reports an internal error too.
 #pragma once
 #include "common.h"
 #include "k_alloc.h"
@@ -201,8 +202,8 @@ __device__ __forceinline__ void chain_load(const AllocBuffers& ab, const double*
     while (i < ab.L) {
         uint32_t polls = 0;
         while (any_empty()) {
-            if (++polls > CHAIN_POLLS) {
-                if (lane_id() == 0) atomicOr(&ab.flags[2], 1u);
+            if (++polls > ab.polls) {
+                if (lane_id() == 0) atomicAdd(&ab.flags[2], 1u);
                 break;
             }
             asm volatile("" ::: "memory");
@@ -227,7 +228,12 @@ __global__ __launch_bounds__(chain_threads(W, GW)) void k_dp_chain(AllocBuffers 
     const uint32_t tid = threadIdx.x;
     if (tid == 0) sh_b = atomicAdd(&ab.flags[1], 1u);
     __syncthreads();
-    const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane(sh_b) * CELLS;
+    const uint32_t number = (uint32_t)__builtin_amdgcn_readfirstlane(sh_b);
+    if (number >= gridDim.x) {
+        if (tid == 0) atomicAdd(&ab.flags[2], 1u);
+        return;
+    }
+    const uint32_t c0 = number * CELLS;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
     for (uint32_t x = tid; x < 2u * CELLS + c0; x += NT) {
         rows[0][x] = x == CELLS ? 0.0 : DP_INF;
@@ -277,7 +283,12 @@ __global__ __launch_bounds__(CHAIN_LONG_NT) void k_dp_chain_long(AllocBuffers ab
     const uint32_t lane = threadIdx.x;
     uint32_t ticket = 0;
     if (lane == 0) ticket = atomicAdd(&ab.flags[1], 1u);
-    const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane(ticket) * CHAIN_LONG_CELLS, c = c0 + lane, c_hi = c0 + 63u;
+    const uint32_t number = (uint32_t)__builtin_amdgcn_readfirstlane(ticket);
+    if (number >= gridDim.x) {
+        if (lane == 0) atomicAdd(&ab.flags[2], 1u);
+        return;
+    }
+    const uint32_t c0 = number * CHAIN_LONG_CELLS, c = c0 + lane, c_hi = c0 + 63u;
     double one = 1.0;
     asm volatile("" : "+v"(one));
     bool gave_up = false;
@@ -317,9 +328,9 @@ __global__ __launch_bounds__(CHAIN_LONG_NT) void k_dp_chain_long(AllocBuffers ab
         };
         uint32_t polls = 0;
         auto give_up = [&]() {
-            if (++polls <= CHAIN_POLLS) return false;
+            if (++polls <= ab.polls) return false;
             gave_up = true;
-            if (lane == 0) atomicOr(&ab.flags[2], 1u);
+            if (lane == 0) atomicAdd(&ab.flags[2], 1u);
             return true;
         };
         if constexpr (SETS > 1) {

@@ -606,8 +606,31 @@ bool band_takes(kimad_plan* p, uint64_t unit, uint64_t cap) {
     return p->band_fits;
 }
 
+// The allocation's tables in the plan's workspace.
+AllocScratch plan_scratch(kimad_plan* p) {
+    const Layout& lo = p->lo;
+    AllocScratch ws;
+    ws.row0 = at<double>(p, lo.row0); ws.row1 = at<double>(p, lo.row1);
+    ws.choice = at<uint8_t>(p, lo.choice); ws.cprev = at<uint16_t>(p, lo.cprev);
+    ws.flags = at<uint32_t>(p, lo.dp_flags);
+    ws.dl.wall = at<uint32_t>(p, lo.dl_wall); ws.dl.w = at<uint32_t>(p, lo.dl_w); ws.dl.jj = at<uint32_t>(p, lo.dl_jj);
+    ws.dl.e = at<double>(p, lo.dl_e); ws.dl.n = at<uint32_t>(p, lo.dl_n); ws.dl.bad = at<uint32_t>(p, lo.dl_bad);
+    ws.dense_E = at<double>(p, lo.dense_E); ws.dense_Kcost = at<uint32_t>(p, lo.dense_Kcost);
+    ws.dense_Kout = at<uint32_t>(p, lo.dense_Kout);
+    ws.band.lo = at<uint32_t>(p, lo.band_lo); ws.band.hi = at<uint32_t>(p, lo.band_hi);
+    ws.band.info = at<uint32_t>(p, lo.band_info);
+    ws.band.live = at<uint32_t>(p, lo.band_live);
+    ws.dl.he = at<double>(p, lo.hull_e); ws.dl.hw = at<uint32_t>(p, lo.hull_w); ws.dl.hn = at<uint32_t>(p, lo.hull_n);
+    ws.dl.habs = at<double>(p, lo.hull_abs);
+    ws.rows_g = at<double>(p, lo.rows_g);
+    ws.rstride = (uint32_t)lo.rstride;
+    ws.max_cells = lo.dp_cells;
+    return ws;
+}
+
 int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_table, uint64_t budget_bytes,
-                     int32_t* j_out, uint64_t* K_out, uint64_t* offsets_out, int32_t* status_out, hipStream_t s) {
+                     int32_t* j_out, uint64_t* K_out, uint64_t* offsets_out, int32_t* status_out, hipStream_t s,
+                     uint32_t polls = CHAIN_POLLS, uint32_t first_ticket = 0u) {
     const Layout& lo = p->lo;
     const uint64_t P = budget_bytes / p->cfg.pair_bytes;
     const uint64_t unit = cost_unit(p->cfg, P);
@@ -631,7 +654,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
     ab.row0 = ws.row0; ab.row1 = ws.row1;
     ab.choice = ws.choice; ab.cprev = ws.cprev; ab.stride = align_up(cap + 1);   // row pitch: <= align_up(max_cells)
     ab.j_out = j_out; ab.K_out = K_out; ab.offsets_out = offsets_out; ab.status = status_out;
-    ab.flags = ws.flags;
+    ab.flags = ws.flags; ab.polls = polls; ab.first_ticket = first_ticket;
     mark(p, s, "begin");
     if (dense) {
         KLAUNCH(p, s, "k_dense_view", k_dense_view, dim3((lo.L * lo.J + 255) / 256), dim3(256), err_table, ab.Ktab,
@@ -909,23 +932,7 @@ int kimad_profile(kimad_plan_t* p, double* err_table, uint64_t budget_hint_bytes
 int kimad_allocate(kimad_plan_t* p, const double* err_table, uint64_t budget_bytes, int32_t* j_out, uint64_t* K_out,
                    uint64_t* offsets_out, int32_t* status_out, void* stream) {
     if (!p || !err_table || !j_out || !K_out || !offsets_out || !status_out) return KIMAD_ERR_INVALID_ARG;
-    const Layout& lo = p->lo;
-    AllocScratch ws;
-    ws.row0 = at<double>(p, lo.row0); ws.row1 = at<double>(p, lo.row1);
-    ws.choice = at<uint8_t>(p, lo.choice); ws.cprev = at<uint16_t>(p, lo.cprev);
-    ws.flags = at<uint32_t>(p, lo.dp_flags);
-    ws.dl.wall = at<uint32_t>(p, lo.dl_wall); ws.dl.w = at<uint32_t>(p, lo.dl_w); ws.dl.jj = at<uint32_t>(p, lo.dl_jj);
-    ws.dl.e = at<double>(p, lo.dl_e); ws.dl.n = at<uint32_t>(p, lo.dl_n); ws.dl.bad = at<uint32_t>(p, lo.dl_bad);
-    ws.dense_E = at<double>(p, lo.dense_E); ws.dense_Kcost = at<uint32_t>(p, lo.dense_Kcost);
-    ws.dense_Kout = at<uint32_t>(p, lo.dense_Kout);
-    ws.band.lo = at<uint32_t>(p, lo.band_lo); ws.band.hi = at<uint32_t>(p, lo.band_hi);
-    ws.band.info = at<uint32_t>(p, lo.band_info);
-    ws.band.live = at<uint32_t>(p, lo.band_live);
-    ws.dl.he = at<double>(p, lo.hull_e); ws.dl.hw = at<uint32_t>(p, lo.hull_w); ws.dl.hn = at<uint32_t>(p, lo.hull_n);
-    ws.dl.habs = at<double>(p, lo.hull_abs);
-    ws.rows_g = at<double>(p, lo.rows_g);
-    ws.rstride = (uint32_t)lo.rstride;
-    ws.max_cells = lo.dp_cells;
+    const AllocScratch ws = plan_scratch(p);
     return enqueue_allocate(p, ws, err_table, budget_bytes, j_out, K_out, offsets_out, status_out,
                             static_cast<hipStream_t>(stream));
 }
@@ -1226,6 +1233,17 @@ int kimad_selftest_wave_primitives(const uint32_t* in_u32, const double* in_f64,
     return hipGetLastError() == hipSuccess ? KIMAD_OK : KIMAD_ERR_HIP;
 }
 
+int kimad_selftest_allocate_withheld(kimad_plan_t* p, const double* err_table, uint64_t budget_bytes, int32_t* j_out,
+                                     uint64_t* K_out, uint64_t* offsets_out, int32_t* status_out, uint32_t polls,
+                                     uint32_t* given_up_out, void* stream) {
+    if (!p || !err_table || !j_out || !K_out || !offsets_out || !status_out || !given_up_out || polls == 0) return KIMAD_ERR_INVALID_ARG;
+    const AllocScratch ws = plan_scratch(p);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const int rc = enqueue_allocate(p, ws, err_table, budget_bytes, j_out, K_out, offsets_out, status_out, s, std::min(polls, CHAIN_POLLS), 1u);
+    if (rc) return rc;
+    return hipMemcpyAsync(given_up_out, ws.flags + 2, 4, hipMemcpyDeviceToDevice, s) == hipSuccess ? KIMAD_OK : KIMAD_ERR_HIP;
+}
+
 uint64_t kimad_budget_bytes(double bandwidth_bits_per_s, double t_seconds, double t_comp_seconds, double alpha,
                             uint64_t cap_bytes) {
     const double B = bandwidth_bits_per_s, t = t_seconds, tc = t_comp_seconds;
@@ -1246,7 +1264,7 @@ const char* kimad_strerror(int status) {
         case KIMAD_ERR_INFEASIBLE: return "budget below the cheapest allocation";
         case KIMAD_ERR_NONFINITE: return "error table holds a non-finite entry";
         case KIMAD_ERR_OFFGRID: return "K is not one of the layer's grid sizes";
-        case KIMAD_ERR_INTERNAL: return "internal error: candidate region overflow";
+        case KIMAD_ERR_INTERNAL: return "internal error: candidate region overflow, or the allocation gave a wait up";
         case KIMAD_ERR_BAD_OFFSETS: return "K/offsets do not fit the payload capacity";
         case KIMAD_ERR_STALE_PROFILE: return "KIMAD_REUSE_PROFILE without a profile of the current g - h";
         case KIMAD_ERR_BAD_PAYLOAD: return "payload offsets or indices do not fit the layers";
