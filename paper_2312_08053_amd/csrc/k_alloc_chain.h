@@ -17,15 +17,17 @@
 // Progress.  A workgroup takes its number b from a counter when it starts, so all lower numbers belong to workgroups
 // that are already running, and it waits for lower numbers only: the lowest unfinished one never waits for long,
 // however few of the others fit on the chip.  A wait is given up after CHAIN_POLLS reads (seconds), which the walk
-// back reports as an internal error.  A number beyond the grid, as calls that share one set of tables and overlap hand out,
-// owns no cells: its workgroup leaves, and the call reports an internal error too.
+// back reports as an internal error.  A wave that has given up waits no more, in this row or a later one, and the loaders of
+// k_dp_chain look every CHAIN_LOOK reads whether one has: the launch ends after a few such waits, however many layers are
+// left.  A number beyond the grid, as calls that share one set of tables and overlap hand out, owns no cells: its workgroup
+// leaves, and the call reports an internal error too.
 #pragma once
 #include "common.h"
 #include "k_alloc.h"
 
 namespace kimad {
 
-constexpr uint32_t CHAIN_POLLS = 1u << 22;
+constexpr uint32_t CHAIN_POLLS = 1u << 22, CHAIN_LOOK = 1u << 12;
 
 __device__ __forceinline__ unsigned long long cell_load(const unsigned long long* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -35,6 +37,15 @@ __device__ __forceinline__ void cell_store(double* p, double v) {
                        __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ bool cell_empty(unsigned long long v) { return (uint32_t)(v >> 32) == 0xFFFFFFFFu; }
+
+// Whether a wait of `polls` reads goes on (the same in all lanes).
+__device__ __forceinline__ bool wait_on(const AllocBuffers& ab, uint32_t polls) {
+    if (polls > ab.polls) {
+        if (lane_id() == 0) atomicAdd(&ab.flags[2], 1u);
+        return false;
+    }
+    return __builtin_amdgcn_readfirstlane(__hip_atomic_load(&ab.flags[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0u;
+}
 
 // Least value over the four 16-lane rows of a wave, in every row (min is exact: the order does not matter).
 __device__ __forceinline__ double min_over_rows(double v) {
@@ -195,6 +206,7 @@ __device__ __forceinline__ void chain_load(const AllocBuffers& ab, const double*
         return ballot(top == 0xFFFFFFFFu) != 0ull;
     };
     ask(g + 1u);
+    uint32_t limit = min(ab.polls, CHAIN_LOOK);       // reads of a wait before the next look; 0: given up
     uint32_t i = 0;                                   // layers whose barrier is behind us
     for (; i < min(g, ab.L); ++i) lds_barrier();
     static_assert(N % 2 == 0, "a group's rows all go to the same half of LDS");
@@ -202,9 +214,12 @@ __device__ __forceinline__ void chain_load(const AllocBuffers& ab, const double*
     while (i < ab.L) {
         uint32_t polls = 0;
         while (any_empty()) {
-            if (++polls > ab.polls) {
-                if (lane_id() == 0) atomicAdd(&ab.flags[2], 1u);
-                break;
+            if (__builtin_expect(++polls > limit, 0)) {
+                if (limit == 0u || !wait_on(ab, polls)) {
+                    limit = 0u;
+                    break;
+                }
+                limit = polls + CHAIN_LOOK;
             }
             asm volatile("" ::: "memory");
             ask(i + 1u);
