@@ -623,26 +623,41 @@ struct Segment {
 };
 __device__ __forceinline__ uint32_t lds_load(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 
-__device__ __forceinline__ void main_extend(const MainCtx& cx, const Segment& sg) {
-    const uint32_t lane = lane_id();
-    uint32_t was = 0;
-    if (lane == 0) was = atomicCAS(sg.state, (uint32_t)LIMIT_FREE, (uint32_t)LIMIT_READING);
-    if (__builtin_amdgcn_readfirstlane(was) != LIMIT_FREE) return;
-    // What is not in the counts read below: chunks from `taken` on, and of those before it the one that a wave is at and the
-    // one it has taken ahead (a wave's LDS instructions run in order: when it takes a chunk, all but its last are counted).
-    const uint32_t taken = lds_load(sg.next_chunk);
-    wave_sync_lds();
-    uint32_t most = 0;
-    for (uint32_t b = lane; b < sg.used; b += 64) most = max(most, lds_load(reinterpret_cast<const uint32_t*>(cx.pk) + 2 * b + 1) >> 12);
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) most = max(most, (uint32_t)__shfl_xor(most, d, 64));
-    const StretchLimit l = stretch_limit_after(sg.end, lds_load(sg.allowed), taken, most, 2u * FUSED_WAVES);
-    if (lane == 0) {
-        if (l.on) __hip_atomic_store(sg.allowed, l.end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_store(sg.state, (uint32_t)(l.on ? LIMIT_FREE : LIMIT_FINAL), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+// A wave's view of a stretch's limit (stretch_limit): every value is the same in all its lanes.
+struct StretchWave {
+    const MainCtx& cx;
+    const Segment& sg;
+    static constexpr uint32_t OPEN = 2u * FUSED_WAVES;
+    __device__ __forceinline__ uint32_t state() const { return __builtin_amdgcn_readfirstlane(lds_load(sg.state)); }
+    __device__ __forceinline__ uint32_t allowed() const { return __builtin_amdgcn_readfirstlane(lds_load(sg.allowed)); }
+    // What is not in the counts that most() reads: chunks from taken() on, and of those before it the one that a wave is at and
+    // the one it has taken ahead (a wave's LDS instructions run in order: when it takes a chunk, all but its last are counted).
+    __device__ __forceinline__ uint32_t taken() const {
+        const uint32_t t = __builtin_amdgcn_readfirstlane(lds_load(sg.next_chunk));
+        wave_sync_lds();
+        return t;
     }
-    wave_sync_lds();
-}
+    __device__ __forceinline__ uint32_t most() const {
+        uint32_t m = 0;
+        for (uint32_t b = lane_id(); b < sg.used; b += 64) m = max(m, lds_load(reinterpret_cast<const uint32_t*>(cx.pk) + 2 * b + 1) >> 12);
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) m = max(m, (uint32_t)__shfl_xor(m, d, 64));
+        return __builtin_amdgcn_readfirstlane(m);
+    }
+    __device__ __forceinline__ bool claim() const {
+        uint32_t was = 0;
+        if (lane_id() == 0) was = atomicCAS(sg.state, (uint32_t)LIMIT_FREE, (uint32_t)LIMIT_READING);
+        return __builtin_amdgcn_readfirstlane(was) == LIMIT_FREE;
+    }
+    __device__ __forceinline__ void allow(uint32_t end) const {
+        if (lane_id() == 0) __hip_atomic_store(sg.allowed, end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ void release(uint32_t next) const {
+        if (lane_id() == 0) __hip_atomic_store(sg.state, next, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        wave_sync_lds();
+    }
+    __device__ __forceinline__ void pause() const { __builtin_amdgcn_s_sleep(1); }
+};
 
 // A wave's chunks of a segment: its first one, then what the segment's counter hands out.  Returns where the segment ends as
 // far as the wave knows: sg.end, or where the stretch does.
@@ -652,13 +667,8 @@ __device__ __forceinline__ uint32_t main_walk(const ProfileBuffers& pb, const Ma
     uint32_t limit = __builtin_amdgcn_readfirstlane(lds_load(sg.allowed));
     for (;;) {
         if (limit < sg.end && chunk + LIMIT_NEAR >= limit) {
-            for (;;) {
-                main_extend(cx, sg);
-                const uint32_t state = __builtin_amdgcn_readfirstlane(lds_load(sg.state));
-                limit = __builtin_amdgcn_readfirstlane(lds_load(sg.allowed));    // (read after the state: final with it)
-                if (chunk < limit || state == LIMIT_FINAL || limit == sg.end) break;
-                __builtin_amdgcn_s_sleep(1);                                     // (another wave is reading)
-            }
+            StretchWave w{cx, sg};
+            limit = stretch_limit(w, chunk, limit, sg.end, StretchWave::OPEN);
         }
         if (chunk >= limit) return limit;
         uint32_t taken = 0;

@@ -51,3 +51,20 @@ def test_an_extension_never_lets_an_entry_overflow(seg):
         if on:
             assert most + (OPEN + max(0, end - taken)) * CHUNK <= MAX_COUNT, (allowed, seg_end, taken, most)
             assert end == seg_end or end >= allowed + 128
+
+
+@pytest.mark.parametrize("chunks", [1024, 1030, 1039, 1200, 4954])
+@pytest.mark.parametrize("fullest", [1024, 512, 64, 8])
+def test_sixteen_waves_walk_a_segment(seg, chunks, fullest):
+    """Threads in the place of waves, with the limit's code as the kernel has it.  Every chunk is counted once, no entry overflows,
+    all waves end a stretch at the same chunk, and a stretch goes on for as long as its fullest entry has room."""
+    rest = 1024 - fullest
+    per = [fullest] + [rest // 16] * 16
+    out = (C.c_uint32 * 4)()
+    for spin in (0, 20, 200):
+        seg.walk(16, chunks, (C.c_uint32 * len(per))(*per), len(per), spin, out)
+        stretches, most, counted, apart = out[:]
+        assert counted == chunks and apart == 0 and most <= MAX_COUNT, (spin, out[:])
+        # a limit seen to 64 chunks ahead stays where the room, less the 32 chunks under way, does not reach 128 beyond it
+        least = min((MAX_COUNT - (64 + OPEN + 128 + 2) * CHUNK) // max(per), chunks)
+        assert stretches <= -(-chunks // max(least, 1023)), (spin, out[:], least)
