@@ -261,11 +261,10 @@ __device__ __forceinline__ void load_chunk(const LayerDesc& L, uint32_t vbase, Q
 // one per chunk: thousands of waves adding to the same address serialise.  Unused tails of blocks
 // are never referenced: chunk records delimit what is valid.
 constexpr uint32_t SPILL_BLOCK = 512;
-// A layer's region of the candidate buffer holds REGION_PER_CHUNK entries per chunk of the layer plus
+// A layer's region of the candidate buffer holds REGION_PER_CHUNK (segment.h) entries per chunk of the layer plus
 // REGION_SLACK: 21/128 of the layer.  The single-pass profile spills at most an eighth of a layer into it
 // (each workgroup into the slice that belongs to its chunks), the compaction pass whatever lies at or above a
 // threshold prefix if that fits; whatever does not fit is served from g and h directly.
-constexpr uint32_t REGION_PER_CHUNK = 168;        // (space is handed out in whole lines of values)
 constexpr uint32_t REGION_SLACK = 2048;
 // The regions of the tiled layers follow one another in the candidate buffer, so a layer's region starts where its
 // first chunk and its number among the tiled layers say: a kernel that walks chunks knows where a chunk's candidates

@@ -443,9 +443,8 @@ __device__ __forceinline__ void main_count(const MainCtx& cx, const float (&x)[N
 // read of the same bytes takes 1470), most of all stores of partial lines, which are written back and fetched again among
 // the streaming reads.  And a store in the loop makes every wait for the next chunk's loads a wait for its acknowledgement
 // as well, and a returning global atomic per reservation serialises thousands of waves on one address.  So:
-//   * the workgroup owns the slice of the layer's candidate region that corresponds to its chunks
-//     (REGION_PER_CHUNK entries of space per chunk, a third more than the largest share of a layer
-//     that k_predict lets spill), handed out in units of a 128-byte line; a slice that still runs
+//   * the workgroup owns the slice of the layer's candidate region that corresponds to its chunks,
+//     handed out in units of a 128-byte line (spill_slice in segment.h, also for short slices); a slice that runs
 //     out marks the layer's spill as incomplete (spill_over) and the layer is served by the passes
 //     that read g and h instead, like any other misprediction;
 //   * a candidate is six bytes: x, and its place in the chunk; a wave takes blocks from an LDS cursor, collects candidates
@@ -456,8 +455,6 @@ __device__ __forceinline__ void main_count(const MainCtx& cx, const float (&x)[N
 // six bytes and whole lines 1906 and 2593, nontemporal 1807 and 2193; pairs of index and x, nontemporal, 1840 and 2210, but
 // the kernels that look at x alone read twice as much then.  1 GB, 1.1 %: 186, 181 and 185.  Nothing written: 1660 and 172.)
 constexpr uint32_t PEND = 16;                   // chunk records a wave holds back
-constexpr uint32_t SPILL_UNIT = 32;             // candidates to a line of values
-constexpr uint32_t SPILL_RUN = 64;              // candidates a wave writes at a time
 
 struct WaveSpill {
     float* win_x;         // LDS window: the block's entries from `flushed` on, entry e at e % STAGE
@@ -465,9 +462,7 @@ struct WaveSpill {
     uint32_t* pend;       // LDS: PEND x (chunk, start, count)
     uint32_t* lds_cursor; // units handed out in this workgroup's slice
     uint32_t* over;       // the layer's spill_over flag
-    uint32_t slice_units; // units the slice holds
-    uint32_t slice_rel;   // first entry of the slice, relative to the layer's region (chunk records are region-relative)
-    uint32_t blk_size;    // entries of a block
+    SpillSlice slice;     // (chunk records are relative to the layer's region like the slice's first entry)
     uint32_t blk;         // region-relative start of the current block (valid if have_blk)
     uint32_t fill;        // entries in the block
     uint32_t flushed;     // of which already written: all below the last multiple of SPILL_RUN
@@ -510,13 +505,13 @@ __device__ __forceinline__ void spill_records(const ProfileBuffers& pb, WaveSpil
 // first.  *ok is false when the slice has no room left for them: nothing may be written then, and the
 // layer is marked.
 __device__ __forceinline__ uint32_t spill_take(WaveSpill& ws, uint32_t entries, bool* ok) {
-    const uint32_t nu = (entries + SPILL_UNIT - 1u) / SPILL_UNIT;
+    const uint32_t nu = (entries + (1u << ws.slice.unit_log) - 1u) >> ws.slice.unit_log;
     uint32_t b = 0;
     if (lane_id() == 0) b = atomicAdd(ws.lds_cursor, nu);
     b = __builtin_amdgcn_readfirstlane(b);
-    *ok = b + nu <= ws.slice_units;             // (the cursor grows by at most 32 units per chunk: no wrap)
+    *ok = b + nu <= ws.slice.units;             // (the cursor grows by at most 128 units per chunk: no wrap)
     if (!*ok && lane_id() == 0) *ws.over = 1u;
-    return ws.slice_rel + b * SPILL_UNIT;
+    return ws.slice.first + (b << ws.slice.unit_log);
 }
 
 // One chunk of the streaming pass for one wave: histogram updates, ranks of the entries to spill,
@@ -543,10 +538,10 @@ __device__ __forceinline__ void main_chunk(const ProfileBuffers& pb, const MainC
     if (total == 0) return;                      // records start out as "nothing spilled"
     if (total <= SPILL_RUN) {
         if (ws.npend == PEND) spill_records(pb, ws);
-        if (!ws.have_blk || ws.fill + total > ws.blk_size) {
+        if (!ws.have_blk || ws.fill + total > ws.slice.block) {
             if (ws.have_blk) spill_write<STREAM>(pb, ws, L.tmp0, ws.fill);
             bool ok;
-            ws.blk = spill_take(ws, ws.blk_size, &ok);
+            ws.blk = spill_take(ws, ws.slice.block, &ok);
             ws.fill = 0; ws.flushed = 0; ws.have_blk = ok;
             if (!ok) return;                     // the chunk's record stays "nothing spilled"; the layer is marked
         }
@@ -720,14 +715,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint3
         ws.win_x = stage_x + wave * STAGE; ws.win_i = stage_i + wave * STAGE;
         ws.pend = pend + wave * PEND * 3; ws.lds_cursor = &lds_cursor;
         ws.over = pb.spill_over + big;
-        {
-            // the slice in whole lines (the buffer's start is one)
-            const uint32_t first = (cur - L.chunk0) * REGION_PER_CHUNK, off = (SPILL_UNIT - (uint32_t)(L.tmp0 + first) % SPILL_UNIT) % SPILL_UNIT;
-            ws.slice_rel = first + off;
-            ws.slice_units = ((seg_end - cur) * REGION_PER_CHUNK - off) / SPILL_UNIT;
-            // every wave may leave a block of the segment nearly empty: at most a tenth of the slice
-            ws.blk_size = seg_end - cur >= 512u ? 512u : seg_end - cur >= 256u ? 256u : 128u;
-        }
+        ws.slice = spill_slice(L.tmp0, cur - L.chunk0, seg_end - cur);
         ws.blk = 0; ws.fill = 0; ws.flushed = 0; ws.npend = 0; ws.have_blk = false;
 
         // (Fetching the wave's next chunk while the current one is worked on was tried at 16, 12 and 8

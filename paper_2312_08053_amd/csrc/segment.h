@@ -1,6 +1,7 @@
-// How far a workgroup of the streaming pass may go with one histogram: arithmetic only, the same on host and device.
+// Arithmetic of a segment of the streaming pass (a workgroup's share of a layer), the same on host and device: how far it may
+// go with one histogram, and how the space for its candidates is handed out.
 //
-// A packed histogram entry counts to 2^20 - 1, which any PK_MAX_CHUNKS chunks fit.  Real layers spread over thousands of
+// Histogram.  A packed histogram entry counts to 2^20 - 1, which any PK_MAX_CHUNKS chunks fit.  Real layers spread over thousands of
 // entries: before a stretch ends, one wave reads the counts and allows as many more chunks as the fullest entry has room
 // for, whatever they hold, while the others go on.  Only where that is next to nothing does the stretch end there, with a
 // part written out and the histogram cleared.
@@ -58,6 +59,35 @@ constexpr uint32_t stretch_limit(W& w, uint32_t chunk, uint32_t limit, uint32_t 
         }
     }
     return limit;
+}
+
+// ---- candidates ----------------------------------------------------------------------------------
+// The segment owns REGION_PER_CHUNK entries of the layer's region per chunk, a third more than the eighth of a layer that
+// k_predict lets spill.  A wave takes a block of `block` entries for the chunks of up to SPILL_RUN candidates, and for a
+// denser chunk as many units as hold it.
+// Units are 128-byte lines of values, from the first whole one of the slice on; but of a slice of a few chunks lines would
+// take what the third is there for: a chunk of 129 candidates takes 160 entries and a slice of one chunk may have 128 in
+// whole lines, so an eighth of a layer spilled overflowed such slices in up to 23 % of cases, each of which sends the whole
+// layer to the passes that read g and h again.  There a unit is eight entries, from the slice's first one: any sixteen
+// chunks of up to 168 candidates fit.
+// (The blocks that sixteen waves leave nearly empty are 2048 entries below 256 chunks, and at most a tenth of the slice from
+// there on.)
+constexpr uint32_t REGION_PER_CHUNK = 168;
+constexpr uint32_t SPILL_LINE_LOG = 5, SPILL_SHORT_LOG = 3;     // (4-byte values)
+constexpr uint32_t SPILL_SHORT = 128;           // chunks below which a slice is handed out in short units
+constexpr uint32_t SPILL_RUN = 64;              // candidates a wave writes at a time
+
+struct SpillSlice {
+    uint32_t first;       // the slice's first entry, relative to the layer's region
+    uint32_t unit_log;    // log2 of the entries of a unit
+    uint32_t units;
+    uint32_t block;
+};
+// region: first entry of the layer's region (the buffer's start is a line's)
+constexpr SpillSlice spill_slice(uint64_t region, uint32_t first_chunk, uint32_t chunks) {
+    const uint32_t first = first_chunk * REGION_PER_CHUNK, log = chunks < SPILL_SHORT ? SPILL_SHORT_LOG : SPILL_LINE_LOG;
+    const uint32_t line = 1u << SPILL_LINE_LOG, off = chunks < SPILL_SHORT ? 0u : (line - (uint32_t)((region + first) % line)) % line;
+    return {first + off, log, (chunks * REGION_PER_CHUNK - off) >> log, chunks >= 512u ? 512u : chunks >= 256u ? 256u : 128u};
 }
 
 }  // namespace kimad

@@ -70,4 +70,29 @@ void walk(uint32_t waves, uint32_t seg_end, const uint32_t* per, uint32_t entrie
     }
 }
 
+// A slice's chunks, of counts[k] candidates each, taken in turn by the wave order[k] says, as main_chunk takes space for them.
+// out: [0] first entry, [1] one past the last entry handed out, [2] whether all of them fitted.
+void spill(uint64_t region, uint32_t first_chunk, uint32_t chunks, const uint32_t* counts, const uint32_t* order, uint32_t* out) {
+    const SpillSlice s = spill_slice(region, first_chunk, chunks);
+    uint32_t cursor = 0, fill[16], last = s.first;
+    bool have[16] = {}, fits = true;
+    auto take = [&](uint32_t entries) {
+        const uint32_t b = cursor, n = (entries + (1u << s.unit_log) - 1u) >> s.unit_log;
+        cursor += n;
+        const bool ok = b + n <= s.units;
+        if (ok) last = s.first + ((b + n) << s.unit_log);
+        return ok;
+    };
+    for (uint32_t k = 0; k < chunks; ++k) {
+        const uint32_t n = counts[k], w = order[k];
+        if (n > SPILL_RUN) {
+            fits = take(n) && fits;
+        } else if (n) {
+            if (!have[w] || fill[w] + n > s.block) { have[w] = take(s.block); fill[w] = 0; fits = have[w] && fits; }
+            fill[w] += n;
+        }
+    }
+    out[0] = s.first; out[1] = last; out[2] = fits;
+}
+
 }  // extern "C"

@@ -111,3 +111,39 @@ def test_one_value_in_a_share_that_ends_soon_after_the_first_limit(chunks):
         E_ref, Kt = ko.profile(gL, hL, ratios)
         gh.assert_table_close(plan.err_table.cpu().numpy(), E_ref, Kt, sizes)
         gh.check_compress(work, plan, hd, plan.K.cpu().numpy(), plan.offsets.cpu().numpy(), plan.idx, plan.val)
+
+
+@pytest.mark.parametrize("chunks", [41, 42, 43, 44])
+@pytest.mark.parametrize("last", [129, 145, 160])
+def test_the_slice_of_one_chunk_holds_its_candidates(chunks, last):
+    """A layer of which an eighth is spilled, less a few entries, and of which the second workgroup has one chunk: more candidates
+    there than an eighth of it, and fewer than the slice has room for, are no reason to read the layer again."""
+    import torch
+    import paper_2312_08053_amd as kimad
+    rng = np.random.default_rng(last)
+    sizes = [chunks * 1024 - 3, (chunks - 2) * 1024 - 3]              # the first workgroup has chunks - 1 of the first layer
+    ratios = np.unique(np.round(np.logspace(-3, 0, 40), 6))
+    d = sum(sizes)
+    gd, hd = torch.empty(d, dtype=torch.float32, device="cuda"), torch.zeros(d, dtype=torch.float32, device="cuda")
+    plan = None
+    for step in range(2):
+        parts, large = [], 0
+        for n in sizes:
+            x = (1e-3 * rng.standard_normal(n)).astype(np.float32)
+            for c in range(0, n, 1024):
+                m = last if n == sizes[0] and c + 1024 > n else (sizes[0] // 8 - last - 8) // (chunks - 1)
+                at = c + rng.choice(min(1024, n - c), size=m, replace=False)
+                x[at] = (rng.uniform(3.0, 9.0, size=m) * rng.choice([-1.0, 1.0], size=m)).astype(np.float32)
+                large += m
+            parts.append(x)
+        g = np.concatenate(parts)
+        gd.copy_(torch.from_numpy(g))
+        hd.zero_()
+        budget = 8 * int(1.05 * large)
+        if plan is None:
+            plan = kimad.Plan(gd, hd, sizes, ratios.tolist(), D=0, max_budget_bytes=2 * budget, capacity_pairs=d, max_workgroups=2)
+        assert plan.step(budget).cpu().tolist() == [0, 0]
+        states = plan.layer_states()
+        assert all(s["spill_valid"] for s in states) and states[0]["spill_cnt"] >= int((abs(parts[0]) > 1).sum()), states
+        work = Workload(name="slice", sizes=np.asarray(sizes, dtype=np.uint64), g=g, h=np.zeros_like(g), ratios=ratios, budget_bytes=budget, cost_units_D=0)
+        gh.check_compress(work, plan, hd, plan.K.cpu().numpy(), plan.offsets.cpu().numpy(), plan.idx, plan.val)

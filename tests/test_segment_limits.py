@@ -1,5 +1,6 @@
-"""How far a workgroup of the streaming pass goes with one histogram (csrc/segment.h, compiled here for the host): no entry may
-ever count past 2^20 - 1, whatever the chunks hold and whichever wave comes first."""
+"""Arithmetic of a workgroup's share of a layer in the streaming pass (csrc/segment.h, compiled here for the host).  How far it
+goes with one histogram: no entry may ever count past 2^20 - 1, whatever the chunks hold and whichever wave comes first.  How
+the space for its candidates is handed out: inside the share's slice, and enough for the eighth of a layer that may spill."""
 import ctypes as C
 import os
 import subprocess
@@ -68,3 +69,35 @@ def test_sixteen_waves_walk_a_segment(seg, chunks, fullest):
         # a limit seen to 64 chunks ahead stays where the room, less the 32 chunks under way, does not reach 128 beyond it
         least = min((MAX_COUNT - (64 + OPEN + 128 + 2) * CHUNK) // max(per), chunks)
         assert stretches <= -(-chunks // max(least, 1023)), (spin, out[:], least)
+
+
+def _spill(seg, region, first_chunk, counts, order):
+    n = len(counts)
+    out = (C.c_uint32 * 3)()
+    seg.spill(C.c_uint64(region), first_chunk, n, (C.c_uint32 * n)(*[int(x) for x in counts]), (C.c_uint32 * n)(*[int(x) for x in order]), out)
+    assert first_chunk * 168 <= out[0] and out[1] <= (first_chunk + n) * 168, (region, first_chunk, out[:])
+    return bool(out[2])
+
+
+def test_short_slices_hold_any_chunks_of_up_to_168_candidates(seg):
+    rng = np.random.default_rng(2)
+    for chunks in range(1, 17):                    # a wave each
+        for region in (0, 8, 2048 + 168 * 9):
+            for first in range(0, 5):
+                for counts in ([168] * chunks, [129] * chunks, [64] * chunks, [1] * chunks, rng.integers(0, 169, size=chunks),
+                               rng.integers(120, 169, size=chunks)):
+                    assert _spill(seg, region, first, counts, range(chunks)), (chunks, region, first, counts)
+
+
+@pytest.mark.parametrize("chunks", [1, 2, 3, 5, 9, 16, 17, 40, 127, 128, 129, 255, 256, 257, 511, 512, 513, 2000])
+def test_a_slice_holds_an_eighth_of_its_entries(seg, chunks):
+    """Counts as an eighth of independent entries gives them, and uneven ones of the same mean."""
+    rng = np.random.default_rng(chunks)
+    for trial in range(300 if chunks < 600 else 30):
+        region, first = int(rng.integers(0, 1 << 20)) * 8, int(rng.integers(0, 1000))
+        even = rng.binomial(1024, 0.125, size=chunks)
+        assert even.max() > 168 or _spill(seg, region, first, even, np.arange(chunks) % 16), (chunks, region, first)
+        if chunks >= 40:
+            uneven = np.where(rng.random(chunks) < 0.4, rng.integers(0, 65, size=chunks), rng.integers(100, 260, size=chunks))
+            if uneven.sum() <= 112 * chunks:
+                assert _spill(seg, region, first, uneven, rng.integers(0, 16, size=chunks)), (chunks, region, first, uneven.sum())
