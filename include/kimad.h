@@ -129,8 +129,11 @@ typedef struct kimad_plan kimad_plan_t; /* host object; owns no device memory */
 
 /* Bytes of DEVICE workspace a plan over these layer sizes needs.  n: HOST array of L sizes.
  * About a quarter of the bytes of g and h for large models: candidate space for a sixth of every layer above
- * 8192 entries (8 bytes an entry), histogram tables, chunk records and the allocation's rows (see
- * kimad_config_t::max_budget_bytes for the latter). */
+ * 8192 entries (6 bytes an entry), histogram tables, chunk records and the allocation's rows (see
+ * kimad_config_t::max_budget_bytes for the latter).
+ * With cost_units_D == 0 and cells = min(max_budget_bytes / pair_bytes, sum of n) + 1 above 4608, it counts rows that only
+ * make the allocation faster as long as 8 (L + 1) (cells + 127) is at most 256 MiB: kimad_plan_create then accepts a
+ * workspace smaller by up to 8 (L + 1) (cells - 4608) bytes, too, and the allocation takes a launch per layer. */
 int kimad_workspace_bytes(const uint64_t* n, uint32_t L, uint32_t J,
                           const kimad_config_t* cfg, uint64_t* bytes_out);
 
@@ -139,7 +142,7 @@ int kimad_workspace_bytes(const uint64_t* n, uint32_t L, uint32_t J,
  * and uploads layer descriptors and tile maps into the workspace.
  *   layers   HOST array of L descriptors (device pointers inside)
  *   ratios   HOST array of J values, strictly ascending, each in (0, 1]
- *   workspace DEVICE, 256-byte aligned, at least kimad_workspace_bytes() bytes; the plan keeps
+ *   workspace DEVICE, 256-byte aligned, at least kimad_workspace_bytes() bytes (or somewhat less, see there); the plan keeps
  *            using it until kimad_plan_destroy.
  * The plan stays valid while the layers' pointers and sizes stay the same. */
 int kimad_plan_create(const kimad_layer_t* layers, uint32_t L,

@@ -63,7 +63,7 @@ struct Layout {
     uint64_t dense_E, dense_Kcost, dense_Kout;
     uint64_t band_lo, band_hi, band_info, band_live, hull_e, hull_w, hull_n, hull_abs;
     uint64_t rstride = 0;            // cells per stored DP row (LDS-resident recurrence only)
-    uint64_t total = 0;
+    uint64_t total = 0, least = 0;   // least: without the rows that only k_dp_chain_long takes
 };
 
 struct HostLayer {
@@ -222,7 +222,7 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     lo.pool_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>((uint64_t)B * J, 1), POOL_LIMIT);
     lo.parts = take(std::max<uint64_t>(8ull * PART_STRIDE * (lo.nparts ? lo.nparts : 1), 4ull * lo.pool_cap * D3_BINS));
     lo.pool_hist = lo.parts;
-    lo.part_head = take(4ull * PART_HEAD * (lo.nparts ? lo.nparts : 1));
+    lo.part_head = take(4ull * PART_HEAD * lo.nparts);
     lo.small_layer = take(4ull * (S ? S : 1));
     lo.swg_layer = take(4ull * (nsw ? nsw : 1));
     lo.swg_first = take(4ull * (nsw ? nsw : 1));
@@ -292,8 +292,10 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
         const uint64_t cells = std::min<uint64_t>(lo.dp_cells, DP_ROW_MAX);
         lo.rstride = 512ull * (cells <= 1024 ? 2 : cells <= 2048 ? 4 : cells <= 3072 ? 6 : 9);
     }
-    lo.rows_g = take(8ull * (L + 1) * std::max(lo.rstride, chain_long_fits(L, lo.dp_cells) ? chain_long_pitch(lo.dp_cells) : 0));
-    lo.total = off;
+    // (last: a workspace that ends with the shorter rows is accepted too, see kimad_plan::all_rows)
+    lo.rows_g = take(8ull * (L + 1) * lo.rstride);
+    lo.least = lo.total = off;
+    if (chain_long_fits(L, lo.dp_cells)) lo.total = std::max(lo.total, lo.rows_g + align_up(8ull * (L + 1) * chain_long_pitch(lo.dp_cells)));
     return KIMAD_OK;
 }
 
@@ -380,6 +382,7 @@ struct kimad_plan {
     uint64_t band_unit = 0, band_cap = 0;   // cost unit and capacity that band_fits holds for (band_takes)
     bool band_fits = false;
     char* ws = nullptr;
+    bool all_rows = false;           // the workspace holds every row of an allocation beyond LDS (Layout::total)
     int device = 0;
     uint32_t main_wgs = 256;         // persistent workgroups of the fused pass (one per compute unit)
     uint32_t chunks_per_wg = 0;
@@ -559,6 +562,7 @@ struct AllocScratch {
     double* rows_g;                      // [(L + 1)][rstride]
     uint32_t rstride;
     uint64_t max_cells;                  // longest row (capacity + 1) the tables hold
+    bool all_rows;                       // rows_g holds all rows of that length (k_dp_chain_long)
 };
 
 // Table memory for callers that cannot allocate (kimad_allocate_static): one array per device, inside the
@@ -625,6 +629,7 @@ AllocScratch plan_scratch(kimad_plan* p) {
     ws.rows_g = at<double>(p, lo.rows_g);
     ws.rstride = (uint32_t)lo.rstride;
     ws.max_cells = lo.dp_cells;
+    ws.all_rows = p->all_rows && chain_long_fits(lo.L, lo.dp_cells);
     return ws;
 }
 
@@ -694,7 +699,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
         KLAUNCH(p, s, "k_dp_choice", k_dp_choice, dim3(cell_blocks, lo.L), dim3(256), ab, dl, (const double*)rows_g, rstride);
         KLAUNCH(p, s, "k_dp_walk", k_dp_walk, dim3(1), dim3(1024), ab, (const double*)(rows_g + (size_t)lo.L * rstride),
                 (const uint32_t*)dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL);
-    } else if (chain_long_fits(lo.L, ws.max_cells)) {
+    } else if (ws.all_rows) {
         const uint64_t pitch = chain_long_pitch(cap + 1);
         // (a row's filling takes several workgroups: one per 32 KB)
         KLAUNCH(p, s, "k_dp_prep", k_dp_prep, dim3(lo.L, (uint32_t)(pitch / 4096 + 1)), dim3(64), ab, ws.dl, 0u, ws.rows_g, pitch, CHAIN_PAD);
@@ -760,7 +765,8 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
     PartTables pt;
     int rc = make_layout(n.data(), L, J, p->cfg, p->lo, &p->hl, &pt);
     if (rc) { delete p; return rc; }
-    if (workspace_bytes < p->lo.total) { delete p; return KIMAD_ERR_WORKSPACE_TOO_SMALL; }
+    if (workspace_bytes < p->lo.least) { delete p; return KIMAD_ERR_WORKSPACE_TOO_SMALL; }
+    p->all_rows = workspace_bytes >= p->lo.total;
     p->ws = static_cast<char*>(workspace);
     if (hipGetDevice(&p->device) != hipSuccess) { delete p; return KIMAD_ERR_HIP; }
     (void)static_scratch_of_current_device();   // set-up: the address of this device's fixed tables is known from here on
@@ -971,6 +977,7 @@ int kimad_allocate_static(kimad_plan_t* p, const double* err_table, uint64_t bud
     ws.rows_g = reinterpret_cast<double*>(take(8ull * (KIMAD_STATIC_MAX_L + 1) * CELLS));
     ws.rstride = (uint32_t)CELLS;
     ws.max_cells = CELLS;
+    ws.all_rows = false;                                        // (rows of this length fit LDS)
     static_assert(KIMAD_STATIC_MAX_CELLS == 1024, "a stored row is two sweeps of the forward kernel's 512 threads");
     if (off > STATIC_SCRATCH_BYTES) return KIMAD_ERR_INTERNAL;
     const int rc = enqueue_allocate(p, ws, err_table, budget_bytes, j_out, K_out, offsets_out, status_out,
