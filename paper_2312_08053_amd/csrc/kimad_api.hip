@@ -18,6 +18,7 @@
 #include "k_alloc.h"
 #include "k_alloc_chain.h"
 #include "k_alloc_band.h"
+#include "list_count.h"
 #include "k_server.h"
 #include "k_selftest.h"
 
@@ -595,17 +596,8 @@ bool band_takes(kimad_plan* p, uint64_t unit, uint64_t cap) {
     const uint64_t L = p->lo.L, J = p->lo.J;
     if (L * J <= BAND_LCAP) return true;
     if (p->band_unit != unit || p->band_cap != cap) {        // (counted once per budget)
-        uint64_t entries = 0;
-        for (uint64_t i = 0; i < L && entries <= BAND_LCAP; ++i) {
-            uint64_t last = 0;
-            for (uint64_t j = 0; j < J; ++j) {
-                const uint64_t w = (p->ktab[i * J + j] + unit - 1) / unit;
-                if (w > cap) break;
-                entries += w != last;
-                last = w;
-            }
-        }
-        p->band_unit = unit; p->band_cap = cap; p->band_fits = entries <= BAND_LCAP;
+        p->band_unit = unit; p->band_cap = cap;
+        p->band_fits = count_list_records(p->ktab.data(), L, J, unit, cap, BAND_LCAP) <= BAND_LCAP;
     }
     return p->band_fits;
 }
