@@ -313,15 +313,15 @@ int kimad_plan_get_timings(kimad_plan_t* plan, char* names, uint32_t names_bytes
 
 /* Self-test of the kernels' wave-level building blocks that are written with DPP operands (the 64-lane prefix sum
  * of the streaming pass, the row-broadcast address and accumulate steps of the allocation's recurrence, the
- * group maxima of its bounds and group minima of its banded recurrence, the lane exchanges of the small layers'
- * sort): one wave runs each on the given per-lane inputs and writes every lane's result, for a test to compare
+ * minimum over a wave's rows that closes a layer of it, the group maxima of its bounds, the lane exchanges of the small
+ * layers' sort): one wave runs each on the given per-lane inputs and writes every lane's result, for a test to compare
  * with host-computed values.  All pointers DEVICE:
- *   in_u32 uint32[128], in_f64 double[128], out_u32 uint32[64 + 1024 + 256], out_f64 double[1024 + 192 + 256];
+ *   in_u32 uint32[128], in_f64 double[128], out_u32 uint32[64 + 1024 + 256], out_f64 double[1024 + 192 + 64];
  *   out_u32[lane]                          = in_u32[0] + ... + in_u32[lane]
  *   out_u32[64 + (4 k + u) * 64 + lane]    = in_u32[lane] + in_u32[64 + 16 (lane / 16) + 4 k + u]      k, u = 0..3
  *   out_f64[(4 k + u) * 64 + lane]         = in_f64[lane] + in_f64[64 + 16 (lane / 16) + 4 k + u]
  *   out_f64[1024 + 64 t + lane]            = max of in_f64 over the lane's aligned group of 2, 4, 8 lanes (t = 0, 1, 2)
- *   out_f64[1216 + 64 t + lane]            = min of in_f64 over the lane's aligned group of 2, 4, 8, 16 lanes (t = 0..3)
+ *   out_f64[1216 + lane]                   = min of in_f64[lane % 16 + 16 r], r = 0..3
  *   out_u32[1088 + 64 t + lane]            = in_u32[lane xor 1, 2, 4, 8] (t = 0..3) */
 int kimad_selftest_wave_primitives(const uint32_t* in_u32, const double* in_f64, uint32_t* out_u32, double* out_f64,
                                    void* stream);

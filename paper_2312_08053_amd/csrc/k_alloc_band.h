@@ -69,15 +69,6 @@ __device__ __forceinline__ double group_max(double v) {
     if (T >= 8) v = max_f64(v, dpp_f64<0x141>(v));     // row_half_mirror: the other quad of the eight
     return v;
 }
-// minimum over the T lanes of a group (T = 1, 2, 4, 8, 16), in every lane of it
-template <int T>
-__device__ __forceinline__ double group_min(double v) {
-    if (T >= 2) v = min_f64(v, dpp_f64<0xB1>(v));
-    if (T >= 4) v = min_f64(v, dpp_f64<0x4E>(v));
-    if (T >= 8) v = min_f64(v, dpp_f64<0x141>(v));
-    if (T >= 16) v = min_f64(v, dpp_f64<0x140>(v));    // row_mirror: the other eight of the sixteen
-    return v;
-}
 
 // The greedy fill, by one wave: lane l looks after layers l, l + 64, ...  Every round the steepest edge that fits what is
 // left is taken (the lowest lane's among equals; only the upper bound's tightness depends on it); returns the steps taken.

@@ -6,6 +6,7 @@
 #include "common.h"
 #include "k_alloc.h"
 #include "k_alloc_band.h"
+#include "k_alloc_chain.h"
 #include "k_profile.h"
 
 namespace kimad {
@@ -16,7 +17,8 @@ namespace kimad {
 // out_f64: [(k4 * 4 + u) * 64 + lane] = in_f64[lane] + in_f64[64 + 16 * (lane / 16) + 4 * k4 + u]
 //          (acc_rec_error4: the accumulator plus the error of lane K + u of the row)
 //          [1024 + t * 64 + lane], t = 0, 1, 2: maximum of in_f64 over the lane's group of 2, 4, 8 lanes (group_max)
-//          [1216 + t * 64 + lane], t = 0..3: minimum of in_f64 over the lane's group of 2, 4, 8, 16 lanes (group_min)
+//          [1216 + lane]: minimum of in_f64 over the four lanes of the wave that stand where this one does in their row of 16
+//          (min_over_rows)
 // out_u32: [1088 + t * 64 + lane], t = 0..3: in_u32[lane xor 1, 2, 4, 8] (lane_xor_u32; its wider moves are shuffles)
 __global__ __launch_bounds__(64) void k_selftest_wave(const uint32_t* in_u32, const double* in_f64, uint32_t* out_u32,
                                                       double* out_f64) {
@@ -44,10 +46,7 @@ __global__ __launch_bounds__(64) void k_selftest_wave(const uint32_t* in_u32, co
     out_f64[1024 + lane] = group_max<2>(acc);
     out_f64[1024 + 64 + lane] = group_max<4>(acc);
     out_f64[1024 + 128 + lane] = group_max<8>(acc);
-    out_f64[1216 + lane] = group_min<2>(acc);
-    out_f64[1216 + 64 + lane] = group_min<4>(acc);
-    out_f64[1216 + 128 + lane] = group_min<8>(acc);
-    out_f64[1216 + 192 + lane] = group_min<16>(acc);
+    out_f64[1216 + lane] = min_over_rows(acc);
     out_u32[1088 + lane] = lane_xor_u32<1>(base);
     out_u32[1088 + 64 + lane] = lane_xor_u32<2>(base);
     out_u32[1088 + 128 + lane] = lane_xor_u32<4>(base);
