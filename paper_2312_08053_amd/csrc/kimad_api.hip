@@ -324,7 +324,11 @@ constexpr uint64_t WHOLE_ROWS_CELLS = 2048;
 // sets lose by it (240 K chunks, 3 %: 370 and 383; 120 K, 1.1 %: 181 and 185), and the kernels that read the candidates too.
 constexpr uint32_t STREAM_CANDIDATES_CHUNKS = 524288;
 // Up to this many small layers share the launch of a kernel on the main stream; more of them, several to a compute unit in
-// turn, go to the side stream beside what follows.
+// turn, go to the side stream beside what follows.  us in a shared launch and on the side stream, small layers of 768
+// entries beside 20 tiled ones of 200 K: profile 67 and 80 with 64 of them, 72 and 80 with 512, 81 and 86 with 1024, 98 and 107
+// with 2048; selection from scratch 97 and 109, 103 and 111, 115 and 119, 142 and 138.  Of 64 to 8192 entries beside 50 layers of
+// 2 M: profile 227 and 235, 242 and 247, 257 and 265, 286 and 295; selection 425 and 429, 441 and 439, 448 and 443, 417 and
+// 398.  The line is the selection's; the profile alone would go on sharing.
 constexpr uint32_t SMALL_BESIDE = 512;
 constexpr uint32_t FALLBACK_GRID = 1024;   // workgroups of a pass that usually has nothing to do
 // A selection from scratch takes the single pass from this many chunks in tiled layers on, if these hold this many each on
@@ -395,8 +399,8 @@ struct kimad_plan {
     std::vector<const char*> ev_name;
     uint32_t ev_n = 0;
     // The small layers (one workgroup each) do not depend on the tiled layers: where they are too many to share a
-    // launch (SMALL_BESIDE), their kernels run on a side stream, forked from and joined back into the caller's stream
-    // with events, so that they overlap the short kernels of the tiled path instead of standing in line with them.
+    // launch (SMALL_BESIDE), or the profile takes two full passes, their kernels run on a side stream, forked from and
+    // joined back into the caller's stream with events, so that they overlap the short kernels of the tiled path.
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     // The single-pass profile predicts from the exact histogram its previous run on this plan left behind, once
@@ -480,11 +484,9 @@ int run_select_passes(kimad_plan* p, const uint32_t* ktab_dev, uint32_t J, doubl
     return KIMAD_OK;
 }
 
-// Single-pass profile: sample, predict, one streaming pass, candidate-fed digit-2 slots, and the
-// classic recount only for layers whose prediction missed.
-// Small layers (one workgroup each, LDS-heavy) go to the side stream once the streaming pass is
-// enqueued on `s`: they then run beside the scans that follow it, which occupy a few dozen
-// workgroups, instead of taking compute units from the persistent grid of the streaming pass.
+// The small layers' profile as a launch of its own, on the side stream (more than SMALL_BESIDE of them: after the streaming
+// pass is enqueued on `s`, so that they run beside the scans that follow it, which occupy a few dozen workgroups, and take no
+// compute units from its persistent grid; or the two full passes, any number of them).
 // *side gets the stream they were put on (to be joined by the caller).
 int launch_small_profile(kimad_plan* p, double* err_table, hipStream_t s, hipStream_t* side,
                          const uint32_t* ktab_dev = nullptr, uint32_t J = 0) {
@@ -497,6 +499,8 @@ int launch_small_profile(kimad_plan* p, double* err_table, hipStream_t s, hipStr
     return KIMAD_OK;
 }
 
+// Single-pass profile: sample, predict, one streaming pass, candidate-fed digit-2 slots, and the
+// classic recount only for layers whose prediction missed.
 // ktab, J: the targets, the plan's grid or one size per layer; without an err_table only thresholds and candidates are
 // wanted (a selection: no small layers, no certified errors).
 int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err_table, uint64_t budget_pairs, hipStream_t s,
@@ -970,7 +974,7 @@ int kimad_allocate_static(kimad_plan_t* p, const double* err_table, uint64_t bud
     ws.rstride = (uint32_t)CELLS;
     ws.max_cells = CELLS;
     ws.all_rows = false;                                        // (rows of this length fit LDS)
-    static_assert(KIMAD_STATIC_MAX_CELLS == 1024, "a stored row is two sweeps of the forward kernel's 512 threads");
+    static_assert(KIMAD_STATIC_MAX_CELLS == 1024, "a stored row holds the cells of k_dp_chain's whole workgroups");
     if (off > STATIC_SCRATCH_BYTES) return KIMAD_ERR_INTERNAL;
     const int rc = enqueue_allocate(p, ws, err_table, budget_bytes, j_out, K_out, offsets_out, status_out,
                                     static_cast<hipStream_t>(stream));
