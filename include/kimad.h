@@ -20,8 +20,9 @@
  *   - Every pointer is marked HOST or DEVICE.  The library never allocates or frees device
  *     memory: gradients, estimator, outputs and the workspace belong to the caller.
  *   - All GPU work is ordered with the given stream (a hipStream_t passed as void*; NULL is the
- *     default stream): it is enqueued there, except that kernels for more than 512 layers of at
- *     most 8192 entries each (or for such layers alone) may run on a side stream of the plan between
+ *     default stream): it is enqueued there, except that in a plan that also has larger layers the kernels
+ *     for layers of at most 8192 entries may run on a side stream of the plan, if there are more than 512 of them, or
+ *     any number in kimad_error_at and under KIMAD_CFG_CLASSIC_PROFILE, between
  *     a fork and a join event on the given stream.  No call waits for the device except kimad_plan_create (synchronous uploads) and
  *     the diagnostics getters.  kimad_profile, kimad_allocate, kimad_compress_ef, kimad_step and
  *     kimad_server_apply may be recorded into a HIP graph by stream capture (per-kernel timing off): tables
@@ -107,8 +108,10 @@ typedef struct kimad_config {
 #define KIMAD_CFG_BAND_DP 4ull          /* allocation: always run it inside the band of cells that Lagrangian bounds
                                            leave.  Same results either way; by default rows of 1537 cells or more
                                            take the band (its cost hardly grows with the row; with up to 7 ratios
-                                           from 2049 on), shorter ones the whole rows.  Rows that do not fit LDS (more than 4224 cells) and plans
-                                           of more than 1024 layers always take whole rows. */
+                                           from 2049 on) unless the grid has one ratio or the layers have more than
+                                           7168 different costs in all; others the whole rows.  Rows that do not fit
+                                           LDS (more than 4224 cells) and plans of more than 1024 layers always take
+                                           whole rows. */
 
 #define KIMAD_CFG_DENSE_FALLBACK 8ull    /* allocation: a layer never costs more than its bare values (4 n bytes).  A grid
                                            point at or beyond the break-even K * pair_bytes >= 4 n stands for sending

@@ -78,8 +78,8 @@ def test_gpt2_full_size_every_layer_against_the_oracle():
         gh.assert_table_close(E_gpu[i:i + 1], row[None, :], Kt[i:i + 1], work.sizes[i:i + 1])
     gh.check_compress(work, plan, h, K, off, plan.idx, plan.val)
 
-    # the same table with the other cost axes the benchmark reports: D = 4096 (rows of 4094 cells, the wide
-    # shape of the single-workgroup recurrence) and D = 0 (one cell per pair: 622 199 cells, one launch per layer)
+    # the same table with the other cost axes the benchmark reports: D = 4096 (rows of 4094 cells, the band of
+    # cells) and D = 0 (one cell per pair: 622 199 cells, too many for all rows to be kept: one launch per layer)
     for D in (4096, 0):
         print(f"gpt2 full size: allocation with D = {D}", flush=True)
         st, j_ref, K_ref, off_ref = ko.allocate(E_gpu, Kt, work.budget_bytes, work.pair_bytes, D)

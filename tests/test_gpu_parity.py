@@ -103,9 +103,8 @@ def test_resnet50_set_discretised_budget():
 @pytest.mark.parametrize("full", [False, True])
 @pytest.mark.parametrize("D", [1500, 3000, 3071, 3072, 4096, 4223, 4224])
 def test_cost_axes_of_every_width_of_the_single_kernel_allocation(D, full):
-    """Rows of 1501, 3001 and 3072 cells take the forward kernel with 4 and 6 cells per thread; 3073, 4097 and
-    4224 cells its wide shape (9 per thread, shorter groups of layers); 4225 cells no longer fit LDS and go
-    through one launch per layer.  Allocation only (the oracle's table in, j out).  `full` runs the recurrence
+    """Rows of 1501 cells take workgroups of eight compute waves, 3001 to 4224 cells of four; 4225 cells no longer fit LDS and
+    every wave reads the previous row from memory.  Allocation only (the oracle's table in, j out).  `full` runs the recurrence
     over whole rows; otherwise only the band of cells that the Lagrangian bounds leave is visited."""
     import torch
     work = ks.make_workload("resnet18", D=D)
