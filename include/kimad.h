@@ -77,8 +77,9 @@ typedef struct kimad_config {
                                            (one cost cell per pair: set max_budget_bytes, see there) */
     uint64_t max_budget_bytes;          /* largest budget kimad_allocate will see; 0 = uncompressed size.
                                            Sizes the DP tables when cost_units_D == 0: the workspace then grows
-                                           by L * max_budget_bytes / pair_bytes bytes, and a plan whose tables
-                                           would pass 4 GiB is refused with KIMAD_ERR_TABLES_TOO_LARGE (the
+                                           by L * max_budget_bytes / pair_bytes bytes, and by eight times that
+                                           while it is at most 256 MiB (kimad_workspace_bytes), and a plan whose
+                                           winners' table would pass 4 GiB is refused with KIMAD_ERR_TABLES_TOO_LARGE (the
                                            default of 0 does that for models beyond a few million elements:
                                            give the budget limit, or a factor such as the paper's 1000). */
     uint64_t flags;                     /* KIMAD_CFG_* */
