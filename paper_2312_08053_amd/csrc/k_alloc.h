@@ -19,8 +19,8 @@ struct AllocBuffers {
     uint32_t cap;            // capacity in units
     double* row0;            // [cap+1]
     double* row1;            // [cap+1]
-    uint8_t* choice;         // [L][stride]
-    uint16_t* cprev;         // [L][stride] rows that fit LDS only: the cell the winning candidate came from
+    uint8_t* choice;         // [L][stride] winners (rows that fit LDS: a piece's winners of a cell side by side, k_dp_walk)
+    uint16_t* cprev;         // [pieces][stride] rows that fit LDS only: the cell of the piece's first row a cell came from
     uint64_t stride;         // >= cap+1
     int32_t* j_out;
     uint64_t* K_out;
@@ -230,12 +230,11 @@ __global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uin
     if (j == 0) { dl.hn[i] = (uint32_t)__builtin_popcountll(mask); dl.habs[i] = largest; }
 }
 
-// The recurrence for capacities whose rows fit LDS, in three kernels:
-//   k_dp_chain    (k_alloc_chain.h) least totals only, a min per candidate and cell, every row stored;
-//   k_dp_choice   all (layer, cell) pairs in parallel: the winning candidate, from the stored rows;
+// The recurrence for capacities whose rows fit LDS, in two kernels:
+//   k_dp_chain    (k_alloc_chain.h) least totals only, a min per candidate and cell, every row stored; beside that, by other
+//                 workgroups of the launch, the winning candidate of every (layer, cell) pair from the stored rows;
 //   k_dp_walk     one workgroup: status, smallest cost attaining the least total, back-tracking, outputs.
-// Only the first is a sequential chain of L steps, so it carries nothing but the minimum: which candidate attains it is
-// order-independent given the previous row and is found afterwards.
+// Only the minimum is a sequential chain of L steps: which candidate attains it is order-independent given the previous row.
 constexpr uint32_t DP_ROW_MAX = 4224;           // cells of the longest row (a discretisation factor of 4096 fits)
 
 // min of two doubles, neither a signalling NaN (the builtin would add a canonicalising max per operand)
@@ -290,71 +289,66 @@ __device__ __forceinline__ uint32_t lds_addr(const double* p) { return (uint32_t
 // distance in the row.
 __device__ __forceinline__ double rec_err(const uint4& r) { return __hiloint2double((int)r.y, (int)r.x); }
 
-// Winning candidate of every (layer, cell): candidates in list order with a strict "<", then the
-// lowest member of the winner's run whose rounded total is the same.
-__global__ __launch_bounds__(256) void k_dp_choice(AllocBuffers ab, DpLists dl, const double* __restrict__ rows_g,
-                                                   uint32_t rstride) {
-    __shared__ uint32_t lw[KIMAD_MAX_J_CONST], lj[KIMAD_MAX_J_CONST];
-    __shared__ double le[2 * KIMAD_MAX_J_CONST];
-    __shared__ double prev[DP_ROW_MAX];       // the previous row up to this workgroup's last cell
-    const uint32_t i = blockIdx.y, tid = threadIdx.x;
-    const uint32_t n = dl.n[i];
-    if (tid < n) {
-        const size_t o = (size_t)i * ab.J + tid;
-        lw[tid] = dl.w[o]; lj[tid] = dl.jj[o];
-        le[2 * tid] = dl.e[2 * o]; le[2 * tid + 1] = dl.e[2 * o + 1];
+// The layers in pieces, whose cells k_dp_chain follows back: of four layers, and the last ones singly, since a piece's work
+// begins when the chain has passed it and the last one's is waited for.
+struct Pieces {
+    static constexpr uint32_t MOST = 4, SINGLE = 24;               // layers of a piece; last layers that are pieces
+    uint32_t in_fours, fours, ones;                                // layers in pieces of four, such pieces, pieces of one
+    __host__ __device__ __forceinline__ explicit Pieces(uint32_t L) {
+        ones = L < SINGLE ? L : SINGLE;
+        in_fours = L - ones;
+        fours = (in_fours + 3u) / 4u;
     }
-    // every candidate of a cell reads one cell of the previous row: from LDS, not one dependent
-    // memory round trip per candidate
-    {
-        const double* prow = rows_g + (size_t)i * rstride;
-        const uint32_t upto = min(blockIdx.x * 256u + 256u, ab.cap + 1u);
-        for (uint32_t x = tid; x < upto; x += 256u) prev[x] = prow[x];
+    __host__ __device__ __forceinline__ uint32_t count() const { return fours + ones; }
+    __host__ __device__ __forceinline__ uint32_t first(uint32_t p) const {          // first layer (p = count(): the number of layers)
+        return p < fours ? 4u * p : in_fours + (p - fours);
     }
-    __syncthreads();
-    const uint32_t c = blockIdx.x * 256u + tid;
-    if (c > ab.cap) return;
-    double best = DP_INF;
-    uint32_t bk = 0xFFu;
-    for (uint32_t k = 0; k < n; ++k) {
-        const uint32_t w = lw[k];
-        if (w > c) break;                          // costs ascend along the list
-        const double t = prev[c - w] + le[2 * k];
-        if (t < best) { best = t; bk = k; }
+    __host__ __device__ __forceinline__ uint32_t of(uint32_t layer) const {         // a layer's piece
+        return layer < in_fours ? layer / 4u : fours + (layer - in_fours);
     }
-    uint32_t bj = 0xFFu;
-    if (bk != 0xFFu) {
-        // Only the winner's run matters: if the member before its last one rounds to the same total
-        // (never for a single: that error is NaN), the lowest such member wins.
-        bj = lj[bk] >> 8;
-        const double p = prev[c - lw[bk]];
-        if (p + le[2 * bk + 1] == best) {
-            const uint32_t jlo = lj[bk] & 0xFFu;
-            uint32_t j = bj - 1u;
-            while (j > jlo && p + ab.E[(size_t)i * ab.J + j - 1] == best) --j;
-            bj = j;
-        }
-    }
-    ab.choice[(size_t)i * ab.stride + c] = (uint8_t)bj;
-    ab.cprev[(size_t)i * ab.stride + c] = bk != 0xFFu ? (uint16_t)(c - lw[bk]) : (uint16_t)0xFFFFu;
-}
+};
 
+// Status, smallest cost attaining the least total, back-tracking, outputs.  The workgroups of k_dp_chain have followed every
+// cell through a piece's m layers: cprev[p][c] is the cell of piece p's first row that cell c behind its last layer came
+// from, and the m winners on that way stand in bytes at choice + (first layer) stride + c m.  So the sequential part is one
+// LDS read a piece; the pieces' rows are staged with one flat copy (they are contiguous, the pitch a multiple of 16 bytes),
+// the first lot before the least total is known.
 constexpr uint32_t DP_STAGE_BYTES = 128u * 1024u;
 constexpr uint32_t DP_WALK_MAX_L = 4224;           // layers whose path cells k_dp_walk keeps in LDS: every layer costs at least one
                                                    // cell, so a feasible path through rows of at most 4224 cells has no more layers
 
-__global__ __launch_bounds__(1024) void k_dp_walk(AllocBuffers ab, const double* __restrict__ last,
-                                                  const uint32_t* __restrict__ bad,
+__global__ __launch_bounds__(1024) void k_dp_walk(AllocBuffers ab, const double* __restrict__ last, const uint32_t* __restrict__ bad,
                                                   int32_t err_infeasible, int32_t err_nonfinite, int32_t err_internal) {
     __shared__ __attribute__((aligned(16))) uint8_t stage[DP_STAGE_BYTES];
-    __shared__ uint16_t s_cell[DP_WALK_MAX_L];     // the path's cell per layer (a store to memory in the chain would be waited for)
+    __shared__ uint16_t s_cell[DP_WALK_MAX_L];     // the path's cell per piece (a store to memory in the chain would be waited for)
     __shared__ double sv[16];
     __shared__ unsigned long long sc[16];
-    __shared__ unsigned long long cstar;
-    __shared__ uint32_t any_bad;
+    __shared__ uint32_t any_bad, cstar;
     __shared__ int32_t st;
     const uint32_t tid = threadIdx.x;
     const uint32_t ncell = ab.cap + 1;
+    const Pieces pieces(ab.L);
+    const uint32_t pitch = (uint32_t)ab.stride;                      // cells per row
+    const uint32_t per_group = DP_STAGE_BYTES / (2u * pitch);
+    const uint16_t* srow = reinterpret_cast<const uint16_t*>(stage);
+    auto stage_rows = [&](uint32_t lo_p, uint32_t nrows) {
+        const uint4* from = reinterpret_cast<const uint4*>(ab.cprev + (size_t)lo_p * pitch);
+        uint4* dst = reinterpret_cast<uint4*>(stage);
+        const uint32_t n16 = nrows * (pitch / 8u);
+        for (uint32_t x0 = 0; x0 < n16; x0 += 8u * 1024u) {
+            uint4 v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const uint32_t x = x0 + k * 1024u + tid;
+                v[k] = x < n16 ? from[x] : make_uint4(0u, 0u, 0u, 0u);
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const uint32_t x = x0 + k * 1024u + tid;
+                if (x < n16) dst[x] = v[k];
+            }
+        }
+    };
     if (tid == 0) any_bad = 0u;
     __syncthreads();
     uint32_t mybad = 0;
@@ -362,29 +356,36 @@ __global__ __launch_bounds__(1024) void k_dp_walk(AllocBuffers ab, const double*
     if (mybad) atomicOr(&any_bad, 1u);
     // least total, smallest cost attaining it
     double best = DP_INF;
-    unsigned long long bc = ~0ull;
+    uint32_t bc = 0xFFFFFFFFu;
     for (uint32_t c = tid; c < ncell; c += 1024) {
         const double v = last[c];
         if (v < best) { best = v; bc = c; }
     }
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
+    uint32_t hi = pieces.count(), lo_p = hi > per_group ? hi - per_group : 0u;
+    if (ab.L <= DP_WALK_MAX_L) stage_rows(lo_p, hi - lo_p);
+    auto least = [&](int d) {
         const double ov = __shfl_xor(best, d, 64);
-        const unsigned long long oc = __shfl_xor(bc, d, 64);
+        const uint32_t oc = __shfl_xor(bc, d, 64);
         if (ov < best || (ov == best && oc < bc)) { best = ov; bc = oc; }
-    }
+    };
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) least(d);
     if (lane_id() == 0) { sv[tid >> 6] = best; sc[tid >> 6] = bc; }
     __syncthreads();
-    if (tid == 0) {
-        for (uint32_t w = 1; w < 16; ++w)
-            if (sv[w] < best || (sv[w] == best && sc[w] < bc)) { best = sv[w]; bc = sc[w]; }
-        int32_t s = 0;
-        if (any_bad) s = err_nonfinite;
-        else if (ab.flags[2]) s = err_internal;
-        else if (!(best < DP_INF) || ab.L > DP_WALK_MAX_L) s = err_infeasible;   // (more layers than cells: no finite total)
-        st = s;
-        cstar = bc;
-        *ab.status = s;
+    if (tid < 64u) {
+        best = sv[tid & 15u];
+        bc = (uint32_t)sc[tid & 15u];
+#pragma unroll
+        for (int d = 8; d > 0; d >>= 1) least(d);
+        if (tid == 0) {
+            int32_t s = 0;
+            if (any_bad) s = err_nonfinite;
+            else if (ab.flags[2]) s = err_internal;
+            else if (!(best < DP_INF) || ab.L > DP_WALK_MAX_L) s = err_infeasible;   // (more layers than cells: no finite total)
+            st = s;
+            cstar = bc;
+            *ab.status = s;
+        }
     }
     __syncthreads();
     if (st != 0) {
@@ -392,57 +393,30 @@ __global__ __launch_bounds__(1024) void k_dp_walk(AllocBuffers ab, const double*
         for (uint32_t i = tid; i <= ab.L; i += 1024) ab.offsets_out[i] = 0;
         return;
     }
-    // Back-tracking.  The sequential part follows only the chain of cells: k_dp_choice stored, beside
-    // every winner, the cell it came from, so a step is one LDS read.  The rows of a group of layers
-    // are staged in LDS with one flat copy (they are contiguous, pitch a multiple of 16 bytes), walked
-    // by one thread that notes each layer's cell, next group.  The winners are then looked up in parallel.
-    const uint32_t pitch = (uint32_t)ab.stride;                      // cells per row
-    const uint32_t per_group = DP_STAGE_BYTES / (2u * pitch);
-    const uint16_t* srow = reinterpret_cast<const uint16_t*>(stage);
-    uint32_t hi = ab.L;
-    while (hi > 0) {
-        const uint32_t lo_l = hi > per_group ? hi - per_group : 0u;
-        const uint32_t nrows = hi - lo_l;
-        __syncthreads();
-        {
-            const uint4* src = reinterpret_cast<const uint4*>(ab.cprev + (size_t)lo_l * pitch);
-            uint4* dst = reinterpret_cast<uint4*>(stage);
-            const uint32_t n16 = nrows * (pitch / 8u);
-            for (uint32_t x0 = 0; x0 < n16; x0 += 8u * 1024u) {
-                uint4 v[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const uint32_t x = x0 + k * 1024u + tid;
-                    v[k] = x < n16 ? src[x] : make_uint4(0u, 0u, 0u, 0u);
-                }
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const uint32_t x = x0 + k * 1024u + tid;
-                    if (x < n16) dst[x] = v[k];
-                }
-            }
-        }
-        __syncthreads();
+    for (;;) {
         if (tid == 0) {
-            uint32_t c = (uint32_t)cstar;
-            const uint16_t* row = srow + (size_t)nrows * pitch;
-            for (uint32_t i = hi; i-- > lo_l;) {
-                row -= pitch;
-                s_cell[i] = (uint16_t)c;
-                c = min((uint32_t)row[c], ab.cap);         // (a feasible path never meets the 0xFFFF of an empty cell)
+            uint32_t c = cstar;
+            for (uint32_t p = hi; p-- > lo_p;) {
+                s_cell[p] = (uint16_t)c;
+                c = min((uint32_t)srow[(size_t)(p - lo_p) * pitch + c], ab.cap);
             }
             cstar = c;
         }
-        hi = lo_l;
+        hi = lo_p;
+        __syncthreads();
+        if (hi == 0u) break;
+        lo_p = hi > per_group ? hi - per_group : 0u;
+        stage_rows(lo_p, hi - lo_p);
+        __syncthreads();
     }
-    __syncthreads();
     // winners along the path, sizes and offsets, in parallel
     unsigned long long carry = 0;
     for (uint32_t i0b = 0; i0b < ab.L; i0b += 1024) {
         const uint32_t i = i0b + tid;
         unsigned long long K = 0;
         if (i < ab.L) {
-            const uint32_t j = ab.choice[(size_t)i * ab.stride + (uint32_t)s_cell[i]];
+            const uint32_t p = pieces.of(i), first = pieces.first(p), m = pieces.first(p + 1u) - first;
+            const uint32_t j = ab.choice[(size_t)first * ab.stride + (size_t)s_cell[p] * m + (i - first)];
             ab.j_out[i] = (int32_t)j;
             K = ab.Kout[(size_t)i * ab.J + j];
             ab.K_out[i] = K;

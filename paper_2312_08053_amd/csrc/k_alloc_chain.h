@@ -20,7 +20,8 @@
 // back reports as an internal error.  A wave that has given up waits no more, in this row or a later one, and the loaders of
 // k_dp_chain look every CHAIN_LOOK reads whether one has: the launch ends after a few such waits, however many layers are
 // left.  A number beyond the grid, as calls that share one set of tables and overlap hand out, owns no cells: its workgroup
-// leaves, and the call reports an internal error too.
+// leaves, and the call reports an internal error too.  (The workgroups that look after a piece of the layers have the highest
+// numbers and wait for the ones that keep cells; nobody waits for them.)
 #pragma once
 #include "common.h"
 #include "k_alloc.h"
@@ -231,14 +232,172 @@ __device__ __forceinline__ void chain_load(const AllocBuffers& ab, const double*
     }
 }
 
-// W: compute waves, GW: waves of a loader group, MAXC: cells of the longest row.
+// ---- which candidate won, and where it came from ------------------------------------------------
+// While the chain goes on, further workgroups of its launch follow the rows as they come, a piece of the layers each, in
+// which every cell finds its winning candidate (in list order with a strict "<", then the lowest member of the winner's run
+// whose rounded total is the same) and is then followed down to the piece's first row.  What is left for k_dp_walk is one
+// step a piece, not one a layer, and when the chain ends the rows of all but the last pieces have been dealt with.
+// Bound by the vector instructions per cell and candidate: a layer takes a workgroup several times as long as the chain.
+// What the last ones take is added to the chain's time, so the last layers are pieces of their own (Pieces, k_alloc.h), and
+// have a workgroup for every BLOCK_CELLS of their cells.  (us, with a launch of one workgroup per layer and 256 cells after the
+// chain and a walk of one step a layer, and now.  148 layers of 999 cells: chain 59, choice 8, walk 18; chain 64, walk 10.  62
+// layers with up to 50 candidates: 31, 10 and 12; 38 and 9.  All launches of the allocation, 64 ratios: 20 layers 36 and 31, 500
+// 230 and 197, 1000 421 and 353; 148 layers of 4097 cells 260 and 245.  Pieces of four throughout: chain 73 and 43; of two, 67
+// and 41.)
+constexpr uint32_t BLOCK_CELLS = 256;
+
+struct PieceList {
+    double e_before[KIMAD_MAX_J_CONST];
+    uint32_t w[KIMAD_MAX_J_CONST], jj[KIMAD_MAX_J_CONST];
+};
+
+// Cells [lo, hi] of layers [first, first + m) for one workgroup of NT threads (m > 1: all cells).  rows: two rows in LDS, `pitch`
+// cells apart, a cell before each.
+template <uint32_t MAXC, uint32_t NT>
+__device__ __forceinline__ void chain_choose(const AllocBuffers& ab, const DpLists& dl, const double* rows_g, uint32_t rstride, uint32_t first,
+                                             uint32_t m, uint32_t piece, uint32_t lo, uint32_t hi, double* rows, uint32_t pitch, PieceList* lists,
+                                             uint16_t (*src)[MAXC], uint8_t (*win)[MAXC]) {
+    constexpr uint32_t CPT = (MAXC + NT - 1u) / NT, U = CPT <= 2u ? 8u : 4u;     // candidates whose cells are asked for together
+    const uint32_t tid = threadIdx.x, lane = lane_id();
+    const uint32_t mine = lo + (uint32_t)__builtin_amdgcn_readfirstlane(tid & ~63u);   // the wave's first cell: none beyond hi
+    unsigned long long v[CPT];
+    auto ask = [&](uint32_t i) {
+        const unsigned long long* row = reinterpret_cast<const unsigned long long*>(rows_g + (size_t)i * rstride);
+#pragma unroll
+        for (uint32_t q = 0; q < CPT; ++q) v[q] = cell_load(row + min(tid + q * NT, hi));
+    };
+    auto any_empty = [&]() {
+        uint32_t top = 0u;
+#pragma unroll
+        for (uint32_t q = 0; q < CPT; ++q) top = max(top, (uint32_t)(v[q] >> 32));
+        return ballot(top == 0xFFFFFFFFu) != 0ull;
+    };
+    uint32_t limit = min(ab.polls, CHAIN_LOOK);       // as in chain_load; but a wait given up is counted if it is the first one
+    uint32_t polls = 0;
+    auto go_on = [&]() {
+        if (__builtin_expect(++polls > limit, 0)) {
+            if (limit && polls > ab.polls && lane == 0) atomicCAS(&ab.flags[2], 0u, 1u);
+            if (limit == 0u || polls > ab.polls ||
+                __builtin_amdgcn_readfirstlane(__hip_atomic_load(&ab.flags[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0u) {
+                limit = 0u;
+                return false;
+            }
+            limit = min(ab.polls, polls + CHAIN_LOOK);
+        }
+        return true;
+    };
+    // one wave waits for the first row's last cell, with pauses: a piece may have to wait for most of the chain
+    if (tid < 64u) {
+        const unsigned long long* cell = reinterpret_cast<const unsigned long long*>(rows_g + (size_t)first * rstride) + hi;
+        while (cell_empty(cell_load(cell)) && go_on()) __builtin_amdgcn_s_sleep(8);
+    }
+    __syncthreads();
+    ask(first);
+    for (uint32_t s = 0; s < m; ++s) {
+        const uint32_t i = first + s;
+        PieceList& list = lists[s & 1u];
+        double* prev = rows + (s & 1u) * pitch + 1u;
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane(dl.n[i]);
+        // lane k of every wave holds list record k (one that is not there costs more than any cell can pay)
+        const size_t o = (size_t)i * ab.J + min(lane, ab.J - 1u);
+        const uint32_t my_w = dl.w[o];
+        const int my_w8 = lane < n ? (int)(8u * my_w) : 0x3FFFFFFF;
+        const double my_e = lane < n ? dl.e[2 * o] : DP_INF;
+        if (tid < n) {
+            list.w[tid] = my_w; list.jj[tid] = dl.jj[o];
+            list.e_before[tid] = dl.e[2 * o + 1];
+        }
+        polls = 0;
+        while (any_empty() && go_on()) {
+            asm volatile("" ::: "memory");
+            ask(i);
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < CPT; ++q)
+            if (tid + q * NT < MAXC) prev[tid + q * NT] = __longlong_as_double((long long)v[q]);
+        if (tid == 0) prev[-1] = DP_INF;
+        if (s + 1u < m) ask(i + 1u);
+        lds_barrier();
+        const int before = (int)lds_addr(prev) - 8;      // the cell of +inf, for what a cell cannot afford
+        // NQ cells a thread, NT apart
+        auto choose = [&](auto nq) {
+            constexpr uint32_t NQ = decltype(nq)::value;
+            double best[NQ];
+            uint32_t bk[NQ];
+            int at[NQ];
+#pragma unroll
+            for (uint32_t q = 0; q < NQ; ++q) { best[q] = DP_INF; bk[q] = 0xFFu; at[q] = before + 8 + 8 * (int)min(lo + tid + q * NT, hi); }
+            for (uint32_t k0 = 0; k0 < n; k0 += U) {
+                double t[U][NQ];
+#pragma unroll
+                for (uint32_t u = 0; u < U; ++u) {
+                    const int w8 = __builtin_amdgcn_readlane(my_w8, (int)(k0 + u));
+#pragma unroll
+                    for (uint32_t q = 0; q < NQ; ++q) t[u][q] = *(lds_cdouble_ptr)(uintptr_t)(uint32_t)max(at[q] - w8, before);
+                }
+#pragma unroll
+                for (uint32_t u = 0; u < U; ++u) {
+                    const double e = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(my_e), (int)(k0 + u)),
+                                                      __builtin_amdgcn_readlane(__double2loint(my_e), (int)(k0 + u)));
+#pragma unroll
+                    for (uint32_t q = 0; q < NQ; ++q) {
+                        const double x = t[u][q] + e;
+                        bk[q] = x < best[q] ? k0 + u : bk[q];
+                        best[q] = min_f64(x, best[q]);
+                    }
+                }
+            }
+#pragma unroll
+            for (uint32_t q = 0; q < NQ; ++q) {
+                const uint32_t c = lo + tid + q * NT;
+                if (c > hi) continue;
+                uint32_t bj = 0xFFu, from = 0xFFFFu;
+                if (bk[q] != 0xFFu) {
+                    // Only the winner's run matters: if the member before its last one rounds to the same total
+                    // (never for a single: that error is NaN), the lowest such member wins.
+                    const uint32_t jj = list.jj[bk[q]];
+                    bj = jj >> 8;
+                    from = c - list.w[bk[q]];
+                    const double p = prev[from];
+                    if (p + list.e_before[bk[q]] == best[q]) {
+                        const uint32_t jlo = jj & 0xFFu;
+                        uint32_t j = bj - 1u;
+                        while (j > jlo && p + ab.E[(size_t)i * ab.J + j - 1] == best[q]) --j;
+                        bj = j;
+                    }
+                }
+                win[s][c] = (uint8_t)bj;
+                src[s][c] = (uint16_t)from;
+            }
+        };
+        if (mine + NT <= hi) choose(std::integral_constant<uint32_t, CPT>{});
+        else if (mine <= hi) choose(std::integral_constant<uint32_t, 1u>{});
+    }
+    __syncthreads();
+    for (uint32_t c = lo + tid; c <= hi; c += NT) {
+        uint32_t at = c;
+        uint8_t* to = ab.choice + (size_t)first * ab.stride + (size_t)c * m;
+        for (uint32_t s = m; s-- > 0u;) {
+            to[s] = win[s][at];
+            at = min((uint32_t)src[s][at], ab.cap);            // (a feasible path never meets the 0xFFFF of an empty cell)
+        }
+        ab.cprev[(size_t)piece * ab.stride + c] = (uint16_t)at;
+    }
+}
+
+// W: compute waves, GW: waves of a loader group, MAXC: cells of the longest row.  The first `keepers` numbers keep cells, the
+// others look after a piece each.
 constexpr uint32_t chain_threads(uint32_t w, uint32_t gw) { return 64u * (w + 1u + CHAIN_LOADERS * gw); }
 template <uint32_t MAXC, uint32_t W, uint32_t GW>
-__global__ __launch_bounds__(chain_threads(W, GW)) void k_dp_chain(AllocBuffers ab, DpLists dl, double* __restrict__ rows_g, uint32_t rstride) {
+__global__ __launch_bounds__(chain_threads(W, GW)) void k_dp_chain(AllocBuffers ab, DpLists dl, double* __restrict__ rows_g, uint32_t rstride,
+                                                                   uint32_t keepers) {
     constexpr uint32_t NT = chain_threads(W, GW), CELLS = 16u * W;
     static_assert(MAXC % CELLS == 0, "whole workgroups");
     __shared__ double rows[2][CELLS + MAXC];       // CELLS cells of +inf before cost 0: a record costs at most c_hi here
     __shared__ uint4 recs[CHAIN_RECS][64];
+    __shared__ PieceList lists[2];
+    __shared__ uint16_t src[Pieces::MOST][MAXC];
+    __shared__ uint8_t win[Pieces::MOST][MAXC];
     __shared__ uint32_t sh_b;
     const uint32_t tid = threadIdx.x;
     if (tid == 0) sh_b = atomicAdd(&ab.flags[1], 1u);
@@ -246,6 +405,15 @@ __global__ __launch_bounds__(chain_threads(W, GW)) void k_dp_chain(AllocBuffers 
     const uint32_t number = (uint32_t)__builtin_amdgcn_readfirstlane(sh_b);
     if (number >= gridDim.x) {
         if (tid == 0) atomicAdd(&ab.flags[2], 1u);
+        return;
+    }
+    if (number >= keepers) {
+        const Pieces pieces(ab.L);
+        const uint32_t blocks = ab.cap / BLOCK_CELLS + 1u, x = number - keepers;
+        const uint32_t p = x < pieces.fours ? x : pieces.fours + (x - pieces.fours) / blocks, first = pieces.first(p);
+        const uint32_t lo = x < pieces.fours ? 0u : (x - pieces.fours) % blocks * BLOCK_CELLS;
+        chain_choose<MAXC, NT>(ab, dl, rows_g, rstride, first, pieces.first(p + 1u) - first, p, lo,
+                               x < pieces.fours ? ab.cap : min(lo + BLOCK_CELLS - 1u, ab.cap), rows[0], CELLS + MAXC, lists, src, win);
         return;
     }
     const uint32_t c0 = number * CELLS;

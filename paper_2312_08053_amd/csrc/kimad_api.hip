@@ -8,6 +8,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/kimad.h"
@@ -663,7 +664,6 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
                 ws.dense_Kout);
         ab.E = ws.dense_E; ab.Ktab = ws.dense_Kcost; ab.Kout = ws.dense_Kout;
     }
-    const uint32_t cell_blocks = (uint32_t)((cap + 1 + 255) / 256);
     if (cap + 1 <= DP_ROW_MAX) {
         const DpLists& dl = ws.dl;
         double* rows_g = ws.rows_g;
@@ -683,18 +683,20 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
                     (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE);
             return KIMAD_OK;
         }
-        if (cap + 1 <= 1024 && lo.L > CHAIN_NARROW_L) {
-            KLAUNCH(p, s, "k_dp_chain", (k_dp_chain<1024, 4, 2>), dim3((uint32_t)(cap / 64 + 1)), dim3(chain_threads(4, 2)), ab, dl, rows_g, rstride);
-        } else if (cap + 1 <= 1024) {
-            KLAUNCH(p, s, "k_dp_chain", (k_dp_chain<1024, 8, 2>), dim3((uint32_t)(cap / 128 + 1)), dim3(chain_threads(8, 2)), ab, dl, rows_g, rstride);
-        } else if (cap + 1 <= 2048) {
-            KLAUNCH(p, s, "k_dp_chain", (k_dp_chain<2048, 8, 3>), dim3((uint32_t)(cap / 128 + 1)), dim3(chain_threads(8, 3)), ab, dl, rows_g, rstride);
-        } else {
-            KLAUNCH(p, s, "k_dp_chain", (k_dp_chain<DP_ROW_MAX, 4, 5>), dim3((uint32_t)(cap / 64 + 1)), dim3(chain_threads(4, 5)), ab, dl, rows_g, rstride);
-        }
-        KLAUNCH(p, s, "k_dp_choice", k_dp_choice, dim3(cell_blocks, lo.L), dim3(256), ab, dl, (const double*)rows_g, rstride);
-        KLAUNCH(p, s, "k_dp_walk", k_dp_walk, dim3(1), dim3(1024), ab, (const double*)(rows_g + (size_t)lo.L * rstride),
-                (const uint32_t*)dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL);
+        // (keepers of 16 cells a compute wave, then a workgroup per piece of the layers)
+        auto chain = [&](auto kern, uint32_t cells, uint32_t threads) -> int {
+            const uint32_t keepers = (uint32_t)(cap / cells + 1);
+            const Pieces pieces(lo.L);
+            const uint32_t others = pieces.fours + pieces.ones * (uint32_t)(cap / BLOCK_CELLS + 1);
+            KLAUNCH(p, s, "k_dp_chain", kern, dim3(keepers + others), dim3(threads), ab, dl, rows_g, rstride, keepers);
+            KLAUNCH(p, s, "k_dp_walk", k_dp_walk, dim3(1), dim3(1024), ab, (const double*)(rows_g + (size_t)lo.L * rstride),
+                    (const uint32_t*)dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL);
+            return KIMAD_OK;
+        };
+        if (cap + 1 <= 1024 && lo.L > CHAIN_NARROW_L) return chain(k_dp_chain<1024, 4, 2>, 64, chain_threads(4, 2));
+        if (cap + 1 <= 1024) return chain(k_dp_chain<1024, 8, 2>, 128, chain_threads(8, 2));
+        if (cap + 1 <= 2048) return chain(k_dp_chain<2048, 8, 3>, 128, chain_threads(8, 3));
+        return chain(k_dp_chain<DP_ROW_MAX, 4, 5>, 64, chain_threads(4, 5));
     } else if (ws.all_rows) {
         const uint64_t pitch = chain_long_pitch(cap + 1);
         // (a row's filling takes several workgroups: one per 32 KB)
@@ -711,6 +713,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
         KLAUNCH(p, s, "k_dp_final", k_dp_final, dim3(1), dim3(1024), ab, (const double*)(ws.rows_g + (uint64_t)lo.L * pitch + CHAIN_PAD),
                 (const uint32_t*)ws.dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL);
     } else {
+        const uint32_t cell_blocks = (uint32_t)((cap + 1 + 255) / 256);
         // (clears with a kernel, not hipMemsetAsync: the call may be recorded into a graph)
         KLAUNCH(p, s, "k_zero16", k_zero16, dim3(1), dim3(256), reinterpret_cast<uint4*>(ws.flags), (uint64_t)1);
         KLAUNCH(p, s, "k_dp_init", k_dp_init, dim3(std::min<uint32_t>(cell_blocks, 1024)), dim3(256), ab);

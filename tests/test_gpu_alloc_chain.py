@@ -52,6 +52,22 @@ def test_edges_of_the_rows(cells, J):
         plan.close()
 
 
+@pytest.mark.parametrize("cells", [200, 256, 257, 1000, 1030, 2049])
+@pytest.mark.parametrize("L", [23, 24, 25, 28, 29, 61])
+def test_pieces_that_the_walk_goes_through(cells, L):
+    """The last 24 layers are followed back singly, the ones before in fours, the last of those shorter."""
+    import torch
+    ratios, sizes, Kt, E = _case(cells, 21, L, 3 * cells + L)          # (seeds that are multiples of 3: ties)
+    budget = 8 * (cells - 1)
+    st_ref, j_ref, K_ref, off_ref = ko.allocate(E, Kt, budget, 8, 0)
+    plan = _plan(sizes, ratios, budget)
+    j, K, off, st = plan.allocate(budget, torch.from_numpy(E.reshape(-1)).cuda())
+    assert int(st.item()) == st_ref
+    if st_ref == ko.OK:
+        assert np.array_equal(j.cpu().numpy(), j_ref) and np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
+    plan.close()
+
+
 @pytest.mark.parametrize("cells", [700, 9000])
 def test_non_finite_errors_end_the_call(cells):
     import torch
