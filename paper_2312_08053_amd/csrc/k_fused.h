@@ -800,28 +800,147 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint3
 // Sum of a layer's parts, written in the layout the scans read: digit-1 counts and sums, then the
 // digit-2 tables of all SLOT_STRIDE slots (zero beyond the slots the pass counted, where k_hist2c
 // adds).  Counts as they are; sums as midpoints in units of 2^16 (exponent 255: the NaN count;
-// bin 0: the exact squares).  One thread per entry, the parts' loads issued four at a time.
+// bin 0: the exact squares).
+// Most layers have a handful of parts, and what a block takes is a chain of memory round trips (the layer's state and the
+// parts' heads, the parts, the stores): a wave looks after a block by itself.  A layer of more than REDUCE_WAVE_PARTS parts
+// has a workgroup to every block, whose waves take a quarter of the parts each.  The host lists the workgroups (reduce_wgs).
+// (us with a workgroup to every block of every layer, and now: ResNet-50 14.6 and 10.5, GPT-2-shaped, whose embedding has 80
+// parts, 14.2 and 12.9, Llama-shaped 38 and 25.)
 constexpr uint32_t LAYER_ENTRIES = D1_BINS + SLOT_STRIDE * D2_BINS;
-constexpr uint32_t REDUCE_ENTRIES = 128;        // entries per workgroup: two per lane, each of the 4 waves takes a quarter of the parts
+constexpr uint32_t REDUCE_ENTRIES = 128;        // entries of a block: two per lane
+constexpr uint32_t REDUCE_BLOCKS = LAYER_ENTRIES / REDUCE_ENTRIES, REDUCE_WAVE_PARTS = 16;
+constexpr uint32_t REDUCE_SPLIT = 0x80000000u;  // in ReduceWg::block: the four waves share the block
+static_assert(REDUCE_BLOCKS * REDUCE_ENTRIES == LAYER_ENTRIES && REDUCE_BLOCKS % 4u == 0u, "four whole blocks to a workgroup");
+
+// Counts and sums of lanes' two entries e, e + 1 as the scans read them.
+__device__ __forceinline__ void reduce_store(const ProfileBuffers& pb, uint32_t big, uint32_t blk, uint32_t lane, const unsigned long long (&cnt)[2],
+                                             const unsigned long long (&t)[2], unsigned long long zeros_sq) {
+    const uint32_t e = blk * REDUCE_ENTRIES + 2u * lane;
+    const uint32_t slot_bin = blk < D1_BINS / REDUCE_ENTRIES ? 0u : pb.slot_bin[(size_t)big * SLOT_STRIDE + (blk - D1_BINS / REDUCE_ENTRIES)];
+    unsigned long long slot_sq = 0;               // this lane's share of the slot's total (blocks beyond the digit-1 bins)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const uint32_t eu = e + (uint32_t)u;
+        unsigned long long s2 = 0;
+        if (cnt[u]) {
+            const uint32_t bin = eu < D1_BINS ? eu : slot_bin;
+            if ((bin >> 4) == 255u) {
+                s2 = t[u];
+            } else if (eu == 0u) {
+                s2 = zeros_sq;
+            } else {
+                s2 = (t[u] << 8) + (cnt[u] << 7);
+            }
+        }
+        if (eu < D1_BINS) {
+            pb.cnt1[(size_t)big * D1_BINS + eu] = (uint32_t)cnt[u];
+            reinterpret_cast<unsigned long long*>(pb.sq1)[(size_t)big * D1_BINS + eu] = s2;
+        } else {
+            const size_t o = (size_t)big * SLOT_STRIDE * D2_BINS + (eu - D1_BINS);
+            pb.cnt2[o] = (uint32_t)cnt[u];
+            reinterpret_cast<unsigned long long*>(pb.sq2)[o] = s2;
+            slot_sq += s2;
+        }
+    }
+    // a block beyond the digit-1 bins holds exactly one slot: its totals, which stand for the slot's bin in the
+    // digit-1 histogram (the pass counts an entry of a slot bin in the slot only), go out with it
+    static_assert(REDUCE_ENTRIES == D2_BINS && D1_BINS % REDUCE_ENTRIES == 0, "one block per slot");
+    if (blk >= D1_BINS / REDUCE_ENTRIES) {
+        unsigned long long slot_cnt = cnt[0] + cnt[1];
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            slot_cnt += __shfl_xor(slot_cnt, d, 64);
+            slot_sq += __shfl_xor(slot_sq, d, 64);
+        }
+        if (lane == 0) {
+            const size_t o = (size_t)big * SLOT_STRIDE + (blk - D1_BINS / REDUCE_ENTRIES);
+            pb.slot_cnt[o] = (uint32_t)slot_cnt;
+            pb.slot_sq[o] = slot_sq;
+        }
+    }
+}
+
+// A packed slot block's entry: count and what is more than the common square (slot_square).
+__device__ __forceinline__ void reduce_packed(const uint2 v, unsigned long long (&c)[2], unsigned long long (&more)[2]) {
+    c[0] += v.x >> NARROW_SHIFT; more[0] += v.x & ((1u << NARROW_SHIFT) - 1u);
+    c[1] += v.y >> NARROW_SHIFT; more[1] += v.y & ((1u << NARROW_SHIFT) - 1u);
+}
+__device__ __forceinline__ void reduce_wide(const ulonglong2 v, unsigned long long (&cnt)[2], unsigned long long (&t)[2]) {
+    cnt[0] += v.x >> 44; t[0] += v.x & PK_MASK;
+    cnt[1] += v.y >> 44; t[1] += v.y & PK_MASK;
+}
+
 __global__ __launch_bounds__(256) void k_reduce_parts(ProfileBuffers pb) {
     __shared__ unsigned long long sh_c[3][REDUCE_ENTRIES], sh_t[3][REDUCE_ENTRIES];
     constexpr uint32_t LIST = 1024;
     __shared__ uint32_t list[LIST], listed[2];
-    const uint32_t big = blockIdx.y, lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
-    const uint32_t e = blockIdx.x * REDUCE_ENTRIES + 2u * lane;     // and e + 1; `used` is even
+    const uint32_t lane = threadIdx.x & 63u, w = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const ReduceWg wg = pb.reduce_wgs[blockIdx.x];
+    const uint32_t big = wg.big, p0 = wg.part0, np = wg.nparts;
     // The totals over the layers that the prediction of this profile read are done with (that launch has ended), and
     // the scan that follows this one adds the new ones up: cleared here, between the two.
-    if (blockIdx.x == 0u && big == 0u)
+    if (blockIdx.x == 0u)
         for (uint32_t b = threadIdx.x; b < D1_BINS; b += 256u) pb.gprev[b] = 0ull;
+    static_assert(REDUCE_ENTRIES == PART_BLOCK, "one block per block");
+    unsigned long long cnt[2] = {0, 0}, t[2] = {0, 0}, zeros_sq = 0;
+    if (!(wg.block & REDUCE_SPLIT)) {
+        const uint32_t blk = wg.block + w, word = 1u + blk / 32u;
+        const bool slot = blk >= D1_BINS / PART_BLOCK;
+        // lane k has part k's head, which block it holds how
+        const uint32_t* h = pb.part_head + (size_t)(p0 + min(lane, np - 1u)) * PART_HEAD;
+        const bool there = h[0] != 0u && lane < np, wide = (h[word] >> (blk % 32u)) & 1u;
+        const LayerState st = pb.state[big];
+        const bool any = blk < (D1_BINS + st.nslots_d * D2_BINS) / PART_BLOCK;
+        uint64_t wides = any ? ballot(there && wide) : 0ull, packed = any && slot ? ballot(there && !wide) : 0ull;
+        if (blk == 0u) {
+            if (there && wide && any) zeros_sq = pb.parts[(size_t)(p0 + lane) * PART_STRIDE + PK_ENTRIES];
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) zeros_sq += __shfl_xor(zeros_sq, d, 64);
+        }
+        constexpr int AT_ONCE = 8;
+        while (wides) {
+            ulonglong2 v[AT_ONCE];
+#pragma unroll
+            for (int u = 0; u < AT_ONCE; ++u) {
+                v[u] = make_ulonglong2(0ull, 0ull);
+                if (!wides) continue;
+                v[u] = *reinterpret_cast<const ulonglong2*>(pb.parts + (size_t)(p0 + (uint32_t)__builtin_ctzll(wides)) * PART_STRIDE + blk * PART_BLOCK + 2u * lane);
+                wides &= wides - 1ull;
+            }
+#pragma unroll
+            for (int u = 0; u < AT_ONCE; ++u) reduce_wide(v[u], cnt, t);
+        }
+        if (packed) {
+            unsigned long long c[2] = {0, 0}, more[2] = {0, 0};
+            while (packed) {
+                uint2 v[AT_ONCE];
+#pragma unroll
+                for (int u = 0; u < AT_ONCE; ++u) {
+                    v[u] = make_uint2(0u, 0u);
+                    if (!packed) continue;
+                    v[u] = *reinterpret_cast<const uint2*>(pb.parts + (size_t)(p0 + (uint32_t)__builtin_ctzll(packed)) * PART_STRIDE + blk * PART_BLOCK + lane);
+                    packed &= packed - 1ull;
+                }
+#pragma unroll
+                for (int u = 0; u < AT_ONCE; ++u) reduce_packed(v[u], c, more);
+            }
+            const uint32_t bin = slot_bin_of(st, blk - D1_BINS / PART_BLOCK);
+#pragma unroll
+            for (uint32_t u = 0; u < 2u; ++u) {
+                cnt[u] += c[u];
+                t[u] += more[u] + c[u] * slot_square(bin, 2u * lane + u);
+            }
+        }
+        reduce_store(pb, big, blk, lane, cnt, t, zeros_sq);
+        return;
+    }
+    const uint32_t blk = wg.block & ~REDUCE_SPLIT, word = 1u + blk / 32u;
+    const uint32_t e = blk * REDUCE_ENTRIES + 2u * lane;             // and e + 1
+    const bool slot = blk >= D1_BINS / PART_BLOCK;
     const LayerState st = pb.state[big];
     const uint32_t used = D1_BINS + st.nslots_d * D2_BINS;
-    const uint32_t p0 = pb.big_part0[big], np = pb.big_nparts[big];
-    unsigned long long cnt[2] = {0, 0}, t[2] = {0, 0}, zeros_sq = 0;
     // which of the layer's parts hold this block, LIST of them at a time: with 64 bits an entry from the list's start,
     // packed from its end
-    static_assert(REDUCE_ENTRIES == PART_BLOCK, "one workgroup per block");
-    const uint32_t blk = blockIdx.x, word = 1u + blk / 32u;
-    const bool slot = blk >= D1_BINS / PART_BLOCK;
     for (uint32_t q0 = 0; q0 < np && blk < used / PART_BLOCK; q0 += LIST) {
         __syncthreads();
         if (threadIdx.x < 2u) listed[threadIdx.x] = 0u;
@@ -844,17 +963,11 @@ __global__ __launch_bounds__(256) void k_reduce_parts(ProfileBuffers pb) {
             for (; k < count; k += 4) take(load(k));
         };
         each(n, [&](uint32_t k) { return *reinterpret_cast<const ulonglong2*>(pb.parts + (size_t)list[k] * PART_STRIDE + e); },
-             [&](const ulonglong2 v) {
-                 cnt[0] += v.x >> 44; t[0] += v.x & PK_MASK;
-                 cnt[1] += v.y >> 44; t[1] += v.y & PK_MASK;
-             });
+             [&](const ulonglong2 v) { reduce_wide(v, cnt, t); });
         if (m) {
             unsigned long long c[2] = {0, 0}, more[2] = {0, 0};
             each(m, [&](uint32_t k) { return *reinterpret_cast<const uint2*>(pb.parts + (size_t)list[LIST - 1u - k] * PART_STRIDE + blk * PART_BLOCK + lane); },
-                 [&](const uint2 v) {
-                     c[0] += v.x >> NARROW_SHIFT; more[0] += v.x & ((1u << NARROW_SHIFT) - 1u);
-                     c[1] += v.y >> NARROW_SHIFT; more[1] += v.y & ((1u << NARROW_SHIFT) - 1u);
-                 });
+                 [&](const uint2 v) { reduce_packed(v, c, more); });
             const uint32_t bin = slot_bin_of(st, blk - D1_BINS / PART_BLOCK);
 #pragma unroll
             for (uint32_t u = 0; u < 2u; ++u) {
@@ -870,53 +983,13 @@ __global__ __launch_bounds__(256) void k_reduce_parts(ProfileBuffers pb) {
         sh_t[w - 1][2 * lane] = t[0]; sh_t[w - 1][2 * lane + 1] = t[1];
     }
     __syncthreads();
-    if (w || e >= LAYER_ENTRIES) return;
+    if (w) return;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
         cnt[0] += sh_c[q][2 * lane]; cnt[1] += sh_c[q][2 * lane + 1];
         t[0] += sh_t[q][2 * lane]; t[1] += sh_t[q][2 * lane + 1];
     }
-    unsigned long long slot_sq = 0;               // this lane's share of the slot's total (blocks beyond the digit-1 bins)
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const uint32_t eu = e + (uint32_t)u;
-        unsigned long long s2 = 0;
-        if (cnt[u]) {
-            const uint32_t bin = eu < D1_BINS ? eu : pb.slot_bin[(size_t)big * SLOT_STRIDE + (eu - D1_BINS) / D2_BINS];
-            if ((bin >> 4) == 255u) {
-                s2 = t[u];
-            } else if (eu == 0u) {
-                s2 = zeros_sq;
-            } else {
-                s2 = (t[u] << 8) + (cnt[u] << 7);
-            }
-        }
-        if (eu < D1_BINS) {
-            pb.cnt1[(size_t)big * D1_BINS + eu] = (uint32_t)cnt[u];
-            reinterpret_cast<unsigned long long*>(pb.sq1)[(size_t)big * D1_BINS + eu] = s2;
-        } else {
-            const size_t o = (size_t)big * SLOT_STRIDE * D2_BINS + (eu - D1_BINS);
-            pb.cnt2[o] = (uint32_t)cnt[u];
-            reinterpret_cast<unsigned long long*>(pb.sq2)[o] = s2;
-            slot_sq += s2;
-        }
-    }
-    // a workgroup beyond the digit-1 bins holds exactly one slot: its totals, which stand for the slot's bin in the
-    // digit-1 histogram (the pass counts an entry of a slot bin in the slot only), go out with it
-    static_assert(REDUCE_ENTRIES == D2_BINS && D1_BINS % REDUCE_ENTRIES == 0, "one workgroup per slot");
-    if (blockIdx.x >= D1_BINS / REDUCE_ENTRIES) {
-        unsigned long long slot_cnt = cnt[0] + cnt[1];
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) {
-            slot_cnt += __shfl_xor(slot_cnt, d, 64);
-            slot_sq += __shfl_xor(slot_sq, d, 64);
-        }
-        if (lane == 0) {
-            const size_t o = (size_t)big * SLOT_STRIDE + (blockIdx.x - D1_BINS / REDUCE_ENTRIES);
-            pb.slot_cnt[o] = (uint32_t)slot_cnt;
-            pb.slot_sq[o] = slot_sq;
-        }
-    }
+    reduce_store(pb, big, blk, lane, cnt, t, zeros_sq);
 }
 
 // ---------------------------------------------------------------------------------------------

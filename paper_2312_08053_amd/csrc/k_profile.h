@@ -8,6 +8,9 @@
 
 namespace kimad {
 
+// A workgroup of k_reduce_parts: a layer's parts (there is room for one every PK_MAX_CHUNKS chunks), and its first block.
+struct ReduceWg { uint32_t big, block, part0, nparts; };
+
 struct ProfileBuffers {
     const LayerDesc* layers;
     const uint32_t* tile_layer;   // tile -> layer
@@ -59,8 +62,7 @@ struct ProfileBuffers {
     uint32_t* part_head;          // [nparts][PART_HEAD] whether there is one, and how its blocks were written
     unsigned long long* parts;    // [nparts][PART_STRIDE] the LDS entries, in blocks, then the exact bin-0 sum
     const uint32_t* wg_part0;     // [workgroups] first part of each workgroup (its parts follow in order)
-    const uint32_t* big_part0;    // [B] first part of each big layer (room for one every PK_MAX_CHUNKS chunks)
-    const uint32_t* big_nparts;   // [B]
+    const ReduceWg* reduce_wgs;   // what each workgroup of k_reduce_parts looks after
     const uint32_t* chunk_big;    // chunk -> big index
     const uint32_t* chunk_first;  // chunk -> first chunk of its layer
     uint32_t nchunks_total;

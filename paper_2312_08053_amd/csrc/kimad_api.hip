@@ -49,8 +49,8 @@ struct Layout {
     uint64_t fresh = 0, hprev = 0, gprev = 0;
     uint64_t zero1_begin, cnt1, sq1, cnt2, sq2, diag, layer_flag, shist, ghist, cursor, spill_over, zero1_end;
     uint64_t cprev = 0;
-    uint64_t big_tmp0, parts, part_head, wg_part0, big_part0, big_nparts, zero1_mid;
-    uint32_t main_wgs = 256, chunks_per_wg = 1, nparts = 0;
+    uint64_t big_tmp0, parts, part_head, wg_part0, reduce_wgs, zero1_mid;
+    uint32_t main_wgs = 256, chunks_per_wg = 1, nparts = 0, nreduce = 0;
     uint64_t pool_prefix, pool_big, pool_t0, pool_cnt, pool_hist, tgt_unsel, tgt_base;
     uint32_t pool_cap = 1;
     uint64_t lut1, nslots, slot_bin, slot_cnt, slot_sq;
@@ -121,22 +121,33 @@ uint32_t stream_workgroups(const kimad_config_t& cfg) {
 // histogram at every layer boundary and, where a count may fill up, no earlier than after PK_MAX_CHUNKS chunks.
 struct PartTables {
     std::vector<uint32_t> wg_part0, big_part0, big_nparts;
+    // the workgroups that sum the parts up: the layers whose blocks take a workgroup each first (they take longest)
+    std::vector<ReduceWg> reduce_wgs() const {
+        std::vector<ReduceWg> wgs;
+        for (int split = 1; split >= 0; --split)
+            for (uint32_t b = 0; b < big_nparts.size(); ++b) {
+                if ((big_nparts[b] > REDUCE_WAVE_PARTS) != (split != 0)) continue;
+                for (uint32_t k = 0; k < REDUCE_BLOCKS; k += split ? 1u : 4u)
+                    wgs.push_back({b, k | (split ? REDUCE_SPLIT : 0u), big_part0[b], big_nparts[b]});
+            }
+        return wgs;
+    }
 };
 uint32_t plan_parts(const std::vector<HostLayer>& hl, uint32_t B, uint32_t nchunks, uint32_t wgs, uint32_t per,
-                    PartTables* out) {
+                    PartTables& out) {
     std::vector<uint32_t> c0(B ? B : 1), c1(B ? B : 1);
     for (const HostLayer& h : hl)
         if (h.big >= 0) { c0[h.big] = h.chunk0; c1[h.big] = h.chunk0 + h.nchunks; }
-    if (out) { out->wg_part0.assign(wgs, 0); out->big_part0.assign(B ? B : 1, 0); out->big_nparts.assign(B ? B : 1, 0); }
+    out.wg_part0.assign(wgs, 0); out.big_part0.assign(B, 0); out.big_nparts.assign(B, 0);
     uint32_t part = 0, b = 0;
     for (uint32_t w = 0; w < wgs; ++w) {
         uint64_t cur = (uint64_t)w * per;
         const uint64_t c_end = std::min<uint64_t>(nchunks, cur + per);
-        if (out) out->wg_part0[w] = part;
+        out.wg_part0[w] = part;
         while (cur < c_end) {
             while (cur >= c1[b]) ++b;
             const uint64_t seg_end = std::min<uint64_t>(std::min<uint64_t>(c_end, c1[b]), cur + PK_MAX_CHUNKS);
-            if (out) { if (out->big_nparts[b]++ == 0) out->big_part0[b] = part; }
+            if (out.big_nparts[b]++ == 0) out.big_part0[b] = part;
             ++part;
             cur = seg_end;
         }
@@ -204,7 +215,10 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     // workgroups with at least 16 chunks each do less of that than one per compute unit would
     lo.main_wgs = std::max<uint32_t>(1, std::min<uint32_t>(stream_workgroups(cfg), (lo.nchunks + 15) / 16));
     lo.chunks_per_wg = std::max<uint32_t>(1, (lo.nchunks + lo.main_wgs - 1) / lo.main_wgs);
-    lo.nparts = plan_parts(*hl, B, lo.nchunks, lo.main_wgs, lo.chunks_per_wg, parts_out);
+    PartTables parts_local;
+    PartTables& parts = parts_out ? *parts_out : parts_local;
+    lo.nparts = plan_parts(*hl, B, lo.nchunks, lo.main_wgs, lo.chunks_per_wg, parts);
+    lo.nreduce = (uint32_t)parts.reduce_wgs().size();
 
     uint64_t off = 0;
     auto take = [&](uint64_t bytes) { uint64_t o = off; off = align_up(off + bytes); return o; };
@@ -217,8 +231,7 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     lo.big_layer = take(4ull * (B ? B : 1));
     lo.big_tmp0 = take(8ull * (B ? B : 1));
     lo.wg_part0 = take(4ull * lo.main_wgs);
-    lo.big_part0 = take(4ull * (B ? B : 1));
-    lo.big_nparts = take(4ull * (B ? B : 1));
+    lo.reduce_wgs = take(sizeof(ReduceWg) * (uint64_t)(lo.nreduce ? lo.nreduce : 1));
     // (the exact pass's pool of last-digit histograms lives in the same memory: the parts are dead once
     // k_reduce_parts has run, and a pool entry is cleared by the workgroup that takes it)
     lo.pool_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>((uint64_t)B * J, 1), POOL_LIMIT);
@@ -533,7 +546,7 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
     } else {
         KLAUNCH(p, s, "k_main", k_main<false>, dim3(p->main_wgs), dim3(FUSED_THREADS), p->pb, p->chunks_per_wg);
     }
-    KLAUNCH(p, s, "k_reduce_parts", k_reduce_parts, dim3((LAYER_ENTRIES + REDUCE_ENTRIES - 1) / REDUCE_ENTRIES, lo.B), dim3(256), p->pb);
+    KLAUNCH(p, s, "k_reduce_parts", k_reduce_parts, dim3(lo.nreduce), dim3(256), p->pb);
     if (err_table && !with_small) {
         rc = launch_small_profile(p, err_table, s, side);
         if (rc) return rc;
@@ -810,6 +823,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
         for (uint32_t j = 0; j < J; ++j) p->ktab[(size_t)i * J + j] = grid_size_K(ratios[j], h.n);
         p->kmax[i] = p->ktab[(size_t)i * J + J - 1];
     }
+    const std::vector<ReduceWg> reduce = pt.reduce_wgs();
     hipStream_t s = static_cast<hipStream_t>(stream);
     auto up = [&](uint64_t off, const void* src, size_t bytes) {
         return hipMemcpyAsync(p->ws + off, src, bytes, hipMemcpyHostToDevice, s) == hipSuccess;
@@ -821,8 +835,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
               up(lo.big_layer, big_layer.data(), 4ull * big_layer.size()) &&
               up(lo.big_tmp0, big_tmp0.data(), 8ull * big_tmp0.size()) &&
               up(lo.wg_part0, pt.wg_part0.data(), 4ull * pt.wg_part0.size()) &&
-              up(lo.big_part0, pt.big_part0.data(), 4ull * pt.big_part0.size()) &&
-              up(lo.big_nparts, pt.big_nparts.data(), 4ull * pt.big_nparts.size()) &&
+              (reduce.empty() || up(lo.reduce_wgs, reduce.data(), sizeof(ReduceWg) * reduce.size())) &&
               up(lo.small_layer, small_layer.data(), 4ull * small_layer.size()) &&
               up(lo.swg_layer, swg_layer.data(), 4ull * swg_layer.size()) &&
               up(lo.swg_first, swg_first.data(), 4ull * swg_first.size()) &&
@@ -853,7 +866,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
     pb.tgt_unsel = at<uint32_t>(p, lo.tgt_unsel); pb.tgt_base = at<double>(p, lo.tgt_base);
     pb.state = at<LayerState>(p, lo.state); pb.big_tmp0 = at<uint64_t>(p, lo.big_tmp0);
     pb.parts = at<unsigned long long>(p, lo.parts); pb.part_head = at<uint32_t>(p, lo.part_head); pb.wg_part0 = at<uint32_t>(p, lo.wg_part0);
-    pb.big_part0 = at<uint32_t>(p, lo.big_part0); pb.big_nparts = at<uint32_t>(p, lo.big_nparts);
+    pb.reduce_wgs = at<ReduceWg>(p, lo.reduce_wgs);
     pb.chunk_big = at<uint32_t>(p, lo.chunk_big); pb.chunk_first = at<uint32_t>(p, lo.chunk_first); pb.nchunks_total = lo.nchunks;
     pb.swg_layer = at<uint32_t>(p, lo.swg_layer); pb.swg_first = at<uint32_t>(p, lo.swg_first);
     pb.shist = at<uint32_t>(p, lo.shist); pb.ghist = at<unsigned long long>(p, lo.ghist);
