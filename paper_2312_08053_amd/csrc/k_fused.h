@@ -999,104 +999,85 @@ __global__ __launch_bounds__(256) void k_reduce_parts(ProfileBuffers pb) {
 //   - its bin is in the spilled range                     -> a slot PRE_SLOTS.. filled from the candidates
 //   - it is bin 0, and that holds zeros only              -> such a slot too, filled here: the count, in digit 2 = 0
 //   - neither (prediction missed), or slots run out       -> redo: exact slots, full recount
-__global__ __launch_bounds__(256) void k_scan1x(ProfileBuffers pb, const uint32_t* Ktab, uint32_t J) {
-    __shared__ uint32_t cnt[D1_BINS];
-    __shared__ uint32_t above[D1_BINS];
-    __shared__ double below[D1_BINS];
+// (Four bins a thread, in whole 16-byte reads and writes.  With sixteen bins each for 256 threads, the writes to LDS, a lane's
+// sixteen words apart from the next lane's, fell on four banks: 12 us on every named set, Llama's 15.5, now 8 and 11; an empty launch takes 4.5.)
+constexpr uint32_t SCAN1X_THREADS = 1024;
+static_assert(SCAN1X_THREADS * 4u == D1_BINS, "four bins a thread");
+__global__ __launch_bounds__(SCAN1X_THREADS) void k_scan1x(ProfileBuffers pb, const uint32_t* Ktab, uint32_t J) {
+    __shared__ __align__(16) uint32_t cnt[D1_BINS];
+    __shared__ __align__(16) uint32_t above[D1_BINS];
+    __shared__ __align__(16) double below[D1_BINS];
     __shared__ uint32_t su[16];
     __shared__ double sd[16];
     __shared__ uint32_t tbin[MAX_SLOTS];
-    __shared__ uint8_t lut[D1_BINS];
+    __shared__ __align__(16) uint8_t lut[D1_BINS];
     __shared__ uint32_t sh_redo, sh_zeros;
     __shared__ uint32_t slot_c[PRE_SLOTS];
     __shared__ unsigned long long slot_s[PRE_SLOTS];
-    const uint32_t tid = threadIdx.x, big = blockIdx.x;
+    const uint32_t tid = threadIdx.x, big = blockIdx.x, b0 = tid * 4u;
     const uint32_t li = pb.big_layer[big];
     const LayerDesc L = pb.layers[li];
     LayerState st = pb.state[big];
-    const uint32_t* gcnt = pb.cnt1 + (size_t)big * D1_BINS;
-    const uint64_t* gsq = pb.sq1 + (size_t)big * D1_BINS;
     uint8_t* glut = pb.lut1 + (size_t)big * D1_BINS;
     uint8_t* glutc = pb.lutc + (size_t)big * D1_BINS;
-    // this thread's sixteen digit-1 entries: asked for now, with the table and the slot totals below, so
-    // that the three groups of loads share one memory round trip instead of taking one per phase
-    uint4 craw[4];
-    ulonglong2 sraw[8];
-    {
-        const uint4* c4 = reinterpret_cast<const uint4*>(gcnt + tid * 16u);
-        const ulonglong2* s2 = reinterpret_cast<const ulonglong2*>(gsq + tid * 16u);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) craw[k] = c4[k];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) sraw[k] = s2[k];
-    }
-    {
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(glut);
-        uint32_t* dst = reinterpret_cast<uint32_t*>(lut);
-        for (uint32_t b = tid; b < D1_BINS / 4; b += 256) dst[b] = src[b];
-    }
+    // this thread's four digit-1 entries and their slots: asked for now, with the slot totals below, so that the groups of
+    // loads share one memory round trip instead of taking one per phase
+    const uint4 craw = *reinterpret_cast<const uint4*>(pb.cnt1 + (size_t)big * D1_BINS + b0);
+    const ulonglong2 s01 = *reinterpret_cast<const ulonglong2*>(pb.sq1 + (size_t)big * D1_BINS + b0);
+    const ulonglong2 s23 = *reinterpret_cast<const ulonglong2*>(pb.sq1 + (size_t)big * D1_BINS + b0 + 2u);
+    const uint32_t slots = *reinterpret_cast<const uint32_t*>(glut + b0);
+    const uint32_t K = tid < J ? Ktab[(size_t)li * J + tid] : 0u;
+    const bool spill_valid = pb.spill_over[big] == 0u;
+    *reinterpret_cast<uint32_t*>(lut + b0) = slots;
+    *reinterpret_cast<uint32_t*>(glutc + b0) = NO_SLOT * 0x01010101u;
     // totals of the slots the pass counted (k_reduce_parts summed them)
-    static_assert(PRE_SLOTS <= 256, "one thread per slot");
+    static_assert(PRE_SLOTS <= SCAN1X_THREADS, "one thread per slot");
     if (tid < st.nslots_d) {
         slot_c[tid] = pb.slot_cnt[(size_t)big * SLOT_STRIDE + tid];
         slot_s[tid] = pb.slot_sq[(size_t)big * SLOT_STRIDE + tid];
     }
     if (tid == 0) sh_redo = 0u;
     __syncthreads();
-    uint32_t c[16];
-    double s[16];
+    uint32_t c[4] = {craw.x, craw.y, craw.z, craw.w};
+    const unsigned long long sq[4] = {s01.x, s01.y, s23.x, s23.y};
+    double s[4];
     uint32_t csum = 0;
     double ssum = 0.0;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const uint32_t b = tid * 16u + k;
-        const uint32_t slot = lut[b];
-        const uint4 cq = craw[k >> 2];
-        uint32_t cc = (k & 3) == 0 ? cq.x : (k & 3) == 1 ? cq.y : (k & 3) == 2 ? cq.z : cq.w;
-        unsigned long long ss = (k & 1) ? sraw[k >> 1].y : sraw[k >> 1].x;
-        if (slot != NO_SLOT) { cc += slot_c[slot]; ss += slot_s[slot]; }
-        c[k] = cc;
-        s[k] = sq_to_double(b, ss, cc);
-        csum += cc;
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t slot = slots >> (8 * k) & 0xFFu;
+        unsigned long long ss = sq[k];
+        if (slot != NO_SLOT) { c[k] += slot_c[slot]; ss += slot_s[slot]; }
+        s[k] = sq_to_double(b0 + (uint32_t)k, ss, c[k]);
+        csum += c[k];
         ssum += s[k];
     }
     if (tid == 0) sh_zeros = s[0] == 0.0 ? 1u : 0u;       // (bin 0's sum is exact: 0 only if every entry there is zero)
-    {
-        // the exact histogram stays for the next profile's prediction, with its sum over the layers
-        uint4* hp = reinterpret_cast<uint4*>(pb.hprev + (size_t)big * D1_BINS + tid * 16u);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) hp[k] = make_uint4(c[4 * k], c[4 * k + 1], c[4 * k + 2], c[4 * k + 3]);
-    }
+    // the exact histogram stays for the next profile's prediction, with its sum over the layers
+    const uint4 counts = make_uint4(c[0], c[1], c[2], c[3]);
+    *reinterpret_cast<uint4*>(pb.hprev + (size_t)big * D1_BINS + b0) = counts;
+    *reinterpret_cast<uint4*>(cnt + b0) = counts;
     uint32_t ctot;
     const uint32_t cex = block_exclusive_scan<uint32_t>(csum, su, &ctot);
     const double sex = block_exclusive_scan<double>(ssum, sd, nullptr);
     {
-        uint32_t run_c = cex;
-        double run_s = sex;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const uint32_t b = tid * 16u + k;
-            cnt[b] = c[k];
-            below[b] = run_s;
-            run_c += c[k];
-            above[b] = ctot - run_c;
-            run_s += s[k];
-        }
+        const uint32_t a0 = ctot - cex - c[0], a1 = a0 - c[1], a2 = a1 - c[2];
+        *reinterpret_cast<uint4*>(above + b0) = make_uint4(a0, a1, a2, a2 - c[3]);
+        const double d1 = sex + s[0], d2 = d1 + s[1];
+        *reinterpret_cast<double2*>(below + b0) = make_double2(sex, d1);
+        *reinterpret_cast<double2*>(below + b0 + 2u) = make_double2(d2, d2 + s[2]);
     }
-    for (uint32_t b = tid; b < D1_BINS; b += 256) glutc[b] = (uint8_t)NO_SLOT;
     __syncthreads();
-    // the sum over the layers: neighbouring lanes add to neighbouring bins (a lane adding its own sixteen bins
-    // touched 64 cache lines per instruction, and the additions of all layers queue up on the same lines)
-    for (uint32_t b = tid; b < D1_BINS; b += 256) {
+    // the sum over the layers: neighbouring lanes add to neighbouring bins (a lane adding its own bins
+    // touched many cache lines per instruction, and the additions of all layers queue up on the same lines)
+    for (uint32_t b = tid; b < D1_BINS; b += SCAN1X_THREADS) {
         const uint32_t cb = cnt[b];
         if (cb) atomicAdd(&pb.gprev[b], (unsigned long long)cb);
     }
 
     const uint32_t spill_cnt = st.spill_bin >= D1_BINS ? 0u
                              : (st.spill_bin == 0u ? ctot : above[st.spill_bin - 1u]);
-    const bool spill_valid = pb.spill_over[big] == 0u;
     if (tid < J) {
-        const uint32_t K = Ktab[(size_t)li * J + tid];
         uint32_t bin = 0xFFFFFFFFu;
         if (K != 0u && K < L.n) {
             uint32_t lo = 0, hi = D1_BINS - 1;
@@ -1132,10 +1113,10 @@ __global__ __launch_bounds__(256) void k_scan1x(ProfileBuffers pb, const uint32_
     const bool redo = sh_redo != 0u;
     if (redo) {
         // exact slots for every boundary bin; their digit-2 counts are recounted by a full pass
-        for (uint32_t b = tid; b < D1_BINS; b += 256) glut[b] = (uint8_t)NO_SLOT;
+        *reinterpret_cast<uint32_t*>(glut + b0) = NO_SLOT * 0x01010101u;
         uint32_t* c2 = pb.cnt2 + (size_t)big * SLOT_STRIDE * D2_BINS;
         unsigned long long* s2 = reinterpret_cast<unsigned long long*>(pb.sq2) + (size_t)big * SLOT_STRIDE * D2_BINS;
-        for (uint32_t e = tid; e < PRE_SLOTS * D2_BINS; e += 256) { c2[e] = 0u; s2[e] = 0ull; }
+        for (uint32_t e = tid; e < PRE_SLOTS * D2_BINS; e += SCAN1X_THREADS) { c2[e] = 0u; s2[e] = 0ull; }
         __syncthreads();
     }
     if (tid < 64) {

@@ -551,7 +551,7 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
         rc = launch_small_profile(p, err_table, s, side);
         if (rc) return rc;
     }
-    KLAUNCH(p, s, "k_scan1x", k_scan1x, dim3(lo.B), dim3(256), p->pb, ktab, J);
+    KLAUNCH(p, s, "k_scan1x", k_scan1x, dim3(lo.B), dim3(SCAN1X_THREADS), p->pb, ktab, J);
     // a grid whose smallest ratio keeps a five-hundredth of a layer has no sparse slots (the two kernels' comments have both sides)
     if (err_table && p->ratio0 >= 1.0 / 512.0) {
         KLAUNCH(p, s, "k_hist2c", k_hist2c_dense, dim3((lo.nchunks + DENSE_CHUNKS - 1) / DENSE_CHUNKS), dim3(DENSE_THREADS), p->pb);
