@@ -202,7 +202,7 @@ def main() -> int:
         if n.startswith("k_dp"):
             stage_ms["allocate"] += v["ms_per_step"]
         elif n in ("k_sample", "k_predict", "k_main", "k_scan1x", "k_hist2c", "k_hist1", "k_scan1", "k_hist2",
-                   "k_scan2", "k_hist3p", "k_scan3p", "k_small_profile"):
+                   "k_hist3p", "k_small_profile"):
             stage_ms["profile"] += v["ms_per_step"]
         elif n != "k_zero16":
             stage_ms["compress"] += v["ms_per_step"]

@@ -293,7 +293,7 @@ __device__ __forceinline__ void predict(const ProfileBuffers& pb, uint32_t big, 
         const uint32_t per = (pb.nchunks_total + nbig - 1u) / nbig;
         const uint32_t c_lo = big * per, c_hi = min(pb.nchunks_total, c_lo + per);
         for (uint32_t c = c_lo + tid; c < c_hi; c += 256) pb.rec_cnt[c] = 0u;
-        if (tid == 0) { pb.layer_flag[big] = 0u; pb.cursor[big] = 0u; pb.spill_over[big] = 0u; }
+        if (tid == 0) { pb.layer_flag[big] = 0u; pb.cursor[big] = 0u; pb.spill_over[big] = 0u; pb.tiles_done[big] = 0u; }
         if (big == 0u && tid < 4u) pb.diag[tid] = 0u;
         if (big == 0u && tid == 4u) *pb.fresh = 0u;
     }

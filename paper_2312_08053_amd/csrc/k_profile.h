@@ -46,6 +46,7 @@ struct ProfileBuffers {
     uint32_t* fresh;              // 1 while the threshold cache and the candidates describe the current g - h:
                                   // set by the profile's last kernels, cleared by the compression
     // exact fallback for entries whose bound is not tight: last-digit histograms of their prefix bins
+    uint32_t* tiles_done;         // [B] tiles of a layer that a pass over its tiles is done with
     uint32_t* layer_flag;         // [B] layer has at least one pool entry
     uint32_t pool_cap;            // pool entries the plan holds: min(B * J, POOL_LIMIT)
     uint32_t* pool_prefix;        // [pool_cap]
@@ -85,7 +86,6 @@ struct ProfileBuffers {
 // more than POOL_LIMIT of them hold POOL_LIMIT, and a candidate that finds the pool full gets NaN
 // in the table (the allocation then reports a non-finite table instead of using a loose value).
 constexpr uint32_t POOL_LIMIT = 65536;          // 16 KB each: at most 1 GB
-constexpr uint32_t POOL_GRID = 256;             // workgroups of the exact scan (it normally finds nothing)
 constexpr uint32_t POOL_NONE = 0xFFFFFFFFu;
 
 // ---------------------------------------------------------------------------------------------
@@ -235,97 +235,6 @@ __global__ __launch_bounds__(256) void k_scan1(ProfileBuffers pb, const uint32_t
 }
 
 // ---------------------------------------------------------------------------------------------
-// Pass 2: digit-2 histograms (count + squares) of the entries that fall in a boundary bin.
-// Workgroups take groups of consecutive tiles in a grid-stride loop and add their tables to the layer's once per group:
-// on a small set, whose tiles are short, the additions of every tile's few thousand entries were nearly all of the pass
-// (ResNet-18 with 50 ratios, every layer: 154 us with a flush per 4096 elements, 36 us with one per 32768).
-// hist2_group_tiles says how long a group is.  `gate` (optional) points at a device word that is
-// zero when no layer needs this pass: the single-pass profile launches it as a fallback that
-// normally has nothing to do, with a small grid that leaves after one load, and with `coarse` set
-// so that the recount holds the same numbers the pass itself would have put into the slot.
-constexpr uint32_t HIST2_MAX_ELEMS = 32768;    // elements a workgroup may count before it flushes: the count field has 16 bits
-// As many tiles as the counts admit, but at least 256 groups, one a compute unit, where the set has the tiles for them.
-// (Groups of 32768 elements left a perceptron of 266 K elements nine workgroups: k_hist2 9 -> 22 us, a classic profile
-// 61 -> 80 us.  At least 512 or 1024 groups: ResNet-18 with every layer recounted 320 -> 337 or 358 us.)
-inline uint32_t hist2_group_tiles(uint32_t ntiles, uint32_t tile_elems) {
-    const uint32_t most = HIST2_MAX_ELEMS / tile_elems, share = ntiles / 256u;
-    return share < 1u ? 1u : share < most ? share : most;
-}
-__global__ __launch_bounds__(512) void k_hist2(ProfileBuffers pb, uint32_t ntiles, uint32_t group_tiles, const uint32_t* gate,
-                                               uint32_t coarse) {
-    __shared__ unsigned long long sub[MAX_SLOTS * D2_BINS];   // 64 KB
-    __shared__ unsigned long long sub0[D2_BINS];              // exact squares when the slot is bin 0
-    __shared__ uint8_t lut[D1_BINS];
-    const uint32_t tid = threadIdx.x;
-    if (gate && *gate == 0u) return;
-    for (uint32_t tile0 = blockIdx.x * group_tiles; tile0 < ntiles; tile0 += gridDim.x * group_tiles) {
-    uint32_t tile = tile0;
-    const uint32_t tile_end = min(ntiles, tile + group_tiles);
-    while (tile < tile_end) {
-    // the group's tiles of one layer
-    const uint32_t li = pb.tile_layer[tile];
-    const LayerDesc L = pb.layers[li];
-    const LayerState st = pb.state[L.big];
-    const uint32_t ns = st.nslots_d;
-    const uint32_t first = tile, last = min(tile_end, L.tile0 + L.ntiles);
-    tile = last;
-    if (!st.redo || ns == 0) continue;
-    {
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(pb.lut1 + (size_t)L.big * D1_BINS);
-        uint32_t* dst = reinterpret_cast<uint32_t*>(lut);
-        for (uint32_t b = tid; b < D1_BINS / 4; b += 512) dst[b] = src[b];
-    }
-    for (uint32_t b = tid; b < ns * D2_BINS; b += 512) sub[b] = 0ull;
-    if (tid < D2_BINS) sub0[tid] = 0ull;
-    __syncthreads();
-
-    const uint32_t vbase = (first - L.tile0) * pb.tile_elems;
-    const uint32_t iters = (last - first) * (pb.tile_elems / 2048u);
-    for (uint32_t it = 0; it < iters; it += 2) {
-        Quad q[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (it + u < iters) load_quad(L, vbase + (it + u) * 2048u + tid * 4u, q[u]);
-            else { q[u].key[0] = q[u].key[1] = q[u].key[2] = q[u].key[3] = KEY_INVALID; }
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t key = q[u].key[c];
-                if (key == KEY_INVALID) continue;
-                const uint32_t bin = key >> D1_SHIFT;
-                const uint32_t slot = lut[bin];
-                if (slot == NO_SLOT) continue;
-                const uint32_t d2 = (key >> D2_SHIFT) & (D2_BINS - 1);
-                if (bin != 0u) {
-                    atomicAdd(&sub[slot * D2_BINS + d2],
-                              CNT_ONE | (unsigned long long)(coarse ? sq_coarse(key) : sq_fixed(key)));
-                } else {
-                    atomicAdd(&sub[slot * D2_BINS + d2], CNT_ONE);
-                    if (key) atomicAdd(&sub0[d2], sq_exact(key));
-                }
-            }
-        }
-    }
-    __syncthreads();
-    uint32_t* cnt = pb.cnt2 + (size_t)L.big * SLOT_STRIDE * D2_BINS;
-    unsigned long long* sq = reinterpret_cast<unsigned long long*>(pb.sq2) + (size_t)L.big * SLOT_STRIDE * D2_BINS;
-    const uint32_t slot0 = lut[0];   // slot of bin 0, if it is a boundary bin
-    for (uint32_t b = tid; b < ns * D2_BINS; b += 512) {
-        const unsigned long long v = sub[b];
-        if (v) {
-            atomicAdd(&cnt[b], (uint32_t)(v >> 48));
-            const unsigned long long s = (b / D2_BINS == slot0) ? sub0[b % D2_BINS] : (v & SQ_MASK);
-            if (s) atomicAdd(&sq[b], s);
-        }
-    }
-    __syncthreads();                            // the next tiles reuse the LDS tables
-    }
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
 // Scan 2: per big layer and candidate, locate the boundary inside digit 2, assemble E_ij and
 // remember the 19-bit threshold prefix.  What is left undecided is how the `unsel` smallest of
 // the `m` entries sharing that prefix split the prefix bin's exact sum of squares Q; their
@@ -438,14 +347,15 @@ __device__ __forceinline__ void scan2_target(const ProfileBuffers& pb, const Sca
 // too wide are then grouped by prefix (equal prefixes are adjacent because K ascends) and each
 // group gets one pool entry for the exact last-digit pass.
 constexpr uint32_t SCAN2_THREADS = 1024;
-__global__ __launch_bounds__(SCAN2_THREADS) void k_scan2(ProfileBuffers pb, const uint32_t* Ktab, uint32_t J,
-                                                         double* err_table, double tol, double widen) {
+__device__ __forceinline__ void scan2(const ProfileBuffers& pb, uint32_t big, const uint32_t* Ktab, uint32_t J, double* err_table, double tol, double widen) {
     __shared__ uint32_t sh_prefix[KIMAD_MAX_J_CONST];
     __shared__ uint32_t sh_flag[KIMAD_MAX_J_CONST];
     __shared__ uint32_t sh_pool[KIMAD_MAX_J_CONST];     // pool entries this layer has taken
     __shared__ uint32_t sh_npool;
-    if (threadIdx.x == 0) sh_npool = 0u;
-    const uint32_t big = blockIdx.x;
+    if (threadIdx.x == 0) {
+        sh_npool = 0u;
+        pb.tiles_done[big] = 0u;                        // (for the exact pass; this layer's counts are complete)
+    }
     const uint32_t li = pb.big_layer[big];
     constexpr uint32_t WAVES = SCAN2_THREADS / 64, PER_WAVE = KIMAD_MAX_J_CONST / WAVES;
     static_assert(PER_WAVE * WAVES == KIMAD_MAX_J_CONST, "every wave looks after the same number of targets");
@@ -511,13 +421,210 @@ __global__ __launch_bounds__(SCAN2_THREADS) void k_scan2(ProfileBuffers pb, cons
         reinterpret_cast<uint4*>(pb.pool_hist + (size_t)sh_pool[k] * D3_BINS)[threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
 }
 
-// Exact fallback, pass: last-digit histogram of every pooled prefix bin.  One workgroup per tile;
-// tiles of layers without pool entries return at once.
-__global__ __launch_bounds__(256) void k_hist3p(ProfileBuffers pb, uint32_t ntiles) {
+// Waits until this wave's additions to memory are there for every compute unit (they are atomics of device scope, carried out
+// beyond the caches: a release fence would write the caches back for nothing).
+__device__ __forceinline__ void additions_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// ---------------------------------------------------------------------------------------------
+// Pass 2: digit-2 histograms (count + squares) of the entries that fall in a boundary bin.
+// Workgroups take groups of consecutive tiles in a grid-stride loop and add their tables to the layer's once per group:
+// on a small set, whose tiles are short, the additions of every tile's few thousand entries were nearly all of the pass
+// (ResNet-18 with 50 ratios, every layer: 154 us with a flush per 4096 elements, 36 us with one per 32768).
+// hist2_group_tiles says how long a group is.  `gate` (optional) points at a device word that is
+// zero when no layer needs this pass: the single-pass profile launches it as a fallback that
+// normally has nothing to do, with a small grid that leaves after one load, and with `coarse` set
+// so that the recount holds the same numbers the pass itself would have put into the slot.
+//
+// The scan of a layer's counts (scan2) belongs to the launch: the first `nbig` workgroups scan a layer each that has nothing to be
+// counted here, and the layers that have are scanned by the workgroup that adds the last of their tiles (tiles_done), so that no
+// workgroup waits for another.  (us of two launches, and of this one.  Nothing to count: ResNet-50 10.6 and 7.5, GPT-2-shaped
+// 14.6 and 11.5; a few layers to count: GPT-2-shaped in overlapped rounds 31 and 28, ResNet-18 with 50 ratios 38 and 40.  A
+// workgroup reports its layers' tiles when it is through with all of them: 44 for that last with a report after each.)
+constexpr uint32_t HIST2_MAX_ELEMS = 32768;    // elements a workgroup may count before it flushes: the count field has 16 bits
+// As many tiles as the counts admit, but at least 256 groups, one a compute unit, where the set has the tiles for them.
+// (Groups of 32768 elements left a perceptron of 266 K elements nine workgroups: k_hist2 9 -> 22 us, a classic profile
+// 61 -> 80 us.  At least 512 or 1024 groups: ResNet-18 with every layer recounted 320 -> 337 or 358 us.)
+inline uint32_t hist2_group_tiles(uint32_t ntiles, uint32_t tile_elems) {
+    const uint32_t most = HIST2_MAX_ELEMS / tile_elems, share = ntiles / 256u;
+    return share < 1u ? 1u : share < most ? share : most;
+}
+constexpr uint32_t HIST2_THREADS = SCAN2_THREADS;
+__global__ __launch_bounds__(HIST2_THREADS) void k_hist2(ProfileBuffers pb, uint32_t nbig, uint32_t ntiles, uint32_t group_tiles, const uint32_t* gate,
+                                                         uint32_t coarse, const uint32_t* Ktab, uint32_t J, double* err_table, double tol,
+                                                         double widen) {
+    __shared__ unsigned long long sub[MAX_SLOTS * D2_BINS];   // 64 KB
+    __shared__ unsigned long long sub0[D2_BINS];              // exact squares when the slot is bin 0
+    __shared__ uint8_t lut[D1_BINS];
+    constexpr uint32_t RUNS = 64;
+    __shared__ uint32_t run_big[RUNS], run_tiles[RUNS];       // tiles counted and not yet reported, by layer
+    __shared__ uint64_t sh_last;
+    const uint32_t tid = threadIdx.x;
+    uint32_t runs = 0u;
+    // the runs' tiles are done: the layers that have none left are scanned
+    auto report = [&]() {
+        additions_done();
+        __syncthreads();
+        if (tid < 64u) {
+            const uint32_t b = tid < runs ? run_big[tid] : 0u;
+            const bool last = tid < runs && atomicAdd(&pb.tiles_done[b], run_tiles[tid]) + run_tiles[tid] == pb.layers[pb.big_layer[b]].ntiles;
+            const uint64_t which = ballot(last);
+            if (tid == 0) sh_last = which;
+        }
+        __syncthreads();
+        uint64_t which = sh_last;
+        if (which) __threadfence();
+        while (which) {
+            scan2(pb, (uint32_t)__builtin_amdgcn_readfirstlane(run_big[__builtin_ctzll(which)]), Ktab, J, err_table, tol, widen);
+            __syncthreads();
+            which &= which - 1ull;
+        }
+        runs = 0u;
+    };
+    if (blockIdx.x < nbig) {
+        const LayerState st = pb.state[blockIdx.x];
+        if (!st.redo || st.nslots_d == 0u) scan2(pb, blockIdx.x, Ktab, J, err_table, tol, widen);
+        return;
+    }
+    if (gate && *gate == 0u) return;
+    for (uint32_t tile0 = (blockIdx.x - nbig) * group_tiles; tile0 < ntiles; tile0 += (gridDim.x - nbig) * group_tiles) {
+    uint32_t tile = tile0;
+    const uint32_t tile_end = min(ntiles, tile + group_tiles);
+    while (tile < tile_end) {
+    // the group's tiles of one layer
+    const uint32_t li = pb.tile_layer[tile];
+    const LayerDesc L = pb.layers[li];
+    const LayerState st = pb.state[L.big];
+    const uint32_t ns = st.nslots_d;
+    const uint32_t first = tile, last = min(tile_end, L.tile0 + L.ntiles);
+    tile = last;
+    if (!st.redo || ns == 0) continue;
+    {
+        const uint32_t* src = reinterpret_cast<const uint32_t*>(pb.lut1 + (size_t)L.big * D1_BINS);
+        uint32_t* dst = reinterpret_cast<uint32_t*>(lut);
+        for (uint32_t b = tid; b < D1_BINS / 4; b += HIST2_THREADS) dst[b] = src[b];
+    }
+    for (uint32_t b = tid; b < ns * D2_BINS; b += HIST2_THREADS) sub[b] = 0ull;
+    if (tid < D2_BINS) sub0[tid] = 0ull;
+    __syncthreads();
+
+    const uint32_t vend = (last - L.tile0) * pb.tile_elems;
+    constexpr uint32_t QUADS = 2;               // a thread's loads under way
+    for (uint32_t v = (first - L.tile0) * pb.tile_elems + tid * 4u; v < vend; v += 4u * QUADS * HIST2_THREADS) {
+        Quad q[QUADS];
+#pragma unroll
+        for (uint32_t u = 0; u < QUADS; ++u) {
+            if (v + u * 4u * HIST2_THREADS < vend) load_quad(L, v + u * 4u * HIST2_THREADS, q[u]);
+            else { q[u].key[0] = q[u].key[1] = q[u].key[2] = q[u].key[3] = KEY_INVALID; }
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < QUADS; ++u) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t key = q[u].key[c];
+                if (key == KEY_INVALID) continue;
+                const uint32_t bin = key >> D1_SHIFT;
+                const uint32_t slot = lut[bin];
+                if (slot == NO_SLOT) continue;
+                const uint32_t d2 = (key >> D2_SHIFT) & (D2_BINS - 1);
+                if (bin != 0u) {
+                    atomicAdd(&sub[slot * D2_BINS + d2],
+                              CNT_ONE | (unsigned long long)(coarse ? sq_coarse(key) : sq_fixed(key)));
+                } else {
+                    atomicAdd(&sub[slot * D2_BINS + d2], CNT_ONE);
+                    if (key) atomicAdd(&sub0[d2], sq_exact(key));
+                }
+            }
+        }
+    }
+    __syncthreads();
+    uint32_t* cnt = pb.cnt2 + (size_t)L.big * SLOT_STRIDE * D2_BINS;
+    unsigned long long* sq = reinterpret_cast<unsigned long long*>(pb.sq2) + (size_t)L.big * SLOT_STRIDE * D2_BINS;
+    const uint32_t slot0 = lut[0];   // slot of bin 0, if it is a boundary bin
+    for (uint32_t b = tid; b < ns * D2_BINS; b += HIST2_THREADS) {
+        const unsigned long long v = sub[b];
+        if (v) {
+            atomicAdd(&cnt[b], (uint32_t)(v >> 48));
+            const unsigned long long s = (b / D2_BINS == slot0) ? sub0[b % D2_BINS] : (v & SQ_MASK);
+            if (s) atomicAdd(&sq[b], s);
+        }
+    }
+    if (tid == 0) { run_big[runs] = (uint32_t)L.big; run_tiles[runs] = last - first; }
+    ++runs;
+    __syncthreads();                            // the next tiles reuse the LDS tables
+    if (runs == RUNS) report();
+    }
+    }
+    if (runs) report();
+}
+
+// Exact fallback, scan of a pool entry by 256 threads.  With the full key known, the squares of the
+// `unsel` smallest entries of the prefix bin are summed exactly in fp64, smallest first.
+__device__ __forceinline__ void scan_pool_entry(const ProfileBuffers& pb, uint32_t f, double* err_table) {
+    __shared__ uint32_t su[16];
+    __shared__ double sd[16];
+    __shared__ uint32_t cum[D3_BINS];      // entries in lower digits
+    __shared__ double sumsq[D3_BINS];      // their squares
+    const uint32_t tid = threadIdx.x;
+    __syncthreads();                            // the previous entry's readers are done with the tables
+    const uint32_t prefix = pb.pool_prefix[f];
+    const uint32_t* h = pb.pool_hist + (size_t)f * D3_BINS;
+    uint32_t c[16];
+    double s[16];
+    uint32_t csum = 0;
+    double ssum = 0.0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) c[k] = __hip_atomic_load(h + tid * 16u + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const uint32_t d3 = tid * 16u + k;
+        const double v = (double)__uint_as_float((prefix << D2_SHIFT) | d3);
+        s[k] = (double)c[k] * v * v;
+        csum += c[k];
+        ssum += s[k];
+    }
+    const uint32_t cex = block_exclusive_scan<uint32_t>(csum, su, nullptr);
+    const double sex = block_exclusive_scan<double>(ssum, sd, nullptr);
+    {
+        uint32_t rc = cex;
+        double rs = sex;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            cum[tid * 16u + k] = rc;
+            sumsq[tid * 16u + k] = rs;
+            rc += c[k];
+            rs += s[k];
+        }
+    }
+    __syncthreads();
+    const uint32_t t0 = pb.pool_t0[f], cnt = pb.pool_cnt[f];
+    for (uint32_t k = tid; k < cnt; k += 256) {
+        const uint32_t t = t0 + k;
+        const uint32_t unsel = pb.tgt_unsel[t];
+        double U = 0.0;
+        if (unsel) {
+            // largest digit d with cum[d] < unsel: digits below d are dropped whole
+            uint32_t lo = 0, hi = D3_BINS - 1;
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi + 1) >> 1;
+                if (cum[mid] < unsel) lo = mid; else hi = mid - 1;
+            }
+            const double v = (double)__uint_as_float((prefix << D2_SHIFT) | lo);
+            U = sumsq[lo] + (double)(unsel - cum[lo]) * v * v;
+        }
+        err_table[t] = pb.tgt_base[t] + U;
+        atomicAdd(&pb.diag[1], 1u);
+    }
+}
+
+// Exact fallback: last-digit histogram of every pooled prefix bin.  One workgroup per tile; tiles of layers without pool
+// entries return at once.  A layer's entries are scanned by the workgroup that counts the last of its tiles, so that no
+// workgroup waits for another.  (A launch of its own for the scans took 4.5 to 5.5 us where there was nothing to scan.)
+__global__ __launch_bounds__(256) void k_hist3p(ProfileBuffers pb, uint32_t ntiles, double* err_table, uint32_t mark_fresh) {
     __shared__ uint32_t pfx[KIMAD_MAX_J_CONST];   // a layer has at most J pooled prefixes
     __shared__ uint32_t pid[KIMAD_MAX_J_CONST];
-    __shared__ uint32_t npool;
+    __shared__ uint32_t npool, sh_last;
     const uint32_t tid = threadIdx.x;
+    if (blockIdx.x == 0 && tid == 0 && mark_fresh) *pb.fresh = 1u;     // the grid profile's last kernel on the caller's stream
     if (pb.diag[2] == 0u) return;               // no pool entries at all: the usual case
     for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const uint32_t li = pb.tile_layer[tile];
@@ -561,67 +668,13 @@ __global__ __launch_bounds__(256) void k_hist3p(ProfileBuffers pb, uint32_t ntil
             }
         }
     }
-    }
-}
-
-// Exact fallback, scan: one workgroup per pool entry.  With the full key known, the squares of the
-// `unsel` smallest entries of the prefix bin are summed exactly in fp64, smallest first.
-__global__ __launch_bounds__(256) void k_scan3p(ProfileBuffers pb, double* err_table, uint32_t mark_fresh) {
-    __shared__ uint32_t su[16];
-    __shared__ double sd[16];
-    __shared__ uint32_t cum[D3_BINS];      // entries in lower digits
-    __shared__ double sumsq[D3_BINS];      // their squares
-    const uint32_t tid = threadIdx.x;
-    const uint32_t total = min(pb.diag[2], pb.pool_cap);
-    if (blockIdx.x == 0 && tid == 0 && mark_fresh) *pb.fresh = 1u;     // the grid profile's last kernel on the caller's stream
-    for (uint32_t f = blockIdx.x; f < total; f += gridDim.x) {
-    __syncthreads();                            // the previous entry's readers are done with the tables
-    const uint32_t prefix = pb.pool_prefix[f];
-    const uint32_t* h = pb.pool_hist + (size_t)f * D3_BINS;
-    uint32_t c[16];
-    double s[16];
-    uint32_t csum = 0;
-    double ssum = 0.0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const uint32_t d3 = tid * 16u + k;
-        c[k] = h[d3];
-        const double v = (double)__uint_as_float((prefix << D2_SHIFT) | d3);
-        s[k] = (double)c[k] * v * v;
-        csum += c[k];
-        ssum += s[k];
-    }
-    const uint32_t cex = block_exclusive_scan<uint32_t>(csum, su, nullptr);
-    const double sex = block_exclusive_scan<double>(ssum, sd, nullptr);
-    {
-        uint32_t rc = cex;
-        double rs = sex;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            cum[tid * 16u + k] = rc;
-            sumsq[tid * 16u + k] = rs;
-            rc += c[k];
-            rs += s[k];
-        }
-    }
+    additions_done();                           // before the tile counts as done
     __syncthreads();
-    const uint32_t t0 = pb.pool_t0[f], cnt = pb.pool_cnt[f];
-    for (uint32_t k = tid; k < cnt; k += 256) {
-        const uint32_t t = t0 + k;
-        const uint32_t unsel = pb.tgt_unsel[t];
-        double U = 0.0;
-        if (unsel) {
-            // largest digit d with cum[d] < unsel: digits below d are dropped whole
-            uint32_t lo = 0, hi = D3_BINS - 1;
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi + 1) >> 1;
-                if (cum[mid] < unsel) lo = mid; else hi = mid - 1;
-            }
-            const double v = (double)__uint_as_float((prefix << D2_SHIFT) | lo);
-            U = sumsq[lo] + (double)(unsel - cum[lo]) * v * v;
-        }
-        err_table[t] = pb.tgt_base[t] + U;
-        atomicAdd(&pb.diag[1], 1u);
+    if (tid == 0) sh_last = atomicAdd(&pb.tiles_done[L.big], 1u) + 1u == L.ntiles ? 1u : 0u;
+    __syncthreads();
+    if (sh_last) {
+        __threadfence();
+        for (uint32_t k = 0; k < np; ++k) scan_pool_entry(pb, pid[k], err_table);
     }
     }
 }

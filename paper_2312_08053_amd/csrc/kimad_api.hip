@@ -47,7 +47,7 @@ struct Layout {
     // zeroed before every profile
     uint64_t swg_layer, swg_first, state, lutc;
     uint64_t fresh = 0, hprev = 0, gprev = 0;
-    uint64_t zero1_begin, cnt1, sq1, cnt2, sq2, diag, layer_flag, shist, ghist, cursor, spill_over, zero1_end;
+    uint64_t zero1_begin, cnt1, sq1, cnt2, sq2, diag, layer_flag, shist, ghist, cursor, spill_over, tiles_done, zero1_end;
     uint64_t cprev = 0;
     uint64_t big_tmp0, parts, part_head, wg_part0, reduce_wgs, zero1_mid;
     uint32_t main_wgs = 256, chunks_per_wg = 1, nparts = 0, nreduce = 0;
@@ -256,6 +256,7 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     lo.ghist = take(8ull * D1_BINS);
     lo.cursor = take(4ull * (B ? B : 1));
     lo.spill_over = take(4ull * (B ? B : 1));
+    lo.tiles_done = take(4ull * (B ? B : 1));
     lo.rec_cnt = take(4ull * (nc ? nc : 1));              // chunk records start out as "nothing spilled"
     lo.zero1_end = off;
     lo.hprev = take(4ull * B * D1_BINS);
@@ -345,6 +346,7 @@ constexpr uint32_t STREAM_CANDIDATES_CHUNKS = 524288;
 // 398.  The line is the selection's; the profile alone would go on sharing.
 constexpr uint32_t SMALL_BESIDE = 512;
 constexpr uint32_t FALLBACK_GRID = 1024;   // workgroups of a pass that usually has nothing to do
+constexpr uint32_t RECOUNT_GRID = 512;     // the same for k_hist2, of which two fit a compute unit
 // A selection from scratch takes the single pass from this many chunks in tiled layers on, if these hold this many each on
 // average; below, its four more launches and its tables per layer cost more than the two reads of g and h it saves.
 // A hundredth kept, single pass and two histogram passes with a compaction, us: 4 layers 81 and 71 at 1 M elements, 95 and
@@ -485,15 +487,10 @@ int run_select_passes(kimad_plan* p, const uint32_t* ktab_dev, uint32_t J, doubl
         KLAUNCH(p, s, "k_hist1", k_hist1, dim3(lo.ntiles), dim3(256), p->pb);
         KLAUNCH(p, s, "k_scan1", k_scan1, dim3(lo.B), dim3(256), p->pb, ktab_dev, J);
         const uint32_t group = hist2_group_tiles(lo.ntiles, lo.tile_elems);
-        KLAUNCH(p, s, "k_hist2", k_hist2, dim3((lo.ntiles + group - 1) / group), dim3(512), p->pb, lo.ntiles, group,
-                (const uint32_t*)nullptr, 0u);
-        KLAUNCH(p, s, "k_scan2", k_scan2, dim3(lo.B), dim3(SCAN2_THREADS), p->pb, ktab_dev, J, err_table, CERT_TOL, 0.0);
-        if (err_table) {
-            // exact last-digit pass for the entries scan 2 could not certify (usually none)
-            KLAUNCH(p, s, "k_hist3p", k_hist3p, dim3(lo.ntiles), dim3(256), p->pb, lo.ntiles);
-            KLAUNCH(p, s, "k_scan3p", k_scan3p, dim3(std::min(lo.pool_cap, POOL_GRID)), dim3(256), p->pb, err_table,
-                    mark_fresh);
-        }
+        KLAUNCH(p, s, "k_hist2", k_hist2, dim3(lo.B + (lo.ntiles + group - 1) / group), dim3(HIST2_THREADS), p->pb, lo.B, lo.ntiles, group,
+                (const uint32_t*)nullptr, 0u, ktab_dev, J, err_table, CERT_TOL, 0.0);
+        // exact last-digit pass for the entries scan 2 could not certify (usually none)
+        if (err_table) KLAUNCH(p, s, "k_hist3p", k_hist3p, dim3(lo.ntiles), dim3(256), p->pb, lo.ntiles, err_table, mark_fresh);
     }
     return KIMAD_OK;
 }
@@ -558,14 +555,12 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
     } else {
         KLAUNCH(p, s, "k_hist2c", k_hist2c, dim3((lo.nchunks + 256u / SUB_HIST - 1) / (256u / SUB_HIST)), dim3(256), p->pb);
     }
-    // fallbacks that normally find nothing to do: small grids
+    // the scan of every layer's slots, and a recount of the layers marked redo: a small grid, since there are none as a rule
     const uint32_t group = hist2_group_tiles(lo.ntiles, lo.tile_elems);
-    KLAUNCH(p, s, "k_hist2", k_hist2, dim3(std::min<uint32_t>((lo.ntiles + group - 1) / group, FALLBACK_GRID)), dim3(512), p->pb,
-            lo.ntiles, group, (const uint32_t*)(at<uint32_t>(p, lo.diag) + 3), 1u);   // layers marked redo only
-    KLAUNCH(p, s, "k_scan2", k_scan2, dim3(lo.B), dim3(SCAN2_THREADS), p->pb, ktab, J, err_table, CERT_TOL, SLOT_WIDEN);
+    KLAUNCH(p, s, "k_hist2", k_hist2, dim3(lo.B + std::min<uint32_t>((lo.ntiles + group - 1) / group, RECOUNT_GRID)), dim3(HIST2_THREADS), p->pb,
+            lo.B, lo.ntiles, group, (const uint32_t*)(at<uint32_t>(p, lo.diag) + 3), 1u, ktab, J, err_table, CERT_TOL, SLOT_WIDEN);
     if (!err_table) return KIMAD_OK;
-    KLAUNCH(p, s, "k_hist3p", k_hist3p, dim3(std::min<uint32_t>(lo.ntiles, FALLBACK_GRID)), dim3(256), p->pb, lo.ntiles);
-    KLAUNCH(p, s, "k_scan3p", k_scan3p, dim3(std::min(lo.pool_cap, POOL_GRID)), dim3(256), p->pb, err_table, 1u);
+    KLAUNCH(p, s, "k_hist3p", k_hist3p, dim3(std::min<uint32_t>(lo.ntiles, FALLBACK_GRID)), dim3(256), p->pb, lo.ntiles, err_table, 1u);
     return KIMAD_OK;
 }
 
@@ -860,6 +855,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
     pb.fresh = at<uint32_t>(p, lo.fresh);
     pb.hprev = at<uint32_t>(p, lo.hprev); pb.gprev = at<unsigned long long>(p, lo.gprev);
     pb.layer_flag = at<uint32_t>(p, lo.layer_flag);
+    pb.tiles_done = at<uint32_t>(p, lo.tiles_done);
     pb.pool_prefix = at<uint32_t>(p, lo.pool_prefix); pb.pool_big = at<uint32_t>(p, lo.pool_big);
     pb.pool_t0 = at<uint32_t>(p, lo.pool_t0); pb.pool_cnt = at<uint32_t>(p, lo.pool_cnt);
     pb.pool_hist = at<uint32_t>(p, lo.pool_hist); pb.pool_cap = lo.pool_cap;
