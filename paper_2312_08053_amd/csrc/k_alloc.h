@@ -7,6 +7,7 @@
 // reproducible bit for bit.
 #pragma once
 #include "common.h"
+#include "k_compress.h"
 
 namespace kimad {
 
@@ -318,7 +319,7 @@ constexpr uint32_t DP_WALK_MAX_L = 4224;           // layers whose path cells k_
                                                    // cell, so a feasible path through rows of at most 4224 cells has no more layers
 
 __global__ __launch_bounds__(1024) void k_dp_walk(AllocBuffers ab, const double* __restrict__ last, const uint32_t* __restrict__ bad,
-                                                  int32_t err_infeasible, int32_t err_nonfinite, int32_t err_internal) {
+                                                  int32_t err_infeasible, int32_t err_nonfinite, int32_t err_internal, StepLookup sl) {
     __shared__ __attribute__((aligned(16))) uint8_t stage[DP_STAGE_BYTES];
     __shared__ uint16_t s_cell[DP_WALK_MAX_L];     // the path's cell per piece (a store to memory in the chain would be waited for)
     __shared__ double sv[16];
@@ -391,6 +392,7 @@ __global__ __launch_bounds__(1024) void k_dp_walk(AllocBuffers ab, const double*
     if (st != 0) {
         for (uint32_t i = tid; i < ab.L; i += 1024) { ab.j_out[i] = 0; ab.K_out[i] = 0; }
         for (uint32_t i = tid; i <= ab.L; i += 1024) ab.offsets_out[i] = 0;
+        step_lookup(sl, 1024u);
         return;
     }
     for (;;) {
@@ -427,12 +429,13 @@ __global__ __launch_bounds__(1024) void k_dp_walk(AllocBuffers ab, const double*
         carry += tot;
     }
     if (tid == 0) ab.offsets_out[ab.L] = carry;
+    step_lookup(sl, 1024u);
 }
 
 // Smallest cost attaining the least total, back-tracking, outputs.  One workgroup.
 // `bad` (not null): per layer, whether its table row holds an Inf or a NaN; else flags[0] says it of the table.
 __global__ __launch_bounds__(1024) void k_dp_final(AllocBuffers ab, const double* last, const uint32_t* __restrict__ bad,
-                                                   int32_t err_infeasible, int32_t err_nonfinite, int32_t err_internal) {
+                                                   int32_t err_infeasible, int32_t err_nonfinite, int32_t err_internal, StepLookup sl) {
     __shared__ double sv[16];
     __shared__ unsigned long long sc[16];
     __shared__ unsigned long long cstar;
@@ -481,6 +484,7 @@ __global__ __launch_bounds__(1024) void k_dp_final(AllocBuffers ab, const double
     if (st != 0) {
         for (uint32_t i = tid; i < ab.L; i += 1024) { ab.j_out[i] = 0; ab.K_out[i] = 0; }
         for (uint32_t i = tid; i <= ab.L; i += 1024) ab.offsets_out[i] = 0;
+        step_lookup(sl, 1024u);
         return;
     }
     // Back-tracking, two layers per memory round trip: with the cell's own choice, lane j asks for the layer before's
@@ -532,6 +536,7 @@ __global__ __launch_bounds__(1024) void k_dp_final(AllocBuffers ab, const double
         carry += tot;
     }
     if (tid == 0) ab.offsets_out[ab.L] = carry;
+    step_lookup(sl, 1024u);
 }
 
 }  // namespace kimad

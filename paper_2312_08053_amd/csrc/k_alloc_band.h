@@ -488,7 +488,7 @@ __device__ __forceinline__ double band_records(uint32_t neg_cost, double err, do
 }
 
 __global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, DpLists dl, BandBuffers bb, double* rows_g,
-                                                              uint32_t rstride, int32_t err_infeasible, int32_t err_nonfinite) {
+                                                              uint32_t rstride, int32_t err_infeasible, int32_t err_nonfinite, StepLookup sl) {
     constexpr uint32_t MAX_WAVES = BANDED_THREADS / 64;
     __shared__ double rows[BAND_CELLS];
     __shared__ uint4 recs[BAND_LIVE_CAP];                 // error bits, cost
@@ -654,6 +654,7 @@ __global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, D
     if (st != 0) {                                         // (the same in every thread)
         for (uint32_t i = tid; i < L; i += T) { ab.j_out[i] = 0; ab.K_out[i] = 0; }
         for (uint32_t i = tid; i <= L; i += T) ab.offsets_out[i] = 0;
+        step_lookup(sl, T);
         return;
     }
     // ---- the walk back, in groups of layers whose records, and staged rows, fit LDS
@@ -735,6 +736,7 @@ __global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, D
         carry += total;
     }
     if (tid == 0) ab.offsets_out[L] = carry;
+    step_lookup(sl, T);
 }
 
 }  // namespace kimad

@@ -83,34 +83,42 @@ __device__ __forceinline__ float emit_value(const CompressBuffers& cb, uint64_t 
 
 // ---------------------------------------------------------------------------------------------
 // Per layer: turn K[i] into a selection record using the profile's threshold cache.
-// One workgroup; thread b handles big layer b (looping).  `reuse`: the thresholds are those of an earlier profile;
-// `use_candidates`: a single pass over g and h (that profile's, or this call's own) has left candidates.
-__global__ __launch_bounds__(256) void k_lookup(CompressBuffers cb, int32_t err_offgrid, int32_t err_offsets,
-                                                int32_t err_stale, uint32_t reuse, uint32_t use_candidates) {
+// One workgroup, of whose threads the first `threads` are there; thread b handles big layer b (looping).  `reuse`: the
+// thresholds are those of an earlier profile; `use_candidates`: a single pass over g and h (that profile's, or this call's own)
+// has left candidates.  In kimad_step the allocation's last kernel does this with the sizes that it has just written (after a
+// barrier that waits for them), and hands over which grid sizes they are, which a launch of its own has to search for.
+// (Walk and look-up, us: two launches 15.0 on the GPT-2-shaped set and 14.9 on ResNet-50, one 13.0 and 13.2; Llama-shaped 20
+// and 17.)
+// `j` (not null): the grid size that every layer's K is.
+__device__ __forceinline__ void lookup(const CompressBuffers& cb, uint32_t threads, int32_t err_offgrid, int32_t err_offsets, int32_t err_stale,
+                                       uint32_t reuse, uint32_t use_candidates, const int32_t* j) {
     __shared__ int bad;
     __shared__ uint32_t need_pass, n_direct;
     const uint32_t tid = threadIdx.x;
     // Thresholds may be reused only if a profile wrote them for the g - h that is there now: the compression
     // itself changes h, so a second call without a new profile in between is refused (status err_stale).
     const bool stale = reuse && *cb.fresh != 1u;
+    const uint32_t my_layer = tid < cb.B ? cb.big_layer[tid] : 0u;           // (asked for ahead of the barriers)
     if (tid == 0) { bad = stale ? 3 : 0; need_pass = 0u; n_direct = 0u; }
     __syncthreads();
     // validate offsets / K for every layer
-    for (uint32_t i = tid; i < cb.L; i += 256) {
+    for (uint32_t i = tid; i < cb.L; i += threads) {
         const uint64_t K = cb.K[i], off = cb.offsets[i];
         if (K > cb.layers[i].n || off > cb.capacity_pairs || K > cb.capacity_pairs - off) atomicMax(&bad, 1);
     }
     __syncthreads();
     const bool offsets_bad = bad == 1;
     __syncthreads();
-    for (uint32_t b = tid; b < cb.B; b += 256) {
+    for (uint32_t b = tid; b < cb.B; b += threads) {
         SelRec r;
         r.mode = SEL_NONE; r.prefix = 0; r.above = 0; r.amb = 0; r.cap = 0; r.K = 0;
-        const uint32_t li = cb.big_layer[b];
-        const uint32_t n = cb.layers[li].n;
-        r.tmp_base = cb.layers[li].tmp0;
-        r.h = cb.layers[li].h;
-        r.mis = cb.layers[li].mis;
+        const uint32_t li = b == tid ? my_layer : cb.big_layer[b];
+        const LayerDesc ld = cb.layers[li];
+        const LayerState st = cb.state[b];
+        const uint32_t n = ld.n;
+        r.tmp_base = ld.tmp0;
+        r.h = ld.h;
+        r.mis = ld.mis;
         r.dst = cb.offsets[li];
         if (!offsets_bad && !stale) {
             const uint32_t K = (uint32_t)cb.K[li];
@@ -123,6 +131,10 @@ __global__ __launch_bounds__(256) void k_lookup(CompressBuffers cb, int32_t err_
                 // the row of grid sizes is read eight entries at a time (a look-up that stops at the
                 // first hit would wait for one load per entry)
                 int found = -1;
+                if (j) {
+                    const uint32_t t = min((uint32_t)j[li], cb.J - 1u);
+                    if (cb.Ktab[(size_t)li * cb.J + t] == K) found = (int)t;
+                }
                 for (uint32_t j0 = 0; j0 < cb.J && found < 0; j0 += 8) {
                     uint32_t kt[8];
 #pragma unroll
@@ -138,8 +150,7 @@ __global__ __launch_bounds__(256) void k_lookup(CompressBuffers cb, int32_t err_
                     r.prefix = cb.sel_prefix[t];
                     r.above = cb.sel_above[t];
                     r.amb = cb.sel_amb[t];
-                    r.cap = cb.layers[li].tmp_cap;
-                    const LayerState st = cb.state[b];
+                    r.cap = ld.tmp_cap;
                     // every entry at or above the threshold prefix already sits in the candidate buffer
                     const bool in_spill = use_candidates && st.spill_valid && st.spill_bin < D1_BINS &&
                                           r.prefix >= (st.spill_bin << D2_BITS);
@@ -147,7 +158,7 @@ __global__ __launch_bounds__(256) void k_lookup(CompressBuffers cb, int32_t err_
                     // waves reserve space in blocks and leave a block's tail unused when the next chunk does not
                     // fit (less than the chunk needs, so at most as much again), and every wave its last block
                     // of a tile.  What would not fit is served from g and h directly.
-                    const uint64_t need = 2ull * ((uint64_t)r.above + r.amb) + 4ull * SPILL_BLOCK * cb.layers[li].ntiles;
+                    const uint64_t need = 2ull * ((uint64_t)r.above + r.amb) + 4ull * SPILL_BLOCK * ld.ntiles;
                     r.mode = in_spill ? SEL_CAND : need <= r.cap ? SEL_PREFIX : SEL_DIRECT;
                 }
             }
@@ -162,7 +173,7 @@ __global__ __launch_bounds__(256) void k_lookup(CompressBuffers cb, int32_t err_
     if (tid == 0) { cb.ncompact[0] = bad ? 0u : need_pass; cb.ncompact[1] = bad ? 0u : n_direct; }
     if (bad) {
         // refuse the whole call: nothing is written by the later kernels
-        for (uint32_t b = tid; b < cb.B; b += 256) { cb.sel[b].mode = SEL_NONE; cb.sel[b].cap = 0; cb.sel[b].K = 0; }
+        for (uint32_t b = tid; b < cb.B; b += threads) { cb.sel[b].mode = SEL_NONE; cb.sel[b].cap = 0; cb.sel[b].K = 0; }
         if (tid == 0) *cb.status = stale ? err_stale : offsets_bad ? err_offsets : err_offgrid;
     } else if (tid == 0) {
         *cb.status = 0;
@@ -170,6 +181,24 @@ __global__ __launch_bounds__(256) void k_lookup(CompressBuffers cb, int32_t err_
     // From here on the cache no longer describes g - h (the estimator is about to change, or a selection from
     // scratch has overwritten the cache); a refused call that reuses the profile leaves both as they were.
     if (tid == 0 && (!reuse || !bad)) *cb.fresh = 0u;
+}
+
+__global__ __launch_bounds__(256) void k_lookup(CompressBuffers cb, int32_t err_offgrid, int32_t err_offsets,
+                                                int32_t err_stale, uint32_t reuse, uint32_t use_candidates) {
+    lookup(cb, 256u, err_offgrid, err_offsets, err_stale, reuse, use_candidates, nullptr);
+}
+
+// What the allocation's last kernel looks up in kimad_step (on: 0 elsewhere).
+struct StepLookup {
+    CompressBuffers cb;
+    const int32_t* j;
+    int32_t err_offgrid, err_offsets, err_stale;
+    uint32_t on;
+};
+__device__ __forceinline__ void step_lookup(const StepLookup& sl, uint32_t threads) {
+    if (!sl.on) return;
+    __syncthreads();                                     // the sizes and offsets are there
+    lookup(sl.cb, threads, sl.err_offgrid, sl.err_offsets, sl.err_stale, 1u, 1u, sl.j);
 }
 
 // A value that is the same in every lane, in scalar registers.

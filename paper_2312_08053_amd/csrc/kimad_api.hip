@@ -640,7 +640,7 @@ AllocScratch plan_scratch(kimad_plan* p) {
 
 int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_table, uint64_t budget_bytes,
                      int32_t* j_out, uint64_t* K_out, uint64_t* offsets_out, int32_t* status_out, hipStream_t s,
-                     uint32_t polls = CHAIN_POLLS, uint32_t first_ticket = 0u) {
+                     uint32_t polls = CHAIN_POLLS, uint32_t first_ticket = 0u, const StepLookup& sl = StepLookup{}) {
     const Layout& lo = p->lo;
     const uint64_t P = budget_bytes / p->cfg.pair_bytes;
     const uint64_t unit = cost_unit(p->cfg, P);
@@ -688,7 +688,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
             bb.table = rows_g;                    // (a stored row has at least BAND_NLAM cells)
             KLAUNCH(p, s, "k_dp_bounds", k_dp_bounds, dim3(1), dim3(BOUNDS_THREADS), ab, dl, bb);
             KLAUNCH(p, s, "k_dp_banded", k_dp_banded, dim3(1), dim3(BANDED_THREADS), ab, dl, bb, rows_g, rstride,
-                    (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE);
+                    (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, sl);
             return KIMAD_OK;
         }
         // (keepers of 16 cells a compute wave, then a workgroup per piece of the layers)
@@ -698,7 +698,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
             const uint32_t others = pieces.fours + pieces.ones * (uint32_t)(cap / BLOCK_CELLS + 1);
             KLAUNCH(p, s, "k_dp_chain", kern, dim3(keepers + others), dim3(threads), ab, dl, rows_g, rstride, keepers);
             KLAUNCH(p, s, "k_dp_walk", k_dp_walk, dim3(1), dim3(1024), ab, (const double*)(rows_g + (size_t)lo.L * rstride),
-                    (const uint32_t*)dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL);
+                    (const uint32_t*)dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL, sl);
             return KIMAD_OK;
         };
         if (cap + 1 <= 1024 && lo.L > CHAIN_NARROW_L) return chain(k_dp_chain<1024, 4, 2>, 64, chain_threads(4, 2));
@@ -719,7 +719,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
             KLAUNCH(p, s, "k_dp_chain", k_dp_chain_long<4>, waves, dim3(CHAIN_LONG_NT), ab, wall, ws.rows_g, pitch);
         }
         KLAUNCH(p, s, "k_dp_final", k_dp_final, dim3(1), dim3(1024), ab, (const double*)(ws.rows_g + (uint64_t)lo.L * pitch + CHAIN_PAD),
-                (const uint32_t*)ws.dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL);
+                (const uint32_t*)ws.dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL, sl);
     } else {
         const uint32_t cell_blocks = (uint32_t)((cap + 1 + 255) / 256);
         // (clears with a kernel, not hipMemsetAsync: the call may be recorded into a graph)
@@ -730,9 +730,45 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
             KLAUNCH(p, s, "k_dp_layer", k_dp_layer, dim3(cell_blocks), dim3(256), ab, i, rows[i & 1], rows[(i + 1) & 1]);
         }
         KLAUNCH(p, s, "k_dp_final", k_dp_final, dim3(1), dim3(1024), ab, (const double*)rows[lo.L & 1], (const uint32_t*)nullptr,
-                (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL);
+                (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL, sl);
     }
     return KIMAD_OK;
+}
+
+// The plan's compression buffers with a call's arguments.
+CompressBuffers compress_buffers(kimad_plan* p, const uint64_t* K, const uint64_t* offsets, uint32_t* idx_out, void* val_out,
+                                 uint64_t capacity_pairs, int32_t* status_out) {
+    CompressBuffers cb = p->cb;
+    cb.K = K; cb.offsets = offsets; cb.idx_out = idx_out; cb.val_out = static_cast<float*>(val_out);
+    cb.value_f16 = p->cfg.value_format == KIMAD_VALUES_F16 ? 1u : 0u;
+    cb.capacity_pairs = capacity_pairs; cb.status = status_out;
+    return cb;
+}
+
+// The compression's kernels behind the look-up.
+int enqueue_compress(kimad_plan* p, const CompressBuffers& cb, hipStream_t s) {
+    const Layout& lo = p->lo;
+    hipStream_t ss = s;
+    const bool with_bases = lo.B && lo.S <= SMALL_BESIDE;
+    if (lo.S && !with_bases) {
+        ss = fork_side(p, s);                 // after the lookup: the small layers read its verdict
+        KLAUNCH(p, ss, "k_small_compress", k_small_compress, dim3(lo.S), dim3(SMALL_THREADS), cb);
+    }
+    if (lo.B) {
+        const uint32_t* chunk_big = at<uint32_t>(p, lo.chunk_big);
+        const uint32_t cblocks = (lo.nchunks + CHUNKS_PER_WG - 1) / CHUNKS_PER_WG;
+        const uint32_t nblocks = (lo.nchunks + 256u / SUB_COUNT - 1) / (256u / SUB_COUNT);   // where candidates are only counted
+        const uint32_t hblocks = (lo.nchunks + 256u / SUB_HIST - 1) / (256u / SUB_HIST);      // and where they are histogrammed
+        KLAUNCH(p, s, "k_candidates", k_candidates, dim3(hblocks + std::min<uint32_t>(lo.ntiles, 4u * FALLBACK_GRID)), dim3(256), cb,
+                lo.nchunks, chunk_big, hblocks, lo.ntiles, (int32_t)KIMAD_ERR_INTERNAL);
+        KLAUNCH(p, s, "k_resolve", k_resolve, dim3(lo.B), dim3(256), cb);
+        // (the workgroups behind the candidates' leave after one load when no layer is served from g and h throughout)
+        const uint32_t dblocks = std::min<uint32_t>(lo.ntiles, FALLBACK_GRID);
+        KLAUNCH(p, s, "k_chunk_count", k_chunk_count, dim3(nblocks + dblocks), dim3(256), cb, lo.nchunks, chunk_big, nblocks, lo.ntiles);
+        KLAUNCH(p, s, "k_chunk_bases", k_chunk_bases, dim3(lo.ncblk + (with_bases ? lo.S : 0u)), dim3(SMALL_THREADS), cb, lo.ncblk);
+        KLAUNCH(p, s, "k_finalize", k_finalize, dim3(cblocks + dblocks), dim3(256), cb, lo.nchunks, chunk_big, cblocks, lo.ntiles);
+    }
+    return join_side(p, s, ss);
 }
 
 }  // namespace
@@ -999,10 +1035,7 @@ int kimad_compress_ef(kimad_plan_t* p, const uint64_t* K, const uint64_t* offset
     if (flags & ~KIMAD_REUSE_PROFILE) return KIMAD_ERR_INVALID_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Layout& lo = p->lo;
-    CompressBuffers cb = p->cb;
-    cb.K = K; cb.offsets = offsets; cb.idx_out = idx_out; cb.val_out = static_cast<float*>(val_out);
-    cb.value_f16 = p->cfg.value_format == KIMAD_VALUES_F16 ? 1u : 0u;
-    cb.capacity_pairs = capacity_pairs; cb.status = status_out;
+    CompressBuffers cb = compress_buffers(p, K, offsets, idx_out, val_out, capacity_pairs, status_out);
     mark(p, s, "begin");
     const bool reuse = (flags & KIMAD_REUSE_PROFILE) != 0;
     const bool single = !(p->cfg.flags & KIMAD_CFG_CLASSIC_PROFILE) && lo.nchunks >= SINGLE_SELECT_CHUNKS &&
@@ -1022,27 +1055,7 @@ int kimad_compress_ef(kimad_plan_t* p, const uint64_t* K, const uint64_t* offset
     KLAUNCH(p, s, "k_lookup", k_lookup, dim3(1), dim3(256), cb, (int32_t)KIMAD_ERR_OFFGRID,
             (int32_t)KIMAD_ERR_BAD_OFFSETS, (int32_t)KIMAD_ERR_STALE_PROFILE,
             (uint32_t)(reuse ? 1u : 0u), (uint32_t)(reuse || single ? 1u : 0u));
-    hipStream_t ss = s;
-    const bool with_bases = lo.B && lo.S <= SMALL_BESIDE;
-    if (lo.S && !with_bases) {
-        ss = fork_side(p, s);                 // after the lookup: the small layers read its verdict
-        KLAUNCH(p, ss, "k_small_compress", k_small_compress, dim3(lo.S), dim3(SMALL_THREADS), cb);
-    }
-    if (lo.B) {
-        const uint32_t* chunk_big = at<uint32_t>(p, lo.chunk_big);
-        const uint32_t cblocks = (lo.nchunks + CHUNKS_PER_WG - 1) / CHUNKS_PER_WG;
-        const uint32_t nblocks = (lo.nchunks + 256u / SUB_COUNT - 1) / (256u / SUB_COUNT);   // where candidates are only counted
-        const uint32_t hblocks = (lo.nchunks + 256u / SUB_HIST - 1) / (256u / SUB_HIST);      // and where they are histogrammed
-        KLAUNCH(p, s, "k_candidates", k_candidates, dim3(hblocks + std::min<uint32_t>(lo.ntiles, 4u * FALLBACK_GRID)), dim3(256), cb,
-                lo.nchunks, chunk_big, hblocks, lo.ntiles, (int32_t)KIMAD_ERR_INTERNAL);
-        KLAUNCH(p, s, "k_resolve", k_resolve, dim3(lo.B), dim3(256), cb);
-        // (the workgroups behind the candidates' leave after one load when no layer is served from g and h throughout)
-        const uint32_t dblocks = std::min<uint32_t>(lo.ntiles, FALLBACK_GRID);
-        KLAUNCH(p, s, "k_chunk_count", k_chunk_count, dim3(nblocks + dblocks), dim3(256), cb, lo.nchunks, chunk_big, nblocks, lo.ntiles);
-        KLAUNCH(p, s, "k_chunk_bases", k_chunk_bases, dim3(lo.ncblk + (with_bases ? lo.S : 0u)), dim3(SMALL_THREADS), cb, lo.ncblk);
-        KLAUNCH(p, s, "k_finalize", k_finalize, dim3(cblocks + dblocks), dim3(256), cb, lo.nchunks, chunk_big, cblocks, lo.ntiles);
-    }
-    return join_side(p, s, ss);
+    return enqueue_compress(p, cb, s);
 }
 
 int kimad_step(kimad_plan_t* p, uint64_t budget_bytes, double* err_table, int32_t* j_out, uint64_t* K_out,
@@ -1051,11 +1064,20 @@ int kimad_step(kimad_plan_t* p, uint64_t budget_bytes, double* err_table, int32_
     if (!status_out) return KIMAD_ERR_INVALID_ARG;
     int rc = kimad_profile(p, err_table, budget_bytes, stream);
     if (rc) return rc;
-    rc = kimad_allocate(p, err_table, budget_bytes, j_out, K_out, offsets_out, status_out, stream);
-    if (rc) return rc;
+    if (!idx_out || !val_out) {
+        // (the allocation is there, and the compression refuses)
+        rc = kimad_allocate(p, err_table, budget_bytes, j_out, K_out, offsets_out, status_out, stream);
+        return rc ? rc : KIMAD_ERR_INVALID_ARG;
+    }
+    if (!j_out || !K_out || !offsets_out) return KIMAD_ERR_INVALID_ARG;
     // On an allocation failure K and offsets are zero-filled, so the compression writes nothing.
-    return kimad_compress_ef(p, K_out, offsets_out, idx_out, val_out, capacity_pairs, KIMAD_REUSE_PROFILE,
-                             status_out + 1, stream);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    StepLookup sl{};
+    sl.cb = compress_buffers(p, K_out, offsets_out, idx_out, val_out, capacity_pairs, status_out + 1);
+    sl.j = j_out;
+    sl.err_offgrid = KIMAD_ERR_OFFGRID; sl.err_offsets = KIMAD_ERR_BAD_OFFSETS; sl.err_stale = KIMAD_ERR_STALE_PROFILE; sl.on = 1u;
+    rc = enqueue_allocate(p, plan_scratch(p), err_table, budget_bytes, j_out, K_out, offsets_out, status_out, s, CHAIN_POLLS, 0u, sl);
+    return rc ? rc : enqueue_compress(p, sl.cb, s);
 }
 
 int kimad_profile_diagnostics(kimad_plan_t* p, uint32_t* out4, void* stream) {
