@@ -442,6 +442,9 @@ __global__ __launch_bounds__(BOUNDS_THREADS) void k_dp_bounds(AllocBuffers ab, D
 // barrier does without them.  148 layers, rows of 4097 cells: 105 to 117 us at bands of 1 and of 76 cells on average (the
 // layers 55 and 75, the walk 30, records, least total and sizes 15); a loop whose lanes read records and cells from LDS in
 // turn took 108 and 137, and 5 more for a second launch that left at once (four waves for narrow bands, sixteen for wide).
+// With the shift from row to row in the records, and one clamp between the cells of +inf in the place of a minimum and an
+// addition: 140 -> 130 us on the GPT-2-shaped set's table (with the step's look-up), the whole allocation of 148 layers of
+// 20 thousand entries 209 -> 195.
 constexpr uint32_t BANDED_THREADS = 1024;
 constexpr uint32_t BAND_FEW = 8;               // records of a layer that a lane takes one after another where the band is wide
 constexpr uint32_t BAND_LIVE_CAP = 2048;       // live records held in LDS at a time
@@ -458,22 +461,28 @@ __device__ __forceinline__ BandRow band_row(const uint4& v) {
     return b;
 }
 
-// Minimum over the live records of the lane's row, of which there are at most 4 B, for one cell: `at` is the byte distance of
-// the cell from the previous row's first one, `limit` that of the cell of +inf behind its last one.
+// Minimum over the live records of the lane's row, of which there are at most 4 B, for one cell.  Addresses in LDS: `at` the
+// cell's own place in its row, counted from the previous row's first cell; a record's z leads from there to its source; what lies
+// outside the row becomes one of the cells of +inf before it and behind it, `below` and `beyond`.
+__device__ __forceinline__ int med3_i32(int a, int b, int c) {
+    int r;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
 template <int K4, int B>
-__device__ __forceinline__ void band_ask(uint32_t neg_cost, uint32_t at, uint32_t limit, uint32_t row, double (&t)[B][4]) {
+__device__ __forceinline__ void band_ask(uint32_t z, uint32_t at, int below, int beyond, double (&t)[B][4]) {
     uint32_t q[4];
-    row_addr_sub4<4 * K4>(at, neg_cost, q);
+    row_addr_sub4<4 * K4>(at, z, q);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) t[K4][u] = *(lds_cdouble_ptr)(uintptr_t)(min(q[u], limit) + row);   // (a source below the row wraps far beyond its end)
+    for (int u = 0; u < 4; ++u) t[K4][u] = *(lds_cdouble_ptr)(uintptr_t)(uint32_t)med3_i32((int)q[u], below, beyond);
 }
 template <int B>
-__device__ __forceinline__ double band_records(uint32_t neg_cost, double err, double one, uint32_t at, uint32_t limit, uint32_t row) {
+__device__ __forceinline__ double band_records(uint32_t z, double err, double one, uint32_t at, int below, int beyond) {
     double t[B][4], m[B];
-    band_ask<0>(neg_cost, at, limit, row, t);
-    if constexpr (B > 1) band_ask<1>(neg_cost, at, limit, row, t);
-    if constexpr (B > 2) band_ask<2>(neg_cost, at, limit, row, t);
-    if constexpr (B > 3) band_ask<3>(neg_cost, at, limit, row, t);
+    band_ask<0>(z, at, below, beyond, t);
+    if constexpr (B > 1) band_ask<1>(z, at, below, beyond, t);
+    if constexpr (B > 2) band_ask<2>(z, at, below, beyond, t);
+    if constexpr (B > 3) band_ask<3>(z, at, below, beyond, t);
     acc_rec_error4<0>(t[0], err, one);
     if constexpr (B > 1) acc_rec_error4<4>(t[1], err, one);
     if constexpr (B > 2) acc_rec_error4<8>(t[2], err, one);
@@ -490,8 +499,9 @@ __device__ __forceinline__ double band_records(uint32_t neg_cost, double err, do
 __global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, DpLists dl, BandBuffers bb, double* rows_g,
                                                               uint32_t rstride, int32_t err_infeasible, int32_t err_nonfinite, StepLookup sl) {
     constexpr uint32_t MAX_WAVES = BANDED_THREADS / 64;
-    __shared__ double rows[BAND_CELLS];
-    __shared__ uint4 recs[BAND_LIVE_CAP];                 // error bits, cost
+    __shared__ double rows_before[BAND_CELLS + 1u];       // a cell of +inf, then the rows, each with one behind it
+    double* const rows = rows_before + 1u;
+    __shared__ uint4 recs[BAND_LIVE_CAP];                 // error bits, the way from a cell's own place to its source in bytes
     __shared__ uint4 s_row[BAND_MAX_L + 1];
     __shared__ double s_val[BAND_MAX_L + 1];              // the path's value per row
     __shared__ uint8_t s_k[BAND_MAX_L];                   // the path's live record per layer
@@ -523,7 +533,7 @@ __global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, D
     }
     __syncthreads();
     const bool any_bad = s_bad != 0u, hopeless = bb.info[4] != 0u;
-    const uint32_t wr = min(cap + 2u, BAND_CELLS / 2u);   // cells per row buffer when only two rows are kept
+    const uint32_t wr = min(cap + 2u, BAND_CELLS / 2u - 1u);   // cells per row buffer when only two rows are kept
     const bool all = cells <= BAND_CELLS;
 
     // the records of layers [a, b) into LDS, eight layers' loads in flight per wave
@@ -531,7 +541,7 @@ __global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, D
         const uint32_t first = s_row[a].w;
         for (uint32_t i0 = a + wave * 8u; i0 < b; i0 += NWAVES * 8u) {
             double e[8];
-            uint32_t w[8], at[8];
+            uint32_t w[8], at[8], shift[8];
             bool in[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
@@ -539,19 +549,23 @@ __global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, D
                 const uint32_t rec = s_row[i].w, cnt = s_row[i + 1u].w - rec;
                 in[u] = i0 + (uint32_t)u < b && lane < cnt;
                 at[u] = rec - first + lane;
+                shift[u] = s_row[i + 1u].x - s_row[i].x;
                 const size_t o = in[u] ? (size_t)i * J + min((uint32_t)s_first[i] + lane, J - 1u) : 0;
                 e[u] = dl.e[2 * o]; w[u] = dl.w[o];
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (in[u]) recs[at[u]] = make_uint4((uint32_t)__double2loint(e[u]), (uint32_t)__double2hiint(e[u]), w[u], 0u);
+                if (in[u]) recs[at[u]] = make_uint4((uint32_t)__double2loint(e[u]), (uint32_t)__double2hiint(e[u]), 8u * (shift[u] - w[u]), 0u);
         }
     };
     int32_t st = any_bad ? err_nonfinite : hopeless ? err_infeasible : 0;
     uint32_t at_last = 0u;                                // where row L's cells are
     uint32_t loaded = 0u;                                 // first layer of the records in LDS
     if (st == 0) {
-        if (tid == 0) { rows[0] = 0.0; rows[1] = DP_INF; if (!all) rows_g[0] = 0.0; }
+        if (tid == 0) {
+            rows[-1] = DP_INF; rows[0] = 0.0; rows[1] = DP_INF;
+            if (!all) { rows[wr] = DP_INF; rows_g[0] = 0.0; }      // (the second buffer starts behind this one)
+        }
         double one = 1.0;
         asm volatile("" : "+v"(one));      // keep 1.0 in a vector register pair
         const uint32_t k = (lane & 15u) * 4u + (lane >> 4);     // this lane's record
@@ -571,38 +585,37 @@ __global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, D
             load_records(i, i1);
             loaded = i;
             __syncthreads();
-            // layer a -> b's record of this lane (beyond the last: one that changes no minimum)
-            auto record = [&](const BandRow& a, const BandRow& b) {
-                const uint32_t n = b.rec - a.rec;
-                uint4 r = recs[min(a.rec - g0 + min(k, max(n, 1u) - 1u), BAND_LIVE_CAP - 1u)];
+            // the record of this lane among n from `rec` on (beyond the last: one that changes no minimum)
+            auto record = [&](uint32_t rec, uint32_t n) {
+                uint4 r = recs[min(rec - g0 + k, BAND_LIVE_CAP - 1u)];
                 r.y = k < n ? r.y : 0x7FF00000u;
                 r.x = k < n ? r.x : 0u;
-                r.z = 0u - 8u * r.z;
                 return r;
             };
             BandRow p = band_row(s_row[i]), c = band_row(s_row[i + 1u]);
-            uint4 R = record(p, c);
+            uint4 R = record(p.rec, c.rec - p.rec);
             BandRow nx = band_row(s_row[min(i + 2u, i1)]);
             for (; i < i1; ++i) {
-                const uint32_t n = c.rec - p.rec, neg = R.z;
+                const uint32_t n = c.rec - p.rec, z = R.z;
                 const double err = rec_err(R);
                 // the next layer's record and the row after that, asked for now: off the critical path
                 const uint4 after = s_row[min(i + 3u, i1)];
-                R = record(c, nx);
-                const uint32_t prow = all ? p.at : (i & 1u) * wr, crow = all ? c.at : ((i + 1u) & 1u) * wr;
+                R = record(c.rec, nx.rec - c.rec);
+                const uint32_t prow = all ? p.at : (i & 1u) * (wr + 1u), crow = all ? c.at : ((i + 1u) & 1u) * (wr + 1u);
                 double* out = all ? nullptr : rows_g + (size_t)(i + 1u) * rstride;
-                const uint32_t row = lds_addr(rows + prow), limit = 8u * (p.span + 1u), shift = c.lo - p.lo;   // (may wrap: so does the source, beyond the limit)
+                const uint32_t row = lds_addr(rows + prow);
+                const int below = (int)row - 8, beyond = (int)(row + 8u * (p.span + 1u));
                 if (n <= BAND_FEW && c.span + 1u >= NWAVES * 16u) {
                     // few records and more cells than the waves have sixteens: a cell a lane, the records one after another
                     for (uint32_t c0 = wave * 64u; c0 <= c.span + 1u; c0 += NWAVES * 64u) {
-                        const uint32_t cell = c0 + lane, at = 8u * (cell + shift);
+                        const uint32_t cell = c0 + lane, at = row + 8u * cell;
                         double best = DP_INF;
                         for (uint32_t j = 0; j < n; ++j) {
                             const int from = (int)((j & 3u) * 16u + (j >> 2));             // (the lane that holds record j)
                             const double e = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(err), from),
                                                               __builtin_amdgcn_readlane(__double2loint(err), from));
-                            const uint32_t q = min(at + (uint32_t)__builtin_amdgcn_readlane((int)neg, from), limit);
-                            best = min_f64(best, *(lds_cdouble_ptr)(uintptr_t)(q + row) + e);
+                            const int q = med3_i32((int)(at + (uint32_t)__builtin_amdgcn_readlane((int)z, from)), below, beyond);
+                            best = min_f64(best, *(lds_cdouble_ptr)(uintptr_t)(uint32_t)q + e);
                         }
                         if (cell <= c.span + 1u) {
                             rows[crow + cell] = cell <= c.span ? best : DP_INF;
@@ -611,12 +624,12 @@ __global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, D
                     }
                 } else {
                     for (uint32_t c0 = wave * 16u; c0 <= c.span + 1u; c0 += NWAVES * 16u) {
-                        const uint32_t cell = c0 + (lane & 15u), at = 8u * (cell + shift);
+                        const uint32_t cell = c0 + (lane & 15u), at = row + 8u * cell;
                         double best;
-                        if (n <= 16u) best = band_records<1>(neg, err, one, at, limit, row);
-                        else if (n <= 32u) best = band_records<2>(neg, err, one, at, limit, row);
-                        else if (n <= 48u) best = band_records<3>(neg, err, one, at, limit, row);
-                        else best = band_records<4>(neg, err, one, at, limit, row);
+                        if (n <= 16u) best = band_records<1>(z, err, one, at, below, beyond);
+                        else if (n <= 32u) best = band_records<2>(z, err, one, at, below, beyond);
+                        else if (n <= 48u) best = band_records<3>(z, err, one, at, below, beyond);
+                        else best = band_records<4>(z, err, one, at, below, beyond);
                         if (lane < 16u && cell <= c.span + 1u) {
                             rows[crow + cell] = cell <= c.span ? best : DP_INF;
                             if (out && cell <= c.span) out[cell] = best;
@@ -627,7 +640,7 @@ __global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, D
                 p = c; c = nx; nx = band_row(after);
             }
         }
-        at_last = all ? s_row[L].z : (L & 1u) * wr;
+        at_last = all ? s_row[L].z : (L & 1u) * (wr + 1u);
     }
     // ---- least total of the last row, smallest cost attaining it
     double best = DP_INF;
@@ -659,7 +672,7 @@ __global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, D
     }
     // ---- the walk back, in groups of layers whose records, and staged rows, fit LDS
     if (tid == 0) s_val[L] = best;
-    uint32_t cell = bc;
+    uint32_t rel = bc - s_row[L].x;                        // the path's cell, counted from its row's first
     double val = best;
     uint32_t hi = L;
     while (hi > 0u) {
@@ -695,13 +708,13 @@ __global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, D
                 const uint4 after = s_row[i > lo + 1u ? i - 2u : lo];
                 // the record of the layer before (`next` is its row), asked for now, as the row before that
                 const uint4 rn = recs[next.rec - rec0 + min(lane, max(p.rec - next.rec, 1u) - 1u)];
-                const uint32_t src = cell - p.lo - r.z;
+                const uint32_t src = rel + (uint32_t)((int)r.z >> 3);            // (counted from the row's first cell)
                 const bool in = lane < n && src <= p.span;
                 const double v = rows[p.at - row0 + (in ? src : 0u)];
                 const uint64_t hit = ballot(in && v + rec_err(r) == val);
                 const uint32_t k = hit ? (uint32_t)__builtin_ctzll(hit) : 0u;  // (there is one)
                 if (lane == k) { s_k[i] = (uint8_t)k; s_val[i] = v; }
-                cell -= (uint32_t)__builtin_amdgcn_readlane((int)r.z, (int)k);
+                rel = (uint32_t)__builtin_amdgcn_readlane((int)src, (int)k);
                 val = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), (int)k),
                                        __builtin_amdgcn_readlane(__double2loint(v), (int)k));
                 r = rn; c = p; p = next; next = band_row(after);
