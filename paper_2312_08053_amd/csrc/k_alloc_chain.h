@@ -257,7 +257,7 @@ template <uint32_t MAXC, uint32_t NT>
 __device__ __forceinline__ void chain_choose(const AllocBuffers& ab, const DpLists& dl, const double* rows_g, uint32_t rstride, uint32_t first,
                                              uint32_t m, uint32_t piece, uint32_t lo, uint32_t hi, double* rows, uint32_t pitch, PieceList* lists,
                                              uint16_t (*src)[MAXC], uint8_t (*win)[MAXC]) {
-    constexpr uint32_t CPT = (MAXC + NT - 1u) / NT, U = CPT <= 2u ? 8u : 4u;     // candidates whose cells are asked for together
+    constexpr uint32_t CPT = (MAXC + NT - 1u) / NT, U = CPT <= 2u ? 8u : CPT <= 3u ? 4u : 2u;     // candidates whose cells are asked for together (four of five cells spill)
     const uint32_t tid = threadIdx.x, lane = lane_id();
     const uint32_t mine = lo + (uint32_t)__builtin_amdgcn_readfirstlane(tid & ~63u);   // the wave's first cell: none beyond hi
     unsigned long long v[CPT];

@@ -489,7 +489,7 @@ int run_select_passes(kimad_plan* p, const uint32_t* ktab_dev, uint32_t J, doubl
         const uint32_t group = hist2_group_tiles(lo.ntiles, lo.tile_elems);
         KLAUNCH(p, s, "k_hist2", k_hist2, dim3(lo.B + (lo.ntiles + group - 1) / group), dim3(HIST2_THREADS), p->pb, lo.B, lo.ntiles, group,
                 (const uint32_t*)nullptr, 0u, ktab_dev, J, err_table, CERT_TOL, 0.0);
-        // exact last-digit pass for the entries scan 2 could not certify (usually none)
+        // exact last-digit pass for the entries that the scan could not certify (usually none)
         if (err_table) KLAUNCH(p, s, "k_hist3p", k_hist3p, dim3(lo.ntiles), dim3(256), p->pb, lo.ntiles, err_table, mark_fresh);
     }
     return KIMAD_OK;
