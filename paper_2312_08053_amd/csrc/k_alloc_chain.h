@@ -73,9 +73,9 @@ __device__ __forceinline__ double min_over_rows(double v) {
 // all: with the records asked for by them, and the cells' stores in the same queue, a layer took 0.4 us.  148 layers of
 // 999 cells: 4 compute waves 61 us, 8 62, 3 65; one loader wave a group 71, two 61, four 62; four groups of one wave 91.
 // Few layers want few workgroups, each of which starts behind the one below, many a short layer: all launches of the
-// allocation with 64 ratios and four or eight waves, 20 layers 41 and 39 us, 60 61 and 56, 148 91 and 91, 500 219 and 234, 1000
-// 309 and 342; with 2000 cells 60 layers 79 and 67.  Rows beyond 2048 cells take four, whose loaders leave no room for
-// eight: 148 layers of 4097 cells 260 and 455.)
+// allocation with 64 ratios and four or eight waves, 20 layers 32 and 30 us, 60 56 and 52, 148 85 and 83, 500 198 and 209, 1000
+// 357 and 384; with 2000 cells, before the winners were found beside the chain, 60 layers 79 and 67.  Rows beyond 2048 cells
+// take four, whose loaders leave no room for eight: 148 layers of 4097 cells 260 and 455, before that too.)
 constexpr uint32_t CHAIN_NARROW_L = 128;        // layers from which on four waves look after rows of up to 1024 cells
 constexpr uint32_t CHAIN_LOADERS = 2;
 constexpr uint32_t CHAIN_RECS = 4;              // layers whose records are in LDS, and under way from memory
