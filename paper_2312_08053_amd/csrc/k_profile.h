@@ -242,51 +242,16 @@ __global__ __launch_bounds__(256) void k_scan1(ProfileBuffers pb, const uint32_t
 // bounds.  Entries whose bound is not tight enough are counted in diag[0].
 __device__ __forceinline__ float prefix_lo(uint32_t prefix) { return __uint_as_float(prefix << D2_SHIFT); }
 
-// One wave per candidate: every lane holds two digit-2 bins of the candidate's boundary bin.
-// `flagged` and `prefix_out` come back the same in every lane.
-// What a target's loads bring: first what its index addresses, then what its slot addresses.  A wave looks after
-// several targets; it asks for all of one kind together, so that the round trips to memory are two per wave, not
-// two per target.
-struct Scan2Target {
-    uint32_t K, slot, r, above1;
-    double below;
-    uint32_t bin;
-    uint2 c;
-    ulonglong2 q;
+// What comes of a candidate; the same in every lane.
+struct Scan2Result {
+    double E, base;
+    uint32_t prefix, above, amb, unsel;
+    bool flagged;
 };
-__device__ __forceinline__ void scan2_load_target(const ProfileBuffers& pb, const uint32_t* Ktab, size_t t, Scan2Target& T) {
-    T.K = Ktab[t];
-    T.slot = pb.tgt_slot[t];
-    T.r = pb.tgt_r[t];
-    T.above1 = pb.tgt_above1[t];
-    T.below = pb.tgt_below[t];
-}
-__device__ __forceinline__ void scan2_load_slot(const ProfileBuffers& pb, uint32_t big, Scan2Target& T) {
-    const uint32_t lane = lane_id();
-    T.bin = pb.slot_bin[(size_t)big * SLOT_STRIDE + T.slot];
-    T.c = reinterpret_cast<const uint2*>(pb.cnt2 + ((size_t)big * SLOT_STRIDE + T.slot) * D2_BINS)[lane];
-    T.q = reinterpret_cast<const ulonglong2*>(pb.sq2 + ((size_t)big * SLOT_STRIDE + T.slot) * D2_BINS)[lane];
-}
-__device__ __forceinline__ void scan2_target(const ProfileBuffers& pb, const Scan2Target& T, uint32_t n, size_t t,
-                                             double* err_table, double tol, double widen, bool* flagged,
-                                             uint32_t* prefix_out) {
-    const uint32_t lane = lane_id();
-    const uint32_t K = T.K;
-    if (T.slot == NO_SLOT) {                    // K == n (or K == 0): nothing / everything dropped
-        if (lane == 0) {
-            if (err_table) err_table[t] = (K == 0u) ? T.below : 0.0;
-            pb.sel_prefix[t] = 0u;
-            pb.sel_above[t] = (K == 0u) ? 0u : n;
-            pb.sel_amb[t] = 0u;
-            pb.tgt_unsel[t] = 0u;
-            pb.tgt_base[t] = 0.0;
-        }
-        return;
-    }
-    const uint32_t bin = T.bin;
-    const uint32_t r = T.r;
-    const uint2 c = T.c;
-    const ulonglong2 q = T.q;
+// One wave per candidate, of rank r in digit-1 bin `bin`, above which are above1 entries, below it squares of `below`: every
+// lane holds two digit-2 bins.
+__device__ __forceinline__ Scan2Result scan2_target(uint32_t lane, uint32_t bin, uint32_t r, uint32_t above1, double below, uint2 c, ulonglong2 q, double tol,
+                                                    double widen) {
     // walk digit 2 from the top until r entries are covered: the boundary is the highest bin u > 0
     // with (entries above u) + cnt[u] >= r, or bin 0
     const uint32_t incl = wave_scan_add_u32(c.x + c.y);
@@ -327,63 +292,84 @@ __device__ __forceinline__ void scan2_target(const ProfileBuffers& pb, const Sca
             half_gap = 0.5 * (ub - lb);
         }
     }
-    const double base = T.below + below2;
+    const double base = below + below2;
     const double E = base + est;
     // single-pass slots hold midpoints of intervals 2^-23 wide (relative): part of the bound
     half_gap += E * widen;
-    if (lane == 0) {
-        if (err_table) err_table[t] = E;
-        pb.sel_prefix[t] = prefix;
-        pb.sel_above[t] = T.above1 + acc;
-        pb.sel_amb[t] = m;
-        pb.tgt_unsel[t] = unsel;
-        pb.tgt_base[t] = base;
-    }
-    *flagged = err_table != nullptr && half_gap > tol * E;
-    *prefix_out = prefix;
+    return {E, base, prefix, above1 + acc, m, unsel, half_gap > tol * E};
 }
 
 // One workgroup per big layer, one wave per candidate at a time.  Candidates whose error bound is
 // too wide are then grouped by prefix (equal prefixes are adjacent because K ascends) and each
 // group gets one pool entry for the exact last-digit pass.
-constexpr uint32_t SCAN2_THREADS = 1024;
+// The counts may have been added by other workgroups of this launch: they are read with loads of device scope, and there
+// is no fence (see k_hist2).
+constexpr uint32_t SCAN2_THREADS = 768;         // (k_hist2 says why)
 __device__ __forceinline__ void scan2(const ProfileBuffers& pb, uint32_t big, const uint32_t* Ktab, uint32_t J, double* err_table, double tol, double widen) {
     __shared__ uint32_t sh_prefix[KIMAD_MAX_J_CONST];
     __shared__ uint32_t sh_flag[KIMAD_MAX_J_CONST];
     __shared__ uint32_t sh_pool[KIMAD_MAX_J_CONST];     // pool entries this layer has taken
     __shared__ uint32_t sh_npool;
-    if (threadIdx.x == 0) {
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));                        // (else addresses are worked out ahead of the caller's loop, and kept through the counting)
+    const uint32_t lane = tid & 63u;
+    if (tid == 0) {
         sh_npool = 0u;
         pb.tiles_done[big] = 0u;                        // (for the exact pass; this layer's counts are complete)
     }
     const uint32_t li = pb.big_layer[big];
-    constexpr uint32_t WAVES = SCAN2_THREADS / 64, PER_WAVE = KIMAD_MAX_J_CONST / WAVES;
-    static_assert(PER_WAVE * WAVES == KIMAD_MAX_J_CONST, "every wave looks after the same number of targets");
-    const uint32_t wave = threadIdx.x >> 6;
+    constexpr uint32_t WAVES = SCAN2_THREADS / 64, PER_WAVE = (KIMAD_MAX_J_CONST + WAVES - 1u) / WAVES;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t n = pb.layers[li].n;
-    Scan2Target T[PER_WAVE];
-#pragma unroll
-    for (uint32_t u = 0; u < PER_WAVE; ++u) {
-        const uint32_t jj = wave + u * WAVES;
-        T[u].slot = NO_SLOT; T[u].K = 1u; T[u].r = 0u; T[u].above1 = 0u; T[u].below = 0.0;
-        if (jj < J) scan2_load_target(pb, Ktab, (size_t)li * J + jj, T[u]);
+    // Lane u holds what there is to know of the wave's target u, and later what has come of it (four targets' fields in
+    // every lane took 60 registers more, and a store per field and target).  The loads take two round trips, what a
+    // target's index addresses, then what its slot addresses; the next target's bins are under way while one is worked on.
+    const uint32_t jj = wave + lane * WAVES;
+    const bool there = lane < PER_WAVE && jj < J;
+    const size_t t = (size_t)li * J + jj;
+    const uint32_t K = there ? Ktab[t] : 1u, slot = there ? pb.tgt_slot[t] : NO_SLOT;
+    const uint32_t r = there ? pb.tgt_r[t] : 0u, above1 = there ? pb.tgt_above1[t] : 0u;
+    const double below = there ? pb.tgt_below[t] : 0.0;
+    const uint32_t bin = slot != NO_SLOT ? pb.slot_bin[(size_t)big * SLOT_STRIDE + slot] : 0u;
+    uint2 c;
+    ulonglong2 q;
+    auto ask = [&](uint32_t u) {
+        const uint32_t s = (uint32_t)__builtin_amdgcn_readlane((int)slot, (int)u);
+        const size_t row = ((size_t)big * SLOT_STRIDE + (s == NO_SLOT ? 0u : s)) * D2_BINS;
+        const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(pb.cnt2 + row) + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long* sq = reinterpret_cast<const unsigned long long*>(pb.sq2 + row) + 2u * lane;
+        c = make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+        q = make_ulonglong2(__hip_atomic_load(sq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                            __hip_atomic_load(sq + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    };
+    // (no slot: K == n or K == 0, nothing or everything is dropped)
+    Scan2Result mine{K == 0u ? below : 0.0, 0.0, 0u, K == 0u ? 0u : n, 0u, 0u, false};
+    uint32_t group = 0xFFFFFFFFu - jj;          // its prefix; distinct for what has none
+    ask(0u);
+#pragma unroll 1
+    for (uint32_t u = 0; u < PER_WAVE && wave + u * WAVES < J; ++u) {
+        const uint2 cu = c;
+        const ulonglong2 qu = q;
+        ask(min(u + 1u, PER_WAVE - 1u));
+        if ((uint32_t)__builtin_amdgcn_readlane((int)slot, (int)u) == NO_SLOT) continue;
+        const Scan2Result res = scan2_target(lane, (uint32_t)__builtin_amdgcn_readlane((int)bin, (int)u), (uint32_t)__builtin_amdgcn_readlane((int)r, (int)u),
+                                             (uint32_t)__builtin_amdgcn_readlane((int)above1, (int)u),
+                                             __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(below), (int)u),
+                                                              __builtin_amdgcn_readlane(__double2loint(below), (int)u)), cu, qu, tol, widen);
+        if (lane == u) { mine = res; group = res.prefix; }
     }
-#pragma unroll
-    for (uint32_t u = 0; u < PER_WAVE; ++u) {
-        T[u].bin = 0u; T[u].c = make_uint2(0u, 0u); T[u].q = make_ulonglong2(0ull, 0ull);
-        if (T[u].slot != NO_SLOT) scan2_load_slot(pb, big, T[u]);
+    if (there) {
+        if (err_table) err_table[t] = mine.E;
+        pb.sel_prefix[t] = mine.prefix;
+        pb.sel_above[t] = mine.above;
+        pb.sel_amb[t] = mine.amb;
+        pb.tgt_unsel[t] = mine.unsel;
+        pb.tgt_base[t] = mine.base;
     }
-#pragma unroll
-    for (uint32_t u = 0; u < PER_WAVE; ++u) {
-        const uint32_t jj = wave + u * WAVES;
-        bool fl = false;
-        uint32_t px = 0xFFFFFFFFu - jj;         // distinct dummy for idle slots and K == n
-        if (jj < J) scan2_target(pb, T[u], n, (size_t)li * J + jj, err_table, tol, widen, &fl, &px);
-        if (lane_id() == 0) { sh_prefix[jj] = px; sh_flag[jj] = fl ? 1u : 0u; }
-    }
+    if (lane < PER_WAVE && jj < KIMAD_MAX_J_CONST) { sh_prefix[jj] = group; sh_flag[jj] = err_table && mine.flagged ? 1u : 0u; }
     __syncthreads();
-    if (threadIdx.x < 64) {
-        const uint32_t j = threadIdx.x;
+    if (tid < 64) {
+        const uint32_t j = tid;
         const bool flagged = sh_flag[j] != 0u;
         const uint32_t prefix = sh_prefix[j];
         const uint32_t prev = __shfl_up(prefix, 1, 64);
@@ -416,9 +402,9 @@ __device__ __forceinline__ void scan2(const ProfileBuffers& pb, uint32_t big, co
     __syncthreads();
     // The pool's histograms share their memory with the streaming pass's histogram parts (dead by now): an
     // entry is cleared here, by the workgroup that takes it, before the exact pass counts into it.
-    static_assert(D3_BINS == 4u * SCAN2_THREADS, "one 16-byte store per thread clears an entry");
     for (uint32_t k = 0; k < sh_npool; ++k)
-        reinterpret_cast<uint4*>(pb.pool_hist + (size_t)sh_pool[k] * D3_BINS)[threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
+        for (uint32_t x = tid; x < D3_BINS / 4u; x += SCAN2_THREADS)
+            reinterpret_cast<uint4*>(pb.pool_hist + (size_t)sh_pool[k] * D3_BINS)[x] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // Waits until this wave's additions to memory are there for every compute unit (they are atomics of device scope, carried out
@@ -429,7 +415,7 @@ __device__ __forceinline__ void additions_done() { asm volatile("s_waitcnt vmcnt
 // Pass 2: digit-2 histograms (count + squares) of the entries that fall in a boundary bin.
 // Workgroups take groups of consecutive tiles in a grid-stride loop and add their tables to the layer's once per group:
 // on a small set, whose tiles are short, the additions of every tile's few thousand entries were nearly all of the pass
-// (ResNet-18 with 50 ratios, every layer: 154 us with a flush per 4096 elements, 36 us with one per 32768).
+// (ResNet-18 with 50 ratios, 19 layers: 160 us with a flush per 4096 elements, 56 with one per 32768).
 // hist2_group_tiles says how long a group is.  `gate` (optional) points at a device word that is
 // zero when no layer needs this pass: the single-pass profile launches it as a fallback that
 // normally has nothing to do, with a small grid that leaves after one load, and with `coarse` set
@@ -437,66 +423,53 @@ __device__ __forceinline__ void additions_done() { asm volatile("s_waitcnt vmcnt
 //
 // The scan of a layer's counts (scan2) belongs to the launch: the first `nbig` workgroups scan a layer each that has nothing to be
 // counted here, and the layers that have are scanned by the workgroup that adds the last of their tiles (tiles_done), so that no
-// workgroup waits for another.  (us of two launches, and of this one.  Nothing to count: ResNet-50 10.6 and 7.5, GPT-2-shaped
-// 14.6 and 11.5; a few layers to count: GPT-2-shaped in overlapped rounds 31 and 28, ResNet-18 with 50 ratios 38 and 40.  A
-// workgroup reports its layers' tiles when it is through with all of them: 44 for that last with a report after each.)
+// workgroup waits for another.  A workgroup reports its layers' tiles when it is through with RUNS of them, or with all.
+// Bound by the loads and LDS additions that the waves keep under way, so two workgroups share a compute unit: one clears, waits
+// at its barriers or flushes while the other counts.  LDS holds two; twelve waves each leave the scan the 80 registers that it
+// needs (sixteen waves leave 64: 18 of the scan's in scratch memory; with eight waves, the counting has fewer loads under way).
+// Whoever finds a layer complete must not fence: a fence of device scope writes its chiplet's cache back first, and everything
+// else that goes through that cache waits.
+// (us by events, two launches, this one, and this one with the fence.  Nothing to count: GPT-2-shaped 19.1, 13.4, 13.4, perceptron
+// 18.5, 12.6.  Recounted layers: 19 of ResNet-18 with 50 ratios 59, 57, 65, 53 of ResNet-50 82, 72, 173, 50 of the GPT-2-shaped
+// set 323, 292, 456, 700 of 9 to 30 thousand entries 71, 74, 206, 169 of the Llama-shaped set 2500, 2540, 2780.  Every layer of the
+// GPT-2-shaped set in the classic profile 296, 280, 503.  Sixteen waves, one workgroup to a compute unit, without the fence: GPT-2-
+// shaped 352, 700 layers 90; eight waves, two: 348 and 78.  A report after four or 64 runs: the same.)
 constexpr uint32_t HIST2_MAX_ELEMS = 32768;    // elements a workgroup may count before it flushes: the count field has 16 bits
 // As many tiles as the counts admit, but at least 256 groups, one a compute unit, where the set has the tiles for them.
 // (Groups of 32768 elements left a perceptron of 266 K elements nine workgroups: k_hist2 9 -> 22 us, a classic profile
-// 61 -> 80 us.  At least 512 or 1024 groups: ResNet-18 with every layer recounted 320 -> 337 or 358 us.)
+// 61 -> 80 us.  At least 512 or 1024 groups: 19 recounted layers of ResNet-18 56 -> 68 or 98 us, 53 of ResNet-50 72 -> 71 or 83;
+// at least 128: the same as 256.)
 inline uint32_t hist2_group_tiles(uint32_t ntiles, uint32_t tile_elems) {
     const uint32_t most = HIST2_MAX_ELEMS / tile_elems, share = ntiles / 256u;
     return share < 1u ? 1u : share < most ? share : most;
 }
 constexpr uint32_t HIST2_THREADS = SCAN2_THREADS;
-__global__ __launch_bounds__(HIST2_THREADS) void k_hist2(ProfileBuffers pb, uint32_t nbig, uint32_t ntiles, uint32_t group_tiles, const uint32_t* gate,
+__global__ __launch_bounds__(HIST2_THREADS, 6) void k_hist2(ProfileBuffers pb, uint32_t nbig, uint32_t ntiles, uint32_t group_tiles, const uint32_t* gate,
                                                          uint32_t coarse, const uint32_t* Ktab, uint32_t J, double* err_table, double tol,
                                                          double widen) {
     __shared__ unsigned long long sub[MAX_SLOTS * D2_BINS];   // 64 KB
     __shared__ unsigned long long sub0[D2_BINS];              // exact squares when the slot is bin 0
     __shared__ uint8_t lut[D1_BINS];
-    constexpr uint32_t RUNS = 64;
+    constexpr uint32_t RUNS = 8;
     __shared__ uint32_t run_big[RUNS], run_tiles[RUNS];       // tiles counted and not yet reported, by layer
-    __shared__ uint64_t sh_last;
-    const uint32_t tid = threadIdx.x;
+    __shared__ uint64_t sh_which;
+    uint32_t tid = threadIdx.x;
+    const bool counting = blockIdx.x >= nbig;
+    if (counting && gate && *gate == 0u) return;
+    if (tid == 0) run_big[0] = blockIdx.x;      // (the layer of one that only scans)
+    uint32_t tile0 = (blockIdx.x - nbig) * group_tiles, tile = tile0;        // the group, and its next tile
+    for (;;) {
     uint32_t runs = 0u;
-    // the runs' tiles are done: the layers that have none left are scanned
-    auto report = [&]() {
-        additions_done();
-        __syncthreads();
-        if (tid < 64u) {
-            const uint32_t b = tid < runs ? run_big[tid] : 0u;
-            const bool last = tid < runs && atomicAdd(&pb.tiles_done[b], run_tiles[tid]) + run_tiles[tid] == pb.layers[pb.big_layer[b]].ntiles;
-            const uint64_t which = ballot(last);
-            if (tid == 0) sh_last = which;
-        }
-        __syncthreads();
-        uint64_t which = sh_last;
-        if (which) __threadfence();
-        while (which) {
-            scan2(pb, (uint32_t)__builtin_amdgcn_readfirstlane(run_big[__builtin_ctzll(which)]), Ktab, J, err_table, tol, widen);
-            __syncthreads();
-            which &= which - 1ull;
-        }
-        runs = 0u;
-    };
-    if (blockIdx.x < nbig) {
-        const LayerState st = pb.state[blockIdx.x];
-        if (!st.redo || st.nslots_d == 0u) scan2(pb, blockIdx.x, Ktab, J, err_table, tol, widen);
-        return;
-    }
-    if (gate && *gate == 0u) return;
-    for (uint32_t tile0 = (blockIdx.x - nbig) * group_tiles; tile0 < ntiles; tile0 += (gridDim.x - nbig) * group_tiles) {
-    uint32_t tile = tile0;
-    const uint32_t tile_end = min(ntiles, tile + group_tiles);
-    while (tile < tile_end) {
+    while (counting && runs < RUNS && tile0 < ntiles) {
+    asm volatile("" : "+v"(tid));               // (else addresses are worked out ahead of the loop, and kept through the scan)
     // the group's tiles of one layer
     const uint32_t li = pb.tile_layer[tile];
     const LayerDesc L = pb.layers[li];
     const LayerState st = pb.state[L.big];
     const uint32_t ns = st.nslots_d;
-    const uint32_t first = tile, last = min(tile_end, L.tile0 + L.ntiles);
+    const uint32_t first = tile, last = min(min(ntiles, tile0 + group_tiles), L.tile0 + L.ntiles);
     tile = last;
+    if (tile == min(ntiles, tile0 + group_tiles)) { tile0 += (gridDim.x - nbig) * group_tiles; tile = tile0; }
     if (!st.redo || ns == 0) continue;
     {
         const uint32_t* src = reinterpret_cast<const uint32_t*>(pb.lut1 + (size_t)L.big * D1_BINS);
@@ -508,12 +481,14 @@ __global__ __launch_bounds__(HIST2_THREADS) void k_hist2(ProfileBuffers pb, uint
     __syncthreads();
 
     const uint32_t vend = (last - L.tile0) * pb.tile_elems;
+    const uint32_t lane4 = 4u * (tid & 63u);
     constexpr uint32_t QUADS = 2;               // a thread's loads under way
-    for (uint32_t v = (first - L.tile0) * pb.tile_elems + tid * 4u; v < vend; v += 4u * QUADS * HIST2_THREADS) {
+    for (uint32_t v = (first - L.tile0) * pb.tile_elems + (uint32_t)__builtin_amdgcn_readfirstlane(tid & ~63u) * 4u; v < vend;
+         v += 4u * QUADS * HIST2_THREADS) {
         Quad q[QUADS];
 #pragma unroll
         for (uint32_t u = 0; u < QUADS; ++u) {
-            if (v + u * 4u * HIST2_THREADS < vend) load_quad(L, v + u * 4u * HIST2_THREADS, q[u]);
+            if (v + u * 4u * HIST2_THREADS < vend) load_quad(L, v + u * 4u * HIST2_THREADS + lane4, q[u]);
             else { q[u].key[0] = q[u].key[1] = q[u].key[2] = q[u].key[3] = KEY_INVALID; }
         }
 #pragma unroll
@@ -551,10 +526,31 @@ __global__ __launch_bounds__(HIST2_THREADS) void k_hist2(ProfileBuffers pb, uint
     if (tid == 0) { run_big[runs] = (uint32_t)L.big; run_tiles[runs] = last - first; }
     ++runs;
     __syncthreads();                            // the next tiles reuse the LDS tables
-    if (runs == RUNS) report();
     }
+    // which of the runs' layers are scanned here
+    if (counting) {
+        if (runs == 0u) return;
+        additions_done();
+        __syncthreads();
+        if (tid < 64u) {
+            const uint32_t b = tid < runs ? run_big[tid] : 0u;
+            const bool last = tid < runs && atomicAdd(&pb.tiles_done[b], run_tiles[tid]) + run_tiles[tid] == pb.layers[pb.big_layer[b]].ntiles;
+            const uint64_t which = ballot(last);
+            if (tid == 0) sh_which = which;
+        }
+    } else if (tid == 0) {
+        const LayerState st = pb.state[blockIdx.x];
+        sh_which = !st.redo || st.nslots_d == 0u ? 1ull : 0ull;
     }
-    if (runs) report();
+    __syncthreads();
+    uint64_t which = sh_which;
+    while (which) {
+        scan2(pb, (uint32_t)__builtin_amdgcn_readfirstlane(run_big[__builtin_ctzll(which)]), Ktab, J, err_table, tol, widen);
+        __syncthreads();
+        which &= which - 1ull;
+    }
+    if (!counting || tile0 >= ntiles) return;
+    }
 }
 
 // Exact fallback, scan of a pool entry by 256 threads.  With the full key known, the squares of the

@@ -346,7 +346,10 @@ constexpr uint32_t STREAM_CANDIDATES_CHUNKS = 524288;
 // 398.  The line is the selection's; the profile alone would go on sharing.
 constexpr uint32_t SMALL_BESIDE = 512;
 constexpr uint32_t FALLBACK_GRID = 1024;   // workgroups of a pass that usually has nothing to do
-constexpr uint32_t RECOUNT_GRID = 512;     // the same for k_hist2, of which two fit a compute unit
+// The same for k_hist2, four times as many as fit: the layers to be recounted lie unevenly among the tiles.  (us with 512, 1024
+// and 2048: 50 layers of the GPT-2-shaped set 323, 308, 293, 169 of the Llama-shaped set 2905, 2762, 2536, 53 of ResNet-50 78, 72,
+// 72; with nothing to count 13.4 each.)
+constexpr uint32_t RECOUNT_GRID = 2048;
 // A selection from scratch takes the single pass from this many chunks in tiled layers on, if these hold this many each on
 // average; below, its four more launches and its tables per layer cost more than the two reads of g and h it saves.
 // A hundredth kept, single pass and two histogram passes with a compaction, us: 4 layers 81 and 71 at 1 M elements, 95 and

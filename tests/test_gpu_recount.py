@@ -41,3 +41,32 @@ def test_recounted_layers(short, lo, hi, long, J):
     assert redone[1] == len(sizes)
     plan.close()
     ref.close()
+
+
+def test_more_layers_than_a_workgroup_reports_at_once():
+    """20 thousand layers of one or two chunks more than the smallest tiled one: every workgroup of the recount counts more runs
+    than it keeps, and reports and scans in between."""
+    import torch
+    import paper_2312_08053_amd as kimad
+    from paper_2312_08053_amd.binding import KIMAD_CFG_SAMPLE_ALWAYS
+    sizes = [8193 + 7 * (i % 3) for i in range(20000)]
+    n, J = sum(sizes), 3
+    ratios = [0.001, 0.02, 0.3]
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    base = torch.randn(n, generator=gen, device="cuda")
+    g, h = base.clone(), torch.zeros(n, device="cuda")
+    plans = [kimad.Plan(g, h, sizes, ratios, D=1000, max_budget_bytes=n // 10, cfg_flags=f, capacity_pairs=1) for f in (0, KIMAD_CFG_SAMPLE_ALWAYS)]
+    start = np.concatenate([[0], np.cumsum(sizes)])
+    Kt = np.array([ko.grid_sizes(ratios, s) for s in sizes])
+    which = [0, 1, 2, 9999, 19998, 19999]
+    for factor in (1.0, 64.0):
+        torch.mul(base, factor, out=g)
+        tables = [p.profile(budget_hint_bytes=n // 10).cpu().numpy().reshape(len(sizes), J) for p in plans]
+        print("profiled", factor, flush=True)
+        assert np.array_equal(tables[0], tables[1])
+        x = {i: g[start[i]:start[i + 1]].cpu().numpy() for i in which}
+        E_ref = np.array([ko.topk_error_profile(x[i], Kt[i]) for i in which])
+        gh.assert_table_close(tables[0][which], E_ref, Kt[which], [sizes[i] for i in which])
+    assert plans[0].diagnostics()["redo_layers"] == len(sizes)
+    for p in plans:
+        p.close()
