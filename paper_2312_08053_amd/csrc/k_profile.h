@@ -553,73 +553,116 @@ __global__ __launch_bounds__(HIST2_THREADS, 6) void k_hist2(ProfileBuffers pb, u
     }
 }
 
-// Exact fallback, scan of a pool entry by 256 threads.  With the full key known, the squares of the
+// Exact fallback, scan of a pool entry by one wave.  With the full key known, the squares of the
 // `unsel` smallest entries of the prefix bin are summed exactly in fp64, smallest first.
-__device__ __forceinline__ void scan_pool_entry(const ProfileBuffers& pb, uint32_t f, double* err_table) {
-    __shared__ uint32_t su[16];
-    __shared__ double sd[16];
-    __shared__ uint32_t cum[D3_BINS];      // entries in lower digits
-    __shared__ double sumsq[D3_BINS];      // their squares
-    const uint32_t tid = threadIdx.x;
-    __syncthreads();                            // the previous entry's readers are done with the tables
-    const uint32_t prefix = pb.pool_prefix[f];
+// A quarter of the digits at a time goes through `stage`, the wave's part of LDS: read from memory in whole lines, summed up
+// sixteen neighbouring digits a lane.  (Four words of them lie at a place that a lane's number moves, so that sixteen lanes'
+// reads fall on all banks.  Entries that need this are ties as a rule, so most digits are empty, and passed over.)
+constexpr uint32_t SCAN3_WORDS = D3_BINS / 4u;
+__device__ __forceinline__ void scan_pool_entry(const ProfileBuffers& pb, uint32_t f, double* err_table, uint32_t* stage) {
+    constexpr uint32_t QUARTERS = 4, PAIRS = SCAN3_WORDS / 128u;
+    static_assert(SCAN3_WORDS == 64u * 16u, "sixteen digits a lane");
+    const uint32_t lane = lane_id();
+    const uint32_t prefix = pb.pool_prefix[f], t0 = pb.pool_t0[f], targets = pb.pool_cnt[f];
+    const uint32_t my_unsel = lane < targets ? pb.tgt_unsel[t0 + lane] : 0u;
+    const double my_base = lane < targets ? pb.tgt_base[t0 + lane] : 0.0;
     const uint32_t* h = pb.pool_hist + (size_t)f * D3_BINS;
-    uint32_t c[16];
-    double s[16];
-    uint32_t csum = 0;
-    double ssum = 0.0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) c[k] = __hip_atomic_load(h + tid * 16u + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const uint32_t d3 = tid * 16u + k;
+    auto square = [&](uint32_t d3) {
         const double v = (double)__uint_as_float((prefix << D2_SHIFT) | d3);
-        s[k] = (double)c[k] * v * v;
-        csum += c[k];
-        ssum += s[k];
-    }
-    const uint32_t cex = block_exclusive_scan<uint32_t>(csum, su, nullptr);
-    const double sex = block_exclusive_scan<double>(ssum, sd, nullptr);
-    {
-        uint32_t rc = cex;
-        double rs = sex;
+        return v * v;
+    };
+    unsigned long long v[PAIRS];
+    auto ask = [&](uint32_t q) {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            cum[tid * 16u + k] = rc;
-            sumsq[tid * 16u + k] = rs;
-            rc += c[k];
-            rs += s[k];
+        for (uint32_t i = 0; i < PAIRS; ++i)
+            v[i] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(h + q * SCAN3_WORDS) + i * 64u + lane, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+    };
+    uint32_t cex[QUARTERS], ctot = 0u;          // entries in digits below the lane's, their squares
+    double sex[QUARTERS], stot = 0.0;
+    ask(0u);
+#pragma unroll
+    for (uint32_t q = 0; q < QUARTERS; ++q) {
+        wave_sync_lds();
+#pragma unroll
+        for (uint32_t i = 0; i < PAIRS; ++i) {
+            const uint32_t owner = 8u * i + lane / 8u, four = (lane / 2u) & 3u;
+            *reinterpret_cast<unsigned long long*>(stage + 16u * owner + 4u * (four ^ ((owner >> 2) & 3u)) + 2u * (lane & 1u)) = v[i];
         }
+        if (q + 1u < QUARTERS) ask(q + 1u);
+        wave_sync_lds();
+        uint32_t csum = 0u;
+        double ssum = 0.0;
+#pragma unroll
+        for (uint32_t four = 0; four < 4u; ++four) {
+            const uint4 c = *reinterpret_cast<const uint4*>(stage + 16u * lane + 4u * (four ^ ((lane >> 2) & 3u)));
+            const uint32_t d3 = q * SCAN3_WORDS + 16u * lane + 4u * four;
+            const uint32_t sum = c.x + c.y + c.z + c.w;
+            if (ballot(sum != 0u) == 0ull) continue;
+            csum += sum;
+            ssum += (double)c.x * square(d3);
+            ssum += (double)c.y * square(d3 + 1u);
+            ssum += (double)c.z * square(d3 + 2u);
+            ssum += (double)c.w * square(d3 + 3u);
+        }
+        cex[q] = ctot;
+        sex[q] = stot;
+        if (ballot(csum != 0u) == 0ull) continue;
+        const uint32_t ci = wave_scan_add_u32(csum);
+        const double si = wave_inclusive_scan<double>(ssum), before = __shfl_up(si, 1, 64);
+        cex[q] += ci - csum;
+        if (lane) sex[q] += before;
+        ctot += (uint32_t)__builtin_amdgcn_readlane((int)ci, 63);
+        stot += __shfl(si, 63, 64);
     }
-    __syncthreads();
-    const uint32_t t0 = pb.pool_t0[f], cnt = pb.pool_cnt[f];
-    for (uint32_t k = tid; k < cnt; k += 256) {
-        const uint32_t t = t0 + k;
-        const uint32_t unsel = pb.tgt_unsel[t];
+    for (uint32_t k = 0; k < targets; ++k) {
+        const uint32_t unsel = (uint32_t)__builtin_amdgcn_readlane((int)my_unsel, (int)k);
         double U = 0.0;
         if (unsel) {
-            // largest digit d with cum[d] < unsel: digits below d are dropped whole
-            uint32_t lo = 0, hi = D3_BINS - 1;
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi + 1) >> 1;
-                if (cum[mid] < unsel) lo = mid; else hi = mid - 1;
+            // the last lane with fewer than `unsel` entries below its digits, then the last such digit: all below it are dropped whole
+            uint32_t quarter = 0u, owner = 0u, below = 0u;
+#pragma unroll
+            for (uint32_t q = 0; q < QUARTERS; ++q) {
+                const uint64_t fewer = ballot(cex[q] < unsel);
+                if (!fewer) continue;
+                quarter = q;
+                owner = 63u - (uint32_t)__clzll((long long)fewer);
+                below = (uint32_t)__builtin_amdgcn_readlane((int)cex[q], (int)owner);
+                U = __shfl(sex[q], (int)owner, 64);
             }
-            const double v = (double)__uint_as_float((prefix << D2_SHIFT) | lo);
-            U = sumsq[lo] + (double)(unsel - cum[lo]) * v * v;
+            const uint32_t d0 = quarter * SCAN3_WORDS + 16u * owner;
+            const uint32_t c = __hip_atomic_load(h + d0 + (lane & 15u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            uint32_t d = 0u;
+            for (; d < 15u; ++d) {
+                const uint32_t cd = (uint32_t)__builtin_amdgcn_readlane((int)c, (int)d);
+                if (below + cd >= unsel) break;
+                below += cd;
+                U += (double)cd * square(d0 + d);
+            }
+            U += (double)(unsel - below) * square(d0 + d);
         }
-        err_table[t] = pb.tgt_base[t] + U;
-        atomicAdd(&pb.diag[1], 1u);
+        if (lane == k) err_table[t0 + k] = my_base + U;
     }
+    if (lane == 0) atomicAdd(&pb.diag[1], targets);
 }
 
 // Exact fallback: last-digit histogram of every pooled prefix bin.  One workgroup per tile; tiles of layers without pool
-// entries return at once.  A layer's entries are scanned by the workgroup that counts the last of its tiles, so that no
-// workgroup waits for another.  (A launch of its own for the scans took 4.5 to 5.5 us where there was nothing to scan.)
-__global__ __launch_bounds__(256) void k_hist3p(ProfileBuffers pb, uint32_t ntiles, double* err_table, uint32_t mark_fresh) {
+// entries return at once.  A layer's entries are scanned by the workgroup that counts the last of its tiles, a wave an
+// entry, so that no workgroup waits for another.  The counting is bound by the loads and additions to memory under way,
+// so the scan is kept to what leaves a SIMD eight waves (64 registers; 4 KB of LDS a wave); sixteen waves take a layer's entries,
+// 64 at most, in four turns.
+// (us by events, as two launches, with a scan by whole workgroups of 256 threads one entry after another, and now.  No entries, as
+// a rule: 12.3, 6.0, 6.0.  About 30 entries a layer: one of 20 thousand 33, 190, 27; of 1 M 318, 473, 320; a perceptron's two 78,
+// 283, 78; 700 of 9 to 30 thousand 1080, 2900, 810; ResNet-50's 2100, 2750, 2050; 50 of the GPT-2-shaped set 14400, 14700, 13500.
+// 512 threads: the same but for 1 M 329, a perceptron 91.  At most 512 or 2048 workgroups: GPT-2-shaped 14100 and 13900.)
+constexpr uint32_t HIST3_THREADS = 1024;
+__global__ __launch_bounds__(HIST3_THREADS, 8) void k_hist3p(ProfileBuffers pb, uint32_t ntiles, double* err_table, uint32_t mark_fresh) {
     __shared__ uint32_t pfx[KIMAD_MAX_J_CONST];   // a layer has at most J pooled prefixes
     __shared__ uint32_t pid[KIMAD_MAX_J_CONST];
     __shared__ uint32_t npool, sh_last;
-    const uint32_t tid = threadIdx.x;
+    __shared__ __align__(16) uint32_t stage[HIST3_THREADS / 64u][SCAN3_WORDS];
+    const uint32_t tid = threadIdx.x, lane4 = 4u * lane_id();
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
     if (blockIdx.x == 0 && tid == 0 && mark_fresh) *pb.fresh = 1u;     // the grid profile's last kernel on the caller's stream
     if (pb.diag[2] == 0u) return;               // no pool entries at all: the usual case
     for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
@@ -630,7 +673,7 @@ __global__ __launch_bounds__(256) void k_hist3p(ProfileBuffers pb, uint32_t ntil
     if (tid == 0) npool = 0;
     __syncthreads();
     const uint32_t total = min(pb.diag[2], pb.pool_cap);
-    for (uint32_t f = tid; f < total; f += 256) {
+    for (uint32_t f = tid; f < total; f += HIST3_THREADS) {
         if (pb.pool_big[f] == (uint32_t)L.big) {
             const uint32_t k = atomicAdd(&npool, 1u);
             if (k < KIMAD_MAX_J_CONST) { pfx[k] = pb.pool_prefix[f]; pid[k] = f; }
@@ -639,10 +682,9 @@ __global__ __launch_bounds__(256) void k_hist3p(ProfileBuffers pb, uint32_t ntil
     __syncthreads();
     const uint32_t np = min(npool, (uint32_t)KIMAD_MAX_J_CONST);
     const uint32_t vbase = (tile - L.tile0) * pb.tile_elems;
-    const uint32_t iters = pb.tile_elems / 1024u;
-    for (uint32_t it = 0; it < iters; ++it) {
+    for (uint32_t v = 256u * wave; v < pb.tile_elems; v += 4u * HIST3_THREADS) {
         Quad q;
-        load_quad(L, vbase + it * 1024u + tid * 4u, q);
+        load_quad(L, vbase + v + lane4, q);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const uint32_t key = q.key[c];
@@ -668,10 +710,8 @@ __global__ __launch_bounds__(256) void k_hist3p(ProfileBuffers pb, uint32_t ntil
     __syncthreads();
     if (tid == 0) sh_last = atomicAdd(&pb.tiles_done[L.big], 1u) + 1u == L.ntiles ? 1u : 0u;
     __syncthreads();
-    if (sh_last) {
-        __threadfence();
-        for (uint32_t k = 0; k < np; ++k) scan_pool_entry(pb, pid[k], err_table);
-    }
+    if (sh_last)
+        for (uint32_t k = wave; k < np; k += HIST3_THREADS / 64u) scan_pool_entry(pb, (uint32_t)__builtin_amdgcn_readfirstlane(pid[k]), err_table, stage[wave]);
     }
 }
 

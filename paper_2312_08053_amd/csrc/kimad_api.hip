@@ -493,7 +493,7 @@ int run_select_passes(kimad_plan* p, const uint32_t* ktab_dev, uint32_t J, doubl
         KLAUNCH(p, s, "k_hist2", k_hist2, dim3(lo.B + (lo.ntiles + group - 1) / group), dim3(HIST2_THREADS), p->pb, lo.B, lo.ntiles, group,
                 (const uint32_t*)nullptr, 0u, ktab_dev, J, err_table, CERT_TOL, 0.0);
         // exact last-digit pass for the entries that the scan could not certify (usually none)
-        if (err_table) KLAUNCH(p, s, "k_hist3p", k_hist3p, dim3(lo.ntiles), dim3(256), p->pb, lo.ntiles, err_table, mark_fresh);
+        if (err_table) KLAUNCH(p, s, "k_hist3p", k_hist3p, dim3(std::min<uint32_t>(lo.ntiles, FALLBACK_GRID)), dim3(HIST3_THREADS), p->pb, lo.ntiles, err_table, mark_fresh);
     }
     return KIMAD_OK;
 }
@@ -563,7 +563,7 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
     KLAUNCH(p, s, "k_hist2", k_hist2, dim3(lo.B + std::min<uint32_t>((lo.ntiles + group - 1) / group, RECOUNT_GRID)), dim3(HIST2_THREADS), p->pb,
             lo.B, lo.ntiles, group, (const uint32_t*)(at<uint32_t>(p, lo.diag) + 3), 1u, ktab, J, err_table, CERT_TOL, SLOT_WIDEN);
     if (!err_table) return KIMAD_OK;
-    KLAUNCH(p, s, "k_hist3p", k_hist3p, dim3(std::min<uint32_t>(lo.ntiles, FALLBACK_GRID)), dim3(256), p->pb, lo.ntiles, err_table, 1u);
+    KLAUNCH(p, s, "k_hist3p", k_hist3p, dim3(std::min<uint32_t>(lo.ntiles, FALLBACK_GRID)), dim3(HIST3_THREADS), p->pb, lo.ntiles, err_table, 1u);
     return KIMAD_OK;
 }
 

@@ -61,7 +61,14 @@ def test_two_recount_workgroups_share_a_compute_unit(kernels):
     assert k["private_segment_fixed_size"] == 0, k
 
 
-@pytest.mark.parametrize("kernel", ["k_hist2"])
+def test_the_exact_pass_counts_with_all_waves(kernels):
+    """Its counting is bound by the loads and additions under way: what the scan takes must not cost it waves."""
+    k = kernels["k_hist3p"]
+    assert resident(k) * -(-k["max_flat_workgroup_size"] // 64) == 4 * WAVES, k
+    assert k["private_segment_fixed_size"] == 0, k
+
+
+@pytest.mark.parametrize("kernel", ["k_hist2", "k_hist3p"])
 def test_a_finished_layer_writes_no_cache_back(code, kernel):
     """A workgroup that finds a layer complete reads sums that were added beyond the caches: nothing is to be written back, and
     a write-back holds up everything that goes through that cache (twice the time of a recount)."""
