@@ -71,12 +71,14 @@ __device__ __forceinline__ double min_over_rows(double v) {
 // Bound by the chain barrier, LDS read, four fp64 additions, minimum over the rows, LDS write: 0.22 us a layer in the first
 // workgroup, and 1 to 2 us that each workgroup starts behind the one below it.  (The compute waves wait for no memory at
 // all: with the records asked for by them, and the cells' stores in the same queue, a layer took 0.4 us.  148 layers of
-// 999 cells: 4 compute waves 61 us, 8 62, 3 65; one loader wave a group 71, two 61, four 62; four groups of one wave 91.
+// 999 cells: one loader wave a group 71 us, two 61, four 62; four groups of one wave 91.
 // Few layers want few workgroups, each of which starts behind the one below, many a short layer: all launches of the
-// allocation with 64 ratios and four or eight waves, 20 layers 32 and 30 us, 60 56 and 52, 148 85 and 83, 500 198 and 209, 1000
-// 357 and 384; with 2000 cells, before the winners were found beside the chain, 60 layers 79 and 67.  Rows beyond 2048 cells
-// take four, whose loaders leave no room for eight: 148 layers of 4097 cells 260 and 455, before that too.)
-constexpr uint32_t CHAIN_NARROW_L = 128;        // layers from which on four waves look after rows of up to 1024 cells
+// allocation with rows of 1001 cells, 64 ratios and four or eight waves, 20 layers 32.9 and 30.7 us, 60 55.9 and 52.3, 128 78.6 and 76.5,
+// 161 89.8 and 88.5, 218 107.9 and 108.9, 300 134.7 and 138.5, 500 198 and 210, 1000 357 and 386; with 16 ratios 60 47.8 and
+// 44.0, 148 73.6 and 72.1, 300 118 and 122.  With 2001 cells the two are the same (60 layers 86.1 and 86.0, 148 169.8 and 169.7, 300 214.7
+// and 213.4).  Rows beyond 2048 cells take four, whose loaders leave no room for eight: 60 layers of 4097 cells 126 and, with three
+// waves a loader group, 192, 148 layers 244 and 396.)
+constexpr uint32_t CHAIN_NARROW_L = 192;        // layers beyond which four waves look after rows of up to 1024 cells
 constexpr uint32_t CHAIN_LOADERS = 2;
 constexpr uint32_t CHAIN_RECS = 4;              // layers whose records are in LDS, and under way from memory
 static_assert(CHAIN_RECS % 2 == 0, "the rows change places every layer");
@@ -242,8 +244,10 @@ __device__ __forceinline__ void chain_load(const AllocBuffers& ab, const double*
 // have a workgroup for every BLOCK_CELLS of their cells.  (us, with a launch of one workgroup per layer and 256 cells after the
 // chain and a walk of one step a layer, and now.  148 layers of 999 cells: chain 59, choice 8, walk 18; chain 64, walk 10.  62
 // layers with up to 50 candidates: 31, 10 and 12; 38 and 9.  All launches of the allocation, 64 ratios: 20 layers 36 and 31, 500
-// 230 and 197, 1000 421 and 353; 148 layers of 4097 cells 260 and 245.  Pieces of four throughout: chain 73 and 43; of two, 67
-// and 41.)
+// 230 and 197, 1000 421 and 357; 148 layers of 4097 cells 260 and 245.)
+// (Blocks of 128, 256 and 512 cells, us: all launches of the allocation, 20 layers 30.3, 30.5, 31.0, 148 84.2, 84.0, 84.0; the chain in
+// the steps of ResNet-18 with 50 ratios 40.8, 41.5, 41.7, of the GPT-2-shaped set 65.4, 65.5, 65.9; that set's round with the allocation
+// beside it, whose kernels go without the compute units that wait here, 415, 404, 400.)
 constexpr uint32_t BLOCK_CELLS = 256;
 
 struct PieceList {

@@ -25,7 +25,7 @@ def _withheld(plan, table, budget, polls):
 
 
 # one workgroup and many of each width, and the single waves of rows beyond LDS
-@pytest.mark.parametrize("cells,L", [(40, 3), (65, 3), (700, 9), (1024, 130), (2000, 20), (4224, 7), (4300, 3), (20011, 12)])
+@pytest.mark.parametrize("cells,L", [(40, 3), (65, 3), (700, 9), (1024, 130), (1024, 193), (2000, 20), (4224, 7), (4300, 3), (20011, 12)])
 @pytest.mark.parametrize("J", [5, 20, 40])
 def test_a_workgroup_that_never_comes_ends_in_an_error(cells, L, J):
     import torch
