@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 FULL = 2
 
 
-def _case(cells, J, L, seed):
+def _case(cells, J, L, seed, ties=None):
     rng = np.random.default_rng(seed)
     ratios = np.sort(rng.uniform(0.0, 1.0, size=J)) ** 3 + np.linspace(1e-6, 1e-3, J)
     ratios = np.minimum(ratios / ratios[-1], 1.0)
@@ -19,7 +19,7 @@ def _case(cells, J, L, seed):
     sizes = [int(x) for x in rng.integers(lo, 8 * lo + 40, size=L)]
     Kt = np.array([ko.grid_sizes(ratios, n) for n in sizes])
     E = np.sort(rng.random((L, J)) * 10.0 ** rng.uniform(-6, 6, size=(L, 1)), axis=1)[:, ::-1].copy()
-    if seed % 3 == 0:
+    if seed % 3 == 0 if ties is None else ties:
         E = np.round(E, 1)                       # ties between totals
     return ratios, sizes, Kt, E
 
@@ -65,6 +65,24 @@ def test_pieces_that_the_walk_goes_through(cells, L):
     assert int(st.item()) == st_ref
     if st_ref == ko.OK:
         assert np.array_equal(j.cpu().numpy(), j_ref) and np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
+    plan.close()
+
+
+@pytest.mark.parametrize("ties", [False, True])
+@pytest.mark.parametrize("L,cells", [(L, c) for L in (25, 28, 29, 61) for c in (257, 1000, 1030, 2049)] +
+                         [(191, 1000), (192, 1000), (193, 300), (193, 1000), (193, 1024), (193, 1025), (220, 2049)])
+def test_ties_within_pieces(L, cells, ties):
+    """Layers in pieces of four, with equal totals and without, in each of the kernels of rows that fit LDS (four waves a
+    workgroup beyond 192 layers of up to 1024 cells, and beyond 2048 cells)."""
+    import torch
+    ratios, sizes, Kt, E = _case(cells, 21, L, 5 * cells + L, ties)
+    budget = 8 * (cells - 1)
+    st_ref, j_ref, K_ref, off_ref = ko.allocate(E, Kt, budget, 8, 0)
+    assert st_ref == ko.OK
+    plan = _plan(sizes, ratios, budget)
+    j, K, off, st = plan.allocate(budget, torch.from_numpy(E.reshape(-1)).cuda())
+    assert int(st.item()) == st_ref
+    assert np.array_equal(j.cpu().numpy(), j_ref) and np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
     plan.close()
 
 
