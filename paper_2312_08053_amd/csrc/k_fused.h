@@ -805,7 +805,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint3
 // parts' heads, the parts, the stores): a wave looks after a block by itself.  A layer of more than REDUCE_WAVE_PARTS parts
 // has a workgroup to every block, whose waves take a quarter of the parts each.  The host lists the workgroups (reduce_wgs).
 // (us with a workgroup to every block of every layer, and now: ResNet-50 14.6 and 10.5, GPT-2-shaped, whose embedding has 80
-// parts, 14.2 and 12.9, Llama-shaped 38 and 25.)
+// parts, 14.2 and 12.9, Llama-shaped 38 and 25.  The line, us by events with waves up to 8, 16 and 32 parts: Llama-shaped 35.3, 27.4,
+// 27.3, ResNet-50 13.2, 13.4, 14.6, with a wide link 15.2, 15.3, 17.1, ResNet-18 with 50 ratios 14.5, 14.0, 14.4.)
 constexpr uint32_t LAYER_ENTRIES = D1_BINS + SLOT_STRIDE * D2_BINS;
 constexpr uint32_t REDUCE_ENTRIES = 128;        // entries of a block: two per lane
 constexpr uint32_t REDUCE_BLOCKS = LAYER_ENTRIES / REDUCE_ENTRIES, REDUCE_WAVE_PARTS = 16;
