@@ -803,14 +803,15 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint3
 // bin 0: the exact squares).
 // Most layers have a handful of parts, and what a block takes is a chain of memory round trips (the layer's state and the
 // parts' heads, the parts, the stores): a wave looks after a block by itself.  A layer of more than REDUCE_WAVE_PARTS parts
-// has a workgroup to every block, whose waves take a quarter of the parts each.  The host lists the workgroups (reduce_wgs).
+// has a workgroup to every block, whose waves take a quarter of the parts each.  The host lists these layers first (reduce_layers).
 // (us with a workgroup to every block of every layer, and now: ResNet-50 14.6 and 10.5, GPT-2-shaped, whose embedding has 80
-// parts, 14.2 and 12.9, Llama-shaped 38 and 25.  The line, us by events with waves up to 8, 16 and 32 parts: Llama-shaped 35.3, 27.4,
-// 27.3, ResNet-50 13.2, 13.4, 14.6, with a wide link 15.2, 15.3, 17.1, ResNet-18 with 50 ratios 14.5, 14.0, 14.4.)
+// parts, 14.2 and 12.9, Llama-shaped 38 and 25.  The line, us by events with waves up to 8, 16 and 32 parts: Llama-shaped 35.0, 25.6,
+// 25.8, ResNet-50 12.6, 12.6, 14.0, with a wide link 14.2, 14.4, 16.4, ResNet-18 with 50 ratios 14.4, 14.1, 14.7.  With a list of the
+// workgroups in the place of one of the layers, Llama-shaped 27.5, ResNet-50 13.0.)
 constexpr uint32_t LAYER_ENTRIES = D1_BINS + SLOT_STRIDE * D2_BINS;
 constexpr uint32_t REDUCE_ENTRIES = 128;        // entries of a block: two per lane
 constexpr uint32_t REDUCE_BLOCKS = LAYER_ENTRIES / REDUCE_ENTRIES, REDUCE_WAVE_PARTS = 16;
-constexpr uint32_t REDUCE_SPLIT = 0x80000000u;  // in ReduceWg::block: the four waves share the block
+inline uint32_t reduce_workgroups(uint32_t nbig, uint32_t nsplit) { return nsplit * REDUCE_BLOCKS + (nbig - nsplit) * (REDUCE_BLOCKS / 4u); }
 static_assert(REDUCE_BLOCKS * REDUCE_ENTRIES == LAYER_ENTRIES && REDUCE_BLOCKS % 4u == 0u, "four whole blocks to a workgroup");
 
 // Counts and sums of lanes' two entries e, e + 1 as the scans read them.
@@ -871,21 +872,24 @@ __device__ __forceinline__ void reduce_wide(const ulonglong2 v, unsigned long lo
     cnt[1] += v.y >> 44; t[1] += v.y & PK_MASK;
 }
 
-__global__ __launch_bounds__(256) void k_reduce_parts(ProfileBuffers pb) {
+// nsplit: layers whose blocks take a workgroup each.
+__global__ __launch_bounds__(256) void k_reduce_parts(ProfileBuffers pb, uint32_t nsplit) {
     __shared__ unsigned long long sh_c[3][REDUCE_ENTRIES], sh_t[3][REDUCE_ENTRIES];
     constexpr uint32_t LIST = 1024;
     __shared__ uint32_t list[LIST], listed[2];
     const uint32_t lane = threadIdx.x & 63u, w = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const ReduceWg wg = pb.reduce_wgs[blockIdx.x];
-    const uint32_t big = wg.big, p0 = wg.part0, np = wg.nparts;
+    const bool split = blockIdx.x < nsplit * REDUCE_BLOCKS;
+    const uint32_t x = split ? blockIdx.x : blockIdx.x - nsplit * REDUCE_BLOCKS, per = split ? REDUCE_BLOCKS : REDUCE_BLOCKS / 4u;
+    const ReduceLayer of = pb.reduce_layers[split ? x / per : nsplit + x / per];
+    const uint32_t big = of.big, p0 = of.part0, np = of.nparts;
     // The totals over the layers that the prediction of this profile read are done with (that launch has ended), and
     // the scan that follows this one adds the new ones up: cleared here, between the two.
     if (blockIdx.x == 0u)
         for (uint32_t b = threadIdx.x; b < D1_BINS; b += 256u) pb.gprev[b] = 0ull;
     static_assert(REDUCE_ENTRIES == PART_BLOCK, "one block per block");
     unsigned long long cnt[2] = {0, 0}, t[2] = {0, 0}, zeros_sq = 0;
-    if (!(wg.block & REDUCE_SPLIT)) {
-        const uint32_t blk = wg.block + w, word = 1u + blk / 32u;
+    if (!split) {
+        const uint32_t blk = 4u * (x % per) + w, word = 1u + blk / 32u;
         const bool slot = blk >= D1_BINS / PART_BLOCK;
         // lane k has part k's head, which block it holds how
         const uint32_t* h = pb.part_head + (size_t)(p0 + min(lane, np - 1u)) * PART_HEAD;
@@ -935,7 +939,7 @@ __global__ __launch_bounds__(256) void k_reduce_parts(ProfileBuffers pb) {
         reduce_store(pb, big, blk, lane, cnt, t, zeros_sq);
         return;
     }
-    const uint32_t blk = wg.block & ~REDUCE_SPLIT, word = 1u + blk / 32u;
+    const uint32_t blk = x % per, word = 1u + blk / 32u;
     const uint32_t e = blk * REDUCE_ENTRIES + 2u * lane;             // and e + 1
     const bool slot = blk >= D1_BINS / PART_BLOCK;
     const LayerState st = pb.state[big];

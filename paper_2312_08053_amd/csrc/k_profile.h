@@ -8,8 +8,8 @@
 
 namespace kimad {
 
-// A workgroup of k_reduce_parts: a layer's parts (there is room for one every PK_MAX_CHUNKS chunks), and its first block.
-struct ReduceWg { uint32_t big, block, part0, nparts; };
+// A layer that k_reduce_parts sums up: its parts (there is room for one every PK_MAX_CHUNKS chunks).
+struct ReduceLayer { uint32_t big, part0, nparts, pad; };
 
 struct ProfileBuffers {
     const LayerDesc* layers;
@@ -63,7 +63,7 @@ struct ProfileBuffers {
     uint32_t* part_head;          // [nparts][PART_HEAD] whether there is one, and how its blocks were written
     unsigned long long* parts;    // [nparts][PART_STRIDE] the LDS entries, in blocks, then the exact bin-0 sum
     const uint32_t* wg_part0;     // [workgroups] first part of each workgroup (its parts follow in order)
-    const ReduceWg* reduce_wgs;   // what each workgroup of k_reduce_parts looks after
+    const ReduceLayer* reduce_layers;   // [B] in the order of k_reduce_parts' workgroups
     const uint32_t* chunk_big;    // chunk -> big index
     const uint32_t* chunk_first;  // chunk -> first chunk of its layer
     uint32_t nchunks_total;

@@ -2,6 +2,7 @@
 // Declarations and the contract of every entry point are in include/kimad.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -49,8 +50,8 @@ struct Layout {
     uint64_t fresh = 0, hprev = 0, gprev = 0;
     uint64_t zero1_begin, cnt1, sq1, cnt2, sq2, diag, layer_flag, shist, ghist, cursor, spill_over, tiles_done, zero1_end;
     uint64_t cprev = 0;
-    uint64_t big_tmp0, parts, part_head, wg_part0, reduce_wgs, zero1_mid;
-    uint32_t main_wgs = 256, chunks_per_wg = 1, nparts = 0, nreduce = 0;
+    uint64_t big_tmp0, parts, part_head, wg_part0, reduce_layers, zero1_mid;
+    uint32_t main_wgs = 256, chunks_per_wg = 1, nparts = 0, nsplit = 0;
     uint64_t pool_prefix, pool_big, pool_t0, pool_cnt, pool_hist, tgt_unsel, tgt_base;
     uint32_t pool_cap = 1;
     uint64_t lut1, nslots, slot_bin, slot_cnt, slot_sq;
@@ -121,16 +122,17 @@ uint32_t stream_workgroups(const kimad_config_t& cfg) {
 // histogram at every layer boundary and, where a count may fill up, no earlier than after PK_MAX_CHUNKS chunks.
 struct PartTables {
     std::vector<uint32_t> wg_part0, big_part0, big_nparts;
-    // the workgroups that sum the parts up: the layers whose blocks take a workgroup each first (they take longest)
-    std::vector<ReduceWg> reduce_wgs() const {
-        std::vector<ReduceWg> wgs;
+    // the layers in the order in which their parts are summed up: those whose blocks take a workgroup each (split) first,
+    // which take longest
+    std::vector<ReduceLayer> reduce_layers() const {
+        std::vector<ReduceLayer> layers;
         for (int split = 1; split >= 0; --split)
-            for (uint32_t b = 0; b < big_nparts.size(); ++b) {
-                if ((big_nparts[b] > REDUCE_WAVE_PARTS) != (split != 0)) continue;
-                for (uint32_t k = 0; k < REDUCE_BLOCKS; k += split ? 1u : 4u)
-                    wgs.push_back({b, k | (split ? REDUCE_SPLIT : 0u), big_part0[b], big_nparts[b]});
-            }
-        return wgs;
+            for (uint32_t b = 0; b < big_nparts.size(); ++b)
+                if ((big_nparts[b] > REDUCE_WAVE_PARTS) == (split != 0)) layers.push_back({b, big_part0[b], big_nparts[b], 0u});
+        return layers;
+    }
+    uint32_t nsplit() const {
+        return (uint32_t)std::count_if(big_nparts.begin(), big_nparts.end(), [](uint32_t n) { return n > REDUCE_WAVE_PARTS; });
     }
 };
 uint32_t plan_parts(const std::vector<HostLayer>& hl, uint32_t B, uint32_t nchunks, uint32_t wgs, uint32_t per,
@@ -218,7 +220,7 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     PartTables parts_local;
     PartTables& parts = parts_out ? *parts_out : parts_local;
     lo.nparts = plan_parts(*hl, B, lo.nchunks, lo.main_wgs, lo.chunks_per_wg, parts);
-    lo.nreduce = (uint32_t)parts.reduce_wgs().size();
+    lo.nsplit = parts.nsplit();
 
     uint64_t off = 0;
     auto take = [&](uint64_t bytes) { uint64_t o = off; off = align_up(off + bytes); return o; };
@@ -231,7 +233,7 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     lo.big_layer = take(4ull * (B ? B : 1));
     lo.big_tmp0 = take(8ull * (B ? B : 1));
     lo.wg_part0 = take(4ull * lo.main_wgs);
-    lo.reduce_wgs = take(sizeof(ReduceWg) * (uint64_t)(lo.nreduce ? lo.nreduce : 1));
+    lo.reduce_layers = take(sizeof(ReduceLayer) * (uint64_t)(B ? B : 1));
     // (the exact pass's pool of last-digit histograms lives in the same memory: the parts are dead once
     // k_reduce_parts has run, and a pool entry is cleared by the workgroup that takes it)
     lo.pool_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>((uint64_t)B * J, 1), POOL_LIMIT);
@@ -294,7 +296,7 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     lo.row0 = take(8 * lo.dp_cells);
     lo.row1 = take(8 * lo.dp_cells);
     lo.choice = take((uint64_t)L * align_up(lo.dp_cells));
-    lo.cprev = take(2ull * L * align_up(std::min<uint64_t>(lo.dp_cells, DP_ROW_MAX)));
+    lo.cprev = take(2ull * Pieces(L).count() * align_up(std::min<uint64_t>(lo.dp_cells, DP_ROW_MAX)));
     lo.dp_flags = take(16);
     lo.ncompact = take(16);
     lo.dl_wall = take(4 * LJ); lo.dl_w = take(4 * LJ); lo.dl_jj = take(4 * LJ); lo.dl_e = take(16 * LJ); lo.dl_n = take(4ull * L);
@@ -546,7 +548,7 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
     } else {
         KLAUNCH(p, s, "k_main", k_main<false>, dim3(p->main_wgs), dim3(FUSED_THREADS), p->pb, p->chunks_per_wg);
     }
-    KLAUNCH(p, s, "k_reduce_parts", k_reduce_parts, dim3(lo.nreduce), dim3(256), p->pb);
+    KLAUNCH(p, s, "k_reduce_parts", k_reduce_parts, dim3(reduce_workgroups(lo.B, lo.nsplit)), dim3(256), p->pb, lo.nsplit);
     if (err_table && !with_small) {
         rc = launch_small_profile(p, err_table, s, side);
         if (rc) return rc;
@@ -571,7 +573,7 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
 // Device memory the allocation's kernels work in besides their inputs and outputs.
 struct AllocScratch {
     double* row0; double* row1;          // per-layer-launch path only
-    uint8_t* choice; uint16_t* cprev;    // [L][pitch]
+    uint8_t* choice; uint16_t* cprev;    // [L][pitch], [pieces][pitch]
     uint32_t* flags;                     // 16 bytes
     DpLists dl;
     BandBuffers band;
@@ -857,7 +859,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
         for (uint32_t j = 0; j < J; ++j) p->ktab[(size_t)i * J + j] = grid_size_K(ratios[j], h.n);
         p->kmax[i] = p->ktab[(size_t)i * J + J - 1];
     }
-    const std::vector<ReduceWg> reduce = pt.reduce_wgs();
+    const std::vector<ReduceLayer> reduce = pt.reduce_layers();
     hipStream_t s = static_cast<hipStream_t>(stream);
     auto up = [&](uint64_t off, const void* src, size_t bytes) {
         return hipMemcpyAsync(p->ws + off, src, bytes, hipMemcpyHostToDevice, s) == hipSuccess;
@@ -869,7 +871,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
               up(lo.big_layer, big_layer.data(), 4ull * big_layer.size()) &&
               up(lo.big_tmp0, big_tmp0.data(), 8ull * big_tmp0.size()) &&
               up(lo.wg_part0, pt.wg_part0.data(), 4ull * pt.wg_part0.size()) &&
-              (reduce.empty() || up(lo.reduce_wgs, reduce.data(), sizeof(ReduceWg) * reduce.size())) &&
+              (reduce.empty() || up(lo.reduce_layers, reduce.data(), sizeof(ReduceLayer) * reduce.size())) &&
               up(lo.small_layer, small_layer.data(), 4ull * small_layer.size()) &&
               up(lo.swg_layer, swg_layer.data(), 4ull * swg_layer.size()) &&
               up(lo.swg_first, swg_first.data(), 4ull * swg_first.size()) &&
@@ -901,7 +903,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
     pb.tgt_unsel = at<uint32_t>(p, lo.tgt_unsel); pb.tgt_base = at<double>(p, lo.tgt_base);
     pb.state = at<LayerState>(p, lo.state); pb.big_tmp0 = at<uint64_t>(p, lo.big_tmp0);
     pb.parts = at<unsigned long long>(p, lo.parts); pb.part_head = at<uint32_t>(p, lo.part_head); pb.wg_part0 = at<uint32_t>(p, lo.wg_part0);
-    pb.reduce_wgs = at<ReduceWg>(p, lo.reduce_wgs);
+    pb.reduce_layers = at<ReduceLayer>(p, lo.reduce_layers);
     pb.chunk_big = at<uint32_t>(p, lo.chunk_big); pb.chunk_first = at<uint32_t>(p, lo.chunk_first); pb.nchunks_total = lo.nchunks;
     pb.swg_layer = at<uint32_t>(p, lo.swg_layer); pb.swg_first = at<uint32_t>(p, lo.swg_first);
     pb.shist = at<uint32_t>(p, lo.shist); pb.ghist = at<unsigned long long>(p, lo.ghist);
@@ -1006,7 +1008,7 @@ int kimad_allocate_static(kimad_plan_t* p, const double* err_table, uint64_t bud
     AllocScratch ws;
     ws.row0 = nullptr; ws.row1 = nullptr;                       // only the per-layer-launch path uses them
     ws.choice = reinterpret_cast<uint8_t*>(take((uint64_t)KIMAD_STATIC_MAX_L * CELLS));
-    ws.cprev = reinterpret_cast<uint16_t*>(take(2ull * KIMAD_STATIC_MAX_L * CELLS));
+    ws.cprev = reinterpret_cast<uint16_t*>(take(2ull * Pieces(KIMAD_STATIC_MAX_L).count() * CELLS));
     ws.flags = reinterpret_cast<uint32_t*>(take(16));
     ws.dl.wall = reinterpret_cast<uint32_t*>(take(4 * LJ)); ws.dl.w = reinterpret_cast<uint32_t*>(take(4 * LJ));
     ws.dl.jj = reinterpret_cast<uint32_t*>(take(4 * LJ)); ws.dl.e = reinterpret_cast<double*>(take(16 * LJ));

@@ -112,3 +112,11 @@ def test_workspace_is_a_quarter_of_the_gradient_buffers_at_most():
         n = [shapes.numel(s) for s in sizes]
         ws = kimad.kimad_workspace_bytes(n, 64, D=1000)
         assert ws <= 0.25 * 8 * sum(n), (ws, 8 * sum(n))
+
+
+def test_the_workspace_holds_no_table_of_workgroups():
+    """What a plan needs beside the tables of its layers' bins: the lists of workgroups took 816 bytes a tiled layer, and the
+    allocation's cells were taken for every layer, where there is a row for four of them."""
+    import paper_2312_08053_amd as kimad
+    assert kimad.kimad_workspace_bytes([9000] * 3000, 64, D=1000, max_budget_bytes=2_000_000) <= 2_314_900_224 - 3000 * 1024
+    assert kimad.kimad_workspace_bytes([100] * 3000, 16, D=1000, max_budget_bytes=200_000) <= 39_365_376 - 3000 * 1024
