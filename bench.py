@@ -27,6 +27,18 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0           # MI355X HBM3E, published peak
 
 STREAMING_KERNELS = ("k_main", "k_hist1", "k_hist2", "k_candidates")
+PROFILE_KERNELS = ("k_sample", "k_predict", "k_main", "k_reduce_parts", "k_scan1x", "k_hist2c", "k_hist1", "k_scan1", "k_hist2",
+                   "k_hist3p", "k_small_profile")
+
+
+def stage_of(kernel: str):
+    """The stage of a step that a kernel is booked under.  (A step's look-up of the selected sizes, of the compression's, is part
+    of the allocation's last kernel and booked with it.)"""
+    if kernel.startswith("k_dp") or kernel == "k_dense_view":
+        return "allocate"
+    if kernel in PROFILE_KERNELS:
+        return "profile"
+    return None if kernel == "k_zero16" else "compress"
 
 
 def main() -> int:
@@ -199,13 +211,8 @@ def main() -> int:
         del settle
     stage_ms = {"profile": 0.0, "allocate": 0.0, "compress": 0.0}
     for n, v in kern.items():
-        if n.startswith("k_dp"):
-            stage_ms["allocate"] += v["ms_per_step"]
-        elif n in ("k_sample", "k_predict", "k_main", "k_scan1x", "k_hist2c", "k_hist1", "k_scan1", "k_hist2",
-                   "k_hist3p", "k_small_profile"):
-            stage_ms["profile"] += v["ms_per_step"]
-        elif n != "k_zero16":
-            stage_ms["compress"] += v["ms_per_step"]
+        if stage_of(n):
+            stage_ms[stage_of(n)] += v["ms_per_step"]
 
     d_big = int(sum(int(n) for n in work.sizes if int(n) > 8192))
     # algorithmic bytes of a streaming kernel: it must read g and h of the tiled layers once
