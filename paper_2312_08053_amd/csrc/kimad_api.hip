@@ -1101,22 +1101,6 @@ int kimad_allocate_diagnostics(kimad_plan_t* p, uint32_t* out4, void* stream) {
     return KIMAD_OK;
 }
 
-#ifdef KIMAD_STAMPS
-int kimad_debug_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t* cfg, uint64_t* out) {
-    Layout lo;
-    int rc = make_layout(n, L, J, *cfg, lo, nullptr);
-    if (rc) return rc;
-    out[0] = lo.parts; out[1] = lo.small_layer; out[2] = lo.state; out[3] = lo.cnt1; out[4] = lo.rec_cnt; out[5] = lo.hprev;
-    out[6] = lo.pool_prefix; out[7] = lo.sel; out[8] = lo.hist3; out[9] = lo.rec_start; out[10] = lo.tmp_i;
-    out[11] = lo.tmp_x; out[12] = lo.row0; out[13] = lo.total;
-    return 0;
-}
-int kimad_debug_band_info(kimad_plan_t* p, uint32_t* out16) {
-    if (hipMemcpy(out16, p->ws + p->lo.band_info, 64, hipMemcpyDeviceToHost) != hipSuccess) return KIMAD_ERR_HIP;
-    return KIMAD_OK;
-}
-#endif
-
 int kimad_plan_set_timing(kimad_plan_t* p, int enable) {
     if (!p) return KIMAD_ERR_INVALID_ARG;
     if (enable && p->ev.empty()) {
