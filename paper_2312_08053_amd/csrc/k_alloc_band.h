@@ -531,6 +531,8 @@ __global__ __launch_bounds__(BANDED_THREADS) void k_dp_banded(AllocBuffers ab, D
         if (in) { s_row[r] = make_uint4(lo, hi - lo, at, rec); s_first[r] = (uint8_t)(live & 0xFFu); }
         cells += ct; live_total += lt;
     }
+    // (a lane without a record takes the way of whatever stands behind its layer's: for the last layer that is loaded, this)
+    for (uint32_t x = tid; x < BAND_LIVE_CAP; x += T) recs[x] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     const bool any_bad = s_bad != 0u, hopeless = bb.info[4] != 0u;
     const uint32_t wr = min(cap + 2u, BAND_CELLS / 2u - 1u);   // cells per row buffer when only two rows are kept
