@@ -357,7 +357,7 @@ constexpr uint32_t RECOUNT_GRID = 2048;
 // A hundredth kept, single pass and two histogram passes with a compaction, us: 4 layers 81 and 71 at 1 M elements, 95 and
 // 118 at 4 M; 60 layers 93 and 90 at 2.4 M, 101 and 133 at 6 M; one layer 98 and 93 at 2 M, 126 and 130 at 4 M, 134 and 196
 // at 8 M.  2000 layers of 9000 to 16000 elements 10 to 20 % the other way, of 24000 644 and 670.  On the headline set at
-// half a percent 337 and 811, and 900 in a round whose every layer the prediction misses, as when all gradients are 64
+// a hundredth 330 and 740, and 770 in a round whose every layer the prediction misses, as when all gradients are 64
 // times the round before's.
 constexpr uint32_t SINGLE_SELECT_CHUNKS = 3072;
 constexpr uint32_t SINGLE_SELECT_PER_LAYER = 24;
