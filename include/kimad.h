@@ -107,12 +107,13 @@ typedef struct kimad_config {
                                            the prediction: a layer it misses is recounted by a full pass. */
 #define KIMAD_CFG_FULL_DP 2ull          /* allocation: always run the recurrence over whole rows of cost cells */
 #define KIMAD_CFG_BAND_DP 4ull          /* allocation: always run it inside the band of cells that Lagrangian bounds
-                                           leave.  Same results either way; by default rows of 1537 cells or more
-                                           take the band (its cost hardly grows with the row; with up to 7 ratios
-                                           from 2049 on) unless the grid has one ratio or the layers have more than
-                                           7168 different costs in all; others the whole rows.  Rows that do not fit
-                                           LDS (more than 4224 cells) and plans of more than 1024 layers always take
-                                           whole rows. */
+                                           leave.  Same results either way; by default plans of 60 to 1024 layers
+                                           (from 24 on with rows of 1537 cells or more) go by a tree of segments,
+                                           and by whole rows where rounding might decide between two allocations;
+                                           fewer layers take the band with rows of 1537 cells or more (with up to 7
+                                           ratios from 2049 on), others the whole rows, as grids of one ratio do.
+                                           Rows that do not fit LDS (more than 4224 cells) and plans of more than
+                                           1024 layers always take whole rows. */
 
 #define KIMAD_CFG_DENSE_FALLBACK 8ull    /* allocation: a layer never costs more than its bare values (4 n bytes).  A grid
                                            point at or beyond the break-even K * pair_bytes >= 4 n stands for sending
@@ -256,7 +257,8 @@ int kimad_profile_diagnostics(kimad_plan_t* plan, uint32_t* out4, void* stream);
 /* DEVICE diagnostics of the last kimad_allocate on the plan (rows that fit LDS only), copied to HOST
  * (synchronises the stream): out[0] = widest band of cost cells the recurrence visited in a row, out[1] = sum of
  * the bands' widths over the rows, out[2] = 1 if the bands were the whole rows (no bound could be used),
- * out[3] = upgrades the upper bound's greedy fill took.  All zero before the first allocation. */
+ * out[3] = upgrades the upper bound's greedy fill took.  Rows long enough for the band that went by the tree of segments
+ * (KIMAD_CFG_BAND_DP): bands of one cell, or the whole rows where those decided.  All zero before the first allocation. */
 int kimad_allocate_diagnostics(kimad_plan_t* plan, uint32_t* out4, void* stream);
 
 /* Per-layer state of the last profile / compression, for benchmarks and tests (synchronises the

@@ -34,8 +34,11 @@ struct AllocBuffers {
 
 constexpr double DP_INF = __builtin_huge_val();
 
+// K / unit, rounded up.  (In 32 bits: a division in 64 is four times as long.)
 __device__ __forceinline__ uint32_t units_of(uint32_t K, uint64_t unit) {
-    return (uint32_t)(((uint64_t)K + unit - 1) / unit);
+    if (unit >> 32) return K ? 1u : 0u;
+    const uint32_t u = (uint32_t)unit, q = K / u;
+    return q + (q * u != K ? 1u : 0u);
 }
 
 // Dense fallback: a layer never costs more than its bare values (n * 4 bytes), so a grid point at or beyond the
@@ -125,6 +128,66 @@ constexpr uint32_t HULL_LAST = 0x80000000u;
 // A cell of a row that nobody has stored yet (a NaN that no total can be).
 constexpr unsigned long long ROW_EMPTY = ~0ull;
 
+// Stored row r of the recurrence, `pitch` cells apart, the first `pad` of them before cost 0, by `threads` threads of which this
+// is number `me`: ROW_EMPTY, and in row 0 the start.
+__device__ __forceinline__ void dp_fill_row(const AllocBuffers& ab, double* rows, uint64_t pitch, uint32_t pad, uint64_t r, uint32_t me, uint32_t threads) {
+    const uint64_t cells = ((uint64_t)pad + ab.cap + 64u) & ~63ull;            // (the pitch holds them)
+    unsigned long long* row = reinterpret_cast<unsigned long long*>(rows + r * pitch);
+    for (uint64_t x = 2ull * me; x < cells; x += 2ull * threads) {
+        ulonglong2 v = make_ulonglong2(ROW_EMPTY, ROW_EMPTY);
+        if (r == 0u || x < pad) v.x = x == pad ? 0ull : 0x7FF0000000000000ull;
+        if (r == 0u || x + 1u < pad) v.y = 0x7FF0000000000000ull;
+        *reinterpret_cast<ulonglong2*>(row + x) = v;
+    }
+}
+
+// Layer i's candidate list, lane j holding candidate j: where a run starts, its last member's error and the error before it.
+struct DpList {
+    uint32_t w, last;              // cost in units, last member of the run that starts here
+    double e_last, e_before;
+    bool start;
+    uint64_t starts, nonfinite;    // lanes where a run starts; with an Inf or a NaN
+};
+__device__ __forceinline__ DpList dp_list(const AllocBuffers& ab, uint32_t i, uint32_t j) {
+    DpList d;
+    const bool valid = j < ab.J;
+    d.w = 0xFFFFFFFFu;
+    double e = 0.0;
+    if (valid) {
+        d.w = units_of(ab.Ktab[(size_t)i * ab.J + j], ab.unit);
+        e = ab.E[(size_t)i * ab.J + j];
+    }
+    d.nonfinite = ballot(valid && !(e - e == 0.0));
+    const uint64_t over = ballot(valid && d.w > ab.cap);
+    const uint32_t n_in = over ? (uint32_t)__builtin_ctzll(over) : ab.J;
+    const uint32_t wprev = __shfl_up(d.w, 1, 64);
+    const double eprev = __shfl_up(e, 1, 64);
+    d.start = j < n_in && (j == 0 || d.w != wprev || !(e <= eprev));
+    d.starts = ballot(d.start);
+    const uint64_t above = j < 63 ? d.starts & ~((2ull << j) - 1ull) : 0ull;
+    d.last = (above ? (uint32_t)__builtin_ctzll(above) : n_in) - 1u;
+    d.e_last = __shfl(e, (int)(d.last & 63u), 64);
+    d.e_before = __shfl(e, (int)((d.last - 1u) & 63u), 64);
+    return d;
+}
+__device__ __forceinline__ void dp_list_store(const AllocBuffers& ab, const DpLists& dl, uint32_t i, uint32_t j, const DpList& d) {
+    const bool valid = j < ab.J;
+    if (valid) dl.wall[(size_t)i * ab.J + j] = d.w;
+    if (d.start) {
+        const size_t o = (size_t)i * ab.J + (uint32_t)__builtin_popcountll(d.starts & ((1ull << j) - 1ull));
+        dl.w[o] = d.w;
+        dl.jj[o] = j | (d.last << 8);
+        dl.e[2 * o] = d.e_last;
+        dl.e[2 * o + 1] = d.last > j ? d.e_before : __longlong_as_double(0x7FF8000000000000ll);
+    }
+    const uint32_t n = (uint32_t)__builtin_popcountll(d.starts);
+    if (valid && j >= n) dl.w[(size_t)i * ab.J + j] = 0xFFFFFFFFu;            // no entry
+    if (j == 0) {
+        dl.n[i] = n;
+        dl.bad[i] = d.nonfinite ? 1u : 0u;
+    }
+}
+
 // One wave per layer, one lane per candidate.  `with_hull`: also the list's lower convex hull.
 // `rows` (not null): the stored rows of the recurrence, `pitch` cells each, the first `pad` of them before cost 0: row i + 1
 // is filled with ROW_EMPTY (row 0: the start), by the gridDim.y workgroups of the layer; and its counters are cleared.
@@ -133,54 +196,17 @@ __global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uin
     __shared__ uint32_t sw[KIMAD_MAX_J_CONST];
     const uint32_t i = blockIdx.x, j = threadIdx.x;
     if (rows) {
-        const uint64_t cells = ((uint64_t)pad + ab.cap + 64u) & ~63ull;        // (the pitch holds them)
-        auto fill = [&](uint64_t r) {
-            unsigned long long* row = reinterpret_cast<unsigned long long*>(rows + r * pitch);
-            for (uint64_t x = 2ull * (blockIdx.y * 64u + j); x < cells; x += 128ull * gridDim.y) {
-                ulonglong2 v = make_ulonglong2(ROW_EMPTY, ROW_EMPTY);
-                if (r == 0u || x < pad) v.x = x == pad ? 0ull : 0x7FF0000000000000ull;
-                if (r == 0u || x + 1u < pad) v.y = 0x7FF0000000000000ull;
-                *reinterpret_cast<ulonglong2*>(row + x) = v;
-            }
-        };
-        fill(i + 1ull);
-        if (i == 0u) fill(0ull);
+        dp_fill_row(ab, rows, pitch, pad, i + 1ull, blockIdx.y * 64u + j, 64u * gridDim.y);
+        if (i == 0u) dp_fill_row(ab, rows, pitch, pad, 0ull, blockIdx.y * 64u + j, 64u * gridDim.y);
         if (i == 0u && blockIdx.y == 0u && j < 4u) ab.flags[j] = j == 1u ? ab.first_ticket : 0u;
         if (blockIdx.y) return;
     }
-    const bool valid = j < ab.J;
-    uint32_t w = 0xFFFFFFFFu;
-    double e = 0.0;
-    if (valid) {
-        w = units_of(ab.Ktab[(size_t)i * ab.J + j], ab.unit);
-        e = ab.E[(size_t)i * ab.J + j];
-        dl.wall[(size_t)i * ab.J + j] = w;
-    }
-    const uint64_t nonfinite = ballot(valid && !(e - e == 0.0));
-    const uint64_t over = ballot(valid && w > ab.cap);
-    const uint32_t n_in = over ? (uint32_t)__builtin_ctzll(over) : ab.J;
-    const bool in = j < n_in;
-    const uint32_t wprev = __shfl_up(w, 1, 64);
-    const double eprev = __shfl_up(e, 1, 64);
-    const bool start = in && (j == 0 || w != wprev || !(e <= eprev));
-    const uint64_t smask = ballot(start);
-    const uint64_t above = j < 63 ? smask & ~((2ull << j) - 1ull) : 0ull;
-    const uint32_t b = (above ? (uint32_t)__builtin_ctzll(above) : n_in) - 1u;   // last member of the run starting here
-    const double e_last = __shfl(e, (int)(b & 63u), 64);
-    const double e_before = __shfl(e, (int)((b - 1u) & 63u), 64);
-    if (start) {
-        const size_t o = (size_t)i * ab.J + (uint32_t)__builtin_popcountll(smask & ((1ull << j) - 1ull));
-        dl.w[o] = w;
-        dl.jj[o] = j | (b << 8);
-        dl.e[2 * o] = e_last;
-        dl.e[2 * o + 1] = b > j ? e_before : __longlong_as_double(0x7FF8000000000000ll);
-    }
-    const uint32_t n = (uint32_t)__builtin_popcountll(smask);
-    if (valid && j >= n) dl.w[(size_t)i * ab.J + j] = 0xFFFFFFFFu;            // no entry
-    if (j == 0) {
-        dl.n[i] = n;
-        dl.bad[i] = nonfinite ? 1u : 0u;
-    }
+    const DpList d = dp_list(ab, i, j);
+    dp_list_store(ab, dl, i, j, d);
+    const uint32_t n = (uint32_t)__builtin_popcountll(d.starts), w = d.w;
+    const uint64_t smask = d.starts;
+    const bool start = d.start;
+    const double e_last = d.e_last;
     if (!with_hull) return;
     // ---- the hull, one list entry per lane.  Every test below drops a point because of other points of the list
     // (one that is no dearer and saves as much; two whose chord passes at or below it), so all lanes test at once, and
@@ -318,12 +344,15 @@ struct Pieces {
 // from, and the m winners on that way stand in bytes at choice + (first layer) stride + c m.  So the sequential part is one
 // LDS read a piece; the pieces' rows are staged with one flat copy (they are contiguous, the pitch a multiple of 16 bytes),
 // the first lot before the least total is known.
+// `gate` (optional): a word that is zero where the allocation is already decided (k_dp_path).
 constexpr uint32_t DP_STAGE_BYTES = 128u * 1024u;
 constexpr uint32_t DP_WALK_MAX_L = 4224;           // layers whose path cells k_dp_walk keeps in LDS: every layer costs at least one
                                                    // cell, so a feasible path through rows of at most 4224 cells has no more layers
 
 __global__ __launch_bounds__(1024) void k_dp_walk(AllocBuffers ab, const double* __restrict__ last, const uint32_t* __restrict__ bad,
-                                                  int32_t err_infeasible, int32_t err_nonfinite, int32_t err_internal, StepLookup sl) {
+                                                  int32_t err_infeasible, int32_t err_nonfinite, int32_t err_internal, StepLookup sl,
+                                                  const uint32_t* __restrict__ gate) {
+    if (gate && *gate == 0u) return;
     __shared__ __attribute__((aligned(16))) uint8_t stage[DP_STAGE_BYTES];
     __shared__ uint16_t s_cell[DP_WALK_MAX_L];     // the path's cell per piece (a store to memory in the chain would be waited for)
     __shared__ double sv[16];

@@ -394,7 +394,8 @@ __device__ __forceinline__ void chain_choose(const AllocBuffers& ab, const DpLis
 constexpr uint32_t chain_threads(uint32_t w, uint32_t gw) { return 64u * (w + 1u + CHAIN_LOADERS * gw); }
 template <uint32_t MAXC, uint32_t W, uint32_t GW>
 __global__ __launch_bounds__(chain_threads(W, GW)) void k_dp_chain(AllocBuffers ab, DpLists dl, double* __restrict__ rows_g, uint32_t rstride,
-                                                                   uint32_t keepers) {
+                                                                   uint32_t keepers, const uint32_t* __restrict__ gate) {
+    if (gate && *gate == 0u) return;               // (decided: k_dp_path)
     constexpr uint32_t NT = chain_threads(W, GW), CELLS = 16u * W;
     static_assert(MAXC % CELLS == 0, "whole workgroups");
     __shared__ double rows[2][CELLS + MAXC];       // CELLS cells of +inf before cost 0: a record costs at most c_hi here

@@ -20,7 +20,7 @@
 #include "k_alloc.h"
 #include "k_alloc_chain.h"
 #include "k_alloc_band.h"
-#include "list_count.h"
+#include "k_alloc_tree.h"
 #include "k_server.h"
 #include "k_selftest.h"
 
@@ -65,6 +65,7 @@ struct Layout {
     uint64_t row0, row1, choice, dp_flags, dl_wall, dl_w, dl_jj, dl_e, dl_n, dl_bad, rows_g;
     uint64_t dense_E, dense_Kcost, dense_Kout;
     uint64_t band_lo, band_hi, band_info, band_live, hull_e, hull_w, hull_n, hull_abs;
+    uint64_t tree_vec, tree_hi, tree_entry, tree_layer, tree_row_hi, tree_single, tree_at, tree_head;
     uint64_t rstride = 0;            // cells per stored DP row (LDS-resident recurrence only)
     uint64_t total = 0, least = 0;   // least: without the rows that only k_dp_chain_long takes
 };
@@ -85,6 +86,24 @@ constexpr uint64_t CHAIN_LONG_BYTES = 256ull << 20;
 inline uint64_t chain_long_pitch(uint64_t cells) { return (CHAIN_PAD + cells + 63ull) & ~63ull; }
 inline bool chain_long_fits(uint64_t L, uint64_t cells) {
     return cells > DP_ROW_MAX && 8ull * (L + 1) * chain_long_pitch(cells) <= CHAIN_LONG_BYTES;
+}
+
+// Rows that fit LDS go by the tree of segments (k_alloc_tree.h) from so many layers on: below, the chain's few steps, or for longer rows
+// the band, take less than the tree's launches.  us of all launches of the allocation, chain and tree: rows of 1000 cells, 21 layers of
+// 64 ratios 31 and 41, 53 of 16 40 and 43, 62 of 50 49 and 41, 74 of 16 46 and 39, 148 of 64 76 and 56, 280 of 50 129 and 59, 700 of 33
+// 230 and 64; of 500 cells 53 of 32 33 and 38, 161 of 16 60 and 42.  Band and tree, rows of 4097 cells: 23 layers of 50 ratios 54 and
+// 68, 56 of 16 77 and 55, 62 of 50 97 and 67, 148 of 64 161 and 117, 268 of 32 282 and 79.  Where rounding may decide, the chain comes
+// behind it: 700 layers of small whole errors 229 and 301.
+constexpr uint32_t TREE_MIN_L = 24, TREE_MIN_L_SHORT = 60;       // (rows of fewer than BAND_AUTO_CELLS cells: the latter)
+// Segments of at most this many layers: a segment's layers are one after another, a level of the tree is a launch.  (us with 3, 6 and
+// 12: rows of 1000 cells, 148 layers of 64 ratios 60, 56, 56, 218 of 64 65, 65, 74, 62 of 50 41, 41, 46.  Of 4097 cells, whose
+// levels cost more, 148 of 64 172, 138, 117, 161 of 64 74, 73, 78.)
+constexpr uint32_t TREE_FEW = 6, TREE_FEW_LONG = 12;
+inline bool tree_takes(uint64_t L, uint64_t J) { return L >= TREE_MIN_L && L <= TREE_MAX_L && J > 1; }
+inline uint32_t tree_segments(uint64_t layers, uint32_t few) {
+    uint32_t s = 1;
+    while (s < TREE_MAX_SEGMENTS && (uint64_t)s * few < layers) s <<= 1;
+    return s;
 }
 
 uint32_t pick_tile_elems(uint64_t d_big) {
@@ -310,6 +329,13 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
         const uint64_t cells = std::min<uint64_t>(lo.dp_cells, DP_ROW_MAX);
         lo.rstride = 512ull * (cells <= 1024 ? 2 : cells <= 2048 ? 4 : cells <= 3072 ? 6 : 9);
     }
+    if (tree_takes(L, J)) {
+        const uint64_t S = tree_segments(L, TREE_FEW), slots = S * TREE_LAYERS;
+        lo.tree_vec = take(16 * S * lo.rstride); lo.tree_hi = take(8 * S);
+        lo.tree_entry = take(sizeof(TreeEntry) * 64 * slots); lo.tree_layer = take(4 * slots); lo.tree_row_hi = take(4 * slots);
+        lo.tree_single = take(sizeof(TreeSingle) * (uint64_t)L); lo.tree_at = take(4ull * L);
+        lo.tree_head = take(32);
+    }
     // (last: a workspace that ends with the shorter rows is accepted too, see kimad_plan::all_rows)
     lo.rows_g = take(8ull * (L + 1) * lo.rstride);
     lo.least = lo.total = off;
@@ -330,7 +356,7 @@ uint64_t cost_unit(const kimad_config_t& cfg, uint64_t P) {
     return D == 0 || P <= D ? 1 : (P + D - 1) / D;
 }
 
-// Rows from this many cost cells on take the banded recurrence by themselves.
+// Rows from this many cost cells on take the banded recurrence by themselves where the layers are too few for the tree.
 constexpr uint64_t BAND_AUTO_CELLS = 1537;
 // With few ratios the lists are short, and whole rows by many workgroups are cheaper than a band by one.
 constexpr uint32_t WHOLE_ROWS_J = 7;
@@ -405,8 +431,6 @@ struct kimad_plan {
     std::vector<uint32_t> ktab;      // host copy of K_ij
     std::vector<uint32_t> kmax;      // K_{i,J-1}
     double ratio0 = 0.0;             // the grid's smallest ratio
-    uint64_t band_unit = 0, band_cap = 0;   // cost unit and capacity that band_fits holds for (band_takes)
-    bool band_fits = false;
     char* ws = nullptr;
     bool all_rows = false;           // the workspace holds every row of an allocation beyond LDS (Layout::total)
     int device = 0;
@@ -582,6 +606,7 @@ struct AllocScratch {
     uint32_t rstride;
     uint64_t max_cells;                  // longest row (capacity + 1) the tables hold
     bool all_rows;                       // rows_g holds all rows of that length (k_dp_chain_long)
+    TreeBuffers tree;                    // (vec: null where there are none)
 };
 
 // Table memory for callers that cannot allocate (kimad_allocate_static): one array per device, inside the
@@ -607,19 +632,6 @@ unsigned char* static_scratch_of_current_device() {
     return g_scratch_ptr[dev];
 }
 
-// Whether the candidate lists of all layers fit the bounds kernel, which otherwise leaves the bands as wide as the rows: one
-// workgroup then sweeps what many share in whole rows (500 layers with 64 ratios, rows of 4097 cells: 9.6 ms, and 0.63).  As
-// many entries as there are different costs up to the capacity, in a table whose errors fall along a row.
-bool band_takes(kimad_plan* p, uint64_t unit, uint64_t cap) {
-    const uint64_t L = p->lo.L, J = p->lo.J;
-    if (L * J <= BAND_LCAP) return true;
-    if (p->band_unit != unit || p->band_cap != cap) {        // (counted once per budget)
-        p->band_unit = unit; p->band_cap = cap;
-        p->band_fits = count_list_records(p->ktab.data(), L, J, unit, cap, BAND_LCAP) <= BAND_LCAP;
-    }
-    return p->band_fits;
-}
-
 // The allocation's tables in the plan's workspace.
 AllocScratch plan_scratch(kimad_plan* p) {
     const Layout& lo = p->lo;
@@ -640,6 +652,15 @@ AllocScratch plan_scratch(kimad_plan* p) {
     ws.rstride = (uint32_t)lo.rstride;
     ws.max_cells = lo.dp_cells;
     ws.all_rows = p->all_rows && chain_long_fits(lo.L, lo.dp_cells);
+    ws.tree = TreeBuffers{};
+    if (tree_takes(lo.L, lo.J)) {
+        TreeBuffers& t = ws.tree;
+        t.vec = at<double>(p, lo.tree_vec); t.hi = at<uint32_t>(p, lo.tree_hi);
+        t.entry = at<TreeEntry>(p, lo.tree_entry); t.layer = at<uint32_t>(p, lo.tree_layer); t.row_hi = at<uint32_t>(p, lo.tree_row_hi);
+        t.single = at<TreeSingle>(p, lo.tree_single); t.at = at<uint32_t>(p, lo.tree_at);
+        t.head = at<uint32_t>(p, lo.tree_head);
+        t.rows = ws.rows_g; t.pitch = ws.rstride;
+    }
     return ws;
 }
 
@@ -654,11 +675,14 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
     // changes no finite cell and so neither the least total nor the smallest cost attaining it.
     const bool dense = (p->cfg.flags & KIMAD_CFG_DENSE_FALLBACK) != 0;
     uint64_t wmax = 0;
+    uint32_t choices = 0;                // layers whose sizes differ in cost
     for (uint32_t i = 0; i < lo.L; ++i) {
-        uint64_t dearest = p->kmax[i];
+        uint64_t dearest = p->kmax[i], cheapest = p->ktab[(size_t)i * lo.J];
         const uint64_t n = p->hl[i].n, pb = p->cfg.pair_bytes;
+        if (dense && cheapest * pb >= n * 4) cheapest = (n * 4 + pb - 1) / pb;
         if (dense && dearest * pb >= n * 4) dearest = (n * 4 + pb - 1) / pb;   // (costs ascend with j up to the break-even, and no grid point costs more than the dense size)
         wmax += (dearest + unit - 1) / unit;
+        choices += (cheapest + unit - 1) / unit != (dearest + unit - 1) / unit;
     }
     if (cap > wmax) cap = wmax;
     if (cap + 1 > ws.max_cells) return KIMAD_ERR_INVALID_ARG;   // budget beyond what the tables were sized for
@@ -681,10 +705,51 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
         const DpLists& dl = ws.dl;
         double* rows_g = ws.rows_g;
         const uint32_t rstride = ws.rstride;
+        const bool long_rows = cap + 1 >= BAND_AUTO_CELLS && lo.J > 1 && !(lo.J <= WHOLE_ROWS_J && cap + 1 <= WHOLE_ROWS_CELLS);
+        // (the withheld workgroup of the self-test is the chain's)
+        const bool tree = ws.tree.vec && !(p->cfg.flags & (KIMAD_CFG_FULL_DP | KIMAD_CFG_BAND_DP)) && first_ticket == 0u &&
+                          lo.L >= (cap + 1 >= BAND_AUTO_CELLS ? TREE_MIN_L : TREE_MIN_L_SHORT);
         const bool band = lo.L <= BAND_MAX_L && !(p->cfg.flags & KIMAD_CFG_FULL_DP) &&
-                          ((p->cfg.flags & KIMAD_CFG_BAND_DP) ||
-                           (cap + 1 >= BAND_AUTO_CELLS && lo.J > 1 && !(lo.J <= WHOLE_ROWS_J && cap + 1 <= WHOLE_ROWS_CELLS) &&
-                            band_takes(p, unit, cap)));
+                          ((p->cfg.flags & KIMAD_CFG_BAND_DP) || (long_rows && lo.L < TREE_MIN_L));
+        // (keepers of 16 cells a compute wave, then a workgroup per piece of the layers)
+        auto chain = [&](auto kern, uint32_t cells, uint32_t threads, const uint32_t* gate) -> int {
+            const uint32_t keepers = (uint32_t)(cap / cells + 1);
+            const Pieces pieces(lo.L);
+            const uint32_t others = pieces.fours + pieces.ones * (uint32_t)(cap / BLOCK_CELLS + 1);
+            KLAUNCH(p, s, "k_dp_chain", kern, dim3(keepers + others), dim3(threads), ab, dl, rows_g, rstride, keepers, gate);
+            KLAUNCH(p, s, "k_dp_walk", k_dp_walk, dim3(1), dim3(1024), ab, (const double*)(rows_g + (size_t)lo.L * rstride),
+                    (const uint32_t*)dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL, sl, gate);
+            return KIMAD_OK;
+        };
+        auto chain_by_size = [&](const uint32_t* gate) -> int {
+            if (cap + 1 <= 1024 && lo.L > CHAIN_NARROW_L) return chain(k_dp_chain<1024, 4, 2>, 64, chain_threads(4, 2), gate);
+            if (cap + 1 <= 1024) return chain(k_dp_chain<1024, 8, 2>, 128, chain_threads(8, 2), gate);
+            if (cap + 1 <= 2048) return chain(k_dp_chain<2048, 8, 3>, 128, chain_threads(8, 3), gate);
+            return chain(k_dp_chain<DP_ROW_MAX, 4, 5>, 64, chain_threads(4, 5), gate);
+        };
+        if (tree) {
+            TreeBuffers tb = ws.tree;
+            tb.S = tree_segments(choices, cap + 1 <= 1024 ? TREE_FEW : TREE_FEW_LONG);
+            if (cap + 1 <= 1024) {
+                KLAUNCH(p, s, "k_dp_segments", k_dp_segments<1024>, dim3(tb.S + (lo.L + 15u) / 16u), dim3(SEGMENT_THREADS), ab, dl, tb);
+            } else {
+                KLAUNCH(p, s, "k_dp_segments", k_dp_segments<DP_ROW_MAX>, dim3(tb.S + (lo.L + 15u) / 16u), dim3(SEGMENT_THREADS), ab, dl, tb);
+            }
+            for (uint32_t first = tb.S / 2u; first >= 2u; first >>= 1) {
+                const uint32_t wide = (uint32_t)(cap / 64 + 1), narrow = (uint32_t)(cap / 16 + 1);
+                if (cap + 1 <= 1024) KLAUNCH(p, s, "k_dp_join", (k_dp_join<1024, 16>), dim3(narrow, first), dim3(JOIN_THREADS), tb, first);
+                else if (first * wide < 512u) KLAUNCH(p, s, "k_dp_join", (k_dp_join<DP_ROW_MAX, 16>), dim3(narrow, first), dim3(JOIN_THREADS), tb, first);
+                else KLAUNCH(p, s, "k_dp_join", (k_dp_join<DP_ROW_MAX, 64>), dim3(wide, first), dim3(JOIN_THREADS), tb, first);
+            }
+            if (cap + 1 <= 1024) {
+                KLAUNCH(p, s, "k_dp_path", k_dp_path<true>, dim3(tb.S), dim3(PATH_THREADS), ab, dl, tb, ws.band.info, long_rows ? 1u : 0u,
+                        (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, sl);
+            } else {
+                KLAUNCH(p, s, "k_dp_path", k_dp_path<false>, dim3(tb.S), dim3(PATH_THREADS), ab, dl, tb, ws.band.info, long_rows ? 1u : 0u,
+                        (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, sl);
+            }
+            return chain_by_size(tb.head + 3);
+        }
         KLAUNCH(p, s, "k_dp_prep", k_dp_prep, dim3(lo.L), dim3(64), ab, dl, band ? 1u : 0u, band ? (double*)nullptr : rows_g,
                 (uint64_t)rstride, 0u);
         if (band) {
@@ -696,20 +761,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
                     (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, sl);
             return KIMAD_OK;
         }
-        // (keepers of 16 cells a compute wave, then a workgroup per piece of the layers)
-        auto chain = [&](auto kern, uint32_t cells, uint32_t threads) -> int {
-            const uint32_t keepers = (uint32_t)(cap / cells + 1);
-            const Pieces pieces(lo.L);
-            const uint32_t others = pieces.fours + pieces.ones * (uint32_t)(cap / BLOCK_CELLS + 1);
-            KLAUNCH(p, s, "k_dp_chain", kern, dim3(keepers + others), dim3(threads), ab, dl, rows_g, rstride, keepers);
-            KLAUNCH(p, s, "k_dp_walk", k_dp_walk, dim3(1), dim3(1024), ab, (const double*)(rows_g + (size_t)lo.L * rstride),
-                    (const uint32_t*)dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL, sl);
-            return KIMAD_OK;
-        };
-        if (cap + 1 <= 1024 && lo.L > CHAIN_NARROW_L) return chain(k_dp_chain<1024, 4, 2>, 64, chain_threads(4, 2));
-        if (cap + 1 <= 1024) return chain(k_dp_chain<1024, 8, 2>, 128, chain_threads(8, 2));
-        if (cap + 1 <= 2048) return chain(k_dp_chain<2048, 8, 3>, 128, chain_threads(8, 3));
-        return chain(k_dp_chain<DP_ROW_MAX, 4, 5>, 64, chain_threads(4, 5));
+        return chain_by_size(nullptr);
     } else if (ws.all_rows) {
         const uint64_t pitch = chain_long_pitch(cap + 1);
         // (a row's filling takes several workgroups: one per 32 KB)
@@ -1027,6 +1079,7 @@ int kimad_allocate_static(kimad_plan_t* p, const double* err_table, uint64_t bud
     ws.rstride = (uint32_t)CELLS;
     ws.max_cells = CELLS;
     ws.all_rows = false;                                        // (rows of this length fit LDS)
+    ws.tree = TreeBuffers{};
     static_assert(KIMAD_STATIC_MAX_CELLS == 1024, "a stored row holds the cells of k_dp_chain's whole workgroups");
     if (off > STATIC_SCRATCH_BYTES) return KIMAD_ERR_INTERNAL;
     const int rc = enqueue_allocate(p, ws, err_table, budget_bytes, j_out, K_out, offsets_out, status_out,

@@ -1,0 +1,60 @@
+"""The allocation by a tree of segments: every plan's sizes are the oracle's dynamic programme's bit for bit, where all choices
+are clear and where rounding decides (ties, errors that vanish beside the total), with layers that have no choice of cost, at the
+edges of rows and segments, from calls in turn on one plan."""
+import numpy as np
+import pytest
+
+from oracle import kimad_oracle as ko
+
+pytestmark = pytest.mark.gpu
+
+
+def _table(rng, sizes, Kt, kind):
+    n = np.array(sizes, dtype=np.float64)[:, None]
+    E = 10.0 ** rng.uniform(-6, 2, size=(len(sizes), 1)) * (1.0 - Kt / n) ** rng.uniform(0.5, 6.0, size=(len(sizes), 1))
+    if kind == "noise":
+        E = rng.random(E.shape) - 0.3                    # neither falling nor convex, negative entries
+    elif kind == "ties":
+        E = np.round(4.0 * E / E.max())
+    elif kind == "tiny":
+        E *= 10.0 ** -rng.integers(0, 20, size=(len(sizes), 1)).astype(np.float64)       # errors below a unit in the total's last place
+    elif kind == "zeros":
+        E[rng.random(len(sizes)) < 0.5] = 0.0
+        E[:, 1::3] = E[:, ::3][:, :E[:, 1::3].shape[1]]  # equal neighbours
+    return E
+
+
+@pytest.mark.parametrize("cells,L", [(90, 60), (64, 61), (1000, 60), (1023, 97), (1024, 192), (1025, 193), (1024, 1024), (1537, 24), (2049, 25),
+                                     (4223, 64), (4224, 48), (4224, 300)])
+@pytest.mark.parametrize("J", [2, 17, 64])
+def test_sizes_are_the_oracles(cells, L, J):
+    import torch
+    import paper_2312_08053_amd as kimad
+    rng = np.random.default_rng(1000 * cells + 10 * L + J)
+    ratios = np.append(np.sort(rng.uniform(0.001, 0.99, size=J - 1)), 1.0)
+    # sizes from a fraction of a cost unit (no choice) to much of the row
+    sizes = [max(1, int(x)) for x in 3000.0 * 10.0 ** rng.uniform(-3, 1.5, size=L)]
+    Kt = np.array([ko.grid_sizes(ratios, n) for n in sizes])
+    n = int(sum(sizes))
+    z = [torch.zeros(n, dtype=torch.float32, device="cuda") for _ in range(2)]
+    least = int(Kt[:, 0].sum())
+    most = max(8 * n, 8 * (cells - 1))
+    plan = kimad.Plan(z[0], z[1], sizes, ratios.tolist(), D=cells - 1, max_budget_bytes=most, capacity_pairs=1)
+    budgets = [8 * (least + int(f * (n - least))) for f in (0.02, 0.3)] + [8 * max(1, least // 3)]
+    for kind in ("falling", "ties", "noise", "tiny", "zeros", "falling"):
+        E = np.ascontiguousarray(_table(rng, sizes, Kt, kind))
+        table = torch.from_numpy(E.reshape(-1)).cuda()
+        for budget in budgets if cells * L * J < 4e6 else budgets[1:2]:
+            st_ref, j_ref, K_ref, off_ref = ko.allocate(E, Kt, budget, 8, cells - 1)
+            j, K, off, st = plan.allocate(budget, table)
+            assert int(st.item()) == st_ref, (kind, budget)
+            if st_ref != ko.OK:
+                assert not K.cpu().numpy().any() and not off.cpu().numpy().any()
+                continue
+            assert np.array_equal(j.cpu().numpy(), j_ref), (kind, budget)
+            assert np.array_equal(K.cpu().numpy().astype(np.uint64), K_ref), (kind, budget)
+            assert np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref), (kind, budget)
+    E[L // 2, J // 2] = np.nan
+    j, K, off, st = plan.allocate(budgets[1], torch.from_numpy(E.reshape(-1)).cuda())
+    assert int(st.item()) == ko.ERR_NONFINITE and not K.cpu().numpy().any()
+    plan.close()
