@@ -238,7 +238,8 @@ __global__ __launch_bounds__(SEGMENT_THREADS) void k_dp_segments(AllocBuffers ab
             }
         };
         // (cells beyond the row's largest cost stay +inf)
-        if (CPT > 2u && base + 2u * NT <= hi) step(std::integral_constant<uint32_t, CPT>{});
+        if (CPT > 4u && base + 4u * NT <= hi) step(std::integral_constant<uint32_t, CPT>{});
+        else if (CPT > 2u && base + 2u * NT <= hi) step(std::integral_constant<uint32_t, CPT < 4u ? CPT : 4u>{});
         else if (CPT > 1u && base + NT <= hi) step(std::integral_constant<uint32_t, CPT < 2u ? CPT : 2u>{});
         else if (base <= hi) step(std::integral_constant<uint32_t, 1u>{});
         cur ^= 1u;
@@ -251,19 +252,22 @@ __global__ __launch_bounds__(SEGMENT_THREADS) void k_dp_segments(AllocBuffers ab
     if (tid == 0u) tb.hi[tb.S + s] = hi;
 }
 
-// Two neighbours together: node k of the level's nodes k = first + blockIdx.y, costs [T blockIdx.x, T blockIdx.x + T).  A lane looks
-// after four neighbouring costs; T / 4 lanes share a part of the costs that the first half may take, four at a time: eight values are
-// read for sixteen sums, and B's stay for the next four.
+// Two neighbours together: node k of the level's nodes k = first + blockIdx.y, T costs.  A lane looks after R neighbouring costs; T / R
+// lanes share a part of the costs that the first half may take, four at a time: eight values are read for 4 R sums, and R + 3 of B's
+// stay for the next four.
+// Bound by the additions and minima, and on rows of 4097 cells with T = 16 by what every workgroup brings to LDS.
+// (us, nodes of 4097 cells, under the profiler: eight, T = 64 and R = 4, 21.9 with the rows brought one load at a time and 17.7 with
+// eight, R = 8 16.7; four, T = 16 19.6 and 14.2, T = 64 and R = 8 11.8; two, T = 16 14.0 and 9.6, T = 32 9.3.)
 constexpr uint32_t JOIN_THREADS = 256;
-template <uint32_t MAXC, uint32_t T>
+template <uint32_t MAXC, uint32_t T, uint32_t R>
 __global__ __launch_bounds__(JOIN_THREADS) void k_dp_join(TreeBuffers tb, uint32_t first) {
-    constexpr uint32_t LANES = T / 4u, PARTS = JOIN_THREADS / LANES, OFF = T + 11u;
-    static_assert(T % 16u == 0 && OFF % 4u == 3u, "a lane's four costs, and what it reads of B, start at whole quads");
+    constexpr uint32_t LANES = T / R, PARTS = JOIN_THREADS / LANES, OFF = T + 11u;
+    static_assert(T % 16u == 0 && R % 4u == 0 && OFF % 4u == 3u, "a lane's costs, and what it reads of B, start at whole quads");
     __shared__ __align__(16) double A[MAXC + 8u];
     __shared__ __align__(16) double B[OFF + MAXC + T + 5u];
     __shared__ double red[JOIN_THREADS / 64u][T];
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    const uint32_t k = first + blockIdx.y, c0 = blockIdx.x * T;
+    const uint32_t k = first + blockIdx.y, c0 = (gridDim.x - 1u - blockIdx.x) * T;      // (those with most to do come first)
     const uint32_t room = tb.head[0];
     if (room == TREE_NO_ROOM) return;
     const uint32_t ha = tb.hi[2u * k], hb = tb.hi[2u * k + 1u], hk = min(room, ha + hb);
@@ -273,24 +277,37 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_dp_join(TreeBuffers tb, uint32
     const uint32_t a_lo = (c0 > hb ? c0 - hb : 0u) & ~3u, a_hi = min(ha, min(top, hk));
     const double* va = tb.vec + (size_t)(2u * k) * tb.pitch;
     const double* vb = tb.vec + (size_t)(2u * k + 1u) * tb.pitch;
-    for (uint32_t x = a_lo + tid; x < a_hi + 4u; x += JOIN_THREADS) A[x] = x <= ha ? va[min(x, ha)] : DP_INF;
-    for (uint32_t x = tid; x < OFF + top + 2u - a_lo; x += JOIN_THREADS) {
-        const uint32_t b = x - OFF;
-        B[x] = x >= OFF && b <= hb ? vb[min(b, hb)] : DP_INF;
+    // (eight loads of each at a time)
+    for (uint32_t x0 = tid; x0 < max(a_hi + 4u, OFF + top + 2u) - a_lo; x0 += 8u * JOIN_THREADS) {
+        double ra[8], rb[8];
+#pragma unroll
+        for (uint32_t u = 0; u < 8u; ++u) {
+            const uint32_t x = x0 + u * JOIN_THREADS, a = a_lo + x, b = x - OFF;
+            ra[u] = va[min(a, ha)];
+            rb[u] = vb[x >= OFF ? min(b, hb) : 0u];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < 8u; ++u) {
+            const uint32_t x = x0 + u * JOIN_THREADS, a = a_lo + x, b = x - OFF;
+            if (a < a_hi + 4u) A[a] = a <= ha ? ra[u] : DP_INF;
+            if (x < OFF + top + 2u - a_lo) B[x] = x >= OFF && b <= hb ? rb[u] : DP_INF;
+        }
     }
     __syncthreads();
-    const uint32_t l = tid % LANES, part = tid / LANES, c = c0 + 4u * l;
+    const uint32_t l = tid % LANES, part = tid / LANES, c = c0 + R * l;
     const uint32_t quads = (a_hi - a_lo) / 4u + 1u, per = (quads + PARTS - 1u) / PARTS;
     const uint32_t a0 = a_lo + 4u * part * per, a1 = min(a0 + 4u * per, a_lo + 4u * quads);
-    double best[4] = {DP_INF, DP_INF, DP_INF, DP_INF};
+    double best[R];
+#pragma unroll
+    for (uint32_t v = 0; v < R; ++v) best[v] = DP_INF;
     if (a0 < a1) {
         // w[v - u + 3] = B[c + v - a - u]
         const double* bp = B + OFF + c - a0 - 3u;
-        double w[7];
-        {
-            const double2 w0 = *reinterpret_cast<const double2*>(bp), w1 = *reinterpret_cast<const double2*>(bp + 2);
-            const double2 w2 = *reinterpret_cast<const double2*>(bp + 4);
-            w[0] = w0.x; w[1] = w0.y; w[2] = w1.x; w[3] = w1.y; w[4] = w2.x; w[5] = w2.y; w[6] = bp[6];
+        double w[R + 4u];
+#pragma unroll
+        for (uint32_t v = 0; v < R + 4u; v += 2u) {
+            const double2 p = *reinterpret_cast<const double2*>(bp + v);
+            w[v] = p.x; w[v + 1u] = p.y;
         }
         for (uint32_t a = a0; a < a1; a += 4u) {
             const double2 x0 = *reinterpret_cast<const double2*>(A + a), x1 = *reinterpret_cast<const double2*>(A + a + 2u);
@@ -298,20 +315,21 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_dp_join(TreeBuffers tb, uint32
             bp -= 4;
             const double2 n0 = *reinterpret_cast<const double2*>(bp), n1 = *reinterpret_cast<const double2*>(bp + 2);
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (uint32_t u = 0; u < 4u; ++u)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) best[v] = min_f64(best[v], x[u] + w[v - u + 3]);
-            w[4] = w[0]; w[5] = w[1]; w[6] = w[2];
+                for (uint32_t v = 0; v < R; ++v) best[v] = min_f64(best[v], x[u] + w[v + 3u - u]);
+#pragma unroll
+            for (uint32_t v = R + 2u; v >= 4u; --v) w[v] = w[v - 4u];
             w[0] = n0.x; w[1] = n0.y; w[2] = n1.x; w[3] = n1.y;
         }
     }
 #pragma unroll
     for (uint32_t d = LANES; d < 64u; d <<= 1)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) best[v] = min_f64(best[v], __shfl_xor(best[v], (int)d, 64));
+        for (uint32_t v = 0; v < R; ++v) best[v] = min_f64(best[v], __shfl_xor(best[v], (int)d, 64));
     if (lane < LANES)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) red[wave][4u * lane + v] = best[v];
+        for (uint32_t v = 0; v < R; ++v) red[wave][R * lane + v] = best[v];
     __syncthreads();
     if (tid < T && c0 + tid <= hk) {
         double r = red[0][tid];

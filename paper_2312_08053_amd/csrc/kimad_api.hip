@@ -736,10 +736,13 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
                 KLAUNCH(p, s, "k_dp_segments", k_dp_segments<DP_ROW_MAX>, dim3(tb.S + (lo.L + 15u) / 16u), dim3(SEGMENT_THREADS), ab, dl, tb);
             }
             for (uint32_t first = tb.S / 2u; first >= 2u; first >>= 1) {
-                const uint32_t wide = (uint32_t)(cap / 64 + 1), narrow = (uint32_t)(cap / 16 + 1);
-                if (cap + 1 <= 1024) KLAUNCH(p, s, "k_dp_join", (k_dp_join<1024, 16>), dim3(narrow, first), dim3(JOIN_THREADS), tb, first);
-                else if (first * wide < 512u) KLAUNCH(p, s, "k_dp_join", (k_dp_join<DP_ROW_MAX, 16>), dim3(narrow, first), dim3(JOIN_THREADS), tb, first);
-                else KLAUNCH(p, s, "k_dp_join", (k_dp_join<DP_ROW_MAX, 64>), dim3(wide, first), dim3(JOIN_THREADS), tb, first);
+                auto join = [&](auto kern, uint32_t costs) -> int {
+                    KLAUNCH(p, s, "k_dp_join", kern, dim3((uint32_t)(cap / costs + 1), first), dim3(JOIN_THREADS), tb, first);
+                    return KIMAD_OK;
+                };
+                const int rc = cap + 1 <= 1024 ? join(k_dp_join<1024, 16, 4>, 16)
+                             : first * (cap / 64 + 1) < 200 ? join(k_dp_join<DP_ROW_MAX, 32, 4>, 32) : join(k_dp_join<DP_ROW_MAX, 64, 8>, 64);
+                if (rc) return rc;
             }
             if (cap + 1 <= 1024) {
                 KLAUNCH(p, s, "k_dp_path", k_dp_path<true>, dim3(tb.S), dim3(PATH_THREADS), ab, dl, tb, ws.band.info, long_rows ? 1u : 0u,
