@@ -113,7 +113,9 @@ typedef struct kimad_config {
                                            fewer layers take the band with rows of 1537 cells or more (with up to 7
                                            ratios from 2049 on), others the whole rows, as grids of one ratio do.
                                            Rows that do not fit LDS (more than 4224 cells) and plans of more than
-                                           1024 layers always take whole rows. */
+                                           1024 layers take whole rows with either flag; by default 16 to 1024 layers
+                                           with rows of up to 131072 cells go by two halves, and by whole rows where
+                                           rounding might decide. */
 
 #define KIMAD_CFG_DENSE_FALLBACK 8ull    /* allocation: a layer never costs more than its bare values (4 n bytes).  A grid
                                            point at or beyond the break-even K * pair_bytes >= 4 n stands for sending

@@ -27,12 +27,13 @@ struct AllocBuffers {
     uint64_t* K_out;
     uint64_t* offsets_out;
     int32_t* status;
-    uint32_t* flags;         // [0] non-finite seen (rows by launch only), [1] workgroups started, [2] waits given up
+    uint32_t* flags;         // [DP_FLAGS] [0] non-finite seen (rows by launch only), [1] workgroups started, [2] waits given up, [4] on: FLAG_..
     uint32_t polls;          // reads after which a wait for a row's cells is given up
     uint32_t first_ticket;   // what flags[1] starts from: 0 (a test that withholds the first workgroups: their number)
 };
 
 constexpr double DP_INF = __builtin_huge_val();
+constexpr uint32_t DP_FLAGS = 12;
 
 // K / unit, rounded up.  (In 32 bits: a division in 64 is four times as long.)
 __device__ __forceinline__ uint32_t units_of(uint32_t K, uint64_t unit) {
@@ -191,15 +192,29 @@ __device__ __forceinline__ void dp_list_store(const AllocBuffers& ab, const DpLi
 // One wave per layer, one lane per candidate.  `with_hull`: also the list's lower convex hull.
 // `rows` (not null): the stored rows of the recurrence, `pitch` cells each, the first `pad` of them before cost 0: row i + 1
 // is filled with ROW_EMPTY (row 0: the start), by the gridDim.y workgroups of the layer; and its counters are cleared.
-__global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uint32_t with_hull, double* rows, uint64_t pitch, uint32_t pad) {
+// `falling` (not null): [L][J] the candidates' errors, +inf for one that is dearer than another and no better.
+__global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uint32_t with_hull, double* rows, uint64_t pitch, uint32_t pad, double* falling) {
     __shared__ double se[KIMAD_MAX_J_CONST];
     __shared__ uint32_t sw[KIMAD_MAX_J_CONST];
     const uint32_t i = blockIdx.x, j = threadIdx.x;
     if (rows) {
         dp_fill_row(ab, rows, pitch, pad, i + 1ull, blockIdx.y * 64u + j, 64u * gridDim.y);
         if (i == 0u) dp_fill_row(ab, rows, pitch, pad, 0ull, blockIdx.y * 64u + j, 64u * gridDim.y);
-        if (i == 0u && blockIdx.y == 0u && j < 4u) ab.flags[j] = j == 1u ? ab.first_ticket : 0u;
+        if (i == 0u && blockIdx.y == 0u && j < DP_FLAGS) ab.flags[j] = j == 1u ? ab.first_ticket : 0u;
         if (blockIdx.y) return;
+    }
+    if (falling) {
+        const double e = j < ab.J ? ab.E[(size_t)i * ab.J + j] : DP_INF;
+        double least = e, largest = j < ab.J ? fabs(e) : 0.0;
+#pragma unroll
+        for (int s = 1; s < 64; s <<= 1) {
+            const double o = __shfl_up(least, s, 64);
+            if ((int)j >= s) least = fmin(least, o);
+            largest = fmax(largest, __shfl_xor(largest, s, 64));
+        }
+        const double before = __shfl_up(least, 1, 64);
+        if (j < ab.J) falling[(size_t)i * ab.J + j] = j == 0u || e < before ? e : DP_INF;
+        if (j == 0u) dl.habs[i] = largest;
     }
     const DpList d = dp_list(ab, i, j);
     dp_list_store(ab, dl, i, j, d);
@@ -467,8 +482,11 @@ __global__ __launch_bounds__(1024) void k_dp_walk(AllocBuffers ab, const double*
 
 // Smallest cost attaining the least total, back-tracking, outputs.  One workgroup.
 // `bad` (not null): per layer, whether its table row holds an Inf or a NaN; else flags[0] says it of the table.
+// `gate`: as in k_dp_walk.
 __global__ __launch_bounds__(1024) void k_dp_final(AllocBuffers ab, const double* last, const uint32_t* __restrict__ bad,
-                                                   int32_t err_infeasible, int32_t err_nonfinite, int32_t err_internal, StepLookup sl) {
+                                                   int32_t err_infeasible, int32_t err_nonfinite, int32_t err_internal, StepLookup sl,
+                                                   const uint32_t* __restrict__ gate) {
+    if (gate && *gate == 0u) return;
     __shared__ double sv[16];
     __shared__ unsigned long long sc[16];
     __shared__ unsigned long long cstar;

@@ -53,14 +53,6 @@ __device__ __forceinline__ double max_f64(double a, double b) {   // neither a s
     return r;
 }
 
-// The value of another lane inside groups of 2, 4, 8 or 16 neighbouring lanes, through DPP moves (a shuffle goes
-// through the LDS crossbar: a dependent round trip per step).
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
-    return __hiloint2double(hi, lo);
-}
 // maximum over the T lanes of a group (T = 1, 2, 4, 8), in every lane of it
 template <int T>
 __device__ __forceinline__ double group_max(double v) {

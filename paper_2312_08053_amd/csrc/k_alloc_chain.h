@@ -61,6 +61,23 @@ __device__ __forceinline__ double min_over_rows(double v) {
     return min_f64(__hiloint2double((int)b.x, (int)a.x), __hiloint2double((int)b.y, (int)a.y));
 }
 
+// The value of another lane inside groups of 2, 4, 8 or 16 neighbouring lanes, through DPP moves (a shuffle goes
+// through the LDS crossbar: a dependent round trip per step).
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+// Least value of a wave, in every lane.
+__device__ __forceinline__ double wave_min_f64(double v) {
+    v = min_f64(v, dpp_f64<0xB1>(v));                      // quad_perm [1,0,3,2]
+    v = min_f64(v, dpp_f64<0x4E>(v));                      // quad_perm [2,3,0,1]
+    v = min_f64(v, dpp_f64<0x141>(v));                     // row_half_mirror
+    v = min_f64(v, dpp_f64<0x140>(v));                     // row_mirror
+    return min_over_rows(v);
+}
+
 // ---- rows that fit LDS -------------------------------------------------------------------------
 // A compute wave looks after sixteen cells, the same ones in each of its four 16-lane rows; lane 16 r + k holds list record
 // 4 k + r and hands it to its row by DPP, so the four rows share a layer's records and a minimum over the rows closes
@@ -462,37 +479,77 @@ __global__ __launch_bounds__(chain_threads(W, GW)) void k_dp_chain(AllocBuffers 
 // layer, 2.3 us).  With more than sixteen candidates the cheapest four's cells are waited for before all are asked for
 // through the caches (149 against 160 us with device-scope loads for all; with sixteen or fewer the wait costs more than it
 // saves, 83 against 72).  Sixteen cells a wave, the candidates shared by its four rows, read twice the lines: 190.
+// Two waves a workgroup, whose source cells lie close together, share what its compute unit's cache holds.  (us of all launches of the
+// allocation, whole rows by workgroups of one, two and four waves: 62 layers of 58 thousand cells 187, 190, 183, 8 of 58 thousand 43, 37, 35,
+// 16 of 131 thousand 98, 88, 82, 161 of 13 thousand 317, 336, 393, of 9 thousand and 5 ratios 164, 182, 215; by halves, below, 132, 128,
+// 130, the 161 layers 212, 213, 241 and 106, 109, 125.)
 constexpr uint32_t CHAIN_PAD = 64;
-constexpr uint32_t CHAIN_LONG_NT = 64;
+constexpr uint32_t CHAIN_LONG_NT = 128;
 constexpr uint32_t CHAIN_LONG_CELLS = CHAIN_LONG_NT;
 
+// Two halves of the layers side by side (k_alloc_halves.h), each from cost 0, every range of cells by two workgroups of neighbouring
+// numbers; or, where order is null, all layers one after another, if `gate` (optional) says so.
+struct ChainHalves {
+    const uint32_t* order;             // [L] the layers, the first half's and then the second's
+    const double* falling;             // [L][J] their errors
+    double* least[2];                  // [cells / 64] least values of the halves' last rows
+    uint32_t split;                    // layers of the first half
+    const uint32_t* gate;
+};
+
 template <int SETS>
-__global__ __launch_bounds__(CHAIN_LONG_NT) void k_dp_chain_long(AllocBuffers ab, const uint32_t* __restrict__ wall, double* rows, uint64_t pitch) {
-    const uint32_t lane = threadIdx.x;
-    uint32_t ticket = 0;
-    if (lane == 0) ticket = atomicAdd(&ab.flags[1], 1u);
-    const uint32_t number = (uint32_t)__builtin_amdgcn_readfirstlane(ticket);
+__global__ __launch_bounds__(CHAIN_LONG_NT) void k_dp_chain_long(AllocBuffers ab, const uint32_t* __restrict__ wall, double* rows, uint64_t pitch,
+                                                                 ChainHalves ch) {
+    const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (ch.gate && *ch.gate == 0u) return;
+    __shared__ uint32_t sh_number;
+    if (threadIdx.x == 0u) sh_number = atomicAdd(&ab.flags[1], 1u);
+    __syncthreads();
+    const uint32_t number = (uint32_t)__builtin_amdgcn_readfirstlane(sh_number);
     if (number >= gridDim.x) {
-        if (lane == 0) atomicAdd(&ab.flags[2], 1u);
+        if (threadIdx.x == 0u) atomicAdd(&ab.flags[2], 1u);
         return;
     }
-    const uint32_t c0 = number * CHAIN_LONG_CELLS, c = c0 + lane, c_hi = c0 + 63u;
+    const bool halves = ch.order != nullptr;
+    const uint32_t half = halves ? number & 1u : 0u;
+    const uint32_t c0 = (halves ? number >> 1 : number) * CHAIN_LONG_CELLS + 64u * wave, c = c0 + lane, c_hi = c0 + 63u;
+    if (c0 > ab.cap) return;
+    uint32_t i0 = half ? ch.split : 0u;
+    const uint32_t first = i0, i1 = halves && !half ? ch.split : ab.L;
+    const double* __restrict__ E = halves ? ch.falling : ab.E;
+    auto layer = [&](uint32_t i) { return halves ? ch.order[min(i, ab.L - 1u)] : min(i, ab.L - 1u); };
     double one = 1.0;
     asm volatile("" : "+v"(one));
     bool gave_up = false;
+    if (halves) {
+        // rows that do not reach these cells yet
+        uint32_t reach = 0u, skip = 0u;
+        for (uint32_t p = first; p < i1; p += 64u) {
+            const uint32_t i = p + lane, w = i < i1 ? min(wall[(size_t)layer(i) * ab.J + ab.J - 1u], ab.cap + 1u) : 0u;
+            const uint32_t upto = reach + wave_scan_add_u32(w);
+            skip += (uint32_t)__popcll(ballot(i < i1 && upto < c0));
+            reach = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+        }
+        for (; skip; --skip, ++i0) {
+            cell_store(rows + (size_t)(i0 + 1u) * pitch + CHAIN_PAD + c, DP_INF);
+            ab.choice[(size_t)i0 * ab.stride + c] = 0xFFu;
+        }
+    }
     uint32_t w_next[SETS];
     double e_next[SETS];
     auto ask_records = [&](uint32_t i) {
+        const size_t o0 = (size_t)layer(i) * ab.J;
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
             const uint32_t k = 16u * (uint32_t)s + (lane & 15u);
-            const size_t o = (size_t)min(i, ab.L - 1u) * ab.J + min(k, ab.J - 1u);
+            const size_t o = o0 + min(k, ab.J - 1u);
             w_next[s] = k < ab.J ? wall[o] : 0xFFFFFFFFu;
-            e_next[s] = ab.E[o];
+            e_next[s] = E[o];
         }
     };
-    ask_records(0u);
-    for (uint32_t i = 0; i < ab.L; ++i) {
+    ask_records(i0);
+    double last = DP_INF;
+    for (uint32_t i = i0; i < i1; ++i) {
         // a candidate that no cell here can afford reads the cells before cost 0
         uint32_t n = 0, neg[SETS];
         double err[SETS];
@@ -504,7 +561,7 @@ __global__ __launch_bounds__(CHAIN_LONG_NT) void k_dp_chain_long(AllocBuffers ab
             err[s] = can ? e_next[s] : DP_INF;
         }
         ask_records(i + 1u);
-        const char* row = reinterpret_cast<const char*>(rows + (size_t)i * pitch);
+        const char* row = reinterpret_cast<const char*>(rows + (size_t)(i == first ? 0u : i) * pitch);
         auto cell = [&](uint32_t at) { return reinterpret_cast<const unsigned long long*>(row + at); };
         const uint32_t here = (CHAIN_PAD + c) * 8u;
         unsigned long long v[SETS][16];
@@ -578,6 +635,11 @@ __global__ __launch_bounds__(CHAIN_LONG_NT) void k_dp_chain_long(AllocBuffers ab
 #pragma unroll
             for (int k = 15; k >= 0; --k) bj = t[s][k] == best ? 16u * (uint32_t)s + (uint32_t)k : bj;
         ab.choice[(size_t)i * ab.stride + c] = (uint8_t)(best < DP_INF ? bj : 0xFFu);
+        last = c <= ab.cap ? best : DP_INF;
+    }
+    if (halves) {
+        last = wave_min_f64(last);
+        if (lane == 0u) ch.least[half][c0 / 64u] = last;
     }
 }
 

@@ -345,14 +345,6 @@ __device__ __forceinline__ void two_add(Two& t, double v, uint32_t at) {
     t.second = min_f64(t.second, max_f64(t.best, v));
     if (v < t.best) { t.best = v; t.at = at; }
 }
-// least value of a wave, in every lane
-__device__ __forceinline__ double wave_min_f64(double v) {
-    v = min_f64(v, dpp_f64<0xB1>(v));                      // quad_perm [1,0,3,2]
-    v = min_f64(v, dpp_f64<0x4E>(v));                      // quad_perm [2,3,0,1]
-    v = min_f64(v, dpp_f64<0x141>(v));                     // row_half_mirror
-    v = min_f64(v, dpp_f64<0x140>(v));                     // row_mirror
-    return min_over_rows(v);
-}
 __device__ __forceinline__ Two two_wave(const Two& t) {
     Two r;
     r.best = wave_min_f64(t.best);

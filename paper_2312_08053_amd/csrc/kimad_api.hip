@@ -9,6 +9,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <numeric>
 #include <type_traits>
 #include <vector>
 
@@ -21,6 +22,7 @@
 #include "k_alloc_chain.h"
 #include "k_alloc_band.h"
 #include "k_alloc_tree.h"
+#include "k_alloc_halves.h"
 #include "k_server.h"
 #include "k_selftest.h"
 
@@ -65,6 +67,7 @@ struct Layout {
     uint64_t row0, row1, choice, dp_flags, dl_wall, dl_w, dl_jj, dl_e, dl_n, dl_bad, rows_g;
     uint64_t dense_E, dense_Kcost, dense_Kout;
     uint64_t band_lo, band_hi, band_info, band_live, hull_e, hull_w, hull_n, hull_abs;
+    uint64_t half_order;
     uint64_t tree_vec, tree_hi, tree_entry, tree_layer, tree_row_hi, tree_single, tree_at, tree_head;
     uint64_t rstride = 0;            // cells per stored DP row (LDS-resident recurrence only)
     uint64_t total = 0, least = 0;   // least: without the rows that only k_dp_chain_long takes
@@ -105,6 +108,13 @@ inline uint32_t tree_segments(uint64_t layers, uint32_t few) {
     while (s < TREE_MAX_SEGMENTS && (uint64_t)s * few < layers) s <<= 1;
     return s;
 }
+
+// Rows beyond LDS go by halves (k_alloc_halves.h) from so many layers on; fewer do not pay for the three launches more, and the three that
+// leave at once.  us of all launches of the allocation, one chain and halves: 62 layers of 58 thousand cells 187 and 128, of 131 thousand 370
+// and 222, 30 of 30 thousand 111 and 85, 161 of 13 thousand 317 and 213, of 9 thousand 164 and 109, 16 of 4300 45 and 41, of 30 thousand 36
+// and 34, 11 of 9 thousand 25 and 29, 6 of 12 thousand 25 and 33.  Where rounding may decide, one chain comes behind them: 16 layers of
+// 85 thousand cells 111 and 170.
+constexpr uint32_t HALVES_MIN_L = 16;
 
 uint32_t pick_tile_elems(uint64_t d_big) {
     // aim at >= 8 tiles per compute unit on large inputs, keep tiles within the 16-bit LDS counters
@@ -316,8 +326,9 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     lo.row1 = take(8 * lo.dp_cells);
     lo.choice = take((uint64_t)L * align_up(lo.dp_cells));
     lo.cprev = take(2ull * Pieces(L).count() * align_up(std::min<uint64_t>(lo.dp_cells, DP_ROW_MAX)));
-    lo.dp_flags = take(16);
+    lo.dp_flags = take(4 * DP_FLAGS);
     lo.ncompact = take(16);
+    lo.half_order = take(4ull * L);
     lo.dl_wall = take(4 * LJ); lo.dl_w = take(4 * LJ); lo.dl_jj = take(4 * LJ); lo.dl_e = take(16 * LJ); lo.dl_n = take(4ull * L);
     lo.dl_bad = take(4ull * L);
     lo.dense_E = take(8 * LJ); lo.dense_Kcost = take(4 * LJ); lo.dense_Kout = take(4 * LJ);
@@ -598,7 +609,7 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
 struct AllocScratch {
     double* row0; double* row1;          // per-layer-launch path only
     uint8_t* choice; uint16_t* cprev;    // [L][pitch], [pieces][pitch]
-    uint32_t* flags;                     // 16 bytes
+    uint32_t* flags;                     // [DP_FLAGS]
     DpLists dl;
     BandBuffers band;
     double* dense_E; uint32_t* dense_Kcost; uint32_t* dense_Kout;   // [L][J] each: the tables as the dense fallback sees them
@@ -754,7 +765,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
             return chain_by_size(tb.head + 3);
         }
         KLAUNCH(p, s, "k_dp_prep", k_dp_prep, dim3(lo.L), dim3(64), ab, dl, band ? 1u : 0u, band ? (double*)nullptr : rows_g,
-                (uint64_t)rstride, 0u);
+                (uint64_t)rstride, 0u, (double*)nullptr);
         if (band) {
             // the recurrence inside the band of cells that Lagrangian bounds leave (same result, a fraction of the cells)
             BandBuffers bb = ws.band;
@@ -767,19 +778,42 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
         return chain_by_size(nullptr);
     } else if (ws.all_rows) {
         const uint64_t pitch = chain_long_pitch(cap + 1);
+        const bool halves = lo.L >= HALVES_MIN_L && lo.L <= HALVES_MAX_L && cap + 1 <= HALVES_MAX_CELLS && first_ticket == 0u &&
+                            !(p->cfg.flags & KIMAD_CFG_FULL_DP);
         // (a row's filling takes several workgroups: one per 32 KB)
-        KLAUNCH(p, s, "k_dp_prep", k_dp_prep, dim3(lo.L, (uint32_t)(pitch / 4096 + 1)), dim3(64), ab, ws.dl, 0u, ws.rows_g, pitch, CHAIN_PAD);
-        const dim3 waves((uint32_t)(cap / CHAIN_LONG_CELLS + 1));
-        const uint32_t* wall = ws.dl.wall;
-        if (lo.J <= 16) {
-            KLAUNCH(p, s, "k_dp_chain", k_dp_chain_long<1>, waves, dim3(CHAIN_LONG_NT), ab, wall, ws.rows_g, pitch);
-        } else if (lo.J <= 32) {
-            KLAUNCH(p, s, "k_dp_chain", k_dp_chain_long<2>, waves, dim3(CHAIN_LONG_NT), ab, wall, ws.rows_g, pitch);
-        } else {
-            KLAUNCH(p, s, "k_dp_chain", k_dp_chain_long<4>, waves, dim3(CHAIN_LONG_NT), ab, wall, ws.rows_g, pitch);
+        const dim3 fill(lo.L, (uint32_t)(pitch / 4096 + 1));
+        KLAUNCH(p, s, "k_dp_prep", k_dp_prep, fill, dim3(64), ab, ws.dl, 0u, ws.rows_g, pitch, CHAIN_PAD, halves ? ws.dl.he : (double*)nullptr);
+        const uint32_t waves = (uint32_t)(cap / CHAIN_LONG_CELLS + 1);
+        auto chain = [&](uint32_t grid, const ChainHalves& ch) -> int {
+            const uint32_t* wall = ws.dl.wall;
+            if (lo.J <= 16) KLAUNCH(p, s, "k_dp_chain", k_dp_chain_long<1>, dim3(grid), dim3(CHAIN_LONG_NT), ab, wall, ws.rows_g, pitch, ch);
+            else if (lo.J <= 32) KLAUNCH(p, s, "k_dp_chain", k_dp_chain_long<2>, dim3(grid), dim3(CHAIN_LONG_NT), ab, wall, ws.rows_g, pitch, ch);
+            else KLAUNCH(p, s, "k_dp_chain", k_dp_chain_long<4>, dim3(grid), dim3(CHAIN_LONG_NT), ab, wall, ws.rows_g, pitch, ch);
+            return KIMAD_OK;
+        };
+        const double* last = ws.rows_g + (uint64_t)lo.L * pitch + CHAIN_PAD;
+        ChainHalves ch{};
+        const uint32_t* gate = nullptr;
+        if (halves) {
+            ch.order = at<uint32_t>(p, lo.half_order); ch.falling = ws.dl.he; ch.least[0] = ws.row0; ch.least[1] = ws.row1;
+            ch.split = lo.L / 2;
+            int rc = chain(2 * waves, ch);
+            if (rc) return rc;
+            double* results = ws.row0 + MEET_RESULTS;
+            KLAUNCH(p, s, "k_dp_meet", k_dp_meet, dim3((uint32_t)(cap / MEET_THREADS + 1)), dim3(MEET_THREADS), ab, (const double*)ws.dl.habs,
+                    (const double*)(ws.rows_g + (uint64_t)ch.split * pitch + CHAIN_PAD), last, (const double*)ws.row1, results);
+            KLAUNCH(p, s, "k_dp_back", k_dp_back, dim3(2), dim3(BACK_THREADS), ab, (const double*)ws.rows_g, pitch, CHAIN_PAD, ch.split, ch.order,
+                    (const uint32_t*)ws.dl.wall, ch.falling, (const uint32_t*)ws.dl.bad, (const double*)ws.row1,
+                    (const double*)(results + 3 * MEET_MAX), (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE,
+                    (int32_t)KIMAD_ERR_INTERNAL, sl);
+            KLAUNCH(p, s, "k_dp_refill", k_dp_refill, dim3(std::min<uint32_t>(lo.L, 64u), 16), dim3(64), ab, ws.rows_g, pitch, CHAIN_PAD);
+            ch.order = nullptr;
+            ch.gate = gate = ws.flags + FLAG_CHAIN;
         }
-        KLAUNCH(p, s, "k_dp_final", k_dp_final, dim3(1), dim3(1024), ab, (const double*)(ws.rows_g + (uint64_t)lo.L * pitch + CHAIN_PAD),
-                (const uint32_t*)ws.dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL, sl);
+        int rc = chain(waves, ch);
+        if (rc) return rc;
+        KLAUNCH(p, s, "k_dp_final", k_dp_final, dim3(1), dim3(1024), ab, last, (const uint32_t*)ws.dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE,
+                (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL, sl, gate);
     } else {
         const uint32_t cell_blocks = (uint32_t)((cap + 1 + 255) / 256);
         // (clears with a kernel, not hipMemsetAsync: the call may be recorded into a graph)
@@ -790,7 +824,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
             KLAUNCH(p, s, "k_dp_layer", k_dp_layer, dim3(cell_blocks), dim3(256), ab, i, rows[i & 1], rows[(i + 1) & 1]);
         }
         KLAUNCH(p, s, "k_dp_final", k_dp_final, dim3(1), dim3(1024), ab, (const double*)rows[lo.L & 1], (const uint32_t*)nullptr,
-                (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL, sl);
+                (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL, sl, (const uint32_t*)nullptr);
     }
     return KIMAD_OK;
 }
@@ -915,6 +949,12 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
         p->kmax[i] = p->ktab[(size_t)i * J + J - 1];
     }
     const std::vector<ReduceLayer> reduce = pt.reduce_layers();
+    // the halves of an allocation beyond LDS: layers that reach least first, dealt out in turn
+    std::vector<uint32_t> by_reach(L), half_order;
+    std::iota(by_reach.begin(), by_reach.end(), 0u);
+    std::stable_sort(by_reach.begin(), by_reach.end(), [&](uint32_t a, uint32_t b) { return p->kmax[a] < p->kmax[b]; });
+    for (uint32_t h = 0; h < 2; ++h)
+        for (uint32_t i = 1 - h; i < L; i += 2) half_order.push_back(by_reach[i]);
     hipStream_t s = static_cast<hipStream_t>(stream);
     auto up = [&](uint64_t off, const void* src, size_t bytes) {
         return hipMemcpyAsync(p->ws + off, src, bytes, hipMemcpyHostToDevice, s) == hipSuccess;
@@ -930,7 +970,8 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
               up(lo.small_layer, small_layer.data(), 4ull * small_layer.size()) &&
               up(lo.swg_layer, swg_layer.data(), 4ull * swg_layer.size()) &&
               up(lo.swg_first, swg_first.data(), 4ull * swg_first.size()) &&
-              up(lo.cblk_big, cblk_big.data(), 4ull * cblk_big.size());
+              up(lo.cblk_big, cblk_big.data(), 4ull * cblk_big.size()) &&
+              up(lo.half_order, half_order.data(), 4ull * L);
     ok = ok && hipStreamSynchronize(s) == hipSuccess;     // host vectors go out of scope below
     if (!ok) { delete p; return KIMAD_ERR_HIP; }
 
@@ -1064,7 +1105,7 @@ int kimad_allocate_static(kimad_plan_t* p, const double* err_table, uint64_t bud
     ws.row0 = nullptr; ws.row1 = nullptr;                       // only the per-layer-launch path uses them
     ws.choice = reinterpret_cast<uint8_t*>(take((uint64_t)KIMAD_STATIC_MAX_L * CELLS));
     ws.cprev = reinterpret_cast<uint16_t*>(take(2ull * Pieces(KIMAD_STATIC_MAX_L).count() * CELLS));
-    ws.flags = reinterpret_cast<uint32_t*>(take(16));
+    ws.flags = reinterpret_cast<uint32_t*>(take(4 * DP_FLAGS));
     ws.dl.wall = reinterpret_cast<uint32_t*>(take(4 * LJ)); ws.dl.w = reinterpret_cast<uint32_t*>(take(4 * LJ));
     ws.dl.jj = reinterpret_cast<uint32_t*>(take(4 * LJ)); ws.dl.e = reinterpret_cast<double*>(take(16 * LJ));
     ws.dl.n = reinterpret_cast<uint32_t*>(take(4ull * KIMAD_STATIC_MAX_L));
