@@ -435,39 +435,73 @@ __device__ __forceinline__ void additions_done() { asm volatile("s_waitcnt vmcnt
 // GPT-2-shaped set in the classic profile 296, 280, 503.  Sixteen waves, one workgroup to a compute unit, without the fence: GPT-2-
 // shaped 352, 700 layers 90; eight waves, two: 348 and 78.  A report after four or 64 runs: the same.)
 constexpr uint32_t HIST2_MAX_ELEMS = 32768;    // elements a workgroup may count before it flushes: the count field has 16 bits
-// As many tiles as the counts admit, but at least 256 groups, one a compute unit, where the set has the tiles for them.
+// As many tiles as the counts admit, but at least 256 groups, one a compute unit, where the layers to be counted have the tiles for them.
 // (Groups of 32768 elements left a perceptron of 266 K elements nine workgroups: k_hist2 9 -> 22 us, a classic profile
 // 61 -> 80 us.  At least 512 or 1024 groups: 19 recounted layers of ResNet-18 56 -> 68 or 98 us, 53 of ResNet-50 72 -> 71 or 83;
 // at least 128: the same as 256.)
-inline uint32_t hist2_group_tiles(uint32_t ntiles, uint32_t tile_elems) {
+__host__ __device__ inline uint32_t hist2_group_tiles(uint32_t ntiles, uint32_t tile_elems) {
     const uint32_t most = HIST2_MAX_ELEMS / tile_elems, share = ntiles / 256u;
     return share < 1u ? 1u : share < most ? share : most;
 }
+// Only tiles of layers that are to be counted are dealt out: the workgroups list these layers, whose tiles then follow one another
+// (beyond LIST layers, all tiles).  (Dealt out with all others, seven layers of ResNet-18 with 50 ratios, of 9 to 37 thousand entries but for one, lay in
+// a dozen workgroups, which took eight tiles each one after another, and scanned two layers in turn: 37 us, now 28 on average and 18 in a round
+// with few of them.)
 constexpr uint32_t HIST2_THREADS = SCAN2_THREADS;
-__global__ __launch_bounds__(HIST2_THREADS, 6) void k_hist2(ProfileBuffers pb, uint32_t nbig, uint32_t ntiles, uint32_t group_tiles, const uint32_t* gate,
+__global__ __launch_bounds__(HIST2_THREADS, 6) void k_hist2(ProfileBuffers pb, uint32_t nbig, uint32_t ntiles, const uint32_t* gate,
                                                          uint32_t coarse, const uint32_t* Ktab, uint32_t J, double* err_table, double tol,
                                                          double widen) {
     __shared__ unsigned long long sub[MAX_SLOTS * D2_BINS];   // 64 KB
     __shared__ unsigned long long sub0[D2_BINS];              // exact squares when the slot is bin 0
     __shared__ uint8_t lut[D1_BINS];
-    constexpr uint32_t RUNS = 8;
+    constexpr uint32_t RUNS = 8, LIST = HIST2_THREADS;
     __shared__ uint32_t run_big[RUNS], run_tiles[RUNS];       // tiles counted and not yet reported, by layer
     __shared__ uint64_t sh_which;
+    __shared__ uint32_t tile_end[1024], su[16];               // tiles up to a listed layer's last; behind them the greatest number
+    __shared__ uint16_t listed[LIST];                         // the layer, counted from the list's first
     uint32_t tid = threadIdx.x;
     const bool counting = blockIdx.x >= nbig;
     if (counting && gate && *gate == 0u) return;
     if (tid == 0) run_big[0] = blockIdx.x;      // (the layer of one that only scans)
+    // with up to LIST layers, those that are to be counted
+    const bool list = nbig <= LIST;
+    if (counting && list) {
+        uint32_t mine = 0u, n;
+        if (tid < nbig) {
+            const LayerState st = pb.state[tid];
+            if (st.redo && st.nslots_d != 0u) mine = pb.layers[pb.big_layer[tid]].ntiles;
+        }
+        for (uint32_t x = tid; x < 1024u; x += HIST2_THREADS) tile_end[x] = 0xFFFFFFFFu;
+        const uint64_t has = ballot(mine != 0u);
+        const uint32_t before = block_exclusive_scan<uint32_t>(mine, su, &n);                            // (has barriers)
+        const uint32_t at = block_exclusive_scan<uint32_t>((tid & 63u) == 0u ? (uint32_t)__popcll(has) : 0u, su, nullptr);
+        const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        if (mine) { tile_end[first + mbcnt(has)] = before + mine; listed[first + mbcnt(has)] = (uint16_t)tid; }
+        ntiles = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
+        __syncthreads();
+    }
+    const uint32_t group_tiles = hist2_group_tiles(ntiles, pb.tile_elems);
     uint32_t tile0 = (blockIdx.x - nbig) * group_tiles, tile = tile0;        // the group, and its next tile
     for (;;) {
     uint32_t runs = 0u;
     while (counting && runs < RUNS && tile0 < ntiles) {
     asm volatile("" : "+v"(tid));               // (else addresses are worked out ahead of the loop, and kept through the scan)
     // the group's tiles of one layer
-    const uint32_t li = pb.tile_layer[tile];
+    uint32_t li, end;                           // the layer, and the tile behind its last
+    if (list) {
+        uint32_t at = 0u;
+        for (uint32_t half = 512u; half; half >>= 1)
+            if ((uint32_t)__builtin_amdgcn_readfirstlane((int)tile_end[at + half - 1u]) <= tile) at += half;
+        end = (uint32_t)__builtin_amdgcn_readfirstlane((int)tile_end[at]);
+        li = pb.big_layer[__builtin_amdgcn_readfirstlane((int)listed[at])];
+    } else {
+        li = pb.tile_layer[tile];
+        end = pb.layers[li].tile0 + pb.layers[li].ntiles;
+    }
     const LayerDesc L = pb.layers[li];
     const LayerState st = pb.state[L.big];
     const uint32_t ns = st.nslots_d;
-    const uint32_t first = tile, last = min(min(ntiles, tile0 + group_tiles), L.tile0 + L.ntiles);
+    const uint32_t last = min(min(ntiles, tile0 + group_tiles), end), first = L.ntiles - (end - tile), count = last - tile;      // (first: in the layer)
     tile = last;
     if (tile == min(ntiles, tile0 + group_tiles)) { tile0 += (gridDim.x - nbig) * group_tiles; tile = tile0; }
     if (!st.redo || ns == 0) continue;
@@ -480,10 +514,10 @@ __global__ __launch_bounds__(HIST2_THREADS, 6) void k_hist2(ProfileBuffers pb, u
     if (tid < D2_BINS) sub0[tid] = 0ull;
     __syncthreads();
 
-    const uint32_t vend = (last - L.tile0) * pb.tile_elems;
+    const uint32_t vend = (first + count) * pb.tile_elems;
     const uint32_t lane4 = 4u * (tid & 63u);
     constexpr uint32_t QUADS = 2;               // a thread's loads under way
-    for (uint32_t v = (first - L.tile0) * pb.tile_elems + (uint32_t)__builtin_amdgcn_readfirstlane(tid & ~63u) * 4u; v < vend;
+    for (uint32_t v = first * pb.tile_elems + (uint32_t)__builtin_amdgcn_readfirstlane(tid & ~63u) * 4u; v < vend;
          v += 4u * QUADS * HIST2_THREADS) {
         Quad q[QUADS];
 #pragma unroll
@@ -523,7 +557,7 @@ __global__ __launch_bounds__(HIST2_THREADS, 6) void k_hist2(ProfileBuffers pb, u
             if (s) atomicAdd(&sq[b], s);
         }
     }
-    if (tid == 0) { run_big[runs] = (uint32_t)L.big; run_tiles[runs] = last - first; }
+    if (tid == 0) { run_big[runs] = (uint32_t)L.big; run_tiles[runs] = count; }
     ++runs;
     __syncthreads();                            // the next tiles reuse the LDS tables
     }

@@ -527,7 +527,7 @@ int run_select_passes(kimad_plan* p, const uint32_t* ktab_dev, uint32_t J, doubl
         KLAUNCH(p, s, "k_hist1", k_hist1, dim3(lo.ntiles), dim3(256), p->pb);
         KLAUNCH(p, s, "k_scan1", k_scan1, dim3(lo.B), dim3(256), p->pb, ktab_dev, J);
         const uint32_t group = hist2_group_tiles(lo.ntiles, lo.tile_elems);
-        KLAUNCH(p, s, "k_hist2", k_hist2, dim3(lo.B + (lo.ntiles + group - 1) / group), dim3(HIST2_THREADS), p->pb, lo.B, lo.ntiles, group,
+        KLAUNCH(p, s, "k_hist2", k_hist2, dim3(lo.B + (lo.ntiles + group - 1) / group), dim3(HIST2_THREADS), p->pb, lo.B, lo.ntiles,
                 (const uint32_t*)nullptr, 0u, ktab_dev, J, err_table, CERT_TOL, 0.0);
         // exact last-digit pass for the entries that the scan could not certify (usually none)
         if (err_table) KLAUNCH(p, s, "k_hist3p", k_hist3p, dim3(std::min<uint32_t>(lo.ntiles, FALLBACK_GRID)), dim3(HIST3_THREADS), p->pb, lo.ntiles, err_table, mark_fresh);
@@ -598,7 +598,7 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
     // the scan of every layer's slots, and a recount of the layers marked redo: a small grid, since there are none as a rule
     const uint32_t group = hist2_group_tiles(lo.ntiles, lo.tile_elems);
     KLAUNCH(p, s, "k_hist2", k_hist2, dim3(lo.B + std::min<uint32_t>((lo.ntiles + group - 1) / group, RECOUNT_GRID)), dim3(HIST2_THREADS), p->pb,
-            lo.B, lo.ntiles, group, (const uint32_t*)(at<uint32_t>(p, lo.diag) + 3), 1u, ktab, J, err_table, CERT_TOL, SLOT_WIDEN);
+            lo.B, lo.ntiles, (const uint32_t*)(at<uint32_t>(p, lo.diag) + 3), 1u, ktab, J, err_table, CERT_TOL, SLOT_WIDEN);
     if (!err_table) return KIMAD_OK;
     KLAUNCH(p, s, "k_hist3p", k_hist3p, dim3(std::min<uint32_t>(lo.ntiles, FALLBACK_GRID)), dim3(HIST3_THREADS), p->pb, lo.ntiles, err_table, 1u);
     return KIMAD_OK;
