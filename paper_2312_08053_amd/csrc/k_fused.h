@@ -96,12 +96,14 @@ __device__ __forceinline__ void predict(const ProfileBuffers& pb, uint32_t big, 
     __shared__ uint32_t bitmap[D1_BINS / 32];
     __shared__ uint32_t su[16];
     __shared__ unsigned long long s64[16];
-    __shared__ uint32_t sh_gbin, sh_spill, sh_eighth, sh_ns, sh_gap, sh_knext;
+    __shared__ uint32_t sh_gbin, sh_spill, sh_eighth, sh_ns, sh_gap, sh_knext, sh_low;
+    __shared__ uint64_t sh_words[D1_BINS / 32 / 64];
     const uint32_t tid = threadIdx.x;
     const uint32_t li = pb.big_layer[big];
     const LayerDesc L = pb.layers[li];
 
-    // this layer's sample counts are asked for together with the global ones of step (1)
+    // this layer's sizes and sample counts are asked for together with the global ones of step (1)
+    const uint32_t K = Ktab[(size_t)li * J + min(tid, J - 1u)], K_next = Ktab[(size_t)li * J + min(tid + 1u, J - 1u)];
     uint32_t c[16], csum = 0;
     {
         const uint4* sh4 = reinterpret_cast<const uint4*>(counts + (size_t)big * D1_BINS + tid * 16u);
@@ -148,22 +150,27 @@ __device__ __forceinline__ void predict(const ProfileBuffers& pb, uint32_t big, 
     if (tid < D1_BINS / 32) bitmap[tid] = 0u;
     __syncthreads();
     const double scale = (double)L.n / (double)(ns_total ? ns_total : 1u);   // population per sample entry
-    // smallest bin with above[bin] < k, i.e. the bin holding the sample entry of rank k (k >= 1)
-    auto find_bin = [&](uint32_t k) {
-        uint32_t lo = 0, hi = D1_BINS - 1;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (above[mid] < k) hi = mid; else lo = mid + 1;
+    // Smallest bins with above[bin] < k, i.e. the bins holding the sample entries of ranks k (k >= 1), several at a time: twelve
+    // reads of LDS one after another, whatever their number.
+    auto find_bins = [&](auto& k, auto& bin) {
+        constexpr int N = sizeof(k) / sizeof(k[0]);
+#pragma unroll
+        for (int q = 0; q < N; ++q) bin[q] = 0u;
+#pragma unroll
+        for (uint32_t half = D1_BINS / 2u; half; half >>= 1) {
+            uint32_t there[N];
+#pragma unroll
+            for (int q = 0; q < N; ++q) there[q] = above[bin[q] + half - 1u];
+#pragma unroll
+            for (int q = 0; q < N; ++q) bin[q] += there[q] >= k[q] ? half : 0u;
         }
-        return lo;
     };
     // The size the allocation will choose for this layer: an allocation cuts all layers at about
     // the same magnitude, rounded to the grid: the second grid size above this layer's entries in the global bins (the
     // first one left a few of ResNet-50's layers short, which then read g and h again).
     if (narrow && tid < J) {
-        const uint32_t K = Ktab[(size_t)li * J + tid], K2 = Ktab[(size_t)li * J + min(tid + 1u, J - 1u)];
         const double here = scale * (double)(sh_gbin ? above[sh_gbin - 1u] : ns_total);
-        if ((double)K >= here) atomicMin(&sh_knext, K2);
+        if ((double)K >= here) atomicMin(&sh_knext, K_next);
     }
     __syncthreads();
     if (tid == 0) {
@@ -174,7 +181,7 @@ __device__ __forceinline__ void predict(const ProfileBuffers& pb, uint32_t big, 
         // times: with 2 % of every layer and the entries of 2.5 budgets the Llama-shaped set's k_main took 2412 us and its
         // step 3360, with this 2267 and 3204.  Without the rounding, 66 to 108 of that set's 169 tiled layers ended short with
         // 2 to 6 % of the bytes to spend and read g and h again: steps of 3970 us at 2 % and 5720 at 6 %, now 3460 and 4530.
-        const uint32_t K0 = Ktab[(size_t)li * J];
+        const uint32_t K0 = K;
         const double k0s = 2.0 * (double)K0 / scale;
         uint32_t floor_rank = (uint32_t)fmin((double)ns_total, ceil(k0s + 3.0 * sqrt(k0s) + 2.0));
         // (a selection has one target: nothing above it needs a slot)
@@ -184,12 +191,15 @@ __device__ __forceinline__ void predict(const ProfileBuffers& pb, uint32_t big, 
             const double kns = (double)min(aim, (unsigned long long)L.n) / scale;
             floor_rank = max(floor_rank, (uint32_t)fmin((double)ns_total, ceil(kns + 3.0 * sqrt(kns) + 2.0)));
         }
-        uint32_t b = find_bin(floor_rank);
-        if (budget_pairs) b = min(b, sh_gbin);
         // never more than the top eighth of the layer: the bin that holds the entry of that rank is spilled only
         // if all of it still lies inside (a layer's candidate region has room for a little more than that share)
         const uint32_t k8 = max(1u, ns_total / 8u);
-        uint32_t bc = find_bin(k8);
+        const uint32_t rank[3] = {floor_rank, k8, max(1u, above[0])};
+        uint32_t bin[3];
+        find_bins(rank, bin);
+        const uint32_t b = budget_pairs ? min(bin[0], sh_gbin) : bin[0];
+        uint32_t bc = bin[1];
+        sh_low = bin[2];
         if ((bc == 0u ? ns_total : above[bc - 1u]) > k8) ++bc;     // D1_BINS: nothing is spilled
         sh_spill = max(b, bc);
         sh_eighth = bc;
@@ -203,7 +213,6 @@ __device__ __forceinline__ void predict(const ProfileBuffers& pb, uint32_t big, 
     // Bin 0 (zeros and the tiniest denormals) never gets a slot here: its squares need the exact
     // accumulators of the full recount.
     if (tid < J) {
-        const uint32_t K = Ktab[(size_t)li * J + tid];
         if (K < L.n) {
             const double ks = (double)K / scale;
             const double sg = sqrt(fmax(0.0, ks * (1.0 - ks / (double)ns_total)));
@@ -211,13 +220,18 @@ __device__ __forceinline__ void predict(const ProfileBuffers& pb, uint32_t big, 
             const uint32_t rlo = (uint32_t)fmin((double)ns_total, fmax(1.0, klo));
             const uint32_t rhi = (uint32_t)fmin((double)ns_total, fmax(1.0, khi));
             // (no lower than the smallest entry above bin 0: where many entries are exactly zero, all bins below it are empty)
-            const uint32_t btop = find_bin(rlo), bbot = max(khi > (double)ns_total ? 0u : find_bin(rhi), find_bin(max(1u, above[0])));
+            const uint32_t rank[2] = {rlo, rhi};
+            uint32_t bin[2];
+            find_bins(rank, bin);
+            const uint32_t btop = bin[0], bbot = max(khi > (double)ns_total ? 0u : bin[1], sh_low);
             // A boundary in the spilled range can also be resolved from the candidates, which is
             // cheap only where few entries lie above it: skip the prediction for the sparse top
             // (fewer than 64 sample entries above), where it would cost many bins.
             const bool sparse_top = ks < 64.0 && bbot >= spill_bin;
-            if (!sparse_top)
-                for (uint32_t b = max(bbot, 1u); b <= btop; ++b) atomicOr(&bitmap[b >> 5], 1u << (b & 31));
+            const uint32_t lo = max(bbot, 1u);
+            if (!sparse_top && lo <= btop)
+                for (uint32_t w = lo >> 5; w <= btop >> 5; ++w)
+                    atomicOr(&bitmap[w], (w == lo >> 5 ? ~0u << (lo & 31u) : ~0u) & (w == btop >> 5 ? ~0u >> (31u - (btop & 31u)) : ~0u));
         }
     }
     __syncthreads();
@@ -247,20 +261,28 @@ __device__ __forceinline__ void predict(const ProfileBuffers& pb, uint32_t big, 
     uint32_t ns = any ? min(PRE_SLOTS, hi_bin - lo_bin + 1u) : 0u, run_a = ns, lo_b = 0u;
     if (any && lo_bin + PRE_SLOTS <= min(hi_bin, spill_bin - 1u)) {    // (the same in every thread; spill_bin is never 0 then)
         // the widest stretch that ends before a marked bin: its width, then that bin
-        if (tid < D1_BINS / 32) {
-            uint32_t m = bitmap[tid], before = 0xFFFFFFFFu;
-            if (m) {
-                for (uint32_t w = tid; w-- > 0u && before == 0xFFFFFFFFu;)
-                    if (bitmap[w]) before = w * 32u + 31u - (uint32_t)__clz((int)bitmap[w]);
-                uint32_t widest = 0u;
-                while (m) {
-                    const uint32_t b = tid * 32u + (uint32_t)__ffs((int)m) - 1u;
-                    m &= m - 1u;
-                    if (before != 0xFFFFFFFFu) widest = max(widest, ((b - before - 1u) << D1_BITS) | b);
-                    before = b;
+        const uint32_t m = tid < D1_BINS / 32 ? bitmap[tid] : 0u;
+        const uint64_t words = ballot(m != 0u);
+        if (tid < D1_BINS / 32 && lane_id() == 0u) sh_words[tid >> 6] = words;
+        __syncthreads();
+        if (m) {
+            // bins whose neighbour below is not marked
+            uint32_t starts = m & ~((m << 1) | (tid ? bitmap[tid - 1u] >> 31 : 0u)), widest = 0u;
+            for (; starts; starts &= starts - 1u) {
+                const uint32_t at = (uint32_t)__ffs((int)starts) - 1u, low = m & ((1u << at) - 1u), b = tid * 32u + at;
+                uint32_t w = tid, word = low;
+                if (!low) {
+                    // the marked word before this one
+                    const uint64_t here = sh_words[tid >> 6] & ((1ull << lane_id()) - 1ull);
+                    const bool one = here != 0ull || (tid >= 64u && sh_words[0] != 0ull);
+                    if (!one) continue;                                // (the lowest marked bin)
+                    w = here ? (tid & ~63u) + 63u - (uint32_t)__clzll((long long)here) : 63u - (uint32_t)__clzll((long long)sh_words[0]);
+                    word = bitmap[w];
                 }
-                atomicMax(&sh_gap, widest);
+                const uint32_t before = w * 32u + 31u - (uint32_t)__clz((int)word);
+                widest = max(widest, ((b - before - 1u) << D1_BITS) | b);
             }
+            atomicMax(&sh_gap, widest);
         }
         __syncthreads();
         const uint32_t gap = sh_gap >> D1_BITS;

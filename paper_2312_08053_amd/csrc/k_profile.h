@@ -769,33 +769,50 @@ __device__ __forceinline__ uint32_t lane_xor_u32(uint32_t v) {
     return __shfl_xor(v, X, 64);
 }
 
+// The smaller of two values where `k` is 0, the larger where it is ~0: one instruction for either direction.
+__device__ __forceinline__ uint32_t min_or_max(uint32_t a, uint32_t b, uint32_t k) {
+    uint32_t r;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(k));
+    return r;
+}
 // Compare-exchange of every value with the lane X away: the lane whose bit X is clear keeps the smaller if `up`.
 template <int X>
 __device__ __forceinline__ void sort_lanes(uint32_t (&v)[SORT_PER], bool up) {
-    const bool keep_min = ((lane_id() & (uint32_t)X) == 0u) == up;
+    const uint32_t k = ((lane_id() & (uint32_t)X) == 0u) == up ? 0u : ~0u;
 #pragma unroll
     for (int r = 0; r < (int)SORT_PER; ++r) {
-        const uint32_t o = lane_xor_u32<X>(v[r]);
-        v[r] = keep_min ? min(v[r], o) : max(v[r], o);
+        if constexpr (X >= 16) {
+            // (both lanes of a pair get both values)
+            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+            const u32x2 p = X == 16 ? __builtin_amdgcn_permlane16_swap(v[r], v[r], false, false) : __builtin_amdgcn_permlane32_swap(v[r], v[r], false, false);
+            v[r] = min_or_max(p.x, p.y, k);
+        } else {
+            v[r] = min_or_max(v[r], lane_xor_u32<X>(v[r]), k);
+        }
     }
 }
 // The same among a thread's own values, distance D = 1, 2, 4; K: the run length being merged if it is inside a thread
 // (2, 4: the direction then alternates among its values), else 8 and `up` holds for all of them.
 template <int D, int K>
 __device__ __forceinline__ void sort_own(uint32_t (&v)[SORT_PER], bool up) {
+    const uint32_t k = up ? 0u : ~0u;
 #pragma unroll
     for (int r = 0; r < (int)SORT_PER; ++r) {
         if (r & D) continue;
-        const uint32_t lo = min(v[r], v[r + D]), hi = max(v[r], v[r + D]);
-        const bool u = K < 8 ? (r & K) == 0 : up;
-        v[r] = u ? lo : hi;
-        v[r + D] = u ? hi : lo;
+        const uint32_t a = v[r], b = v[r + D];
+        if (K < 8) {
+            v[r] = (r & K) == 0 ? min(a, b) : max(a, b);
+            v[r + D] = (r & K) == 0 ? max(a, b) : min(a, b);
+        } else {
+            v[r] = min_or_max(a, b, k);
+            v[r + D] = min_or_max(a, b, ~k);
+        }
     }
 }
 
 // Bitonic sort, ascending, of P values (a power of two, 8 to SMALL_MAX): value 8 t + r is v[r] of thread t; threads
 // from P / 8 on take part in the barriers only.  The result is left in `a` (P words), behind a barrier.  Distances below
-// 8 are inside a thread, below 512 inside a wave (DPP moves, two shuffles for the widest), and only the ten steps of the
+// 8 are inside a thread, below 512 inside a wave (DPP moves, lane swaps for the two widest), and only the ten steps of the
 // largest layer that cross waves go through LDS.  Sorting (magnitude, index) pairs of 64 bits through LDS at every
 // step, as before, took 65 to 79 us of k_small_profile on a layer of 8192 entries and 40 us on one of 4096; the order
 // among equal magnitudes changes no sum.
@@ -823,9 +840,9 @@ __device__ __forceinline__ void sort_small(uint32_t (&v)[SORT_PER], uint32_t* a,
                 const uint4* from = reinterpret_cast<const uint4*>(a + (base ^ d));
                 const uint4 o0 = from[0], o1 = from[1];
                 const uint32_t o[SORT_PER] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
-                const bool keep_min = ((base & d) == 0u) == up;
+                const uint32_t keep = ((base & d) == 0u) == up ? 0u : ~0u;
 #pragma unroll
-                for (int r = 0; r < (int)SORT_PER; ++r) v[r] = keep_min ? min(v[r], o[r]) : max(v[r], o[r]);
+                for (int r = 0; r < (int)SORT_PER; ++r) v[r] = min_or_max(v[r], o[r], keep);
             }
             __syncthreads();
         }
