@@ -336,7 +336,7 @@ __global__ __launch_bounds__(SMALL_THREADS, 8) void k_predict(ProfileBuffers pb,
 }
 
 // ---------------------------------------------------------------------------------------------
-// The streaming pass.  Persistent grid: workgroup w owns a contiguous range of chunks, walks it
+// The streaming pass.  Persistent grid: workgroup w owns a contiguous range of chunks (shares.h), walks it
 // layer by layer, and keeps that layer's histograms in LDS as one array of packed entries
 // [count:20 | sum:44] of (significand^2 >> 24): 4096 digit-1 bins, then up to PRE_SLOTS slots x 128 digit-2
 // bins.  Entries whose bin has a slot are counted only there.  Bin 0 (zeros, tiniest denormals)
@@ -705,7 +705,7 @@ __device__ __forceinline__ uint32_t main_walk(const ProfileBuffers& pb, const Ma
 
 // STREAM: the candidates are stored nontemporally.
 template <bool STREAM>
-__global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint32_t chunks_per_wg) {
+__global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb) {
     __shared__ __align__(16) unsigned long long pk[PK_ENTRIES];   // 140 KB
     __shared__ unsigned long long sq0;
     __shared__ float stage_x[FUSED_WAVES * STAGE];                // 8 KB and 4 KB: per-wave block windows
@@ -715,13 +715,11 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_main(ProfileBuffers pb, uint3
     __shared__ uint32_t next_chunk, allowed, limit_state;         // Segment
     __shared__ uint32_t head[PART_HEAD];
     const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t c_begin = blockIdx.x * chunks_per_wg;
-    const uint32_t c_end = min(pb.nchunks_total, c_begin + chunks_per_wg);
-    uint32_t cur = c_begin;
-    uint32_t part = pb.wg_part0[blockIdx.x];
-    while (cur < c_end) {
-        const uint32_t big = pb.chunk_big[cur];
-        const uint32_t li = pb.big_layer[big];
+    const MainShare share = pb.shares[blockIdx.x];
+    const uint32_t c_end = pb.shares[blockIdx.x + 1u].chunk;
+    uint32_t cur = share.chunk, part = share.part0, li = share.li;
+    for (uint32_t big = share.big, next_li; cur < c_end; ++big, li = next_li) {
+        next_li = pb.big_layer[big + 1u];
         const LayerDesc L = pb.layers[li];
         const LayerState st = pb.state[big];
         const uint32_t seg_end = min(c_end, L.chunk0 + L.nchunks);

@@ -10,6 +10,9 @@ namespace kimad {
 
 // A layer that k_reduce_parts sums up: its parts (there is room for one every PK_MAX_CHUNKS chunks).
 struct ReduceLayer { uint32_t big, part0, nparts, pad; };
+// A workgroup's share of the streaming pass: the first chunk (it ends where the next one begins), its first part (the others follow in
+// order), and the first chunk's layer, among the tiled ones and among all.
+struct MainShare { uint32_t chunk, part0, big, li; };
 
 struct ProfileBuffers {
     const LayerDesc* layers;
@@ -62,7 +65,7 @@ struct ProfileBuffers {
     // histograms of the streaming pass, one copy ("part") per workgroup and layer, or more where a copy's counts fill up
     uint32_t* part_head;          // [nparts][PART_HEAD] whether there is one, and how its blocks were written
     unsigned long long* parts;    // [nparts][PART_STRIDE] the LDS entries, in blocks, then the exact bin-0 sum
-    const uint32_t* wg_part0;     // [workgroups] first part of each workgroup (its parts follow in order)
+    const MainShare* shares;      // [workgroups + 1]
     const ReduceLayer* reduce_layers;   // [B] in the order of k_reduce_parts' workgroups
     const uint32_t* chunk_big;    // chunk -> big index
     const uint32_t* chunk_first;  // chunk -> first chunk of its layer

@@ -15,6 +15,7 @@
 
 #include "../../include/kimad.h"
 #include "common.h"
+#include "shares.h"
 #include "k_profile.h"
 #include "k_fused.h"
 #include "k_compress.h"
@@ -52,8 +53,8 @@ struct Layout {
     uint64_t fresh = 0, hprev = 0, gprev = 0;
     uint64_t zero1_begin, cnt1, sq1, cnt2, sq2, diag, layer_flag, shist, ghist, cursor, spill_over, tiles_done, zero1_end;
     uint64_t cprev = 0;
-    uint64_t big_tmp0, parts, part_head, wg_part0, reduce_layers, zero1_mid;
-    uint32_t main_wgs = 256, chunks_per_wg = 1, nparts = 0, nsplit = 0;
+    uint64_t big_tmp0, parts, part_head, shares, reduce_layers, zero1_mid;
+    uint32_t main_wgs = 0, nparts = 0, nsplit = 0;
     uint64_t pool_prefix, pool_big, pool_t0, pool_cnt, pool_hist, tgt_unsel, tgt_base;
     uint32_t pool_cap = 1;
     uint64_t lut1, nslots, slot_bin, slot_cnt, slot_sq;
@@ -147,10 +148,11 @@ uint32_t stream_workgroups(const kimad_config_t& cfg) {
     return w;
 }
 
-// The parts of the streaming pass: workgroup w walks chunks [w * per, (w + 1) * per) and starts a new
-// histogram at every layer boundary and, where a count may fill up, no earlier than after PK_MAX_CHUNKS chunks.
+// A workgroup of the streaming pass starts a new histogram (a part) at every layer boundary of its share and, where a count may
+// fill up, no earlier than after PK_MAX_CHUNKS chunks.
 struct PartTables {
-    std::vector<uint32_t> wg_part0, big_part0, big_nparts;
+    std::vector<MainShare> shares;               // one more than there are workgroups
+    std::vector<uint32_t> big_part0, big_nparts;
     // the layers in the order in which their parts are summed up: those whose blocks take a workgroup each (split) first,
     // which take longest
     std::vector<ReduceLayer> reduce_layers() const {
@@ -164,25 +166,27 @@ struct PartTables {
         return (uint32_t)std::count_if(big_nparts.begin(), big_nparts.end(), [](uint32_t n) { return n > REDUCE_WAVE_PARTS; });
     }
 };
-uint32_t plan_parts(const std::vector<HostLayer>& hl, uint32_t B, uint32_t nchunks, uint32_t wgs, uint32_t per,
-                    PartTables& out) {
-    std::vector<uint32_t> c0(B ? B : 1), c1(B ? B : 1);
-    for (const HostLayer& h : hl)
-        if (h.big >= 0) { c0[h.big] = h.chunk0; c1[h.big] = h.chunk0 + h.nchunks; }
-    out.wg_part0.assign(wgs, 0); out.big_part0.assign(B, 0); out.big_nparts.assign(B, 0);
+// Returns the number of parts.
+uint32_t plan_parts(const std::vector<HostLayer>& hl, uint32_t B, uint32_t nchunks, uint32_t wgs, PartTables& out) {
+    std::vector<uint32_t> ends(B), li(B);
+    for (uint32_t i = 0; i < hl.size(); ++i)
+        if (hl[i].big >= 0) { ends[hl[i].big] = hl[i].chunk0 + hl[i].nchunks; li[hl[i].big] = i; }
+    std::vector<uint32_t> first = plan_shares(ends, wgs);
+    first.push_back(nchunks);
+    out.shares.clear(); out.big_part0.assign(B, 0); out.big_nparts.assign(B, 0);
     uint32_t part = 0, b = 0;
-    for (uint32_t w = 0; w < wgs; ++w) {
-        uint64_t cur = (uint64_t)w * per;
-        const uint64_t c_end = std::min<uint64_t>(nchunks, cur + per);
-        out.wg_part0[w] = part;
-        while (cur < c_end) {
-            while (cur >= c1[b]) ++b;
-            const uint64_t seg_end = std::min<uint64_t>(std::min<uint64_t>(c_end, c1[b]), cur + PK_MAX_CHUNKS);
+    for (size_t w = 0; w + 1 < first.size(); ++w) {
+        uint32_t cur = first[w];
+        if (cur == ends[b]) ++b;
+        out.shares.push_back({cur, part, b, li[b]});
+        while (cur < first[w + 1]) {
+            if (cur == ends[b]) ++b;
             if (out.big_nparts[b]++ == 0) out.big_part0[b] = part;
             ++part;
-            cur = seg_end;
+            cur = std::min<uint32_t>(std::min(first[w + 1], ends[b]), cur + PK_MAX_CHUNKS);
         }
     }
+    out.shares.push_back({nchunks, part, 0u, 0u});
     return part;
 }
 
@@ -242,13 +246,10 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     // budget limit that is L * d bytes, 18 GB for a 124M-element model: refused rather than asked of the caller)
     if ((uint64_t)L * align_up(lo.dp_cells) > (4ull << 30)) return KIMAD_ERR_TABLES_TOO_LARGE;
     lo.tmp_cap = tmp_run;                                 // one region per tiled layer
-    // a workgroup of the streaming pass writes its histograms out whole (140 KB a part): on small sets fewer
-    // workgroups with at least 16 chunks each do less of that than one per compute unit would
-    lo.main_wgs = std::max<uint32_t>(1, std::min<uint32_t>(stream_workgroups(cfg), (lo.nchunks + 15) / 16));
-    lo.chunks_per_wg = std::max<uint32_t>(1, (lo.nchunks + lo.main_wgs - 1) / lo.main_wgs);
     PartTables parts_local;
     PartTables& parts = parts_out ? *parts_out : parts_local;
-    lo.nparts = plan_parts(*hl, B, lo.nchunks, lo.main_wgs, lo.chunks_per_wg, parts);
+    lo.nparts = plan_parts(*hl, B, lo.nchunks, stream_workgroups(cfg), parts);
+    lo.main_wgs = (uint32_t)parts.shares.size() - 1u;
     lo.nsplit = parts.nsplit();
 
     uint64_t off = 0;
@@ -259,9 +260,9 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     lo.tile_layer = take(4ull * (nt ? nt : 1));
     lo.chunk_big = take(4ull * (nc ? nc : 1));
     lo.chunk_first = take(4ull * (nc ? nc : 1));
-    lo.big_layer = take(4ull * (B ? B : 1));
+    lo.big_layer = take(4ull * (B + 1ull));               // (k_main reads a layer ahead)
     lo.big_tmp0 = take(8ull * (B ? B : 1));
-    lo.wg_part0 = take(4ull * lo.main_wgs);
+    lo.shares = take(sizeof(MainShare) * parts.shares.size());
     lo.reduce_layers = take(sizeof(ReduceLayer) * (uint64_t)(B ? B : 1));
     // (the exact pass's pool of last-digit histograms lives in the same memory: the parts are dead once
     // k_reduce_parts has run, and a pool entry is cleared by the workgroup that takes it)
@@ -446,7 +447,6 @@ struct kimad_plan {
     bool all_rows = false;           // the workspace holds every row of an allocation beyond LDS (Layout::total)
     int device = 0;
     uint32_t main_wgs = 256;         // persistent workgroups of the fused pass (one per compute unit)
-    uint32_t chunks_per_wg = 0;
     kimad::ProfileBuffers pb;
     kimad::CompressBuffers cb;
     // optional per-kernel timing (events recorded after every launch)
@@ -579,9 +579,9 @@ int run_single_pass(kimad_plan* p, const uint32_t* ktab, uint32_t J, double* err
     }
     p->hist_valid = true;
     if (lo.nchunks >= STREAM_CANDIDATES_CHUNKS) {
-        KLAUNCH(p, s, "k_main", k_main<true>, dim3(p->main_wgs), dim3(FUSED_THREADS), p->pb, p->chunks_per_wg);
+        KLAUNCH(p, s, "k_main", k_main<true>, dim3(p->main_wgs), dim3(FUSED_THREADS), p->pb);
     } else {
-        KLAUNCH(p, s, "k_main", k_main<false>, dim3(p->main_wgs), dim3(FUSED_THREADS), p->pb, p->chunks_per_wg);
+        KLAUNCH(p, s, "k_main", k_main<false>, dim3(p->main_wgs), dim3(FUSED_THREADS), p->pb);
     }
     KLAUNCH(p, s, "k_reduce_parts", k_reduce_parts, dim3(reduce_workgroups(lo.B, lo.nsplit)), dim3(256), p->pb, lo.nsplit);
     if (err_table && !with_small) {
@@ -913,7 +913,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
     std::vector<LayerDesc> ld(L);
     std::vector<uint32_t> tile_layer(lo.ntiles ? lo.ntiles : 1), chunk_big(lo.nchunks ? lo.nchunks : 1);
     std::vector<uint32_t> chunk_first(lo.nchunks ? lo.nchunks : 1);
-    std::vector<uint32_t> big_layer(lo.B ? lo.B : 1), small_layer(lo.S ? lo.S : 1);
+    std::vector<uint32_t> big_layer(lo.B + 1), small_layer(lo.S ? lo.S : 1);
     std::vector<uint64_t> big_tmp0(lo.B ? lo.B : 1);
     std::vector<uint32_t> swg_layer(lo.nswg ? lo.nswg : 1), swg_first(lo.nswg ? lo.nswg : 1);
     std::vector<uint32_t> cblk_big(lo.ncblk ? lo.ncblk : 1);
@@ -965,7 +965,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
               up(lo.chunk_first, chunk_first.data(), 4ull * chunk_first.size()) &&
               up(lo.big_layer, big_layer.data(), 4ull * big_layer.size()) &&
               up(lo.big_tmp0, big_tmp0.data(), 8ull * big_tmp0.size()) &&
-              up(lo.wg_part0, pt.wg_part0.data(), 4ull * pt.wg_part0.size()) &&
+              up(lo.shares, pt.shares.data(), sizeof(MainShare) * pt.shares.size()) &&
               (reduce.empty() || up(lo.reduce_layers, reduce.data(), sizeof(ReduceLayer) * reduce.size())) &&
               up(lo.small_layer, small_layer.data(), 4ull * small_layer.size()) &&
               up(lo.swg_layer, swg_layer.data(), 4ull * swg_layer.size()) &&
@@ -998,7 +998,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
     pb.pool_hist = at<uint32_t>(p, lo.pool_hist); pb.pool_cap = lo.pool_cap;
     pb.tgt_unsel = at<uint32_t>(p, lo.tgt_unsel); pb.tgt_base = at<double>(p, lo.tgt_base);
     pb.state = at<LayerState>(p, lo.state); pb.big_tmp0 = at<uint64_t>(p, lo.big_tmp0);
-    pb.parts = at<unsigned long long>(p, lo.parts); pb.part_head = at<uint32_t>(p, lo.part_head); pb.wg_part0 = at<uint32_t>(p, lo.wg_part0);
+    pb.parts = at<unsigned long long>(p, lo.parts); pb.part_head = at<uint32_t>(p, lo.part_head); pb.shares = at<MainShare>(p, lo.shares);
     pb.reduce_layers = at<ReduceLayer>(p, lo.reduce_layers);
     pb.chunk_big = at<uint32_t>(p, lo.chunk_big); pb.chunk_first = at<uint32_t>(p, lo.chunk_first); pb.nchunks_total = lo.nchunks;
     pb.swg_layer = at<uint32_t>(p, lo.swg_layer); pb.swg_first = at<uint32_t>(p, lo.swg_first);
@@ -1008,7 +1008,6 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
     pb.rec_start = at<uint32_t>(p, lo.rec_start); pb.rec_cnt = at<uint32_t>(p, lo.rec_cnt);
     pb.tmp_x = at<float>(p, lo.tmp_x); pb.tmp_i = at<uint16_t>(p, lo.tmp_i);
     p->main_wgs = lo.main_wgs;
-    p->chunks_per_wg = lo.chunks_per_wg;
     // Layer states start as "nothing spilled, nothing cached".
     if (hipMemsetAsync(p->ws + lo.state, 0, sizeof(LayerState) * (uint64_t)(lo.B ? lo.B : 1), s) != hipSuccess ||
         hipMemsetAsync(p->ws + lo.zero2_begin, 0, lo.zero2_end - lo.zero2_begin, s) != hipSuccess ||
