@@ -145,9 +145,10 @@ __device__ __forceinline__ void dp_fill_row(const AllocBuffers& ab, double* rows
 // Layer i's candidate list, lane j holding candidate j: where a run starts, its last member's error and the error before it.
 struct DpList {
     uint32_t w, last;              // cost in units, last member of the run that starts here
-    double e_last, e_before;
+    double e, e_last, e_before;    // the candidate's own error, the last member's, that of the member before
     bool start;
     uint64_t starts, nonfinite;    // lanes where a run starts; with an Inf or a NaN
+    uint64_t same;                 // members whose error is that of the one before
 };
 __device__ __forceinline__ DpList dp_list(const AllocBuffers& ab, uint32_t i, uint32_t j) {
     DpList d;
@@ -165,6 +166,8 @@ __device__ __forceinline__ DpList dp_list(const AllocBuffers& ab, uint32_t i, ui
     const double eprev = __shfl_up(e, 1, 64);
     d.start = j < n_in && (j == 0 || d.w != wprev || !(e <= eprev));
     d.starts = ballot(d.start);
+    d.e = e;
+    d.same = ballot(j < n_in && !d.start && e == eprev);
     const uint64_t above = j < 63 ? d.starts & ~((2ull << j) - 1ull) : 0ull;
     d.last = (above ? (uint32_t)__builtin_ctzll(above) : n_in) - 1u;
     d.e_last = __shfl(e, (int)(d.last & 63u), 64);

@@ -32,13 +32,13 @@ constexpr uint32_t TREE_NO_ROOM = 0xFFFFFFFFu;
 
 // An entry of the list of a layer that has a choice, as k_dp_path takes it.
 struct TreeEntry {
-    double e, before;      // error; of the run's member before the last (NaN: there is none)
+    double e, before;      // error; of the run's next member that has another one (NaN: there is none)
     uint32_t w;            // cost beyond the layer's cheapest; 0xFFFFFFFF: no entry
-    uint32_t place;        // place in the layer's list (DpLists) | the run's last member << 16
+    uint32_t place;        // place in the layer's list (DpLists) | the run's lowest member of this error << 16
     uint32_t K;
     uint32_t pad;
 };
-// A layer all of whose sizes cost the same: its best entry, and how much worse the next best and the member before it are.
+// A layer all of whose sizes cost the same: its best entry, and how much worse the next best and the run's next member are.
 struct TreeSingle {
     double next, before;   // (+inf, NaN: there is none)
     uint32_t place, K;     // place as above; 0xFFFFFFFF: the layer has a choice
@@ -102,7 +102,19 @@ __device__ __forceinline__ TreeKept tree_kept(const DpList& d) {
     t.w = d.w - (uint32_t)__builtin_amdgcn_readfirstlane((int)d.w);
     return t;
 }
-__device__ __forceinline__ uint32_t tree_place(const DpList& d) { return mbcnt(d.starts) | (d.last << 16); }
+// Of a run of equal costs, its lowest member of the last one's very error: whatever the sums from the left, theirs are the same, so
+// the chain names no higher one.  And the error of the next member down, which may come to the same total by rounding (NaN: none).
+// (Grids name many a size of a short layer twice.  With the run's member before the last in its place, the totals from the left were
+// formed in every step of ResNet-18, ResNet-50 and the Llama-shaped set: 3.5, 3.6 to 7 and 5.5 us of k_dp_path, one after another.)
+struct TreeRun { uint32_t low; double before; };
+__device__ __forceinline__ TreeRun tree_run(const DpList& d) {
+    const uint32_t last = d.last & 63u;
+    TreeRun r;
+    r.low = last - min(last, (uint32_t)__clzll((long long)~(d.same << (63u - last))));       // (the run's first is not marked)
+    const double below = __shfl(d.e, (int)((r.low - 1u) & 63u), 64);
+    r.before = r.low > lane_id() ? below : __longlong_as_double(0x7FF8000000000000ll);
+    return r;
+}
 
 // Least totals of the segments, by workgroup s < S; the lists, a wave a layer, by the others.
 // Bound by the LDS reads and instructions of a row's cells and a layer's entries (TREE_FEW), and by the way there: the sizes, the
@@ -130,6 +142,7 @@ __global__ __launch_bounds__(SEGMENT_THREADS) void k_dp_segments(AllocBuffers ab
         if (lane == 0u) dl.habs[i] = largest;
         const bool choice = units_of(ab.Ktab[(size_t)i * ab.J], ab.unit) != units_of(ab.Ktab[(size_t)i * ab.J + ab.J - 1u], ab.unit);
         const TreeKept t = tree_kept(d);
+        const TreeRun run = tree_run(d);
         const uint64_t kept = t.kept;
         const int last = kept ? 63 - __builtin_clzll(kept) : 0;                    // the best entry's lane, and the next best's
         const uint64_t others = kept & ~(1ull << last);
@@ -137,9 +150,9 @@ __global__ __launch_bounds__(SEGMENT_THREADS) void k_dp_segments(AllocBuffers ab
         if (lane == (uint32_t)last) {
             TreeSingle one;
             one.next = others ? next - d.e_last : DP_INF;
-            one.before = d.last > lane ? d.e_before - d.e_last : __longlong_as_double(0x7FF8000000000000ll);
-            one.place = choice || !kept ? 0xFFFFFFFFu : tree_place(d);
-            one.K = ab.Kout[(size_t)i * ab.J + min(d.last, ab.J - 1u)];
+            one.before = run.before - d.e_last;
+            one.place = choice || !kept ? 0xFFFFFFFFu : mbcnt(d.starts) | (run.low << 16);
+            one.K = ab.Kout[(size_t)i * ab.J + min(run.low, ab.J - 1u)];
             tb.single[i] = one;
         }
         return;
@@ -170,6 +183,7 @@ __global__ __launch_bounds__(SEGMENT_THREADS) void k_dp_segments(AllocBuffers ab
         const uint32_t i = (uint32_t)__builtin_amdgcn_readfirstlane((int)sorted[wave]);
         const DpList d = dp_list(ab, i, lane);
         const TreeKept t = tree_kept(d);
+        const TreeRun run = tree_run(d);
         const bool fits = t.keep && t.w <= room;                                   // (costs ascend: the first ones)
         const uint32_t n = (uint32_t)__popcll(ballot(fits));
         TreeEntry* out = tb.entry + ((size_t)s * TREE_LAYERS + wave) * 64u;
@@ -177,8 +191,8 @@ __global__ __launch_bounds__(SEGMENT_THREADS) void k_dp_segments(AllocBuffers ab
             recs[wave][t.at] = make_uint4((uint32_t)__double2loint(d.e_last), (uint32_t)__double2hiint(d.e_last), 8u * t.w, 0u);
             TreeEntry x;
             x.e = d.e_last;
-            x.before = d.last > lane ? d.e_before : __longlong_as_double(0x7FF8000000000000ll);
-            x.w = t.w; x.place = tree_place(d); x.K = ab.Kout[(size_t)i * ab.J + min(d.last, ab.J - 1u)]; x.pad = 0u;
+            x.before = run.before;
+            x.w = t.w; x.place = mbcnt(d.starts) | (run.low << 16); x.K = ab.Kout[(size_t)i * ab.J + min(run.low, ab.J - 1u)]; x.pad = 0u;
             out[t.at] = x;
             if (t.at == n - 1u) rec_hi[wave] = t.w;
         }
@@ -641,8 +655,8 @@ __global__ __launch_bounds__(PATH_THREADS) void k_dp_path(AllocBuffers ab, DpLis
         step_lookup(sl, NT);
         return;
     }
-    // Of a run of equal costs the chain names the lowest member whose rounded total is the last one's: where the member before it
-    // is that near, the totals from the left are formed.
+    // Of a run of equal costs the chain names the lowest member whose rounded total is the last one's: where one of another error is
+    // that near, the totals from the left are formed.
     if (state & TREE_NEAR) {
         double* sum = stage;                               // [L + 1]
         static_assert(PATH_STAGE > TREE_MAX_L, "the path's totals fit");
