@@ -104,8 +104,7 @@ __device__ __forceinline__ TreeKept tree_kept(const DpList& d) {
 }
 // Of a run of equal costs, its lowest member of the last one's very error: whatever the sums from the left, theirs are the same, so
 // the chain names no higher one.  And the error of the next member down, which may come to the same total by rounding (NaN: none).
-// (Grids name many a size of a short layer twice.  With the run's member before the last in its place, the totals from the left were
-// formed in every step of ResNet-18, ResNet-50 and the Llama-shaped set: 3.5, 3.6 to 7 and 5.5 us of k_dp_path, one after another.)
+// (Grids name many a size of a short layer twice, and that alone is no reason to form the totals from the left.)
 struct TreeRun { uint32_t low; double before; };
 __device__ __forceinline__ TreeRun tree_run(const DpList& d) {
     const uint32_t last = d.last & 63u;
@@ -629,13 +628,14 @@ __global__ __launch_bounds__(PATH_THREADS) void k_dp_path(AllocBuffers ab, DpLis
     __syncthreads();
     if (!s_last) return;
     const uint32_t state = __hip_atomic_load(&tb.head[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    uint32_t K[LT];                                            // of layers LT tid + q
+    uint32_t K[LT], entry_at[LT];                              // of layers LT tid + q
     int32_t j[LT];
 #pragma unroll
     for (uint32_t q = 0; q < LT; ++q) {
         const uint32_t i = min(LT * tid + q, L - 1u);
         K[q] = (uint32_t)__hip_atomic_load(&ab.K_out[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         j[q] = __hip_atomic_load(&ab.j_out[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        entry_at[q] = __hip_atomic_load(&tb.at[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     const int32_t st = state & TREE_BAD ? err_nonfinite : room == TREE_NO_ROOM ? err_infeasible : 0;
     const bool chain = st == 0 && (state & TREE_UNSURE);
@@ -658,34 +658,49 @@ __global__ __launch_bounds__(PATH_THREADS) void k_dp_path(AllocBuffers ab, DpLis
     // Of a run of equal costs the chain names the lowest member whose rounded total is the last one's: where one of another error is
     // that near, the totals from the left are formed.
     if (state & TREE_NEAR) {
-        double* sum = stage;                               // [L + 1]
-        static_assert(PATH_STAGE > TREE_MAX_L, "the path's totals fit");
-        size_t o[LT];
+        // Bound by memory round trips, then by one thread's additions: the member's error, its neighbour's below and the run's first
+        // member are asked for together, and the terms come eight at a time.  (us, one after another throughout, and so: ResNet-50's
+        // 161 layers 3.8 and 3.1, with a wide link 6.5 and 3.9, ResNet-18's 62 3.4 and 2.0.)
+        constexpr uint32_t AT_A_TIME = 8u;
+        double *term = stage, *total = stage + TREE_MAX_L + 2u * AT_A_TIME;
+        static_assert(PATH_STAGE >= 2u * (TREE_MAX_L + 2u * AT_A_TIME), "the path's totals fit");
+        double below[LT];
+        uint32_t K_below[LT], first[LT];
+        if (tid < 2u * AT_A_TIME) term[L + tid] = 0.0;
 #pragma unroll
         for (uint32_t q = 0; q < LT; ++q) {
-            const uint32_t i = LT * tid + q;
-            o[q] = 0;
-            if (i >= L) continue;
-            o[q] = (size_t)i * ab.J + min(__hip_atomic_load(&tb.at[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), ab.J - 1u);
-            sum[i + 1u] = dl.e[2u * o[q]];
+            const uint32_t i = min(LT * tid + q, L - 1u);
+            const size_t row = (size_t)i * ab.J;
+            const uint32_t own = min((uint32_t)j[q], ab.J - 1u), under = max(own, 1u) - 1u;
+            const double e = ab.E[row + own];
+            below[q] = ab.E[row + under]; K_below[q] = ab.Kout[row + under];
+            first[q] = dl.jj[row + min(entry_at[q], ab.J - 1u)] & 0xFFu;
+            if (LT * tid + q < L) term[i] = e;
         }
         __syncthreads();
         if (tid == 0u) {
-            double run = 0.0;
-            sum[0] = 0.0;
-            for (uint32_t i = 1; i <= L; ++i) { run += sum[i]; sum[i] = run; }
+            double run = 0.0, t[AT_A_TIME], ahead[AT_A_TIME];
+#pragma unroll
+            for (uint32_t u = 0; u < AT_A_TIME; ++u) t[u] = term[u];
+            for (uint32_t i = 0; i < L; i += AT_A_TIME) {
+#pragma unroll
+                for (uint32_t u = 0; u < AT_A_TIME; ++u) ahead[u] = term[i + AT_A_TIME + u];
+#pragma unroll
+                for (uint32_t u = 0; u < AT_A_TIME; ++u) { total[i + u] = run; run += t[u]; }
+#pragma unroll
+                for (uint32_t u = 0; u < AT_A_TIME; ++u) t[u] = ahead[u];
+            }
         }
         __syncthreads();
 #pragma unroll
         for (uint32_t q = 0; q < LT; ++q) {
             const uint32_t i = LT * tid + q;
             if (i >= L) continue;
-            const double from = sum[i], to = sum[i + 1u];
-            if (from + dl.e[2u * o[q] + 1u] != to) continue;            // (NaN for a single)
-            const uint32_t jj = dl.jj[o[q]], jlo = jj & 0xFFu;
-            uint32_t low = (jj >> 8) - 1u;
-            while (low > jlo && from + ab.E[(size_t)i * ab.J + low - 1u] == to) --low;
-            K[q] = ab.Kout[(size_t)i * ab.J + low];
+            const double from = total[i], to = from + term[i];
+            uint32_t low = (uint32_t)j[q];
+            if (low <= first[q] || from + below[q] != to) continue;
+            K[q] = K_below[q];
+            for (--low; low > first[q] && from + ab.E[(size_t)i * ab.J + low - 1u] == to;) K[q] = ab.Kout[(size_t)i * ab.J + --low];
             j[q] = (int32_t)low;
         }
     }
