@@ -23,6 +23,7 @@
 #include "common.h"
 #include "k_alloc.h"
 #include "k_alloc_band.h"
+#include "last_of_cost.h"
 
 namespace kimad {
 
@@ -211,8 +212,8 @@ __global__ __launch_bounds__(SEGMENT_THREADS) void k_dp_segments(AllocBuffers ab
         double* out = tb.rows + (size_t)i * tb.pitch;
         if (tid == 0u) tb.row_hi[s * TREE_LAYERS + u] = hi;
         if (u == 0u) {
-            // the first layer's row: its entries
-            if (tid < n) rows[0][MAXC + mine.z / 8u] = rec_err(mine);
+            // the first layer's row: its entries, of equal costs the last (two lanes' stores to one cell have no order)
+            if (tid < n && last_of_cost(tid, n, [&](uint32_t k) { return recs[0][k].z; })) rows[0][MAXC + mine.z / 8u] = rec_err(mine);
             __syncthreads();
             for (uint32_t c = tid; c <= hi; c += NT) out[c] = rows[0][MAXC + c];
             continue;

@@ -58,3 +58,45 @@ def test_sizes_are_the_oracles(cells, L, J):
     j, K, off, st = plan.allocate(budgets[1], torch.from_numpy(E.reshape(-1)).cuda())
     assert int(st.item()) == ko.ERR_NONFINITE and not K.cpu().numpy().any()
     plan.close()
+
+
+def _rising_within_runs(cells, L, J, seed):
+    """Sizes of which many cost the same, errors that fall from cost to cost and, at one cost, in no order: layers keep several entries
+    of one cost, the later ones of less error."""
+    rng = np.random.default_rng(seed)
+    ratios = np.append(np.sort(rng.uniform(0.001, 0.99, size=J - 1)), 1.0)
+    sizes = [int(x) for x in 10.0 ** rng.uniform(2.5, 4.2, size=L)]
+    Kt = np.array([ko.grid_sizes(ratios, s) for s in sizes])
+    n = int(sum(sizes))
+    budget = 8 * (int(Kt[:, 0].sum()) + n // 4)
+    E = (1.0 - Kt / np.array(sizes)[:, None]) ** 2 + 0.2 * rng.random(Kt.shape)
+    E *= 10.0 ** rng.uniform(-3, 0, size=(L, 1))
+    unit = -(-(budget // 8) // (cells - 1))
+    w = -(-Kt // unit)
+    pairs = 0
+    for i in range(L):                                   # (kept entries of a cost that has another one)
+        least, last = np.inf, -1
+        for j in range(J):
+            if j + 1 < J and w[i, j + 1] == w[i, j] and E[i, j + 1] <= E[i, j]:
+                continue                                 # not the last of its run
+            pairs += int(E[i, j] < least and last == w[i, j])
+            if E[i, j] < least:
+                least, last = E[i, j], w[i, j]
+    assert pairs > L                                     # (a layer of them is a segment's first somewhere)
+    return ratios, sizes, Kt, E, budget
+
+
+@pytest.mark.parametrize("cells,L,J", [(200, 64, 33), (1000, 96, 64), (1600, 128, 64), (4200, 300, 64)])
+def test_entries_of_equal_costs(cells, L, J):
+    import torch
+    import paper_2312_08053_amd as kimad
+    ratios, sizes, Kt, E, budget = _rising_within_runs(cells, L, J, cells + L)
+    z = [torch.zeros(int(sum(sizes)), dtype=torch.float32, device="cuda") for _ in range(2)]
+    plan = kimad.Plan(z[0], z[1], sizes, ratios.tolist(), D=cells - 1, max_budget_bytes=budget, capacity_pairs=1)
+    st_ref, j_ref, K_ref, off_ref = ko.allocate(E, Kt, budget, 8, cells - 1)
+    j, K, off, st = plan.allocate(budget, torch.from_numpy(E.reshape(-1)).cuda())
+    assert int(st.item()) == st_ref == ko.OK
+    assert np.array_equal(j.cpu().numpy(), j_ref)
+    assert np.array_equal(K.cpu().numpy().astype(np.uint64), K_ref)
+    assert np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
+    plan.close()
