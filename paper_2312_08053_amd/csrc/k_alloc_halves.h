@@ -139,7 +139,9 @@ __global__ __launch_bounds__(BACK_THREADS) void k_dp_back(AllocBuffers ab, const
     const uint32_t half = blockIdx.x, i0 = half ? split : 0u, i1 = half ? ab.L : split, J = ab.J;
     const double least = results[0], margin = results[1];
     const bool there = least < DP_INF;
-    bool unsure = false;
+    // (errors so large that a half's sum may leave the doubles where the layers' own order does not: the least total says nothing)
+    const bool beyond = !(margin < DP_INF);
+    bool unsure = beyond;
     if (there) {
         const uint32_t n = (i1 - i0) * J;
         const bool in_lds = n <= W_LDS;
@@ -215,7 +217,7 @@ __global__ __launch_bounds__(BACK_THREADS) void k_dp_back(AllocBuffers ab, const
     unsure = __hip_atomic_load(&ab.flags[FLAG_UNSURE], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
     const int32_t j = tid < ab.L ? __hip_atomic_load(&ab.j_out[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     const bool any_bad = __syncthreads_or(tid < ab.L && bad[tid] ? 1 : 0) != 0;
-    const int32_t st = any_bad ? err_nonfinite : ab.flags[2] ? err_internal : there ? 0 : err_infeasible;
+    const int32_t st = any_bad ? err_nonfinite : ab.flags[2] ? err_internal : there || beyond ? 0 : err_infeasible;
     const bool chain = st == 0 && unsure;
     if (tid == 0u) {
         ab.flags[FLAG_CHAIN] = chain ? 1u : 0u;

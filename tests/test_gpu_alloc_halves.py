@@ -38,3 +38,32 @@ def test_sizes_are_the_oracles(cells, L, J):
     j, K, off, st = plan.allocate(8 * (cells - 1), torch.from_numpy(E.reshape(-1)).cuda())
     assert int(st.item()) == ko.ERR_NONFINITE and not K.cpu().numpy().any()
     plan.close()
+
+
+@pytest.mark.parametrize("cells,L", [(4225, 16), (9000, 33), (400, 64), (4200, 64)])
+@pytest.mark.parametrize("scale", [1e308, 1e300, 1e-310, 1e-318])
+def test_errors_at_the_ends_of_the_doubles(cells, L, scale):
+    """Errors of both signs, one after the other in the layers' own order, whose sums over every second layer leave the doubles: the
+    sizes are those of the sums in that order all the same (rows beyond LDS, and by the tree of segments)."""
+    import torch
+    import paper_2312_08053_amd as kimad
+    rng = np.random.default_rng(cells + L)
+    J = 12
+    ratios = np.append(np.sort(rng.uniform(0.001, 0.99, size=J - 1)), 1.0)
+    # layers that reach least first: every second one has errors below zero
+    sizes = sorted(max(40, int(x)) for x in cells / L * 10.0 ** rng.uniform(-0.5, 0.9, size=L))
+    Kt = np.array([ko.grid_sizes(ratios, n) for n in sizes])
+    sign = np.where(np.arange(L) % 2, 1.0, -1.0)[:, None]
+    E = scale * sign * (1.0 - rng.uniform(0.0, 0.8 / L, size=(L, 1)) * (Kt / np.array(sizes)[:, None]) ** rng.uniform(0.3, 1.0, size=(L, 1)) * sign)
+    assert np.isfinite(E).all()
+    budget = 8 * max(cells - 1, int(Kt[:, 0].sum()) + 1)
+    D = 0 if cells > 4224 else cells - 1
+    z = [torch.zeros(int(sum(sizes)), dtype=torch.float32, device="cuda") for _ in range(2)]
+    plan = kimad.Plan(z[0], z[1], sizes, ratios.tolist(), D=D, max_budget_bytes=budget, capacity_pairs=1)
+    st_ref, j_ref, K_ref, off_ref = ko.allocate(E, Kt, budget, 8, D)
+    j, K, off, st = plan.allocate(budget, torch.from_numpy(np.ascontiguousarray(E).reshape(-1)).cuda())
+    assert int(st.item()) == st_ref == ko.OK
+    assert np.array_equal(j.cpu().numpy(), j_ref)
+    assert np.array_equal(K.cpu().numpy().astype(np.uint64), K_ref)
+    assert np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
+    plan.close()
