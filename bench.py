@@ -257,6 +257,7 @@ def main() -> int:
         "stage_ms_from_kernel_events": {k: round(v, 4) for k, v in stage_ms.items()},
         "kernels": {n: {k: round(v, 5) for k, v in kern[n].items()} for n in order},
         "roofline": roofline,
+        "allocation_route": plan.allocate_route(),
         "allocation_band": plan.allocate_diagnostics(),
         "input_generation_s": round(t_gen, 1),
     }
@@ -368,6 +369,7 @@ def main() -> int:
         out["other_D"] = {"cost_units_D": args.also_D, "status": dplan.status.cpu().tolist(), "ms_per_step": round(dms, 4),
                           "gradient_GBs": round(4.0 * d / (dms * 1e-3) / 1e9, 2),
                           "payload_pairs": int(dplan.offsets[-1].item()),
+                          "allocation_route": dplan.allocate_route(),
                           "allocation_band": dplan.allocate_diagnostics()}
         del dplan
 

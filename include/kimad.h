@@ -256,12 +256,21 @@ int kimad_payload_layer_counts(const uint32_t* idx, uint64_t pairs, const uint64
  * out[3] = layers whose sampled prediction missed and were recounted by a full pass. */
 int kimad_profile_diagnostics(kimad_plan_t* plan, uint32_t* out4, void* stream);
 
-/* DEVICE diagnostics of the last kimad_allocate on the plan (rows that fit LDS only), copied to HOST
- * (synchronises the stream): out[0] = widest band of cost cells the recurrence visited in a row, out[1] = sum of
+/* DEVICE diagnostics of the last kimad_allocate on the plan, copied to HOST (synchronises the stream), where it went by
+ * the band (KIMAD_ROUTE_BAND): out[0] = widest band of cost cells the recurrence visited in a row, out[1] = sum of
  * the bands' widths over the rows, out[2] = 1 if the bands were the whole rows (no bound could be used),
- * out[3] = upgrades the upper bound's greedy fill took.  Rows long enough for the band that went by the tree of segments
- * (KIMAD_CFG_BAND_DP): bands of one cell, or the whole rows where those decided.  All zero before the first allocation. */
+ * out[3] = upgrades the upper bound's greedy fill took.  All zero after any other allocation, and before the first. */
 int kimad_allocate_diagnostics(kimad_plan_t* plan, uint32_t* out4, void* stream);
+
+/* How the last kimad_allocate on the plan found its sizes (KIMAD_CFG_BAND_DP says which plans go which way), copied to HOST
+ * (synchronises the stream): out[0] = KIMAD_ROUTE_*, 0 before the first; out[1] = KIMAD_HOW_* bits. */
+#define KIMAD_ROUTE_ROWS 1u             /* the recurrence over whole rows */
+#define KIMAD_ROUTE_BAND 2u             /* inside the band of cells that Lagrangian bounds leave */
+#define KIMAD_ROUTE_TREE 3u             /* the tree of segments */
+#define KIMAD_ROUTE_HALVES 4u           /* two halves of the layers */
+#define KIMAD_HOW_ROWS 1u               /* tree or halves: rounding might have decided, and whole rows did */
+#define KIMAD_HOW_FROM_LEFT 2u          /* tree: sizes of equal cost were told apart by the totals summed up from the first layer */
+int kimad_allocate_route(kimad_plan_t* plan, uint32_t* out2, void* stream);
 
 /* Per-layer state of the last profile / compression, for benchmarks and tests (synchronises the
  * stream).  For each layer larger than 8192 entries, 8 words are written to `out` (HOST):

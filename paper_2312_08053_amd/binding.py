@@ -23,7 +23,8 @@ EXPORTED_SYMBOLS = [
     "kimad_workspace_bytes", "kimad_plan_create", "kimad_plan_destroy", "kimad_plan_grid_sizes",
     "kimad_profile", "kimad_allocate", "kimad_allocate_static", "kimad_compress_ef", "kimad_step",
     "kimad_error_at", "kimad_uniform_sizes", "kimad_payload_layer_counts",
-    "kimad_profile_diagnostics", "kimad_allocate_diagnostics", "kimad_plan_layer_states", "kimad_plan_set_timing", "kimad_plan_get_timings",
+    "kimad_profile_diagnostics", "kimad_allocate_diagnostics", "kimad_allocate_route", "kimad_plan_layer_states",
+    "kimad_plan_set_timing", "kimad_plan_get_timings",
     "kimad_server_apply", "kimad_selftest_wave_primitives", "kimad_selftest_allocate_withheld",
     "kimad_budget_bytes", "kimad_strerror", "kimad_version",
 ]
@@ -78,6 +79,7 @@ def lib() -> C.CDLL:
     L.kimad_payload_layer_counts.argtypes = [vp, u64, vp, u32, vp, vp]
     L.kimad_profile_diagnostics.argtypes = [vp, C.POINTER(C.c_uint32), vp]
     L.kimad_allocate_diagnostics.argtypes = [vp, C.POINTER(C.c_uint32), vp]
+    L.kimad_allocate_route.argtypes = [vp, C.POINTER(C.c_uint32), vp]
     L.kimad_plan_layer_states.argtypes = [vp, C.POINTER(C.c_uint32), u32, C.POINTER(C.c_uint32), vp]
     L.kimad_plan_set_timing.argtypes = [vp, C.c_int]
     L.kimad_plan_get_timings.argtypes = [vp, C.c_char_p, u32, C.POINTER(C.c_float), u32, C.POINTER(C.c_uint32)]
@@ -346,6 +348,12 @@ class Plan:
         _check(lib().kimad_allocate_diagnostics(C.c_void_p(self.handle), out, C.c_void_p(_stream(None))),
                "kimad_allocate_diagnostics")
         return dict(max_band=int(out[0]), sum_bands=int(out[1]), whole_rows=int(out[2]), upgrades=int(out[3]))
+
+    def allocate_route(self):
+        """How the last allocation went: dict(route, rows_decided, from_left)."""
+        out = (C.c_uint32 * 2)()
+        _check(lib().kimad_allocate_route(C.c_void_p(self.handle), out, C.c_void_p(_stream(None))), "kimad_allocate_route")
+        return dict(route=("none", "rows", "band", "tree", "halves")[out[0]], rows_decided=bool(out[1] & 1), from_left=bool(out[1] & 2))
 
     def layer_states(self):
         """Per tiled layer: dict(layer, spill_bin, slots_pre, slots_cand, redo, spill_cnt, spill_valid, mode)."""

@@ -30,10 +30,20 @@ struct AllocBuffers {
     uint32_t* flags;         // [DP_FLAGS] [0] non-finite seen (rows by launch only), [1] workgroups started, [2] waits given up, [4] on: FLAG_..
     uint32_t polls;          // reads after which a wait for a row's cells is given up
     uint32_t first_ticket;   // what flags[1] starts from: 0 (a test that withholds the first workgroups: their number)
+    uint32_t* info;          // [INFO_WORDS] what there is to ask of the last allocation
 };
 
 constexpr double DP_INF = __builtin_huge_val();
 constexpr uint32_t DP_FLAGS = 12;
+
+// Words of AllocBuffers::info: the band's (k_alloc_band.h, 0 to 4; zero where none was run), the route taken (KIMAD_ROUTE_..) and how.
+enum : uint32_t { INFO_ROUTE = 8, INFO_HOW = 9, INFO_WORDS = 16 };
+enum : uint32_t { ROUTE_ROWS = 1, ROUTE_BAND = 2, ROUTE_TREE = 3, ROUTE_HALVES = 4 };
+enum : uint32_t { HOW_ROWS = 1, HOW_FROM_LEFT = 2 };           // whole rows decided behind it; the path's totals from the left were formed
+__device__ __forceinline__ void alloc_report(const AllocBuffers& ab, uint32_t route, uint32_t how) {      // (one thread; no band)
+    for (uint32_t x = 0; x < 5u; ++x) ab.info[x] = 0u;
+    ab.info[INFO_ROUTE] = route; ab.info[INFO_HOW] = how;
+}
 
 // K / unit, rounded up.  (In 32 bits: a division in 64 is four times as long.)
 __device__ __forceinline__ uint32_t units_of(uint32_t K, uint64_t unit) {
@@ -362,7 +372,7 @@ struct Pieces {
 // from, and the m winners on that way stand in bytes at choice + (first layer) stride + c m.  So the sequential part is one
 // LDS read a piece; the pieces' rows are staged with one flat copy (they are contiguous, the pitch a multiple of 16 bytes),
 // the first lot before the least total is known.
-// `gate` (optional): a word that is zero where the allocation is already decided (k_dp_path).
+// `gate` (optional): a word that is zero where the allocation is already decided (by k_dp_path, which has said what there is to ask).
 constexpr uint32_t DP_STAGE_BYTES = 128u * 1024u;
 constexpr uint32_t DP_WALK_MAX_L = 4224;           // layers whose path cells k_dp_walk keeps in LDS: every layer costs at least one
                                                    // cell, so a feasible path through rows of at most 4224 cells has no more layers
@@ -437,6 +447,7 @@ __global__ __launch_bounds__(1024) void k_dp_walk(AllocBuffers ab, const double*
             st = s;
             cstar = bc;
             *ab.status = s;
+            if (!gate) alloc_report(ab, ROUTE_ROWS, 0u);
         }
     }
     __syncthreads();
@@ -533,6 +544,7 @@ __global__ __launch_bounds__(1024) void k_dp_final(AllocBuffers ab, const double
         st = s;
         cstar = bc;
         *ab.status = s;
+        if (!gate) alloc_report(ab, ROUTE_ROWS, 0u);
     }
     __syncthreads();
     if (st != 0) {

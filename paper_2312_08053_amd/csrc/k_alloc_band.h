@@ -41,7 +41,7 @@ constexpr uint32_t BAND_GROUPS = BOUNDS_THREADS / BAND_NLAM;             // 32 g
 struct BandBuffers {
     uint32_t* lo;          // [L + 1] first cell of row r's band (row 0 is the start: cell 0)
     uint32_t* hi;          // [L + 1] last cell
-    uint32_t* info;        // [16] max width, sum of widths, 1 if the bands are the whole rows, upgrades taken, 1 if nothing fits
+    uint32_t* info;        // [INFO_WORDS] max width, sum of widths, 1 if the bands are the whole rows, upgrades taken, 1 if nothing fits
     // the list records that can connect the bands of rows i and i + 1 (the only ones the banded recurrence visits)
     uint32_t* live;        // [L] first record | count << 8
     double* table;         // [(L + 1) * BAND_NLAM] prefix sums of the per-layer minima; the rows' memory before there are rows
@@ -155,6 +155,7 @@ __global__ __launch_bounds__(BOUNDS_THREADS) void k_dp_bounds(AllocBuffers ab, D
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t L = ab.L, J = ab.J, cap = ab.cap;
 
+    if (tid == 0) { bb.info[INFO_ROUTE] = ROUTE_BAND; bb.info[INFO_HOW] = 0u; }
     // no bound to use: whole rows, every record live (or, if `hopeless`, nothing fits and the recurrence is not run)
     auto whole_rows = [&](bool hopeless) {
         for (uint32_t r = tid; r <= L; r += BOUNDS_THREADS) { bb.lo[r] = 0u; bb.hi[r] = r ? cap : 0u; }

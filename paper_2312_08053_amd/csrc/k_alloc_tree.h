@@ -404,10 +404,9 @@ __device__ __forceinline__ void tree_store(const AllocBuffers& ab, const TreeBuf
 }
 enum : uint32_t { TREE_UNSURE = 1u, TREE_BAD = 2u, TREE_NEAR = 4u };         // head[2]
 
-// report: this call's diagnostics are a band's (one cell a row, or the whole rows)
 template <bool NODES>
-__global__ __launch_bounds__(PATH_THREADS) void k_dp_path(AllocBuffers ab, DpLists dl, TreeBuffers tb, uint32_t* info, uint32_t report,
-                                                          int32_t err_infeasible, int32_t err_nonfinite, StepLookup sl) {
+__global__ __launch_bounds__(PATH_THREADS) void k_dp_path(AllocBuffers ab, DpLists dl, TreeBuffers tb, int32_t err_infeasible, int32_t err_nonfinite,
+                                                          StepLookup sl) {
     constexpr uint32_t NT = PATH_THREADS, WAVES = NT / 64u, LR = TREE_LAYERS / WAVES, LT = TREE_MAX_L / NT;
     constexpr uint32_t ROW = NODES ? 1024u : DP_ROW_MAX, PER = (ROW + NT - 1u) / NT;
     __shared__ __align__(16) double stage[PATH_STAGE];         // the nodes' totals, then rows
@@ -642,7 +641,7 @@ __global__ __launch_bounds__(PATH_THREADS) void k_dp_path(AllocBuffers ab, DpLis
     const bool chain = st == 0 && (state & TREE_UNSURE);
     if (tid == 0u) {
         tb.head[3] = chain ? 1u : 0u;
-        if (report) { info[0] = chain ? ab.cap + 1u : 1u; info[1] = chain ? L * (ab.cap + 1u) : L; info[2] = chain ? 1u : 0u; info[3] = 0u; }
+        alloc_report(ab, ROUTE_TREE, chain ? HOW_ROWS : st == 0 && (state & TREE_NEAR) ? HOW_FROM_LEFT : 0u);
         if (!chain) *ab.status = st;
     }
     if (chain) {

@@ -334,7 +334,7 @@ int make_layout(const uint64_t* n, uint32_t L, uint32_t J, const kimad_config_t&
     lo.dl_bad = take(4ull * L);
     lo.dense_E = take(8 * LJ); lo.dense_Kcost = take(4 * LJ); lo.dense_Kout = take(4 * LJ);
     lo.band_lo = take(4ull * (L + 1)); lo.band_hi = take(4ull * (L + 1));
-    lo.band_info = take(64);
+    lo.band_info = take(4 * INFO_WORDS);
     lo.band_live = take(4ull * L);
     lo.hull_e = take(8 * LJ); lo.hull_w = take(4 * LJ); lo.hull_n = take(4ull * L); lo.hull_abs = take(8ull * L);
     {
@@ -704,7 +704,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
     ab.row0 = ws.row0; ab.row1 = ws.row1;
     ab.choice = ws.choice; ab.cprev = ws.cprev; ab.stride = align_up(cap + 1);   // row pitch: <= align_up(max_cells)
     ab.j_out = j_out; ab.K_out = K_out; ab.offsets_out = offsets_out; ab.status = status_out;
-    ab.flags = ws.flags; ab.polls = polls; ab.first_ticket = first_ticket;
+    ab.flags = ws.flags; ab.polls = polls; ab.first_ticket = first_ticket; ab.info = ws.band.info;
     mark(p, s, "begin");
     if (dense) {
         KLAUNCH(p, s, "k_dense_view", k_dense_view, dim3((lo.L * lo.J + 255) / 256), dim3(256), err_table, ab.Ktab,
@@ -756,11 +756,11 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
                 if (rc) return rc;
             }
             if (cap + 1 <= 1024) {
-                KLAUNCH(p, s, "k_dp_path", k_dp_path<true>, dim3(tb.S), dim3(PATH_THREADS), ab, dl, tb, ws.band.info, long_rows ? 1u : 0u,
-                        (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, sl);
+                KLAUNCH(p, s, "k_dp_path", k_dp_path<true>, dim3(tb.S), dim3(PATH_THREADS), ab, dl, tb, (int32_t)KIMAD_ERR_INFEASIBLE,
+                        (int32_t)KIMAD_ERR_NONFINITE, sl);
             } else {
-                KLAUNCH(p, s, "k_dp_path", k_dp_path<false>, dim3(tb.S), dim3(PATH_THREADS), ab, dl, tb, ws.band.info, long_rows ? 1u : 0u,
-                        (int32_t)KIMAD_ERR_INFEASIBLE, (int32_t)KIMAD_ERR_NONFINITE, sl);
+                KLAUNCH(p, s, "k_dp_path", k_dp_path<false>, dim3(tb.S), dim3(PATH_THREADS), ab, dl, tb, (int32_t)KIMAD_ERR_INFEASIBLE,
+                        (int32_t)KIMAD_ERR_NONFINITE, sl);
             }
             return chain_by_size(tb.head + 3);
         }
@@ -1011,7 +1011,7 @@ int kimad_plan_create(const kimad_layer_t* layers, uint32_t L, const double* rat
     // Layer states start as "nothing spilled, nothing cached".
     if (hipMemsetAsync(p->ws + lo.state, 0, sizeof(LayerState) * (uint64_t)(lo.B ? lo.B : 1), s) != hipSuccess ||
         hipMemsetAsync(p->ws + lo.zero2_begin, 0, lo.zero2_end - lo.zero2_begin, s) != hipSuccess ||
-        hipMemsetAsync(p->ws + lo.band_info, 0, 64, s) != hipSuccess ||
+        hipMemsetAsync(p->ws + lo.band_info, 0, 4 * INFO_WORDS, s) != hipSuccess ||
         hipMemsetAsync(p->ws + lo.fresh, 0, 16, s) != hipSuccess ||
         hipMemsetAsync(p->ws + lo.gprev, 0, 8ull * D1_BINS, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess) { delete p; return KIMAD_ERR_HIP; }
@@ -1113,7 +1113,7 @@ int kimad_allocate_static(kimad_plan_t* p, const double* err_table, uint64_t bud
     ws.dense_Kout = reinterpret_cast<uint32_t*>(take(4 * LJ));
     ws.band.lo = reinterpret_cast<uint32_t*>(take(4ull * (KIMAD_STATIC_MAX_L + 1)));
     ws.band.hi = reinterpret_cast<uint32_t*>(take(4ull * (KIMAD_STATIC_MAX_L + 1)));
-    ws.band.info = reinterpret_cast<uint32_t*>(take(64));
+    ws.band.info = reinterpret_cast<uint32_t*>(take(4 * INFO_WORDS));
     ws.band.live = reinterpret_cast<uint32_t*>(take(4ull * KIMAD_STATIC_MAX_L));
     ws.dl.he = reinterpret_cast<double*>(take(8 * LJ)); ws.dl.hw = reinterpret_cast<uint32_t*>(take(4 * LJ));
     ws.dl.hn = reinterpret_cast<uint32_t*>(take(4ull * KIMAD_STATIC_MAX_L));
@@ -1193,6 +1193,16 @@ int kimad_allocate_diagnostics(kimad_plan_t* p, uint32_t* out4, void* stream) {
     if (!p || !out4) return KIMAD_ERR_INVALID_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (hipMemcpyAsync(out4, p->ws + p->lo.band_info, 16, hipMemcpyDeviceToHost, s) != hipSuccess) return KIMAD_ERR_HIP;
+    if (hipStreamSynchronize(s) != hipSuccess) return KIMAD_ERR_HIP;
+    return KIMAD_OK;
+}
+
+int kimad_allocate_route(kimad_plan_t* p, uint32_t* out2, void* stream) {
+    static_assert(KIMAD_ROUTE_ROWS == ROUTE_ROWS && KIMAD_ROUTE_BAND == ROUTE_BAND && KIMAD_ROUTE_TREE == ROUTE_TREE &&
+                  KIMAD_ROUTE_HALVES == ROUTE_HALVES && KIMAD_HOW_ROWS == HOW_ROWS && KIMAD_HOW_FROM_LEFT == HOW_FROM_LEFT, "header and kernel constants");
+    if (!p || !out2) return KIMAD_ERR_INVALID_ARG;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (hipMemcpyAsync(out2, at<uint32_t>(p, p->lo.band_info) + INFO_ROUTE, 8, hipMemcpyDeviceToHost, s) != hipSuccess) return KIMAD_ERR_HIP;
     if (hipStreamSynchronize(s) != hipSuccess) return KIMAD_ERR_HIP;
     return KIMAD_OK;
 }

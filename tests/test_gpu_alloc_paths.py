@@ -177,18 +177,21 @@ def test_more_layers_than_cost_cells_is_infeasible():
     _check(sizes, ratios, E, int(0.5 * 8 * sum(sizes)), 4200)
 
 
-@pytest.mark.parametrize("J,cells", [(1, 2048), (2, 1537), (2, 2048), (2, 2049), (3, 4001), (7, 2048), (7, 2049), (8, 1537), (8, 2048)])
-def test_the_path_taken_by_itself_with_few_ratios(J, cells):
-    """Around the lines where rows of few ratios leave the whole-row recurrence; bands of layers with one or two records."""
+@pytest.mark.parametrize("L", [20, 23, 24, 70])
+@pytest.mark.parametrize("J,cells", [(1, 2048), (2, 1537), (2, 2048), (2, 2049), (3, 4001), (7, 2048), (7, 2049), (8, 1536), (8, 1537), (8, 2048)])
+def test_the_path_taken_by_itself_with_few_ratios(J, cells, L):
+    """Around the lines where rows of few ratios leave the whole-row recurrence for the band (with few layers) or for the tree of
+    segments; bands of layers with one or two records."""
     import torch
     rng = np.random.default_rng(100 * J + cells)
     ratios = np.logspace(-2, -0.3, J)
-    sizes = [int(x) for x in rng.integers(20000, 90000, size=70)]
+    sizes = [int(x) for x in rng.integers(20000, 90000, size=L)]
     E = _convex_table(rng, sizes, ratios, -2, 2)
     E[::3] *= rng.uniform(0.5, 1.0, size=E[::3].shape)
     Kt = np.array([ko.grid_sizes(ratios, n) for n in sizes])
-    # a budget of whole cost units, so that the rows have exactly this many cells
-    unit = int(0.35 * Kt[:, -1].sum()) // (cells - 1) if J > 1 else int(1.1 * Kt.sum()) // (cells - 1)
+    # a budget of whole cost units, so that the rows have exactly this many cells (of one ratio, all sizes fit: they cost at most
+    # (cells - 1) / 1.1 + L units)
+    unit = int(0.35 * Kt[:, -1].sum()) // (cells - 1) if J > 1 else -(-int(1.1 * Kt.sum()) // (cells - 1))
     budget = 8 * unit * (cells - 1)
     _check(sizes, ratios, E, budget, cells - 1)
     st_ref, j_ref, K_ref, off_ref = ko.allocate(E, Kt, budget, 8, cells - 1)
@@ -197,4 +200,8 @@ def test_the_path_taken_by_itself_with_few_ratios(J, cells):
     assert int(st.item()) == st_ref == ko.OK
     assert np.array_equal(j.cpu().numpy(), j_ref)
     assert np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
-    assert (plan.allocate_diagnostics()["max_band"] > 0) == (J > 7 or cells > 2048)
+    tree = J > 1 and L >= (24 if cells >= 1537 else 60)
+    band = not tree and J > 1 and cells >= 1537 and (J > 7 or cells > 2048)
+    route = plan.allocate_route()
+    assert route["route"] == ("tree" if tree else "band" if band else "rows") and not route["rows_decided"], route
+    assert (plan.allocate_diagnostics()["max_band"] > 0) == band

@@ -1,0 +1,95 @@
+"""Which way an allocation goes, and what decides it: by the tree of segments and by halves the sizes are there where every choice is
+clear, and whole rows decide where equal totals leave a choice to rounding, and only there; calls of other plans in between, and
+calls in turn on one plan, report what they did themselves.  The sizes are the oracle's throughout."""
+import numpy as np
+import pytest
+
+from oracle import kimad_oracle as ko
+
+pytestmark = pytest.mark.gpu
+
+TREE = [(300, 64, 16), (1000, 62, 50), (1024, 200, 33), (1025, 70, 5), (1537, 24, 64), (4097, 148, 64), (4224, 300, 16)]
+HALVES = [(4225, 16, 5), (9000, 40, 32), (20011, 62, 64)]
+
+
+def _case(cells, L, J, alike):
+    """Sizes and errors of layers that differ in scale by no more than a hundred, or (`alike`) are all the same."""
+    rng = np.random.default_rng(cells + 10 * L + J)
+    ratios = np.append(np.sort(rng.uniform(0.001, 0.99, size=J - 1)), 1.0)
+    lo = max(60, 4 * cells // L)
+    sizes = [lo + 17] * L if alike else [int(x) for x in rng.integers(lo, 4 * lo, size=L)]
+    Kt = np.array([ko.grid_sizes(ratios, n) for n in sizes])
+    n = np.array(sizes, dtype=np.float64)[:, None]
+    E = 10.0 ** rng.uniform(-1, 1, size=(L, 1)) * (1.0 - Kt / n) ** rng.uniform(1.0, 4.0, size=(L, 1))
+    if alike:
+        E[:] = E[0]
+    D = cells - 1 if cells <= 4224 else 0
+    pairs = cells - 1 if D == 0 else (cells - 1) * max(1, int(0.3 * sum(sizes)) // (cells - 1))
+    return ratios, sizes, Kt, np.ascontiguousarray(E), 8 * pairs, D
+
+
+def _plan(sizes, ratios, D, budget, flags=0):
+    import torch
+    import paper_2312_08053_amd as kimad
+    z = [torch.zeros(int(sum(sizes)), dtype=torch.float32, device="cuda") for _ in range(2)]
+    return kimad.Plan(z[0], z[1], list(sizes), list(ratios), D=D, max_budget_bytes=budget, cfg_flags=flags, capacity_pairs=1)
+
+
+def _allocate(plan, E, Kt, budget, D):
+    import torch
+    st_ref, j_ref, K_ref, off_ref = ko.allocate(E, Kt, budget, 8, D)
+    j, K, off, st = plan.allocate(budget, torch.from_numpy(E.reshape(-1)).cuda())
+    assert int(st.item()) == st_ref == ko.OK
+    assert np.array_equal(j.cpu().numpy(), j_ref)
+    assert np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
+    return plan.allocate_route()
+
+
+@pytest.mark.parametrize("cells,L,J", TREE + HALVES)
+def test_clear_choices_need_no_whole_rows_and_ties_do(cells, L, J):
+    name = "halves" if cells > 4224 else "tree"
+    ratios, sizes, Kt, E, budget, D = _case(cells, L, J, False)
+    plan = _plan(sizes, ratios, D, budget)
+    assert plan.allocate_route() == dict(route="none", rows_decided=False, from_left=False)
+    clear = _allocate(plan, E, Kt, budget, D)
+    assert clear["route"] == name and not clear["rows_decided"], clear
+    assert not any(plan.allocate_diagnostics().values())
+    if L <= 1024 and cells <= 4224:
+        banded = _plan(sizes, ratios, D, budget, flags=4)
+        assert _allocate(banded, E, Kt, budget, D)["route"] == "band" and banded.allocate_diagnostics()["max_band"] > 0
+        banded.close()
+    rows = _plan(sizes, ratios, D, budget, flags=2)
+    assert _allocate(rows, E, Kt, budget, D) == dict(route="rows", rows_decided=False, from_left=False)
+    rows.close()
+    assert plan.allocate_route() == clear                 # (other plans' calls are not this one's)
+    plan.close()
+    ratios, sizes, Kt, E, budget, D = _case(cells, L, J, True)
+    plan = _plan(sizes, ratios, D, budget)
+    for _ in range(2):
+        tied = _allocate(plan, E, Kt, budget, D)
+        assert tied == dict(route=name, rows_decided=True, from_left=False), tied
+    assert not any(plan.allocate_diagnostics().values())
+    E2 = np.ascontiguousarray(E * (1.0 + 0.5 * np.random.default_rng(L).random((L, 1))))
+    assert not _allocate(plan, E2, Kt, budget, D)["rows_decided"]
+    plan.close()
+
+
+def test_members_of_a_run_apart_by_rounding_are_told_apart_from_the_left():
+    """Small layers whose sizes all cost one unit, of errors a few units in the last place of the total apart."""
+    rng = np.random.default_rng(3)
+    L, cells, J = 80, 700, 24
+    ratios = np.append(np.sort(rng.uniform(0.05, 0.95, size=J - 1)), 1.0)
+    sizes = [int(x) for x in np.where(np.arange(L) % 2, 150, rng.integers(3000, 20000, size=L))]
+    Kt = np.array([ko.grid_sizes(ratios, n) for n in sizes])
+    budget = 8 * (cells - 1) * (int(0.3 * sum(sizes)) // (cells - 1))
+    unit = budget // 8 // (cells - 1)
+    assert unit >= 150
+    n = np.array(sizes, dtype=np.float64)[:, None]
+    E = rng.uniform(1.0, 9.0, size=(L, 1)) * (1.0 - Kt / n) ** 2
+    for near, left in ((1e-3, False), (4e-15, True)):
+        Ek = E.copy()
+        Ek[1::2] = 1.0 + near * np.arange(J)[::-1]
+        plan = _plan(sizes, ratios, cells - 1, budget)
+        route = _allocate(plan, np.ascontiguousarray(Ek), Kt, budget, cells - 1)
+        assert route == dict(route="tree", rows_decided=False, from_left=left), (near, route)
+        plan.close()
