@@ -479,13 +479,17 @@ __global__ __launch_bounds__(chain_threads(W, GW)) void k_dp_chain(AllocBuffers 
 // layer, 2.3 us).  With more than sixteen candidates the cheapest four's cells are waited for before all are asked for
 // through the caches (149 against 160 us with device-scope loads for all; with sixteen or fewer the wait costs more than it
 // saves, 83 against 72).  Sixteen cells a wave, the candidates shared by its four rows, read twice the lines: 190.
-// Two waves a workgroup, whose source cells lie close together, share what its compute unit's cache holds.  (us of all launches of the
-// allocation, whole rows by workgroups of one, two and four waves: 62 layers of 58 thousand cells 187, 190, 183, 8 of 58 thousand 43, 37, 35,
-// 16 of 131 thousand 98, 88, 82, 161 of 13 thousand 317, 336, 393, of 9 thousand and 5 ratios 164, 182, 215; by halves, below, 132, 128,
-// 130, the 161 layers 212, 213, 241 and 106, 109, 125.)
+// Two waves a workgroup, whose source cells lie close together, share what its compute unit's cache holds, and wait for each other's
+// start: worth it for few layers from 16384 cells on, for any number from 65536 on, and for halves.  (us of all launches of the
+// allocation, workgroups of one wave and of two.  8 layers of 64 candidates and 9 thousand cells 36 and 38, 13 37 and 39, 20 42 and 41,
+// 58 64 and 60, of 5 candidates 27 and 27 at 13, 31 and 30 at 20, 47 and 42 at 58; 16 of 131 thousand and 32 114 and 105; 62 of 32 and 4300
+// cells 122 and 127, 42 thousand 161 and 177, 58 174 and 182, 90 218 and 215, 131 262 and 256; 161 of 64 and 4300 388 and 439, 58 thousand 606
+// and 620, 131 1000 and 914.  By halves 62 layers of 32 and 4300 cells 85 and 90, 13 thousand 96 and 93, 58 125 and 122, 131 177 and 168;
+// 161 of 64 236 and 247, 259 and 260, 326 and 354, 432 and 461; 30 of 5 and 58 thousand 76 and 67.)
 constexpr uint32_t CHAIN_PAD = 64;
-constexpr uint32_t CHAIN_LONG_NT = 128;
-constexpr uint32_t CHAIN_LONG_CELLS = CHAIN_LONG_NT;
+constexpr uint32_t CHAIN_LONG_WAVES = 2;             // of a workgroup, at most
+constexpr uint32_t CHAIN_FEW_L = 16;                 // (the halves' fewest)
+inline uint32_t chain_long_waves(uint64_t L, uint64_t cells) { return cells >= 65536u || (L < CHAIN_FEW_L && cells >= 16384u) ? CHAIN_LONG_WAVES : 1u; }
 
 // Two halves of the layers side by side (k_alloc_halves.h), each from cost 0, every range of cells by two workgroups of neighbouring
 // numbers; or, where order is null, all layers one after another, if `gate` (optional) says so.
@@ -497,8 +501,11 @@ struct ChainHalves {
     const uint32_t* gate;
 };
 
-template <int SETS>
-__global__ __launch_bounds__(CHAIN_LONG_NT) void k_dp_chain_long(AllocBuffers ab, const uint32_t* __restrict__ wall, double* rows, uint64_t pitch,
+// PAIR: two waves a workgroup, which may be in halves.  (What only halves need costs workgroups of one wave up to a tenth: 161 layers of 32
+// candidates and 9 thousand cells 296 -> 326 us.  Two waves are the faster for it, and for `order` looked at as the kernel runs: 8 layers
+// of 131 thousand cells and 64 candidates take 92 us and 95 without, halves of 161 layers and 58 thousand cells 354 and 361.)
+template <int SETS, bool PAIR>
+__global__ __launch_bounds__(PAIR ? 64u * CHAIN_LONG_WAVES : 64u) void k_dp_chain_long(AllocBuffers ab, const uint32_t* __restrict__ wall, double* rows, uint64_t pitch,
                                                                  ChainHalves ch) {
     const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (ch.gate && *ch.gate == 0u) return;
@@ -510,9 +517,9 @@ __global__ __launch_bounds__(CHAIN_LONG_NT) void k_dp_chain_long(AllocBuffers ab
         if (threadIdx.x == 0u) atomicAdd(&ab.flags[2], 1u);
         return;
     }
-    const bool halves = ch.order != nullptr;
+    const bool halves = PAIR && ch.order != nullptr;
     const uint32_t half = halves ? number & 1u : 0u;
-    const uint32_t c0 = (halves ? number >> 1 : number) * CHAIN_LONG_CELLS + 64u * wave, c = c0 + lane, c_hi = c0 + 63u;
+    const uint32_t c0 = (halves ? number >> 1 : number) * blockDim.x + 64u * wave, c = c0 + lane, c_hi = c0 + 63u;
     if (c0 > ab.cap) return;
     uint32_t i0 = half ? ch.split : 0u;
     const uint32_t first = i0, i1 = halves && !half ? ch.split : ab.L;

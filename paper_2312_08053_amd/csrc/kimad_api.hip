@@ -115,7 +115,7 @@ inline uint32_t tree_segments(uint64_t layers, uint32_t few) {
 // and 222, 30 of 30 thousand 111 and 85, 161 of 13 thousand 317 and 213, of 9 thousand 164 and 109, 16 of 4300 45 and 41, of 30 thousand 36
 // and 34, 11 of 9 thousand 25 and 29, 6 of 12 thousand 25 and 33.  Where rounding may decide, one chain comes behind them: 16 layers of
 // 85 thousand cells 111 and 170.
-constexpr uint32_t HALVES_MIN_L = 16;
+constexpr uint32_t HALVES_MIN_L = CHAIN_FEW_L;
 
 uint32_t pick_tile_elems(uint64_t d_big) {
     // aim at >= 8 tiles per compute unit on large inputs, keep tiles within the 16-bit LDS counters
@@ -783,13 +783,17 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
         // (a row's filling takes several workgroups: one per 32 KB)
         const dim3 fill(lo.L, (uint32_t)(pitch / 4096 + 1));
         KLAUNCH(p, s, "k_dp_prep", k_dp_prep, fill, dim3(64), ab, ws.dl, 0u, ws.rows_g, pitch, CHAIN_PAD, halves ? ws.dl.he : (double*)nullptr);
-        const uint32_t waves = (uint32_t)(cap / CHAIN_LONG_CELLS + 1);
-        auto chain = [&](uint32_t grid, const ChainHalves& ch) -> int {
+        auto chain_of = [&](auto pair, const ChainHalves& ch) -> int {
+            constexpr bool PAIR = decltype(pair)::value;
             const uint32_t* wall = ws.dl.wall;
-            if (lo.J <= 16) KLAUNCH(p, s, "k_dp_chain", k_dp_chain_long<1>, dim3(grid), dim3(CHAIN_LONG_NT), ab, wall, ws.rows_g, pitch, ch);
-            else if (lo.J <= 32) KLAUNCH(p, s, "k_dp_chain", k_dp_chain_long<2>, dim3(grid), dim3(CHAIN_LONG_NT), ab, wall, ws.rows_g, pitch, ch);
-            else KLAUNCH(p, s, "k_dp_chain", k_dp_chain_long<4>, dim3(grid), dim3(CHAIN_LONG_NT), ab, wall, ws.rows_g, pitch, ch);
+            const dim3 block(PAIR ? 64u * CHAIN_LONG_WAVES : 64u), grid((uint32_t)(cap / block.x + 1) * (ch.order ? 2u : 1u));
+            if (lo.J <= 16) KLAUNCH(p, s, "k_dp_chain", (k_dp_chain_long<1, PAIR>), grid, block, ab, wall, ws.rows_g, pitch, ch);
+            else if (lo.J <= 32) KLAUNCH(p, s, "k_dp_chain", (k_dp_chain_long<2, PAIR>), grid, block, ab, wall, ws.rows_g, pitch, ch);
+            else KLAUNCH(p, s, "k_dp_chain", (k_dp_chain_long<4, PAIR>), grid, block, ab, wall, ws.rows_g, pitch, ch);
             return KIMAD_OK;
+        };
+        auto chain = [&](const ChainHalves& ch) -> int {
+            return ch.order || chain_long_waves(lo.L, cap + 1) == CHAIN_LONG_WAVES ? chain_of(std::true_type{}, ch) : chain_of(std::false_type{}, ch);
         };
         const double* last = ws.rows_g + (uint64_t)lo.L * pitch + CHAIN_PAD;
         ChainHalves ch{};
@@ -797,7 +801,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
         if (halves) {
             ch.order = at<uint32_t>(p, lo.half_order); ch.falling = ws.dl.he; ch.least[0] = ws.row0; ch.least[1] = ws.row1;
             ch.split = lo.L / 2;
-            int rc = chain(2 * waves, ch);
+            int rc = chain(ch);
             if (rc) return rc;
             double* results = ws.row0 + MEET_RESULTS;
             KLAUNCH(p, s, "k_dp_meet", k_dp_meet, dim3((uint32_t)(cap / MEET_THREADS + 1)), dim3(MEET_THREADS), ab, (const double*)ws.dl.habs,
@@ -810,7 +814,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
             ch.order = nullptr;
             ch.gate = gate = ws.flags + FLAG_CHAIN;
         }
-        int rc = chain(waves, ch);
+        int rc = chain(ch);
         if (rc) return rc;
         KLAUNCH(p, s, "k_dp_final", k_dp_final, dim3(1), dim3(1024), ab, last, (const uint32_t*)ws.dl.bad, (int32_t)KIMAD_ERR_INFEASIBLE,
                 (int32_t)KIMAD_ERR_NONFINITE, (int32_t)KIMAD_ERR_INTERNAL, sl, gate);

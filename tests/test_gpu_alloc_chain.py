@@ -52,6 +52,22 @@ def test_edges_of_the_rows(cells, J):
         plan.close()
 
 
+@pytest.mark.parametrize("cells,L", [(16383, 15), (16384, 15), (16385, 15), (16448, 16), (65535, 16), (65536, 16), (65601, 16), (65664, 3)])
+@pytest.mark.parametrize("J", [6, 40])
+def test_one_wave_a_workgroup_and_two(cells, L, J):
+    """Around the lines from which a workgroup of rows beyond LDS has two waves, the last workgroup full, of one wave and nearly empty."""
+    import torch
+    ratios, sizes, Kt, E = _case(cells, J, L, cells + L)
+    budget = 8 * (cells - 1)
+    st_ref, j_ref, K_ref, off_ref = ko.allocate(E, Kt, budget, 8, 0)
+    assert st_ref == ko.OK
+    plan = _plan(sizes, ratios, budget)
+    j, K, off, st = plan.allocate(budget, torch.from_numpy(E.reshape(-1)).cuda())
+    assert int(st.item()) == st_ref
+    assert np.array_equal(j.cpu().numpy(), j_ref) and np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
+    plan.close()
+
+
 @pytest.mark.parametrize("cells", [200, 256, 257, 1000, 1030, 2049])
 @pytest.mark.parametrize("L", [23, 24, 25, 28, 29, 61])
 def test_pieces_that_the_walk_goes_through(cells, L):
