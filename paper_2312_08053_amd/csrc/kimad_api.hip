@@ -111,11 +111,13 @@ inline uint32_t tree_segments(uint64_t layers, uint32_t few) {
 }
 
 // Rows beyond LDS go by halves (k_alloc_halves.h) from so many layers on; fewer do not pay for the three launches more, and the three that
-// leave at once.  us of all launches of the allocation, one chain and halves: 62 layers of 58 thousand cells 187 and 128, of 131 thousand 370
-// and 222, 30 of 30 thousand 111 and 85, 161 of 13 thousand 317 and 213, of 9 thousand 164 and 109, 16 of 4300 45 and 41, of 30 thousand 36
-// and 34, 11 of 9 thousand 25 and 29, 6 of 12 thousand 25 and 33.  Where rounding may decide, one chain comes behind them: 16 layers of
-// 85 thousand cells 111 and 170.
-constexpr uint32_t HALVES_MIN_L = CHAIN_FEW_L;
+// leave at once, and nor do some more whose steps are short, of up to sixteen candidates over shorter rows.  us of all launches of the
+// allocation, one chain and halves: 62 layers of 32 candidates and 58 thousand cells 174 and 122, of 131 thousand 262 and 167, 161 of 64 and
+// 13 thousand 404 and 260; 16 layers of 17 candidates and 4300 cells 42 and 42, of 64 52 and 49; 16 of 16 and 4300 35 and 39, 13 thousand
+// 38 and 40, 20 thousand 45 and 43, 42 thousand 59 and 50; 20 of 16 and 4300 39 and 42, 13 thousand 44 and 44; 24 45 and 45, 49 and 46, 30 52 and
+// 50, 57 and 53; 8 of 5 and 9 thousand 26 and 33.  Where rounding may decide, one chain comes behind them: 16 layers of 85 thousand cells 111 and 170.
+constexpr uint32_t HALVES_MIN_L = CHAIN_FEW_L, HALVES_MIN_L_SHORT = 24;          // (the latter: up to HALVES_FEW_J ratios, fewer than HALVES_LONG cells)
+constexpr uint32_t HALVES_FEW_J = 16, HALVES_LONG = 16384;
 
 uint32_t pick_tile_elems(uint64_t d_big) {
     // aim at >= 8 tiles per compute unit on large inputs, keep tiles within the 16-bit LDS counters
@@ -778,7 +780,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
         return chain_by_size(nullptr);
     } else if (ws.all_rows) {
         const uint64_t pitch = chain_long_pitch(cap + 1);
-        const bool halves = lo.L >= HALVES_MIN_L && lo.L <= HALVES_MAX_L && cap + 1 <= HALVES_MAX_CELLS && first_ticket == 0u &&
+        const bool halves = lo.L >= (lo.J <= HALVES_FEW_J && cap + 1 < HALVES_LONG ? HALVES_MIN_L_SHORT : HALVES_MIN_L) && lo.L <= HALVES_MAX_L && cap + 1 <= HALVES_MAX_CELLS && first_ticket == 0u &&
                             !(p->cfg.flags & KIMAD_CFG_FULL_DP);
         // (a row's filling takes several workgroups: one per 32 KB)
         const dim3 fill(lo.L, (uint32_t)(pitch / 4096 + 1));

@@ -40,7 +40,7 @@ def test_sizes_are_the_oracles(cells, L, J):
     plan.close()
 
 
-@pytest.mark.parametrize("cells,L", [(4225, 16), (9000, 33), (400, 64), (4200, 64)])
+@pytest.mark.parametrize("cells,L", [(4225, 24), (9000, 33), (400, 64), (4200, 64)])
 @pytest.mark.parametrize("scale", [1e308, 1e300, 1e-310, 1e-318])
 def test_errors_at_the_ends_of_the_doubles(cells, L, scale):
     """Errors of both signs, one after the other in the layers' own order, whose sums over every second layer leave the doubles: the

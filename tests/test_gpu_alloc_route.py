@@ -9,13 +9,13 @@ from oracle import kimad_oracle as ko
 pytestmark = pytest.mark.gpu
 
 TREE = [(300, 64, 16), (1000, 62, 50), (1024, 200, 33), (1025, 70, 5), (1537, 24, 64), (4097, 148, 64), (4224, 300, 16)]
-HALVES = [(4225, 16, 5), (9000, 40, 32), (20011, 62, 64)]
+HALVES = [(4225, 24, 5), (4225, 16, 17), (9000, 40, 32), (16384, 16, 16), (20011, 62, 64)]
 
 
 def _case(cells, L, J, alike):
     """Sizes and errors of layers that differ in scale by no more than a hundred, or (`alike`) are all the same."""
     rng = np.random.default_rng(cells + 10 * L + J)
-    ratios = np.append(np.sort(rng.uniform(0.001, 0.99, size=J - 1)), 1.0)
+    ratios = np.concatenate([[0.001], np.sort(rng.uniform(0.002, 0.99, size=J - 2)), [1.0]])     # (the cheapest sizes always fit)
     lo = max(60, 4 * cells // L)
     sizes = [lo + 17] * L if alike else [int(x) for x in rng.integers(lo, 4 * lo, size=L)]
     Kt = np.array([ko.grid_sizes(ratios, n) for n in sizes])
@@ -71,6 +71,15 @@ def test_clear_choices_need_no_whole_rows_and_ties_do(cells, L, J):
     assert not any(plan.allocate_diagnostics().values())
     E2 = np.ascontiguousarray(E * (1.0 + 0.5 * np.random.default_rng(L).random((L, 1))))
     assert not _allocate(plan, E2, Kt, budget, D)["rows_decided"]
+    plan.close()
+
+
+@pytest.mark.parametrize("cells,L,J,want", [(4225, 23, 16, "rows"), (4225, 24, 16, "halves"), (4225, 15, 17, "rows"), (4225, 16, 17, "halves"),
+                                           (16383, 23, 16, "rows"), (16384, 15, 16, "rows"), (16384, 16, 16, "halves")])
+def test_the_line_where_rows_beyond_lds_take_halves(cells, L, J, want):
+    ratios, sizes, Kt, E, budget, D = _case(cells, L, J, False)
+    plan = _plan(sizes, ratios, D, budget)
+    assert _allocate(plan, E, Kt, budget, D) == dict(route=want, rows_decided=False, from_left=False)
     plan.close()
 
 
