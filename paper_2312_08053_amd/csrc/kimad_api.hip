@@ -93,12 +93,22 @@ inline bool chain_long_fits(uint64_t L, uint64_t cells) {
 }
 
 // Rows that fit LDS go by the tree of segments (k_alloc_tree.h) from so many layers on: below, the chain's few steps, or for longer rows
-// the band, take less than the tree's launches.  us of all launches of the allocation, chain and tree: rows of 1000 cells, 21 layers of
-// 64 ratios 31 and 41, 53 of 16 40 and 43, 62 of 50 49 and 41, 74 of 16 46 and 39, 148 of 64 76 and 56, 280 of 50 129 and 59, 700 of 33
-// 230 and 64; of 500 cells 53 of 32 33 and 38, 161 of 16 60 and 42.  Band and tree, rows of 4097 cells: 23 layers of 50 ratios 54 and
-// 68, 56 of 16 77 and 55, 62 of 50 97 and 67, 148 of 64 161 and 117, 268 of 32 282 and 79.  Where rounding may decide, the chain comes
-// behind it: 700 layers of small whole errors 229 and 301.
-constexpr uint32_t TREE_MIN_L = 24, TREE_MIN_L_SHORT = 60;       // (rows of fewer than BAND_AUTO_CELLS cells: the latter)
+// the band, take less than the tree's launches.  us of all launches of the allocation, chain and tree, layers of 5 and of 64 ratios:
+//   256 cells  60 layers 31 and 32, 33 and 34; 64 layers 32 and 32, 35 and 33; 74 layers 34 and 33, 37 and 34
+//   384        60 32 and 33, 34 and 35; 64 33 and 33, 36 and 35
+//   500        60 33 and 34, 35 and 36; 64 34 and 34, 36 and 36; 74 37 and 35, 39 and 38; 161 60 and 40, 63 and 40
+//   512        60 33 and 34, 35 and 36
+//   600        60 34 and 34, 41 and 38; 700 cells 38 and 35, 41 and 39
+//   1000       60 41 and 37, 48 and 41 (21 of 64 31 and 41, 53 of 16 40 and 43); 161 75 and 43, 78 and 47; 700 of 33 230 and 64
+//   1025       60 46 and 35, 53 and 43; 161 85 and 42, 87 and 49
+//   1536       60 51 and 38, 62 and 47; 300 145 and 49, 151 and 54
+// and from BAND_AUTO_CELLS on the better of chain and band, layers of 2, 16 and 64 ratios:
+//   1537       24 36 and 31, 37 and 37, 40 and 48 (band 58); 40 44 and 34, 45 and 38, 50 and 49; 161 91 and 45, 92 and 47, 98 and 54
+//   4097       24 56 and 38, 56 and 46, 61 and 73 (band 69); 40 78 and 45, 75 and 51, 78 and 68; 161 216 and 66, 170 and 69, 193 and 84
+// Where rounding may decide, the chain comes behind it: what both take together, against the better of chain and band alone, 148 layers of 16
+// and of 64 ratios: 1000 cells 118 and 72, 154 and 107; 1537 cells 144 and 92, 183 and 98; 4097 cells 302 and 183, 352 and 223.
+constexpr uint32_t TREE_MIN_L = 24, TREE_MIN_L_SHORT = 60;       // (rows of fewer than BAND_AUTO_CELLS cells: the latter;
+constexpr uint32_t TREE_MIN_L_SHORTEST = 64, TREE_SHORTEST = 576;          //  of fewer than TREE_SHORTEST cells: this)
 // Segments of at most this many layers: a segment's layers are one after another, a level of the tree is a launch.  (us with 3, 6 and
 // 12: rows of 1000 cells, 148 layers of 64 ratios 60, 56, 56, 218 of 64 65, 65, 74, 62 of 50 41, 41, 46.  Of 4097 cells, whose
 // levels cost more, 148 of 64 172, 138, 117, 161 of 64 74, 73, 78.)
@@ -721,7 +731,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
         const bool long_rows = cap + 1 >= BAND_AUTO_CELLS && lo.J > 1 && !(lo.J <= WHOLE_ROWS_J && cap + 1 <= WHOLE_ROWS_CELLS);
         // (the withheld workgroup of the self-test is the chain's)
         const bool tree = ws.tree.vec && !(p->cfg.flags & (KIMAD_CFG_FULL_DP | KIMAD_CFG_BAND_DP)) && first_ticket == 0u &&
-                          lo.L >= (cap + 1 >= BAND_AUTO_CELLS ? TREE_MIN_L : TREE_MIN_L_SHORT);
+                          lo.L >= (cap + 1 >= BAND_AUTO_CELLS ? TREE_MIN_L : cap + 1 >= TREE_SHORTEST ? TREE_MIN_L_SHORT : TREE_MIN_L_SHORTEST);
         const bool band = lo.L <= BAND_MAX_L && !(p->cfg.flags & KIMAD_CFG_FULL_DP) &&
                           ((p->cfg.flags & KIMAD_CFG_BAND_DP) || (long_rows && lo.L < TREE_MIN_L));
         // (keepers of 16 cells a compute wave, then a workgroup per piece of the layers)

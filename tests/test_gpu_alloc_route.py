@@ -75,11 +75,14 @@ def test_clear_choices_need_no_whole_rows_and_ties_do(cells, L, J):
 
 
 @pytest.mark.parametrize("cells,L,J,want", [(4225, 23, 16, "rows"), (4225, 24, 16, "halves"), (4225, 15, 17, "rows"), (4225, 16, 17, "halves"),
-                                           (16383, 23, 16, "rows"), (16384, 15, 16, "rows"), (16384, 16, 16, "halves")])
-def test_the_line_where_rows_beyond_lds_take_halves(cells, L, J, want):
+                                           (16383, 23, 16, "rows"), (16384, 15, 16, "rows"), (16384, 16, 16, "halves"),
+                                           (575, 63, 8, "rows"), (575, 64, 8, "tree"), (576, 59, 8, "rows"), (576, 60, 8, "tree"),
+                                           (1536, 59, 8, "rows"), (1537, 23, 8, "band"), (1537, 24, 8, "tree"), (90, 64, 8, "tree")])
+def test_the_lines_where_halves_and_the_tree_begin(cells, L, J, want):
     ratios, sizes, Kt, E, budget, D = _case(cells, L, J, False)
     plan = _plan(sizes, ratios, D, budget)
-    assert _allocate(plan, E, Kt, budget, D) == dict(route=want, rows_decided=False, from_left=False)
+    route = _allocate(plan, E, Kt, budget, D)
+    assert route["route"] == want and not route["rows_decided"], route
     plan.close()
 
 

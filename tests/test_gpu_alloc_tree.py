@@ -24,7 +24,7 @@ def _table(rng, sizes, Kt, kind):
     return E
 
 
-@pytest.mark.parametrize("cells,L", [(90, 60), (64, 61), (1000, 60), (1023, 97), (1024, 192), (1025, 193), (1024, 1024), (1537, 24), (2049, 25),
+@pytest.mark.parametrize("cells,L", [(90, 60), (64, 61), (90, 64), (66, 65), (575, 64), (576, 60), (1000, 60), (1023, 97), (1024, 192), (1025, 193), (1024, 1024), (1537, 24), (2049, 25),
                                      (4223, 64), (4224, 48), (4224, 300)])
 @pytest.mark.parametrize("J", [2, 17, 64])
 def test_sizes_are_the_oracles(cells, L, J):
