@@ -37,12 +37,12 @@ constexpr double DP_INF = __builtin_huge_val();
 constexpr uint32_t DP_FLAGS = 12;
 
 // Words of AllocBuffers::info: the band's (k_alloc_band.h, 0 to 4; zero where none was run), the route taken (KIMAD_ROUTE_..) and how.
-enum : uint32_t { INFO_ROUTE = 8, INFO_HOW = 9, INFO_WORDS = 16 };
+// An allocation's first kernel writes them, and what is found out later adds how.
+enum : uint32_t { INFO_ROUTE = 5, INFO_HOW = 6, INFO_REPORT = 7, INFO_WORDS = 16 };
 enum : uint32_t { ROUTE_ROWS = 1, ROUTE_BAND = 2, ROUTE_TREE = 3, ROUTE_HALVES = 4 };
 enum : uint32_t { HOW_ROWS = 1, HOW_FROM_LEFT = 2 };           // whole rows decided behind it; the path's totals from the left were formed
-__device__ __forceinline__ void alloc_report(const AllocBuffers& ab, uint32_t route, uint32_t how) {      // (one thread; no band)
-    for (uint32_t x = 0; x < 5u; ++x) ab.info[x] = 0u;
-    ab.info[INFO_ROUTE] = route; ab.info[INFO_HOW] = how;
+__device__ __forceinline__ void alloc_report(const AllocBuffers& ab, uint32_t route, uint32_t thread) {
+    if (thread < INFO_REPORT) ab.info[thread] = thread == INFO_ROUTE ? route : 0u;
 }
 
 // K / unit, rounded up.  (In 32 bits: a division in 64 is four times as long.)
@@ -204,9 +204,10 @@ __device__ __forceinline__ void dp_list_store(const AllocBuffers& ab, const DpLi
 
 // One wave per layer, one lane per candidate.  `with_hull`: also the list's lower convex hull.
 // `rows` (not null): the stored rows of the recurrence, `pitch` cells each, the first `pad` of them before cost 0: row i + 1
-// is filled with ROW_EMPTY (row 0: the start), by the gridDim.y workgroups of the layer; and its counters are cleared.
+// is filled with ROW_EMPTY (row 0: the start), by the gridDim.y workgroups of the layer; its counters are cleared, and `route` is reported.
 // `falling` (not null): [L][J] the candidates' errors, +inf for one that is dearer than another and no better.
-__global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uint32_t with_hull, double* rows, uint64_t pitch, uint32_t pad, double* falling) {
+__global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uint32_t with_hull, double* rows, uint64_t pitch, uint32_t pad, double* falling,
+                                                uint32_t route) {
     __shared__ double se[KIMAD_MAX_J_CONST];
     __shared__ uint32_t sw[KIMAD_MAX_J_CONST];
     const uint32_t i = blockIdx.x, j = threadIdx.x;
@@ -214,6 +215,7 @@ __global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uin
         dp_fill_row(ab, rows, pitch, pad, i + 1ull, blockIdx.y * 64u + j, 64u * gridDim.y);
         if (i == 0u) dp_fill_row(ab, rows, pitch, pad, 0ull, blockIdx.y * 64u + j, 64u * gridDim.y);
         if (i == 0u && blockIdx.y == 0u && j < DP_FLAGS) ab.flags[j] = j == 1u ? ab.first_ticket : 0u;
+        if (i == 0u && blockIdx.y == 0u) alloc_report(ab, route, j);
         if (blockIdx.y) return;
     }
     if (falling) {
@@ -372,7 +374,7 @@ struct Pieces {
 // from, and the m winners on that way stand in bytes at choice + (first layer) stride + c m.  So the sequential part is one
 // LDS read a piece; the pieces' rows are staged with one flat copy (they are contiguous, the pitch a multiple of 16 bytes),
 // the first lot before the least total is known.
-// `gate` (optional): a word that is zero where the allocation is already decided (by k_dp_path, which has said what there is to ask).
+// `gate` (optional): a word that is zero where the allocation is already decided (k_dp_path).
 constexpr uint32_t DP_STAGE_BYTES = 128u * 1024u;
 constexpr uint32_t DP_WALK_MAX_L = 4224;           // layers whose path cells k_dp_walk keeps in LDS: every layer costs at least one
                                                    // cell, so a feasible path through rows of at most 4224 cells has no more layers
@@ -447,7 +449,6 @@ __global__ __launch_bounds__(1024) void k_dp_walk(AllocBuffers ab, const double*
             st = s;
             cstar = bc;
             *ab.status = s;
-            if (!gate) alloc_report(ab, ROUTE_ROWS, 0u);
         }
     }
     __syncthreads();
@@ -508,6 +509,7 @@ __global__ __launch_bounds__(1024) void k_dp_final(AllocBuffers ab, const double
     __shared__ int32_t st;
     const uint32_t tid = threadIdx.x;
     if (tid == 0) any_bad = bad ? 0u : ab.flags[0];
+    if (!bad) alloc_report(ab, ROUTE_ROWS, tid);           // (no kernel of a launch per layer has)
     __syncthreads();
     if (bad) {
         uint32_t mine = 0u;
@@ -544,7 +546,6 @@ __global__ __launch_bounds__(1024) void k_dp_final(AllocBuffers ab, const double
         st = s;
         cstar = bc;
         *ab.status = s;
-        if (!gate) alloc_report(ab, ROUTE_ROWS, 0u);
     }
     __syncthreads();
     if (st != 0) {

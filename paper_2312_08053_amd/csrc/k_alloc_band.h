@@ -155,7 +155,7 @@ __global__ __launch_bounds__(BOUNDS_THREADS) void k_dp_bounds(AllocBuffers ab, D
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t L = ab.L, J = ab.J, cap = ab.cap;
 
-    if (tid == 0) { bb.info[INFO_ROUTE] = ROUTE_BAND; bb.info[INFO_HOW] = 0u; }
+    if (tid == INFO_ROUTE || tid == INFO_HOW) bb.info[tid] = tid == INFO_ROUTE ? ROUTE_BAND : 0u;
     // no bound to use: whole rows, every record live (or, if `hopeless`, nothing fits and the recurrence is not run)
     auto whole_rows = [&](bool hopeless) {
         for (uint32_t r = tid; r <= L; r += BOUNDS_THREADS) { bb.lo[r] = 0u; bb.hi[r] = r ? cap : 0u; }

@@ -221,7 +221,7 @@ __global__ __launch_bounds__(BACK_THREADS) void k_dp_back(AllocBuffers ab, const
     const bool chain = st == 0 && unsure;
     if (tid == 0u) {
         ab.flags[FLAG_CHAIN] = chain ? 1u : 0u;
-        alloc_report(ab, ROUTE_HALVES, chain ? HOW_ROWS : 0u);
+        if (chain) ab.info[INFO_HOW] = HOW_ROWS;
         if (!chain) *ab.status = st;
     }
     if (chain) return;

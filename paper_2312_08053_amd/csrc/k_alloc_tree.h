@@ -163,6 +163,7 @@ __global__ __launch_bounds__(SEGMENT_THREADS) void k_dp_segments(AllocBuffers ab
     all.find(ab, su);
     const uint32_t room = all.room;
     if (s == 0u && tid < 5u) tb.head[tid] = tid == 0u ? room : tid == 4u ? all.count : 0u;
+    if (s == 0u) alloc_report(ab, ROUTE_TREE, tid);
     if (room == TREE_NO_ROOM) return;
     // (the host has chosen S so that a segment has at most TREE_LAYERS)
     const uint32_t per = min((all.count + tb.S - 1u) / tb.S, TREE_LAYERS), first = min(s * per, all.count), m = min(per, all.count - first);
@@ -641,7 +642,8 @@ __global__ __launch_bounds__(PATH_THREADS) void k_dp_path(AllocBuffers ab, DpLis
     const bool chain = st == 0 && (state & TREE_UNSURE);
     if (tid == 0u) {
         tb.head[3] = chain ? 1u : 0u;
-        alloc_report(ab, ROUTE_TREE, chain ? HOW_ROWS : st == 0 && (state & TREE_NEAR) ? HOW_FROM_LEFT : 0u);
+        if (chain) ab.info[INFO_HOW] = HOW_ROWS;
+        else if (st == 0 && (state & TREE_NEAR)) ab.info[INFO_HOW] = HOW_FROM_LEFT;
         if (!chain) *ab.status = st;
     }
     if (chain) {

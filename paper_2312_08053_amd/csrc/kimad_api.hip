@@ -777,7 +777,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
             return chain_by_size(tb.head + 3);
         }
         KLAUNCH(p, s, "k_dp_prep", k_dp_prep, dim3(lo.L), dim3(64), ab, dl, band ? 1u : 0u, band ? (double*)nullptr : rows_g,
-                (uint64_t)rstride, 0u, (double*)nullptr);
+                (uint64_t)rstride, 0u, (double*)nullptr, (uint32_t)ROUTE_ROWS);
         if (band) {
             // the recurrence inside the band of cells that Lagrangian bounds leave (same result, a fraction of the cells)
             BandBuffers bb = ws.band;
@@ -794,7 +794,8 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
                             !(p->cfg.flags & KIMAD_CFG_FULL_DP);
         // (a row's filling takes several workgroups: one per 32 KB)
         const dim3 fill(lo.L, (uint32_t)(pitch / 4096 + 1));
-        KLAUNCH(p, s, "k_dp_prep", k_dp_prep, fill, dim3(64), ab, ws.dl, 0u, ws.rows_g, pitch, CHAIN_PAD, halves ? ws.dl.he : (double*)nullptr);
+        KLAUNCH(p, s, "k_dp_prep", k_dp_prep, fill, dim3(64), ab, ws.dl, 0u, ws.rows_g, pitch, CHAIN_PAD, halves ? ws.dl.he : (double*)nullptr,
+                (uint32_t)(halves ? ROUTE_HALVES : ROUTE_ROWS));
         auto chain_of = [&](auto pair, const ChainHalves& ch) -> int {
             constexpr bool PAIR = decltype(pair)::value;
             const uint32_t* wall = ws.dl.wall;
