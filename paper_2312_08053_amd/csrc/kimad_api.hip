@@ -113,6 +113,11 @@ constexpr uint32_t TREE_MIN_L_SHORTEST = 64, TREE_SHORTEST = 576;          //  o
 // 12: rows of 1000 cells, 148 layers of 64 ratios 60, 56, 56, 218 of 64 65, 65, 74, 62 of 50 41, 41, 46.  Of 4097 cells, whose
 // levels cost more, 148 of 64 172, 138, 117, 161 of 64 74, 73, 78.)
 constexpr uint32_t TREE_FEW = 6, TREE_FEW_LONG = 12;
+// A join of rows of more than 1024 cells takes 64 costs a workgroup where that makes a workgroup a compute unit and a few more, else 32.
+// (us of all launches of the allocation with 64 costs from 0, 100, 200, 300 and 600 such workgroups on, and never: 96 layers of 16 ratios, a
+// join of two and one of four nodes, 2048 cells 50, 48, 47, 47, 47, 47, 4097 70, 69, 66, 64, 64, 64; 190 layers, eight nodes too, 2048 55, 54,
+// 52, 52, 52, 52, 4097 75, 75, 72, 73, 75, 74; 760, sixteen and 32 too, 2560 65, 64, 63, 64, 63, 66, 3600 76, 76, 74, 73, 74, 78.)
+constexpr uint32_t JOIN_WIDE_WGS = 300;
 inline bool tree_takes(uint64_t L, uint64_t J) { return L >= TREE_MIN_L && L <= TREE_MAX_L && J > 1; }
 inline uint32_t tree_segments(uint64_t layers, uint32_t few) {
     uint32_t s = 1;
@@ -764,7 +769,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
                     return KIMAD_OK;
                 };
                 const int rc = cap + 1 <= 1024 ? join(k_dp_join<1024, 16, 4>, 16)
-                             : first * (cap / 64 + 1) < 200 ? join(k_dp_join<DP_ROW_MAX, 32, 4>, 32) : join(k_dp_join<DP_ROW_MAX, 64, 8>, 64);
+                             : first * (cap / 64 + 1) < JOIN_WIDE_WGS ? join(k_dp_join<DP_ROW_MAX, 32, 4>, 32) : join(k_dp_join<DP_ROW_MAX, 64, 8>, 64);
                 if (rc) return rc;
             }
             if (cap + 1 <= 1024) {
