@@ -350,10 +350,11 @@ class Plan:
         return dict(max_band=int(out[0]), sum_bands=int(out[1]), whole_rows=int(out[2]), upgrades=int(out[3]))
 
     def allocate_route(self):
-        """How the last allocation went: dict(route, rows_decided, from_left)."""
+        """How the last allocation went: dict(route, rows_decided, from_left, at_once)."""
         out = (C.c_uint32 * 2)()
         _check(lib().kimad_allocate_route(C.c_void_p(self.handle), out, C.c_void_p(_stream(None))), "kimad_allocate_route")
-        return dict(route=("none", "rows", "band", "tree", "halves")[out[0]], rows_decided=bool(out[1] & 1), from_left=bool(out[1] & 2))
+        return dict(route=("none", "rows", "band", "tree", "halves")[out[0]], rows_decided=bool(out[1] & 1), from_left=bool(out[1] & 2),
+                    at_once=bool(out[1] & 4))
 
     def layer_states(self):
         """Per tiled layer: dict(layer, spill_bin, slots_pre, slots_cand, redo, spill_cnt, spill_valid, mode)."""

@@ -38,9 +38,9 @@ constexpr uint32_t DP_FLAGS = 12;
 
 // Words of AllocBuffers::info: the band's (k_alloc_band.h, 0 to 4; zero where none was run), the route taken (KIMAD_ROUTE_..) and how.
 // An allocation's first kernel writes them, and what is found out later adds how.
-enum : uint32_t { INFO_ROUTE = 5, INFO_HOW = 6, INFO_REPORT = 7, INFO_WORDS = 16 };
+enum : uint32_t { INFO_ROUTE = 5, INFO_HOW = 6, INFO_REPORT = 7, INFO_AHEAD = 8, INFO_STREAK = 9, INFO_WORDS = 16 };
 enum : uint32_t { ROUTE_ROWS = 1, ROUTE_BAND = 2, ROUTE_TREE = 3, ROUTE_HALVES = 4 };
-enum : uint32_t { HOW_ROWS = 1, HOW_FROM_LEFT = 2 };           // whole rows decided behind it; the path's totals from the left were formed
+enum : uint32_t { HOW_ROWS = 1, HOW_FROM_LEFT = 2, HOW_AT_ONCE = 4 };     // whole rows decided; the path's totals from the left were formed; .. at once
 __device__ __forceinline__ void alloc_report(const AllocBuffers& ab, uint32_t route, uint32_t thread) {
     if (thread < INFO_REPORT) ab.info[thread] = thread == INFO_ROUTE ? route : 0u;
 }

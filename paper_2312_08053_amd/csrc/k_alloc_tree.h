@@ -30,6 +30,7 @@ namespace kimad {
 constexpr uint32_t TREE_MAX_L = 1024, TREE_MAX_SEGMENTS = 64, TREE_LAYERS = 16;     // layers, segments, layers of a segment
 static_assert(TREE_MAX_SEGMENTS * TREE_LAYERS == TREE_MAX_L, "every layer has a place");
 constexpr uint32_t TREE_NO_ROOM = 0xFFFFFFFFu;
+enum : uint32_t { TREE_UNSURE = 1u, TREE_BAD = 2u, TREE_NEAR = 4u, TREE_AT_ONCE = 8u };         // head[2]
 
 // An entry of the list of a layer that has a choice, as k_dp_path takes it.
 struct TreeEntry {
@@ -157,11 +158,20 @@ __global__ __launch_bounds__(SEGMENT_THREADS) void k_dp_segments(AllocBuffers ab
         }
         return;
     }
-    const uint32_t s = blockIdx.x;
+    const uint32_t s = blockIdx.x, ahead = ab.info[INFO_AHEAD];
     for (uint32_t x = tid; x < 4u * MAXC; x += NT) (&rows[0][0])[x] = DP_INF;
     TreeLayers all;
     all.find(ab, su);
     const uint32_t room = all.room;
+    if (ahead) {
+        // whole rows at once: they are made ready for the chain, and nothing else looks at a tree that has no room
+        for (uint32_t r = s * WAVES + wave; r <= ab.L; r += tb.S * WAVES) dp_fill_row(ab, tb.rows, tb.pitch, 0u, r, lane, 64u);
+        if (s) return;
+        if (tid < 5u) tb.head[tid] = tid == 0u ? TREE_NO_ROOM : tid == 2u ? (uint32_t)TREE_AT_ONCE : tid == 3u ? 1u : 0u;
+        if (tid < 4u) ab.flags[tid] = tid == 1u ? ab.first_ticket : 0u;
+        if (tid < INFO_REPORT) ab.info[tid] = tid == INFO_ROUTE ? ROUTE_TREE : tid == INFO_HOW ? HOW_ROWS | HOW_AT_ONCE : 0u;
+        return;
+    }
     if (s == 0u && tid < 5u) tb.head[tid] = tid == 0u ? room : tid == 4u ? all.count : 0u;
     if (s == 0u) alloc_report(ab, ROUTE_TREE, tid);
     if (room == TREE_NO_ROOM) return;
@@ -397,13 +407,21 @@ constexpr uint32_t PATH_THREADS = 512;
 constexpr uint32_t PATH_STAGE = 12288;             // cells of rows in LDS (a row of the longest kind fits)
 constexpr uint32_t PATH_LEVELS = 6;
 static_assert(1u << PATH_LEVELS == TREE_MAX_SEGMENTS && PATH_STAGE >= 2u * PATH_LEVELS * 1024u && PATH_STAGE >= DP_ROW_MAX, "the nodes' totals fit");
+// A table in which rounding may decide is often followed by others: a layer whose errors vanish beside the total makes one in every
+// round.  Behind so many allocations in a row that the chain had to decide, the plan's next ROWS_AHEAD go by the chain at once, the tree's
+// kernels leave, and then it is tried again.  The sizes do not hang on it.
+// (us of all launches of the allocation, the chain or the band alone, tree and chain, and the chain at once, of 16 and of 64 ratios: 148 layers,
+// 1000 cells 72, 118, 84 and 107, 154, 119; 1537 cells 144 in place of 177 by the band, 102, and 183 in place of 170, 139; 4097 cells 183, 302, 230
+// and 223, 352, 284; 62 layers, 1000 cells 48, 82, 58.  The halves' kernels are too finely balanced for it: the word looked at by
+// k_dp_chain_long cost every clear allocation 1 to 13 us.)
+constexpr uint32_t TIES_IN_A_ROW = 8, ROWS_AHEAD = 31;
+
 // What a segment has found for a layer goes beyond the caches: the segment that is through last reads it.
 __device__ __forceinline__ void tree_store(const AllocBuffers& ab, const TreeBuffers& tb, uint32_t i, uint32_t place, uint32_t K) {
     __hip_atomic_store(&tb.at[i], place & 0xFFFFu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&ab.j_out[i], (int32_t)(place >> 16), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&ab.K_out[i], (uint64_t)K, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-enum : uint32_t { TREE_UNSURE = 1u, TREE_BAD = 2u, TREE_NEAR = 4u };         // head[2]
 
 template <bool NODES>
 __global__ __launch_bounds__(PATH_THREADS) void k_dp_path(AllocBuffers ab, DpLists dl, TreeBuffers tb, int32_t err_infeasible, int32_t err_nonfinite,
@@ -450,6 +468,10 @@ __global__ __launch_bounds__(PATH_THREADS) void k_dp_path(AllocBuffers ab, DpLis
 #pragma unroll
             for (uint32_t q = 0; q < 4u; ++q) v[lev][q] = tb.vec[(size_t)(2u * node_at(lev) + (q >> 1)) * tb.pitch + tid + (q & 1u) * NT];
         }
+    }
+    if (room == TREE_NO_ROOM && (tb.head[2] & TREE_AT_ONCE)) {
+        if (s == 0u && tid == 0u) ab.info[INFO_AHEAD] -= 1u;
+        return;
     }
     if (tid < 2u * TREE_MAX_SEGMENTS) s_hi[tid] = room == TREE_NO_ROOM || tid >= 2u * tb.S ? 0u : my_hi;
     if (tid == 0u) s_state = 0u;
@@ -642,8 +664,15 @@ __global__ __launch_bounds__(PATH_THREADS) void k_dp_path(AllocBuffers ab, DpLis
     const bool chain = st == 0 && (state & TREE_UNSURE);
     if (tid == 0u) {
         tb.head[3] = chain ? 1u : 0u;
-        if (chain) ab.info[INFO_HOW] = HOW_ROWS;
-        else if (st == 0 && (state & TREE_NEAR)) ab.info[INFO_HOW] = HOW_FROM_LEFT;
+        uint32_t streak = 0u;
+        if (chain) {
+            streak = min(ab.info[INFO_STREAK] + 1u, TIES_IN_A_ROW);
+            if (streak == TIES_IN_A_ROW) ab.info[INFO_AHEAD] = ROWS_AHEAD;
+            ab.info[INFO_HOW] = HOW_ROWS;
+        } else if (st == 0 && (state & TREE_NEAR)) {
+            ab.info[INFO_HOW] = HOW_FROM_LEFT;
+        }
+        ab.info[INFO_STREAK] = streak;
         if (!chain) *ab.status = st;
     }
     if (chain) {

@@ -1221,7 +1221,8 @@ int kimad_allocate_diagnostics(kimad_plan_t* p, uint32_t* out4, void* stream) {
 
 int kimad_allocate_route(kimad_plan_t* p, uint32_t* out2, void* stream) {
     static_assert(KIMAD_ROUTE_ROWS == ROUTE_ROWS && KIMAD_ROUTE_BAND == ROUTE_BAND && KIMAD_ROUTE_TREE == ROUTE_TREE &&
-                  KIMAD_ROUTE_HALVES == ROUTE_HALVES && KIMAD_HOW_ROWS == HOW_ROWS && KIMAD_HOW_FROM_LEFT == HOW_FROM_LEFT, "header and kernel constants");
+                  KIMAD_ROUTE_HALVES == ROUTE_HALVES && KIMAD_HOW_ROWS == HOW_ROWS && KIMAD_HOW_FROM_LEFT == HOW_FROM_LEFT &&
+                  KIMAD_HOW_AT_ONCE == HOW_AT_ONCE, "header and kernel constants");
     if (!p || !out2) return KIMAD_ERR_INVALID_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (hipMemcpyAsync(out2, at<uint32_t>(p, p->lo.band_info) + INFO_ROUTE, 8, hipMemcpyDeviceToHost, s) != hipSuccess) return KIMAD_ERR_HIP;

@@ -50,7 +50,7 @@ def test_clear_choices_need_no_whole_rows_and_ties_do(cells, L, J):
     name = "halves" if cells > 4224 else "tree"
     ratios, sizes, Kt, E, budget, D = _case(cells, L, J, False)
     plan = _plan(sizes, ratios, D, budget)
-    assert plan.allocate_route() == dict(route="none", rows_decided=False, from_left=False)
+    assert plan.allocate_route() == dict(route="none", rows_decided=False, from_left=False, at_once=False)
     clear = _allocate(plan, E, Kt, budget, D)
     assert clear["route"] == name and not clear["rows_decided"], clear
     assert not any(plan.allocate_diagnostics().values())
@@ -59,7 +59,7 @@ def test_clear_choices_need_no_whole_rows_and_ties_do(cells, L, J):
         assert _allocate(banded, E, Kt, budget, D)["route"] == "band" and banded.allocate_diagnostics()["max_band"] > 0
         banded.close()
     rows = _plan(sizes, ratios, D, budget, flags=2)
-    assert _allocate(rows, E, Kt, budget, D) == dict(route="rows", rows_decided=False, from_left=False)
+    assert _allocate(rows, E, Kt, budget, D) == dict(route="rows", rows_decided=False, from_left=False, at_once=False)
     rows.close()
     assert plan.allocate_route() == clear                 # (other plans' calls are not this one's)
     plan.close()
@@ -67,7 +67,7 @@ def test_clear_choices_need_no_whole_rows_and_ties_do(cells, L, J):
     plan = _plan(sizes, ratios, D, budget)
     for _ in range(2):
         tied = _allocate(plan, E, Kt, budget, D)
-        assert tied == dict(route=name, rows_decided=True, from_left=False), tied
+        assert tied == dict(route=name, rows_decided=True, from_left=False, at_once=False), tied
     assert not any(plan.allocate_diagnostics().values())
     E2 = np.ascontiguousarray(E * (1.0 + 0.5 * np.random.default_rng(L).random((L, 1))))
     assert not _allocate(plan, E2, Kt, budget, D)["rows_decided"]
@@ -103,5 +103,53 @@ def test_members_of_a_run_apart_by_rounding_are_told_apart_from_the_left():
         Ek[1::2] = 1.0 + near * np.arange(J)[::-1]
         plan = _plan(sizes, ratios, cells - 1, budget)
         route = _allocate(plan, np.ascontiguousarray(Ek), Kt, budget, cells - 1)
-        assert route == dict(route="tree", rows_decided=False, from_left=left), (near, route)
+        assert route == dict(route="tree", rows_decided=False, from_left=left, at_once=False), (near, route)
         plan.close()
+
+
+@pytest.mark.parametrize("cells,L,J", [(600, 64, 16), (1200, 70, 33), (4097, 40, 16)])
+@pytest.mark.parametrize("recorded", [False, True])
+def test_ties_in_a_row_go_by_whole_rows_at_once(cells, L, J, recorded):
+    """Behind eight allocations that whole rows had to decide, the next 31 do not ask the tree first, whatever their tables; then it is tried again.  Called one by one, and as replays of a recorded graph."""
+    import torch
+    ratios, sizes, Kt, E, budget, D = _case(cells, L, J, True)
+    clear = np.ascontiguousarray(E * (1.0 + 0.5 * np.random.default_rng(L).random((L, 1))))
+    want = {id(t): ko.allocate(t, Kt, budget, 8, D) for t in (E, clear)}
+    plan = _plan(sizes, ratios, D, budget)
+    table = torch.empty(L * J, dtype=torch.float64, device="cuda")
+    table.copy_(torch.from_numpy(clear.reshape(-1)))
+    out = plan.allocate(budget, table)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    if recorded:
+        with torch.cuda.graph(graph):
+            out = plan.allocate(budget, table)
+
+    def call(t):
+        table.copy_(torch.from_numpy(t.reshape(-1)))
+        for v in out:
+            v.fill_(-7)
+        if recorded:
+            graph.replay()
+        else:
+            plan.allocate(budget, table)
+        torch.cuda.synchronize()
+        st_ref, j_ref, K_ref, off_ref = want[id(t)]
+        j, K, off, st = out
+        assert int(st.item()) == st_ref == ko.OK
+        assert np.array_equal(j.cpu().numpy(), j_ref) and np.array_equal(K.cpu().numpy().astype(np.uint64), K_ref)
+        assert np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
+        torch.full((1 << 18,), 1.0, device="cuda").sum().item()
+        r = plan.allocate_route()
+        assert r["route"] == "tree" and not r["from_left"]
+        return r["rows_decided"], r["at_once"]
+
+    assert [call(E) for _ in range(7)] == [(True, False)] * 7
+    assert call(clear) == (False, False)                                 # (not in a row)
+    assert [call(E) for _ in range(8)] == [(True, False)] * 8
+    assert [call((E, clear)[k % 3 == 1]) for k in range(31)] == [(True, True)] * 31
+    assert call(E) == (True, False)                                      # tried again, and again by rows
+    assert [call(E) for _ in range(31)] == [(True, True)] * 31
+    assert [call(clear) for _ in range(3)] == [(False, False)] * 3
+    assert [call(E) for _ in range(7)] == [(True, False)] * 7
+    plan.close()
