@@ -108,14 +108,16 @@ typedef struct kimad_config {
 #define KIMAD_CFG_FULL_DP 2ull          /* allocation: always run the recurrence over whole rows of cost cells */
 #define KIMAD_CFG_BAND_DP 4ull          /* allocation: always run it inside the band of cells that Lagrangian bounds
                                            leave.  Same results either way; by default plans of 60 to 1024 layers
-                                           (from 24 on with rows of 1537 cells or more) go by a tree of segments,
-                                           and by whole rows where rounding might decide between two allocations;
+                                           (from 24 on with rows of 1537 cells or more, from 64 with fewer than 576)
+                                           go by a tree of segments, and by whole rows where rounding might decide
+                                           between two allocations;
                                            fewer layers take the band with rows of 1537 cells or more (with up to 7
                                            ratios from 2049 on), others the whole rows, as grids of one ratio do.
                                            Rows that do not fit LDS (more than 4224 cells) and plans of more than
-                                           1024 layers take whole rows with either flag; by default 16 to 1024 layers
-                                           with rows of up to 131072 cells go by two halves, and by whole rows where
-                                           rounding might decide. */
+                                           1024 layers know no band: 16 to 1024 layers (from 24 on with up to 16
+                                           ratios and fewer than 16384 cells) with rows of 4225 to 131072 cells go
+                                           by two halves, and by whole rows where rounding might decide, the others
+                                           by whole rows, with this flag as without any. */
 
 #define KIMAD_CFG_DENSE_FALLBACK 8ull    /* allocation: a layer never costs more than its bare values (4 n bytes).  A grid
                                            point at or beyond the break-even K * pair_bytes >= 4 n stands for sending
@@ -194,7 +196,8 @@ int kimad_allocate(kimad_plan_t* plan, const double* err_table, uint64_t budget_
 
 /* kimad_allocate for callers that cannot allocate device memory or hand over a workspace at the point of
  * the call: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
- * arguments, same kernels, same results as kimad_allocate, but the dynamic programme's tables live in a
+ * arguments, same results as kimad_allocate, but it always goes by whole rows or the band (no tree of
+ * segments, see KIMAD_CFG_BAND_DP), and the dynamic programme's tables live in a
  * fixed array inside the library (4 MiB per device, held until the process ends) instead of the plan's
  * workspace; nothing is allocated or freed, by HIP or otherwise.  The plan supplies sizes, configuration and
  * the candidate sizes K_ij only.  Limits: at most KIMAD_STATIC_MAX_L layers and rows of at most

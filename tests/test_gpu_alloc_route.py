@@ -86,6 +86,14 @@ def test_the_lines_where_halves_and_the_tree_begin(cells, L, J, want):
     plan.close()
 
 
+@pytest.mark.parametrize("flags,want", [(0, "halves"), (2, "rows"), (4, "halves")])
+def test_rows_beyond_lds_know_no_band(flags, want):
+    ratios, sizes, Kt, E, budget, D = _case(9000, 40, 12, False)
+    plan = _plan(sizes, ratios, D, budget, flags)
+    assert _allocate(plan, E, Kt, budget, D)["route"] == want
+    plan.close()
+
+
 def test_members_of_a_run_apart_by_rounding_are_told_apart_from_the_left():
     """Small layers whose sizes all cost one unit, of errors a few units in the last place of the total apart."""
     rng = np.random.default_rng(3)
@@ -152,4 +160,46 @@ def test_ties_in_a_row_go_by_whole_rows_at_once(cells, L, J, recorded):
     assert [call(E) for _ in range(31)] == [(True, True)] * 31
     assert [call(clear) for _ in range(3)] == [(False, False)] * 3
     assert [call(E) for _ in range(7)] == [(True, False)] * 7
+    plan.close()
+
+
+@pytest.mark.parametrize("cells,L,J", [(900, 66, 12), (4100, 30, 40), (4225, 24, 5), (9000, 20, 20), (20011, 62, 33)])
+def test_replays_of_a_recorded_allocation(cells, L, J):
+    """Clear tables, ties and tables with a NaN one after another through one recorded graph, by the tree and by halves: what a replay
+    leaves (counters, rows that the chain has refilled, the word that says it decides) is cleared by the next, with the program's own
+    work and synchronizations in between."""
+    import torch
+    ratios, sizes, Kt, tied, budget, D = _case(cells, L, J, True)
+    tables = {"tied": tied}
+    for k in range(3):
+        tables["clear%d" % k] = np.ascontiguousarray(tied * (1.0 + 0.5 * np.random.default_rng(L + k).random((L, 1))))
+    tables["bad"] = tables["clear0"].copy()
+    tables["bad"][L // 2, J // 2] = np.nan
+    want = {k: ko.allocate(t, Kt, budget, 8, D) for k, t in tables.items()}
+    plan = _plan(sizes, ratios, D, budget)
+    table = torch.from_numpy(tied.reshape(-1).copy()).cuda()
+    plan.allocate(budget, table)                         # (an eager call that the chain has decided)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        j, K, off, st = plan.allocate(budget, table)
+    for k in ("tied", "clear0", "tied", "tied", "clear1", "bad", "clear2", "bad", "tied", "clear0"):
+        table.copy_(torch.from_numpy(tables[k].reshape(-1)))
+        for v in (j, K, off, st):
+            v.fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        st_ref, j_ref, K_ref, off_ref = want[k]
+        assert int(st.item()) == st_ref == (ko.ERR_NONFINITE if k == "bad" else ko.OK), k
+        if k == "bad":
+            assert not j.cpu().numpy().any() and not K.cpu().numpy().any() and not off.cpu().numpy().any()
+        else:
+            assert np.array_equal(j.cpu().numpy(), j_ref), k
+            assert np.array_equal(K.cpu().numpy().astype(np.uint64), K_ref) and np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref), k
+        route = plan.allocate_route()
+        assert route["route"] == ("halves" if cells > 4224 else "tree") and route["rows_decided"] == (k == "tied") and not route["at_once"], (k, route)
+        torch.full((1 << 20,), 2.0, device="cuda").sum().item()
+        if k == "clear1":                                # an eager call on the plan between two replays
+            j2, K2, off2, st2 = plan.allocate(budget, torch.from_numpy(tables["tied"].reshape(-1).copy()).cuda())
+            assert np.array_equal(j2.cpu().numpy(), want["tied"][1])
     plan.close()
