@@ -273,7 +273,7 @@ int kimad_allocate_diagnostics(kimad_plan_t* plan, uint32_t* out4, void* stream)
 #define KIMAD_ROUTE_HALVES 4u           /* two halves of the layers */
 #define KIMAD_HOW_ROWS 1u               /* tree or halves: rounding might have decided, and whole rows did */
 #define KIMAD_HOW_FROM_LEFT 2u          /* tree: sizes of equal cost were told apart by the totals summed up from the first layer */
-#define KIMAD_HOW_AT_ONCE 4u            /* tree, with KIMAD_HOW_ROWS: at once, behind several allocations in a row that they had to decide */
+#define KIMAD_HOW_AT_ONCE 4u            /* with KIMAD_HOW_ROWS: at once, behind several allocations in a row that they had to decide */
 int kimad_allocate_route(kimad_plan_t* plan, uint32_t* out2, void* stream);
 
 /* Per-layer state of the last profile / compression, for benchmarks and tests (synchronises the

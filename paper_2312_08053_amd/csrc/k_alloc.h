@@ -35,6 +35,8 @@ struct AllocBuffers {
 
 constexpr double DP_INF = __builtin_huge_val();
 constexpr uint32_t DP_FLAGS = 12;
+enum : uint32_t { FLAG_MET = 4u, FLAG_UNSURE = 5u, FLAG_COST = 6u, FLAG_CHAIN = 7u, FLAG_BACK = 8u, FLAG_AT_ONCE = 9u };      // (k_alloc_halves.h)
+constexpr uint32_t NO_TICKET = 1u << 30;       // (no launch has so many workgroups)
 
 // Words of AllocBuffers::info: the band's (k_alloc_band.h, 0 to 4; zero where none was run), the route taken (KIMAD_ROUTE_..) and how.
 // An allocation's first kernel writes them, and what is found out later adds how.
@@ -43,6 +45,20 @@ enum : uint32_t { ROUTE_ROWS = 1, ROUTE_BAND = 2, ROUTE_TREE = 3, ROUTE_HALVES =
 enum : uint32_t { HOW_ROWS = 1, HOW_FROM_LEFT = 2, HOW_AT_ONCE = 4 };     // whole rows decided; the path's totals from the left were formed; .. at once
 __device__ __forceinline__ void alloc_report(const AllocBuffers& ab, uint32_t route, uint32_t thread) {
     if (thread < INFO_REPORT) ab.info[thread] = thread == INFO_ROUTE ? route : 0u;
+}
+
+// A table in which rounding may decide is often followed by others: a layer whose errors vanish beside the total makes one in every
+// round.  Behind so many allocations in a row that whole rows had to decide, the plan's next ROWS_AHEAD go by whole rows at once, and then
+// the tree or the halves are tried again.  The sizes do not hang on it.
+constexpr uint32_t TIES_IN_A_ROW = 8, ROWS_AHEAD = 31;
+__device__ __forceinline__ void alloc_decided(const AllocBuffers& ab, bool by_rows) {      // (one thread, where the tree or the halves have been)
+    uint32_t streak = 0u;
+    if (by_rows) {
+        streak = min(ab.info[INFO_STREAK] + 1u, TIES_IN_A_ROW);
+        if (streak == TIES_IN_A_ROW) ab.info[INFO_AHEAD] = ROWS_AHEAD;
+        ab.info[INFO_HOW] = HOW_ROWS;
+    }
+    ab.info[INFO_STREAK] = streak;
 }
 
 // K / unit, rounded up.  (In 32 bits: a division in 64 is four times as long.)
@@ -210,12 +226,16 @@ __global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uin
                                                 uint32_t route) {
     __shared__ double se[KIMAD_MAX_J_CONST];
     __shared__ uint32_t sw[KIMAD_MAX_J_CONST];
-    const uint32_t i = blockIdx.x, j = threadIdx.x;
+    const uint32_t i = blockIdx.x, j = threadIdx.x, ahead = route == ROUTE_HALVES ? ab.info[INFO_AHEAD] : 0u;
     if (rows) {
         dp_fill_row(ab, rows, pitch, pad, i + 1ull, blockIdx.y * 64u + j, 64u * gridDim.y);
         if (i == 0u) dp_fill_row(ab, rows, pitch, pad, 0ull, blockIdx.y * 64u + j, 64u * gridDim.y);
-        if (i == 0u && blockIdx.y == 0u && j < DP_FLAGS) ab.flags[j] = j == 1u ? ab.first_ticket : 0u;
-        if (i == 0u && blockIdx.y == 0u) alloc_report(ab, route, j);
+        if (i == 0u && blockIdx.y == 0u) {
+            // (halves that are passed over: the chains find no number that is theirs, and leave)
+            if (j < DP_FLAGS) ab.flags[j] = j == 1u ? (ahead ? NO_TICKET : ab.first_ticket) : (j == FLAG_CHAIN || j == FLAG_AT_ONCE) && ahead ? 1u : 0u;
+            alloc_report(ab, route, j);
+            if (ahead && j == 0u) { ab.info[INFO_AHEAD] = ahead - 1u; ab.info[INFO_HOW] = HOW_ROWS | HOW_AT_ONCE; }
+        }
         if (blockIdx.y) return;
     }
     if (falling) {

@@ -25,8 +25,6 @@ namespace kimad {
 
 constexpr uint32_t HALVES_MAX_L = 1024, HALVES_MAX_CELLS = 131072;
 constexpr uint32_t MEET_THREADS = 1024, MEET_MAX = HALVES_MAX_CELLS / MEET_THREADS;
-// flags of AllocBuffers
-enum : uint32_t { FLAG_MET = 4u, FLAG_UNSURE = 5u, FLAG_COST = 6u, FLAG_CHAIN = 7u, FLAG_BACK = 8u };
 
 // The halves' last rows' least values by 64 cells, and behind the first half's what the workgroups of k_dp_meet have found:
 // least total, second least and where, [MEET_MAX + 1][3], and as the last the whole's with the margin.
@@ -67,13 +65,18 @@ __global__ __launch_bounds__(MEET_THREADS) void k_dp_meet(AllocBuffers ab, const
     __shared__ double upto[NT], sg[WAVES], sl[WAVES];
     __shared__ Two s_two[WAVES];
     __shared__ uint32_t s_last;
-    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, cap = ab.cap;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, cap = ab.cap, at_once = ab.flags[FLAG_AT_ONCE];
     const uint32_t x0 = blockIdx.x * NT, a_top = cap - x0;                    // (the grid ends with the capacity)
     const bool has_a = a_top + tid >= NT - 1u;
     const uint32_t a = has_a ? a_top + tid - (NT - 1u) : 0u;
     const double f = has_a ? F[a] : DP_INF, g = x0 + tid <= cap ? G[x0 + tid] : DP_INF;
     double lg = DP_INF;                                    // least of G below
     for (uint32_t w = tid; w < x0 / 64u; w += NT) lg = min_f64(lg, gmin[w]);
+    if (at_once) {
+        // (nothing is known of a least total, and the numbers that nobody drew are no waits given up)
+        if (blockIdx.x == 0u && tid == 0u) { results[3u * MEET_MAX] = DP_INF; results[3u * MEET_MAX + 1u] = DP_INF; ab.flags[2] = 0u; }
+        return;
+    }
     lg = wave_min_f64(lg);
     const double in = wave_scan_min_f64(g);
     if (lane == 63u) { sg[wave] = in; sl[wave] = lg; }
@@ -113,10 +116,15 @@ __global__ __launch_bounds__(MEET_THREADS) void k_dp_meet(AllocBuffers ab, const
     }
 }
 
-// The rows as k_dp_prep leaves them, for the layers in their own order.
+// The rows as k_dp_prep leaves them, for the layers in their own order.  Behind ties in a row (alloc_decided) the halves are passed over:
+// k_dp_chain_long's workgroups draw no number of theirs, k_dp_meet leaves without a least total, and the rows are as k_dp_prep has left them.
+// (us of all launches of the allocation, whole rows alone, behind the halves, and at once: 24 layers of 32 ratios and 4300 cells
+// 56, 100, 66, 62 of 32 and 20 thousand 140, 233, 156, 161 of 5 and 58 thousand 295, 484, 326.  A word of its own for
+// k_dp_chain_long to look at cost every clear allocation 1 to 13 us.)
 __global__ __launch_bounds__(64) void k_dp_refill(AllocBuffers ab, double* rows, uint64_t pitch, uint32_t pad) {
     if (ab.flags[FLAG_CHAIN] == 0u) return;
-    for (uint32_t r = 1u + blockIdx.x; r <= ab.L; r += gridDim.x)
+    const bool as_left = ab.flags[FLAG_AT_ONCE] != 0u;
+    for (uint32_t r = 1u + blockIdx.x; r <= ab.L && !as_left; r += gridDim.x)
         dp_fill_row(ab, rows, pitch, pad, r, blockIdx.y * 64u + threadIdx.x, 64u * gridDim.y);
     if (blockIdx.x == 0u && blockIdx.y == 0u && threadIdx.x == 0u) ab.flags[1] = 0u;
 }
@@ -221,7 +229,7 @@ __global__ __launch_bounds__(BACK_THREADS) void k_dp_back(AllocBuffers ab, const
     const bool chain = st == 0 && unsure;
     if (tid == 0u) {
         ab.flags[FLAG_CHAIN] = chain ? 1u : 0u;
-        if (chain) ab.info[INFO_HOW] = HOW_ROWS;
+        if (!(chain && ab.flags[FLAG_AT_ONCE])) alloc_decided(ab, chain);
         if (!chain) *ab.status = st;
     }
     if (chain) return;

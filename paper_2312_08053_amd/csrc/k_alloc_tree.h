@@ -407,14 +407,10 @@ constexpr uint32_t PATH_THREADS = 512;
 constexpr uint32_t PATH_STAGE = 12288;             // cells of rows in LDS (a row of the longest kind fits)
 constexpr uint32_t PATH_LEVELS = 6;
 static_assert(1u << PATH_LEVELS == TREE_MAX_SEGMENTS && PATH_STAGE >= 2u * PATH_LEVELS * 1024u && PATH_STAGE >= DP_ROW_MAX, "the nodes' totals fit");
-// A table in which rounding may decide is often followed by others: a layer whose errors vanish beside the total makes one in every
-// round.  Behind so many allocations in a row that the chain had to decide, the plan's next ROWS_AHEAD go by the chain at once, the tree's
-// kernels leave, and then it is tried again.  The sizes do not hang on it.
+// Behind ties in a row (alloc_decided) the chain comes at once, and the tree's kernels leave.
 // (us of all launches of the allocation, the chain or the band alone, tree and chain, and the chain at once, of 16 and of 64 ratios: 148 layers,
 // 1000 cells 72, 118, 84 and 107, 154, 119; 1537 cells 144 in place of 177 by the band, 102, and 183 in place of 170, 139; 4097 cells 183, 302, 230
-// and 223, 352, 284; 62 layers, 1000 cells 48, 82, 58.  The halves' kernels are too finely balanced for it: the word looked at by
-// k_dp_chain_long cost every clear allocation 1 to 13 us.)
-constexpr uint32_t TIES_IN_A_ROW = 8, ROWS_AHEAD = 31;
+// and 223, 352, 284; 62 layers, 1000 cells 48, 82, 58.)
 
 // What a segment has found for a layer goes beyond the caches: the segment that is through last reads it.
 __device__ __forceinline__ void tree_store(const AllocBuffers& ab, const TreeBuffers& tb, uint32_t i, uint32_t place, uint32_t K) {
@@ -664,15 +660,8 @@ __global__ __launch_bounds__(PATH_THREADS) void k_dp_path(AllocBuffers ab, DpLis
     const bool chain = st == 0 && (state & TREE_UNSURE);
     if (tid == 0u) {
         tb.head[3] = chain ? 1u : 0u;
-        uint32_t streak = 0u;
-        if (chain) {
-            streak = min(ab.info[INFO_STREAK] + 1u, TIES_IN_A_ROW);
-            if (streak == TIES_IN_A_ROW) ab.info[INFO_AHEAD] = ROWS_AHEAD;
-            ab.info[INFO_HOW] = HOW_ROWS;
-        } else if (st == 0 && (state & TREE_NEAR)) {
-            ab.info[INFO_HOW] = HOW_FROM_LEFT;
-        }
-        ab.info[INFO_STREAK] = streak;
+        alloc_decided(ab, chain);
+        if (!chain && st == 0 && (state & TREE_NEAR)) ab.info[INFO_HOW] = HOW_FROM_LEFT;
         if (!chain) *ab.status = st;
     }
     if (chain) {

@@ -105,8 +105,8 @@ inline bool chain_long_fits(uint64_t L, uint64_t cells) {
 // and from BAND_AUTO_CELLS on the better of chain and band, layers of 2, 16 and 64 ratios:
 //   1537       24 36 and 31, 37 and 37, 40 and 48 (band 58); 40 44 and 34, 45 and 38, 50 and 49; 161 91 and 45, 92 and 47, 98 and 54
 //   4097       24 56 and 38, 56 and 46, 61 and 73 (band 69); 40 78 and 45, 75 and 51, 78 and 68; 161 216 and 66, 170 and 69, 193 and 84
-// Where rounding may decide, the chain comes behind it: what both take together, against the better of chain and band alone, 148 layers of 16
-// and of 64 ratios: 1000 cells 118 and 72, 154 and 107; 1537 cells 144 and 92, 183 and 98; 4097 cells 302 and 183, 352 and 223.
+// Where rounding may decide, the chain comes behind it, and behind ties in a row at once: chain or band alone, both, and the chain at once,
+// 148 layers of 16 and of 64 ratios: 1000 cells 72, 118, 84 and 107, 154, 119; 4097 cells 183, 302, 230 and 223, 352, 284.
 constexpr uint32_t TREE_MIN_L = 24, TREE_MIN_L_SHORT = 60;       // (rows of fewer than BAND_AUTO_CELLS cells: the latter;
 constexpr uint32_t TREE_MIN_L_SHORTEST = 64, TREE_SHORTEST = 576;          //  of fewer than TREE_SHORTEST cells: this)
 // Segments of at most this many layers: a segment's layers are one after another, a level of the tree is a launch.  (us with 3, 6 and
@@ -130,7 +130,8 @@ inline uint32_t tree_segments(uint64_t layers, uint32_t few) {
 // allocation, one chain and halves: 62 layers of 32 candidates and 58 thousand cells 174 and 122, of 131 thousand 262 and 167, 161 of 64 and
 // 13 thousand 404 and 260; 16 layers of 17 candidates and 4300 cells 42 and 42, of 64 52 and 49; 16 of 16 and 4300 35 and 39, 13 thousand
 // 38 and 40, 20 thousand 45 and 43, 42 thousand 59 and 50; 20 of 16 and 4300 39 and 42, 13 thousand 44 and 44; 24 45 and 45, 49 and 46, 30 52 and
-// 50, 57 and 53; 8 of 5 and 9 thousand 26 and 33.  Where rounding may decide, one chain comes behind them: 16 layers of 85 thousand cells 111 and 170.
+// 50, 57 and 53; 8 of 5 and 9 thousand 26 and 33.  Where rounding may decide, one chain comes
+// behind them (k_dp_refill).
 constexpr uint32_t HALVES_MIN_L = CHAIN_FEW_L, HALVES_MIN_L_SHORT = 24;          // (the latter: up to HALVES_FEW_J ratios, fewer than HALVES_LONG cells)
 constexpr uint32_t HALVES_FEW_J = 16, HALVES_LONG = 16384;
 

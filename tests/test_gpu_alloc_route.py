@@ -115,10 +115,11 @@ def test_members_of_a_run_apart_by_rounding_are_told_apart_from_the_left():
         plan.close()
 
 
-@pytest.mark.parametrize("cells,L,J", [(600, 64, 16), (1200, 70, 33), (4097, 40, 16)])
+@pytest.mark.parametrize("cells,L,J", [(600, 64, 16), (1200, 70, 33), (4097, 40, 16), (4225, 24, 5), (9000, 20, 20)])
 @pytest.mark.parametrize("recorded", [False, True])
 def test_ties_in_a_row_go_by_whole_rows_at_once(cells, L, J, recorded):
-    """Behind eight allocations that whole rows had to decide, the next 31 do not ask the tree first, whatever their tables; then it is tried again.  Called one by one, and as replays of a recorded graph."""
+    """Behind eight allocations that whole rows had to decide, the next 31 do not ask the tree or the halves first, whatever
+    their tables; then it is tried again.  Called one by one, and as replays of a recorded graph."""
     import torch
     ratios, sizes, Kt, E, budget, D = _case(cells, L, J, True)
     clear = np.ascontiguousarray(E * (1.0 + 0.5 * np.random.default_rng(L).random((L, 1))))
@@ -149,7 +150,7 @@ def test_ties_in_a_row_go_by_whole_rows_at_once(cells, L, J, recorded):
         assert np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
         torch.full((1 << 18,), 1.0, device="cuda").sum().item()
         r = plan.allocate_route()
-        assert r["route"] == "tree" and not r["from_left"]
+        assert r["route"] == ("halves" if cells > 4224 else "tree") and not r["from_left"]
         return r["rows_decided"], r["at_once"]
 
     assert [call(E) for _ in range(7)] == [(True, False)] * 7
