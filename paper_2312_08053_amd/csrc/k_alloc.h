@@ -233,8 +233,8 @@ __global__ __launch_bounds__(64) void k_dp_prep(AllocBuffers ab, DpLists dl, uin
         if (i == 0u && blockIdx.y == 0u) {
             // (halves that are passed over: the chains find no number that is theirs, and leave)
             if (j < DP_FLAGS) ab.flags[j] = j == 1u ? (ahead ? NO_TICKET : ab.first_ticket) : (j == FLAG_CHAIN || j == FLAG_AT_ONCE) && ahead ? 1u : 0u;
-            alloc_report(ab, route, j);
-            if (ahead && j == 0u) { ab.info[INFO_AHEAD] = ahead - 1u; ab.info[INFO_HOW] = HOW_ROWS | HOW_AT_ONCE; }
+            if (j < INFO_REPORT) ab.info[j] = j == INFO_ROUTE ? route : j == INFO_HOW && ahead ? HOW_ROWS | HOW_AT_ONCE : 0u;
+            if (ahead && j == 0u) ab.info[INFO_AHEAD] = ahead - 1u;
         }
         if (blockIdx.y) return;
     }

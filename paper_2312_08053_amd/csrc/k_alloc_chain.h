@@ -479,17 +479,21 @@ __global__ __launch_bounds__(chain_threads(W, GW)) void k_dp_chain(AllocBuffers 
 // layer, 2.3 us).  With more than sixteen candidates the cheapest four's cells are waited for before all are asked for
 // through the caches (149 against 160 us with device-scope loads for all; with sixteen or fewer the wait costs more than it
 // saves, 83 against 72).  Sixteen cells a wave, the candidates shared by its four rows, read twice the lines: 190.
-// Two waves a workgroup, whose source cells lie close together, share what its compute unit's cache holds, and wait for each other's
-// start: worth it for few layers from 16384 cells on, for any number from 65536 on, and for halves.  (us of all launches of the
-// allocation, workgroups of one wave and of two.  8 layers of 64 candidates and 9 thousand cells 36 and 38, 13 37 and 39, 20 42 and 41,
-// 58 64 and 60, of 5 candidates 27 and 27 at 13, 31 and 30 at 20, 47 and 42 at 58; 16 of 131 thousand and 32 114 and 105; 62 of 32 and 4300
-// cells 122 and 127, 42 thousand 161 and 177, 58 174 and 182, 90 218 and 215, 131 262 and 256; 161 of 64 and 4300 388 and 439, 58 thousand 606
-// and 620, 131 1000 and 914.  By halves 62 layers of 32 and 4300 cells 85 and 90, 13 thousand 96 and 93, 58 125 and 122, 131 177 and 168;
-// 161 of 64 236 and 247, 259 and 260, 326 and 354, 432 and 461; 30 of 5 and 58 thousand 76 and 67.)
+// Two waves a workgroup, whose source cells lie close together, share what its compute unit's cache holds, and are half as many workgroups
+// to start one behind the other; but they share its paths, so that a layer takes longer, the more the more candidates it has: worth it
+// where the row is long for the layers, on any row from 90112 cells on, and for halves.  (us of all launches of the allocation, workgroups of one
+// wave and of two, layers of 16 candidates: 2 layers 8 thousand cells 19 and 18, 58 thousand 36 and 31; 6 layers 8 thousand 24 and 24, 10.5
+// 25 and 25, 13.5 26 and 25, 58 45 and 40; 20 layers 13.5 44 and 46, 17 47 and 47, 22 51 and 51, 58 76 and 73; 62 layers 13.5
+// 99 and 107, 28 120 and 118, 58 146 and 151, 95 182 and 180.  Of 64: 2 layers 8 thousand cells 22 and 22, 13.5 23 and 23; 8 layers 13.5 38 and 40, 17
+// 40 and 41, 22 43 and 42, 58 64 and 60; 15 layers 22 64 and 64, 46 81 and 86, 74 105 and 102; 161 layers 4300 cells 385 and 448, 58 thousand
+// 608 and 615, 74 678 and 719, 95 747 and 736, 120 994 and 882.  By halves 62 layers of 32 and 4300 cells 85 and 90, 13 thousand 96 and 93, 58 125
+// and 122, 131 177 and 168; 161 of 64 236 and 247, 259 and 260, 326 and 354, 432 and 461; 30 of 5 and 58 thousand 76 and 67.)
 constexpr uint32_t CHAIN_PAD = 64;
 constexpr uint32_t CHAIN_LONG_WAVES = 2;             // of a workgroup, at most
-constexpr uint32_t CHAIN_FEW_L = 16;                 // (the halves' fewest)
-inline uint32_t chain_long_waves(uint64_t L, uint64_t cells) { return cells >= 65536u || (L < CHAIN_FEW_L && cells >= 16384u) ? CHAIN_LONG_WAVES : 1u; }
+inline uint32_t chain_long_waves(uint64_t L, uint64_t J, uint64_t cells) {
+    const bool short_lists = J <= 16;
+    return cells >= 90112u || (L <= (short_lists ? 30u : 15u) && cells >= 8192u + (short_lists ? 512u : 1024u) * L) ? CHAIN_LONG_WAVES : 1u;
+}
 
 // Two halves of the layers side by side (k_alloc_halves.h), each from cost 0, every range of cells by two workgroups of neighbouring
 // numbers; or, where order is null, all layers one after another, if `gate` (optional) says so.

@@ -132,7 +132,7 @@ inline uint32_t tree_segments(uint64_t layers, uint32_t few) {
 // 38 and 40, 20 thousand 45 and 43, 42 thousand 59 and 50; 20 of 16 and 4300 39 and 42, 13 thousand 44 and 44; 24 45 and 45, 49 and 46, 30 52 and
 // 50, 57 and 53; 8 of 5 and 9 thousand 26 and 33.  Where rounding may decide, one chain comes
 // behind them (k_dp_refill).
-constexpr uint32_t HALVES_MIN_L = CHAIN_FEW_L, HALVES_MIN_L_SHORT = 24;          // (the latter: up to HALVES_FEW_J ratios, fewer than HALVES_LONG cells)
+constexpr uint32_t HALVES_MIN_L = 16, HALVES_MIN_L_SHORT = 24;          // (the latter: up to HALVES_FEW_J ratios, fewer than HALVES_LONG cells)
 constexpr uint32_t HALVES_FEW_J = 16, HALVES_LONG = 16384;
 
 uint32_t pick_tile_elems(uint64_t d_big) {
@@ -812,7 +812,7 @@ int enqueue_allocate(kimad_plan* p, const AllocScratch& ws, const double* err_ta
             return KIMAD_OK;
         };
         auto chain = [&](const ChainHalves& ch) -> int {
-            return ch.order || chain_long_waves(lo.L, cap + 1) == CHAIN_LONG_WAVES ? chain_of(std::true_type{}, ch) : chain_of(std::false_type{}, ch);
+            return ch.order || chain_long_waves(lo.L, lo.J, cap + 1) == CHAIN_LONG_WAVES ? chain_of(std::true_type{}, ch) : chain_of(std::false_type{}, ch);
         };
         const double* last = ws.rows_g + (uint64_t)lo.L * pitch + CHAIN_PAD;
         ChainHalves ch{};

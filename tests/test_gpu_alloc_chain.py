@@ -52,8 +52,8 @@ def test_edges_of_the_rows(cells, J):
         plan.close()
 
 
-@pytest.mark.parametrize("cells,L", [(16383, 15), (16384, 15), (16385, 15), (16448, 16), (65535, 16), (65536, 16), (65601, 16), (65664, 3)])
-@pytest.mark.parametrize("J", [6, 40])
+@pytest.mark.parametrize("cells,L,J", [(11263, 6, 16), (11264, 6, 16), (11329, 6, 5), (14335, 6, 17), (14336, 6, 17), (23551, 30, 6), (23552, 30, 6), (24064, 31, 6),
+                                         (23551, 15, 40), (23552, 15, 40), (24577, 16, 40), (90111, 17, 20), (90112, 17, 20), (90177, 17, 6)])
 def test_one_wave_a_workgroup_and_two(cells, L, J):
     """Around the lines from which a workgroup of rows beyond LDS has two waves, the last workgroup full, of one wave and nearly empty."""
     import torch
