@@ -47,9 +47,10 @@ __device__ __forceinline__ void alloc_report(const AllocBuffers& ab, uint32_t ro
     if (thread < INFO_REPORT) ab.info[thread] = thread == INFO_ROUTE ? route : 0u;
 }
 
-// A table in which rounding may decide is often followed by others: a layer whose errors vanish beside the total makes one in every
-// round.  Behind so many allocations in a row that whole rows had to decide, the plan's next ROWS_AHEAD go by whole rows at once, and then
-// the tree or the halves are tried again.  The sizes do not hang on it.
+// A table in which rounding may decide is often followed by others: two tensors alike make one whenever their sizes differ, and, where the
+// budget covers all the others, a layer whose errors are less than some 1e-12 of the total makes one in every round.  Behind so many
+// allocations in a row that whole rows had to decide, the plan's next ROWS_AHEAD go by whole rows at once, and then the tree or the halves
+// are tried again.  The sizes do not hang on it.
 constexpr uint32_t TIES_IN_A_ROW = 8, ROWS_AHEAD = 31;
 __device__ __forceinline__ void alloc_decided(const AllocBuffers& ab, bool by_rows) {      // (one thread, where the tree or the halves have been)
     uint32_t streak = 0u;
