@@ -31,6 +31,8 @@ def test_sizes_are_the_oracles(cells, L, J):
             st_ref, j_ref, K_ref, off_ref = ko.allocate(E, Kt, budget, 8, 0)
             j, K, off, st = plan.allocate(budget, table)
             assert int(st.item()) == st_ref == ko.OK, (kind, budget)
+            if budget == 8 * (cells - 1):
+                assert plan.allocate_route()["route"] == ("halves" if L >= (24 if J <= 16 and cells < 16384 else 16) else "rows")
             assert np.array_equal(j.cpu().numpy(), j_ref), (kind, budget)
             assert np.array_equal(K.cpu().numpy().astype(np.uint64), K_ref), (kind, budget)
             assert np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref), (kind, budget)

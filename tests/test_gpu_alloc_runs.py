@@ -22,6 +22,7 @@ def test_members_of_a_run(J, big):
     n = int(sum(sizes))
     z = [torch.zeros(n, dtype=torch.float32, device="cuda") for _ in range(2)]
     plan = kimad.Plan(z[0], z[1], sizes, ratios.tolist(), D=cells, max_budget_bytes=8 * n, capacity_pairs=1)
+    ways = []
     budget = 8 * (int(Kt[:, 0].sum()) + (n - int(Kt[:, 0].sum())) // 3)
     for turn in range(6):
         E = np.empty((L, J))
@@ -36,6 +37,10 @@ def test_members_of_a_run(J, big):
         j, K, off, st = plan.allocate(budget, torch.from_numpy(E.reshape(-1)).cuda())
         assert int(st.item()) == st_ref == ko.OK
         assert np.array_equal(j.cpu().numpy(), j_ref), turn
+        ways.append(plan.allocate_route())
         assert np.array_equal(K.cpu().numpy().astype(np.uint64), K_ref)
         assert np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
+    assert all(w["route"] == "tree" for w in ways)
+    if J >= 16:                                          # (of two or three sizes, whole rows decide)
+        assert any(w["from_left"] for w in ways)
     plan.close()

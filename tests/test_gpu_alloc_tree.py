@@ -15,7 +15,7 @@ def _table(rng, sizes, Kt, kind):
     if kind == "noise":
         E = rng.random(E.shape) - 0.3                    # neither falling nor convex, negative entries
     elif kind == "ties":
-        E = np.round(4.0 * E / E.max())
+        E = np.round(4.0 * E / np.maximum(E.max(axis=1, keepdims=True), 1e-300))           # small whole numbers in every layer
     elif kind == "tiny":
         E *= 10.0 ** -rng.integers(0, 20, size=(len(sizes), 1)).astype(np.float64)       # errors below a unit in the total's last place
     elif kind == "zeros":
@@ -25,13 +25,14 @@ def _table(rng, sizes, Kt, kind):
 
 
 @pytest.mark.parametrize("cells,L", [(90, 60), (64, 61), (90, 64), (66, 65), (575, 64), (576, 60), (1000, 60), (1023, 97), (1024, 192), (1025, 193), (1024, 1024), (1537, 24), (2049, 25),
-                                     (4223, 64), (4224, 48), (4224, 300)])
+                                     (4223, 64), (4224, 48), (4224, 300), (1536, 1024)])
 @pytest.mark.parametrize("J", [2, 17, 64])
 def test_sizes_are_the_oracles(cells, L, J):
     import torch
     import paper_2312_08053_amd as kimad
     rng = np.random.default_rng(1000 * cells + 10 * L + J)
-    ratios = np.append(np.sort(rng.uniform(0.001, 0.99, size=J - 1)), 1.0)
+    # (the cheapest sizes are few, so that most budgets have room for them)
+    ratios = np.concatenate([rng.uniform(0.001, 0.02, size=1), np.sort(rng.uniform(0.02, 0.99, size=J - 2)), [1.0]])
     # sizes from a fraction of a cost unit (no choice) to much of the row
     sizes = [max(1, int(x)) for x in 3000.0 * 10.0 ** rng.uniform(-3, 1.5, size=L)]
     Kt = np.array([ko.grid_sizes(ratios, n) for n in sizes])
@@ -40,7 +41,9 @@ def test_sizes_are_the_oracles(cells, L, J):
     least = int(Kt[:, 0].sum())
     most = max(8 * n, 8 * (cells - 1))
     plan = kimad.Plan(z[0], z[1], sizes, ratios.tolist(), D=cells - 1, max_budget_bytes=most, capacity_pairs=1)
-    budgets = [8 * (least + int(f * (n - least))) for f in (0.02, 0.3)] + [8 * max(1, least // 3)]
+    # whole cost units, so that the rows have exactly this many cells; and too little for the cheapest
+    budgets = [8 * (cells - 1) * max(1, (least + int(f * (n - least))) // (cells - 1)) for f in (0.02, 0.3)] + [8 * max(1, least // 3)]
+    way = "tree" if L >= (24 if cells >= 1537 else 60 if cells >= 576 else 64) else "rows"
     for kind in ("falling", "ties", "noise", "tiny", "zeros", "falling"):
         E = np.ascontiguousarray(_table(rng, sizes, Kt, kind))
         table = torch.from_numpy(E.reshape(-1)).cuda()
@@ -48,6 +51,7 @@ def test_sizes_are_the_oracles(cells, L, J):
             st_ref, j_ref, K_ref, off_ref = ko.allocate(E, Kt, budget, 8, cells - 1)
             j, K, off, st = plan.allocate(budget, table)
             assert int(st.item()) == st_ref, (kind, budget)
+            assert budget == budgets[2] or plan.allocate_route()["route"] == way
             if st_ref != ko.OK:
                 assert not K.cpu().numpy().any() and not off.cpu().numpy().any()
                 continue
